@@ -26,8 +26,8 @@
  * Order: descending logit; equal logits: smaller id first.  Logits are accumulated in
  * fp32 from exact bf16 products, and the log-probabilities are fp32 values: their
  * absolute accuracy is that of fp32 at the magnitude of the logits (about 1e-3 at logits
- * of a few thousand, 1e-1 at 1e5), whatever the path.  With few rows t = h A stays in fp32 throughout.  With
- * many rows the matrix cores take a 16-bit t (bf16, or f16 for k > 12) for the sum of
+ * of a few thousand, 1e-1 at 1e5), whatever the path.  With up to 48 rows, and for k > 16, t = h A stays in fp32
+ * throughout (r <= 2048; beyond, up to four rows).  With more rows the matrix cores take a 16-bit t (bf16, or f16 for k > 12) for the sum of
  * exponentials and for finding the candidates; every candidate whose rank or reported
  * value could depend on that rounding is then evaluated again from the fp32 t.
  *
@@ -107,8 +107,8 @@ int slimspec_transpose_weights(const void *M, int32_t K, int32_t V, void *Mt, vo
 
 /* slimspec_head_topk (second display of section 4.1) for weights that do not change
  * between calls, as in serving: the caller also passes Bt[V, r], the column-major copy of B
- * made by slimspec_transpose_weights(B, r, V, Bt).  Same operation and outputs.  With five rows
- * or more and k <= 16 the projection runs on 16-bit operands and uncertain ranks are settled
+ * made by slimspec_transpose_weights(B, r, V, Bt).  Same operation and outputs.  With more than 48
+ * rows (five, for r > 2048) and k <= 16 the projection runs on 16-bit operands and uncertain ranks are settled
  * by exact fp32 logits of single columns: a column is r adjacent elements of Bt but one
  * element per 128-byte line of B, so these reads shrink by the line length.  Log-probabilities
  * may differ from slimspec_head_topk's in the last bits (another summation order of the exact
@@ -207,7 +207,7 @@ int truncated_head_topk(const void *h, const void *W_tr, slimspec_dtype w_dtype,
  *     y_v = h W[:, v] for v in S       (exact full-head logits, fp32 accumulation)
  *     outputs: the k best of S by y (equal y: smaller id) with y_v - log sum_{u in S} exp(y_u)
  * W [d, V] bf16 or fp32; 1 <= k <= k_route <= SLIMSPEC_KMAX.  Workspace: routed_workspace_bytes.
- * (A router k above 16 takes the streaming kernels in groups of 8 rows: meant for few rows.) */
+ * (A router k above 16 reads B once per 48 rows, for r > 2048 once per 8: meant for few rows.) */
 size_t routed_workspace_bytes(const slimspec_shape *shape, int32_t k_route);
 int routed_head_topk(const void *h, const void *A, const void *B, const void *W, slimspec_dtype w_dtype,
                      const slimspec_shape *shape, int32_t k_route, int32_t k,

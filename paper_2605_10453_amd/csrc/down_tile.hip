@@ -136,6 +136,9 @@ __device__ __forceinline__ void column_scale_block(const uint16_t *__restrict__ 
 // 64 ct + 32 wc + 8 (i / 4) + 4 (lane / 32) + i % 4.
 // Block g works on XCD g % 8 (each XCD has its own L2): slices are dealt to the XCDs first, so that an XCD reads
 // only its slices' rows of A and columns of h.
+// STEPWISE: every 16-element step is summed on its own and then added (for the callers that report fp32-exact logits):
+// the matrix unit's internal roundings then happen at the size of one step's sum.
+template <bool STEPWISE>
 __global__ __launch_bounds__(256) void down_tile_kernel(
     const uint16_t *__restrict__ h, const uint16_t *__restrict__ A, float *__restrict__ part,
     int d, int r, DownGrid g)
@@ -216,8 +219,15 @@ __global__ __launch_bounds__(256) void down_tile_kernel(
                 const v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_PTR(v4i16, buf + ma + ks * 2048 + 512));
                 mf[ks] = __builtin_bit_cast(u32x4, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
             }
-            acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, mf[0]), __builtin_bit_cast(bf16x8, xf[0]), acc0, 0, 0, 0);
-            acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, mf[1]), __builtin_bit_cast(bf16x8, xf[1]), acc1, 0, 0, 0);
+            f32x16 c0 = acc0, c1 = acc1;
+            if constexpr (STEPWISE) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) { c0[i] = 0.f; c1[i] = 0.f; }
+            }
+            c0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, mf[0]), __builtin_bit_cast(bf16x8, xf[0]), c0, 0, 0, 0);
+            c1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, mf[1]), __builtin_bit_cast(bf16x8, xf[1]), c1, 0, 0, 0);
+            if constexpr (STEPWISE) { acc0 += c0; acc1 += c1; }
+            else { acc0 = c0; acc1 = c1; }
             // the next loads go to the buffer of stage q - 1, which every wavefront finished reading before the barrier above
             issue_stage();
             buf = (buf + kDStageBytes == lds0 + kDLds) ? lds0 : buf + kDStageBytes;
@@ -235,6 +245,9 @@ __global__ __launch_bounds__(256) void down_tile_kernel(
 //   t16   [8 ceil(r / 64), rows_pad]   16-byte vectors of 8 values t log2(e) in bf16 or f16 (round to nearest even),
 //                                      zero for k >= r and for padding rows
 //   stat  [2 ceil(r / 64), rows_pad]   per 32-column piece: (sum of (t - its 16-bit value)^2, sum of t^2) of its entries
+// PIECES: t leaves as three bf16 pieces instead, t16 [3][8 ceil(r / 64)][rows_pad] (no t32, stat or column scales).
+// The pieces are cut off the top of t's significand, 8 bits each: their sum is t exactly.
+template <bool PIECES>
 __global__ __launch_bounds__(256) void down_finish_kernel(
     const float *__restrict__ part, const uint16_t *__restrict__ h, const uint16_t *__restrict__ A,
     int rows_pad, int d, int r,
@@ -245,7 +258,7 @@ __global__ __launch_bounds__(256) void down_finish_kernel(
     __shared__ float red_a[4 * 32], red_b[4 * 32];
     __shared__ float colsh[3 * 64 * 8];
     const int tid = threadIdx.x;
-    if ((int)blockIdx.x >= 4 * g.n_rt_all * g.n_ct) {
+    if (!PIECES && (int)blockIdx.x >= 4 * g.n_rt_all * g.n_ct) {
         // (next to the tile kernel's blocks instead, these blocks cost 6.7 us at 512 rows; here 2-3)
         column_scale_block(B, r, V, tilescale, (int)blockIdx.x - 4 * g.n_rt_all * g.n_ct, colsh, tid);
         return;
@@ -307,6 +320,31 @@ __global__ __launch_bounds__(256) void down_finish_kernel(
 #pragma unroll
         for (int e = 0; e < 8; ++e) v[e] = valid ? tile[row * 33 + cg * 8 + e] : 0.f;
         float a = 0.f, b = 0.f;
+        if constexpr (PIECES) {
+            uint32_t b[3][8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const uint32_t u = __float_as_uint(v[e]);
+                const bool number = (u & 0x7f800000u) != 0x7f800000u;
+                const uint32_t hi = u & 0xffff0000u;
+                const float rest = v[e] - __uint_as_float(hi);
+                const uint32_t mid = __float_as_uint(rest) & 0xffff0000u;
+                const uint32_t lo = __float_as_uint(rest - __uint_as_float(mid));
+                // infinity and not-a-number stay whole in the first piece (the low bits of a not-a-number may be all it has)
+                b[0][e] = number ? hi : hi | ((u & 0x007fffffu) ? 0x00400000u : 0u);
+                b[1][e] = number ? mid : 0u;
+                b[2][e] = number ? lo : 0u;
+            }
+            if (mine) {
+                const size_t piece_stride = (size_t)((r + 63) / 64 * 8) * rows_pad;
+#pragma unroll
+                for (int p = 0; p < 3; ++p)
+                    t16[p * piece_stride + (size_t)kg * rows_pad + row0 + row] =
+                        make_uint4((b[p][0] >> 16) | (b[p][1] & 0xffff0000u), (b[p][2] >> 16) | (b[p][3] & 0xffff0000u),
+                                   (b[p][4] >> 16) | (b[p][5] & 0xffff0000u), (b[p][6] >> 16) | (b[p][7] & 0xffff0000u));
+            }
+            return;
+        }
         if (mine && kg < (r >> 3)) {
             float4 *o = reinterpret_cast<float4 *>(t32 + (size_t)(row0 + row) * r + kg * 8);
             o[0] = make_float4(v[0], v[1], v[2], v[3]);
@@ -339,6 +377,7 @@ __global__ __launch_bounds__(256) void down_finish_kernel(
         red_a[cg * 32 + row] = a;
         red_b[cg * 32 + row] = b;
     }
+    if constexpr (PIECES) return;
     __syncthreads();
     if (tid < 32 && row0 + tid < row_end)
         stat[(size_t)(n0 >> 5) * rows_pad + row0 + tid] =
@@ -346,21 +385,38 @@ __global__ __launch_bounds__(256) void down_finish_kernel(
                         ((red_b[tid] + red_b[32 + tid]) + red_b[64 + tid]) + red_b[96 + tid]);
 }
 
+template <bool STEPWISE>
+static hipError_t launch_down_tiles(const uint16_t *h, const uint16_t *A, float *part, const DownGrid &g, int d, int r, hipStream_t st)
+{
+    static LdsLimit lds_limit;
+    hipError_t e = lds_limit.raise(reinterpret_cast<const void *>(down_tile_kernel<STEPWISE>), kDLds);
+    if (e != hipSuccess) return e;
+    const int tiles = g.n_rt * g.n_ct;
+    // slices >= 8: every XCD has slices / 8 slices of every tile; fewer: 8 / slices XCDs share a slice and split the tiles
+    const int blocks = g.slices >= 8 ? tiles * g.slices : 8 * ((tiles + 8 / g.slices - 1) / (8 / g.slices));
+    down_tile_kernel<STEPWISE><<<blocks, 256, kDLds, st>>>(h, A, part, d, r, g);
+    return hipGetLastError();
+}
+
 hipError_t launch_down_projection_tiles(const uint16_t *h, const uint16_t *A, float *part, const DownGrid &g,
                                         int rows_pad, int d, int r,
                                         float *t32, void *t16, float2 *stat, const uint16_t *B, int V, float2 *tilescale,
                                         bool as_f16, hipStream_t st)
 {
-    static LdsLimit lds_limit;
-    hipError_t e = lds_limit.raise(reinterpret_cast<const void *>(down_tile_kernel), kDLds);
+    const hipError_t e = launch_down_tiles<false>(h, A, part, g, d, r, st);
     if (e != hipSuccess) return e;
-    const int tiles = g.n_rt * g.n_ct;
-    // slices >= 8: every XCD has slices / 8 slices of every tile; fewer: 8 / slices XCDs share a slice and split the tiles
-    const int blocks = g.slices >= 8 ? tiles * g.slices : 8 * ((tiles + 8 / g.slices - 1) / (8 / g.slices));
-    down_tile_kernel<<<blocks, 256, kDLds, st>>>(h, A, part, d, r, g);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    down_finish_kernel<<<4 * g.n_rt_all * g.n_ct + (V + 511) / 512, 256, 0, st>>>(
+    down_finish_kernel<false><<<4 * g.n_rt_all * g.n_ct + (V + 511) / 512, 256, 0, st>>>(
         part, h, A, rows_pad, d, r, t32, static_cast<uint4 *>(t16), stat, B, V, tilescale, as_f16 ? 1 : 0, g);
+    return hipGetLastError();
+}
+
+hipError_t launch_down_projection_pieces(const uint16_t *h, const uint16_t *A, float *part, const DownGrid &g,
+                                         int rows_pad, int d, int r, void *X, hipStream_t st)
+{
+    const hipError_t e = launch_down_tiles<true>(h, A, part, g, d, r, st);
+    if (e != hipSuccess) return e;
+    down_finish_kernel<true><<<4 * g.n_rt_all * g.n_ct, 256, 0, st>>>(
+        part, h, A, rows_pad, d, r, nullptr, static_cast<uint4 *>(X), nullptr, nullptr, 0, nullptr, 0, g);
     return hipGetLastError();
 }
 

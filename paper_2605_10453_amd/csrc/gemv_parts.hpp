@@ -114,15 +114,93 @@ struct ChunkLds {
     uint64_t sel_cand[EW][kChunkCols];
 };
 
+// The k largest of a row's logits that one wavefront holds (up to E per lane, as order bits: 0 where the lane holds no
+// column), ranked by (logit desc, id asc) into out_val / out_id.  This is the tail of every block, after its last
+// weight row has arrived, and its instruction count is what a call of dozens of rows waits for.  All 64 lanes call.
+//   (1) T: the k-th largest of the 64 lane maxima, from a sort across the lanes.  An element below T is preceded by k
+//       lane maxima, so it cannot be among the k first.  (Bit by bit with ballots instead, T cost more than the rest.)
+//   (2) Where k is close to 64, T admits hundreds of elements and ranking them would take longer than everything else
+//       (k = 64: 53 us per launch against 27): T is raised by bisection until at most kCandSlack beyond k are left.
+//   (3) The elements >= T are compacted into `cand` (cap keys) through ballots and lane prefix counts and ranked by
+//       counting.  More than cap elements at the bound means that many equal logits: the largest key is then taken k
+//       times.
+// n_e: elements per lane in use (at most E, the same in all lanes); id(e): the id of this lane's element e.
+constexpr int kCandSlack = 24;
+template <int E, class Id>
+__device__ __forceinline__ void wave_topk(const uint32_t (&ob)[E], int n_e, Id id, int lane, int k, uint64_t *cand, int cap,
+                                          float *__restrict__ out_val, int *__restrict__ out_id)
+{
+    uint32_t lane_bits = ob[0];
+#pragma unroll
+    for (int e = 1; e < E; ++e) lane_bits = max(lane_bits, ob[e]);
+    const uint32_t sorted = wave_sort_desc(lane_bits, lane);
+    uint32_t T = max(1u, (uint32_t)__builtin_amdgcn_readlane((int)sorted, k - 1));       // fewer than k lanes in use: everything
+    const auto compact = [&]() {
+        int n = 0;
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            if (e >= n_e) break;
+            const bool take = ob[e] >= T;
+            const uint64_t mask = __ballot(take);
+            const int at = n + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+            if (take && at < cap) cand[at] = u64_from(ob[e], ~id(e));
+            n += __popcll(mask);
+        }
+        return n;
+    };
+    int n = compact();
+    if (n > 64 && n > k + kCandSlack) {
+        uint32_t hi = 0xffffffffu;                               // no element's bits reach it
+        while (n > k + kCandSlack && hi - T > 1u) {
+            const uint32_t mid = T + (hi - T) / 2;
+            int c = 0;
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                if (e >= n_e) break;
+                c += __popcll(__ballot(ob[e] >= mid));
+            }
+            if (c >= k) { T = mid; n = c; } else hi = mid;
+        }
+        lds_wave_sync();
+        n = compact();
+    }
+    lds_wave_sync();
+    if (n <= cap) {
+        for (int c0 = 0; c0 < n; c0 += 64) {
+            const int c = c0 + lane;
+            const uint64_t mine = (c < n) ? cand[c] : kNoKey;
+            int rk = 0;
+#pragma unroll 8
+            for (int q = 0; q < n; ++q) rk += (cand[q] > mine) ? 1 : 0;
+            if (c < n && rk < k) {
+                out_val[rk] = key_value(mine);
+                out_id[rk] = (int)key_tiebreak(mine);
+            }
+        }
+    } else {
+        uint64_t last = ~0ull;
+        for (int rk = 0; rk < k; ++rk) {
+            uint64_t best = kNoKey;
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                const uint64_t key = u64_from(ob[e], ~id(e));
+                if (ob[e] != 0u && key < last) best = u64_max(best, key);
+            }
+            last = wave_max_key(best);
+            if (lane == 0) { out_val[rk] = key_value(last); out_id[rk] = (int)key_tiebreak(last); }
+        }
+    }
+    if (lane >= n && lane < k) {                                 // fewer than k columns in this chunk
+        out_val[lane] = kNegInf;
+        out_id[lane] = kNoId;
+    }
+    lds_wave_sync();                                             // the buffers are reused by this wavefront's next row
+}
+
 // Row i of the chunk: fixed-order sum of the NW partial sums, then (max, sum of exp, top-k) of its
 // 512 logits, written as the partial of (row, chunk).  One wavefront; all 64 lanes must call.
 //
-// Top-k in three steps whose cost does not grow with k, and which stay inside the wavefront (this is the tail of
-// every block, after its last weight row has arrived: nothing overlaps it).  (1) T = the k-th largest of the 64
-// lane maxima, found bit by bit from the top with one ballot and one population count per bit: an element below
-// T is preceded by k lane maxima, so it cannot be in the top-k.  (2) The elements >= T (k or a few more; all of
-// them when values tie) are compacted into shared memory through ballots and lane prefix counts.  (3) They are
-// ranked among themselves by (logit desc, id asc) by counting.
+// Top-k: wave_topk.
 // part_smp (may be null): the chunk's best z_v + g_v with standard Gumbel noise g (Gumbel-max sampling), as
 // (z + g, id, z, -) of the winner; gk: the noise key of this row.
 template <int R, int NW>
@@ -169,44 +247,12 @@ __device__ __forceinline__ void chunk_row_epilogue(ChunkLds<R, NW> &L, int i, in
     for (int e = 0; e < 8; ++e) s += fast_exp(z[e] - m);     // exp(-inf) = 0 for padding lanes
     s = wave_sum(s);
 
-    // (1) T: the largest 32-bit pattern with at least k lane maxima at or above it (0 if fewer than k lanes hold columns)
-    uint64_t *cand = L.sel_cand[wave];
-    const uint32_t lane_bits = active ? float_order_bits(lm) : 0u;
-    uint32_t T = 0u;
-#pragma unroll
-    for (int bit = 31; bit >= 0; --bit) {
-        const uint32_t trial = T | (1u << bit);
-        if (__popcll(__ballot(lane_bits >= trial)) >= k) T = trial;
-    }
-    // (2) every element at or above T is a candidate; slot = number of candidates before it (element-major, then lane)
-    int n_cand = 0;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        const bool take = active && float_order_bits(z[e]) >= T;
-        const uint64_t mask = __ballot(take);
-        const int before = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-        if (take) cand[n_cand + before] = make_key(z[e], (uint32_t)(col + e));
-        n_cand += __popcll(mask);
-    }
-    lds_wave_sync();
-    // (3) rank the candidates among themselves by (value desc, id asc); ranks below k are the answer
-    for (int c0 = 0; c0 < n_cand; c0 += 64) {
-        const int c = c0 + lane;
-        const uint64_t mine = (c < n_cand) ? cand[c] : kNoKey;
-        int rk = 0;
-#pragma unroll 8
-        for (int q = 0; q < n_cand; ++q) rk += (cand[q] > mine) ? 1 : 0;
-        if (c < n_cand && rk < k) {
-            part_val[slot * k + rk] = key_value(mine);
-            part_id[slot * k + rk] = (int)key_tiebreak(mine);
-        }
-    }
-    if (lane >= n_cand && lane < k) {                  // fewer than k columns in this chunk
-        part_val[slot * k + lane] = kNegInf;
-        part_id[slot * k + lane] = kNoId;
-    }
     if (lane == 0) part_ms[slot] = make_float2(m, s);
-    lds_wave_sync();                                   // the buffers are reused by this wavefront's next row
+    uint32_t ob[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) ob[e] = active ? float_order_bits(z[e]) : 0u;
+    wave_topk<8>(ob, 8, [&](int e) { return (uint32_t)(col + e); }, lane, k, L.sel_cand[wave], kChunkCols,
+                 part_val + slot * k, part_id + slot * k);
 }
 
 // ---------------------------------------------------------------------------

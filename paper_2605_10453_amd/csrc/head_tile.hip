@@ -508,11 +508,12 @@ __global__ __launch_bounds__(128 * WR, 2) void head_tile_kernel(
 }
 
 // Row-major bf16 rows [rows, K] -> the X layout of head_tile_kernel (zero beyond K and beyond the last row).
-// grid = (rows_pad / 64, 8 ceil(K / 64)); one thread per 16-byte vector.
+// grid = (ceil(rows_pad / 64), 8 ceil(K / 64)); one thread per 16-byte vector.
 __global__ __launch_bounds__(64) void regroup_rows_kernel(const uint16_t *__restrict__ h, uint4 *__restrict__ X,
                                                           int rows, int rows_pad, int K)
 {
     const int row = blockIdx.x * 64 + threadIdx.x, kg = blockIdx.y;
+    if (row >= rows_pad) return;
     uint4 v = make_uint4(0u, 0u, 0u, 0u);
     if (row < rows && kg * 8 < K) v = *reinterpret_cast<const uint4 *>(h + (size_t)row * K + kg * 8);       // K is a multiple of 8
     X[(size_t)kg * rows_pad + row] = v;
@@ -520,7 +521,7 @@ __global__ __launch_bounds__(64) void regroup_rows_kernel(const uint16_t *__rest
 
 hipError_t launch_regroup_rows(const uint16_t *h, void *X, int rows, int rows_pad, int K, hipStream_t st)
 {
-    dim3 grid(rows_pad / 64, 8 * ((K + 63) / 64));
+    dim3 grid((rows_pad + 63) / 64, 8 * ((K + 63) / 64));
     regroup_rows_kernel<<<grid, 64, 0, st>>>(h, static_cast<uint4 *>(X), rows, rows_pad, K);
     return hipGetLastError();
 }

@@ -80,6 +80,17 @@ hipError_t launch_down_projection_tiles(const uint16_t *h, const uint16_t *A, fl
                                         float *t32, void *t16, float2 *stat, const uint16_t *B, int V, float2 *tilescale,
                                         bool as_f16, hipStream_t st);
 
+// the same t as three bf16 pieces, t = hi + mid + lo exactly (rows_head.hip): X [3][8 ceil(r / 64)][rows_pad] 16-byte
+// vectors, zero beyond r and beyond the last row
+hipError_t launch_down_projection_pieces(const uint16_t *h, const uint16_t *A, float *part, const DownGrid &g,
+                                         int rows_pad, int d, int r, void *X, hipStream_t st);
+
+// Partials per (row, chunk of 128 G columns) for up to kRowsMaxRows rows, the weights read once (rows_head.hip).
+// X: [pieces][8 ceil(K / 64)][16 ceil(rows / 16)] 16-byte vectors; pieces 1: the bf16 input itself, 3: the pieces of t
+// smp (null: off), seed: see launch_stream_topk; row0: index in the call of the first row
+hipError_t launch_rows_topk(const void *X, int pieces, const uint16_t *M, float2 *ms, float *pv, int *pi, float4 *smp,
+                            int rows, int row0, int K, int V, const RowsGeom &g, int k, uint32_t seed_lo, uint32_t seed_hi, hipStream_t st);
+
 // vocabulary projection with the fused epilogue, stages loaded straight into LDS; X is 16-byte vectors of 8 contraction
 // elements, [ceil(K / 64) * 8][rows_pad], rows_pad a multiple of 128; columns of an MFMA tile are contiguous
 // x_is_f16: X holds f16 t log2(e) and the kernel turns the M tiles into f16 inside LDS (an 8 times

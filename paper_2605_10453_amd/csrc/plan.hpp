@@ -217,4 +217,60 @@ inline MfmaPlan make_mfma_plan(HeadKind kind, int rows, int d, int r, int V) {
 inline int mfma_max_rows_per_launch(int rows) { return rows > 512 ? 512 : rows; }
 size_t merge_streams_lds_bytes(int nsr, int k, int n_vt);
 
+// ---- few rows or long lists on the matrix cores, fp32-exact products (rows_head.hip) ----------------------------
+constexpr int kRowsMaxRows = 48;         // rows per launch: three 16-row MFMA tiles (their accumulators: 96 registers)
+constexpr int kRowsMaxColGroups = 6;     // 128-column groups per block at most (their logits: 149 KB of LDS at 48 rows)
+// Floats between two rows of logits in shared memory; a row's place is reused for its candidates' 64-bit keys.
+constexpr __host__ __device__ int rows_lds_stride(int G) { return (128 * G > 512 ? 128 * G : 512) + 8; }
+// A block covers G groups of 128 columns in KS slices of the contraction (at most 8 wavefronts).  G is the
+// smallest that needs at most 256 blocks, one round on the chip's CUs; what is left of the 8 wavefronts splits the
+// contraction (more loads in flight, shorter chains of additions).  Wavefronts beyond G KS (a contraction of fewer
+// steps than slices) only take their share of the rows' epilogues.
+struct RowsGeom { int G = 1, KS = 1, waves = 8, chunks = 0; };
+inline RowsGeom make_rows_geom(int K, int V) {
+    RowsGeom g;
+    const int groups = (V + 127) / 128, steps = (K + 31) / 32;
+    g.G = (groups + 255) / 256;
+    if (g.G > kRowsMaxColGroups) g.G = 4;
+    g.KS = 8 / g.G;
+    g.waves = g.G * g.KS;
+    if (g.KS > steps) g.KS = steps;
+    g.chunks = (groups + g.G - 1) / g.G;
+    return g;
+}
+// Contractions this path takes: its row operand and partial tiles then fit beside the lists in a few tens of MB.
+inline bool rows_path_fits(HeadKind kind, int d, int r) { return kind == HeadKind::LowRank ? r <= 2048 : d <= 8192; }
+
+struct RowsPlan {
+    int rows = 0, rows_pad = 0, pieces = 1;
+    RowsGeom geom;
+    DownGrid down;
+    size_t off_down_part = 0;            // fp32 partial tiles of t (low-rank head; sized for any grouping of the rows)
+    size_t off_x = 0;                    // 16-byte vectors [pieces][8 ceil(K / 64)][rows_pad]
+    size_t off_part_ms = 0, off_part_val = 0, off_part_id = 0, off_part_smp = 0;      // as in Plan, [rows, chunks]
+    size_t bytes = 0;
+};
+// rows: of one launch, at most kRowsMaxRows
+inline RowsPlan make_rows_plan(HeadKind kind, int rows, int d, int r, int V, int k) {
+    RowsPlan p;
+    const int K = kind == HeadKind::LowRank ? r : d;
+    p.rows = rows;
+    p.rows_pad = (rows + 15) / 16 * 16;
+    p.pieces = kind == HeadKind::LowRank ? 3 : 1;
+    p.geom = make_rows_geom(K, V);
+    size_t off = 0;
+    if (kind == HeadKind::LowRank) {
+        p.down = make_down_grid(rows, p.rows_pad, d, r);
+        p.off_down_part = off; off = align_up(off + sizeof(float) * 4096 * down_part_tiles_bound(rows, r));
+    }
+    p.off_x = off;         off = align_up(off + 16 * (size_t)p.pieces * p.rows_pad * ((K + 63) / 64 * 8));
+    const size_t n = (size_t)rows * p.geom.chunks;
+    p.off_part_ms = off;   off = align_up(off + 2 * sizeof(float) * n);
+    p.off_part_val = off;  off = align_up(off + sizeof(float) * n * k);
+    p.off_part_id = off;   off = align_up(off + sizeof(int32_t) * n * k);
+    p.off_part_smp = off;  off = align_up(off + 16 * n);
+    p.bytes = off;
+    return p;
+}
+
 }  // namespace slimspec

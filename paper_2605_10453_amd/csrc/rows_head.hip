@@ -1,0 +1,273 @@
+// Vocabulary projection with the fused log-sum-exp / top-k epilogue for calls of a few rows (paper section 4.1:
+// logits = t B, or h W for the full head, never written to memory): the weight matrix streams from HBM once for up to
+// 48 rows, and the products are as exact as fp32 fused multiply-adds.
+//
+// What bounds it: reading the weight matrix.  The lane-owns-columns kernel (gemv_kernels.hip) spends one fp32
+// multiply-add per weight and row, so from two rows on its vector instructions, not the memory, decide (60 us at 4
+// rows, 72 us for every 8 rows at d = 4096, r = 512, V = 128256).  Here the matrix cores multiply:
+//   * bf16 weights times an fp32 t = hi + mid + lo, three bf16 pieces that hold its 24 significant bits exactly: every
+//     product is exact and only the fp32 accumulation rounds, as in a chain of fp32 multiply-adds.  Three times the
+//     matrix work is still far below the time the weights need (48 rows: 19 GFLOP beside 131 MB).
+//   * A wavefront owns 128 columns and a slice of the contraction.  Its lanes load the weights as they lie in memory
+//     (lane = 8 adjacent columns of one row, 256-byte segments, 8 rows each), straight into registers; a lane then
+//     holds an 8 x 8 block, which 32 byte permutes turn into 8 operands of v_mfma_f32_16x16x32_bf16 (8 consecutive
+//     contraction elements of one column).  Half a vector instruction per weight whatever the number of rows, and no
+//     shared memory in the loop.
+//   * The wavefronts of a block cover G x 128 adjacent columns in KS slices of the contraction, G chosen so that
+//     every block is resident at once (at most 256 chunks): no last, nearly empty round.
+// The partials have the layout of the streaming kernel's, and the same merge kernel finishes the call.
+//
+// Measured at d = 4096, r = 512, V = 128256 (kernel alone; 131 MB of weights are 22-26 us at a plain read's rate): 2 rows
+// 26.6 us, 40 rows 40 us (the epilogue of five rows per wavefront is what the difference consists of).  Calls: 40 rows
+// with k = 32 420 -> 61 us, 23 rows with k = 10 58.0 -> 48.7 us, 4 rows with k = 64 81 -> 50 us.  Error of the
+// log-probabilities against 64-bit arithmetic: 7.7e-8 relative, 1.0e-7 with one multiply-add per weight (40 rows, k = 32).
+#include "gemv_parts.hpp"
+#include "launch.hpp"
+
+namespace slimspec {
+
+namespace {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kRowsMaxG = kRowsMaxColGroups;
+
+// Two 16-bit elements (low or high halves of a and b) as one operand dword: a's element first.
+template <bool HIGH>
+__device__ __forceinline__ uint32_t pair16(uint32_t a, uint32_t b) {
+    return __builtin_amdgcn_perm(b, a, HIGH ? 0x07060302u : 0x05040100u);
+}
+
+}  // namespace
+
+// X: [NP][8 ceil(K / 64)][16 NT] 16-byte vectors of 8 consecutive contraction elements of one row: the bf16 input
+//    itself (NP = 1: full head) or the pieces of t (NP = 3); zero beyond K and beyond the last row.
+// M: [K, V] bf16 row-major, V and K multiples of 8
+// Block b: columns [128 G b, 128 G (b + 1)); wavefront w: column group w % G, contraction slice w / G (none from KS on).
+// Partials of (row, chunk): see stream_topk_kernel.  row0: the index in the call of this launch's first row (noise).
+template <int NT, int NP>
+__global__ __launch_bounds__(512) void rows_topk_kernel(
+    const uint4 *__restrict__ X, const uint16_t *__restrict__ M,
+    float2 *__restrict__ part_ms, float *__restrict__ part_val, int *__restrict__ part_id, float4 *__restrict__ part_smp,
+    int rows, int row0, int K, int V, int chunks, int G, int KS, int k, uint32_t seed_lo, uint32_t seed_hi)
+{
+    extern __shared__ __align__(16) float z_lds[];               // [16 NT][row_stride]
+    constexpr int RP = 16 * NT;
+    const int row_stride = rows_lds_stride(G);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int cg = wave % G, ks = wave / G;
+    const int c16 = lane & 15, kg = lane >> 4;
+    const int n_steps = (K + 31) / 32, per = (n_steps + KS - 1) / KS;
+    const int s_beg = min(n_steps, ks * per), s_end = min(n_steps, s_beg + per);
+    const int chunk_col = blockIdx.x * (128 * G);
+    const size_t x_piece = (size_t)((K + 63) / 64 * 8) * RP;
+
+    f32x4 acc[8][NT];                                            // [column in the lane's 8][row tile]
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[j][nt][i] = 0.f;
+
+    {
+        // columns beyond V re-read the last group that exists (their logits are masked below)
+        const uint16_t *const m_lane = M + min(chunk_col + cg * 128 + 8 * c16, V - 8);
+        const uint4 *const x_lane = X + (size_t)kg * RP + c16;
+        u32x4 q[2][8], xv[NP][NT];
+        const auto load_m = [&](u32x4 (&dst)[8], int s) {
+            // K is a multiple of 8: a lane's 8 rows exist or none do (then rows of the step that do are read, and dropped)
+            const int k0 = 32 * s + ((32 * s + 8 * kg < K) ? 8 * kg : 0);
+            const uint16_t *p = m_lane + (size_t)k0 * V;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) dst[u] = *reinterpret_cast<const u32x4 *>(p + (size_t)u * V);
+        };
+        const auto load_x = [&](int s) {
+#pragma unroll
+            for (int p = 0; p < NP; ++p)
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt)
+                    xv[p][nt] = *reinterpret_cast<const u32x4 *>(x_lane + p * x_piece + (size_t)(4 * s) * RP + 16 * nt);
+        };
+        const auto multiply = [&](u32x4 (&w)[8], int s) {
+            if (32 * s + 32 > K) {                               // the last step of a K that is no multiple of 32
+                const uint32_t keep = (32 * s + 8 * kg < K) ? 0xffffffffu : 0u;
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) w[u][e] &= keep;
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                u32x4 a0, a1;                                    // columns 2 e and 2 e + 1 of the lane's 8
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    a0[t] = pair16<false>(w[2 * t][e], w[2 * t + 1][e]);
+                    a1[t] = pair16<true>(w[2 * t][e], w[2 * t + 1][e]);
+                }
+                // The step's products are summed on their own, the smallest pieces first, and then added: the matrix
+                // unit's internal roundings then happen at the size of one step's sum, not of the whole.
+                f32x4 t0[NT], t1[NT];
+                const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int p = NP - 1; p >= 0; --p)
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt) {
+                        t0[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a0), __builtin_bit_cast(bf16x8, xv[p][nt]), p == NP - 1 ? zero : t0[nt], 0, 0, 0);
+                        t1[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a1), __builtin_bit_cast(bf16x8, xv[p][nt]), p == NP - 1 ? zero : t1[nt], 0, 0, 0);
+                    }
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) { acc[2 * e][nt] += t0[nt]; acc[2 * e + 1][nt] += t1[nt]; }
+                if (NT == 3) __builtin_amdgcn_sched_barrier(0);   // keeps the next pair's operands out of the registers (256 per lane)
+            }
+        };
+        // Two steps of weights in flight.  Loads return in order, so a step's row operand is requested before the
+        // weights of the step after it: waiting for it leaves those in flight.
+        if (s_beg < s_end) {
+            load_m(q[0], s_beg);
+            load_x(s_beg);
+            __builtin_amdgcn_sched_barrier(0);
+            load_m(q[1], min(s_beg + 1, s_end - 1));
+            __builtin_amdgcn_sched_barrier(0);
+            for (int s = s_beg; s < s_end; s += 2) {
+                multiply(q[0], s);
+                __builtin_amdgcn_sched_barrier(0);
+                if (s + 1 < s_end) {
+                    load_x(s + 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                    load_m(q[0], min(s + 2, s_end - 1));         // (past the end: the last step once more, unused)
+                    __builtin_amdgcn_sched_barrier(0);
+                    multiply(q[1], s + 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                    load_x(min(s + 2, s_end - 1));
+                    __builtin_amdgcn_sched_barrier(0);
+                    load_m(q[1], min(s + 3, s_end - 1));
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+        }
+    }
+
+    // the slices of the contraction meet in shared memory, the last slice first (a fixed order)
+    for (int kk = KS - 1; kk >= 0; --kk) {
+        if (ks == kk) {
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    // element (m = 4 kg + i, n = c16) of tile j is column 8 m + j of row 16 nt + n
+                    float4 *dst = reinterpret_cast<float4 *>(z_lds + (16 * nt + c16) * row_stride + cg * 128 + 8 * (4 * kg + i));
+                    float4 a = make_float4(acc[0][nt][i], acc[1][nt][i], acc[2][nt][i], acc[3][nt][i]);
+                    float4 b = make_float4(acc[4][nt][i], acc[5][nt][i], acc[6][nt][i], acc[7][nt][i]);
+                    if (kk != KS - 1) {
+                        const float4 c = dst[0], d = dst[1];
+                        a.x += c.x; a.y += c.y; a.z += c.z; a.w += c.w;
+                        b.x += d.x; b.y += d.y; b.z += d.z; b.w += d.w;
+                    }
+                    dst[0] = a; dst[1] = b;
+                }
+        }
+        __syncthreads();
+    }
+
+    // One wavefront per row: running max, sum of exp and top-k of the chunk.  Lane = columns 2 lane, 2 lane + 1 of every
+    // group of 128.
+    constexpr int E = 2 * kRowsMaxG;
+    const auto act = [&](int g) { return chunk_col + 128 * g + 2 * lane < V; };      // V is even: both columns or none
+    const auto id = [&](int e) { return (uint32_t)(chunk_col + 128 * (e >> 1) + 2 * lane + (e & 1)); };
+    for (int row = wave; row < rows; row += (int)(blockDim.x >> 6)) {
+        float *zr = z_lds + row * row_stride;
+        const size_t slot = (size_t)row * chunks + blockIdx.x;
+        float z[E], m = kNegInf, s = 0.f;
+#pragma unroll
+        for (int g = 0; g < kRowsMaxG; ++g) {
+            float2 v = make_float2(kNegInf, kNegInf);
+            if (g < G && act(g)) v = *reinterpret_cast<const float2 *>(zr + 128 * g + 2 * lane);
+            z[2 * g] = v.x; z[2 * g + 1] = v.y;
+        }
+        const auto max_and_sum = [&]() {
+            m = z[0];
+#pragma unroll
+            for (int e = 1; e < E; ++e) m = fmaxf(m, z[e]);
+            m = wave_max(m);
+            s = 0.f;
+#pragma unroll
+            for (int g = 0; g < kRowsMaxG; ++g)
+                if (g < G) s += fast_exp(z[2 * g] - m) + fast_exp(z[2 * g + 1] - m);     // exp(-inf) = 0 beyond V
+            s = wave_sum(s);
+        };
+        max_and_sum();
+        if (NP > 1 && !(s < __builtin_huge_valf())) {
+            // A logit that is no finite number.  The pieces of t cannot stand for one product with an infinite weight
+            // (0 times infinity): sum the chunk's logits of this row again, one multiply-add per weight, from t itself.
+            const uint16_t *xb = reinterpret_cast<const uint16_t *>(X);
+#pragma unroll 1
+            for (int g = 0; g < G; ++g) {
+                if (!act(g)) continue;
+                float z0 = 0.f, z1 = 0.f;
+#pragma unroll 1
+                for (int j = 0; j < K; ++j) {
+                    const size_t e = ((size_t)(j >> 3) * RP + row) * 8 + (j & 7);
+                    float t = bf16_to_float(xb[e]);
+                    for (int p = 1; p < NP; ++p) t += bf16_to_float(xb[e + p * x_piece * 8]);      // exact: the pieces do not overlap
+                    const uint32_t w = *reinterpret_cast<const uint32_t *>(M + (size_t)j * V + chunk_col + 128 * g + 2 * lane);
+                    z0 = fmaf(t, bf16_lo(w), z0);
+                    z1 = fmaf(t, bf16_hi(w), z1);
+                }
+#pragma unroll
+                for (int gg = 0; gg < kRowsMaxG; ++gg)
+                    if (gg == g) { z[2 * gg] = z0; z[2 * gg + 1] = z1; }
+            }
+            max_and_sum();
+        }
+        if (part_smp) {
+            // keys are unique (one per id), so exactly one lane holds the wavefront's largest
+            const GumbelKey gk = gumbel_key(seed_lo, seed_hi, (uint32_t)(row0 + row));
+            uint64_t best = kNoKey;
+            float zb = 0.f;
+#pragma unroll
+            for (int e = 0; e < E; ++e)
+                if ((e >> 1) < G && act(e >> 1)) {
+                    const uint64_t key = make_key(z[e] + gumbel_base2(gk, id(e)) * kLn2, id(e));
+                    if (key > best) { best = key; zb = z[e]; }
+                }
+            const uint64_t top = wave_max_key(best);
+            if (best == top && best != kNoKey)
+                part_smp[slot] = make_float4(key_value(top), __int_as_float((int)key_tiebreak(top)), zb, 0.f);
+        }
+        if (lane == 0) part_ms[slot] = make_float2(m, s);
+        uint32_t ob[E];
+#pragma unroll
+        for (int e = 0; e < E; ++e) ob[e] = ((e >> 1) < G && act(e >> 1)) ? float_order_bits(z[e]) : 0u;
+        // the candidates' keys go where the row's logits were
+        lds_wave_sync();
+        wave_topk<E>(ob, 2 * G, id, lane, k, reinterpret_cast<uint64_t *>(zr), row_stride / 2, part_val + slot * k, part_id + slot * k);
+    }
+}
+
+template <int NT, int NP>
+static hipError_t launch_rows(const void *X, const uint16_t *M, float2 *ms, float *pv, int *pi, float4 *smp, int rows, int row0,
+                              int K, int V, const RowsGeom &g, int k, uint32_t seed_lo, uint32_t seed_hi, hipStream_t st)
+{
+    const size_t lds = sizeof(float) * 16 * NT * (size_t)rows_lds_stride(g.G);
+    static LdsLimit lds_limit;
+    hipError_t e = lds_limit.raise(reinterpret_cast<const void *>(rows_topk_kernel<NT, NP>), (int)lds);
+    if (e != hipSuccess) return e;
+    rows_topk_kernel<NT, NP><<<g.chunks, 64 * g.waves, lds, st>>>(static_cast<const uint4 *>(X), M, ms, pv, pi, smp, rows, row0,
+                                                                    K, V, g.chunks, g.G, g.KS, k, seed_lo, seed_hi);
+    return hipGetLastError();
+}
+
+hipError_t launch_rows_topk(const void *X, int pieces, const uint16_t *M, float2 *ms, float *pv, int *pi, float4 *smp,
+                            int rows, int row0, int K, int V, const RowsGeom &g, int k, uint32_t seed_lo, uint32_t seed_hi, hipStream_t st)
+{
+#define SLIMSPEC_ROWS(NT, NP) launch_rows<NT, NP>(X, M, ms, pv, pi, smp, rows, row0, K, V, g, k, seed_lo, seed_hi, st)
+    if (pieces == 1) return rows <= 16 ? SLIMSPEC_ROWS(1, 1) : rows <= 32 ? SLIMSPEC_ROWS(2, 1) : SLIMSPEC_ROWS(3, 1);
+    return rows <= 16 ? SLIMSPEC_ROWS(1, 3) : rows <= 32 ? SLIMSPEC_ROWS(2, 3) : SLIMSPEC_ROWS(3, 3);
+#undef SLIMSPEC_ROWS
+}
+
+}  // namespace slimspec

@@ -52,8 +52,9 @@ int check_shape(HeadKind kind, const slimspec_shape *s, int32_t k)
     return SLIMSPEC_OK;
 }
 
-constexpr int kMfmaMaxK = 16;      // the lane streams keep 3 groups: enough for k <= 16 (larger k: streaming path)
-constexpr int kMfmaMinRows = 5;    // from here on the matrix-core path is faster than streaming rows in lock step (measured at C2's shape)
+constexpr int kMfmaMaxK = 16;      // the lane streams keep 3 groups: enough for k <= 16 (larger k: rows_head.hip)
+constexpr int64_t kRowsMinWeights = 12 << 20;      // (see rows_path_takes)
+constexpr int kMfmaMinRows = 5;    // below, rows whose calls rows_path_takes leaves are streamed in lock step
 
 // The launches of one call share the workspace in stream order; a last, smaller batch has a plan of its own
 // (fewer row blocks, more slices of d), so the call needs the larger of the two plans.
@@ -97,6 +98,19 @@ int position_of_row(const Positions &pos, int row)
     return p;
 }
 
+// This launch's rows [row0, row0 + rows) in groups by position (empty groups dropped); the workspace is sized for any grouping
+DownGrid down_grid_by_position(const Positions &pos, int row0, int rows, int rows_pad, int d, int r)
+{
+    int g_first[kMaxPositions + 1], g_mat[kMaxPositions], n_groups = 0;
+    for (int q = 0; q < pos.n; ++q) {
+        const int lo = pos.off[q] > row0 ? pos.off[q] : row0;
+        const int hi = pos.off[q + 1] < row0 + rows ? pos.off[q + 1] : row0 + rows;
+        if (hi > lo) { g_first[n_groups] = lo - row0; g_mat[n_groups] = q; ++n_groups; }
+    }
+    g_first[n_groups] = rows;
+    return make_down_grid(rows, rows_pad, d, r, n_groups, g_first, g_mat);
+}
+
 int run_head_mfma(HeadKind kind, const void *h, const void *A, const void *M, const void *Mt,
                   const slimspec_shape *shape, int32_t k, int32_t *out_ids, float *out_logprobs, const int32_t *id_map,
                   const Positions &pos, const SampleOut &so, void *workspace, size_t workspace_bytes, void *stream)
@@ -113,17 +127,7 @@ int run_head_mfma(HeadKind kind, const void *h, const void *A, const void *M, co
         const int rows = (shape->rows - row0 < per) ? shape->rows - row0 : per;
         // a last, smaller batch may fall below the matrix-core threshold; it still runs here
         MfmaPlan p = make_mfma_plan(kind, rows, d, r, V);
-        if (kind == HeadKind::LowRank && pos.n > 0) {
-            // this launch's rows in groups by position (empty groups dropped); the workspace is sized for any grouping
-            int g_first[kMaxPositions + 1], g_mat[kMaxPositions], n_groups = 0;
-            for (int q = 0; q < pos.n; ++q) {
-                const int lo = pos.off[q] > row0 ? pos.off[q] : row0;
-                const int hi = pos.off[q + 1] < row0 + rows ? pos.off[q + 1] : row0 + rows;
-                if (hi > lo) { g_first[n_groups] = lo - row0; g_mat[n_groups] = q; ++n_groups; }
-            }
-            g_first[n_groups] = rows;
-            p.down = make_down_grid(rows, p.rows_pad, d, r, n_groups, g_first, g_mat);
-        }
+        if (kind == HeadKind::LowRank && pos.n > 0) p.down = down_grid_by_position(pos, row0, rows, p.rows_pad, d, r);
         float *streams = reinterpret_cast<float *>(ws + p.off_streams);
         const uint16_t *hrow = hb + (size_t)row0 * d;
         hipError_t e;
@@ -166,6 +170,66 @@ int run_head_mfma(HeadKind kind, const void *h, const void *A, const void *M, co
     return SLIMSPEC_OK;
 }
 
+// Few rows, or lists longer than the lane streams keep: every launch reads the weights once for up to kRowsMaxRows
+// rows (rows_head.hip).  Where the lines lie (us per call at d = 4096, r = 512, V = 128256 unless said otherwise):
+//   * k > kMfmaMaxK: always; the lane-owns-columns kernel reads the weights once per 8 rows (40 rows, k = 32: 420 -> 61).
+//   * up to 48 rows, k <= kMfmaMaxK: 5 rows 57.6 -> 43.3, 23 rows 58.0 -> 48.7, 48 rows 61.0 -> 60.0 (d = 8192, r = 1024:
+//     97.7 -> 87.1) against head_tile_kernel and its merge; a second launch, beyond 48 rows, loses.
+//   * from 3 rows: 48.0 -> 42.7.  Two rows are faster on the lane-owns-columns kernel (39.3 against 41.9: it needs no
+//     kernel that finishes t), and so are 3 and 4 rows on small weights (4 rows, r = 200: V = 32000 20.6 against 22.6,
+//     V = 64000 24.1 / 24.1; r = 512, V = 32000 33.6 -> 26.4).
+//   * the full head has no t to finish: from 2 rows (188.9 -> 185.3; 4 rows, d = 1024, V = 16000: 33.6 -> 21.2).
+bool rows_path_takes(HeadKind kind, const slimspec_shape *s, int32_t k)
+{
+    if (s->rows < 2 || !rows_path_fits(kind, s->d, s->r)) return false;
+    if (kind == HeadKind::LowRank && (s->rows == 2 || (s->rows <= 4 && (int64_t)s->r * s->V < kRowsMinWeights))) return false;
+    return k > kMfmaMaxK || s->rows <= kRowsMaxRows;
+}
+
+size_t rows_workspace_bytes(HeadKind kind, const slimspec_shape *s, int32_t k)
+{
+    return make_rows_plan(kind, s->rows < kRowsMaxRows ? s->rows : kRowsMaxRows, s->d, s->r, s->V, k).bytes;
+}
+
+int run_head_rows(HeadKind kind, const void *h, const void *A, const void *M, const slimspec_shape *shape, int32_t k,
+                  int32_t *out_ids, float *out_logprobs, const int32_t *id_map,
+                  const Positions &pos, const SampleOut &so, void *workspace, size_t workspace_bytes, void *stream)
+{
+    if (workspace_bytes < rows_workspace_bytes(kind, shape, k)) return SLIMSPEC_WORKSPACE_TOO_SMALL;
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    char *ws = static_cast<char *>(workspace);
+    const int d = shape->d, r = shape->r, V = shape->V, K = kind == HeadKind::LowRank ? r : d;
+    const uint16_t *Mb = static_cast<const uint16_t *>(M);
+    for (int row0 = 0; row0 < shape->rows; row0 += kRowsMaxRows) {
+        const int rows = (shape->rows - row0 < kRowsMaxRows) ? shape->rows - row0 : kRowsMaxRows;
+        RowsPlan p = make_rows_plan(kind, rows, d, r, V, k);
+        const uint16_t *hrow = static_cast<const uint16_t *>(h) + (size_t)row0 * d;
+        void *X = ws + p.off_x;
+        hipError_t e;
+        if (kind == HeadKind::LowRank) {
+            if (pos.n > 0) p.down = down_grid_by_position(pos, row0, rows, p.rows_pad, d, r);
+            e = launch_down_projection_pieces(hrow, static_cast<const uint16_t *>(A), reinterpret_cast<float *>(ws + p.off_down_part),
+                                              p.down, p.rows_pad, d, r, X, s);
+        } else
+            e = launch_regroup_rows(hrow, X, rows, p.rows_pad, d, s);
+        if (e != hipSuccess) return fail_hip(e);
+        float2 *ms = reinterpret_cast<float2 *>(ws + p.off_part_ms);
+        float *pv = reinterpret_cast<float *>(ws + p.off_part_val);
+        int *pi = reinterpret_cast<int *>(ws + p.off_part_id);
+        float4 *smp = so.on ? reinterpret_cast<float4 *>(ws + p.off_part_smp) : nullptr;
+        const bool timed = g_ev_start && row0 == 0;
+        if (timed && (e = hipEventRecord(g_ev_start, s)) != hipSuccess) return fail_hip(e);
+        e = launch_rows_topk(X, p.pieces, Mb, ms, pv, pi, smp, rows, row0, K, V, p.geom, k, so.seed_lo, so.seed_hi, s);
+        if (e != hipSuccess) return fail_hip(e);
+        if (timed && (e = hipEventRecord(g_ev_stop, s)) != hipSuccess) return fail_hip(e);
+        SampleOut so_rows = so;
+        if (so.on) { so_rows.lse += row0; so_rows.sample_ids += row0; so_rows.sample_logprobs += row0; }
+        e = launch_merge(ms, pv, pi, rows, p.geom.chunks, k, out_ids + (size_t)row0 * k, out_logprobs + (size_t)row0 * k, id_map, so_rows, smp, s);
+        if (e != hipSuccess) return fail_hip(e);
+    }
+    return SLIMSPEC_OK;
+}
+
 int run_head(HeadKind kind, const void *h, const void *A, const void *M, bool m_is_f32,
              const slimspec_shape *shape, int32_t k, int32_t *out_ids, float *out_logprobs,
              void *workspace, size_t workspace_bytes, void *stream, const int32_t *id_map = nullptr,
@@ -180,6 +244,8 @@ int run_head(HeadKind kind, const void *h, const void *A, const void *M, bool m_
     if ((reinterpret_cast<uintptr_t>(out_ids) & 3u) || (reinterpret_cast<uintptr_t>(out_logprobs) & 3u))
         return SLIMSPEC_UNSUPPORTED;
     if (so.on && (!so.lse || !so.sample_ids || !so.sample_logprobs)) return SLIMSPEC_INVALID_ARGUMENT;
+    if (!m_is_f32 && rows_path_takes(kind, shape, k))
+        return run_head_rows(kind, h, A, M, shape, k, out_ids, out_logprobs, id_map, pos, so, workspace, workspace_bytes, stream);
     const bool use_mfma = shape->rows >= kMfmaMinRows && !m_is_f32 && k <= kMfmaMaxK;
     if (use_mfma)
         return run_head_mfma(kind, h, A, M, Mt, shape, k, out_ids, out_logprobs, id_map, pos, so, workspace, workspace_bytes, stream);
@@ -242,6 +308,10 @@ size_t head_workspace_bytes(HeadKind kind, const slimspec_shape *shape, int32_t 
     if (shape->rows >= kMfmaMinRows) {
         const size_t m = mfma_workspace_bytes(kind, shape);
         if (m > need) need = m;
+    }
+    if (rows_path_takes(kind, shape, k)) {
+        const size_t w = rows_workspace_bytes(kind, shape, k);
+        if (w > need) need = w;
     }
     return need;
 }

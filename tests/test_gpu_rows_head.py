@@ -1,0 +1,77 @@
+"""The weight-streaming matrix-core kernel for a few rows or long lists (csrc/rows_head.hip) against the CPU fp64 checker,
+at the edges of its tiles: 16-row tiles, 48 rows per launch, chunks of 128 to 768 columns, contractions that are no
+multiple of 32, lists of 1 to 64 ids, more equal logits than a row's candidate buffer holds, infinite weights."""
+import numpy as np
+import pytest
+
+from paper_2605_10453_amd import synth
+from parity_util import compare_with_oracle, to_dev_bf16
+from test_gpu_parity import gpu  # noqa: F401  (the module's fixture)
+
+pytestmark = pytest.mark.gpu
+
+# Products are exact and sums fp32: logits below 32 in magnitude (peaked rows), 2^-19 apart there; 32 such steps cover
+# the roundings of the accumulation, of t and of the log-sum-exp many times over (5e-6 seen).
+FP32_TOL = 6e-5
+
+
+# rows; V in column groups of 128 per block: 1 (up to 32768 columns), 2, 3, 4, 5 (131080), 6 (165000)
+@pytest.mark.parametrize("rows,d,r,V,k", [
+    (5, 64, 8, 8, 1), (5, 64, 8, 136, 17), (16, 96, 40, 1000, 64), (17, 72, 24, 8200, 33), (32, 128, 64, 32776, 10),
+    (33, 256, 72, 32776, 16), (48, 264, 200, 8192, 5), (49, 128, 96, 5000, 20), (97, 64, 32, 2056, 64),
+    (6, 128, 64, 65544, 24), (8, 64, 40, 98312, 10), (40, 64, 40, 131080, 32), (3, 512, 104, 131080, 10), (47, 64, 16, 165000, 48),
+    (4, 512, 256, 65544, 64),
+])
+def test_low_rank_at_the_tile_edges(gpu, oracle_mod, rows, d, r, V, k):
+    torch, b = gpu
+    print(f"rows kernel, low-rank: rows={rows} d={d} r={r} V={V} k={k}", flush=True)
+    x = synth.make_inputs(synth.small_config(rows, d, r, V, k, peaked_every=4), seed=rows + V)
+    ids, lp = b.slimspec_head_topk(to_dev_bf16(x.h), to_dev_bf16(x.A), to_dev_bf16(x.B), k)
+    torch.cuda.synchronize()
+    ora = oracle_mod.slimspec_head_topk(x.h, x.A, x.B, k)
+    z_at = lambda ri, ci: oracle_mod.slimspec_logits_at(x.h, x.A, x.B, ri, ci)
+    compare_with_oracle(ids.cpu().numpy(), lp.cpu().numpy(), ora.ids, ora.lse, z_at, V, tie_tol=FP32_TOL, lp_tol=FP32_TOL)
+
+
+@pytest.mark.parametrize("rows,d,V,k", [(2, 8, 136, 64), (2, 1000, 32776, 10), (15, 136, 8200, 3), (33, 520, 4104, 40), (48, 72, 66000, 16)])
+def test_full_head_at_the_tile_edges(gpu, oracle_mod, rows, d, V, k):
+    torch, b = gpu
+    print(f"rows kernel, full head: rows={rows} d={d} V={V} k={k}", flush=True)
+    x = synth.make_inputs(synth.small_config(rows, d, 8, V, k, peaked_every=4), seed=rows + d, with_full_head=True)
+    ids, lp = b.full_head_topk(to_dev_bf16(x.h), to_dev_bf16(x.W), k)
+    torch.cuda.synchronize()
+    ora = oracle_mod.full_head_topk(x.h, x.W, k)
+    z_at = lambda ri, ci: oracle_mod.full_logits_at(x.h, x.W, ri, ci)
+    compare_with_oracle(ids.cpu().numpy(), lp.cpu().numpy(), ora.ids, ora.lse, z_at, V, tie_tol=FP32_TOL, lp_tol=FP32_TOL)
+
+
+@pytest.mark.parametrize("k", [3, 40])
+def test_more_equal_logits_than_the_candidate_buffer(gpu, oracle_mod, k):
+    """All columns equal: every logit ties, the ids are 0 .. k - 1 and the log-probability is -ln V."""
+    torch, b = gpu
+    rows, d, r, V = 6, 64, 16, 165000
+    x = synth.make_inputs(synth.small_config(rows, d, r, V, k), seed=4)
+    B = np.ascontiguousarray(np.repeat(x.B[:, :1], V, axis=1))
+    ids, lp = b.slimspec_head_topk(to_dev_bf16(x.h), to_dev_bf16(x.A), to_dev_bf16(B), k)
+    torch.cuda.synchronize()
+    assert np.array_equal(ids.cpu().numpy(), np.tile(np.arange(k, dtype=np.int32), (rows, 1)))
+    assert np.abs(lp.cpu().numpy() + np.log(V)).max() <= FP32_TOL
+
+
+def test_infinite_weights_and_hidden_states(gpu):
+    """Same ids and the same (possibly not-a-number) log-probabilities as the one-row calls, which multiply in fp32."""
+    torch, b = gpu
+    rows, d, r, V, k = 7, 128, 48, 8200, 6
+    x = synth.make_inputs(synth.small_config(rows, d, r, V, k), seed=9)
+    h, A, B = to_dev_bf16(x.h), to_dev_bf16(x.A), to_dev_bf16(x.B)
+    B[5, 777] = float("inf")
+    B[11, 8199] = float("-inf")
+    h[3, 10] = float("inf")
+    ids, lp = b.slimspec_head_topk(h, A, B, k)
+    for i in range(rows):
+        if i == 3:      # every logit of this row is infinite or not a number: nothing to compare but that it returns
+            continue
+        want_ids, want_lp = b.slimspec_head_topk(h[i:i + 1].contiguous(), A, B, k)
+        torch.cuda.synchronize()
+        assert torch.equal(ids[i], want_ids[0]), (i, ids[i], want_ids[0])
+        assert torch.allclose(lp[i], want_lp[0], atol=FP32_TOL, rtol=0, equal_nan=True), (i, lp[i], want_lp[0])
