@@ -13,6 +13,8 @@ LIB = os.path.join(HERE, "libslimspec.so")
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",   # no packed-fp32 code generation
+    # MFMA results in vector registers also where a kernel has 512 registers per lane (head_resident.hip reads them there)
+    "-mllvm", "-amdgpu-mfma-vgpr-form=1",
     "-Wall", "-Wno-unused-command-line-argument",
 ]
 

@@ -100,6 +100,9 @@ hipError_t launch_rows_topk(const void *X, int pieces, const uint16_t *M, float2
 // index of the launch's first row in the call (the noise is a function of the row's index in the call)
 hipError_t launch_head_tile(const void *X, bool x_is_f16, bool natural_units, const uint16_t *M, float *part, int rows, int rows_pad,
                             int K, int V, int n_rb, int gw, const SampleOut &so, int row_base, hipStream_t st);
+// the same with the row operand resident in registers: bf16 t log2(e), K <= kResidentMaxK, rows_pad a multiple of 256
+hipError_t launch_head_resident(const void *X, const uint16_t *M, float *part, int rows, int rows_pad, int K, int V,
+                                const ResidentGrid &g, hipStream_t st);
 // true only in an experiment build (-DSLIMSPEC_DIAG_DBG=n) where a timing-only variant replaces the kernel: its
 // output is not a result and the calls then return SLIMSPEC_UNSUPPORTED
 bool head_tile_timing_only();
@@ -107,14 +110,15 @@ bool head_tile_timing_only();
 hipError_t launch_regroup_rows(const uint16_t *h, void *X, int rows, int rows_pad, int K, hipStream_t st);
 
 // stream partials -> final ids / log-probabilities, with exact fp32 re-evaluation of uncertain ranks
-// nsr records per row (4, 2 or 1 for each of the gw column blocks of the head kernel's grid); unit: factor from the
+// nsr records per row (4, 2 or 1 for each of the gw column blocks of the head kernel's grid; resident: they are
+// head_resident_kernel's); unit: factor from the
 // records' values to natural-log logits; tiny_w: magnitude below which the kernel flushed weights to zero;
 // operand16: 0 the head kernel's row operand was exact, 1 it was t log2(e) rounded to bf16, 2 to f16 (the merge then
 // recomputes, from the same rounding, the logit the head kernel saw for a column that has no recorded value);
 // Mt: null, or the column-major copy of M, [V, K] (an exact logit then reads K adjacent elements; rows are not parked);
 // defer_buf: merge_defer_bytes(rows) of scratch, or null: with it, rows that need exact re-evaluations are finished by
 // two more launches that spread the column gathers over many CUs (worth it for long contractions only)
-hipError_t launch_merge_streams(const float *part, int rows, int nsr, int gw, int n_vt,
+hipError_t launch_merge_streams(const float *part, int rows, int nsr, int gw, int n_vt, bool resident,
                                 const void *xexact, bool x_is_bf16, int ldx, int operand16,
                                 const uint16_t *M, int K, int V, const uint16_t *Mt,
                                 const float2 *stat, int n_stat, int rows_pad, const float2 *tilescale, int k,

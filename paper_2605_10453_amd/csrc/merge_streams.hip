@@ -181,6 +181,7 @@ __device__ __forceinline__ int head_rank_share(const uint64_t *group, int part, 
 // for every stream whose best is within the rounding bound of the largest.
 __global__ __launch_bounds__(kMergeThreads) void merge_streams_kernel(
     const float *__restrict__ part, int rec_stride, int nsr, int gw, int n_vt,
+    int resident,       // 0: records of head_tile_kernel, 1: of head_resident_kernel
     const void *__restrict__ xexact, int x_is_bf16, int ldx,
     int operand16,      // 0: the head kernel's row operand was exact; 1: it was t log2(e) rounded to bf16; 2: to f16
     const uint16_t *__restrict__ M, int K, int V,
@@ -688,22 +689,33 @@ __global__ __launch_bounds__(kMergeThreads) void merge_streams_kernel(
 #pragma unroll
             for (int l = 0; l < L; ++l) listed[l] = (r[3 + 3 * l] > kNoValue) ? __float_as_int(r[5 + 3 * l]) : -1;
             const int spb = nsr / gw, col = sidx / spb, sub = sidx % spb;       // 4, 2 or 1 records per column block
-            const int n_tiles = (n_vt - col + gw - 1) / gw;
+            int n_e;                                          // columns the record covers
             const int per_tile = 256 / spb, sh = (spb == 4) ? 6 : (spb == 2) ? 7 : 8;
-            for (int e = tid; e < n_tiles * per_tile; e += NT) {
-                const int vt = col + (e >> sh) * gw, m = e & (per_tile - 1);
-                // spb 4: (column half, half-wavefront) = sub; 2: column half = sub, both half-wavefronts; 1: everything
-                const int half = (spb == 4) ? (sub & 1) : ((m >> 4) & 1);
-                const int j = (spb == 4) ? 4 * (sub >> 1) + ((m >> 4) & 3) : (spb == 2) ? 4 * sub + ((m >> 5) & 3) : ((m >> 5) & 7);
-                const int rawtag = (vt * 8 + j) * 2 + half;
+            if (!resident) n_e = (n_vt - col + gw - 1) / gw * per_tile;
+            else {
+                // 64-column tiles col, col + gw, ...: 32 columns of each belong to a half-wavefront's record
+                const int n_t = (V + kResidentTileCols - 1) / kResidentTileCols;
+                n_e = (n_t - col + gw - 1) / gw * 32;
+            }
+            for (int e0 = 0; e0 < n_e; e0 += NT) {            // (whole wavefronts: every lane takes part in the slot count)
+                const int e = e0 + tid;
+                int rawtag;
+                if (!resident) {
+                    const int vt = col + (e >> sh) * gw, m = e & (per_tile - 1);
+                    // spb 4: (column half, half-wavefront) = sub; 2: column half = sub, both half-wavefronts; 1: everything
+                    const int half = (spb == 4) ? (sub & 1) : ((m >> 4) & 1);
+                    const int j = (spb == 4) ? 4 * (sub >> 1) + ((m >> 4) & 3) : (spb == 2) ? 4 * sub + ((m >> 5) & 3) : ((m >> 5) & 7);
+                    rawtag = (vt * 8 + j) * 2 + half;
+                } else
+                    rawtag = ((col + (e >> 5) * gw) * 2 + ((e >> 4) & 1)) * 2 + sub;
                 bool is_listed = false;
 #pragma unroll
                 for (int l = 0; l < L; ++l) is_listed |= (listed[l] == rawtag);
                 const int id = id_of(rawtag >> 1, e & 15, rawtag & 1);
-                const bool take = !is_listed && id < V;           // (a wavefront's 64 values of e are all inside the range or all outside)
+                const bool take = e < n_e && !is_listed && id < V;
                 int n_taken;
                 const uint32_t slot = wave_slots(&cnt_work, take, n_taken);
-                if (take && slot < (uint32_t)kWorkCap) { w_id[slot] = id; w_val[slot] = 0.f; w_need[slot] = 1; w_apx[slot] = 0.f; w_eps[slot] = eps_of_tile(vt); }
+                if (take && slot < (uint32_t)kWorkCap) { w_id[slot] = id; w_val[slot] = 0.f; w_need[slot] = 1; w_apx[slot] = 0.f; w_eps[slot] = eps_of_tile(rawtag >> 4); }
                 if (lane == 0 && n_taken != 0) atomicAdd(&cnt_hidden, (uint32_t)n_taken);
             }
         }
@@ -1016,7 +1028,7 @@ size_t merge_streams_lds_bytes(int nsr, int k, int n_vt) {
            + sizeof(float) * (((size_t)(n_vt < kTsCap ? n_vt : kTsCap) + 3) & ~(size_t)3);
 }
 
-hipError_t launch_merge_streams(const float *part, int rows, int nsr, int gw, int n_vt,
+hipError_t launch_merge_streams(const float *part, int rows, int nsr, int gw, int n_vt, bool resident,
                                 const void *xexact, bool x_is_bf16, int ldx, int operand16,
                                 const uint16_t *M, int K, int V, const uint16_t *Mt,
                                 const float2 *stat, int n_stat, int rows_pad, const float2 *tilescale, int k,
@@ -1030,14 +1042,14 @@ hipError_t launch_merge_streams(const float *part, int rows, int nsr, int gw, in
     // sampling calls evaluate in place; with a column-major copy an exact logit is one short read: nothing to park
     int *defer = (so.on || Mt != nullptr) ? nullptr : static_cast<int *>(defer_buf);
     const int rec_stride = so.on ? kStreamRecSample : kStreamRec;
-    merge_streams_kernel<<<rows, kMergeThreads, lds, st>>>(part, rec_stride, nsr, gw, n_vt, xexact, x_is_bf16 ? 1 : 0, ldx,
+    merge_streams_kernel<<<rows, kMergeThreads, lds, st>>>(part, rec_stride, nsr, gw, n_vt, resident ? 1 : 0, xexact, x_is_bf16 ? 1 : 0, ldx,
                                                            operand16, M, K, V, Mt, stat, n_stat, rows_pad, tilescale, k, unit, tiny_w, out_ids, out_logprobs, id_map,
                                                            defer, 0, so, row_base);
     if ((e = hipGetLastError()) != hipSuccess || !defer) return e;
     // parked rows: their exact columns on many CUs, then the rest of their merge
     exact_cols_kernel<<<dim3(kDeferSlices, rows), 256, 0, st>>>(defer, xexact, x_is_bf16 ? 1 : 0, ldx, M, K, V);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    merge_streams_kernel<<<rows, kMergeThreads, lds, st>>>(part, rec_stride, nsr, gw, n_vt, xexact, x_is_bf16 ? 1 : 0, ldx,
+    merge_streams_kernel<<<rows, kMergeThreads, lds, st>>>(part, rec_stride, nsr, gw, n_vt, resident ? 1 : 0, xexact, x_is_bf16 ? 1 : 0, ldx,
                                                            operand16, M, K, V, Mt, stat, n_stat, rows_pad, tilescale, k, unit, tiny_w, out_ids, out_logprobs, id_map,
                                                            defer, 1, so, row_base);
     return hipGetLastError();

@@ -166,8 +166,30 @@ inline size_t down_part_tiles_bound(int rows, int r) {
     return tiles > 512 ? tiles : 512;
 }
 
+// ---- row operand resident in registers (head_resident.hip) -------------------------------------------------------
+constexpr int kResidentTileCols = 64;
+constexpr int kResidentMaxK = 512;       // 32 rows x 512 elements: 128 of a wavefront's 256 registers per lane
+// Blocks of n_rb row blocks (256 rows) x gw column blocks; n_t tiles of 64 columns; two records (half-wavefronts) per
+// block and row, of up to 32 groups at 128 column blocks.  (Four records of 16 groups each make a crowded record, i.e. an
+// exact rescan of its columns, eight times rarer, one 512-row call in a hundred at k = 10, but cost every call 4 us.)
+struct ResidentGrid { int n_rb = 1, gw = 8, n_t = 0, nsr = 0; };
+inline ResidentGrid make_resident_grid(int n_rb, int V) {
+    ResidentGrid g;
+    g.n_rb = n_rb;
+    g.n_t = (V + kResidentTileCols - 1) / kResidentTileCols;
+    int colgroups = kPlanSlotsPerXcd / n_rb;
+    if (colgroups < 1) colgroups = 1;
+    const int need = (g.n_t + 7) / 8;
+    if (colgroups > need) colgroups = need;
+    g.gw = 8 * colgroups;
+    g.nsr = 2 * g.gw;
+    return g;
+}
+
 struct MfmaPlan {
     int rows = 0, rows_pad = 0, rt = 0, n_rb = 0, gw = 0, nsr = 0, n_vt = 0;
+    bool resident = false;               // the row operand fits a wavefront's registers (bf16 operands)
+    ResidentGrid res;
     DownGrid down;
     size_t off_down_part = 0;            // fp32 [slices][n_rt][n_ct][4][16][64]: partial tiles of t (sized for any grouping of the rows)
     size_t off_t32 = 0;                  // fp32 [rows_pad, r]
@@ -205,7 +227,9 @@ inline MfmaPlan make_mfma_plan(HeadKind kind, int rows, int d, int r, int V) {
     } else {
         p.off_t16 = off;       off = align_up(off + 2 * (size_t)p.rows_pad * ((d + 63) / 64 * 64));      // h regrouped for the kernel
     }
-    p.off_streams = off;       off = align_up(off + sizeof(float) * (size_t)rows * p.nsr * kStreamRecPlan);
+    p.resident = kind == HeadKind::LowRank && p.rt == 256 && r <= kResidentMaxK && V <= (1 << 26);
+    if (p.resident) p.res = make_resident_grid(p.n_rb, V);
+    p.off_streams = off;       off = align_up(off + sizeof(float) * (size_t)rows * (p.nsr > p.res.nsr ? p.nsr : p.res.nsr) * kStreamRecPlan);
     p.defer = (kind == HeadKind::Full ? d : r) >= kDeferMinKFine;      // room for it; the call decides (merge_parks_rows)
     if (p.defer) { p.off_defer = off; off = align_up(off + merge_defer_bytes(rows)); }
     p.bytes = off;

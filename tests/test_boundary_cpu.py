@@ -107,11 +107,12 @@ def test_product_path_does_not_touch_the_checker():
             assert "paper_2605_10453_amd" not in text and "libslimspec" not in text
 
 
-@pytest.mark.parametrize("source,kernel", [("head_tile.hip", "head_tile_kernel"), ("merge_streams.hip", "merge_streams_kernel")])
+@pytest.mark.parametrize("source,kernel", [("head_tile.hip", "head_tile_kernel"), ("merge_streams.hip", "merge_streams_kernel"),
+                                           ("head_resident.hip", "head_resident_kernel")])
 def test_kernels_use_no_scratch_memory(source, kernel):
-    """head_tile_kernel counts its own vector-memory loads (s_waitcnt vmcnt(N)); a register spill would add
+    """head_tile_kernel and head_resident_kernel count their own vector-memory loads (s_waitcnt vmcnt(N)); a register spill would add
     loads the count does not know about.  merge_streams_kernel once kept a small array in scratch memory, which
-    cost 12 MB of writes per 512-row call.  The compiler must report no scratch for every instance of either."""
+    cost 12 MB of writes per 512-row call.  The compiler must report no scratch for every instance of them."""
     import shutil
     import subprocess
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

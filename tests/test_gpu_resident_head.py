@@ -1,0 +1,42 @@
+"""The head kernel with the row operand in registers (csrc/head_resident.hip: more than 128 rows, r <= 512) against the CPU
+fp64 checker, at the edges of its tiles: 256-row blocks, 64-column tiles, stages of 128 contraction elements, column
+blocks with one tile or none; and the rescan of a record whose stream dropped a candidate."""
+import numpy as np
+import pytest
+
+from paper_2605_10453_amd import synth
+from test_gpu_parity import check_low_rank, gpu  # noqa: F401  (the module's fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+# contractions of one to four stages, full and ragged; vocabularies of one tile, ragged last tiles, odd and even tile counts
+@pytest.mark.parametrize("rows,d,r,V,k", [
+    (129, 64, 8, 8, 3), (200, 64, 72, 72, 10), (256, 96, 128, 1000, 12), (257, 64, 136, 8200, 10), (300, 128, 256, 4104, 1),
+    (513, 64, 264, 2056, 6), (140, 256, 384, 16392, 10), (512, 128, 392, 16456, 7), (260, 512, 512, 32840, 12), (130, 64, 512, 70008, 5),
+])
+def test_tile_edges(gpu, oracle_mod, rows, d, r, V, k):
+    x = synth.make_inputs(synth.small_config(rows, d, r, V, k, peaked_every=6), seed=rows + r)
+    check_low_rank(gpu, oracle_mod, x, k)
+
+
+@pytest.mark.parametrize("rows,V", [(300, 40960), (200, 70016)])
+def test_four_best_logits_in_one_stream(gpu, oracle_mod, rows, V):
+    """A stream is a half-wavefront's share of the 64-column tiles col, col + gw, ... (gw = 128 column blocks for two row
+    blocks, 256 for one).  A row's four largest logits sit in four groups of 16 of one stream, one more than it lists."""
+    gw = 128 if rows > 256 else 256
+    cfg = synth.small_config(rows=rows, d=64, r=64, V=V, k=5)
+    x = synth.make_inputs(cfg, seed=rows + V)
+    t = synth.bf16_bits_to_f64(x.h) @ synth.bf16_bits_to_f64(x.A)
+    B = synth.bf16_bits_to_f32(x.B)
+    planted = {}
+    for n, i in enumerate((0, 9, rows - 1)):
+        col = 3 + 5 * n
+        cols = [64 * (col + gw * tile) + 32 * jj + 4 for tile in (1, 2) for jj in (0, 1)]      # + 4: the upper half-wavefront
+        for c, alpha in zip(cols, (12.0, 11.5, 11.0, 10.5)):
+            B[:, c] = (alpha * t[i] / (t[i] @ t[i])).astype(np.float32)
+        planted[i] = cols
+    x.B = synth.f32_to_bf16_bits(B)
+    g_ids, _, _, _ = check_low_rank(gpu, oracle_mod, x, cfg.k, exact_rows=list(planted))
+    for i, cols in planted.items():
+        assert g_ids[i, :4].tolist() == cols, (i, g_ids[i], cols)
