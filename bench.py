@@ -243,7 +243,8 @@ def main():
                    "mfma_frac_same_kernel": mfma / MFMA_PEAK_TFLOPS}
         out.update({"traffic": measured_traffic(name),
                     "kernel": "vocabulary projection + running log-sum-exp / top-k "
-                              + ("(head_tile_kernel)" if rows > GEMV_MAX_ROWS else "(stream_topk_kernel)"),
+                              + ("(stream_topk_kernel)" if rows <= 2 else "(rows_topk_kernel)" if rows <= 48 else
+                                 "(head_resident_kernel)" if rows > 128 and K <= 512 else "(head_tile_kernel)"),
                     "kernel_us": kern_ms * 1e3,
                     "kernel_us_minus_empty_event_pair": (kern_ms - null_ms) * 1e3,
                     "empty_event_pair_us": null_ms * 1e3,

@@ -23,7 +23,7 @@
 // (global_load_lds_dwordx4), eight stage buffers.  The 16-byte pieces of a 128-byte stage row are stored XOR-swizzled by
 // twice (row mod 4), so that the four rows of a transposing read (ds_read_b64_tr_b16) fall into different banks.
 // The compiler does not see these loads: every wavefront issues exactly two per stage, vector memory returns in order,
-// and "s_waitcnt vmcnt(2 (NB - 3))" means that the stage needed next has landed.  Nothing else in the loop may use
+// and "s_waitcnt vmcnt(N)" means that the stages needed next have landed (see do_tile).  Nothing else in the loop may use
 // vector memory: the kernel must not spill.
 #include "head_stream.hpp"
 #include "launch.hpp"
