@@ -324,8 +324,9 @@ __device__ __forceinline__ void merge_row(unsigned char *dyn, bool cache_ids, Me
     for (int c = tid; c < chunks; c += NT) {
         const bool first = c == tid;
         heads[c] = make_key(first ? head0 : pv[(size_t)c * k], (uint32_t)(c * k));
-        float2 p = first ? ms0 : ms[c];
-        float m_new = fmaxf(m_t, p.x);
+        const float2 p = first ? ms0 : ms[c];
+        if (p.x == kNegInf) continue;                   // no logit above -inf: nothing to add (its sum is not a number)
+        const float m_new = fmaxf(m_t, p.x);
         s_t = s_t * fast_exp(m_t - m_new) + p.y * fast_exp(p.x - m_new);
         m_t = m_new;
     }
@@ -385,9 +386,13 @@ __device__ __forceinline__ void merge_row(unsigned char *dyn, bool cache_ids, Me
     for (int c = tid; c < chunks; c += NT) {
         if (heads[c] < bound) continue;
         for (int p = 0; p < k; ++p) {
-            const float v = vals[c * k + p];
-            const uint64_t key = make_key(v, (uint32_t)(c * k + p));
-            if (v == kNegInf || key < bound) break;     // lists are sorted
+            const int e = c * k + p;
+            const float v = vals[e];
+            const uint64_t key = make_key(v, (uint32_t)e);
+            if (key < bound) break;                     // lists are sorted
+            // what fills up the list of a chunk of fewer than k columns has no id; a logit of -inf has one, and is wanted
+            // where the row has fewer than k logits above it
+            if (v == kNegInf && (cache_ids ? ids[e] : pi[e]) == kNoId) break;
             cand[atomicAdd(&S.cnt, 1u)] = key;
         }
     }
@@ -402,7 +407,7 @@ __device__ __forceinline__ void merge_row(unsigned char *dyn, bool cache_ids, Me
         if (rank < k) S.winners[rank] = key_tiebreak(mine);
     }
     __syncthreads();
-    if (tid < k) {                                      // n_cand >= k whenever k <= V
+    if (tid < k) {                                      // n_cand >= k: k heads, or (fewer lists) every column of lists that hold min(k, columns) each
         const uint32_t e = S.winners[tid];
         const int id = cache_ids ? ids[e] : pi[e];
         out_ids[tid] = id_map ? id_map[id] : id;                // truncated vocabulary: column -> vocabulary id
