@@ -324,9 +324,11 @@ __global__ __launch_bounds__(kMergeThreads) void merge_streams_kernel(
             const uint64_t thr = thr_key;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const float m_new = fmaxf(em, z[e]);
-                es = es * fast_exp(em - m_new) + fast_exp(z[e] - m_new);
-                em = m_new;
+                if (!(z[e] == kNegInf && em == kNegInf)) {     // (-inf - -inf is not a number)
+                    const float m_new = fmaxf(em, z[e]);
+                    es = es * fast_exp(em - m_new) + fast_exp(z[e] - m_new);
+                    em = m_new;
+                }
                 const uint64_t key = make_key(z[e], (uint32_t)(col + e));
                 if (key > thr) work[atomicAdd(&cnt_buf, 1u)] = key;     // at most k + 4 NT = kExhaustCap entries: fits
                 if (so.on) {

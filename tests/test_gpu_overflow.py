@@ -15,7 +15,6 @@ D = 64
 # logits of the finite columns are below 16 in magnitude and summed in fp32 from exact products (t: 64 products first);
 # 2^-20 is half a step of fp32 there, 64 of them cover both sums and the log-sum-exp
 FP32_TOL = 64 * 2.0 ** -20
-BF16_T_TOL = 2e-2               # more than 48 rows: the suite's bar for a 16-bit t
 
 
 def _inputs(rows, V, n_finite, seed):
@@ -55,6 +54,18 @@ def test_full_head(gpu, rows, V, k, n_finite):
     ids, lp = b.full_head_topk(to_dev_bf16(h), to_dev_bf16(W), k)
     torch.cuda.synchronize()
     _check(ids.cpu().numpy(), lp.cpu().numpy(), h, W, finite, k, FP32_TOL)
+
+
+@pytest.mark.parametrize("rows,V,k,n_finite", [(64, 16, 16, 5), (64, 16392, 10, 2), (130, 4104, 16, 3)])
+def test_both_heads_above_48_rows(gpu, rows, V, k, n_finite):
+    """The stream records' merge: it finds its bound infinite and evaluates every logit of the row in fp32."""
+    torch, b = gpu
+    h, M, finite = _inputs(rows, V, n_finite, seed=rows + V)
+    A = to_dev_bf16(synth.f32_to_bf16_bits(np.eye(D, dtype=np.float32)))       # t = h
+    hd, Md = to_dev_bf16(h), to_dev_bf16(M)
+    for ids, lp in (b.full_head_topk(hd, Md, k), b.slimspec_head_topk(hd, A, Md, k)):
+        torch.cuda.synchronize()
+        _check(ids.cpu().numpy(), lp.cpu().numpy(), h, M, finite, k, FP32_TOL)
 
 
 def test_fp32_weights(gpu):
