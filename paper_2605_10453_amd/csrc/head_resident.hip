@@ -54,6 +54,7 @@ __device__ __forceinline__ void dma16(uint32_t buf, uint32_t voff, const void *b
 }
 template <int N>
 __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory"); }
+__device__ __forceinline__ void wait_lds_reads() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 template <int N> using Int = std::integral_constant<int, N>;
 
 // calls f(Int<B>{}), ..., f(Int<E - 1>{})
@@ -265,10 +266,12 @@ __global__ __launch_bounds__(512, 2) void head_resident_kernel(
                     __builtin_bit_cast(bf16x8, xr[k]), c, 0, 0, 0);
                 constexpr bool stage_end = ks == 8 - kAhead && jj == 0;
                 if constexpr (stage_end && ((k >> 3) + 1) % SYNC == 0) {
-                    // The next SYNC stages have landed, in every wavefront's share (stage q ends here; up to stage
-                    // q + kRNB - 1 - SYNC is asked for, q + SYNC is needed); and every wavefront is past its last read of
-                    // the SYNC stages before this one, whose buffers are loaded again.
-                    wait_loads<(kRNB - 1 - 2 * SYNC) * kRLoads>();
+                    // The next SYNC stages have landed, in every wavefront's share: stage q ends here, up to stage
+                    // q + kRNB - 2 is asked for (with either SYNC), q + SYNC is needed.  And every wavefront's reads of
+                    // stage q have returned, the fragment of the MFMA after this one included: until the next barrier the
+                    // buffers of stages q - 1 (SYNC 1) or q - 1 and q (SYNC 2) are loaded again.
+                    wait_loads<(kRNB - 2 - SYNC) * kRLoads>();
+                    wait_lds_reads();
                     __builtin_amdgcn_s_barrier();
                 }
                 if constexpr (stage_end) {

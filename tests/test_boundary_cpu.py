@@ -132,6 +132,36 @@ def test_kernels_use_no_scratch_memory(source, kernel):
     assert all(sz == 0 for _, sz in found), found
 
 
+@pytest.mark.parametrize("source,kernel", [("head_resident.hip", "head_resident_kernel"), ("head_tile.hip", "head_tile_kernel")])
+def test_no_shared_memory_read_is_in_flight_at_a_barrier(source, kernel):
+    """After a barrier of these kernels stage buffers are loaded again by wavefronts that do not know of the others' reads:
+    a wavefront's own reads must have returned before it reaches the barrier.  Counted in the assembly of every instance
+    (two reads were in flight at the resident kernel's barriers before it waited for them)."""
+    import shutil
+    import subprocess
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    if not (os.path.exists(hipcc) or shutil.which(hipcc)):
+        pytest.skip("hipcc not available")
+    from paper_2605_10453_amd import build as build_mod
+    flags = [f for f in build_mod.HIPCC_FLAGS if f not in ("-shared", "-fPIC")]
+    out = subprocess.run([hipcc, *flags, "--cuda-device-only", "-S", os.path.join(build_mod.CSRC, source), "-o", "-"],
+                         capture_output=True, text=True)
+    assert out.returncode == 0, out.stderr[-2000:]
+    function, in_flight, found = "", 0, []
+    for line in out.stdout.splitlines():
+        label = re.match(r"(_ZN\S+):", line)
+        wait = re.match(r"\s+s_waitcnt\b.*lgkmcnt\((\d+)\)", line)
+        if label:
+            function, in_flight = label.group(1), 0
+        elif wait:
+            in_flight = min(in_flight, int(wait.group(1)))
+        elif re.match(r"\s+ds_read", line):
+            in_flight += 1
+        elif re.match(r"\s+s_barrier", line) and kernel in function:
+            found.append((function, in_flight))
+    assert len(found) > 4 and all(n == 0 for _, n in found), found
+
+
 def test_workspace_check_covers_every_batch_of_a_call(lib):
     """Calls with more than 512 rows run in batches that reuse the workspace; the last batch has a plan of its own
     (fewer row blocks, more slices of d) that can need more room than the first.  The size the call checks must be
