@@ -96,8 +96,8 @@ __global__ __launch_bounds__(512, 2) void head_resident_kernel(
     if (n_tiles > 0) {
         // ---- direct-to-LDS loads.  Load u of this wavefront: stage rows 16 wave + 8 u + lane / 8; stored piece lane % 8
         // holds source piece (lane % 8) ^ 2 (row % 4).  A lane's byte offsets from the stage's corner are kept in
-        // registers (V <= 2^26: 127 rows fit 32 bits), so that a stage costs few scalar instructions: with one wavefront
-        // per SIMD they take issue slots from everything else.
+        // registers, so that a stage costs few scalar instructions, which take issue slots from everything else.
+        static_assert((uint64_t)kRStageK * 2u * kResidentMaxV <= (uint64_t)1 << 32, "a stage's offsets fit 32 bits");
         const uint32_t rowb = (uint32_t)V * 2u;
         const uint32_t src_piece = (uint32_t)((lane & 7) ^ (((lane >> 3) & 3) << 1)) * 16u;
         uint32_t voff[kRLoads];

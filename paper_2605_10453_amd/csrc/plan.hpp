@@ -169,6 +169,7 @@ inline size_t down_part_tiles_bound(int rows, int r) {
 // ---- row operand resident in registers (head_resident.hip) -------------------------------------------------------
 constexpr int kResidentTileCols = 64;
 constexpr int kResidentMaxK = 512;       // 32 rows x 512 elements: 128 of a wavefront's 256 registers per lane
+constexpr int kResidentMaxV = 1 << 24;   // the kernel's 32-bit offsets reach over the 128 rows of a stage of the weights
 // Blocks of n_rb row blocks (256 rows) x gw column blocks; n_t tiles of 64 columns; two records (half-wavefronts) per
 // block and row, of up to 32 groups at 128 column blocks.  (Four records of 16 groups each make a crowded record, i.e. an
 // exact rescan of its columns, eight times rarer, one 512-row call in a hundred at k = 10, but cost every call 4 us.)
@@ -227,7 +228,7 @@ inline MfmaPlan make_mfma_plan(HeadKind kind, int rows, int d, int r, int V) {
     } else {
         p.off_t16 = off;       off = align_up(off + 2 * (size_t)p.rows_pad * ((d + 63) / 64 * 64));      // h regrouped for the kernel
     }
-    p.resident = kind == HeadKind::LowRank && p.rt == 256 && r <= kResidentMaxK && V <= (1 << 26);
+    p.resident = kind == HeadKind::LowRank && p.rt == 256 && r <= kResidentMaxK && V <= kResidentMaxV;
     if (p.resident) p.res = make_resident_grid(p.n_rb, V);
     p.off_streams = off;       off = align_up(off + sizeof(float) * (size_t)rows * (p.nsr > p.res.nsr ? p.nsr : p.res.nsr) * kStreamRecPlan);
     p.defer = (kind == HeadKind::Full ? d : r) >= kDeferMinKFine;      // room for it; the call decides (merge_parks_rows)

@@ -42,7 +42,8 @@ int check_shape(HeadKind kind, const slimspec_shape *s, int32_t k)
     if ((s->d & 7) || (s->V & 7)) return SLIMSPEC_UNSUPPORTED;
     if (kind == HeadKind::LowRank && (s->r & 7)) return SLIMSPEC_UNSUPPORTED;
     // Index arithmetic inside the kernels: 32-bit ids, 64-bit base addresses, 32-bit lane offsets of a few rows of a
-    // weight matrix (up to four rows of V bf16 values) and of an element of A (d * r).
+    // weight matrix (up to four rows of V bf16 values; head_resident_kernel, which needs 128, has a limit of its own:
+    // kResidentMaxV) and of an element of A (d * r).
     if ((int64_t)s->V > (int64_t)1 << 28) return SLIMSPEC_UNSUPPORTED;
     if (kind == HeadKind::LowRank && (int64_t)s->d * s->r >= (int64_t)1 << 31) return SLIMSPEC_UNSUPPORTED;
     // ... and of a row of h inside one launch's 512 rows, and of 32 rows of A (the many-row down-projection)
