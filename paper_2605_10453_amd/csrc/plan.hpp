@@ -230,7 +230,9 @@ inline MfmaPlan make_mfma_plan(HeadKind kind, int rows, int d, int r, int V) {
     }
     p.resident = kind == HeadKind::LowRank && p.rt == 256 && r <= kResidentMaxK && V <= kResidentMaxV;
     if (p.resident) p.res = make_resident_grid(p.n_rb, V);
-    p.off_streams = off;       off = align_up(off + sizeof(float) * (size_t)rows * (p.nsr > p.res.nsr ? p.nsr : p.res.nsr) * kStreamRecPlan);
+    // (room for the records of one row block, the most a row has: a workspace then serves fewer rows as well)
+    const int nsr_res = p.resident ? make_resident_grid(1, V).nsr : 0;
+    p.off_streams = off;       off = align_up(off + sizeof(float) * (size_t)rows * (p.nsr > nsr_res ? p.nsr : nsr_res) * kStreamRecPlan);
     p.defer = (kind == HeadKind::Full ? d : r) >= kDeferMinKFine;      // room for it; the call decides (merge_parks_rows)
     if (p.defer) { p.off_defer = off; off = align_up(off + merge_defer_bytes(rows)); }
     p.bytes = off;

@@ -312,8 +312,11 @@ size_t head_workspace_bytes(HeadKind kind, const slimspec_shape *shape, int32_t 
         const size_t m = mfma_workspace_bytes(kind, shape);
         if (m > need) need = m;
     }
-    if (rows_path_takes(kind, shape, k)) {
-        const size_t w = rows_workspace_bytes(kind, shape, k);
+    // (also where only a call of fewer rows takes that path: a workspace serves fewer rows as well)
+    slimspec_shape fewer = *shape;
+    if (fewer.rows > kRowsMaxRows) fewer.rows = kRowsMaxRows;
+    if (rows_path_takes(kind, &fewer, k)) {
+        const size_t w = rows_workspace_bytes(kind, &fewer, k);
         if (w > need) need = w;
     }
     return need;
