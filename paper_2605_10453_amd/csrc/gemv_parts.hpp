@@ -266,6 +266,7 @@ __device__ __forceinline__ void chunk_row_epilogue(ChunkLds<R, NW> &L, int i, in
 //   (1) the k-th largest list head (by all-pairs counting) bounds the answer from below;
 //   (2) the entries that reach the bound (at most k lists, k entries each) are gathered;
 //   (3) they are ranked among themselves by counting; ranks below k are the output.
+// last_len: columns in the last chunk's list (the others hold k).
 // NT threads (a multiple of 64, at most 1024) call together; `dyn` holds merge_lds_bytes(chunks, k, cache_ids).
 struct MergeSmall {
     float red_m[16], red_s[16];
@@ -279,7 +280,7 @@ struct MergeSmall {
 template <int NT>
 __device__ __forceinline__ void merge_row(unsigned char *dyn, bool cache_ids, MergeSmall &S, int tid,
                                           const float2 *__restrict__ ms, const float *__restrict__ pv,
-                                          const int *__restrict__ pi, int chunks, int k,
+                                          const int *__restrict__ pi, int chunks, int k, int last_len,
                                           int32_t *__restrict__ out_ids, float *__restrict__ out_logprobs,
                                           const int32_t *__restrict__ id_map,
                                           const float4 *__restrict__ smp, float *__restrict__ out_lse,
@@ -385,14 +386,12 @@ __device__ __forceinline__ void merge_row(unsigned char *dyn, bool cache_ids, Me
     // (2) gather what reaches the bound
     for (int c = tid; c < chunks; c += NT) {
         if (heads[c] < bound) continue;
-        for (int p = 0; p < k; ++p) {
-            const int e = c * k + p;
-            const float v = vals[e];
-            const uint64_t key = make_key(v, (uint32_t)e);
+        // (only the last chunk can have fewer than k columns, and filler at the end of its list: a logit of -inf is an
+        // entry like any other, wanted where the row has fewer than k logits above it)
+        const int len = c == chunks - 1 ? last_len : k;
+        for (int p = 0; p < len; ++p) {
+            const uint64_t key = make_key(vals[c * k + p], (uint32_t)(c * k + p));
             if (key < bound) break;                     // lists are sorted
-            // what fills up the list of a chunk of fewer than k columns has no id; a logit of -inf has one, and is wanted
-            // where the row has fewer than k logits above it
-            if (v == kNegInf && (cache_ids ? ids[e] : pi[e]) == kNoId) break;
             cand[atomicAdd(&S.cnt, 1u)] = key;
         }
     }

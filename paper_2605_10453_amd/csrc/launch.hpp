@@ -58,9 +58,10 @@ struct SampleOut {
 };
 
 // id_map (may be null): the vocabulary id of every column, for heads over a kept subset of the vocabulary
-// part_smp [rows, chunks]: the chunks' Gumbel-max winners (when so.on)
+// part_smp [rows, chunks]: the chunks' Gumbel-max winners (when so.on); chunk_cols: columns per chunk (at least KMAX; the
+// last chunk has what is left of V)
 hipError_t launch_merge(const float2 *part_ms, const float *part_val, const int *part_id,
-                        int rows, int chunks, int k, int32_t *out_ids, float *out_logprobs, const int32_t *id_map,
+                        int rows, int chunks, int chunk_cols, int V, int k, int32_t *out_ids, float *out_logprobs, const int32_t *id_map,
                         const SampleOut &so, const float4 *part_smp, hipStream_t st);
 
 // ---- matrix-core path (rows > kGemvMaxRows, bf16 weights) ----

@@ -227,7 +227,7 @@ int run_head_rows(HeadKind kind, const void *h, const void *A, const void *M, co
         if (timed && (e = hipEventRecord(g_ev_stop, s)) != hipSuccess) return fail_hip(e);
         SampleOut so_rows = so;
         if (so.on) { so_rows.lse += row0; so_rows.sample_ids += row0; so_rows.sample_logprobs += row0; }
-        e = launch_merge(ms, pv, pi, rows, p.geom.chunks, k, out_ids + (size_t)row0 * k, out_logprobs + (size_t)row0 * k, id_map, so_rows, smp, s);
+        e = launch_merge(ms, pv, pi, rows, p.geom.chunks, 128 * p.geom.G, V, k, out_ids + (size_t)row0 * k, out_logprobs + (size_t)row0 * k, id_map, so_rows, smp, s);
         if (e != hipSuccess) return fail_hip(e);
     }
     return SLIMSPEC_OK;
@@ -288,7 +288,7 @@ int run_head(HeadKind kind, const void *h, const void *A, const void *M, bool m_
         if (e != hipSuccess) return fail_hip(e);
         if (timed && (e = hipEventRecord(g_ev_stop, s)) != hipSuccess) return fail_hip(e);
     }
-    hipError_t e = launch_merge(part_ms, part_val, part_id, p.rows, p.chunks, k, out_ids, out_logprobs, id_map, so, part_smp, s);
+    hipError_t e = launch_merge(part_ms, part_val, part_id, p.rows, p.chunks, 8 * p.lanes, p.V, k, out_ids, out_logprobs, id_map, so, part_smp, s);
     if (e != hipSuccess) return fail_hip(e);
     return SLIMSPEC_OK;
 }
