@@ -300,4 +300,58 @@ inline RowsPlan make_rows_plan(HeadKind kind, int rows, int d, int r, int V, int
     return p;
 }
 
+// ---- which kernels a call runs ------------------------------------------------------------------------------------
+constexpr int kMfmaMaxK = 16;            // the lane streams keep 3 groups: enough for k <= 16 (larger k: rows_head.hip)
+constexpr int kMfmaMinRows = 5;          // below, rows whose calls rows_path_takes leaves are streamed in lock step
+constexpr int64_t kRowsMinWeights = 12 << 20;
+
+// Few rows, or lists longer than the lane streams keep (rows_head.hip); the rest is tile_path_takes's or streamed.
+// Where the lines lie (us per call at d = 4096, r = 512, V = 128256 unless said otherwise; the other path's time first,
+// this one's second):
+//   * k > kMfmaMaxK: always; the lane-owns-columns kernel reads the weights once per 8 rows (40 rows, k = 32: 420 / 61).
+//   * 3 and 4 rows, low-rank: the streaming kernel needs no kernel that finishes t.  It is ahead up to 256 chunks of 512
+//     columns (one round of its blocks) while r is small: r = 256 27.4 / 29.0, 384 34.6 / 35.2, 448 39.6 / 38.2, 512
+//     47.0 / 42.3; r = 256, V = 64000 24.9 / 25.6; beyond 256 chunks (V = 151936) r = 128 29.7 / 24.8, r = 512 71 / 45.  Small
+//     weights: r = 200, V = 32000 20.6 / 22.6, r = 512, V = 32000 33.6 / 27.4.  Two rows: 39.3 / 41.9.
+//   * full head, from 2 rows: 188.9 / 185.3; d = 1024, V = 8192 24.3 / 17.8.  Two rows with d = 256, V = 32000: 15.7 / 16.4.
+//   * up to 32 rows, k <= kMfmaMaxK: 23 rows 58.0 / 48.7; with prepared weights 24 rows 51.2 / 48.5, 32 rows 51.9 / 50.8.
+//   * about 32 to 48 rows: a wavefront finishes up to six rows after the weights, which a short contraction does not pay
+//     for, while head_tile_kernel's cost stays the same and its merge is cheap with prepared weights or small k.
+//       prepared: 33 rows 51.0 / 54.4, 48 rows 51.5 / 58.9 (r = 1024: 76.8 / 84.1); this kernel only where few tiles of the
+//         vocabulary leave head_tile_kernel long contractions on few CUs (48 rows, r = 2048: V = 32000 74 / 68, V = 8192 68 / 53);
+//       plain low-rank calls stay, and with them their fp32 t: 48 rows, k = 10 0.99 to 1.4 times as fast; with k = 3 and r = 256
+//         they give up a little (40 rows, V = 8192 30.9 / 33.1, 48 rows, V = 32000 34.1 / 36.9);
+//       full head, k = 4, 48 rows: d = 256 22.7 / 28.8 at V = 32000, 30.0 / 34.4 at V = 128256; d = 1024 41.8 / 36.0 and 67.3 / 66.3.
+//         Up to d = 768 behind for k <= 6 unless V is small, at k = 10 (more re-evaluations) only with d <= 512 and a large V.
+//     Sampling calls stay: the noise is dearer in head_tile_kernel (r = 64, V = 8192, 48 rows 47.2 / 33.4).
+//   * more rows would need a second launch, and lose.
+inline bool rows_path_takes(HeadKind kind, int rows, int d, int r, int V, int k, bool prepared, bool sampling) {
+    const bool low_rank = kind == HeadKind::LowRank;
+    if (rows < 2 || !rows_path_fits(kind, d, r)) return false;
+    if (low_rank && rows <= 4)
+        return rows > 2 && (int64_t)r * V >= kRowsMinWeights && (V > 256 * kChunkCols || r > 384);
+    if (k > kMfmaMaxK) return true;
+    if (!low_rank && rows == 2) return d > 256;
+    if (rows > kRowsMaxRows) return false;
+    if (rows < 32 || sampling) return true;
+    if (!low_rank) return !(d <= 768 && V >= 16 * d && k <= 6) && !(d <= 512 && V >= 100 * d && k <= 10);
+    return rows == 32 || !prepared || (r >= 1024 && V <= 16 * r);
+}
+
+inline bool tile_path_takes(int rows, int k) { return rows >= kMfmaMinRows && k <= kMfmaMaxK; }
+
+// The direct-to-LDS kernel takes bf16 operands as they are, or turns the weight tiles into f16 inside LDS and takes an f16
+// t (8 times finer).  The conversion costs the projection kernel about 12 %; the finer operand saves most of the merge's
+// exact re-evaluations, which grow with k: measured break-even at k = 10, 5-9 % of the call in favour of f16 at k = 16.
+// With a column-major copy the re-evaluations cost little: bf16 as it is.
+inline bool tile_operand_f16(int k, bool prepared) {
+#ifdef SLIMSPEC_DIAG_OPERAND_F16      // experiment builds only: force the operand mode (1 f16, 0 bf16)
+    return SLIMSPEC_DIAG_OPERAND_F16 != 0 && !prepared;
+#endif
+    return k > 12 && !prepared;
+}
+
+// head_resident_kernel instead of head_tile_kernel: bf16 operands, no noise.
+inline bool resident_takes(const MfmaPlan &p, bool f16_operand, bool sampling) { return p.resident && !f16_operand && !sampling; }
+
 }  // namespace slimspec

@@ -7,7 +7,6 @@
 #include <atomic>
 
 using namespace slimspec;
-namespace slimspec { bool head_tile_f16(int k); }
 
 namespace {
 
@@ -52,10 +51,6 @@ int check_shape(HeadKind kind, const slimspec_shape *s, int32_t k)
     if (merge_lds_bytes(chunks, k) > kMergeLdsLimit) return SLIMSPEC_UNSUPPORTED;
     return SLIMSPEC_OK;
 }
-
-constexpr int kMfmaMaxK = 16;      // the lane streams keep 3 groups: enough for k <= 16 (larger k: rows_head.hip)
-constexpr int64_t kRowsMinWeights = 12 << 20;      // (see rows_path_takes)
-constexpr int kMfmaMinRows = 5;    // below, rows whose calls rows_path_takes leaves are streamed in lock step
 
 // The launches of one call share the workspace in stream order; a last, smaller batch has a plan of its own
 // (fewer row blocks, more slices of d), so the call needs the larger of the two plans.
@@ -138,13 +133,12 @@ int run_head_mfma(HeadKind kind, const void *h, const void *A, const void *M, co
             void *t16 = ws + p.off_t16;
             float2 *stat = reinterpret_cast<float2 *>(ws + p.off_stat);
             float2 *tilescale = reinterpret_cast<float2 *>(ws + p.off_tilescale);
-            // (with a column-major copy the re-evaluations the finer operand saves cost little: bf16 as it is)
-            const bool tile_f16 = head_tile_f16(k) && Mtb == nullptr;
+            const bool tile_f16 = tile_operand_f16(k, Mtb != nullptr);
             e = launch_down_projection_tiles(hrow, static_cast<const uint16_t *>(A), reinterpret_cast<float *>(ws + p.off_down_part), p.down,
                                              p.rows_pad, d, r, t32, t16, stat, Mb, V, tilescale, tile_f16, s);
             if (e != hipSuccess) return fail_hip(e);
             if (timed && (e = hipEventRecord(g_ev_start, s)) != hipSuccess) return fail_hip(e);
-            const bool resident = p.resident && !tile_f16 && !so.on;
+            const bool resident = resident_takes(p, tile_f16, so.on != 0);
             e = resident ? launch_head_resident(t16, Mb, streams, rows, p.rows_pad, r, V, p.res, s)
                          : launch_head_tile(t16, tile_f16, false, Mb, streams, rows, p.rows_pad, r, V, p.n_rb, p.gw, so, row0, s);
             if (e != hipSuccess) return fail_hip(e);
@@ -173,22 +167,7 @@ int run_head_mfma(HeadKind kind, const void *h, const void *A, const void *M, co
     return SLIMSPEC_OK;
 }
 
-// Few rows, or lists longer than the lane streams keep: every launch reads the weights once for up to kRowsMaxRows
-// rows (rows_head.hip).  Where the lines lie (us per call at d = 4096, r = 512, V = 128256 unless said otherwise):
-//   * k > kMfmaMaxK: always; the lane-owns-columns kernel reads the weights once per 8 rows (40 rows, k = 32: 420 -> 61).
-//   * up to 48 rows, k <= kMfmaMaxK: 5 rows 57.6 -> 43.3, 23 rows 58.0 -> 48.7, 48 rows 61.0 -> 60.0 (d = 8192, r = 1024:
-//     97.7 -> 87.1) against head_tile_kernel and its merge; a second launch, beyond 48 rows, loses.
-//   * from 3 rows: 48.0 -> 42.7.  Two rows are faster on the lane-owns-columns kernel (39.3 against 41.9: it needs no
-//     kernel that finishes t), and so are 3 and 4 rows on small weights (4 rows, r = 200: V = 32000 20.6 against 22.6,
-//     V = 64000 24.1 / 24.1; r = 512, V = 32000 33.6 -> 26.4).
-//   * the full head has no t to finish: from 2 rows (188.9 -> 185.3; 4 rows, d = 1024, V = 16000: 33.6 -> 21.2).
-bool rows_path_takes(HeadKind kind, const slimspec_shape *s, int32_t k)
-{
-    if (s->rows < 2 || !rows_path_fits(kind, s->d, s->r)) return false;
-    if (kind == HeadKind::LowRank && (s->rows == 2 || (s->rows <= 4 && (int64_t)s->r * s->V < kRowsMinWeights))) return false;
-    return k > kMfmaMaxK || s->rows <= kRowsMaxRows;
-}
-
+// Every launch reads the weights once for up to kRowsMaxRows rows (rows_head.hip; rows_path_takes says which calls come here).
 size_t rows_workspace_bytes(HeadKind kind, const slimspec_shape *s, int32_t k)
 {
     return make_rows_plan(kind, s->rows < kRowsMaxRows ? s->rows : kRowsMaxRows, s->d, s->r, s->V, k).bytes;
@@ -247,10 +226,9 @@ int run_head(HeadKind kind, const void *h, const void *A, const void *M, bool m_
     if ((reinterpret_cast<uintptr_t>(out_ids) & 3u) || (reinterpret_cast<uintptr_t>(out_logprobs) & 3u))
         return SLIMSPEC_UNSUPPORTED;
     if (so.on && (!so.lse || !so.sample_ids || !so.sample_logprobs)) return SLIMSPEC_INVALID_ARGUMENT;
-    if (!m_is_f32 && rows_path_takes(kind, shape, k))
+    if (!m_is_f32 && rows_path_takes(kind, shape->rows, shape->d, shape->r, shape->V, k, Mt != nullptr, so.on != 0))
         return run_head_rows(kind, h, A, M, shape, k, out_ids, out_logprobs, id_map, pos, so, workspace, workspace_bytes, stream);
-    const bool use_mfma = shape->rows >= kMfmaMinRows && !m_is_f32 && k <= kMfmaMaxK;
-    if (use_mfma)
+    if (!m_is_f32 && tile_path_takes(shape->rows, k))
         return run_head_mfma(kind, h, A, M, Mt, shape, k, out_ids, out_logprobs, id_map, pos, so, workspace, workspace_bytes, stream);
     const Plan p = make_plan(kind, shape->rows, shape->d, shape->r, shape->V, k);
     if (workspace_bytes < p.bytes) return SLIMSPEC_WORKSPACE_TOO_SMALL;
@@ -312,30 +290,17 @@ size_t head_workspace_bytes(HeadKind kind, const slimspec_shape *shape, int32_t 
         const size_t m = mfma_workspace_bytes(kind, shape);
         if (m > need) need = m;
     }
-    // (also where only a call of fewer rows takes that path: a workspace serves fewer rows as well)
-    slimspec_shape fewer = *shape;
-    if (fewer.rows > kRowsMaxRows) fewer.rows = kRowsMaxRows;
-    if (rows_path_takes(kind, &fewer, k)) {
-        const size_t w = rows_workspace_bytes(kind, &fewer, k);
+    // (whichever form of the call takes that path, and also where only a call of fewer rows does: a workspace serves fewer
+    // rows as well.  Of the forms the plain sampling call takes it wherever another one does.)
+    const int fewer = shape->rows < kRowsMaxRows ? shape->rows : kRowsMaxRows;
+    if (rows_path_takes(kind, fewer, shape->d, shape->r, shape->V, k, false, true)) {
+        const size_t w = rows_workspace_bytes(kind, shape, k);
         if (w > need) need = w;
     }
     return need;
 }
 
 }  // namespace
-
-namespace slimspec {
-bool head_tile_f16(int k) {
-    // The direct-to-LDS kernel takes bf16 operands as they are, or turns the weight tiles into f16 inside LDS and
-    // takes an f16 t (8 times finer).  The conversion costs the projection kernel about 12 %; the finer operand
-    // saves most of the merge's exact re-evaluations, which grow with k: measured break-even at k = 10, 5-9 % of
-    // the call in favour of f16 at k = 16.
-#ifdef SLIMSPEC_DIAG_OPERAND_F16      // experiment builds only: force the operand mode (1 f16, 0 bf16)
-    return SLIMSPEC_DIAG_OPERAND_F16 != 0;
-#endif
-    return k > 12;
-}
-}  // namespace slimspec
 
 extern "C" {
 

@@ -1,5 +1,6 @@
-// Prints, for every line "kind rows d r V" of standard input (kind: low or full), what csrc/plan.hpp plans for one
-// launch of that many rows.  Host arithmetic only; linked with the library for the rules it keeps in its sources.
+// Prints, for every line "kind rows d r V k fp32 prepared sampling" of standard input (kind: low or full; the last three
+// 0 or 1), what csrc/plan.hpp plans for the call and its first launch.  Host arithmetic only; linked with the library for
+// the rules it keeps in its sources.
 #define __host__
 #define __device__
 #include "../paper_2605_10453_amd/csrc/plan.hpp"
@@ -11,11 +12,17 @@ using namespace slimspec;
 int main()
 {
     char kind_name[16];
-    int rows, d, r, V;
-    while (std::scanf("%15s %d %d %d %d", kind_name, &rows, &d, &r, &V) == 5) {
+    int rows, d, r, V, k, fp32, prepared, sampling;
+    while (std::scanf("%15s %d %d %d %d %d %d %d %d", kind_name, &rows, &d, &r, &V, &k, &fp32, &prepared, &sampling) == 9) {
         const HeadKind kind = std::strcmp(kind_name, "full") == 0 ? HeadKind::Full : HeadKind::LowRank;
-        const MfmaPlan p = make_mfma_plan(kind, rows, d, r, V);
-        std::printf("resident=%d rows_per_block=%d gw=%d nsr=%d\n", p.resident ? 1 : 0, p.rt, p.gw, p.nsr);
+        const bool low_rank = kind == HeadKind::LowRank;
+        const MfmaPlan p = make_mfma_plan(kind, mfma_max_rows_per_launch(rows), d, r, V);
+        const bool f16 = low_rank && tile_operand_f16(k, prepared != 0), resident = resident_takes(p, f16, sampling != 0);
+        const bool rows_path = !fp32 && rows_path_takes(kind, rows, d, r, V, k, prepared != 0, sampling != 0);
+        const char *kernel = rows_path ? "rows" : fp32 || !tile_path_takes(rows, k) ? "stream" : resident ? "resident" : "tile";
+        const int gw = resident ? p.res.gw : p.gw, nsr = resident ? p.res.nsr : p.nsr;
+        std::printf("kernel=%s resident_fits=%d f16=%d rows_per_block=%d col_blocks=%d records=%d parks=%d\n", kernel, p.resident ? 1 : 0,
+                    f16 ? 1 : 0, p.rt, gw, nsr / gw, p.defer && merge_parks_rows(low_rank ? r : d, !low_rank || f16) && !prepared && !sampling ? 1 : 0);
     }
     return 0;
 }

@@ -19,7 +19,16 @@ def _probe() -> str:
     return exe
 
 
-def launch_plan(kind: str, rows: int, d: int, r: int, V: int) -> dict:
-    """The matrix-core plan of one launch: resident, rows_per_block, gw (column blocks), nsr (records per row)."""
-    out = subprocess.run([_probe()], input=f"{kind} {rows} {d} {r} {V}\n", capture_output=True, text=True, check=True).stdout
-    return {k: int(v) for k, v in (f.split("=") for f in out.split())}
+def plan_of(kind: str, rows: int, d: int, r: int, V: int, k: int, fp32=False, prepared=False, sampling=False) -> dict:
+    """What a call runs.  kernel: stream, rows, tile or resident; and, for the last two, f16 (operands), rows_per_block,
+    col_blocks, records (per row and column block), parks (rows that wait for their exact columns); resident_fits."""
+    line = f"{kind} {rows} {d} {r} {V} {k} {int(fp32)} {int(prepared)} {int(sampling)}\n"
+    out = subprocess.run([_probe()], input=line, capture_output=True, text=True, check=True).stdout
+    fields = dict(f.split("=") for f in out.split())
+    return {key: v if key == "kernel" else int(v) for key, v in fields.items()}
+
+
+def assert_plan(kind: str, rows: int, d: int, r: int, V: int, k: int, fp32=False, prepared=False, sampling=False, **expected):
+    """A test that is about one kernel or branch says so, and fails when a later rule sends its shape elsewhere."""
+    plan = plan_of(kind, rows, d, r, V, k, fp32, prepared, sampling)
+    assert {key: plan[key] for key in expected} == expected, plan

@@ -4,15 +4,15 @@ import ctypes
 import pytest
 
 from paper_2605_10453_amd import binding
-from plan_util import launch_plan
+from plan_util import plan_of
 
 
 def test_resident_head_only_where_its_offsets_fit():
     """head_resident_kernel addresses the 128 rows of a stage of the weights with 32-bit byte offsets: 128 * 2 V <= 2^32."""
-    assert launch_plan("low", 512, 4096, 512, 128256)["resident"] == 1
-    assert launch_plan("low", 512, 4096, 512, 1 << 24)["resident"] == 1
+    assert plan_of("low", 512, 4096, 512, 128256, 10)["resident_fits"] == 1
+    assert plan_of("low", 512, 4096, 512, 1 << 24, 10)["resident_fits"] == 1
     for V in ((1 << 24) + 8, 1 << 25, 1 << 26):
-        assert launch_plan("low", 512, 4096, 512, V)["resident"] == 0, V
+        assert plan_of("low", 512, 4096, 512, V, 10)["resident_fits"] == 0, V
 
 
 @pytest.mark.parametrize("d,r,V,k", [(512, 64, 16384, 10), (4096, 512, 16384, 12), (4096, 512, 128256, 10), (6248, 392, 2789880, 1),
@@ -26,3 +26,26 @@ def test_a_workspace_serves_fewer_rows(d, r, V, k):
         sizes = [query(n) for n in range(1, 1100)]
         falls = [(n + 1, sizes[n - 1], sizes[n]) for n in range(1, len(sizes)) if sizes[n] < sizes[n - 1]]
         assert sizes[0] > 0 and not falls, (name, falls[:3])
+
+
+@pytest.mark.parametrize("r,V", [(256, 8192), (256, 32000), (512, 32000), (512, 128256), (1024, 128256)])
+def test_prepared_weights_decide_between_33_and_48_rows(r, V):
+    """With the column-major copy the stream records' merge is cheap: from 33 rows on such calls were 4 to 15 % slower on the
+    kernel for few rows than on head_tile_kernel."""
+    for rows in (24, 32):
+        assert plan_of("low", rows, 8 * r, r, V, 10, prepared=True)["kernel"] == "rows"
+    for rows in (33, 40, 48, 49):
+        assert plan_of("low", rows, 8 * r, r, V, 10, prepared=True)["kernel"] == "tile"
+        assert plan_of("low", rows, 8 * r, r, V, 10, prepared=True, sampling=True)["kernel"] == ("rows" if rows <= 48 else "tile")
+    assert plan_of("low", 40, 8 * r, r, V, 40, prepared=True)["kernel"] == "rows"          # a list the records cannot hold
+
+
+@pytest.mark.parametrize("kind,rows,d,r,V,k,kernel", [
+    ("low", 4, 2048, 256, 128256, 10, "stream"), ("low", 3, 4096, 512, 128256, 10, "rows"), ("low", 4, 1024, 128, 151936, 32, "rows"),
+    ("low", 4, 4096, 512, 16384, 10, "stream"), ("low", 2, 4096, 512, 128256, 40, "stream"), ("low", 48, 2048, 256, 32000, 3, "rows"),
+    ("full", 2, 256, 8, 32000, 10, "stream"), ("full", 2, 264, 8, 32000, 10, "rows"),
+    ("full", 33, 512, 8, 64000, 1, "tile"), ("full", 48, 1024, 8, 64000, 1, "rows"), ("full", 48, 768, 8, 8192, 4, "rows"),
+    ("full", 40, 512, 8, 128256, 10, "tile"), ("full", 40, 512, 8, 128256, 16, "rows"), ("full", 31, 256, 8, 8192, 1, "rows"), ("full", 32, 256, 8, 8192, 1, "tile"),
+])
+def test_few_rows_take_the_kernel_that_measures_faster(kind, rows, d, r, V, k, kernel):
+    assert plan_of(kind, rows, d, r, V, k)["kernel"] == kernel
