@@ -13,7 +13,10 @@ LIB = os.path.join(HERE, "libslimspec.so")
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",   # no packed-fp32 code generation
-    # MFMA results in vector registers also where a kernel has 512 registers per lane (head_resident.hip reads them there)
+    # MFMA results in vector registers.  A condition of correctness, not a preference: head_resident_kernel<32> keeps its row
+    # operand in the 128 accumulation registers it has, and without this it also accumulates there and spills 80 bytes per
+    # lane; the kernel counts its own vector loads (s_waitcnt vmcnt(N)), which spills would falsify.  A test holds every
+    # instance to no scratch memory.  Of the other kernels it changes down_tile_kernel only (no accumulation registers).
     "-mllvm", "-amdgpu-mfma-vgpr-form=1",
     "-Wall", "-Wno-unused-command-line-argument",
 ]

@@ -24,7 +24,7 @@
 // twice (row mod 4), so that the four rows of a transposing read (ds_read_b64_tr_b16) fall into different banks.
 // The compiler does not see these loads: every wavefront issues exactly two per stage, vector memory returns in order,
 // and "s_waitcnt vmcnt(N)" means that the stages needed next have landed (see do_tile).  Nothing else in the loop may use
-// vector memory: the kernel must not spill.
+// vector memory: the kernel must not spill (for which it needs the build's -amdgpu-mfma-vgpr-form).
 #include "head_stream.hpp"
 #include "launch.hpp"
 #include <type_traits>
