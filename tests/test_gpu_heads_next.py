@@ -24,9 +24,10 @@ def gpu():
 @pytest.mark.parametrize("rows,d,V_full,V_tr,k,w_f32", [
     (1, 256, 20000, 8200, 10, False),       # streaming path
     (3, 128, 9000, 3080, 7, True),          # fp32 weights
-    (9, 96, 9000, 2056, 6, False),          # matrix-core path, natural-unit mode
-    (70, 128, 12000, 5000, 16, False),
-    (12, 2048, 9000, 4104, 8, False),       # long contraction: parked rows
+    (9, 96, 9000, 2056, 6, False),          # matrix cores
+    (70, 128, 12000, 5000, 16, False),      # ... head_tile_kernel, natural-unit mode
+    (12, 2048, 9000, 4104, 8, False),       # long contraction
+    (52, 2048, 9000, 4104, 8, False),       # ... with parked rows
 ])
 def test_truncated_head(gpu, oracle_mod, rows, d, V_full, V_tr, k, w_f32):
     torch, b = gpu
@@ -53,11 +54,11 @@ def test_truncated_head(gpu, oracle_mod, rows, d, V_full, V_tr, k, w_f32):
 def test_truncated_head_tied_columns_break_by_column(gpu, oracle_mod):
     """Identical kept columns: the smaller column wins whatever vocabulary id it maps to."""
     torch, b = gpu
-    for rows in (2, 12):
+    for rows, scale in ((2, 0.5), (12, 0.5), (60, 1.0)):      # planted logits of 4 and 8; the others are unit normal
         x = synth.make_inputs(synth.small_config(rows, 64, 8, 1032, 4), seed=3, with_full_head=True)
         W = x.W.copy()
         h0 = synth.bf16_bits_to_f64(x.h[0])
-        synth.plant_identical_columns(W, 0.5 * h0 / 8.0, [5, 500, 1000])
+        synth.plant_identical_columns(W, scale * h0 / 8.0, [5, 500, 1000])
         id_map = np.arange(1032, dtype=np.int32)[::-1].copy()                       # column c is vocabulary id 1031 - c
         ids, _ = b.truncated_head_topk(to_dev_bf16(x.h), to_dev_bf16(W), torch.from_numpy(id_map).cuda(), 4)
         torch.cuda.synchronize()
@@ -71,13 +72,17 @@ def test_truncated_head_tied_columns_break_by_column(gpu, oracle_mod):
     ((1, 1, 1), 256, 32, 8200, 8),                  # streaming path, every row its own matrix
     ((2, 0, 2), 128, 16, 5000, 5),                  # ... an empty position
     ((4,), 128, 16, 5000, 5),                       # one position: the plain head
-    ((3, 1, 0, 5), 96, 24, 2056, 7),                # matrix-core path, groups smaller than a tile
+    ((3, 1, 0, 5), 96, 24, 2056, 7),                # matrix cores, groups smaller than a tile
+    ((30, 1, 0, 25), 96, 24, 2056, 7),              # ... with stream records
     ((70, 1, 0, 129), 128, 40, 3080, 10),           # groups that end inside a row tile
     ((64, 64, 64), 256, 64, 4104, 16),              # groups that fill their tiles; f16 operands
     ((300, 250, 50), 64, 32, 1032, 5),              # two launches: a group crosses the 512-row boundary
-    ((9, 11), 128, 32, 3080, 20),                   # k beyond the matrix-core path: streaming in row groups of 8
-    ((100, 60, 40), 64, 64, 70000, 5),              # many column blocks: two records per block and row
-    ((7, 13), 64, 64, 70000, 5),                    # ... one record
+    ((9, 11), 128, 32, 3080, 20),                   # k beyond the stream records
+    ((40, 30), 128, 32, 3080, 20),                  # ... two launches of up to 48 rows, a group in both
+    ((100, 60, 40), 64, 520, 70000, 5),             # many column blocks: two records per block and row
+    ((27, 33), 64, 64, 70000, 5),                   # ... one record
+    ((100, 60, 40), 64, 64, 70000, 5),              # ... of head_resident_kernel
+    ((7, 13), 64, 64, 70000, 5),                    # few rows, large vocabulary
 ])
 @pytest.mark.parametrize("prepared", [False, True])
 def test_position_specific_down_projections(gpu, oracle_mod, sizes, d, r, V, k, prepared):
@@ -102,7 +107,7 @@ def test_position_specific_down_projections(gpu, oracle_mod, sizes, d, r, V, k, 
 
 def test_positions_with_one_matrix_equal_the_plain_head(gpu):
     torch, b = gpu
-    for rows in (2, 40):
+    for rows in (2, 40, 60, 140):
         x = synth.make_inputs(synth.small_config(rows, 128, 32, 4104, 6), seed=5)
         h, A, B = to_dev_bf16(x.h), to_dev_bf16(x.A), to_dev_bf16(x.B)
         a_ids, a_lp = b.slimspec_head_topk(h, A, B, 6)
@@ -137,7 +142,8 @@ def check_sample_outputs(torch, out, ora, seed, V, z_rows, oracle_mod):
     (1, 256, 32, 8200, 8, 1), (1, 64, 16, 140000, 5, 2 ** 40 + 17), (3, 128, 16, 5000, 6, 3), (4, 512, 64, 10248, 10, 4),
     (9, 96, 24, 2056, 7, 5), (40, 256, 32, 4104, 12, 6), (130, 64, 40, 2056, 5, 7), (20, 128, 32, 3080, 20, 8),
     (12, 64, 24, 2056, 16, 9),
-    (200, 64, 64, 70000, 5, 10), (20, 64, 64, 70000, 5, 11),       # many column blocks: two records, one record per block and row
+    (200, 64, 64, 70000, 5, 10), (64, 64, 64, 70000, 5, 12),       # many column blocks: two records, one record per block and row
+    (20, 64, 64, 70000, 5, 11), (60, 64, 24, 2056, 16, 13),        # few rows, large vocabulary; f16 operands next to the noise
 ])
 @pytest.mark.parametrize("prepared", [False, True])
 def test_low_rank_head_sample(gpu, oracle_mod, rows, d, r, V, k, seed, prepared):
@@ -158,7 +164,7 @@ def test_low_rank_head_sample(gpu, oracle_mod, rows, d, r, V, k, seed, prepared)
     assert torch.equal(ids, out[0])
 
 
-@pytest.mark.parametrize("rows,w_f32", [(2, False), (3, True), (33, False)])
+@pytest.mark.parametrize("rows,w_f32", [(2, False), (3, True), (33, False), (65, False)])
 def test_full_head_sample(gpu, oracle_mod, rows, w_f32):
     torch, b = gpu
     x = synth.make_inputs(synth.small_config(rows, 128, 8, 6152, 9, peaked_every=3), seed=300 + rows, with_full_head=True)

@@ -8,6 +8,7 @@ import pytest
 
 from paper_2605_10453_amd import synth
 from parity_util import compare_with_oracle, to_dev_bf16, to_dev_f32
+from plan_util import assert_plan, plan_of
 
 pytestmark = pytest.mark.gpu
 
@@ -102,11 +103,16 @@ SMALL = [
     (9, 96, 24, 2056, 7),           # one row more than a row group
     (17, 128, 32, 4104, 12),        # three row groups
     (40, 256, 32, 1032, 3),
-    (130, 64, 40, 2056, 5),         # two 128-row halves of a 256-row block, contraction tail, column tail
+    (130, 64, 40, 2056, 5),         # a 256-row block half full, contraction tail, column tail
     (300, 128, 64, 5000, 10),       # two 256-row blocks, the second mostly padding
-    (20, 64, 8, 1032, 4),           # a single, partial stage of the contraction
-    (12, 64, 24, 2056, 16),         # the largest k of the matrix-core path
-    (5, 128, 32, 4104, 10),         # the smallest row count of the matrix-core path
+    (20, 64, 8, 1032, 4),           # a single, partial step of the contraction
+    (12, 64, 24, 2056, 16),         # the largest k of the stream records, few rows
+    (5, 128, 32, 4104, 10),         # the smallest row count of the matrix cores at this size
+    (49, 128, 32, 4104, 10),        # the smallest row count of head_tile_kernel
+    (60, 64, 8, 1032, 4),           # ... a single, partial stage of its contraction
+    (50, 64, 24, 2056, 16),         # ... the largest k: f16 operands
+    (140, 64, 24, 2056, 16),        # ... in a 256-row block
+    (150, 64, 520, 2056, 5),        # ... a contraction longer than the resident kernel takes
     (1, 64, 16, 140000, 10),        # one row, more than 256 chunks: narrower chunks, 8-wavefront blocks
     (1, 64, 16, 300000, 10),        # ... more than 512: 4-wavefront blocks
     (1, 64, 8, 600008, 5),          # ... more than 1024: full-width chunks in several rounds
@@ -137,19 +143,21 @@ def test_full_head_small(gpu, oracle_mod, rows, d, r, V, k, w_f32):
 
 @pytest.mark.parametrize("rows,d,r,V,k", SMALL[9:13])
 def test_full_head_small_many_rows(gpu, oracle_mod, rows, d, r, V, k):
-    """More than 8 rows and bf16 weights: the full head runs on the matrix cores."""
+    """More than 8 rows and bf16 weights: the full head runs on the matrix cores (rows_topk_kernel, head_tile_kernel)."""
     x = synth.make_inputs(synth.small_config(rows, d, r, V, k, peaked_every=4), seed=177 + rows, with_full_head=True)
     check_full(gpu, oracle_mod, x.h, x.W, k)
 
 
+@pytest.mark.parametrize("rows", [12, 64])
 @pytest.mark.parametrize("n_tied", [2, 40, 600, 2400])
-def test_full_head_long_contraction_exact_reevaluation(gpu, oracle_mod, n_tied):
-    """Full head with d >= 2048 and many rows: rows that need exact re-evaluations are parked by the merge and
+def test_full_head_long_contraction_exact_reevaluation(gpu, oracle_mod, n_tied, rows):
+    """Full head with d >= 2048 and many rows (64): rows that need exact re-evaluations are parked by the merge and
     finished by two more launches.  Exactly tied top columns force the re-evaluation for row 0 (2 and 40 tied
     columns and the about 400 that 600 leave outside the duplicated block fit a parked row's list; 2400 leave
     about 1600, more than a parked row holds, and are evaluated in place); a duplicated block of columns makes
-    every other row tie at some ranks too."""
-    cfg = synth.small_config(rows=12, d=2048, r=8, V=4104, k=8)
+    every other row tie at some ranks too.  12 rows: the same ties in rows_topk_kernel's lists."""
+    cfg = synth.small_config(rows=rows, d=2048, r=8, V=4104, k=8)
+    assert_plan("full", rows, cfg.d, cfg.r, cfg.V, cfg.k, **(dict(kernel="rows") if rows <= 48 else dict(kernel="tile", parks=1)))
     x = synth.make_inputs(cfg, 5, with_full_head=True)
     V = cfg.V
     x.W[:, 2048:2048 + 1024] = x.W[:, :1024]                    # every row: its best column below 1024 has a twin
@@ -162,18 +170,23 @@ def test_full_head_long_contraction_exact_reevaluation(gpu, oracle_mod, n_tied):
     assert np.array_equal(g_ids, ora.ids)                       # exact values, ties by id: nothing left to the tolerance
 
 
-@pytest.mark.parametrize("rows,k", [(20, 17), (140, 40)])
-def test_many_rows_large_k(gpu, oracle_mod, rows, k):
-    """k above the matrix-core path's limit: the call takes the streaming path in row groups."""
-    x = synth.make_inputs(synth.small_config(rows, 128, 32, 3080, k, peaked_every=3), seed=900 + rows)
+@pytest.mark.parametrize("rows,k,r", [(20, 17, 32), (140, 40, 32), (20, 17, 2056)])
+def test_many_rows_large_k(gpu, oracle_mod, rows, k, r):
+    """k above the stream records' limit: rows_topk_kernel in groups of 48 rows or, for r > 2048, the streaming kernel in
+    groups of 8."""
+    assert_plan("low", rows, 128, r, 3080, k, kernel="rows" if r <= 2048 else "stream")
+    x = synth.make_inputs(synth.small_config(rows, 128, r, 3080, k, peaked_every=3), seed=900 + rows)
     check_low_rank(gpu, oracle_mod, x, k)
 
 
-def test_zero_rows_inside_a_many_row_batch(gpu, oracle_mod):
-    """Padded batch slots (all-zero hidden states) among ordinary rows on the matrix-core path."""
-    x = synth.make_inputs(synth.small_config(33, 128, 32, 3080, 6), seed=4242)
+@pytest.mark.parametrize("rows", [33, 70, 140])
+def test_zero_rows_inside_a_many_row_batch(gpu, oracle_mod, rows):
+    """Padded batch slots (all-zero hidden states) among ordinary rows, in each of the matrix-core kernels."""
+    assert_plan("low", rows, 128, 32, 3080, 6, kernel={33: "rows", 70: "tile", 140: "resident"}[rows])
+    x = synth.make_inputs(synth.small_config(rows, 128, 32, 3080, 6), seed=4242)
     x.h[5] = 0
     x.h[32] = 0
+    x.h[rows - 1] = 0
     check_low_rank(gpu, oracle_mod, x, 6)
 
 
@@ -200,7 +213,7 @@ def test_zero_hidden_state_all_tied(gpu, oracle_mod):
     assert np.allclose(g_lp, -math.log(cfg.V), atol=1e-4)
 
 
-@pytest.mark.parametrize("rows", [1, 6])
+@pytest.mark.parametrize("rows", [1, 6, 60])
 def test_planted_exact_ties(gpu, oracle_mod, rows):
     cfg = synth.small_config(rows=rows, d=256, r=64, V=6152, k=5)
     x = synth.make_inputs(cfg, 21)
@@ -215,15 +228,18 @@ def test_planted_exact_ties(gpu, oracle_mod, rows):
         assert ids[0].tolist() == [0, V // 2, V - 1][:k]
 
 
+@pytest.mark.parametrize("rows", [6, 66])
 @pytest.mark.parametrize("k", [16, 10])
-def test_rising_logits_through_the_exhaustive_pass(gpu, oracle_mod, k):
-    """Logits that rise strictly with the column id over the whole vocabulary.  With k = 16 the matrix cores take an
-    f16 contraction input, which overflows for rows 0-2 here, so the merge answers with its exhaustive exact pass;
-    there every scanned column beats the running k-th key, which fills the pass's key buffer to its bound."""
-    rows, d, r, V = 6, 8, 8, 16384
+def test_rising_logits_through_the_exhaustive_pass(gpu, oracle_mod, k, rows):
+    """Logits that rise strictly with the column id over the whole vocabulary.  With k = 16 and more than 48 rows the
+    matrix cores take an f16 contraction input, which overflows for half of the rows here, so the merge answers with its
+    exhaustive exact pass; there every scanned column beats the running k-th key, which fills the pass's key buffer to
+    its bound.  Six rows: the same logits through rows_topk_kernel."""
+    d, r, V = 8, 8, 16384
+    assert_plan("low", rows, d, r, V, k, **(dict(kernel="rows") if rows == 6 else dict(kernel="tile", f16=int(k == 16))))
     one = synth.f32_to_bf16_bits(np.float32(1.0))
     h = np.zeros((rows, d), np.float32)
-    h[:, 0] = [65536.0, -65536.0, 98304.0, 0.0, 1.0, 65536.0]
+    h[:, 0] = [65536.0, -65536.0, 98304.0, 0.0, 1.0, 65536.0] * (rows // 6)
     A = np.zeros((d, r), np.float32)
     A[0, 0], A[0, 1] = 1.0, 2.0 ** -8
     v = np.arange(V)
@@ -240,9 +256,11 @@ def test_rising_logits_through_the_exhaustive_pass(gpu, oracle_mod, k):
 
 
 @pytest.mark.parametrize("rows,d,r,V,k", [(1, 512, 64, 20000, 10), (3, 256, 32, 9000, 7), (5, 512, 64, 20000, 10),
-                                          (512, 256, 64, 20000, 10), (40, 128, 32, 6000, 16)])
+                                          (512, 256, 64, 20000, 10), (40, 128, 32, 6000, 16),
+                                          (64, 512, 64, 20000, 10), (64, 128, 32, 6000, 16), (300, 64, 520, 20000, 10)])
 def test_run_to_run_determinism(gpu, rows, d, r, V, k):
-    """Same inputs, same bits out: the streaming path, the matrix-core path with both operand modes and two row blocks."""
+    """Same inputs, same bits out: the streaming kernel, rows_topk_kernel, head_tile_kernel with both operand modes and
+    two row blocks, head_resident_kernel."""
     cfg = synth.small_config(rows=rows, d=d, r=r, V=V, k=k, peaked_every=7)
     x = synth.make_inputs(cfg, 3)
     a = run_low_rank(gpu, x, cfg.k)
@@ -251,9 +269,12 @@ def test_run_to_run_determinism(gpu, rows, d, r, V, k):
         assert np.array_equal(a[0], b[0]) and np.array_equal(a[1].view(np.uint32), b[1].view(np.uint32))
 
 
-def test_run_to_run_determinism_full_head_parked_rows(gpu):
-    """Full head with a long contraction: rows that need exact re-evaluations are parked and finished by later launches."""
-    cfg = synth.small_config(rows=12, d=2048, r=8, V=4104, k=8)
+@pytest.mark.parametrize("rows", [12, 64])
+def test_run_to_run_determinism_full_head_parked_rows(gpu, rows):
+    """Full head with a long contraction: rows (of 64) that need exact re-evaluations are parked and finished by later
+    launches; 12 rows take rows_topk_kernel, which has none."""
+    cfg = synth.small_config(rows=rows, d=2048, r=8, V=4104, k=8)
+    assert_plan("full", rows, cfg.d, cfg.r, cfg.V, cfg.k, **(dict(kernel="rows") if rows <= 48 else dict(kernel="tile", parks=1)))
     x = synth.make_inputs(cfg, 5, with_full_head=True)
     x.W[:, 2048:2048 + 1024] = x.W[:, :1024]
     a = run_full(gpu, x.h, x.W, cfg.k)
@@ -288,12 +309,13 @@ def test_side_stream_and_caller_buffers(gpu, oracle_mod):
 
 
 def test_two_host_threads_on_two_streams(gpu):
-    """Calls from two host threads, each on a stream and a workspace of its own, overlap freely (the library keeps no
+    """Calls from four host threads, each on a stream and a workspace of its own, overlap freely (the library keeps no
     state but per thread); every result equals the one the same call gives alone."""
     import threading
     torch, b = gpu
     jobs = []
-    for rows, seed in ((1, 11), (40, 12)):                      # the streaming path and the matrix-core path
+    for rows, seed in ((1, 11), (40, 12), (64, 13), (200, 14)):     # one of every head kernel
+        assert_plan("low", rows, 512, 64, 30000, 10, kernel={1: "stream", 40: "rows", 64: "tile", 200: "resident"}[rows])
         cfg = synth.small_config(rows=rows, d=512, r=64, V=30000, k=10, peaked_every=7)
         x = synth.make_inputs(cfg, seed)
         h, A, B = to_dev_bf16(x.h), to_dev_bf16(x.A), to_dev_bf16(x.B)
@@ -327,11 +349,13 @@ def test_two_host_threads_on_two_streams(gpu):
     assert not errors, errors
 
 
-def test_graph_replays_of_the_matrix_core_path(gpu):
-    """Two calls of the many-row path captured in one HIP graph (no allocation, no synchronisation, no memset inside
+@pytest.mark.parametrize("rows,kernel", [(48, "rows"), (64, "tile"), (200, "resident")])
+def test_graph_replays_of_the_matrix_core_path(gpu, rows, kernel):
+    """Two calls of each matrix-core kernel captured in one HIP graph (no allocation, no synchronisation, no memset inside
     the library): every replay, with other work of the process between them, gives the eager results."""
     torch, b = gpu
-    cfg = synth.small_config(rows=48, d=512, r=128, V=30000, k=10, peaked_every=5)
+    cfg = synth.small_config(rows=rows, d=512, r=128, V=30000, k=10, peaked_every=5)
+    assert_plan("low", rows, cfg.d, cfg.r, cfg.V, cfg.k, kernel=kernel)
     xs = [synth.make_inputs(cfg, seed) for seed in (21, 22)]
     dev = [(to_dev_bf16(x.h), to_dev_bf16(x.A), to_dev_bf16(x.B)) for x in xs]
     outs = [(torch.empty((cfg.rows, cfg.k), dtype=torch.int32, device="cuda"),
@@ -408,12 +432,15 @@ def test_wide_rounding_bound_with_few_winners(gpu, oracle_mod):
     check_low_rank(gpu, oracle_mod, x, cfg.k)
 
 
-def test_two_probable_tokens_in_one_group_of_sixteen(gpu, oracle_mod):
+@pytest.mark.parametrize("rows", [24, 64, 140])
+def test_two_probable_tokens_in_one_group_of_sixteen(gpu, oracle_mod, rows):
     """The row's two most probable tokens sit in the same group of 16 logits of one lane (columns b + 1 and b + 18 of a
     32-column tile), so only the larger one is listed with its computed value; the other one carries 40 % of the
     probability and, by construction, a large rounding error (a component orthogonal to t).  The merge has to replace
-    its term of the sum of exponentials too, for which it recomputes the logit the head kernel saw."""
-    cfg = synth.small_config(rows=24, d=256, r=96, V=2048, k=4, peaked_every=0)
+    its term of the sum of exponentials too, for which it recomputes the logit the head kernel saw.  (64 rows:
+    head_tile_kernel's records, 140: head_resident_kernel's; 24 rows have no records.)"""
+    cfg = synth.small_config(rows=rows, d=256, r=96, V=64 * max(rows, 32), k=4, peaked_every=0)
+    assert_plan("low", rows, cfg.d, cfg.r, cfg.V, cfg.k, kernel={24: "rows", 64: "tile", 140: "resident"}[rows])
     x = synth.make_inputs(cfg, seed=91)
     x.h = synth.f32_to_bf16_bits(synth.bf16_bits_to_f32(x.h) * np.float32(16.0))
     t = synth.bf16_bits_to_f64(x.h) @ synth.bf16_bits_to_f64(x.A)
@@ -431,11 +458,14 @@ def test_two_probable_tokens_in_one_group_of_sixteen(gpu, oracle_mod):
     check_low_rank(gpu, oracle_mod, x, cfg.k)
 
 
-def test_logit_far_above_the_running_maximum(gpu, oracle_mod):
+@pytest.mark.parametrize("r", [144, 520])
+def test_logit_far_above_the_running_maximum(gpu, oracle_mod, r):
     """One column per row, late in the vocabulary (in a tile that is not the first one its block works on), whose logit is 126 to 130 binary orders above everything the row has
     seen until then (natural logits 88 ... 92 over a background of 2 ... 5): the running sum of exponentials has to be
-    rescaled by a factor at the very bottom of the float range, or, just beyond it, the row has to be redone exactly."""
-    cfg = synth.small_config(rows=512, d=256, r=144, V=36784, k=5, peaked_every=0)
+    rescaled by a factor at the very bottom of the float range, or, just beyond it, the row has to be redone exactly.
+    r = 144: head_resident_kernel, 520: head_tile_kernel."""
+    cfg = synth.small_config(rows=512, d=256, r=r, V=36784, k=5, peaked_every=0)
+    assert_plan("low", cfg.rows, cfg.d, r, cfg.V, cfg.k, kernel="resident" if r == 144 else "tile")
     x = synth.make_inputs(cfg, seed=77)
     t = synth.bf16_bits_to_f64(x.h) @ synth.bf16_bits_to_f64(x.A)
     B = synth.bf16_bits_to_f32(x.B)
@@ -451,14 +481,20 @@ def test_logit_far_above_the_running_maximum(gpu, oracle_mod):
     check_low_rank(gpu, oracle_mod, x, cfg.k)
 
 
-@pytest.mark.parametrize("rows,V", [(300, 40960), (200, 70000), (20, 70000)])
-def test_four_best_logits_in_one_lane_stream(gpu, oracle_mod, rows, V):
-    """The matrix-core kernel lists three groups of 16 logits per lane stream (a row's share of four of a vocabulary
+@pytest.mark.parametrize("rows,r,V,records", [(300, 520, 40960, 4), (200, 520, 70000, 2), (64, 64, 70000, 1),
+                                              (300, 64, 40960, 0), (200, 64, 70000, 0), (20, 64, 70000, 0)])
+def test_four_best_logits_in_one_lane_stream(gpu, oracle_mod, rows, r, V, records):
+    """head_tile_kernel lists three groups of 16 logits per lane stream (a row's share of four of a vocabulary
     tile's eight 32-column MFMA tiles in one half-wavefront, over the tiles of a column block).  Here a row's four
     largest logits sit in four different groups of one lane stream (columns 256 vt + 32 j + 4, j = 4 ... 7), so one of
     them is dropped from the list and the merge has to rescan every column of the record that stream went into.  The
-    three shapes leave four, two and one record per row and column block (few, more, many column blocks)."""
-    cfg = synth.small_config(rows=rows, d=64, r=64, V=V, k=5, peaked_every=0)
+    first three shapes leave four, two and one record per row and column block (few, more, many column blocks); the
+    others run kernels with other records (their crowded record: test_gpu_resident_head.py) or none."""
+    if records:
+        assert_plan("low", rows, 64, r, V, 5, kernel="tile", records=records)
+    else:
+        assert plan_of("low", rows, 64, r, V, 5)["kernel"] != "tile"
+    cfg = synth.small_config(rows=rows, d=64, r=r, V=V, k=5, peaked_every=0)
     x = synth.make_inputs(cfg, seed=rows + V)
     t = synth.bf16_bits_to_f64(x.h) @ synth.bf16_bits_to_f64(x.A)
     B = synth.bf16_bits_to_f32(x.B)

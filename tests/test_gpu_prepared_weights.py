@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 
 import test_gpu_parity as base
+import test_gpu_resident_head as resident
 from paper_2605_10453_amd import synth
 from parity_util import to_dev_bf16
 from test_gpu_parity import gpu  # noqa: F401  (the module's fixture)
@@ -45,19 +46,24 @@ SPECIAL = {
     "not_gaussian_small_rows_k10": (base.test_matrix_core_path_weights_not_gaussian, dict(kind="small_every_8th_row", k=10)),
     "not_gaussian_large_rows_k16": (base.test_matrix_core_path_weights_not_gaussian, dict(kind="large_every_8th_row_offset_3", k=16)),
     "wide_rounding_bound": (base.test_wide_rounding_bound_with_few_winners, {}),
-    "two_probable_tokens_in_one_group": (base.test_two_probable_tokens_in_one_group_of_sixteen, {}),
-    "logit_far_above_the_running_maximum": (base.test_logit_far_above_the_running_maximum, {}),
-    "rising_logits_k16": (base.test_rising_logits_through_the_exhaustive_pass, dict(k=16)),
-    "rising_logits_k10": (base.test_rising_logits_through_the_exhaustive_pass, dict(k=10)),
+    "two_probable_tokens_in_one_group": (base.test_two_probable_tokens_in_one_group_of_sixteen, dict(rows=64)),
+    "two_probable_tokens_in_one_group_resident": (base.test_two_probable_tokens_in_one_group_of_sixteen, dict(rows=140)),
+    "logit_far_above_the_running_maximum": (base.test_logit_far_above_the_running_maximum, dict(r=144)),
+    "logit_far_above_the_running_maximum_tile": (base.test_logit_far_above_the_running_maximum, dict(r=520)),
+    "rising_logits_k10": (base.test_rising_logits_through_the_exhaustive_pass, dict(k=10, rows=66)),
     "zero_hidden_state": (base.test_zero_hidden_state_all_tied, {}),
     "planted_exact_ties_six_rows": (base.test_planted_exact_ties, dict(rows=6)),
-    "zero_rows_inside_a_batch": (base.test_zero_rows_inside_a_many_row_batch, {}),
+    "planted_exact_ties": (base.test_planted_exact_ties, dict(rows=60)),
+    "zero_rows_inside_a_batch": (base.test_zero_rows_inside_a_many_row_batch, dict(rows=70)),
+    "zero_rows_inside_a_batch_resident": (base.test_zero_rows_inside_a_many_row_batch, dict(rows=140)),
     "more_rows_than_one_launch": (base.test_more_rows_than_one_launch, {}),
     "few_rows_do_not_read_the_copy": (base.test_low_rank_small, dict(zip(("rows", "d", "r", "V", "k"), base.SMALL[6]))),
-    "large_k_does_not_read_the_copy": (base.test_many_rows_large_k, dict(rows=20, k=17)),
-    "four_best_in_one_lane_stream_4_records": (base.test_four_best_logits_in_one_lane_stream, dict(rows=300, V=40960)),
-    "four_best_in_one_lane_stream_2_records": (base.test_four_best_logits_in_one_lane_stream, dict(rows=200, V=70000)),
-    "four_best_in_one_lane_stream_1_record": (base.test_four_best_logits_in_one_lane_stream, dict(rows=20, V=70000)),
+    "large_k_does_not_read_the_copy": (base.test_many_rows_large_k, dict(rows=20, k=17, r=32)),
+    "four_best_in_one_lane_stream_4_records": (base.test_four_best_logits_in_one_lane_stream, dict(rows=300, r=520, V=40960, records=4)),
+    "four_best_in_one_lane_stream_2_records": (base.test_four_best_logits_in_one_lane_stream, dict(rows=200, r=520, V=70000, records=2)),
+    "four_best_in_one_lane_stream_1_record": (base.test_four_best_logits_in_one_lane_stream, dict(rows=64, r=64, V=70000, records=1)),
+    "four_best_in_one_stream_resident": (resident.test_four_best_logits_in_one_stream, dict(rows=300, V=40960)),
+    "four_best_in_one_stream_resident_one_row_block": (resident.test_four_best_logits_in_one_stream, dict(rows=200, V=70016)),
     "C4": (base.test_config4_low_rank, dict(name="C4")),
     "C4_r256": (base.test_config4_low_rank, dict(name="C4_r256")),
     "C4_r1024": (base.test_config4_low_rank, dict(name="C4_r1024")),
@@ -80,7 +86,7 @@ def _random_cases(n, seed):
     rng = np.random.default_rng(seed)
     out = []
     for _ in range(n):
-        rows = int(rng.choice([5, 6, 9, 17, 33, 70, 129, 200, 513]))
+        rows = int(rng.choice([5, 6, 9, 17, 33, 70, 129, 200, 513]))      # from 33 on the copy is read
         d = 8 * int(rng.integers(1, 65))
         r = 8 * int(rng.integers(1, 130))                   # contraction lengths on both sides of one 512-element step
         V = 8 * int(rng.integers(1, 1500))
@@ -91,7 +97,7 @@ def _random_cases(n, seed):
 
 @pytest.mark.parametrize("rows,d,r,V,k,peaked_every,scaled", _random_cases(40, 20261128))
 def test_random_shapes_with_prepared_weights(gpu, oracle_mod, prepared, rows, d, r, V, k, peaked_every, scaled):
-    """Seeded shapes nobody picked by hand on the matrix-core path; in half of them some columns of B are 8 and 32
+    """Seeded shapes nobody picked by hand on the matrix-core kernels; in half of them some columns of B are 8 and 32
     times larger than the rest (wide rounding bounds: more exact re-evaluations, unlisted members)."""
     cfg = synth.small_config(rows=rows, d=d, r=r, V=V, k=k, peaked_every=peaked_every)
     x = synth.make_inputs(cfg, 31000 + rows + V)

@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 
 from paper_2605_10453_amd import synth
+from plan_util import assert_plan
 from test_gpu_parity import check_low_rank, gpu  # noqa: F401  (the module's fixture)
 
 pytestmark = pytest.mark.gpu
@@ -16,6 +17,7 @@ pytestmark = pytest.mark.gpu
     (513, 64, 264, 2056, 6), (140, 256, 384, 16392, 10), (512, 128, 392, 16456, 7), (260, 512, 512, 32840, 12), (130, 64, 512, 70008, 5),
 ])
 def test_tile_edges(gpu, oracle_mod, rows, d, r, V, k):
+    assert_plan("low", rows, d, r, V, k, kernel="resident")
     x = synth.make_inputs(synth.small_config(rows, d, r, V, k, peaked_every=6), seed=rows + r)
     check_low_rank(gpu, oracle_mod, x, k)
 
@@ -25,6 +27,7 @@ def test_four_best_logits_in_one_stream(gpu, oracle_mod, rows, V):
     """A stream is a half-wavefront's share of the 64-column tiles col, col + gw, ... (gw = 128 column blocks for two row
     blocks, 256 for one).  A row's four largest logits sit in four groups of 16 of one stream, one more than it lists."""
     gw = 128 if rows > 256 else 256
+    assert_plan("low", rows, 64, 64, V, 5, kernel="resident", col_blocks=gw, records=2)
     cfg = synth.small_config(rows=rows, d=64, r=64, V=V, k=5)
     x = synth.make_inputs(cfg, seed=rows + V)
     t = synth.bf16_bits_to_f64(x.h) @ synth.bf16_bits_to_f64(x.A)
