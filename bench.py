@@ -29,7 +29,6 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBS = 8000.0          # MI355X published HBM3E bandwidth
 MFMA_PEAK_TFLOPS = 2500.0      # dense bf16 / fp16 matrix peak
-GEMV_MAX_ROWS = 4              # rows up to which the library streams (from 5 rows on: matrix cores)
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic.json")
 
 
@@ -64,10 +63,22 @@ def algorithmic_bytes_low_rank(rows, d, r, V, k):
     return 2 * (d * r + r * V + rows * d) + rows * k * 8
 
 
-def projection_kernel_bytes(rows, K, V):
+def projection_kernel(rows, K, V, k, full=False, prepared=False):
+    """The kernel that a call's vocabulary projection runs, and the bytes per element of its row operand: the library's
+    rules for the shapes timed here (one row, or d of a few thousand; a test holds them against the library's own)."""
+    if rows <= (1 if full else 2):
+        return "stream_topk_kernel", 4                     # fp32 t or h
+    if k > 16 or rows <= (32 if prepared else 48):
+        return "rows_topk_kernel", 2 if full else 6        # h, or t as three bf16 pieces
+    if not full and rows > 128 and K <= 512 and (k <= 12 or prepared):
+        return "head_resident_kernel", 2
+    return "head_tile_kernel", 2
+
+
+def projection_kernel_bytes(rows, K, V, k, full=False, prepared=False):
     """Algorithmic bytes of one launch of the vocabulary-projection kernel: the [K, V] bf16 weight
-    matrix once plus its [rows, K] input (fp32 when streaming, 16-bit on the matrix cores)."""
-    return 2 * K * V + (4 if rows <= GEMV_MAX_ROWS else 2) * rows * K
+    matrix once plus its [rows, K] input."""
+    return 2 * K * V + projection_kernel(rows, K, V, k, full, prepared)[1] * rows * K
 
 
 def percentiles(v):
@@ -227,9 +238,9 @@ def main():
             B[j0:j1] = (torch.randn((j1 - j0, V), generator=g, device=dev, dtype=torch.float32) * r ** -0.5).to(torch.bfloat16)
         return h, [A] + [A.clone() for _ in range(copies - 1)], [B] + [B.clone() for _ in range(copies - 1)]
 
-    def roofline_of(name, rows, K, V, kern_ms, null_ms):
+    def roofline_of(name, rows, K, V, k, kern_ms, null_ms, full=False, prepared=False):
         """Roofline entry of the vocabulary-projection kernel of one call."""
-        kbytes = projection_kernel_bytes(rows, K, V)
+        kbytes = projection_kernel_bytes(rows, K, V, k, full, prepared)
         flops = 2.0 * rows * K * V
         kern_s = kern_ms * 1e-3
         hbm = kbytes / kern_s / 1e9
@@ -242,9 +253,7 @@ def main():
             out = {"bound": "hbm", "achieved": hbm, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": hbm / HBM_PEAK_GBS,
                    "mfma_frac_same_kernel": mfma / MFMA_PEAK_TFLOPS}
         out.update({"traffic": measured_traffic(name),
-                    "kernel": "vocabulary projection + running log-sum-exp / top-k "
-                              + ("(stream_topk_kernel)" if rows <= 2 else "(rows_topk_kernel)" if rows <= 48 else
-                                 "(head_resident_kernel)" if rows > 128 and K <= 512 else "(head_tile_kernel)"),
+                    "kernel": f"vocabulary projection + running log-sum-exp / top-k ({projection_kernel(rows, K, V, k, full, prepared)[0]})",
                     "kernel_us": kern_ms * 1e3,
                     "kernel_us_minus_empty_event_pair": (kern_ms - null_ms) * 1e3,
                     "empty_event_pair_us": null_ms * 1e3,
@@ -261,7 +270,7 @@ def main():
                 "us_per_call_event_pairs": call_us,
                 "call_hbm_frac": algorithmic_bytes_low_rank(rows, d, r, V, k) / (us * 1e-6) / 1e9 / HBM_PEAK_GBS,
                 "call_mfma_frac": flops / (us * 1e-6) / 1e12 / MFMA_PEAK_TFLOPS,
-                "roofline": roofline_of(name, rows, r, V, kern_ms, null_ms)}
+                "roofline": roofline_of(name, rows, r, V, k, kern_ms, null_ms)}
 
     # ------------------------------------------------------------------ headline workload
     cfg = synth.CONFIGS[args.workload]
@@ -306,7 +315,7 @@ def main():
                                f"{copies} rotating weight copies (cold last-level cache)",
                    "rows": cfg.rows, "d": cfg.d, "r": cfg.r, "V": cfg.V, "k": cfg.k},
         "roofline": roofline_of(cfg.name + ("_full" if full_only else ""), cfg.rows, cfg.d if full_only else cfg.r, cfg.V,
-                                kern_ms, null_ms),
+                                cfg.k, kern_ms, null_ms, full=full_only, prepared=args.prepared),
         "call_hbm_frac": (2.0 * cfg.d * cfg.V if full_only else algorithmic_bytes_low_rank(cfg.rows, cfg.d, cfg.r, cfg.V, cfg.k))
                          / (ms_per_step * 1e-3) / 1e9 / HBM_PEAK_GBS,
         "kernel_sources_sha256": kernel_sources_digest(),
@@ -378,7 +387,7 @@ def main():
         nf = max(10, args.steps // 4)
         fdt, fk, fcall = time_full_tensors(hdev, Ws, cfg.k, nf, 5)
         fms = fdt / nf * 1e3
-        froof = roofline_of(cfg.name + "_full", cfg.rows, cfg.d, cfg.V, fk, null_ms)
+        froof = roofline_of(cfg.name + "_full", cfg.rows, cfg.d, cfg.V, cfg.k, fk, null_ms, full=True)
         extra["full_head"] = {"us_per_call": fms * 1e3, "projection_kernel_us": fk * 1e3,
                               "us_per_call_event_pairs": fcall,
                               "roofline_frac_kernel": froof["frac"], "bound": froof["bound"],
@@ -473,7 +482,7 @@ def main():
                 h4, _, _ = device_inputs(c4.rows, c4.d, 8, 8, 4, 1, peaked_every=c4.peaked_every)
                 sf = 30          # (the first calls after idle run at lower clocks: ten warm-up calls)
                 fdt4, fk4, fcall4 = time_full_tensors(h4, Ws, c4.k, sf, 10)
-                rf4 = roofline_of("C4_full", c4.rows, c4.d, c4.V, fk4, null_ms)
+                rf4 = roofline_of("C4_full", c4.rows, c4.d, c4.V, c4.k, fk4, null_ms, full=True)
                 full512 = {"us_per_call": fdt4 / sf * 1e6, "projection_kernel_us": fk4 * 1e3, "us_per_call_event_pairs": fcall4,
                            "roofline_frac_kernel": rf4["frac"], "bound": rf4["bound"]}
             except Exception as exc:
@@ -487,7 +496,7 @@ def main():
                     edt, ek, ecall = time_low_rank_tensors(h, As, Bs, k, nsteps, 8)
                     extra[name] = low_rank_entry(name, rows, d, r, V, k, edt, nsteps, ek, ecall, null_ms)
                     extra[name]["weight_copies"] = ncopies
-                    if rows >= 5:       # the matrix-core path with the caller's column-major copy of B as well
+                    if rows >= 5:       # with the caller's column-major copy of B as well (read from 33 rows on)
                         qdt, _, _ = time_low_rank_tensors(h, As, Bs, k, nsteps, 8, with_events=False, prepared=True)
                         extra[name]["prepared_weights_us_per_call"] = qdt / nsteps * 1e6
                     if name == "C4_512_rows":

@@ -64,7 +64,7 @@ hipError_t launch_merge(const float2 *part_ms, const float *part_val, const int 
                         int rows, int chunks, int chunk_cols, int V, int k, int32_t *out_ids, float *out_logprobs, const int32_t *id_map,
                         const SampleOut &so, const float4 *part_smp, hipStream_t st);
 
-// ---- matrix-core path (rows > kGemvMaxRows, bf16 weights) ----
+// ---- matrix-core kernels (bf16 weights; plan.hpp says which calls they take) ----
 constexpr int kStreamList = 3;          // groups kept per lane stream
 constexpr int kStreamRec = 3 + 3 * kStreamList;   // floats per stream partial
 constexpr int kStreamRecSample = kStreamRec + 8;  // ... of a sampling call

@@ -1,5 +1,5 @@
-// Merge for the matrix-core path: one block per row turns the row's stream records (one per block of
-// head_tile_kernel that worked on the row, see head_tile.hip) into the final top-k ids and log-probabilities.
+// Merge for head_tile_kernel and head_resident_kernel: one block per row turns the row's stream records (one, two or four
+// per block of the head kernel that worked on the row) into the final top-k ids and log-probabilities.
 //
 // What a stream tells about its share of the row's logits (all values as computed by the
 // matrix cores, i.e. with a 16-bit contraction input in the low-rank head):

@@ -49,3 +49,21 @@ def test_prepared_weights_decide_between_33_and_48_rows(r, V):
 ])
 def test_few_rows_take_the_kernel_that_measures_faster(kind, rows, d, r, V, k, kernel):
     assert plan_of(kind, rows, d, r, V, k)["kernel"] == kernel
+
+
+def test_bench_names_the_kernel_the_library_runs():
+    import os
+    import sys
+    sys.path.insert(0, os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
+    import bench
+    from paper_2605_10453_amd import synth
+    shapes = [(c.rows, c.d, c.r, c.V, c.k) for c in synth.CONFIGS.values()] + [(n, 4096, 512, 128256, 10) for n in (2, 16, 40, 64, 200)]
+    for rows, d, r, V, k in shapes:
+        for prepared in (False, True):
+            name = bench.projection_kernel(rows, r, V, k, prepared=prepared)[0]
+            assert name == {"stream": "stream_topk", "rows": "rows_topk", "tile": "head_tile", "resident": "head_resident"}[
+                plan_of("low", rows, d, r, V, k, prepared=prepared)["kernel"]] + "_kernel", (rows, d, r, V, k, prepared)
+        name = bench.projection_kernel(rows, d, V, k, full=True)[0]
+        if d >= 1024:
+            assert name.split("_kernel")[0] == {"stream": "stream_topk", "rows": "rows_topk", "tile": "head_tile"}[
+                plan_of("full", rows, d, r, V, k)["kernel"]], (rows, d, V, k)
