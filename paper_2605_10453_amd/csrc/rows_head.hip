@@ -204,20 +204,26 @@ __global__ __launch_bounds__(512) void rows_topk_kernel(
             // A logit that is no finite number.  The pieces of t cannot stand for one product with an infinite weight
             // (0 times infinity): sum the chunk's logits of this row again, one multiply-add per weight, from t itself.
             // Eight weights in flight: a row of nothing but such logits comes here in every chunk (one not-a-number row of 4 at
-            // d = 4096, r = 512, V = 128256: 613 us a call with one weight in flight, 147 with eight; 38 without such a row).
+            // d = 4096, r = 512, V = 128256: 611 us a call with one weight in flight, 242 with eight; 38 without such a row).
+            // What this needs is made opaque, or the compiler computes the eight strides ahead for every row and spills scalar
+            // registers for them: 0.4 us at 16 to 32 rows and 1 us at 48 for calls without such logits.
+            const uint16_t *Mq = M;
+            const uint4 *Xq = X;
+            int Vq = V, Kq = K, rowq = row;
+            asm volatile("" : "+s"(Mq), "+s"(Xq), "+s"(Vq), "+s"(Kq), "+s"(rowq));
 #pragma unroll 1
             for (int g = 0; g < G; ++g) {
                 if (!act(g)) continue;
-                const uint16_t *mp = M + chunk_col + 128 * g + 2 * lane;
+                const uint16_t *mp = Mq + chunk_col + 128 * g + 2 * lane;
                 float z0 = 0.f, z1 = 0.f;
 #pragma unroll 1
-                for (int j = 0; j < K; j += 8) {                 // K is a multiple of 8
+                for (int j = 0; j < Kq; j += 8) {                // K is a multiple of 8
                     uint32_t w[8];
                     u32x4 xp[NP];
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) w[u] = *reinterpret_cast<const uint32_t *>(mp + (size_t)(j + u) * V);
+                    for (int u = 0; u < 8; ++u) w[u] = *reinterpret_cast<const uint32_t *>(mp + (size_t)(j + u) * Vq);
 #pragma unroll
-                    for (int p = 0; p < NP; ++p) xp[p] = *reinterpret_cast<const u32x4 *>(X + p * x_piece + (size_t)(j >> 3) * RP + row);
+                    for (int p = 0; p < NP; ++p) xp[p] = *reinterpret_cast<const u32x4 *>(Xq + p * ((size_t)((Kq + 63) / 64 * 8) * RP) + (size_t)(j >> 3) * RP + rowq);
 #pragma unroll
                     for (int u = 0; u < 8; ++u) {
                         float t = 0.f;                           // the pieces' sum, exact: they do not overlap
