@@ -26,8 +26,8 @@
  * Order: descending logit; equal logits: smaller id first.  Logits are accumulated in
  * fp32 from exact bf16 products, and the log-probabilities are fp32 values: their
  * absolute accuracy is that of fp32 at the magnitude of the logits (about 1e-3 at logits
- * of a few thousand, 1e-1 at 1e5), whatever the path.  With up to 48 rows (32 where the caller
- * passes prepared weights and does not sample), and for k > 16, t = h A stays in fp32
+ * of a few thousand, 1e-1 at 1e5), whatever the path.  With up to 48 rows (32 where the
+ * caller passes prepared weights and does not sample and r > 64), and for k > 16, t = h A stays in fp32
  * throughout (r <= 2048; beyond, up to four rows).  With more rows the matrix cores take a 16-bit t (bf16, or f16 for k > 12) for the sum of
  * exponentials and for finding the candidates; every candidate whose rank or reported
  * value could depend on that rounding is then evaluated again from the fp32 t.
@@ -109,7 +109,7 @@ int slimspec_transpose_weights(const void *M, int32_t K, int32_t V, void *Mt, vo
 /* slimspec_head_topk (second display of section 4.1) for weights that do not change
  * between calls, as in serving: the caller also passes Bt[V, r], the column-major copy of B
  * made by slimspec_transpose_weights(B, r, V, Bt).  Same operation and outputs.  From 33
- * rows on (49 for r >= 1024 and V <= 16 r, five for r > 2048) and with k <= 16 the projection runs on 16-bit operands and uncertain ranks are settled
+ * rows on (49 for r <= 64, and for r >= 1024 with V <= 16 r; five for r > 2048) and with k <= 16 the projection runs on 16-bit operands and uncertain ranks are settled
  * by exact fp32 logits of single columns: a column is r adjacent elements of Bt but one
  * element per 128-byte line of B, so these reads shrink by the line length.  Log-probabilities
  * may differ from slimspec_head_topk's in the last bits (another summation order of the exact

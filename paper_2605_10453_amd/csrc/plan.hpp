@@ -313,31 +313,35 @@ constexpr int64_t kRowsMinWeights = 12 << 20;
 //   * k > kMfmaMaxK: always; the lane-owns-columns kernel reads the weights once per 8 rows (40 rows, k = 32: 420 / 61).
 //   * 3 and 4 rows, low-rank: the streaming kernel needs no kernel that finishes t.  It is ahead up to 256 chunks of 512
 //     columns (one round of its blocks) while r is small: r = 256 27.4 / 29.0, 384 34.6 / 35.2, 448 39.6 / 38.2, 512
-//     47.0 / 42.3; r = 256, V = 64000 24.9 / 25.6; beyond 256 chunks (V = 151936) r = 128 29.7 / 24.8, r = 512 71 / 45.  Small
+//     47.0 / 42.3; r = 256, V = 64000 24.9 / 25.6, r = 320 27.3 / 26.7; beyond 256 chunks (V = 151936) r = 128 29.7 / 24.8, r = 512 71 / 45.  Small
 //     weights: r = 200, V = 32000 20.6 / 22.6, r = 512, V = 32000 33.6 / 27.4.  Two rows: 39.3 / 41.9.
 //   * full head, from 2 rows: 188.9 / 185.3; d = 1024, V = 8192 24.3 / 17.8.  Two rows with d = 256, V = 32000: 15.7 / 16.4.
 //   * up to 32 rows, k <= kMfmaMaxK: 23 rows 58.0 / 48.7; with prepared weights 24 rows 51.2 / 48.5, 32 rows 51.9 / 50.8.
-//   * about 32 to 48 rows: a wavefront finishes up to six rows after the weights, which a short contraction does not pay
-//     for, while head_tile_kernel's cost stays the same and its merge is cheap with prepared weights or small k.
+//   * 33 to 48 rows: a wavefront finishes up to six rows after the weights, which a short contraction does not pay for,
+//     while head_tile_kernel's cost stays the same and its merge is cheap with prepared weights or few candidates.
 //       prepared: 33 rows 51.0 / 54.4, 48 rows 51.5 / 58.9 (r = 1024: 76.8 / 84.1); this kernel only where few tiles of the
-//         vocabulary leave head_tile_kernel long contractions on few CUs (48 rows, r = 2048: V = 32000 74 / 68, V = 8192 68 / 53);
+//         vocabulary leave head_tile_kernel long contractions on few CUs (48 rows, r = 2048: V = 32000 74 / 68, V = 8192 68 / 53)
+//         and for the smallest ranks, whose wide rounding bounds send peaked rows to head_tile_kernel's exact passes now and then
+//         (48 rows, r = 64: V = 32000 28.0 / 29.7, V = 128256 211 / 36);
 //       plain low-rank calls stay, and with them their fp32 t: 48 rows, k = 10 0.99 to 1.4 times as fast; with k = 3 and r = 256
 //         they give up a little (40 rows, V = 8192 30.9 / 33.1, 48 rows, V = 32000 34.1 / 36.9);
 //       full head, k = 4, 48 rows: d = 256 22.7 / 28.8 at V = 32000, 30.0 / 34.4 at V = 128256; d = 1024 41.8 / 36.0 and 67.3 / 66.3.
-//         Up to d = 768 behind for k <= 6 unless V is small, at k = 10 (more re-evaluations) only with d <= 512 and a large V.
+//         The other path's re-evaluated columns cost in proportion to k d, this one's epilogue to V: it is behind up to d = 768 while
+//         k d stays below about 17 sqrt(V) and k below 16 (V = 8192: k = 4, d = 256 22.8 / 26.9, 36 rows, k = 6, d = 512 31.6 / 26.6; V =
+//         128256: k = 10, d = 512 46.1 / 47.0, k = 16 51.8 / 47.4), not with so small a V that head_tile_kernel's blocks are few (d = 768, V = 8192, k = 1 28.3 / 25.3).
 //     Sampling calls stay: the noise is dearer in head_tile_kernel (r = 64, V = 8192, 48 rows 47.2 / 33.4).
 //   * more rows would need a second launch, and lose.
 inline bool rows_path_takes(HeadKind kind, int rows, int d, int r, int V, int k, bool prepared, bool sampling) {
     const bool low_rank = kind == HeadKind::LowRank;
     if (rows < 2 || !rows_path_fits(kind, d, r)) return false;
     if (low_rank && rows <= 4)
-        return rows > 2 && (int64_t)r * V >= kRowsMinWeights && (V > 256 * kChunkCols || r > 384);
+        return rows > 2 && (int64_t)r * V >= kRowsMinWeights && (V > 256 * kChunkCols || r > (V > 65536 ? 384 : 256));
     if (k > kMfmaMaxK) return true;
     if (!low_rank && rows == 2) return d > 256;
     if (rows > kRowsMaxRows) return false;
-    if (rows < 32 || sampling) return true;
-    if (!low_rank) return !(d <= 768 && V >= 16 * d && k <= 6) && !(d <= 512 && V >= 100 * d && k <= 10);
-    return rows == 32 || !prepared || (r >= 1024 && V <= 16 * r);
+    if (rows <= 32 || sampling) return true;
+    if (!low_rank) return d > 768 || k > 10 || V < 16 * d || (int64_t)k * d * k * d > (int64_t)300 * V;
+    return !prepared || r <= 64 || (r >= 1024 && V <= 16 * r);
 }
 
 inline bool tile_path_takes(int rows, int k) { return rows >= kMfmaMinRows && k <= kMfmaMaxK; }

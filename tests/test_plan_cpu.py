@@ -38,14 +38,17 @@ def test_prepared_weights_decide_between_33_and_48_rows(r, V):
         assert plan_of("low", rows, 8 * r, r, V, 10, prepared=True)["kernel"] == "tile"
         assert plan_of("low", rows, 8 * r, r, V, 10, prepared=True, sampling=True)["kernel"] == ("rows" if rows <= 48 else "tile")
     assert plan_of("low", 40, 8 * r, r, V, 40, prepared=True)["kernel"] == "rows"          # a list the records cannot hold
+    assert plan_of("low", 48, 512, 64, V, 10, prepared=True)["kernel"] == "rows"           # wide rounding bounds
 
 
 @pytest.mark.parametrize("kind,rows,d,r,V,k,kernel", [
-    ("low", 4, 2048, 256, 128256, 10, "stream"), ("low", 3, 4096, 512, 128256, 10, "rows"), ("low", 4, 1024, 128, 151936, 32, "rows"),
+    ("low", 4, 2048, 256, 128256, 10, "stream"), ("low", 4, 3072, 384, 128256, 10, "stream"), ("low", 4, 2560, 320, 64000, 10, "rows"),
+    ("low", 3, 4096, 512, 128256, 10, "rows"), ("low", 4, 1024, 128, 151936, 32, "rows"),
     ("low", 4, 4096, 512, 16384, 10, "stream"), ("low", 2, 4096, 512, 128256, 40, "stream"), ("low", 48, 2048, 256, 32000, 3, "rows"),
     ("full", 2, 256, 8, 32000, 10, "stream"), ("full", 2, 264, 8, 32000, 10, "rows"),
     ("full", 33, 512, 8, 64000, 1, "tile"), ("full", 48, 1024, 8, 64000, 1, "rows"), ("full", 48, 768, 8, 8192, 4, "rows"),
-    ("full", 40, 512, 8, 128256, 10, "tile"), ("full", 40, 512, 8, 128256, 16, "rows"), ("full", 31, 256, 8, 8192, 1, "rows"), ("full", 32, 256, 8, 8192, 1, "tile"),
+    ("full", 40, 512, 8, 128256, 10, "tile"), ("full", 40, 512, 8, 128256, 16, "rows"), ("full", 32, 256, 8, 8192, 1, "rows"),
+    ("full", 33, 256, 8, 8192, 1, "tile"), ("full", 36, 512, 8, 8192, 6, "rows"), ("full", 36, 640, 8, 8192, 1, "rows"),
 ])
 def test_few_rows_take_the_kernel_that_measures_faster(kind, rows, d, r, V, k, kernel):
     assert plan_of(kind, rows, d, r, V, k)["kernel"] == kernel
