@@ -169,10 +169,10 @@ __global__ __launch_bounds__(256) void down_tile_kernel(
 #pragma unroll
     for (int i = 0; i < 16; ++i) { acc0[i] = 0.f; acc1[i] = 0.f; }
 
-    // stages [s_beg, s_end) of the d / 32 full ones; what is left of d (8, 16 or 24 elements) is added by the finish kernel
-    const int n_full = d / kDKB;
-    const int per = (n_full + g.slices - 1) / g.slices;
-    const int s_beg = min(n_full, slice * per), s_end = min(n_full, s_beg + per);
+    // stages [s_beg, s_end); the last stage of all may hold 8, 16 or 24 elements only (see `ragged`)
+    const int n_stages = (d + kDKB - 1) / kDKB;
+    const int per = (n_stages + g.slices - 1) / g.slices;
+    const int s_beg = min(n_stages, slice * per), s_end = min(n_stages, s_beg + per);
     const int nst = (n0 < r) ? s_end - s_beg : 0;                         // columns of padding load nothing
     if (nst > 0) {
         // The two loads of this wavefront per stage:
@@ -182,8 +182,18 @@ __global__ __launch_bounds__(256) void down_tile_kernel(
         //   h: rows 16 wave + lane % 16, 8-element group lane / 16 of the stage (rows beyond the last: the last)
         const int a_row = 8 * wave + (lane >> 3);
         const int a_piece = (lane & 7) ^ ((a_row & 2) << 1);
-        const uint32_t a_off = (uint32_t)a_row * (uint32_t)r * 2u + (uint32_t)min(n0 + 8 * a_piece, r - 8) * 2u;
-        const uint32_t h_off = (uint32_t)min(row0 + 16 * wave + (lane & 15), rows - 1) * (uint32_t)d * 2u + (uint32_t)(lane >> 4) * 16u;
+        // A stage that reaches beyond d re-reads its last row of A and its last group of h there, and both operands of
+        // those elements are cleared before they are multiplied (d is a multiple of 8: a lane's 8 elements exist or none do).
+        // (Left to the finish kernel, one multiply-add at a time, 8 elements cost it 2 us and 24 took 10 to 13: 17.0 us
+        // instead of 4.4 at 57 rows, d = 2808, r = 480.)
+        uint32_t a_off, h_off;
+        const auto set_offsets = [&](int stage) {
+            const int left = d - kDKB * stage;
+            a_off = (uint32_t)min(a_row, left - 1) * (uint32_t)r * 2u + (uint32_t)min(n0 + 8 * a_piece, r - 8) * 2u;
+            h_off = (uint32_t)min(row0 + 16 * wave + (lane & 15), rows - 1) * (uint32_t)d * 2u + (uint32_t)min(lane >> 4, (left >> 3) - 1) * 16u;
+        };
+        set_offsets(s_beg);
+        const bool ragged = s_end == n_stages && (d & (kDKB - 1)) != 0;      // this slice ends with such a stage
         // (Blocks of one XCD walk the same slice in step.  Starting them at different points of it, so that they
         // prefetch for each other, measured slower: 10.0 against 8.9 us at 512 rows.)
         const unsigned char *a_ptr = reinterpret_cast<const unsigned char *>(A) + (size_t)s_beg * kDKB * r * 2;
@@ -196,7 +206,10 @@ __global__ __launch_bounds__(256) void down_tile_kernel(
             dma16(buf_ahead + a_lds, a_off, a_ptr);
             dma16(buf_ahead + h_lds, h_off, h_ptr);
             // past the end the last stage is loaded once more (into a buffer nobody reads): the count stays uniform
-            if (++issued < nst) { a_ptr += a_step; h_ptr += h_step; }
+            if (++issued < nst) {
+                a_ptr += a_step; h_ptr += h_step;
+                if (ragged && issued == nst - 1) set_offsets(s_end - 1);
+            }
             buf_ahead = (buf_ahead + kDStageBytes == lds0 + kDLds) ? lds0 : buf_ahead + kDStageBytes;
         };
 #pragma unroll
@@ -218,6 +231,14 @@ __global__ __launch_bounds__(256) void down_tile_kernel(
                 const v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_PTR(v4i16, buf + ma + ks * 2048));
                 const v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_PTR(v4i16, buf + ma + ks * 2048 + 512));
                 mf[ks] = __builtin_bit_cast(u32x4, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+            }
+            if (ragged && q == nst - 1) {
+#pragma unroll
+                for (int ks = 0; ks < 2; ++ks) {
+                    const uint32_t keep = (kDKB * (s_end - 1) + 16 * ks + 8 * half < d) ? 0xffffffffu : 0u;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) { xf[ks][e] &= keep; mf[ks][e] &= keep; }
+                }
             }
             f32x16 c0 = acc0, c1 = acc1;
             if constexpr (STEPWISE) {
@@ -249,8 +270,7 @@ __global__ __launch_bounds__(256) void down_tile_kernel(
 // The pieces are cut off the top of t's significand, 8 bits each: their sum is t exactly.
 template <bool PIECES>
 __global__ __launch_bounds__(256) void down_finish_kernel(
-    const float *__restrict__ part, const uint16_t *__restrict__ h, const uint16_t *__restrict__ A,
-    int rows_pad, int d, int r,
+    const float *__restrict__ part, int rows_pad, int r,
     float *__restrict__ t32, uint4 *__restrict__ t16, float2 *__restrict__ stat,
     const uint16_t *__restrict__ B, int V, float2 *__restrict__ tilescale, int as_f16, DownGrid g)
 {
@@ -270,12 +290,10 @@ __global__ __launch_bounds__(256) void down_finish_kernel(
     const int row0 = g.g_row0[grp] + (rt - g.g_tile0[grp]) * kDT + 32 * (w >> 1), n0 = ct * kDT + 32 * (w & 1);
     const int row_end = g.g_row0[grp + 1];                     // this piece's rows end with its group
     const int rows = (grp < g.n_groups) ? row_end : 0;         // rows that carry values
-    A += (size_t)g.g_mat[grp < g.n_groups ? grp : 0] * d * r;
 
     // the slices, in order: several loads of a thread are in flight together (they come from other CUs' writes)
     const size_t slice_stride = (size_t)g.n_rt * g.n_ct * 4 * (16 * 64);
     const float *src = part + (((size_t)rt * g.n_ct + ct) * 4 + w) * (16 * 64);
-    const int k_tail0 = (d / kDKB) * kDKB;
     // a thread owns four (i, lane) pairs of the accumulator layout; the loads of SB slices of all four are in flight together
     constexpr int SB = 8;
     float v4[4] = {0.f, 0.f, 0.f, 0.f};
@@ -299,14 +317,8 @@ __global__ __launch_bounds__(256) void down_finish_kernel(
     for (int e = 0; e < 4; ++e) {
         const int qq = tid + 256 * e;                          // (i, lane) pair
         const int i = qq >> 6, ln = qq & 63;
-        float v = v4[e];
         const int row = ln & 31, n = 8 * (i >> 2) + 4 * (ln >> 5) + (i & 3);
-        if (k_tail0 < d && row0 + row < rows && n0 + n < r) {
-            const uint16_t *hr = h + (size_t)(row0 + row) * d;
-            for (int kk = k_tail0; kk < d; ++kk)
-                v = fmaf(bf16_to_float(hr[kk]), bf16_to_float(A[(size_t)kk * r + n0 + n]), v);
-        }
-        tile[row * 33 + n] = v;
+        tile[row * 33 + n] = v4[e];
     }
     __syncthreads();
 
@@ -406,7 +418,7 @@ hipError_t launch_down_projection_tiles(const uint16_t *h, const uint16_t *A, fl
     const hipError_t e = launch_down_tiles<false>(h, A, part, g, d, r, st);
     if (e != hipSuccess) return e;
     down_finish_kernel<false><<<4 * g.n_rt_all * g.n_ct + (V + 511) / 512, 256, 0, st>>>(
-        part, h, A, rows_pad, d, r, t32, static_cast<uint4 *>(t16), stat, B, V, tilescale, as_f16 ? 1 : 0, g);
+        part, rows_pad, r, t32, static_cast<uint4 *>(t16), stat, B, V, tilescale, as_f16 ? 1 : 0, g);
     return hipGetLastError();
 }
 
@@ -416,7 +428,7 @@ hipError_t launch_down_projection_pieces(const uint16_t *h, const uint16_t *A, f
     const hipError_t e = launch_down_tiles<true>(h, A, part, g, d, r, st);
     if (e != hipSuccess) return e;
     down_finish_kernel<true><<<4 * g.n_rt_all * g.n_ct, 256, 0, st>>>(
-        part, h, A, rows_pad, d, r, nullptr, static_cast<uint4 *>(X), nullptr, nullptr, 0, nullptr, 0, g);
+        part, rows_pad, r, nullptr, static_cast<uint4 *>(X), nullptr, nullptr, 0, nullptr, 0, g);
     return hipGetLastError();
 }
 

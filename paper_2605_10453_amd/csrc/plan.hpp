@@ -153,10 +153,10 @@ inline DownGrid make_down_grid(int rows, int rows_pad, int d, int r, int n_group
     g.g_row0[n_groups + 1] = rows_pad; g.g_tile0[n_groups + 1] = tile;
     g.n_rt_all = tile;
     g.n_ct = (r + 63) / 64;
-    const int tiles = g.n_rt * g.n_ct, n_full = d / 32;
+    const int tiles = g.n_rt * g.n_ct, n_stages = (d + 31) / 32;
     // (two blocks per CU, i.e. twice the slices, measured slower: 10.7 + 4.6 against 8.9 + 4.5 us at 512 rows)
     // (at most 16 slices: with 32, at 16 and 64 rows, the tile kernel measures the same and the sum of the slices 1.1 us more)
-    while (g.slices < 16 && tiles * g.slices < 256 && n_full / (2 * g.slices) >= 2) g.slices *= 2;
+    while (g.slices < 16 && tiles * g.slices < 256 && n_stages / (2 * g.slices) >= 2) g.slices *= 2;
     return g;
 }
 // Partial tiles of t, in 64 x 64 tiles of floats, for any grouping of `rows` rows into at most kMaxPositions groups:
