@@ -1,6 +1,5 @@
-// Device-side pieces shared by the streaming ("lane owns columns") kernels: raw weight loads,
-// the per-chunk epilogue (running max, sum of exp, top-k of one 512-column chunk) and the
-// per-row merge of the chunk partials.
+// Device-side pieces shared by the streaming ("lane owns columns") kernels: raw weight loads and
+// the per-chunk epilogue (running max, sum of exp, top-k of one 512-column chunk).
 #pragma once
 #include "device_utils.hpp"
 #include "plan.hpp"
@@ -150,7 +149,7 @@ __device__ __forceinline__ void wave_topk(const uint32_t (&ob)[E], int n_e, Id i
     };
     int n = compact();
     if (n > 64 && n > k + kCandSlack) {
-        uint32_t hi = 0xffffffffu;                               // no element's bits reach it
+        uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)sorted) + 1u;      // no element's bits reach it
         while (n > k + kCandSlack && hi - T > 1u) {
             const uint32_t mid = T + (hi - T) / 2;
             int c = 0;
@@ -253,166 +252,6 @@ __device__ __forceinline__ void chunk_row_epilogue(ChunkLds<R, NW> &L, int i, in
     for (int e = 0; e < 8; ++e) ob[e] = active ? float_order_bits(z[e]) : 0u;
     wave_topk<8>(ob, 8, [&](int e) { return (uint32_t)(col + e); }, lane, k, L.sel_cand[wave], kChunkCols,
                  part_val + slot * k, part_id + slot * k);
-}
-
-// ---------------------------------------------------------------------------
-// Merge of one row's chunk partials (running max m_c, sum of exp s_c, sorted top-k list per chunk):
-//     lse = M + ln sum_c s_c exp(m_c - M),   M = max_c m_c
-// and the k globally first (logit desc, id asc) candidates.  The order of every reduction is fixed
-// and the selection works on unique keys, so the output does not depend on scheduling.
-//
-// Partials of one row cover increasing, disjoint id ranges and each list is already in output
-// order, so "smaller list position e = c * k + p" breaks ties exactly like "smaller id".
-//   (1) the k-th largest list head (by all-pairs counting) bounds the answer from below;
-//   (2) the entries that reach the bound (at most k lists, k entries each) are gathered;
-//   (3) they are ranked among themselves by counting; ranks below k are the output.
-// last_len: columns in the last chunk's list (the others hold k).
-// NT threads (a multiple of 64, at most 1024) call together; `dyn` holds merge_lds_bytes(chunks, k, cache_ids).
-struct MergeSmall {
-    float red_m[16], red_s[16];
-    uint64_t bound;
-    uint32_t cnt;
-    uint32_t winners[SLIMSPEC_KMAX_INTERNAL];
-    uint64_t smp_key[16];
-    float smp_z[16];
-};
-
-template <int NT>
-__device__ __forceinline__ void merge_row(unsigned char *dyn, bool cache_ids, MergeSmall &S, int tid,
-                                          const float2 *__restrict__ ms, const float *__restrict__ pv,
-                                          const int *__restrict__ pi, int chunks, int k, int last_len,
-                                          int32_t *__restrict__ out_ids, float *__restrict__ out_logprobs,
-                                          const int32_t *__restrict__ id_map,
-                                          const float4 *__restrict__ smp, float *__restrict__ out_lse,
-                                          int32_t *__restrict__ out_sample_id, float *__restrict__ out_sample_lp)
-{
-    constexpr int NWAVES = NT / 64;
-    uint64_t *heads = reinterpret_cast<uint64_t *>(dyn);                      // [chunks]
-    uint64_t *cand = heads + chunks;                                           // [k * k]
-    float *vals = reinterpret_cast<float *>(cand + (size_t)k * k);            // [chunks * k]
-    int *ids = reinterpret_cast<int *>(vals + (size_t)chunks * k);            // [chunks * k]
-    const int lane = tid & 63, wave = tid >> 6;
-
-    const int n = chunks * k;
-    // The partials were written by other CUs: every load is a trip to the memory side.  All loads of a thread are
-    // therefore issued before the first of them is used (four list entries per thread and trip, and the first
-    // chunk's head and (max, sum) with them), instead of one trip per loop iteration.
-    const bool own_chunk = tid < chunks;
-    const float head0 = own_chunk ? pv[(size_t)tid * k] : 0.f;
-    const float2 ms0 = own_chunk ? ms[tid] : make_float2(kNegInf, 0.f);
-    for (int e0 = tid; e0 < n; e0 += 4 * NT) {
-        float v[4];
-        int id[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int e = min(e0 + u * NT, n - 1);
-            v[u] = pv[e];
-            id[u] = cache_ids ? pi[e] : 0;              // when they fit: no dependent load at the end
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int e = e0 + u * NT;
-            if (e < n) {
-                vals[e] = v[u];
-                if (cache_ids) ids[e] = id[u];
-            }
-        }
-    }
-    if (tid == 0) { S.bound = kNoKey; S.cnt = 0u; }
-
-    // log-sum-exp: every thread folds its chunks in increasing order, then the block combines
-    float m_t = kNegInf, s_t = 0.f;
-    for (int c = tid; c < chunks; c += NT) {
-        const bool first = c == tid;
-        heads[c] = make_key(first ? head0 : pv[(size_t)c * k], (uint32_t)(c * k));
-        const float2 p = first ? ms0 : ms[c];
-        if (p.x == kNegInf) continue;                   // no logit above -inf: nothing to add (its sum is not a number)
-        const float m_new = fmaxf(m_t, p.x);
-        s_t = s_t * fast_exp(m_t - m_new) + p.y * fast_exp(p.x - m_new);
-        m_t = m_new;
-    }
-    const float m_w = wave_max(m_t);
-    float s_w = (m_t == kNegInf) ? 0.f : s_t * fast_exp(m_t - m_w);
-    s_w = wave_sum(s_w);
-    if (lane == 0) { S.red_m[wave] = m_w; S.red_s[wave] = s_w; }
-    __syncthreads();
-    float M = S.red_m[0];
-#pragma unroll
-    for (int w = 1; w < NWAVES; ++w) M = fmaxf(M, S.red_m[w]);
-    float Ssum = 0.f;
-#pragma unroll
-    for (int w = 0; w < NWAVES; ++w) Ssum += (S.red_m[w] == kNegInf) ? 0.f : S.red_s[w] * fast_exp(S.red_m[w] - M);
-    const float lse = M + fast_log(Ssum);
-    if (smp) {
-        // stochastic-decoding outputs: the row's log-sum-exp and the Gumbel-max draw (largest z + g over the chunks)
-        uint64_t best = kNoKey;
-        float zb = 0.f;
-        for (int c = tid; c < chunks; c += NT) {
-            const float4 e = smp[c];
-            const uint64_t key = make_key(e.x, (uint32_t)__float_as_int(e.y));
-            if (key > best) { best = key; zb = e.z; }
-        }
-        const uint64_t top_w = wave_max_key(best);
-        if (lane == 0) S.smp_key[wave] = top_w;
-        if (best == top_w && best != kNoKey) S.smp_z[wave] = zb;
-        __syncthreads();
-        if (tid == 0) {
-            int wb = 0;
-            for (int w = 1; w < NWAVES; ++w) if (S.smp_key[w] > S.smp_key[wb]) wb = w;
-            const int id = (int)key_tiebreak(S.smp_key[wb]);
-            *out_lse = lse;
-            *out_sample_id = id_map ? id_map[id] : id;
-            *out_sample_lp = S.smp_z[wb] - lse;
-        }
-    }
-
-    // (1) the k-th largest head: four adjacent lanes share one head, each counts a quarter of the others
-    {
-        const int quarter = (chunks + 3) / 4;
-        const int q0 = (tid & 3) * quarter, q1 = min(chunks, q0 + quarter);
-        for (int c0 = 0; c0 < chunks; c0 += NT / 4) {              // trip count uniform over the block
-            const int c = c0 + (tid >> 2);
-            const uint64_t mine = heads[min(c, chunks - 1)];
-            int rank = 0;
-#pragma unroll 8
-            for (int q = q0; q < q1; ++q) rank += (heads[q] > mine) ? 1 : 0;
-            rank += __shfl_xor(rank, 1);
-            rank += __shfl_xor(rank, 2);
-            if (c < chunks && (tid & 3) == 0 && rank == k - 1) S.bound = mine;      // keys are unique: one writer at most
-        }
-    }
-    __syncthreads();
-    const uint64_t bound = S.bound;                     // kNoKey when there are fewer than k lists: keep everything
-    // (2) gather what reaches the bound
-    for (int c = tid; c < chunks; c += NT) {
-        if (heads[c] < bound) continue;
-        // (only the last chunk can have fewer than k columns, and filler at the end of its list: a logit of -inf is an
-        // entry like any other, wanted where the row has fewer than k logits above it)
-        const int len = c == chunks - 1 ? last_len : k;
-        for (int p = 0; p < len; ++p) {
-            const uint64_t key = make_key(vals[c * k + p], (uint32_t)(c * k + p));
-            if (key < bound) break;                     // lists are sorted
-            cand[atomicAdd(&S.cnt, 1u)] = key;
-        }
-    }
-    __syncthreads();
-    // (3) rank the gathered entries
-    const int n_cand = (int)S.cnt;
-    for (int c = tid; c < n_cand; c += NT) {
-        const uint64_t mine = cand[c];
-        int rank = 0;
-#pragma unroll 8
-        for (int q = 0; q < n_cand; ++q) rank += (cand[q] > mine) ? 1 : 0;
-        if (rank < k) S.winners[rank] = key_tiebreak(mine);
-    }
-    __syncthreads();
-    if (tid < k) {                                      // n_cand >= k: k heads, or (fewer lists) every column of lists that hold min(k, columns) each
-        const uint32_t e = S.winners[tid];
-        const int id = cache_ids ? ids[e] : pi[e];
-        out_ids[tid] = id_map ? id_map[id] : id;                // truncated vocabulary: column -> vocabulary id
-        out_logprobs[tid] = vals[e] - lse;
-    }
-    __syncthreads();                                    // the buffers may be reused for the next row
 }
 
 }  // namespace slimspec

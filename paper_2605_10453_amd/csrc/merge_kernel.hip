@@ -1,39 +1,296 @@
-// Cross-workgroup merge for the streaming path: one block per row combines the row's chunk
-// partials into the final ids and log-probabilities (see merge_row in gemv_parts.hpp).
+// Cross-workgroup merge for the streaming path and for rows_topk_kernel: one block per row combines the row's chunk
+// partials (running max m_c, sum of exp s_c, top-k list per chunk) into the final ids and log-probabilities:
+//     lse = M + ln sum_c s_c exp(m_c - M),   M = max_c m_c
+// and the k first (logit desc, id asc) of all lists' entries.  The order of every reduction is fixed and the selection
+// works on unique keys (order bits of the logit, then the inverted id), so the output does not depend on scheduling.
+//
+// What bounds it: latency.  The partials were written by other CUs, so every load is a trip to the memory side (about
+// 1 us), and a block-wide step costs a barrier; there is hardly any work.  So one wavefront does everything that is a
+// chain, without barriers, and the others only fetch lists:
+//   (1) wavefront 0 reads the chunk maxima (the lists' heads), up to 8 per lane in flight, and folds the log-sum-exp.
+//       T = the k-th largest of its 64 lanes' maxima: k heads reach it, so it bounds the answer from below.  (All-pairs
+//       counting of 251 heads by 1024 threads took longer than the loads: 6.6 us a launch, 13.5 with 500 chunks and a draw.)
+//       Wavefront 1 meanwhile finds the draw of a sampling call.
+//   (2) all threads: the lists' entries that reach T go to shared memory.  Where a row has few entries they were
+//       requested at the start, before T is known (one trip instead of two); otherwise the first eight of the lists whose
+//       heads reach T are read, and more of a list only where all eight are taken.
+//   (3) wavefront 0 selects and ranks the k first of them.
 #include "gemv_parts.hpp"
 #include "launch.hpp"
 
 namespace slimspec {
 
-constexpr int kRowMergeThreads = 1024;   // one block per row: the more threads, the shorter the load and rank phases
+namespace {
+
+constexpr int kRowMergeThreads = 512;
+constexpr int kMergeHeads = 8;                                   // heads per lane in flight
+constexpr int kMergeAhead = 5;                                   // entries per thread that are requested before T is known
+constexpr int kMergeLists = SLIMSPEC_KMAX_INTERNAL + kCandSlack; // lists that may hold winners, at most
+constexpr int kMergeCand = kMergeLists * SLIMSPEC_KMAX_INTERNAL; // their entries, at most
+constexpr int kMergeSel = 256;                                   // entries that are ranked all pairs, at most
+static_assert(kMergeAhead * kRowMergeThreads <= kMergeCand, "entries taken ahead fit as well");
+static_assert(kMergeSel >= 2 * kMergeLists, "what a bound admits beyond this many are equal logits");
+
+struct MergeLds {
+    uint64_t cand[kMergeCand];
+    uint64_t sel[kMergeSel];
+    int list[kMergeLists];
+    uint32_t n_list, n_cand, T, all_lists;
+    uint64_t draw;
+    float draw_z;
+};
+
+// The k largest of n keys in shared memory, by one wavefront: f(key, rank).
+template <class F>
+__device__ __forceinline__ void wave_rank_keys(const uint64_t *keys, int n, int k, int lane, F f) {
+    for (int c0 = 0; c0 < n; c0 += 64) {
+        const int c = c0 + lane;
+        const uint64_t mine = (c < n) ? keys[c] : kNoKey;
+        int rank = 0;
+#pragma unroll 8
+        for (int q = 0; q < n; ++q) rank += (keys[q] > mine) ? 1 : 0;
+        if (c < n && rank < k) f(mine, rank);
+    }
+}
+
+}  // namespace
 
 __global__ __launch_bounds__(kRowMergeThreads) void merge_kernel(
     const float2 *__restrict__ part_ms, const float *__restrict__ part_val, const int *__restrict__ part_id,
-    int chunks, int k, int last_len, int cache_ids, int32_t *__restrict__ out_ids, float *__restrict__ out_logprobs,
+    int chunks, int k, int last_len, int32_t *__restrict__ out_ids, float *__restrict__ out_logprobs,
     const int32_t *__restrict__ id_map, SampleOut so, const float4 *__restrict__ part_smp)
 {
-    extern __shared__ __align__(16) unsigned char lds_raw[];
-    __shared__ MergeSmall small;
-    const int row = blockIdx.x;
-    merge_row<kRowMergeThreads>(lds_raw, cache_ids != 0, small, threadIdx.x, part_ms + (size_t)row * chunks,
-                             part_val + (size_t)row * chunks * k, part_id + (size_t)row * chunks * k,
-                             chunks, k, last_len, out_ids + (size_t)row * k, out_logprobs + (size_t)row * k, id_map,
-                             so.on ? part_smp + (size_t)row * chunks : nullptr, so.lse + row, so.sample_ids + row, so.sample_logprobs + row);
+    __shared__ MergeLds S;
+    constexpr int NT = kRowMergeThreads, H = kMergeHeads;
+    const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const float2 *ms = part_ms + (size_t)row * chunks;
+    const float *pv = part_val + (size_t)row * chunks * k;
+    const int *pi = part_id + (size_t)row * chunks * k;
+
+    // Entries of the last chunk's list from last_len on are filler (it may have fewer than k columns; the others have k).
+    const int n_entries = (chunks - 1) * k + last_len;
+    const bool ahead = n_entries <= kMergeAhead * NT;
+    float2 hm[H];
+    if (wave == 0) {
+#pragma unroll
+        for (int e = 0; e < H; ++e) hm[e] = ms[min(64 * e + lane, chunks - 1)];
+    }
+    float v_ahead[kMergeAhead];
+    int id_ahead[kMergeAhead];
+    if (ahead) {
+#pragma unroll
+        for (int u = 0; u < kMergeAhead; ++u) {
+            const int e = min(tid + u * NT, n_entries - 1);
+            v_ahead[u] = pv[e];
+            id_ahead[u] = pi[e];
+        }
+    }
+
+    float lse = 0.f;
+    if (wave == 0) {
+        // this lane's chunks in increasing order, H at a time
+        const auto load_heads = [&](int c0) {
+            if (c0 == 0 && chunks <= 64 * H) return;             // still in registers
+#pragma unroll
+            for (int e = 0; e < H; ++e) hm[e] = ms[min(c0 + 64 * e + lane, chunks - 1)];
+        };
+        const auto bits_of = [&](int c0, int e) { return (c0 + 64 * e + lane < chunks) ? float_order_bits(hm[e].x) : 0u; };
+        float m_t = kNegInf, s_t = 0.f;
+        uint32_t lane_bits = 0u;
+        for (int c0 = 0; c0 < chunks; c0 += 64 * H) {
+            load_heads(c0);
+            float m_new = m_t;
+#pragma unroll
+            for (int e = 0; e < H; ++e) {
+                if (c0 + 64 * e + lane < chunks) m_new = fmaxf(m_new, hm[e].x);
+                lane_bits = max(lane_bits, bits_of(c0, e));
+            }
+            s_t = (m_t == kNegInf) ? 0.f : s_t * fast_exp(m_t - m_new);
+#pragma unroll
+            for (int e = 0; e < H; ++e)                          // a chunk with no logit above -inf adds nothing (its sum is not a number)
+                if (c0 + 64 * e + lane < chunks && hm[e].x != kNegInf) s_t += hm[e].y * fast_exp(hm[e].x - m_new);
+            m_t = m_new;
+        }
+        const float M = wave_max(m_t);
+        const float s = wave_sum(m_t == kNegInf ? 0.f : s_t * fast_exp(m_t - M));
+        lse = M + fast_log(s);
+
+        const uint32_t sorted = wave_sort_desc(lane_bits, lane);
+        uint32_t T = max(1u, (uint32_t)__builtin_amdgcn_readlane((int)sorted, k - 1));      // fewer than k lists: everything
+        const auto count = [&](uint32_t bound) {
+            int n = 0;
+            for (int c0 = 0; c0 < chunks; c0 += 64 * H) {
+                load_heads(c0);
+#pragma unroll
+                for (int e = 0; e < H; ++e) n += __popcll(__ballot(bits_of(c0, e) >= bound));
+            }
+            return n;
+        };
+        // many lists at the bound (k close to 64): raise it while k of them reach it
+        int n = count(T), above = 0;
+        if (n > k + kCandSlack) {
+            uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)sorted) + 1u;        // no head reaches it
+            while (n > k + kCandSlack && hi - T > 1u) {
+                const uint32_t mid = T + (hi - T) / 2;
+                const int c = count(mid);
+                if (c >= k) { T = mid; n = c; } else { hi = mid; above = c; }
+            }
+        }
+        // Still more: lists with equal heads.  Of those, the first ones of the row suffice: their heads precede
+        // every entry of the later ones.
+        const bool ties = n > k + kCandSlack;
+        int quota = ties ? k - above : n;                        // lists with a head equal to T that are taken (above: the heads beyond it)
+        int at = 0;
+        for (int c0 = 0; c0 < chunks; c0 += 64 * H) {
+            load_heads(c0);
+#pragma unroll
+            for (int e = 0; e < H; ++e) {
+                const uint32_t b = bits_of(c0, e);
+                bool take = b >= T;
+                if (ties) {
+                    const uint64_t equal = __ballot(b == T);
+                    const int before = __builtin_amdgcn_mbcnt_hi((uint32_t)(equal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)equal, 0u));
+                    take = b > T || (b == T && before < quota);
+                    quota = max(0, quota - (int)__popcll(equal));
+                }
+                const uint64_t mask = __ballot(take);
+                const int slot = at + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+                if (take && slot < kMergeLists) S.list[slot] = c0 + 64 * e + lane;
+                at += __popcll(mask);
+            }
+        }
+        if (lane == 0) { S.n_list = (uint32_t)min(at, kMergeLists); S.n_cand = 0u; S.T = T; S.all_lists = ties ? 0u : 1u; }
+    } else if (wave == 1 && part_smp) {
+        // the Gumbel-max draw: the largest z + g over the chunks (unique keys)
+        const float4 *smp = part_smp + (size_t)row * chunks;
+        uint64_t best = kNoKey;
+        float zb = 0.f;
+        for (int c0 = 0; c0 < chunks; c0 += 64 * H) {
+            float4 x[H];
+#pragma unroll
+            for (int e = 0; e < H; ++e) x[e] = smp[min(c0 + 64 * e + lane, chunks - 1)];
+#pragma unroll
+            for (int e = 0; e < H; ++e) {
+                const uint64_t key = make_key(x[e].x, (uint32_t)__float_as_int(x[e].y));
+                if (key > best) { best = key; zb = x[e].z; }
+            }
+        }
+        const uint64_t top = wave_max_key(best);
+        if (best == top) { S.draw = top; S.draw_z = zb; }        // (a clamped lane may hold the last chunk's as well: the same values)
+    }
+    __syncthreads();
+
+    // ---- the entries that reach T
+    const uint32_t T = S.T;
+    const auto push = [&](bool in, float v, int id) {
+        const uint32_t bits = float_order_bits(v);
+        const bool take = in && bits >= T;
+        const uint64_t mask = __ballot(take);
+        if (mask == 0ull) return mask;
+        const int before = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+        uint32_t base = 0u;
+        if (take && before == 0) base = atomicAdd(&S.n_cand, (uint32_t)__popcll(mask));
+        base = (uint32_t)__builtin_amdgcn_readlane((int)base, __ffsll((unsigned long long)mask) - 1);
+        if (take) S.cand[base + before] = u64_from(bits, ~(uint32_t)id);
+        return mask;
+    };
+    if (ahead && S.all_lists) {
+#pragma unroll
+        for (int u = 0; u < kMergeAhead; ++u) push(tid + u * NT < n_entries, v_ahead[u], id_ahead[u]);
+    } else {
+        // eight lanes per list, which is sorted: its next eight entries only where all of these were taken
+        const int sub = lane & 7, n_list = (int)S.n_list;
+        constexpr int GROUPS = NT / 8, PASSES = (kMergeLists + GROUPS - 1) / GROUPS;
+        const auto entry = [&](int l, int p, bool &in) {
+            const int e = S.list[min(l, n_list - 1)] * k + p;
+            in = l < n_list && p < k && e < n_entries;
+            return min(e, n_entries - 1);
+        };
+        float v[PASSES];
+        int id[PASSES];
+        bool in[PASSES];
+#pragma unroll
+        for (int u = 0; u < PASSES; ++u) {
+            const int e = entry((tid >> 3) + u * GROUPS, sub, in[u]);
+            v[u] = pv[e];
+            id[u] = pi[e];
+        }
+#pragma unroll
+        for (int u = 0; u < PASSES; ++u) {
+            uint64_t taken = push(in[u], v[u], id[u]);
+            for (int p = 8; p < k && ((taken >> (lane & 56)) & 0xffu) == 0xffu; p += 8) {
+                bool more;
+                const int e = entry((tid >> 3) + u * GROUPS, p + sub, more);
+                taken = push(more, pv[e], pi[e]);
+            }
+        }
+    }
+    __syncthreads();
+    if (wave != 0) return;
+
+    // ---- the k first of them
+    const auto emit = [&](uint64_t key, int rank) {
+        const int id = (int)key_tiebreak(key);
+        out_ids[(size_t)row * k + rank] = id_map ? id_map[id] : id;      // truncated vocabulary: column -> vocabulary id
+        out_logprobs[(size_t)row * k + rank] = key_value(key) - lse;
+    };
+    const int n = (int)S.n_cand;
+    if (n <= 2 * kCandSlack + k) wave_rank_keys(S.cand, n, k, lane, emit);
+    else {
+        // as with the lists: the k-th largest lane maximum, raised where it admits many
+        uint32_t lane_bits = 0u;
+        for (int c = lane; c < n; c += 64) lane_bits = max(lane_bits, (uint32_t)(S.cand[c] >> 32));
+        const uint32_t sorted = wave_sort_desc(lane_bits, lane);
+        uint32_t T2 = max(1u, (uint32_t)__builtin_amdgcn_readlane((int)sorted, k - 1));
+        const auto count = [&](uint32_t bound) {
+            int m = 0;
+            for (int c0 = 0; c0 < n; c0 += 64) m += __popcll(__ballot(c0 + lane < n && (uint32_t)(S.cand[min(c0 + lane, n - 1)] >> 32) >= bound));
+            return m;
+        };
+        int n2 = count(T2);
+        uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)sorted) + 1u;
+        while (n2 > k + 2 * kCandSlack && hi - T2 > 1u) {
+            const uint32_t mid = T2 + (hi - T2) / 2;
+            const int c = count(mid);
+            if (c >= k) { T2 = mid; n2 = c; } else hi = mid;
+        }
+        if (n2 <= kMergeSel) {
+            int at = 0;
+            for (int c0 = 0; c0 < n; c0 += 64) {
+                const uint64_t key = (c0 + lane < n) ? S.cand[c0 + lane] : kNoKey;
+                const bool take = (uint32_t)(key >> 32) >= T2;
+                const uint64_t mask = __ballot(take);
+                if (take) S.sel[at + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u))] = key;
+                at += __popcll(mask);
+            }
+            lds_wave_sync();
+            wave_rank_keys(S.sel, n2, k, lane, emit);
+        } else {                                                 // that many equal logits: the largest key, k times
+            uint64_t last = ~0ull;
+            for (int rank = 0; rank < k; ++rank) {
+                uint64_t best = kNoKey;
+                for (int c = lane; c < n; c += 64) { const uint64_t key = S.cand[c]; if (key < last) best = u64_max(best, key); }
+                last = wave_max_key(best);
+                if (lane == 0) emit(last, rank);
+            }
+        }
+    }
+    if (part_smp && lane == 0) {
+        const int id = (int)key_tiebreak(S.draw);
+        so.lse[row] = lse;
+        so.sample_ids[row] = id_map ? id_map[id] : id;
+        so.sample_logprobs[row] = S.draw_z - lse;
+    }
 }
 
 hipError_t launch_merge(const float2 *part_ms, const float *part_val, const int *part_id,
                         int rows, int chunks, int chunk_cols, int V, int k, int32_t *out_ids, float *out_logprobs, const int32_t *id_map,
                         const SampleOut &so, const float4 *part_smp, hipStream_t st)
 {
-    const bool cache_ids = merge_lds_bytes(chunks, k, true) <= 64 * 1024;
-    size_t lds = merge_lds_bytes(chunks, k, cache_ids);
-    if (lds > 48 * 1024) {
-        static LdsLimit lds_limit;
-        hipError_t e = lds_limit.raise(reinterpret_cast<const void *>(merge_kernel), (int)lds);
-        if (e != hipSuccess) return e;
-    }
     const int last_cols = V - (chunks - 1) * chunk_cols;
-    merge_kernel<<<rows, kRowMergeThreads, lds, st>>>(part_ms, part_val, part_id, chunks, k, last_cols < k ? last_cols : k, cache_ids ? 1 : 0, out_ids, out_logprobs, id_map, so, part_smp);
+    merge_kernel<<<rows, kRowMergeThreads, 0, st>>>(part_ms, part_val, part_id, chunks, k, last_cols < k ? last_cols : k, out_ids, out_logprobs,
+                                                    id_map, so, so.on ? part_smp : nullptr);
     return hipGetLastError();
 }
 

@@ -95,12 +95,12 @@ inline Plan make_plan(HeadKind kind, int rows, int d, int r, int V, int k) {
     return p;
 }
 
-// Dynamic shared memory of the merge kernel: the head key of every list, the gathered
-// candidates (at most k lists of k entries), every list's k logits and, optionally, its k ids.
-inline size_t merge_lds_bytes(int chunks, int k, bool with_ids = false) {
-    return sizeof(uint64_t) * ((size_t)chunks + (size_t)k * k) + (with_ids ? 2 : 1) * sizeof(float) * (size_t)chunks * k;
+// The largest vocabulary a call may have, by the entries of a row's lists: 8 bytes for every list and 4 for each of its
+// entries, and 8 k k for the winners', within 159 KB.
+inline bool lists_supported(int rows, int V, int k) {
+    const size_t chunks = (size_t)make_chunk_geom(rows, V).chunks;
+    return 8 * (chunks + (size_t)k * k) + 4 * chunks * k <= 159 * 1024;
 }
-constexpr size_t kMergeLdsLimit = 160 * 1024 - 1024;
 
 // ---- matrix-core path -------------------------------------------------------------------
 constexpr int kPlanSlotsPerXcd = 32;     // blocks per XCD of the persistent kernel (256 CUs / 8 XCDs)

@@ -1,0 +1,76 @@
+"""The merge of the chunk lists (csrc/merge_kernel.hip) against the CPU fp64 checker: fewer lists than k and many more, lists whose
+heads are all equal, one list that holds every winner, more entries than are fetched ahead, short last lists, draws."""
+from dataclasses import replace
+
+import numpy as np
+import pytest
+
+from paper_2605_10453_amd import synth
+from parity_util import compare_with_oracle, to_dev_bf16
+from test_gpu_heads_next import check_sample_outputs
+from test_gpu_parity import gpu  # noqa: F401  (the module's fixture)
+
+pytestmark = pytest.mark.gpu
+
+FP32_TOL = 6e-5      # fp32 sums of exact products: see test_gpu_rows_head.py
+
+
+def check(gpu, oracle_mod, x, k):
+    torch, b = gpu
+    V = x.B.shape[1]
+    ids, lp = b.slimspec_head_topk(to_dev_bf16(x.h), to_dev_bf16(x.A), to_dev_bf16(x.B), k)
+    torch.cuda.synchronize()
+    ora = oracle_mod.slimspec_head_topk(x.h, x.A, x.B, k)
+    z_at = lambda ri, ci: oracle_mod.slimspec_logits_at(x.h, x.A, x.B, ri, ci)
+    compare_with_oracle(ids.cpu().numpy(), lp.cpu().numpy(), ora.ids, ora.lse, z_at, V, tie_tol=FP32_TOL, lp_tol=FP32_TOL)
+    return ids.cpu().numpy(), lp.cpu().numpy()
+
+
+@pytest.mark.parametrize("rows", [1, 2, 7])
+@pytest.mark.parametrize("V,k", [(64, 64), (72, 33), (520, 64), (4096, 40), (12096, 39), (33000, 64), (70000, 10), (131080, 63), (300000, 5), (300000, 24)])
+def test_lists_of_every_number_and_length(gpu, oracle_mod, rows, V, k):
+    print(f"merge: rows={rows} V={V} k={k}", flush=True)
+    check(gpu, oracle_mod, synth.make_inputs(synth.small_config(rows, 64, 16, V, k, peaked_every=3), seed=V + k + rows), k)
+
+
+@pytest.mark.parametrize("rows", [1, 6])
+@pytest.mark.parametrize("k", [1, 10, 50])
+@pytest.mark.parametrize("V", [9000, 131080])
+def test_equal_heads_and_crowded_lists(gpu, oracle_mod, rows, k, V):
+    """Periodic columns: every chunk's list is the same, the first chunks' ids win.  Then one chunk that holds all winners."""
+    x = synth.make_inputs(synth.small_config(rows, 64, 16, V, k), seed=k)
+    period = np.ascontiguousarray(np.tile(x.B[:, :8], (1, V // 8)))
+    ids, _ = check(gpu, oracle_mod, replace(x, B=period), k)
+    # the winners of each group of equal logits are the smallest ids of their residue, in order
+    for row in ids:
+        for res in range(8):
+            mine = row[row % 8 == res]
+            assert np.array_equal(mine, res + 8 * np.arange(len(mine)))
+    crowded = x.B.copy()
+    lo = V // 2 // 8 * 8
+    big = (crowded[:, lo:lo + 64].astype(np.uint32) << 16).view(np.float32) * 8.0
+    crowded[:, lo:lo + 64] = (big.view(np.uint32) >> 16).astype(np.uint16)
+    check(gpu, oracle_mod, replace(x, B=crowded), k)
+
+
+def test_zero_hidden_state(gpu):
+    torch, b = gpu
+    V, k = 20000, 64
+    x = synth.make_inputs(synth.small_config(3, 64, 16, V, k), seed=1)
+    h = to_dev_bf16(np.zeros_like(x.h))
+    for n in (1, 3):
+        ids, lp = b.slimspec_head_topk(h[:n].contiguous(), to_dev_bf16(x.A), to_dev_bf16(x.B), k)
+        torch.cuda.synchronize()
+        assert np.array_equal(ids.cpu().numpy(), np.tile(np.arange(k, dtype=np.int32), (n, 1)))
+        assert np.abs(lp.cpu().numpy() + np.log(V)).max() <= FP32_TOL
+
+
+@pytest.mark.parametrize("rows,V", [(1, 72), (1, 200000), (1, 600000), (5, 200000)])
+def test_draws(gpu, oracle_mod, rows, V):
+    torch, b = gpu
+    k = 7
+    x = synth.make_inputs(synth.small_config(rows, 64, 16, V, k), seed=V)
+    out = b.slimspec_head_sample(to_dev_bf16(x.h), to_dev_bf16(x.A), to_dev_bf16(x.B), k, 1234)
+    torch.cuda.synchronize()
+    ora = oracle_mod.head_sample(x.h, x.A, x.B, k, 1234, return_logits=True)
+    check_sample_outputs(torch, out, ora, 1234, V, ora.z, oracle_mod)
