@@ -3,12 +3,13 @@
 // O(rd + Vr) low-rank head and the O(Vd) full head).
 //
 //   down_items_kernel     t = h A as slices over d, one block per (64 columns of A) x (slice of d)
-//   widen_rows_kernel     bf16 h -> fp32 (contraction input of the full head)
-//   stream_topk_kernel    z[:, chunk] = x M[:, chunk] for a 512-column chunk, then the
+//   stream_topk_kernel    z[:, chunk] = x M[:, chunk] for a chunk of 64 to 512 columns, then the
 //                         chunk's running max, sum of exp and top-k, one partial per
 //                         (row, chunk); no logit is written to memory
+//   widen_rows_kernel     bf16 h -> fp32 (contraction input of a full head whose rows do not fit shared memory)
 #include "gemv_parts.hpp"
 #include "launch.hpp"
+#include <type_traits>
 
 namespace slimspec {
 
@@ -34,30 +35,47 @@ __global__ __launch_bounds__(256) void widen_rows_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// One block per 512-column chunk of the vocabulary.  x is the fp32 contraction
-// input [R, K] (t or h), M the [K, V] weight matrix (bf16 or fp32).  The NW
-// wavefronts split K; every lane owns 8 adjacent columns and keeps R x 8 fp32
-// accumulators.  After a fixed-order sum over the wavefronts, wavefront i % NW
-// reduces row i of the chunk to (max, sum of exp, top-k) and writes the partial.
+// One block per chunk of 8 * lanes adjacent columns of the vocabulary.  M is the [K, V] weight matrix (bf16 or fp32).
+// A lane owns 8 adjacent columns; a wavefront's 64 lanes are 64 / lanes (`k_parts`) rows of M at a time, so a narrow
+// chunk fills the wavefront as well, and the NW k_parts lane groups of a block split the contraction into ranges of
+// `per` rows (a multiple of 8).  Their partial sums meet in shared memory in a fixed order, and wavefront i % NW reduces
+// row i of the chunk to (max, sum of exp, top-k) and writes the partial.
 //
-// SLICES: x is not the contraction input itself but nds partial sums of it, [nds][R][K] (the
-// slices of t left by down_items_kernel); the block first adds them, in slice order, into shared
-// memory.  The first weight rows are requested before that, so the adds hide behind them.
-template <int R, int NW, typename WT, bool SLICES>
+// What bounds it: the weights' way from HBM, as long as every CU has a block and asks for enough of them (plan.hpp chooses
+// the chunks for that); with small weights the chain of trips before and after: the contraction input (one trip: all
+// of a thread's loads are requested together, and the first weights right behind them), the weights, the epilogue of one
+// wavefront.
+//
+// Measured, one row (kernel; chunks of 512 columns and x as it comes, before, in brackets): full head, d = 7984, V = 37208 109 us
+// (180), d = 3208, V = 33184 41 (70); r = 1568, V = 40248 27.4 (44); r = 72, V = 103472 7.4 (10.5); d = 4096, V = 128256, where
+// the chunks are the same, 170.6 (171.3, and 4.7 in a launch that widened the row to fp32).  3 rows, r = 496, V = 19072 15.9 (22.3).
+//
+// SRC: what x is.  kSlices: nds partial sums of the contraction input, [nds][R][K] fp32 (down_items_kernel's); four
+// adjacent lanes add a quarter of the slices each.  kHalfRows: the bf16 rows themselves, [rows_here][K] (full head).  Both
+// are put into shared memory.  kGlobal: fp32 [R][K], read from memory (rows too long for that; k_parts is 1).
+enum { kGlobal = 0, kSlices = 1, kHalfRows = 2 };
+
+template <int R, int NW, typename WT, int SRC>
 __global__ __launch_bounds__(NW * 64) void stream_topk_kernel(
-    const float *__restrict__ x, int nds, const WT *__restrict__ M,
+    const void *__restrict__ x_src, int nds, const WT *__restrict__ M,
     float2 *__restrict__ part_ms, float *__restrict__ part_val, int *__restrict__ part_id,
-    int rows_here, int row0, int K, int V, int chunks, int lanes, int k,
+    int rows_here, int row0, int K, int V, int chunks, int lanes, int k_parts, StreamParts sp, int k,
     float4 *__restrict__ part_smp, uint32_t seed_lo, uint32_t seed_hi)
 {
-    extern __shared__ __align__(16) unsigned char dyn[];         // ChunkLds, then (SLICES) t as fp32 [R][K]
-    ChunkLds<R, NW> &L = *reinterpret_cast<ChunkLds<R, NW> *>(dyn);
-    float *xs = reinterpret_cast<float *>(dyn + sizeof(ChunkLds<R, NW>));
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int chunk = blockIdx.x;
-    const int col = (chunk * lanes + lane) * 8;             // the chunk covers 8 * lanes adjacent columns
-    const bool active = lane < lanes && col < V;          // V is a multiple of 8: all 8 columns valid or none
+    constexpr int NT = NW * 64, EW = (R < NW) ? R : NW;
+    extern __shared__ __align__(16) unsigned char dyn[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // Blocks are dealt round-robin to the 8 XCDs: adjacent chunks, which share a cache line per row of M wherever the rows
+    // are no multiples of 128 bytes, go to one XCD.
+    const int per_xcd = (chunks + 7) >> 3;
+    const int chunk = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    if (chunk >= chunks) return;
+    int kp = 0;                                             // lane / lanes
+    for (int first = lanes; first < 64; first += lanes) kp += lane >= first ? 1 : 0;
+    const int g = lane - kp * lanes;
+    const int cw = 8 * lanes, chunk_col = chunk * cw, col = chunk_col + 8 * g;
+    const bool active = kp < k_parts && col < V;          // V is a multiple of 8: all 8 columns valid or none
 
     float acc[R][8];
 #pragma unroll
@@ -65,122 +83,175 @@ __global__ __launch_bounds__(NW * 64) void stream_topk_kernel(
 #pragma unroll
         for (int e = 0; e < 8; ++e) acc[i][e] = 0.f;
 
-    // rows [j0, j1) of M for this wavefront
-    const int per = ((K + NW - 1) / NW + 7) & ~7;            // multiple of 8: keeps 8-wide reads of x aligned
-    const int j0 = min(K, wave * per), j1 = min(K, j0 + per);
-    constexpr int U = (sizeof(WT) == 2 && R <= 2) ? 16 : 8;
+    // Rows [j0, j1) of M for this wavefront, 8 k_parts at a time of which lane group kp takes the eight from 8 kp on: the
+    // rows' addresses are the same in all lanes but for an offset kept in one register.  K is a multiple of 8.
+    const int n_parts = sp.n, step = 8 * k_parts;
+    const int j0 = min(K, wave * sp.per), j1 = min(K, j0 + sp.per);
+    float *red = reinterpret_cast<float *>(dyn);                              // [n_parts][R][cw]
+    float *red2 = red + n_parts * R * cw;                                     // [kSumParts][R][cw] if n_parts > kDirectParts
+    uint64_t *sel = reinterpret_cast<uint64_t *>(red2 + (n_parts > kDirectParts ? kSumParts * R * cw : 0));      // [EW][cw]
+    unsigned char *xs_raw = reinterpret_cast<unsigned char *>(sel + EW * cw);                                   // x: [R][K], fp32 (kSlices) or bf16
+    constexpr int U = (sizeof(WT) == 2 && R <= 2) ? 16 : 8, UG = U / 8;
     using RawT = decltype(load_raw8(static_cast<const WT *>(nullptr)));
-    const WT *base = M + (active ? col : 0);
+    const uint32_t off = active ? (uint32_t)(8 * kp) * (uint32_t)V + (uint32_t)col : 0u;      // (8 k_parts rows of at most 2^17 columns when k_parts > 1)
+    const auto load_row = [&](int j) { return load_raw8(M + (size_t)j * V + off); };          // row j + 8 kp
 
-    if constexpr (SLICES) {
-        // slices of t first (they come from L2), then the first batch of weight rows, then the adds
-        constexpr int NT = NW * 64;
-        constexpr int PER_T = 8;
-        const size_t stride = (size_t)R * K;
-        RawT q0[U];
-        const bool first_full = active && (j0 + U <= j1);
-        for (int e0 = 0; e0 < R * K; e0 += NT) {
-            const int e = e0 + threadIdx.x;
-            float s = 0.f;
-            if (e < R * K) {
-                int ds = 0;
-                for (; ds + PER_T <= nds; ds += PER_T) {
-                    float v[PER_T];
+    if constexpr (SRC != kGlobal) {
+        RawT q[U];
+        const auto load_batch = [&](int j) {
 #pragma unroll
-                    for (int u = 0; u < PER_T; ++u) v[u] = x[(size_t)(ds + u) * stride + e];
+            for (int u = 0; u < U; ++u) q[u] = load_row(j + (u >> 3) * step + (u & 7));
+        };
+        // (where the wavefront's range ends inside it, a lane group without rows reads the first group's)
+        const bool in_first = active && j0 < j1;
+        const auto load_first = [&]() {
+            if (!in_first) return;
 #pragma unroll
-                    for (int u = 0; u < PER_T; ++u) s += v[u];
+            for (int g8 = 0; g8 < UG; ++g8) {
+                if (g8 > 0 && j0 + g8 * step >= j1) continue;   // (the same for the whole wavefront)
+                const bool have = j0 + g8 * step + 8 * kp < j1;
+                const uint32_t o = have ? off : (uint32_t)col;
+#pragma unroll
+                for (int u = 0; u < 8; ++u) q[8 * g8 + u] = load_raw8(M + (size_t)(j0 + g8 * step + u) * V + o);
+            }
+        };
+        if constexpr (SRC == kSlices) {
+            const float4 *x = static_cast<const float4 *>(x_src);
+            float4 *xs = reinterpret_cast<float4 *>(xs_raw);
+            const uint32_t n4 = (uint32_t)(R * K) / 4u, sg = tid & 3u, last = (uint32_t)nds - 1u;
+            constexpr uint32_t SL = 8;                          // slices of a lane: sg, sg + 4, ... (at most 32 in all: make_down_plan)
+            float4 v[SL];
+            const auto load_slices = [&](uint32_t e) {
+                if (e >= n4) return;                            // (a wavefront of none goes on to its weights)
+#pragma unroll
+                for (uint32_t u = 0; u < SL; ++u) v[u] = x[min(sg + 4u * u, last) * n4 + e];
+            };
+            const auto add_slices = [&](uint32_t e) {
+                float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+                for (uint32_t u = 0; u < SL; ++u) {
+                    const uint32_t on = sg + 4u * u <= last ? 0xffffffffu : 0u;      // (a condition becomes a branch per slice)
+                    const auto kept = [&](float f) { return __uint_as_float(__float_as_uint(f) & on); };
+                    s.x += kept(v[u].x); s.y += kept(v[u].y); s.z += kept(v[u].z); s.w += kept(v[u].w);
                 }
-                for (; ds < nds; ++ds) s += x[(size_t)ds * stride + e];
-                xs[e] = s;
+                const auto quad = [](float f) { f += dpp_f32<0xB1>(f); return f + dpp_f32<0x4E>(f); };
+                s.x = quad(s.x); s.y = quad(s.y); s.z = quad(s.z); s.w = quad(s.w);
+                if (sg == 0 && e < n4) xs[e] = s;
+            };
+            uint32_t e = (uint32_t)tid >> 2;
+            for (uint32_t e0 = 0; e0 + NT / 4 < n4; e0 += NT / 4, e += NT / 4) { load_slices(e); add_slices(e); }
+            load_slices(e);
+            __builtin_amdgcn_sched_barrier(0);
+            load_first();                                       // behind the last of them: vector memory returns in order
+            __builtin_amdgcn_sched_barrier(0);
+            add_slices(e);
+        } else {
+            uint4 *xs = reinterpret_cast<uint4 *>(xs_raw);
+            const int n8 = rows_here * K / 8;                   // rows beyond the last stay undefined: nobody reads their sums
+            const uint4 *x = static_cast<const uint4 *>(x_src);
+            for (int e0 = 0; e0 < n8; e0 += NT) {
+                const uint4 v = x[min(e0 + tid, n8 - 1)];
+                if (e0 + NT >= n8) load_first();
+                if (e0 + tid < n8) xs[e0 + tid] = v;
             }
         }
-        if (first_full) {
-#pragma unroll
-            for (int u = 0; u < U; ++u) q0[u] = load_raw8(base + (size_t)(j0 + u) * V);
-        }
         __syncthreads();
-        auto fma_batch = [&](const RawT (&q)[U], int j) {
+        const auto fma_group = [&](const RawT *w, int j) __attribute__((always_inline)) {      // rows j + 8 kp ... of the lane group
+            float xv[R][8];
 #pragma unroll
-            for (int g = 0; g < U / 8; ++g) {
-                float xv[R][8];
-#pragma unroll
-                for (int i = 0; i < R; ++i) {
-                    const float4 *p = reinterpret_cast<const float4 *>(xs + i * K + j + 8 * g);
+            for (int i = 0; i < R; ++i) {
+                if constexpr (SRC == kSlices) {
+                    const float4 *p = reinterpret_cast<const float4 *>(xs_raw) + (i * K + j) / 4 + 2 * kp;
                     const float4 a = p[0], b = p[1];
                     xv[i][0] = a.x; xv[i][1] = a.y; xv[i][2] = a.z; xv[i][3] = a.w;
                     xv[i][4] = b.x; xv[i][5] = b.y; xv[i][6] = b.z; xv[i][7] = b.w;
-                }
+                } else
+                    widen8(Raw8Bf16{reinterpret_cast<const uint4 *>(xs_raw)[(min(i, rows_here - 1) * K + j) / 8 + kp]}, xv[i]);
+            }
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    float f[8];
-                    widen8(q[8 * g + u], f);
+            for (int u = 0; u < 8; ++u) {
+                float f[8];
+                widen8(w[u], f);
 #pragma unroll
-                    for (int i = 0; i < R; ++i)
+                for (int i = 0; i < R; ++i)
 #pragma unroll
-                        for (int e = 0; e < 8; ++e) acc[i][e] = fmaf(xv[i][u], f[e], acc[i][e]);
-                }
+                    for (int e = 0; e < 8; ++e) acc[i][e] = fmaf(xv[i][u], f[e], acc[i][e]);
             }
         };
         if (active) {
             int j = j0;
-            if (first_full) { fma_batch(q0, j); j += U; }
-            for (; j + U <= j1; j += U) {
-                RawT q[U];
 #pragma unroll
-                for (int u = 0; u < U; ++u) q[u] = load_raw8(base + (size_t)(j + u) * V);
-                fma_batch(q, j);
+            for (int g8 = 0; g8 < UG; ++g8)
+                if (j + g8 * step + 8 * kp < j1) fma_group(q + 8 * g8, j + g8 * step);
+            j += UG * step;
+            for (; j + UG * step <= j1; j += UG * step) {
+                load_batch(j);
+#pragma unroll
+                for (int g8 = 0; g8 < UG; ++g8) fma_group(q + 8 * g8, j + g8 * step);
             }
-            for (; j < j1; ++j) {
-                float f[8];
-                widen8(load_raw8(base + (size_t)j * V), f);
+            for (; j < j1; j += step)
+                if (j + 8 * kp < j1) {
+                    RawT w[8];
 #pragma unroll
-                for (int i = 0; i < R; ++i) {
-                    const float xv = xs[i * K + j];
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) acc[i][e] = fmaf(xv, f[e], acc[i][e]);
+                    for (int u = 0; u < 8; ++u) w[u] = load_row(j + u);
+                    fma_group(w, j);
                 }
-            }
         }
     } else if (active) {
-        int j = j0;
-        for (; j + U <= j1; j += U) {
-            RawT q[U];
+        const float *x = static_cast<const float *>(x_src);
+        const auto rows_from = [&](int j, auto n_tag) {         // (k_parts is 1)
+            constexpr int N = decltype(n_tag)::value;
+            RawT q[N];
 #pragma unroll
-            for (int u = 0; u < U; ++u) q[u] = load_raw8(base + (size_t)(j + u) * V);
+            for (int u = 0; u < N; ++u) q[u] = load_row(j + u);
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
+            for (int u = 0; u < N; ++u) {
                 float f[8];
                 widen8(q[u], f);
 #pragma unroll
                 for (int i = 0; i < R; ++i) {
-                    float xv = x[(size_t)i * K + j + u];
+                    const float xv = x[(size_t)i * K + j + u];
 #pragma unroll
                     for (int e = 0; e < 8; ++e) acc[i][e] = fmaf(xv, f[e], acc[i][e]);
                 }
             }
-        }
-        for (; j < j1; ++j) {
-            float f[8];
-            widen8(load_raw8(base + (size_t)j * V), f);
-#pragma unroll
-            for (int i = 0; i < R; ++i) {
-                float xv = x[(size_t)i * K + j];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) acc[i][e] = fmaf(xv, f[e], acc[i][e]);
-            }
-        }
+        };
+        int j = j0;
+        for (; j + U <= j1; j += U) rows_from(j, std::integral_constant<int, U>{});
+        if constexpr (U > 8)
+            for (; j < j1; j += 8) rows_from(j, std::integral_constant<int, 8>{});
     }
+    const int part = wave * k_parts + kp;
+    if (kp < k_parts && part < n_parts) {
 #pragma unroll
-    for (int i = 0; i < R; ++i) {
-        float4 *dst = reinterpret_cast<float4 *>(&L.red[wave][i][lane * 8]);
-        dst[0] = make_float4(acc[i][0], acc[i][1], acc[i][2], acc[i][3]);
-        dst[1] = make_float4(acc[i][4], acc[i][5], acc[i][6], acc[i][7]);
+        for (int i = 0; i < R; ++i) {
+            float4 *dst = reinterpret_cast<float4 *>(red + (part * R + i) * cw + 8 * g);
+            dst[0] = make_float4(acc[i][0], acc[i][1], acc[i][2], acc[i][3]);
+            dst[1] = make_float4(acc[i][4], acc[i][5], acc[i][6], acc[i][7]);
+        }
     }
     __syncthreads();
+    // many lane groups (narrow chunks): every thread adds some of their sums first
+    const float *sums = red;
+    int n_sums = n_parts;
+    if (n_parts > kDirectParts) {
+        const int n2 = R * cw / 2;                              // pairs of columns
+        for (int item = tid; item < kSumParts * n2; item += NT) {
+            const int p0 = item / n2, c2 = item - p0 * n2;
+            float2 s = make_float2(0.f, 0.f);
+            for (int p = p0; p < n_parts; p += kSumParts) {
+                const float2 v = reinterpret_cast<const float2 *>(red)[p * n2 + c2];
+                s.x += v.x; s.y += v.y;
+            }
+            reinterpret_cast<float2 *>(red2)[item] = s;
+        }
+        __syncthreads();
+        sums = red2;
+        n_sums = kSumParts;
+    }
     for (int i = wave; i < rows_here; i += NW)
-        chunk_row_epilogue<R, NW>(L, i, wave, lane, active, col, k, (size_t)(row0 + i) * chunks + chunk,
-                                  part_ms, part_val, part_id, part_smp, gumbel_key(seed_lo, seed_hi, (uint32_t)(row0 + i)));
+        chunk_row_epilogue(sums + i * cw, n_sums, R * cw, cw, chunk_col, V, lane, k, sel + (wave % EW) * cw, (size_t)(row0 + i) * chunks + chunk,
+                           part_ms, part_val, part_id, part_smp, gumbel_key(seed_lo, seed_hi, (uint32_t)(row0 + i)));
 }
 
 // ---------------------------------------------------------------------------
@@ -213,67 +284,79 @@ hipError_t launch_down_projection(const uint16_t *h, const uint16_t *A, float *t
     return launch_down<8>(h, A, tpart, rows_here, d, r, fp, mat_of_row, st);
 }
 
-hipError_t launch_widen_rows(const uint16_t *h, float *x, int n, hipStream_t st)
+static hipError_t launch_widen_rows(const uint16_t *h, float *x, int n, hipStream_t st)
 {
     widen_rows_kernel<<<(n + 255) / 256, 256, 0, st>>>(h, x, n);
     return hipGetLastError();
 }
 
+// What a launch of stream_topk_kernel is given (the instances differ in types only).
+template <typename WT>
+struct StreamCall {
+    const void *x; int nds;
+    const WT *M;
+    float2 *ms; float *pv; int *pi;
+    int rows_here, row0, K, V;
+    ChunkGeom g;
+    int k;
+    float4 *smp; uint32_t seed_lo, seed_hi;
+};
+
 constexpr size_t kStreamLdsLimit = 150 * 1024;      // of the CU's 160 KB
 
-template <int R, int NW>
-constexpr size_t stream_lds_bytes(bool slices, int K) {
-    return sizeof(ChunkLds<R, NW>) + (slices ? sizeof(float) * (size_t)R * K : 0);
-}
-
-template <int R, int NW, typename WT>
-static hipError_t launch_stream(const float *x, int nds, const WT *M, float2 *ms, float *pv, int *pi,
-                                int rows_here, int row0, int K, int V, int chunks, int lanes, int k,
-                                float4 *smp, uint32_t seed_lo, uint32_t seed_hi, hipStream_t st)
+template <int R, int NW, typename WT, int SRC>
+static hipError_t launch_stream(const StreamCall<WT> &c, hipStream_t st)
 {
-    static_assert(sizeof(ChunkLds<R, NW>) % 16 == 0, "t follows the struct in shared memory");
-    const size_t dyn = stream_lds_bytes<R, NW>(nds > 0, K);
-    const void *fn = nds > 0 ? reinterpret_cast<const void *>(stream_topk_kernel<R, NW, WT, true>)
-                             : reinterpret_cast<const void *>(stream_topk_kernel<R, NW, WT, false>);
+    const int per_xcd = (c.g.chunks + 7) / 8, k_parts = SRC == kGlobal ? 1 : c.g.k_parts;
+    const size_t dyn = stream_lds_bytes(R, NW, c.g, c.K, SRC == kGlobal ? 0 : SRC == kSlices ? 4 : 2);
     if (dyn > 32 * 1024) {
-        static LdsLimit lds_limit[2];
-        hipError_t e = lds_limit[nds > 0 ? 1 : 0].raise(fn, (int)dyn);
+        static LdsLimit lds_limit;
+        const hipError_t e = lds_limit.raise(reinterpret_cast<const void *>(stream_topk_kernel<R, NW, WT, SRC>), (int)dyn);
         if (e != hipSuccess) return e;
     }
-    if (nds > 0)
-        stream_topk_kernel<R, NW, WT, true><<<chunks, NW * 64, dyn, st>>>(x, nds, M, ms, pv, pi, rows_here, row0, K, V, chunks, lanes, k,
-                                                                          smp, seed_lo, seed_hi);
-    else
-        stream_topk_kernel<R, NW, WT, false><<<chunks, NW * 64, dyn, st>>>(x, 0, M, ms, pv, pi, rows_here, row0, K, V, chunks, lanes, k,
-                                                                           smp, seed_lo, seed_hi);
+    stream_topk_kernel<R, NW, WT, SRC><<<8 * per_xcd, NW * 64, dyn, st>>>(c.x, c.nds, c.M, c.ms, c.pv, c.pi, c.rows_here, c.row0, c.K, c.V, c.g.chunks,
+                                                                          c.g.lanes, k_parts, stream_parts(NW, k_parts, c.K), c.k, c.smp, c.seed_lo, c.seed_hi);
     return hipGetLastError();
 }
 
-template <typename WT>
-static hipError_t launch_stream_rows(const float *x, int nds, const WT *M, float2 *ms, float *pv, int *pi,
-                                     int rows_here, int row0, int K, int V, int chunks, int lanes, int nw1, int k,
-                                     float4 *smp, uint32_t seed_lo, uint32_t seed_hi, hipStream_t st)
+template <typename WT, int SRC>
+static hipError_t launch_stream_rows(const StreamCall<WT> &c, hipStream_t st)
 {
-#define SLIMSPEC_STREAM(R, NW) launch_stream<R, NW, WT>(x, nds, M, ms, pv, pi, rows_here, row0, K, V, chunks, lanes, k, smp, seed_lo, seed_hi, st)
-#define SLIMSPEC_FITS(R, NW) (stream_lds_bytes<R, NW>(nds > 0, K) <= kStreamLdsLimit)
     // One row: the block size the chunk geometry asks for.  More rows: as many wavefronts as the shared memory of
     // the partial sums (NW * R * 2 KB) allows; they split the contraction, and every one of them keeps loads in flight.
-    if (rows_here <= 1) return nw1 == 4 ? SLIMSPEC_STREAM(1, 4) : nw1 == 8 ? SLIMSPEC_STREAM(1, 8) : SLIMSPEC_STREAM(1, 16);
-    if (rows_here <= 2) return SLIMSPEC_FITS(2, 16) ? SLIMSPEC_STREAM(2, 16) : SLIMSPEC_STREAM(2, 8);
-    if (rows_here <= 4) return SLIMSPEC_FITS(4, 8) ? SLIMSPEC_STREAM(4, 8) : SLIMSPEC_STREAM(4, 4);
-    return SLIMSPEC_FITS(8, 4) ? SLIMSPEC_STREAM(8, 4) : SLIMSPEC_STREAM(8, 2);
-#undef SLIMSPEC_FITS
-#undef SLIMSPEC_STREAM
+    const auto fits = [&](int R, int NW) { return stream_lds_bytes(R, NW, c.g, c.K, SRC == kGlobal ? 0 : SRC == kSlices ? 4 : 2) <= kStreamLdsLimit; };
+    if (c.rows_here <= 1) {
+        if (c.g.nw1 == 16 && fits(1, 16)) return launch_stream<1, 16, WT, SRC>(c, st);
+        if (c.g.nw1 >= 8 && fits(1, 8)) return launch_stream<1, 8, WT, SRC>(c, st);
+        return launch_stream<1, 4, WT, SRC>(c, st);
+    }
+    if (c.rows_here <= 2)
+        return fits(2, 16) ? launch_stream<2, 16, WT, SRC>(c, st) : fits(2, 8) ? launch_stream<2, 8, WT, SRC>(c, st) : launch_stream<2, 4, WT, SRC>(c, st);
+    if (c.rows_here <= 4) return fits(4, 8) ? launch_stream<4, 8, WT, SRC>(c, st) : launch_stream<4, 4, WT, SRC>(c, st);
+    return fits(8, 4) ? launch_stream<8, 4, WT, SRC>(c, st) : launch_stream<8, 2, WT, SRC>(c, st);
 }
 
-// nds > 0: x holds nds slices [nds][R][K] of the contraction input (R = 1, 2, 4 or 8 as chosen for rows_here)
-hipError_t launch_stream_topk(const float *x, int nds, const void *M, bool m_is_f32, float2 *ms, float *pv, int *pi,
-                              int rows_here, int row0, int K, int V, int chunks, int lanes, int nw1, int k,
+template <typename WT>
+static hipError_t launch_stream_src(StreamCall<WT> c, float *wide, hipStream_t st)
+{
+    if constexpr (sizeof(WT) == 2)                      // (the low-rank head's weights are bf16)
+        if (c.nds > 0) return launch_stream_rows<WT, kSlices>(c, st);
+    // the smallest block's need decides: rows too long for it are read from memory as fp32
+    const int R = c.rows_here <= 1 ? 1 : c.rows_here <= 2 ? 2 : c.rows_here <= 4 ? 4 : 8;
+    if (stream_lds_bytes(R, R == 8 ? 2 : 4, c.g, c.K, 2) <= kStreamLdsLimit) return launch_stream_rows<WT, kHalfRows>(c, st);
+    const hipError_t e = launch_widen_rows(static_cast<const uint16_t *>(c.x), wide, c.rows_here * c.K, st);
+    if (e != hipSuccess) return e;
+    c.x = wide;
+    return launch_stream_rows<WT, kGlobal>(c, st);
+}
+
+hipError_t launch_stream_topk(const void *x, int nds, float *wide, const void *M, bool m_is_f32, float2 *ms, float *pv, int *pi,
+                              int rows_here, int row0, int K, int V, const ChunkGeom &g, int k,
                               float4 *smp, uint32_t seed_lo, uint32_t seed_hi, hipStream_t st)
 {
     if (m_is_f32)
-        return launch_stream_rows<float>(x, nds, (const float *)M, ms, pv, pi, rows_here, row0, K, V, chunks, lanes, nw1, k, smp, seed_lo, seed_hi, st);
-    return launch_stream_rows<uint16_t>(x, nds, (const uint16_t *)M, ms, pv, pi, rows_here, row0, K, V, chunks, lanes, nw1, k, smp, seed_lo, seed_hi, st);
+        return launch_stream_src<float>({x, nds, static_cast<const float *>(M), ms, pv, pi, rows_here, row0, K, V, g, k, smp, seed_lo, seed_hi}, wide, st);
+    return launch_stream_src<uint16_t>({x, nds, static_cast<const uint16_t *>(M), ms, pv, pi, rows_here, row0, K, V, g, k, smp, seed_lo, seed_hi}, wide, st);
 }
 
 }  // namespace slimspec

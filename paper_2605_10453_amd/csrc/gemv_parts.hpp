@@ -104,15 +104,6 @@ __device__ __forceinline__ void down_item(float (*redd)[R][kItemCols], const uin
 
 
 // ---------------------------------------------------------------------------
-// Shared memory of the chunk epilogue: the partial sums of the NW wavefronts that split the
-// contraction, and the selection scratch of the wavefronts that reduce a row each.
-template <int R, int NW>
-struct ChunkLds {
-    static constexpr int EW = (R < NW) ? R : NW;
-    float red[NW][R][kChunkCols];
-    uint64_t sel_cand[EW][kChunkCols];
-};
-
 // The k largest of a row's logits that one wavefront holds (up to E per lane, as order bits: 0 where the lane holds no
 // column), ranked by (logit desc, id asc) into out_val / out_id.  This is the tail of every block, after its last
 // weight row has arrived, and its instruction count is what a call of dozens of rows waits for.  All 64 lanes call.
@@ -196,62 +187,74 @@ __device__ __forceinline__ void wave_topk(const uint32_t (&ob)[E], int n_e, Id i
     lds_wave_sync();                                             // the buffers are reused by this wavefront's next row
 }
 
-// Row i of the chunk: fixed-order sum of the NW partial sums, then (max, sum of exp, top-k) of its
-// 512 logits, written as the partial of (row, chunk).  One wavefront; all 64 lanes must call.
+// One row of a chunk of cw columns (at most 512) from chunk_col on: fixed-order sum of its n partial sums (sums[p * stride + c] for
+// column c), then (max, sum of exp, top-k) of the logits, written as the partial of (row, chunk).  One wavefront; all 64
+// lanes must call.  sel: cw keys of shared memory.
 //
-// Top-k: wave_topk.
+// Top-k: wave_topk.  Lane = columns 2 lane, 2 lane + 1 of every 128.
 // part_smp (may be null): the chunk's best z_v + g_v with standard Gumbel noise g (Gumbel-max sampling), as
 // (z + g, id, z, -) of the winner; gk: the noise key of this row.
-template <int R, int NW>
-__device__ __forceinline__ void chunk_row_epilogue(ChunkLds<R, NW> &L, int i, int wave, int lane, bool active,
-                                                   int col, int k, size_t slot,
+__device__ __forceinline__ void chunk_row_epilogue(const float *sums, int n, int stride, int cw, int chunk_col, int V, int lane, int k,
+                                                   uint64_t *sel, size_t slot,
                                                    float2 *__restrict__ part_ms, float *__restrict__ part_val,
                                                    int *__restrict__ part_id,
                                                    float4 *__restrict__ part_smp, const GumbelKey &gk)
 {
-    float z[8];
+    constexpr int E = kChunkCols / 64;
+    const auto act = [&](int e) { const int c = 128 * (e >> 1) + 2 * lane; return c < cw && chunk_col + c < V; };      // V and cw are even: both columns or none
+    const auto id = [&](int e) { return (uint32_t)(chunk_col + 128 * (e >> 1) + 2 * lane + (e & 1)); };
+    float z[E];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) z[e] = 0.f;
+    for (int e = 0; e < E; e += 2) {
+        float2 s = make_float2(kNegInf, kNegInf);
+        if (64 * e < cw && act(e)) {
+            const float *src = sums + 64 * e + 2 * lane;
+            s = make_float2(0.f, 0.f);
+            int p = 0;                          // fixed order: the first rows of the contraction first
+            for (; p + 8 <= n; p += 8) {
+                float2 v[8];
 #pragma unroll
-    for (int w = 0; w < NW; ++w) {          // fixed order: wavefront 0 first
-        const float4 *src = reinterpret_cast<const float4 *>(&L.red[w][i][lane * 8]);
-        float4 a = src[0], b = src[1];
-        z[0] += a.x; z[1] += a.y; z[2] += a.z; z[3] += a.w;
-        z[4] += b.x; z[5] += b.y; z[6] += b.z; z[7] += b.w;
+                for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const float2 *>(src + (p + u) * stride);
+#pragma unroll
+                for (int u = 0; u < 8; ++u) { s.x += v[u].x; s.y += v[u].y; }
+            }
+            for (; p < n; ++p) {
+                const float2 v = *reinterpret_cast<const float2 *>(src + p * stride);
+                s.x += v.x; s.y += v.y;
+            }
+        }
+        z[e] = s.x; z[e + 1] = s.y;
     }
-#pragma unroll
-    for (int e = 0; e < 8; ++e) z[e] = active ? z[e] : kNegInf;
 
     if (part_smp) {
         // keys are unique (one per id), so exactly one lane holds the wavefront's largest
         uint64_t best = kNoKey;
         float zb = 0.f;
-        if (active) {
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const uint64_t key = make_key(z[e] + gumbel_base2(gk, (uint32_t)(col + e)) * kLn2, (uint32_t)(col + e));
+        for (int e = 0; e < E; ++e)
+            if (act(e)) {
+                const uint64_t key = make_key(z[e] + gumbel_base2(gk, id(e)) * kLn2, id(e));
                 if (key > best) { best = key; zb = z[e]; }
             }
-        }
         const uint64_t top = wave_max_key(best);
-        if (active && best == top)
+        if (best != kNoKey && best == top)
             part_smp[slot] = make_float4(key_value(top), __int_as_float((int)key_tiebreak(top)), zb, 0.f);
     }
     float lm = z[0];
 #pragma unroll
-    for (int e = 1; e < 8; ++e) lm = fmaxf(lm, z[e]);
+    for (int e = 1; e < E; ++e) lm = fmaxf(lm, z[e]);
     const float m = wave_max(lm);
     float s = 0.f;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) s += fast_exp(z[e] - m);     // exp(-inf) = 0 for padding lanes
+    for (int e = 0; e < E; e += 2)
+        if (64 * e < cw) s += fast_exp(z[e] - m) + fast_exp(z[e + 1] - m);     // exp(-inf) = 0 for padding lanes
     s = wave_sum(s);
 
     if (lane == 0) part_ms[slot] = make_float2(m, s);
-    uint32_t ob[8];
+    uint32_t ob[E];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) ob[e] = active ? float_order_bits(z[e]) : 0u;
-    wave_topk<8>(ob, 8, [&](int e) { return (uint32_t)(col + e); }, lane, k, L.sel_cand[wave], kChunkCols,
-                 part_val + slot * k, part_id + slot * k);
+    for (int e = 0; e < E; ++e) ob[e] = act(e) ? float_order_bits(z[e]) : 0u;
+    wave_topk<E>(ob, 2 * ((cw + 127) / 128), id, lane, k, sel, cw, part_val + slot * k, part_id + slot * k);
 }
 
 }  // namespace slimspec

@@ -35,15 +35,13 @@ struct LdsLimit {
 hipError_t launch_down_projection(const uint16_t *h, const uint16_t *A, float *tpart,
                                   int rows_here, int d, int r, const DownPlan &dp, const int *mat_of_row, hipStream_t st);
 
-// x = float(h) for the full head.
-hipError_t launch_widen_rows(const uint16_t *h, float *x, int n, hipStream_t st);
-
-// One partial (max, sum of exp, top-k) per (row, 512-column chunk) from x [rows_here, K] (nds = 0) or
-// from nds slices of it (the output of launch_down_projection), and M [K, V].
+// One partial (max, sum of exp, top-k) per (row, chunk of 8 g.lanes columns) from the bf16 rows x [rows_here, K] (nds = 0; wide:
+// fp32 scratch [rows_here, K] for rows too long for shared memory) or from nds slices of a contraction input (the output of
+// launch_down_projection), and M [K, V].
 // part_smp (null: off): one Gumbel-max winner per (row, chunk) for sampling with the seed (seed_lo, seed_hi)
-hipError_t launch_stream_topk(const float *x, int nds, const void *M, bool m_is_f32,
+hipError_t launch_stream_topk(const void *x, int nds, float *wide, const void *M, bool m_is_f32,
                               float2 *part_ms, float *part_val, int *part_id,
-                              int rows_here, int row0, int K, int V, int chunks, int lanes, int nw1, int k,
+                              int rows_here, int row0, int K, int V, const ChunkGeom &g, int k,
                               float4 *part_smp, uint32_t seed_lo, uint32_t seed_hi, hipStream_t st);
 
 // Combine the partials of every row into the final ids and log-probabilities.

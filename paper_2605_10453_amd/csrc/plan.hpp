@@ -34,34 +34,54 @@ inline DownPlan make_down_plan(bool low_rank, int d, int r) {
     return p;
 }
 
-// Geometry of the streaming kernel: a block owns one chunk of 8 * lanes adjacent columns (lanes <= 64 lanes of every
-// wavefront hold columns) and its nw wavefronts split the contraction.  One block of 16 wavefronts fills a CU, so
-// up to 256 chunks run as one round.  A vocabulary with more 512-column chunks than that (151936 columns: 297)
-// would leave 41 CUs with two chunks and the others waiting: for a single row the chunks are instead made narrower
-// and the blocks smaller (8 wavefronts: two blocks share a CU, 512 at once; 4 wavefronts: 1024 at once) so that all
-// of them are resident together and every CU gets the same number of columns within a few per cent.
-struct ChunkGeom { int lanes = 64, nw1 = 16, chunks = 0; };
-inline ChunkGeom make_chunk_geom(int rows, int V) {
+// Geometry of the streaming kernel: a block owns one chunk of 8 * lanes adjacent columns (8 <= lanes <= 64).  A wavefront's
+// lanes cover k_parts rows of the weights at a time, and the block's wavefronts split the contraction (nw1 of them for a single
+// row; the launcher's choice otherwise).  The chunks are made so narrow that every CU gets one, and all of them are resident
+// together: up to 131072 columns as 256 blocks of 16 wavefronts, beyond (297 chunks of 512 at 151936 columns would be two
+// on 41 CUs) for a single row as 512 of 8 or 1024 of 4.  Multiples of 64 columns: whole cache lines wherever the rows are.
+// (With 512 columns whatever V, 66 to 90 CUs of 256 had a block at V = 33184 to 45856: 3.0-3.3 TB/s where 5.2-5.5 are reached now.)
+// Short contractions take smaller blocks: wavefronts without rows only lengthen the barriers.
+constexpr int kNarrowChunkRows = 64;     // more rows (fp32 weights) keep chunks of 512 columns: their lists would fill the workspace
+struct ChunkGeom { int lanes = 64, k_parts = 1, nw1 = 16, chunks = 0; };
+inline ChunkGeom make_chunk_geom(int rows, int K, int V) {
     ChunkGeom g;
-    g.chunks = (V + kChunkCols - 1) / kChunkCols;
-    if (rows == 1 && g.chunks > 256) {
-        const int n16 = (V + 7) / 8;                         // 16-byte column groups
-        const int slots = g.chunks <= 512 ? 512 : 1024;
-        g.nw1 = g.chunks <= 512 ? 8 : 4;
-        if (g.chunks <= slots) {
-            g.lanes = (n16 + slots - 1) / slots;
-            g.chunks = (n16 + g.lanes - 1) / g.lanes;
-        }
+    const int n16 = (V + 7) / 8;                             // 16-byte column groups
+    const int full = (V + kChunkCols - 1) / kChunkCols;
+    int slots = 256;
+    if (rows == 1 && full > 256) {
+        slots = full <= 512 ? 512 : 1024;
+        g.nw1 = full <= 512 ? 8 : 4;
     }
+    if (rows <= kNarrowChunkRows) {
+        g.lanes = ((n16 + slots - 1) / slots + 7) / 8 * 8;
+        if (g.lanes > 64) g.lanes = 64;
+    }
+    g.k_parts = 64 / g.lanes;
+    g.chunks = (n16 + g.lanes - 1) / g.lanes;
+    while (g.nw1 > 4 && g.nw1 * g.k_parts * 4 >= K) g.nw1 /= 2;
     return g;
+}
+
+// How a block's nw wavefronts of k_parts lane groups share the contraction: `per` rows per wavefront, n partial sums in all.
+struct StreamParts { int per, n; };
+constexpr __host__ __device__ StreamParts stream_parts(int nw, int k_parts, int K) {
+    const int step = 8 * k_parts, per = ((K + nw - 1) / nw + step - 1) / step * step;
+    return {per, (K + per - 1) / per * k_parts};
+}
+constexpr int kDirectParts = 16;         // partial sums that a row's epilogue adds by itself; more are first added kSumParts ways
+constexpr int kSumParts = 8;
+// Shared memory of a block for R rows: partial sums, the epilogues' candidates, and the contraction input of x_bytes per element (0: none).
+inline size_t stream_lds_bytes(int R, int nw, const ChunkGeom &g, int K, int x_bytes) {
+    const int n = stream_parts(nw, x_bytes ? g.k_parts : 1, K).n, cw = 8 * g.lanes;
+    return 4 * (size_t)R * cw * (n + (n > kDirectParts ? kSumParts : 0)) + 8 * (size_t)(R < nw ? R : nw) * cw + (size_t)x_bytes * R * K;
 }
 
 struct Plan {
     bool ok = false;
     int rows = 0, d = 0, r = 0, V = 0, k = 0;
     int K = 0;                 // contraction length of the vocabulary projection (r or d)
+    ChunkGeom geom;
     int chunks = 0;            // partials per row
-    int lanes = 64, nw1 = 16;  // see ChunkGeom
     // byte offsets into the workspace
     size_t off_x = 0;          // fp32 [kGemvMaxRows, K]: t (low-rank) or widened h (full)
     size_t off_tpart = 0;      // fp32 [nds, kGemvMaxRows, r]  slices of t
@@ -78,8 +98,8 @@ inline Plan make_plan(HeadKind kind, int rows, int d, int r, int V, int k) {
     Plan p;
     p.rows = rows; p.d = d; p.r = r; p.V = V; p.k = k;
     p.K = (kind == HeadKind::LowRank) ? r : d;
-    const ChunkGeom cg = make_chunk_geom(rows, V);
-    p.chunks = cg.chunks; p.lanes = cg.lanes; p.nw1 = cg.nw1;
+    p.geom = make_chunk_geom(rows, p.K, V);
+    p.chunks = p.geom.chunks;
     size_t off = 0;
     p.off_x = off;          off = align_up(off + sizeof(float) * kGemvMaxRows * (size_t)p.K);
     {
@@ -95,10 +115,14 @@ inline Plan make_plan(HeadKind kind, int rows, int d, int r, int V, int k) {
     return p;
 }
 
-// The largest vocabulary a call may have, by the entries of a row's lists: 8 bytes for every list and 4 for each of its
-// entries, and 8 k k for the winners', within 159 KB.
+// The largest vocabulary a call may have: a row's lists, counted in chunks of 512 columns (for a single row beyond 131072 columns
+// in 512 or 1024 chunks), at 8 bytes for every list and 4 for each of its entries, and 8 k k for the winners', within 159 KB.
 inline bool lists_supported(int rows, int V, int k) {
-    const size_t chunks = (size_t)make_chunk_geom(rows, V).chunks;
+    size_t chunks = ((size_t)V + kChunkCols - 1) / kChunkCols;
+    if (rows == 1 && chunks > 256 && chunks <= 1024) {
+        const size_t n16 = ((size_t)V + 7) / 8, slots = chunks <= 512 ? 512 : 1024, lanes = (n16 + slots - 1) / slots;
+        chunks = (n16 + lanes - 1) / lanes;
+    }
     return 8 * (chunks + (size_t)k * k) + 4 * chunks * k <= 159 * 1024;
 }
 

@@ -253,19 +253,17 @@ int run_head(HeadKind kind, const void *h, const void *A, const void *M, bool m_
             for (int i = 0; i < rows_here; ++i) mat_of_row[i] = pos.n > 0 ? position_of_row(pos, row0 + i) : 0;
             e = launch_down_projection(hb + (size_t)row0 * p.d, static_cast<const uint16_t *>(A),
                                        tpart, rows_here, p.d, p.r, dp, mat_of_row, s);
+            if (e != hipSuccess) return fail_hip(e);
         }
-        else
-            e = launch_widen_rows(hb + (size_t)row0 * p.d, x, rows_here * p.d, s);
-        if (e != hipSuccess) return fail_hip(e);
         const bool timed = g_ev_start && row0 == 0;
         if (timed && (e = hipEventRecord(g_ev_start, s)) != hipSuccess) return fail_hip(e);
-        e = launch_stream_topk(kind == HeadKind::LowRank ? tpart : x, kind == HeadKind::LowRank ? dp.nds : 0, M, m_is_f32,
-                               part_ms, part_val, part_id,
-                               rows_here, row0, p.K, p.V, p.chunks, p.lanes, p.nw1, k, part_smp, so.seed_lo, so.seed_hi, s);
+        e = launch_stream_topk(kind == HeadKind::LowRank ? static_cast<const void *>(tpart) : hb + (size_t)row0 * p.d, kind == HeadKind::LowRank ? dp.nds : 0, x,
+                               M, m_is_f32, part_ms, part_val, part_id,
+                               rows_here, row0, p.K, p.V, p.geom, k, part_smp, so.seed_lo, so.seed_hi, s);
         if (e != hipSuccess) return fail_hip(e);
         if (timed && (e = hipEventRecord(g_ev_stop, s)) != hipSuccess) return fail_hip(e);
     }
-    hipError_t e = launch_merge(part_ms, part_val, part_id, p.rows, p.chunks, 8 * p.lanes, p.V, k, out_ids, out_logprobs, id_map, so, part_smp, s);
+    hipError_t e = launch_merge(part_ms, part_val, part_id, p.rows, p.chunks, 8 * p.geom.lanes, p.V, k, out_ids, out_logprobs, id_map, so, part_smp, s);
     if (e != hipSuccess) return fail_hip(e);
     return SLIMSPEC_OK;
 }
@@ -285,6 +283,10 @@ size_t head_workspace_bytes(HeadKind kind, const slimspec_shape *shape, int32_t 
 {
     if (check_shape(kind, shape, k) != SLIMSPEC_OK) return 0;
     size_t need = make_plan(kind, shape->rows, shape->d, shape->r, shape->V, k).bytes;
+    if (shape->rows > kNarrowChunkRows) {      // (fewer rows have more chunks each: a workspace serves them as well)
+        const size_t w = make_plan(kind, kNarrowChunkRows, shape->d, shape->r, shape->V, k).bytes;
+        if (w > need) need = w;
+    }
     if (shape->rows >= kMfmaMinRows) {
         const size_t m = mfma_workspace_bytes(kind, shape);
         if (m > need) need = m;

@@ -1,0 +1,51 @@
+"""The lane-owns-columns kernel (stream_topk_kernel) against the CPU fp64 checker, at the edges of its chunks and of the way a block
+shares the contraction: chunks of 64 to 512 columns, 1 to 8 rows of the weights at a time, blocks of 4 to 16 wavefronts,
+wavefronts and lane groups without rows, row inputs that shared memory does not hold."""
+import numpy as np
+import pytest
+
+from paper_2605_10453_amd import synth
+from parity_util import compare_with_oracle, to_dev_bf16, to_dev_f32
+from plan_util import assert_plan
+from test_gpu_parity import gpu  # noqa: F401  (the module's fixture)
+
+pytestmark = pytest.mark.gpu
+
+FP32_TOL = 6e-5      # fp32 sums of exact products: see test_gpu_rows_head.py
+
+
+@pytest.mark.parametrize("rows,d,r,V,k", [
+    (1, 64, 8, 8, 3), (1, 64, 8, 64, 64), (1, 72, 16, 72, 5), (1, 128, 40, 16384, 7), (1, 128, 72, 16392, 10), (1, 264, 136, 32776, 9),
+    (1, 64, 264, 37208, 4), (1, 512, 320, 65544, 12), (1, 96, 104, 103472, 5), (1, 64, 24, 131072, 40), (1, 64, 48, 131080, 6),
+    (1, 64, 16, 262152, 5), (1, 64, 8, 530000, 3), (1, 4096, 1032, 2056, 10), (1, 4096, 8, 4104, 33), (1, 64, 5000, 1000, 5),
+    (2, 96, 56, 20000, 11), (2, 64, 1000, 520, 6), (2, 64, 24, 131080, 9), (3, 64, 200, 9000, 17), (4, 520, 264, 40008, 64), (4, 64, 8, 8, 8),
+])
+def test_low_rank(gpu, oracle_mod, rows, d, r, V, k):
+    torch, b = gpu
+    print(f"stream kernel, low-rank: rows={rows} d={d} r={r} V={V} k={k}", flush=True)
+    assert_plan("low", rows, d, r, V, k, kernel="stream")
+    x = synth.make_inputs(synth.small_config(rows, d, r, V, k, peaked_every=2), seed=rows + V)
+    ids, lp = b.slimspec_head_topk(to_dev_bf16(x.h), to_dev_bf16(x.A), to_dev_bf16(x.B), k)
+    torch.cuda.synchronize()
+    ora = oracle_mod.slimspec_head_topk(x.h, x.A, x.B, k)
+    z_at = lambda ri, ci: oracle_mod.slimspec_logits_at(x.h, x.A, x.B, ri, ci)
+    compare_with_oracle(ids.cpu().numpy(), lp.cpu().numpy(), ora.ids, ora.lse, z_at, V, tie_tol=FP32_TOL, lp_tol=FP32_TOL)
+
+
+@pytest.mark.parametrize("rows,d,V,k,fp32", [
+    (1, 8, 8, 2, False), (1, 1000, 37208, 4, False), (1, 3208, 4104, 8, False), (1, 72, 131080, 64 - 4, False), (2, 104, 33000, 5, False),
+    (1, 40000, 520, 5, False),                                                 # h does not fit beside the partial sums
+    (1, 104, 20000, 6, True), (2, 1000, 2056, 6, True), (5, 264, 9000, 10, True), (8, 2048, 1032, 20, True), (8, 6000, 520, 3, True),
+    (19, 136, 8200, 5, True), (70, 72, 1544, 5, True),                         # groups of 8 rows; chunks of 512 columns from 65 rows on
+])
+def test_full_head(gpu, oracle_mod, rows, d, V, k, fp32):
+    torch, b = gpu
+    print(f"stream kernel, full head: rows={rows} d={d} V={V} k={k} fp32={fp32}", flush=True)
+    assert_plan("full", rows, d, 8, V, k, fp32=fp32, kernel="stream")
+    x = synth.make_inputs(synth.small_config(rows, d, 8, V, k, peaked_every=4), seed=rows + d, with_full_head=True)
+    W = synth.bf16_bits_to_f32(x.W) + np.float32(1e-4) if fp32 else x.W
+    ids, lp = b.full_head_topk(to_dev_bf16(x.h), to_dev_f32(W) if fp32 else to_dev_bf16(W), k)
+    torch.cuda.synchronize()
+    ora = oracle_mod.full_head_topk(x.h, W, k)
+    z_at = lambda ri, ci: oracle_mod.full_logits_at(x.h, W, ri, ci)
+    compare_with_oracle(ids.cpu().numpy(), lp.cpu().numpy(), ora.ids, ora.lse, z_at, V, tie_tol=FP32_TOL, lp_tol=FP32_TOL)
