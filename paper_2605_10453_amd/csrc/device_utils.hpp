@@ -125,50 +125,50 @@ __device__ __forceinline__ uint64_t wave_max_key(uint64_t k) {
     return u64_max(u64_from(ha, la), u64_from(hb, lb));
 }
 
-// Sorts the 64 lanes' values in descending order (lane i: the i-th largest): a bitonic network, 21 exchanges between
-// lanes, each two DPP min / max and a select.  An exchange pairs lane i with i ^ 1, 2, 8, 16 directly, with the mirror
-// image in its block of 4, 8, 16, 32 or 64, and with i ^ 4 as mirror in 8 after mirror in 4.
-__device__ __forceinline__ uint32_t wave_sort_desc(uint32_t v, int lane) {
-    const auto keep = [&](uint32_t p, int upper_bit) {           // the lane below the partner keeps the larger value
-        const uint32_t hi = v > p ? v : p, lo = v > p ? p : v;
-        v = (lane & upper_bit) ? lo : hi;
-    };
-    const auto keep_swapped = [&](uint32_t a, uint32_t b, int upper_bit) {
-        const uint32_t hi = a > b ? a : b, lo = a > b ? b : a;
-        v = (lane & upper_bit) ? lo : hi;
-    };
+// Bitonic sorts across lanes, descending.  An exchange pairs lane i with i ^ 1, 2, 8, 16 directly, with the mirror image in its
+// block of 4, 8, 16, 32 or 64, and with i ^ 4 as mirror in 8 after mirror in 4: two DPP min / max and a select each.
+__device__ __forceinline__ void sort_keep(uint32_t &v, uint32_t p, int lane, int upper_bit) {
+    const uint32_t hi = v > p ? v : p, lo = v > p ? p : v;       // the lane below the partner keeps the larger value
+    v = (lane & upper_bit) ? lo : hi;
+}
+// the value of the lane 16 away (XOR), of x
+__device__ __forceinline__ uint32_t lane_xor16(uint32_t x, int lane) {
     uint32_t a, b;
-#define SLIMSPEC_X1 keep(dpp_u32<0xB1>(v), 1);
-#define SLIMSPEC_X2 keep(dpp_u32<0x4E>(v), 2);
-#define SLIMSPEC_X4 keep(dpp_u32<0x141>(dpp_u32<0x1B>(v)), 4);
-#define SLIMSPEC_X8 keep(dpp_u32<0x128>(v), 8);
+    swap_pair<16>(x, a, b);
+    return (lane & 16) ? a : b;
+}
+#define SLIMSPEC_X1 sort_keep(v, dpp_u32<0xB1>(v), lane, 1);
+#define SLIMSPEC_X2 sort_keep(v, dpp_u32<0x4E>(v), lane, 2);
+#define SLIMSPEC_X4 sort_keep(v, dpp_u32<0x141>(dpp_u32<0x1B>(v)), lane, 4);
+#define SLIMSPEC_X8 sort_keep(v, dpp_u32<0x128>(v), lane, 8);
+// each half of 32 lanes by itself (lane i of a half: the i-th largest): 15 exchanges
+__device__ __forceinline__ uint32_t half_sort_desc(uint32_t v, int lane) {
     SLIMSPEC_X1
-    keep(dpp_u32<0x1B>(v), 2); SLIMSPEC_X1
-    keep(dpp_u32<0x141>(v), 4); SLIMSPEC_X2 SLIMSPEC_X1
-    keep(dpp_u32<0x140>(v), 8); SLIMSPEC_X4 SLIMSPEC_X2 SLIMSPEC_X1
-    // mirror in 32: the upper row of 16 meets the lower one reversed
-    {
-        const uint32_t m = dpp_u32<0x140>(v);
-        swap_pair<16>(m, a, b);
-        keep((lane & 16) ? a : b, 16);
-    }
+    sort_keep(v, dpp_u32<0x1B>(v), lane, 2); SLIMSPEC_X1
+    sort_keep(v, dpp_u32<0x141>(v), lane, 4); SLIMSPEC_X2 SLIMSPEC_X1
+    sort_keep(v, dpp_u32<0x140>(v), lane, 8); SLIMSPEC_X4 SLIMSPEC_X2 SLIMSPEC_X1
+    sort_keep(v, lane_xor16(dpp_u32<0x140>(v), lane), lane, 16);             // mirror in 32: the upper row of 16 meets the lower one reversed
     SLIMSPEC_X8 SLIMSPEC_X4 SLIMSPEC_X2 SLIMSPEC_X1
-    {
-        uint32_t m = dpp_u32<0x140>(v);                          // mirror in 64
-        swap_pair<16>(m, a, b);
-        m = (lane & 16) ? a : b;
-        swap_pair<32>(m, a, b);
-        keep((lane & 32) ? a : b, 32);
-    }
-    swap_pair<16>(v, a, b);
-    keep_swapped(a, b, 16);
+    return v;
+}
+// each half's 32 values, where they are a bitonic sequence
+__device__ __forceinline__ uint32_t half_merge_desc(uint32_t v, int lane) {
+    sort_keep(v, lane_xor16(v, lane), lane, 16);
     SLIMSPEC_X8 SLIMSPEC_X4 SLIMSPEC_X2 SLIMSPEC_X1
+    return v;
+}
+// all 64 lanes (lane i: the i-th largest): 21 exchanges
+__device__ __forceinline__ uint32_t wave_sort_desc(uint32_t v, int lane) {
+    v = half_sort_desc(v, lane);
+    uint32_t a, b;
+    swap_pair<32>(lane_xor16(dpp_u32<0x140>(v), lane), a, b);                // mirror in 64
+    sort_keep(v, (lane & 32) ? a : b, lane, 32);
+    return half_merge_desc(v, lane);
+}
 #undef SLIMSPEC_X1
 #undef SLIMSPEC_X2
 #undef SLIMSPEC_X4
 #undef SLIMSPEC_X8
-    return v;
-}
 
 // ---------------------------------------------------------------------------
 // Standard Gumbel noise as a pure function of (seed, row, vocabulary id), for one draw per row from softmax(z) by

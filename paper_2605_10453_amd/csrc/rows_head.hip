@@ -17,9 +17,13 @@
 //     every block is resident at once (at most 256 chunks): no last, nearly empty round.
 // The partials have the layout of the streaming kernel's, and the same merge kernel finishes the call.
 //
-// Measured at d = 4096, r = 512, V = 128256 (kernel alone; 131 MB of weights are 22-26 us at a plain read's rate): 2 rows
-// 26.6 us, 40 rows 40 us (the epilogue of five rows per wavefront is what the difference consists of).  Calls: 40 rows
-// with k = 32 420 -> 61 us, 23 rows with k = 10 58.0 -> 48.7 us, 4 rows with k = 64 81 -> 50 us.  Error of the
+// The epilogue is a chain of a few hundred instructions per row that nothing overlaps.  With lists of up to 32 ids a wavefront
+// takes two rows at a time (the sort, the reductions and the ranking serve both), and what a lane holds of a row is known
+// when compiled (GM): without it every step branched.
+//
+// Measured at d = 4096, r = 512, V = 128256 (kernel alone; 131 MB of weights are 22-26 us at a plain read's rate; one row per
+// wavefront and step, in brackets): 23 rows, k = 10 28.6 us (33.0), 40 rows, k = 32 37.7 (42.9), 4 rows, k = 64 30.1 (31.3); 27 rows with
+// draws, r = 456, V = 31664 17.5 (22.4).  Calls: 40 rows with k = 32 54.4 us, 23 rows 45.2.  Error of the
 // log-probabilities against 64-bit arithmetic: 7.7e-8 relative, 1.0e-7 with one multiply-add per weight (40 rows, k = 32).
 #include "gemv_parts.hpp"
 #include "launch.hpp"
@@ -32,13 +36,52 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kRowsMaxG = kRowsMaxColGroups;
 
 // Two 16-bit elements (low or high halves of a and b) as one operand dword: a's element first.
 template <bool HIGH>
 __device__ __forceinline__ uint32_t pair16(uint32_t a, uint32_t b) {
     return __builtin_amdgcn_perm(b, a, HIGH ? 0x07060302u : 0x05040100u);
 }
+
+// What the epilogue of two rows needs in shared memory beside their logits, per wavefront: each row's candidates.
+constexpr int kPairCand = 64;
+constexpr int kPairMaxK = 32;            // longer lists take one row per wavefront
+constexpr int kPairKeys = kPairCand + 2; // (the two rows' candidates in different banks)
+
+// Sum over each half of 32 lanes, in every lane of it.
+__device__ __forceinline__ float half_sum(float v) {
+    v += dpp_f32<0xB1>(v);
+    v += dpp_f32<0x4E>(v);
+    v += dpp_f32<0x141>(v);
+    v += dpp_f32<0x140>(v);
+    uint32_t a, b;
+    swap_pair<16>(__float_as_uint(v), a, b);
+    return __uint_as_float(a) + __uint_as_float(b);
+}
+__device__ __forceinline__ uint64_t half_max_key(uint64_t k) {
+    const auto step = [&](uint32_t hi, uint32_t lo) { k = u64_max(k, u64_from(hi, lo)); };
+    step(dpp_u32<0xB1>((uint32_t)(k >> 32)), dpp_u32<0xB1>((uint32_t)k));
+    step(dpp_u32<0x4E>((uint32_t)(k >> 32)), dpp_u32<0x4E>((uint32_t)k));
+    step(dpp_u32<0x141>((uint32_t)(k >> 32)), dpp_u32<0x141>((uint32_t)k));
+    step(dpp_u32<0x140>((uint32_t)(k >> 32)), dpp_u32<0x140>((uint32_t)k));
+    uint32_t ha, hb, la, lb;
+    swap_pair<16>((uint32_t)(k >> 32), ha, hb);
+    swap_pair<16>((uint32_t)k, la, lb);
+    return u64_max(u64_from(ha, la), u64_from(hb, lb));
+}
+// Sum of v over the lanes of this half up to and including this one.
+__device__ __forceinline__ uint32_t half_prefix_sum(uint32_t v) {
+    v += dpp_u32<0x111>(v);                                      // row_shr:1, 2, 4, 8 (zero from outside the row of 16)
+    v += dpp_u32<0x112>(v);
+    v += dpp_u32<0x114>(v);
+    v += dpp_u32<0x118>(v);
+    return v + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);      // row_bcast:15 into the upper row of a half
+}
+// bits = 2 bits + (z >= t)
+__device__ __forceinline__ void shift_in_ge(uint32_t &bits, float z, float t) {
+    asm("v_cmp_ge_f32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(bits) : "v"(z), "v"(t) : "vcc");
+}
+__device__ __forceinline__ float max3_number(float a, float b, float c) { float d; asm("v_max3_f32 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c)); return d; }
 
 }  // namespace
 
@@ -47,7 +90,8 @@ __device__ __forceinline__ uint32_t pair16(uint32_t a, uint32_t b) {
 // M: [K, V] bf16 row-major, V and K multiples of 8
 // Block b: columns [128 G b, 128 G (b + 1)); wavefront w: column group w % G, contraction slice w / G (none from KS on).
 // Partials of (row, chunk): see stream_topk_kernel.  row0: the index in the call of this launch's first row (noise).
-template <int NT, int NP>
+// GM: G at most (what a lane keeps of a row's logits is sized by it: known when compiled, or every step of the epilogue branches)
+template <int NT, int NP, int GM>
 __global__ __launch_bounds__(512) void rows_topk_kernel(
     const uint4 *__restrict__ X, const uint16_t *__restrict__ M,
     float2 *__restrict__ part_ms, float *__restrict__ part_val, int *__restrict__ part_id, float4 *__restrict__ part_smp,
@@ -125,29 +169,47 @@ __global__ __launch_bounds__(512) void rows_topk_kernel(
             }
         };
         // Two steps of weights in flight.  Loads return in order, so a step's row operand is requested before the
-        // weights of the step after it: waiting for it leaves those in flight.
-        if (s_beg < s_end) {
-            load_m(q[0], s_beg);
-            load_x(s_beg);
-            __builtin_amdgcn_sched_barrier(0);
-            load_m(q[1], min(s_beg + 1, s_end - 1));
-            __builtin_amdgcn_sched_barrier(0);
+        // weights of the step after it: waiting for it leaves those in flight.  No step is requested that does not exist: its
+        // registers could not be used again before it had arrived, at the end of the block, when nothing hides the trip (0.7 us
+        // at 2 to 23 rows).  But with three row tiles the copies of the step that this takes do not fit the registers.
+        const auto then = []() __attribute__((always_inline)) { __builtin_amdgcn_sched_barrier(0); };
+        if (NT == 3 && s_beg < s_end) {
+            load_m(q[0], s_beg); load_x(s_beg); then();
+            load_m(q[1], min(s_beg + 1, s_end - 1)); then();
             for (int s = s_beg; s < s_end; s += 2) {
-                multiply(q[0], s);
-                __builtin_amdgcn_sched_barrier(0);
+                multiply(q[0], s); then();
                 if (s + 1 < s_end) {
-                    load_x(s + 1);
-                    __builtin_amdgcn_sched_barrier(0);
-                    load_m(q[0], min(s + 2, s_end - 1));         // (past the end: the last step once more, unused)
-                    __builtin_amdgcn_sched_barrier(0);
-                    multiply(q[1], s + 1);
-                    __builtin_amdgcn_sched_barrier(0);
-                    load_x(min(s + 2, s_end - 1));
-                    __builtin_amdgcn_sched_barrier(0);
-                    load_m(q[1], min(s + 3, s_end - 1));
-                    __builtin_amdgcn_sched_barrier(0);
+                    load_x(s + 1); then();
+                    load_m(q[0], min(s + 2, s_end - 1)); then();         // (past the end: the last step once more, unused)
+                    multiply(q[1], s + 1); then();
+                    load_x(min(s + 2, s_end - 1)); then();
+                    load_m(q[1], min(s + 3, s_end - 1)); then();
                 }
             }
+        } else if (s_beg + 1 == s_end) {
+            load_m(q[0], s_beg); load_x(s_beg); then();
+            multiply(q[0], s_beg);
+        } else if (s_beg < s_end) {
+            load_m(q[0], s_beg); load_x(s_beg); then();
+            load_m(q[1], s_beg + 1); then();
+            int s = s_beg;
+            for (; s + 3 < s_end; s += 2) {
+                multiply(q[0], s); then();
+                load_x(s + 1); then();
+                load_m(q[0], s + 2); then();
+                multiply(q[1], s + 1); then();
+                load_x(s + 2); then();
+                load_m(q[1], s + 3); then();
+            }
+            multiply(q[0], s); then();                           // two or three steps are left
+            load_x(s + 1); then();
+            if (s + 2 < s_end) {
+                load_m(q[0], s + 2); then();
+                multiply(q[1], s + 1); then();
+                load_x(s + 2); then();
+                multiply(q[0], s + 2);
+            } else
+                multiply(q[1], s + 1);
         }
     }
 
@@ -173,19 +235,23 @@ __global__ __launch_bounds__(512) void rows_topk_kernel(
         __syncthreads();
     }
 
-    // One wavefront per row: running max, sum of exp and top-k of the chunk.  Lane = columns 2 lane, 2 lane + 1 of every
+    // One row by a whole wavefront: running max, sum of exp and top-k of the chunk.  Lane = columns 2 lane, 2 lane + 1 of every
     // group of 128.
-    constexpr int E = 2 * kRowsMaxG;
-    const auto act = [&](int g) { return chunk_col + 128 * g + 2 * lane < V; };      // V is even: both columns or none
-    const auto id = [&](int e) { return (uint32_t)(chunk_col + 128 * (e >> 1) + 2 * lane + (e & 1)); };
-    for (int row = wave; row < rows; row += (int)(blockDim.x >> 6)) {
+    constexpr int E = 2 * GM;
+    const auto finish_row = [&](int row) __attribute__((always_inline)) {
+        // (what does not depend on the row would be computed ahead of the loop over the rows, by the calls too that never come
+        // here: 0.6 us at the end of every block)
+        int lane = tid & 63;
+        asm volatile("" : "+v"(lane));
+        const auto act = [&](int g) { return (g < GM / 2 + 1 || g < G) && chunk_col + 128 * g + 2 * lane < V; };      // V is even: both columns or none
+        const auto id = [&](int e) { return (uint32_t)(chunk_col + 128 * (e >> 1) + 2 * lane + (e & 1)); };
         float *zr = z_lds + row * row_stride;
         const size_t slot = (size_t)row * chunks + blockIdx.x;
         float z[E], m = kNegInf, s = 0.f;
 #pragma unroll
-        for (int g = 0; g < kRowsMaxG; ++g) {
+        for (int g = 0; g < GM; ++g) {
             float2 v = make_float2(kNegInf, kNegInf);
-            if (g < G && act(g)) v = *reinterpret_cast<const float2 *>(zr + 128 * g + 2 * lane);
+            if (act(g)) v = *reinterpret_cast<const float2 *>(zr + 128 * g + 2 * lane);
             z[2 * g] = v.x; z[2 * g + 1] = v.y;
         }
         const auto max_and_sum = [&]() {
@@ -195,8 +261,8 @@ __global__ __launch_bounds__(512) void rows_topk_kernel(
             m = wave_max(m);
             s = 0.f;
 #pragma unroll
-            for (int g = 0; g < kRowsMaxG; ++g)
-                if (g < G) s += fast_exp(z[2 * g] - m) + fast_exp(z[2 * g + 1] - m);     // exp(-inf) = 0 beyond V
+            for (int g = 0; g < GM; ++g)
+                s += fast_exp(z[2 * g] - m) + fast_exp(z[2 * g + 1] - m);     // exp(-inf) = 0 beyond V
             s = wave_sum(s);
         };
         max_and_sum();
@@ -237,7 +303,7 @@ __global__ __launch_bounds__(512) void rows_topk_kernel(
                     }
                 }
 #pragma unroll
-                for (int gg = 0; gg < kRowsMaxG; ++gg)
+                for (int gg = 0; gg < GM; ++gg)
                     if (gg == g) { z[2 * gg] = z0; z[2 * gg + 1] = z1; }
             }
             max_and_sum();
@@ -249,7 +315,7 @@ __global__ __launch_bounds__(512) void rows_topk_kernel(
             float zb = 0.f;
 #pragma unroll
             for (int e = 0; e < E; ++e)
-                if ((e >> 1) < G && act(e >> 1)) {
+                if (act(e >> 1)) {
                     const uint64_t key = make_key(z[e] + gumbel_base2(gk, id(e)) * kLn2, id(e));
                     if (key > best) { best = key; zb = z[e]; }
                 }
@@ -260,33 +326,164 @@ __global__ __launch_bounds__(512) void rows_topk_kernel(
         if (lane == 0) part_ms[slot] = make_float2(m, s);
         uint32_t ob[E];
 #pragma unroll
-        for (int e = 0; e < E; ++e) ob[e] = ((e >> 1) < G && act(e >> 1)) ? float_order_bits(z[e]) : 0u;
+        for (int e = 0; e < E; ++e) ob[e] = act(e >> 1) ? float_order_bits(z[e]) : 0u;
         // the candidates' keys go where the row's logits were
         lds_wave_sync();
         wave_topk<E>(ob, 2 * G, id, lane, k, reinterpret_cast<uint64_t *>(zr), row_stride / 2, part_val + slot * k, part_id + slot * k);
+    };
+
+    const int n_waves = (int)(blockDim.x >> 6);
+    // Lists of up to kPairMaxK ids: two rows at a time, one per half-wavefront.  This is bound by its own instruction count, and
+    // everything that is done once per row (the sort, the reductions, the ranking) then serves two.  Lane = columns
+    // 4 l ... 4 l + 3 of every group of 128.  Rows that hold something else than finite numbers, more candidates than
+    // the buffer or fewer than k lanes with columns go through finish_row.
+    const int half = lane >> 5, l32 = lane & 31;
+    const auto act4 = [&](int g) { return (g < GM / 2 + 1 || g < G) && chunk_col + 128 * g + 4 * l32 < V; };      // all four columns or none
+    uint32_t *const cand_bits = reinterpret_cast<uint32_t *>(z_lds + RP * row_stride) + (wave * 2 + half) * (2 * kPairKeys), *const cand_id = cand_bits + kPairCand;
+    const auto finish_pair = [&](int row0p) __attribute__((always_inline)) {                    // false: these rows are finish_row's
+        const int row = row0p + half;                            // (an odd last row is done twice, and written once)
+        const bool exists = row < rows;
+        const float *zr = z_lds + min(row, rows - 1) * row_stride + 4 * l32;
+        const size_t slot = (size_t)min(row, rows - 1) * chunks + blockIdx.x;
+        float z[4 * GM], sub[2] = {kNegInf, kNegInf};
+#pragma unroll
+        for (int g = 0; g < GM; ++g)
+            {
+                float4 v = make_float4(kNegInf, kNegInf, kNegInf, kNegInf);
+                if (act4(g)) v = *reinterpret_cast<const float4 *>(zr + 128 * g);      // all four columns or none
+                z[4 * g] = v.x; z[4 * g + 1] = v.y; z[4 * g + 2] = v.z; z[4 * g + 3] = v.w;
+                sub[0] = max3_number(sub[0], v.x, v.y);
+                sub[1] = max3_number(sub[1], v.z, v.w);
+            }
+        // T: the k-th largest of the row's 32 lane maxima, or of the 64 maxima of half lanes (k > 16): k elements reach it
+        uint32_t sorted;
+        if (k <= 16) sorted = half_sort_desc(float_order_bits(fmaxf(sub[0], sub[1])), lane);
+        else {
+            const uint32_t a = half_sort_desc(float_order_bits(sub[0]), lane), b = half_sort_desc(float_order_bits(sub[1]), lane);
+            const uint32_t rev = lane_xor16(dpp_u32<0x140>(b), lane);
+            sorted = half_merge_desc(a > rev ? a : rev, lane);   // the 32 largest of both
+        }
+        const auto of_half = [&](int at) {
+            const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)sorted, at), hi = (uint32_t)__builtin_amdgcn_readlane((int)sorted, 32 + at);
+            return float_from_order_bits(half ? hi : lo);
+        };
+        const float m = of_half(0), T = of_half(k - 1);
+        float s = 0.f;
+#pragma unroll
+        for (int g = 0; g < GM; ++g)
+            s += (fast_exp(z[4 * g] - m) + fast_exp(z[4 * g + 1] - m)) + (fast_exp(z[4 * g + 2] - m) + fast_exp(z[4 * g + 3] - m));      // exp(-inf) = 0 beyond V
+        s = half_sum(s);
+        uint32_t bits = 0u;                                      // the elements that reach T, the first one in the highest place
+#pragma unroll
+        for (int e = 0; e < 4 * GM; ++e) shift_in_ge(bits, z[e], T);
+        const uint32_t mine = (uint32_t)__popc(bits), upto = half_prefix_sum(mine);
+        const int n0 = __builtin_amdgcn_readlane((int)upto, 31), n1 = __builtin_amdgcn_readlane((int)upto, 63), n_max = max(n0, n1);
+        if (n_max > kPairCand || __ballot(!(s < __builtin_huge_valf()) || T == kNegInf) != 0ull) return false;
+        const auto id_at = [&](int e) { return (uint32_t)(chunk_col + 128 * (e >> 2) + 4 * l32 + (e & 3)); };
+        if (part_smp) {
+            const GumbelKey gk = gumbel_key(seed_lo, seed_hi, (uint32_t)(row0 + row));
+            uint64_t best = kNoKey;
+            float zb = 0.f;
+#pragma unroll
+            for (int e = 0; e < 4 * GM; ++e)
+                if (act4(e >> 2)) {
+                    const uint64_t key = make_key(z[e] + gumbel_base2(gk, id_at(e)) * kLn2, id_at(e));
+                    if (key > best) { best = key; zb = z[e]; }
+                }
+            const uint64_t top = half_max_key(best);             // keys are unique: one lane of the half holds it
+            if (exists && best == top && best != kNoKey)
+                part_smp[slot] = make_float4(key_value(top), __int_as_float((int)key_tiebreak(top)), zb, 0.f);
+        }
+        if (exists && l32 == 0) part_ms[slot] = make_float2(m, s);
+        // The candidates, compacted, in the row's part of the buffer: first their order bits, then their ids.
+        uint32_t at = upto - mine;
+        const int n = half ? n1 : n0;
+        if (l32 >= n) cand_bits[l32] = 0u;                       // what follows the last is cleared for the ranking
+        if (32 + l32 >= n) cand_bits[32 + l32] = 0u;
+        while (__ballot(bits != 0u) != 0ull) {
+            if (bits != 0u) {
+                const int top_bit = 31 - __clz((int)bits), e = 4 * GM - 1 - top_bit;
+                cand_bits[at] = float_order_bits(zr[128 * (e >> 2) + (e & 3)]);
+                cand_id[at++] = id_at(e);
+                bits ^= 1u << top_bit;
+            }
+        }
+        lds_wave_sync();
+        // Ranked by their logits alone; equal ones (the same rank twice) are told apart by their ids afterwards.
+        const uint32_t b0 = cand_bits[l32], b1 = cand_bits[32 + l32], i0 = cand_id[l32], i1 = cand_id[32 + l32];
+        int r0 = 0, r1 = 0;
+        const uint4 *four = reinterpret_cast<const uint4 *>(cand_bits);
+        if (n_max <= 32) {
+#pragma unroll 2
+            for (int q = 0; q < n_max; q += 4) {
+                const uint4 c = four[q >> 2];
+                r0 += (c.x > b0 ? 1 : 0) + (c.y > b0 ? 1 : 0) + (c.z > b0 ? 1 : 0) + (c.w > b0 ? 1 : 0);
+            }
+        } else {
+#pragma unroll 2
+            for (int q = 0; q < n_max; q += 4) {
+                const uint4 c = four[q >> 2];
+                r0 += (c.x > b0 ? 1 : 0) + (c.y > b0 ? 1 : 0) + (c.z > b0 ? 1 : 0) + (c.w > b0 ? 1 : 0);
+                r1 += (c.x > b1 ? 1 : 0) + (c.y > b1 ? 1 : 0) + (c.z > b1 ? 1 : 0) + (c.w > b1 ? 1 : 0);
+            }
+        }
+        lds_wave_sync();
+        const bool have0 = l32 < n, have1 = 32 + l32 < n;
+        if (have0) cand_bits[r0] = (uint32_t)l32;
+        if (have1) cand_bits[r1] = (uint32_t)(32 + l32);
+        lds_wave_sync();
+        if (__ballot((have0 && cand_bits[r0] != (uint32_t)l32) || (have1 && cand_bits[r1] != (uint32_t)(32 + l32))) != 0ull) {
+            lds_wave_sync();
+            if (have0) cand_bits[l32] = b0;
+            if (have1) cand_bits[32 + l32] = b1;
+            lds_wave_sync();
+            for (int q = 0; q < n_max; ++q) {                    // (beyond a row's n: cleared bits, or a stale rank below any finite logit's)
+                const uint32_t c = q < n ? cand_bits[q] : 0u, ci = cand_id[q];
+                r0 += c == b0 && ci < i0 ? 1 : 0;
+                r1 += c == b1 && ci < i1 ? 1 : 0;
+            }
+        }
+        const auto put = [&](uint32_t bits_of, uint32_t id_of, int rank) {
+            part_val[slot * k + rank] = float_from_order_bits(bits_of);
+            part_id[slot * k + rank] = (int)id_of;
+        };
+        if (exists && have0 && r0 < k) put(b0, i0, r0);
+        if (n_max > 32 && exists && have1 && r1 < k) put(b1, i1, r1);
+        lds_wave_sync();                                         // the buffer is this wavefront's next rows'
+        return true;
+    };
+    // (Up to a row per wavefront and long lists, one row each: 7 rows, k = 27 7.1 us against 7.4.)
+    const int at_once = k <= 16 || (k <= kPairMaxK && rows > n_waves) ? 2 : 1;
+    for (int row = at_once * wave; row < rows; row += at_once * n_waves) {
+        const int n_left = (at_once == 2 && finish_pair(row)) ? 0 : min(at_once, rows - row);
+#pragma unroll 1
+        for (int q = 0; q < n_left; ++q) finish_row(row + q);
     }
 }
 
-template <int NT, int NP>
+template <int NT, int NP, int GM>
 static hipError_t launch_rows(const void *X, const uint16_t *M, float2 *ms, float *pv, int *pi, float4 *smp, int rows, int row0,
                               int K, int V, const RowsGeom &g, int k, uint32_t seed_lo, uint32_t seed_hi, hipStream_t st)
 {
-    const size_t lds = sizeof(float) * 16 * NT * (size_t)rows_lds_stride(g.G);
+    const size_t lds = sizeof(float) * 16 * NT * (size_t)rows_lds_stride(g.G) + (k <= kPairMaxK ? sizeof(uint64_t) * 2 * kPairKeys * g.waves : 0);
     static LdsLimit lds_limit;
-    hipError_t e = lds_limit.raise(reinterpret_cast<const void *>(rows_topk_kernel<NT, NP>), (int)lds);
+    hipError_t e = lds_limit.raise(reinterpret_cast<const void *>(rows_topk_kernel<NT, NP, GM>), (int)lds);
     if (e != hipSuccess) return e;
-    rows_topk_kernel<NT, NP><<<g.chunks, 64 * g.waves, lds, st>>>(static_cast<const uint4 *>(X), M, ms, pv, pi, smp, rows, row0,
-                                                                    K, V, g.chunks, g.G, g.KS, k, seed_lo, seed_hi);
+    rows_topk_kernel<NT, NP, GM><<<g.chunks, 64 * g.waves, lds, st>>>(static_cast<const uint4 *>(X), M, ms, pv, pi, smp, rows, row0,
+                                                                      K, V, g.chunks, g.G, g.KS, k, seed_lo, seed_hi);
     return hipGetLastError();
 }
 
 hipError_t launch_rows_topk(const void *X, int pieces, const uint16_t *M, float2 *ms, float *pv, int *pi, float4 *smp,
                             int rows, int row0, int K, int V, const RowsGeom &g, int k, uint32_t seed_lo, uint32_t seed_hi, hipStream_t st)
 {
-#define SLIMSPEC_ROWS(NT, NP) launch_rows<NT, NP>(X, M, ms, pv, pi, smp, rows, row0, K, V, g, k, seed_lo, seed_hi, st)
+    static_assert(kRowsMaxColGroups == 6, "the instances cover G = 1, 2, up to 4 and up to 6");
+#define SLIMSPEC_ROWS_G(NT, NP, GM) launch_rows<NT, NP, GM>(X, M, ms, pv, pi, smp, rows, row0, K, V, g, k, seed_lo, seed_hi, st)
+#define SLIMSPEC_ROWS(NT, NP) (g.G == 1 ? SLIMSPEC_ROWS_G(NT, NP, 1) : g.G == 2 ? SLIMSPEC_ROWS_G(NT, NP, 2) : g.G <= 4 ? SLIMSPEC_ROWS_G(NT, NP, 4) : SLIMSPEC_ROWS_G(NT, NP, 6))
     if (pieces == 1) return rows <= 16 ? SLIMSPEC_ROWS(1, 1) : rows <= 32 ? SLIMSPEC_ROWS(2, 1) : SLIMSPEC_ROWS(3, 1);
     return rows <= 16 ? SLIMSPEC_ROWS(1, 3) : rows <= 32 ? SLIMSPEC_ROWS(2, 3) : SLIMSPEC_ROWS(3, 3);
 #undef SLIMSPEC_ROWS
+#undef SLIMSPEC_ROWS_G
 }
 
 }  // namespace slimspec

@@ -6,6 +6,7 @@ import pytest
 
 from paper_2605_10453_amd import synth
 from parity_util import compare_with_oracle, to_dev_bf16
+from plan_util import assert_plan
 from test_gpu_parity import gpu  # noqa: F401  (the module's fixture)
 
 pytestmark = pytest.mark.gpu
@@ -75,3 +76,41 @@ def test_infinite_weights_and_hidden_states(gpu):
         torch.cuda.synchronize()
         assert torch.equal(ids[i], want_ids[0]), (i, ids[i], want_ids[0])
         assert torch.allclose(lp[i], want_lp[0], atol=FP32_TOL, rtol=0, equal_nan=True), (i, lp[i], want_lp[0])
+
+
+@pytest.mark.parametrize("rows", [3, 5, 9, 16, 17, 33])
+@pytest.mark.parametrize("k", [16, 17, 32, 33])
+@pytest.mark.parametrize("V", [64, 4104, 40000])
+def test_rows_in_pairs(gpu, oracle_mod, rows, k, V):
+    """Two rows per wavefront: odd numbers of rows, both ways to bound a list, equal logits (columns of period 24: each value 2 to 1700
+    times), a row with an infinite weight's logits beside an ordinary one, and a draw per row."""
+    from test_gpu_heads_next import check_sample_outputs
+    torch, b = gpu
+    d, r = 64, 72
+    print(f"rows in pairs: rows={rows} k={k} V={V}", flush=True)
+    x = synth.make_inputs(synth.small_config(rows, d, r, V, k, peaked_every=3), seed=rows + k)
+    h, A = to_dev_bf16(x.h), to_dev_bf16(x.A)
+    assert_plan("full", rows, r, 8, V, k, kernel="rows", sampling=True)
+    W = x.B                                              # the full head takes rows as they are: every value of z is exact up to fp32 sums
+    hr = np.ascontiguousarray(np.tile(x.h, (1, 2))[:, :r])
+    out = b.full_head_sample(to_dev_bf16(hr), to_dev_bf16(W), k, 5)
+    torch.cuda.synchronize()
+    ora = oracle_mod.head_sample(hr, None, W, k, 5, return_logits=True)
+    check_sample_outputs(torch, out, ora, 5, V, ora.z, oracle_mod)
+    assert np.abs(out[2].cpu().numpy() - ora.lse).max() <= FP32_TOL
+    period = np.ascontiguousarray(np.tile(W[:, :24], (1, V // 24 + 1))[:, :V])
+    ids, lp = b.full_head_topk(to_dev_bf16(hr), to_dev_bf16(period), k)
+    torch.cuda.synchronize()
+    ora = oracle_mod.full_head_topk(hr, period, k)
+    z_at = lambda ri, ci: oracle_mod.full_logits_at(hr, period, ri, ci)
+    compare_with_oracle(ids.cpu().numpy(), lp.cpu().numpy(), ora.ids, ora.lse, z_at, V, tie_tol=FP32_TOL, lp_tol=FP32_TOL)
+    for row in ids.cpu().numpy():                        # among equal logits the smaller id comes first
+        for res in range(24):
+            mine = row[row % 24 == res]
+            assert np.array_equal(mine, res + 24 * np.arange(len(mine)))
+    Bi = to_dev_bf16(x.B)
+    Bi[3, V // 2] = float("inf")
+    ids, lp = b.slimspec_head_topk(h, A, Bi, k)
+    want, want_lp = b.slimspec_head_topk(h[:1].contiguous(), A, Bi, k)
+    torch.cuda.synchronize()
+    assert torch.equal(ids[0], want[0]) and torch.allclose(lp[0], want_lp[0], atol=FP32_TOL, rtol=0, equal_nan=True)
