@@ -136,8 +136,9 @@ def slimspec_set_timing_events(start_event: Optional[torch.cuda.Event],
 
 
 def _stream_handle(stream: Optional[torch.cuda.Stream]) -> int:
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return int(s.cuda_stream)
+    if stream is None:      # the current stream's handle without a Stream object around it (1.5 us a call less)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return int(stream.cuda_stream)
 
 
 def _dev_ptr(t: torch.Tensor, name: str) -> int:
@@ -155,14 +156,15 @@ def _outputs(rows, k, device, out_ids, out_logprobs):
         out_logprobs = torch.empty((rows, k), dtype=torch.float32, device=device)
     if out_ids.dtype != torch.int32 or out_logprobs.dtype != torch.float32:
         raise ValueError("out_ids must be int32 and out_logprobs float32")
-    if tuple(out_ids.shape) != (rows, k) or tuple(out_logprobs.shape) != (rows, k):
+    if out_ids.shape != (rows, k) or out_logprobs.shape != (rows, k):
         raise ValueError("outputs must be [rows, k]")
     return out_ids, out_logprobs
 
 
-def _workspace(nbytes: int, device, workspace):
+def _workspace(query, shape, k: int, device, workspace):
+    """The caller's workspace (the call itself checks its size), or a new one of the size that `query` names."""
     if workspace is None:
-        workspace = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=device)
+        workspace = torch.empty(max(int(query(shape, k)), 256), dtype=torch.uint8, device=device)
     return workspace
 
 
@@ -185,12 +187,11 @@ def slimspec_head_topk(h: torch.Tensor, A: torch.Tensor, B: torch.Tensor, k: int
             raise ValueError(f"{n} must hold bf16 (2-byte) elements")
     out_ids, out_logprobs = _outputs(rows, k, h.device, out_ids, out_logprobs)
     lib = load_library()
-    shape = SlimspecShape(rows, d, r, V)
-    need = int(lib.slimspec_workspace_bytes(ctypes.byref(shape), k))
-    workspace = _workspace(need, h.device, workspace)
-    st = lib.slimspec_head_topk(_dev_ptr(h, "h"), _dev_ptr(A, "A"), _dev_ptr(B, "B"), ctypes.byref(shape), k,
+    shape = ctypes.byref(SlimspecShape(rows, d, r, V))
+    workspace = _workspace(lib.slimspec_workspace_bytes, shape, k, h.device, workspace)
+    st = lib.slimspec_head_topk(_dev_ptr(h, "h"), _dev_ptr(A, "A"), _dev_ptr(B, "B"), shape, k,
                                 _dev_ptr(out_ids, "out_ids"), _dev_ptr(out_logprobs, "out_logprobs"),
-                                _dev_ptr(workspace, "workspace"), workspace.numel() * workspace.element_size(),
+                                _dev_ptr(workspace, "workspace"), workspace.nbytes,
                                 _stream_handle(stream))
     if st != STATUS_OK:
         _raise(st)
@@ -229,13 +230,12 @@ def slimspec_head_topk_prepared(h: torch.Tensor, A: torch.Tensor, B: torch.Tenso
             raise ValueError(f"{n} must hold bf16 (2-byte) elements")
     out_ids, out_logprobs = _outputs(rows, k, h.device, out_ids, out_logprobs)
     lib = load_library()
-    shape = SlimspecShape(rows, d, r, V)
-    need = int(lib.slimspec_workspace_bytes(ctypes.byref(shape), k))
-    workspace = _workspace(need, h.device, workspace)
+    shape = ctypes.byref(SlimspecShape(rows, d, r, V))
+    workspace = _workspace(lib.slimspec_workspace_bytes, shape, k, h.device, workspace)
     st = lib.slimspec_head_topk_prepared(_dev_ptr(h, "h"), _dev_ptr(A, "A"), _dev_ptr(B, "B"), _dev_ptr(Bt, "Bt"),
-                                         ctypes.byref(shape), k,
+                                         shape, k,
                                          _dev_ptr(out_ids, "out_ids"), _dev_ptr(out_logprobs, "out_logprobs"),
-                                         _dev_ptr(workspace, "workspace"), workspace.numel() * workspace.element_size(),
+                                         _dev_ptr(workspace, "workspace"), workspace.nbytes,
                                          _stream_handle(stream))
     if st != STATUS_OK:
         _raise(st)
@@ -258,9 +258,9 @@ def slimspec_head_topk_static(h: torch.Tensor, A: torch.Tensor, B: torch.Tensor,
         if t.element_size() != 2:
             raise ValueError(f"{n} must hold bf16 (2-byte) elements")
     out_ids, out_logprobs = _outputs(rows, k, h.device, out_ids, out_logprobs)
-    shape = SlimspecShape(rows, d, r, V)
+    shape = ctypes.byref(SlimspecShape(rows, d, r, V))
     st = load_library().slimspec_head_topk_static(
-        _dev_ptr(h, "h"), _dev_ptr(A, "A"), _dev_ptr(B, "B"), ctypes.byref(shape), k,
+        _dev_ptr(h, "h"), _dev_ptr(A, "A"), _dev_ptr(B, "B"), shape, k,
         _dev_ptr(out_ids, "out_ids"), _dev_ptr(out_logprobs, "out_logprobs"), _stream_handle(stream))
     if st != STATUS_OK:
         _raise(st)
@@ -286,12 +286,11 @@ def full_head_topk(h: torch.Tensor, W: torch.Tensor, k: int,
         raise ValueError("W must be bf16 or float32")
     out_ids, out_logprobs = _outputs(rows, k, h.device, out_ids, out_logprobs)
     lib = load_library()
-    shape = SlimspecShape(rows, d, 0, V)
-    need = int(lib.slimspec_workspace_bytes(ctypes.byref(shape), k))
-    workspace = _workspace(need, h.device, workspace)
-    st = lib.full_head_topk(_dev_ptr(h, "h"), _dev_ptr(W, "W"), w_dtype, ctypes.byref(shape), k,
+    shape = ctypes.byref(SlimspecShape(rows, d, 0, V))
+    workspace = _workspace(lib.slimspec_workspace_bytes, shape, k, h.device, workspace)
+    st = lib.full_head_topk(_dev_ptr(h, "h"), _dev_ptr(W, "W"), w_dtype, shape, k,
                             _dev_ptr(out_ids, "out_ids"), _dev_ptr(out_logprobs, "out_logprobs"),
-                            _dev_ptr(workspace, "workspace"), workspace.numel() * workspace.element_size(),
+                            _dev_ptr(workspace, "workspace"), workspace.nbytes,
                             _stream_handle(stream))
     if st != STATUS_OK:
         _raise(st)
@@ -319,12 +318,11 @@ def truncated_head_topk(h: torch.Tensor, W_tr: torch.Tensor, id_map: torch.Tenso
         raise ValueError("W_tr must be bf16 or float32")
     out_ids, out_logprobs = _outputs(rows, k, h.device, out_ids, out_logprobs)
     lib = load_library()
-    shape = SlimspecShape(rows, d, 0, V)
-    need = int(lib.slimspec_workspace_bytes(ctypes.byref(shape), k))
-    workspace = _workspace(need, h.device, workspace)
+    shape = ctypes.byref(SlimspecShape(rows, d, 0, V))
+    workspace = _workspace(lib.slimspec_workspace_bytes, shape, k, h.device, workspace)
     st = lib.truncated_head_topk(_dev_ptr(h, "h"), _dev_ptr(W_tr, "W_tr"), w_dtype, _dev_ptr(id_map, "id_map"),
-                                 ctypes.byref(shape), k, _dev_ptr(out_ids, "out_ids"), _dev_ptr(out_logprobs, "out_logprobs"),
-                                 _dev_ptr(workspace, "workspace"), workspace.numel() * workspace.element_size(),
+                                 shape, k, _dev_ptr(out_ids, "out_ids"), _dev_ptr(out_logprobs, "out_logprobs"),
+                                 _dev_ptr(workspace, "workspace"), workspace.nbytes,
                                  _stream_handle(stream))
     if st != STATUS_OK:
         _raise(st)
@@ -364,12 +362,11 @@ def _positions(h, A_stack, pos_offsets, B, Bt, k, out_ids, out_logprobs, workspa
             raise ValueError(f"{n} must hold bf16 (2-byte) elements")
     out_ids, out_logprobs = _outputs(rows, k, h.device, out_ids, out_logprobs)
     lib = load_library()
-    shape = SlimspecShape(rows, d, r, V)
-    need = int(lib.slimspec_workspace_bytes(ctypes.byref(shape), k))
-    workspace = _workspace(need, h.device, workspace)
+    shape = ctypes.byref(SlimspecShape(rows, d, r, V))
+    workspace = _workspace(lib.slimspec_workspace_bytes, shape, k, h.device, workspace)
     off_arr = (ctypes.c_int32 * (n_pos + 1))(*off)
-    tail = (ctypes.byref(shape), k, _dev_ptr(out_ids, "out_ids"), _dev_ptr(out_logprobs, "out_logprobs"),
-            _dev_ptr(workspace, "workspace"), workspace.numel() * workspace.element_size(), _stream_handle(stream))
+    tail = (shape, k, _dev_ptr(out_ids, "out_ids"), _dev_ptr(out_logprobs, "out_logprobs"),
+            _dev_ptr(workspace, "workspace"), workspace.nbytes, _stream_handle(stream))
     if Bt is None:
         st = lib.slimspec_head_topk_positions(_dev_ptr(h, "h"), _dev_ptr(A_stack, "A_stack"), n_pos, off_arr, _dev_ptr(B, "B"), *tail)
     else:
@@ -406,11 +403,11 @@ def _sample(h, A, B, Bt, k, seed, workspace, stream):
     out_ids, out_logprobs = _outputs(rows, k, h.device, None, None)
     lse, sid, slp = _sample_outputs(rows, h.device)
     lib = load_library()
-    shape = SlimspecShape(rows, d, r, V)
-    workspace = _workspace(int(lib.slimspec_workspace_bytes(ctypes.byref(shape), k)), h.device, workspace)
-    tail = (ctypes.byref(shape), k, seed, _dev_ptr(out_ids, "out_ids"), _dev_ptr(out_logprobs, "out_logprobs"),
+    shape = ctypes.byref(SlimspecShape(rows, d, r, V))
+    workspace = _workspace(lib.slimspec_workspace_bytes, shape, k, h.device, workspace)
+    tail = (shape, k, seed, _dev_ptr(out_ids, "out_ids"), _dev_ptr(out_logprobs, "out_logprobs"),
             _dev_ptr(lse, "lse"), _dev_ptr(sid, "sample_ids"), _dev_ptr(slp, "sample_logprobs"),
-            _dev_ptr(workspace, "workspace"), workspace.numel() * workspace.element_size(), _stream_handle(stream))
+            _dev_ptr(workspace, "workspace"), workspace.nbytes, _stream_handle(stream))
     if Bt is None:
         st = lib.slimspec_head_sample(_dev_ptr(h, "h"), _dev_ptr(A, "A"), _dev_ptr(B, "B"), *tail)
     else:
@@ -433,12 +430,12 @@ def full_head_sample(h: torch.Tensor, W: torch.Tensor, k: int, seed: int,
     out_ids, out_logprobs = _outputs(rows, k, h.device, None, None)
     lse, sid, slp = _sample_outputs(rows, h.device)
     lib = load_library()
-    shape = SlimspecShape(rows, d, 0, V)
-    workspace = _workspace(int(lib.slimspec_workspace_bytes(ctypes.byref(shape), k)), h.device, workspace)
-    st = lib.full_head_sample(_dev_ptr(h, "h"), _dev_ptr(W, "W"), w_dtype, ctypes.byref(shape), k, seed,
+    shape = ctypes.byref(SlimspecShape(rows, d, 0, V))
+    workspace = _workspace(lib.slimspec_workspace_bytes, shape, k, h.device, workspace)
+    st = lib.full_head_sample(_dev_ptr(h, "h"), _dev_ptr(W, "W"), w_dtype, shape, k, seed,
                               _dev_ptr(out_ids, "out_ids"), _dev_ptr(out_logprobs, "out_logprobs"),
                               _dev_ptr(lse, "lse"), _dev_ptr(sid, "sample_ids"), _dev_ptr(slp, "sample_logprobs"),
-                              _dev_ptr(workspace, "workspace"), workspace.numel() * workspace.element_size(),
+                              _dev_ptr(workspace, "workspace"), workspace.nbytes,
                               _stream_handle(stream))
     if st != STATUS_OK:
         _raise(st)
@@ -458,11 +455,11 @@ def routed_head_topk(h: torch.Tensor, A: torch.Tensor, B: torch.Tensor, W: torch
     w_dtype = SLIMSPEC_F32 if W.dtype == torch.float32 else SLIMSPEC_BF16
     out_ids, out_logprobs = _outputs(rows, k, h.device, out_ids, out_logprobs)
     lib = load_library()
-    shape = SlimspecShape(rows, d, r, V)
-    workspace = _workspace(int(lib.routed_workspace_bytes(ctypes.byref(shape), k_route)), h.device, workspace)
+    shape = ctypes.byref(SlimspecShape(rows, d, r, V))
+    workspace = _workspace(lib.routed_workspace_bytes, shape, k_route, h.device, workspace)
     st = lib.routed_head_topk(_dev_ptr(h, "h"), _dev_ptr(A, "A"), _dev_ptr(B, "B"), _dev_ptr(W, "W"), w_dtype,
-                              ctypes.byref(shape), k_route, k, _dev_ptr(out_ids, "out_ids"), _dev_ptr(out_logprobs, "out_logprobs"),
-                              _dev_ptr(workspace, "workspace"), workspace.numel() * workspace.element_size(),
+                              shape, k_route, k, _dev_ptr(out_ids, "out_ids"), _dev_ptr(out_logprobs, "out_logprobs"),
+                              _dev_ptr(workspace, "workspace"), workspace.nbytes,
                               _stream_handle(stream))
     if st != STATUS_OK:
         _raise(st)
@@ -483,12 +480,12 @@ def routed_head_topk_prepared(h: torch.Tensor, A: torch.Tensor, B: torch.Tensor,
     w_dtype = SLIMSPEC_F32 if Wt.dtype == torch.float32 else SLIMSPEC_BF16
     out_ids, out_logprobs = _outputs(rows, k, h.device, out_ids, out_logprobs)
     lib = load_library()
-    shape = SlimspecShape(rows, d, r, V)
-    workspace = _workspace(int(lib.routed_workspace_bytes(ctypes.byref(shape), k_route)), h.device, workspace)
+    shape = ctypes.byref(SlimspecShape(rows, d, r, V))
+    workspace = _workspace(lib.routed_workspace_bytes, shape, k_route, h.device, workspace)
     st = lib.routed_head_topk_prepared(_dev_ptr(h, "h"), _dev_ptr(A, "A"), _dev_ptr(B, "B"),
                                        _dev_ptr(Bt, "Bt") if Bt is not None else None, _dev_ptr(Wt, "Wt"), w_dtype,
-                                       ctypes.byref(shape), k_route, k, _dev_ptr(out_ids, "out_ids"), _dev_ptr(out_logprobs, "out_logprobs"),
-                                       _dev_ptr(workspace, "workspace"), workspace.numel() * workspace.element_size(),
+                                       shape, k_route, k, _dev_ptr(out_ids, "out_ids"), _dev_ptr(out_logprobs, "out_logprobs"),
+                                       _dev_ptr(workspace, "workspace"), workspace.nbytes,
                                        _stream_handle(stream))
     if st != STATUS_OK:
         _raise(st)
