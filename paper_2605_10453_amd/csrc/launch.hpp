@@ -84,6 +84,9 @@ hipError_t launch_down_projection_tiles(const uint16_t *h, const uint16_t *A, fl
 hipError_t launch_down_projection_pieces(const uint16_t *h, const uint16_t *A, float *part, const DownGrid &g,
                                          int rows_pad, int d, int r, void *X, hipStream_t st);
 
+// ... in one launch, for up to kRowsMaxRows rows (down_rows.hip; plan.hpp: down_rows_takes)
+hipError_t launch_down_rows(const uint16_t *h, const uint16_t *A, void *X, int rows_pad, int d, int r, const DownGrid &g, hipStream_t st);
+
 // Partials per (row, chunk of 128 G columns) for up to kRowsMaxRows rows, the weights read once (rows_head.hip).
 // X: [pieces][8 ceil(K / 64)][16 ceil(rows / 16)] 16-byte vectors; pieces 1: the bf16 input itself, 3: the pieces of t
 // smp (null: off), seed: see launch_stream_topk; row0: index in the call of the first row

@@ -291,6 +291,17 @@ inline RowsGeom make_rows_geom(int K, int V) {
     g.chunks = (groups + g.G - 1) / g.G;
     return g;
 }
+// Its down-projection in one launch (down_rows.hip) or in two (down_tile.hip).  One block per 16 columns of t reads all of h and
+// of its columns of A, 32 bytes of every row: that takes longer than the second launch once there are many rows of either, and
+// from 1 KB per row of A on they come from few of the L2's channels.  Calls at V = 32768 (one / two launches, us; rows of the largest
+// group with one matrix): d = 1024, r = 128 5 rows 14.8 / 18.2, 23 rows 19.7 / 21.2, 40 rows 24.0 / 25.0; d = 2048, r = 256 5 rows 20.8 / 21.9, 16 rows
+// 22.3 / 22.5, 23 rows 26.1 / 25.6, 12 rows in four groups 21.1 / 23.5; d = 4096, r = 512, V = 128256 5 rows 50.6 / 42.0.
+inline bool down_rows_takes(const DownGrid &g, int d, int r) {
+    int most = 0;
+    for (int q = 0; q < g.n_groups; ++q) most = g.g_row0[q + 1] - g.g_row0[q] > most ? g.g_row0[q + 1] - g.g_row0[q] : most;
+    return r <= 256 && (d <= 1024 || (d <= 2048 && most <= 16));
+}
+
 // Contractions this path takes: its row operand and partial tiles then fit beside the lists in a few tens of MB.
 inline bool rows_path_fits(HeadKind kind, int d, int r) { return kind == HeadKind::LowRank ? r <= 2048 : d <= 8192; }
 

@@ -189,8 +189,11 @@ int run_head_rows(HeadKind kind, const void *h, const void *A, const void *M, co
         hipError_t e;
         if (kind == HeadKind::LowRank) {
             if (pos.n > 0) p.down = down_grid_by_position(pos, row0, rows, p.rows_pad, d, r);
-            e = launch_down_projection_pieces(hrow, static_cast<const uint16_t *>(A), reinterpret_cast<float *>(ws + p.off_down_part),
-                                              p.down, p.rows_pad, d, r, X, s);
+            if (down_rows_takes(p.down, d, r))
+                e = launch_down_rows(hrow, static_cast<const uint16_t *>(A), X, p.rows_pad, d, r, p.down, s);
+            else
+                e = launch_down_projection_pieces(hrow, static_cast<const uint16_t *>(A), reinterpret_cast<float *>(ws + p.off_down_part),
+                                                  p.down, p.rows_pad, d, r, X, s);
         } else
             e = launch_regroup_rows(hrow, X, rows, p.rows_pad, d, s);
         if (e != hipSuccess) return fail_hip(e);

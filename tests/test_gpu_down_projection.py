@@ -1,5 +1,6 @@
-"""The many-row down-projection (csrc/down_tile.hip) where the hidden size is no multiple of its 32-element stages: the last
-stage holds 8, 16 or 24 elements, alone or after full ones, in a slice of its own or at the end of one."""
+"""The down-projections of several rows (csrc/down_tile.hip, csrc/down_rows.hip) where the hidden size is no multiple of their
+32-element stages: the last stage holds 8, 16 or 24 elements, alone or after full ones, in a slice of its own or at the end of
+one.  And ranks that are no multiples of a block's columns, rows in one, two and three tiles, groups of rows."""
 import numpy as np
 import pytest
 
@@ -14,7 +15,7 @@ LOGPROB_TOL = 2e-2   # more rows: t travels as 16 bits
 
 
 @pytest.mark.parametrize("d", [8, 24, 40, 64 + 8, 7 * 32 + 16, 1024 + 24, 4064 + 8])
-@pytest.mark.parametrize("rows,r", [(6, 8), (17, 72), (70, 40), (150, 136)])
+@pytest.mark.parametrize("rows,r", [(6, 8), (17, 72), (40, 264), (70, 40), (150, 136)])
 def test_ragged_hidden_size(gpu, oracle_mod, rows, r, d):
     torch, b = gpu
     print(f"down-projection: rows={rows} d={d} r={r}", flush=True)
@@ -29,10 +30,12 @@ def test_ragged_hidden_size(gpu, oracle_mod, rows, r, d):
     compare_with_oracle(ids.cpu().numpy(), lp.cpu().numpy(), ora.ids, ora.lse, z_at, V, **tol)
 
 
-def test_ragged_hidden_size_with_a_matrix_per_position(gpu):
-    """Every position's rows as a call of their own with that position's matrix (same kernels, other row tiles)."""
+@pytest.mark.parametrize("r,d", [(72, 104), (256, 1024), (24, 2040), (272, 264)])
+@pytest.mark.parametrize("off", [[0, 7, 7, 30, 41], [0, 0, 3], [0, 33, 48]])
+def test_ragged_hidden_size_with_a_matrix_per_position(gpu, r, d, off):
+    """Every position's rows as a call of their own with that position's matrix (other row tiles, other kernels for one row)."""
     torch, b = gpu
-    d, r, V, k, off = 104, 72, 4104, 5, [0, 7, 7, 30, 41]
+    V, k = 4104, 5
     x = synth.make_inputs(synth.small_config(off[-1], d, r, V, k), seed=3)
     A = [synth.make_inputs(synth.small_config(1, d, r, V, k), seed=10 + p).A for p in range(len(off) - 1)]
     h, B = to_dev_bf16(x.h), to_dev_bf16(x.B)
