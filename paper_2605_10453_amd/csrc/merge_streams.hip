@@ -38,6 +38,7 @@ constexpr float kNoValue = -1.0e38f;    // stream fields at or below this are em
 constexpr float kExactWinnersEps = 8.0e-3f;   // largest eps at which a computed winner's log-probability is reported as is
 static_assert(kStreamsPerBlock == 4, "a record's place in its block names (column half, half-wavefront)");
 constexpr int kCrowdCap = 8;              // streams of a row whose unlisted groups are all listed member by member (more: exhaustive pass)
+constexpr int kTauCand = 128;             // listed maxima that are ranked all pairs for tau, at most
 constexpr int kGatherRound = 32;          // columns of a column-major copy evaluated per round of loads
 constexpr float kExhaustiveEps = 0.25f;       // from this eps on the row takes the exhaustive exact pass
 // The streams' sum of exponentials is made of computed logits; the merge replaces the terms of the logits it
@@ -161,19 +162,6 @@ __device__ __forceinline__ void rank_all_pairs_wide(const uint64_t *keys, int n,
     if (c < n && part == 0) f(c, mine, rank);
 }
 
-// This lane's share (one of PH lanes) of the rank of `mine` among the 64 stream heads of its group
-template <int PH>
-__device__ __forceinline__ int head_rank_share(const uint64_t *group, int part, uint64_t mine) {
-    const uint4 *grp = reinterpret_cast<const uint4 *>(group);      // 64 keys, two per 16-byte read
-    int rank = 0;
-#pragma unroll
-    for (int q = 0; q < 32 / PH; ++q) {
-        const uint4 v = grp[part + q * PH];
-        rank += (u64_from(v.y, v.x) > mine ? 1 : 0) + (u64_from(v.w, v.z) > mine ? 1 : 0);
-    }
-    return rank;
-}
-
 }  // namespace
 
 // so.on (sampling calls): the records have rec_stride = kStreamRecSample floats and also carry every stream's best
@@ -193,13 +181,11 @@ __global__ __launch_bounds__(kMergeThreads) void merge_streams_kernel(
     constexpr int L = kStreamList, REC = kStreamRec, NT = kMergeThreads, NWAVES = kMergeThreads / 64;
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const int n = nsr * L;
-    const int ngroups = (nsr + 63) / 64;                                // groups of 64 stream heads
     uint64_t *keys = reinterpret_cast<uint64_t *>(lds_raw);            // [n]            every listed maximum
-    uint64_t *hkeys = keys + n;                                         // [ngroups * 64] the streams' largest maxima, padded with kNoKey
-    uint64_t *surv = hkeys + (size_t)ngroups * 64;                      // [max(ngroups, 3) * k]  best k of every 64 heads; then the candidates for tau
-    // (the final keys and the fallback's buffer lie over the three arrays above, which are dead by then)
+    uint64_t *surv = keys + n;                                          // [kTauCand]      the candidates for tau
+    // (the final keys and the fallback's buffer lie over the two arrays above, which are dead by then)
     uint64_t *work = keys;                                              // [kExhaustCap]  final keys / fallback buffer
-    const size_t n_front = (size_t)n + (size_t)ngroups * 64 + (size_t)(ngroups > 3 ? ngroups : 3) * k;
+    const size_t n_front = (size_t)n + kTauCand;
     int *w_id = reinterpret_cast<int *>(keys + (n_front > (size_t)kExhaustCap ? n_front : (size_t)kExhaustCap));   // [kWorkCap]
     float *w_val = reinterpret_cast<float *>(w_id + kWorkCap);          // [kWorkCap]
     int *w_need = reinterpret_cast<int *>(w_val + kWorkCap);            // [kWorkCap]     0 no, 1 / 2 yes; later: list of items to evaluate
@@ -211,8 +197,8 @@ __global__ __launch_bounds__(kMergeThreads) void merge_streams_kernel(
     float *xrow16 = xrow + K;                                           // [K]            ... as the head kernel had it (operand16 != 0)
     __shared__ float red_m[NWAVES], red_s[NWAVES];
     __shared__ uint64_t tau_key;
-    __shared__ uint32_t cnt_surv, cnt_work, cnt_hidden, cnt_need;
-    __shared__ int tau_slot, eps_violated;
+    __shared__ uint32_t cnt_work, cnt_hidden, cnt_need;
+    __shared__ int tau_slot, eps_violated, redo_sh;
     __shared__ uint32_t cnt_crowd;                                      // streams whose best unlisted group is a candidate
     __shared__ int crowd[kCrowdCap];
     __shared__ float mass_eval_sh;
@@ -261,6 +247,32 @@ __global__ __launch_bounds__(kMergeThreads) void merge_streams_kernel(
     // The tail of the row's merge once every collected logit has its final value: rank the collected set, correct
     // the sum of exp by the changes of the re-evaluated terms (summed in rank order: a fixed order), write.
     const auto finish = [&](int n_work, float S, float Mx, float lse) {
+        if (n_work <= 64) {                                  // as a rule: by one wavefront, without barriers
+            if (wave != 0) return;
+            const uint64_t mine = lane < n_work ? make_key(w_val[lane], (uint32_t)w_id[lane]) : kNoKey;
+            work[lane] = mine;
+            lds_wave_sync();
+            int rank = 0;
+#pragma unroll 4
+            for (int q = 0; q < n_work; ++q) rank += work[q] > mine ? 1 : 0;
+            float *by_rank = reinterpret_cast<float *>(w_need);
+            if (lane < n_work) {
+                by_rank[rank] = w_apx[lane];
+                if (rank < k) winners[rank] = (uint32_t)lane;
+            }
+            lds_wave_sync();
+            float corr = 0.f;
+            for (int q = 0; q < n_work; ++q) corr += by_rank[q];
+            const float s_fixed = S + corr;
+            const float lse_fixed = (s_fixed > 0.f) ? (Mx + __builtin_amdgcn_logf(s_fixed)) * kLn2 : lse;
+            if (lane == 0) lse_out_sh = lse_fixed;
+            if (lane < k) {
+                const uint32_t c = winners[lane];
+                out_ids[(size_t)row * k + lane] = id_map ? id_map[w_id[c]] : w_id[c];
+                out_logprobs[(size_t)row * k + lane] = w_val[c] - lse_fixed;
+            }
+            return;
+        }
         for (int c = tid; c < n_work; c += NT) work[c] = make_key(w_val[c], (uint32_t)w_id[c]);
         __syncthreads();
         float *by_rank = reinterpret_cast<float *>(w_need);
@@ -397,7 +409,7 @@ __global__ __launch_bounds__(kMergeThreads) void merge_streams_kernel(
         return;
     }
     if (tid == 0) {
-        tau_key = kNoKey; cnt_surv = 0u; cnt_work = 0u; cnt_hidden = 0u; cnt_need = 0u; cnt_crowd = 0u; tau_slot = -1; eps_violated = 0;
+        tau_key = kNoKey; cnt_work = 0u; cnt_hidden = 0u; cnt_need = 0u; cnt_crowd = 0u; tau_slot = -1; eps_violated = 0;
         if (park) park[0] = 0;                              // not parked, unless decided otherwise below
     }
 
@@ -487,7 +499,6 @@ __global__ __launch_bounds__(kMergeThreads) void merge_streams_kernel(
             keys[sidx * L + l] = (x > kNoValue) ? make_key(mask4(x) * unit, (uint32_t)(sidx * L + l)) : kNoKey;
         }
     }
-    for (int sidx = tid; sidx < ngroups * 64; sidx += NT) hkeys[sidx] = (sidx < nsr) ? keys[sidx * L] : kNoKey;   // own writes
     __syncthreads();
     float Mx = red_m[0], X2 = 0.f, X1 = 0.f;
 #pragma unroll
@@ -524,39 +535,55 @@ __global__ __launch_bounds__(kMergeThreads) void merge_streams_kernel(
         }
         return;
     }
-    // ---- tau: the k-th largest listed maximum.  The lists are sorted, so first T = the k-th largest of the
-    // streams' heads (best k of every 64 heads, then all pairs); every listed maximum >= T (at most 3 k of them,
-    // all of them if there are fewer than k heads) is a candidate, and tau is the k-th largest candidate.
-    // (with few streams, PH = 2 or 4 lanes share the 64 comparisons of one head)
-    const int ph = (4 * ngroups * 64 <= NT) ? 2 : (2 * ngroups * 64 <= NT) ? 1 : 0, PH = 1 << ph;
-    for (int e0 = 0; e0 < ngroups * 64; e0 += NT >> ph) {
-        const int e = e0 + (tid >> ph), part = tid & (PH - 1);
-        const uint64_t mine = (e < ngroups * 64) ? hkeys[e] : kNoKey;
-        int rank = 0;
-        if (mine != kNoKey) {
-            const uint64_t *group = hkeys + (e & ~63);
-            rank = (ph == 2) ? head_rank_share<4>(group, part, mine)
-                 : (ph == 1) ? head_rank_share<2>(group, part, mine) : head_rank_share<1>(group, part, mine);
+    // ---- tau: the k-th largest listed maximum, found by one wavefront (a chain: with all of them each link was a barrier).
+    // T = the k-th largest of its 64 lanes' largest listed maxima: k of them reach it, so tau does.  Those that reach T are few (k, and
+    // what else their lanes hold) but for equal ones, and are ranked among themselves.  (Ranking 256 to 512 heads all pairs, then the best k of every 64 of them, then their lists: 4.0 us of the kernel.)
+    if (wave == 0) {
+        constexpr int KPL = 24;                                  // keys per lane read together (512 records of 3)
+        uint32_t lane_bits = 0u, hi[KPL];
+        const auto load_bits = [&](int e0) {
+#pragma unroll
+            for (int i = 0; i < KPL; ++i) hi[i] = e0 + 64 * i < n ? (uint32_t)(keys[min(e0 + 64 * i + lane, n - 1)] >> 32) : 0u;
+        };
+        for (int e0 = 0; e0 < n; e0 += 64 * KPL) {
+            load_bits(e0);
+#pragma unroll
+            for (int i = 0; i < KPL; ++i) lane_bits = max(lane_bits, hi[i]);
         }
-        rank = lanes_sum(rank, PH);
-        if (mine != kNoKey && part == 0 && rank < k) surv[atomicAdd(&cnt_surv, 1u)] = mine;
+        const uint32_t T = max(1u, (uint32_t)__builtin_amdgcn_readlane((int)wave_sort_desc(lane_bits, lane), k - 1));
+        int n_cand = 0;
+        for (int e0 = 0; e0 < n; e0 += 64 * KPL) {
+            if (n > 64 * KPL) load_bits(e0);
+#pragma unroll
+            for (int i = 0; i < KPL; ++i) {
+                if (e0 + 64 * i >= n) break;
+                const bool take = hi[i] >= T && e0 + 64 * i + lane < n;
+                const uint64_t mask = __ballot(take);
+                if (mask == 0ull) continue;
+                const int slot = n_cand + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+                if (take && slot < kTauCand) surv[slot] = keys[e0 + 64 * i + lane];
+                n_cand += __popcll(mask);
+            }
+        }
+        lds_wave_sync();
+        if (n_cand <= kTauCand) {
+            for (int c0 = 0; c0 < n_cand; c0 += 64) {
+                const uint64_t mine = c0 + lane < n_cand ? surv[c0 + lane] : kNoKey;
+                int rank = 0;
+#pragma unroll 4
+                for (int q = 0; q < n_cand; ++q) rank += surv[q] > mine ? 1 : 0;
+                if (c0 + lane < n_cand && rank == k - 1) tau_key = mine;
+            }
+        } else {                                                 // that many equal maxima: the largest key, k times
+            uint64_t last = ~0ull;
+            for (int rank = 0; rank < k; ++rank) {
+                uint64_t best = kNoKey;
+                for (int e = lane; e < n; e += 64) { const uint64_t key = keys[e]; if (key < last) best = u64_max(best, key); }
+                last = wave_max_key(best);
+            }
+            if (lane == 0) tau_key = last;
+        }
     }
-    __syncthreads();
-    const int n_surv = (int)cnt_surv;
-    __shared__ uint64_t head_bound;
-    __shared__ uint32_t cnt_cand;
-    if (tid == 0) { head_bound = kNoKey; cnt_cand = 0u; }
-    __syncthreads();
-    rank_all_pairs_wide(surv, n_surv, tid, NT, [&](int, uint64_t key, int rank) { if (rank == k - 1) head_bound = key; });
-    __syncthreads();
-    const uint64_t T = head_bound;                                       // kNoKey (smallest): fewer than k heads
-    __syncthreads();                                                     // surv is reused below
-    for (int e = tid; e < n; e += NT) {
-        const uint64_t mine = keys[e];
-        if (mine != kNoKey && mine >= T) surv[atomicAdd(&cnt_cand, 1u)] = mine;
-    }
-    __syncthreads();
-    rank_all_pairs_wide(surv, (int)cnt_cand, tid, NT, [&](int, uint64_t key, int rank) { if (rank == k - 1) tau_key = key; });
     __syncthreads();
     const bool have_tau = tau_key != kNoKey;
     const float tau = have_tau ? key_value(tau_key) : kNegInf;
@@ -622,10 +649,9 @@ __global__ __launch_bounds__(kMergeThreads) void merge_streams_kernel(
     }
 
     // ---- collect
-    auto push = [&](int id, float val, int need, float e_item) {
+    auto push = [&](int id, float val, float e_item) {
         const uint32_t slot = atomicAdd(&cnt_work, 1u);
-        if (slot < (uint32_t)kWorkCap) { w_id[slot] = id; w_val[slot] = val; w_need[slot] = need; w_apx[slot] = 0.f; w_eps[slot] = e_item; }
-        if (need) atomicAdd(&cnt_hidden, 1u);
+        if (slot < (uint32_t)kWorkCap) { w_id[slot] = id; w_val[slot] = val; w_need[slot] = 0; w_apx[slot] = 0.f; w_eps[slot] = e_item; }
         return slot;
     };
     // column of member i of a group: MFMA tile (tag & 7) of vocabulary tile (tag >> 3) covers 32 adjacent columns
@@ -634,6 +660,15 @@ __global__ __launch_bounds__(kMergeThreads) void merge_streams_kernel(
         return (tag >> 3) * 256 + 32 * (tag & 7) + pos;
     };
     const bool wide = eps > kWideEps;
+    // May the tokens that keep their computed logits, `rest` of the probability, still move the log-sum-exp?
+    const auto leaves_too_much = [&](float rest) {
+        if (rest * eps > kLseGuard) return true;
+        // The part of the rounding error that lies along t itself, (t - rounded t) . t / |t|^2 =: rho, scales every
+        // logit by 1 - rho: errors of one sign, proportional to the logit, which do not average out of the sum of
+        // exponentials.  rho is known exactly; with a long contraction it is a few 1e-5, with a rank of a few dozen
+        // it reaches 1e-3 and more.  Where it could move the log-sum-exp of the tokens left over, the row is redone.
+        return stat != nullptr && rest * fabsf(tdt_sh / X2) * fabsf(Mx * kLn2) > kCommonModeTol;
+    };
     // computed logits from here on belong to tokens of probability >= kMassCut / eps
     const float v_mass = wide ? lse + __builtin_amdgcn_logf(kMassCut / eps) * kLn2 : __builtin_huge_valf();
     if (!exhaustive) {
@@ -659,13 +694,21 @@ __global__ __launch_bounds__(kMergeThreads) void merge_streams_kernel(
                 const bool cand = xv >= tau - eps - e_item;
                 const bool mass_on = e_item > kExactWinnersEps;      // (such a token is re-evaluated: see the need pass)
                 if (!cand && !(mass_on && xv >= v_mass)) continue;
-                const uint32_t slot = push(id_max, xv, 0, e_item);
+                const uint32_t slot = push(id_max, xv, e_item);
                 if (cand && keys[sidx * L + l] == tau_key) tau_slot = (int)slot;      // one writer: keys are unique
                 // the group's other members, when its second largest value is a candidate or a probable token itself
                 if (y > kNoValue && ((cand && yv >= tau - eps - e_item) || (mass_on && yv >= v_mass))) {
+                    // (15 slots at once: one atomic after the other, a single row like that held the kernel up for 3 us)
+                    int n_more = 0;
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) n_more += (i != imax && (unsigned)id_of(tag, i, half) < (unsigned)V) ? 1 : 0;
+                    uint32_t at = atomicAdd(&cnt_work, (uint32_t)n_more);
+                    atomicAdd(&cnt_hidden, (uint32_t)n_more);
                     for (int i = 0; i < 16; ++i) {
                         const int id = id_of(tag, i, half);
-                        if (i != imax && (unsigned)id < (unsigned)V) push(id, 0.f, 1, e_item);
+                        if (i == imax || (unsigned)id >= (unsigned)V) continue;
+                        if (at < (uint32_t)kWorkCap) { w_id[at] = id; w_val[at] = 0.f; w_need[at] = 1; w_apx[at] = 0.f; w_eps[at] = e_item; }
+                        ++at;
                     }
                 }
             }
@@ -727,70 +770,98 @@ __global__ __launch_bounds__(kMergeThreads) void merge_streams_kernel(
     if (n_work > kWorkCap || n_work < k) exhaustive = true;
 
     if (!exhaustive) {
-        // ---- which listed maxima need the exact value
-        const bool any_hidden = cnt_hidden != 0u;
-        // (PN lanes share the scan of one item: the collected set is a dozen items, the block 512 threads)
-        const int pn = lanes_per_item_log2(n_work, NT), PN = 1 << pn;
-        for (int c0 = 0; c0 < n_work; c0 += NT >> pn) {
-            const int c = c0 + (tid >> pn), part = tid & (PN - 1);
-            const bool open = c < n_work && w_need[c] == 0;
-            int need = 0;
-            if (open) {
-                // a computed value may be off by its eps_v: beyond kExactWinnersEps a log-probability takes the exact value
-                const float mine = w_val[c], e_mine = w_eps[c];
-                if (any_hidden || e_mine > kExactWinnersEps) need = 1;
-                else {
-#pragma unroll 4
-                    for (int q = part; q < n_work; q += PN)
-                        need |= (q != c && fabsf(w_val[q] - mine) <= w_eps[q] + e_mine) ? 1 : 0;
-                }
-            }
-            need = lanes_sum(need, PN);
-            if (open && part == 0 && need) w_need[c] = 2;    // 2: decided in this pass (w_val still the computed value)
-        }
-        __syncthreads();
-        if (wide) {
-            // probability mass of the listed logits that get their exact value (fixed order: lanes, then the DPP tree)
+        // ---- which listed maxima need the exact value, and the list of what to evaluate.  A dozen items as a rule: one
+        // wavefront, without barriers (more than 64: further below, by the whole block).
+        if (n_work <= 64) {
             if (wave == 0) {
-                float pm = 0.f;
-                for (int c = lane; c < n_work; c += 64)
-                    if (w_need[c] == 2) pm += __builtin_amdgcn_exp2f((w_val[c] - lse) * kLog2e);
-                pm = wave_sum(pm);
-                if (lane == 0) mass_eval_sh = pm;
+                const bool item = lane < n_work;
+                const float mine = item ? w_val[lane] : 0.f, e_mine = item ? w_eps[lane] : 0.f;
+                int need = item ? w_need[lane] : 0;
+                const bool open = item && need == 0;
+                if (cnt_hidden != 0u || e_mine > kExactWinnersEps) need = open ? 2 : need;
+                int close = 0;
+                for (int q = 0; q < n_work; ++q) close |= (q != lane && fabsf(w_val[q] - mine) <= w_eps[q] + e_mine) ? 1 : 0;
+                if (open && need == 0 && close) need = 2;
+                bool redo = false;
+                if (wide) {
+                    const float pm = wave_sum(need == 2 ? __builtin_amdgcn_exp2f((mine - lse) * kLog2e) : 0.f);
+                    redo = leaves_too_much(1.f - fminf(pm, 1.f));
+                }
+                const uint64_t mask = __ballot(need != 0);
+                int n_need = __popcll(mask);
+                lds_wave_sync();
+                if (need != 0)
+                    w_need[__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u))] = lane | (need == 2 ? kListedBit : 0);
+                if (n_need == 0 && tau_slot >= 0 && tau_slot < n_work && stat != nullptr) {
+                    if (lane == 0) w_need[0] = tau_slot | kListedBit;      // (see below)
+                    n_need = 1;
+                }
+                if (lane == 0) { cnt_need = (uint32_t)n_need; redo_sh = redo ? 1 : 0; }
             }
             __syncthreads();
-            const float rest = 1.f - fminf(mass_eval_sh, 1.f);
-            if (rest * eps > kLseGuard) exhaustive = true;
-            // The part of the rounding error that lies along t itself, (t - rounded t) . t / |t|^2 =: rho, scales every
-            // logit by 1 - rho: errors of one sign, proportional to the logit, which do not average out of the sum of
-            // exponentials.  rho is known exactly; with a long contraction it is a few 1e-5, with a rank of a few dozen
-            // it reaches 1e-3 and more.  Where it could move the log-sum-exp of the tokens left over, the row is redone.
-            if (stat != nullptr && rest * fabsf(tdt_sh / X2) * fabsf(Mx * kLn2) > kCommonModeTol) exhaustive = true;
+            exhaustive = redo_sh != 0;
+        } else {
+            // ---- which listed maxima need the exact value
+            const bool any_hidden = cnt_hidden != 0u;
+            // (PN lanes share the scan of one item: the collected set is a dozen items, the block 512 threads)
+            const int pn = lanes_per_item_log2(n_work, NT), PN = 1 << pn;
+            for (int c0 = 0; c0 < n_work; c0 += NT >> pn) {
+                const int c = c0 + (tid >> pn), part = tid & (PN - 1);
+                const bool open = c < n_work && w_need[c] == 0;
+                int need = 0;
+                if (open) {
+                    // a computed value may be off by its eps_v: beyond kExactWinnersEps a log-probability takes the exact value
+                    const float mine = w_val[c], e_mine = w_eps[c];
+                    if (any_hidden || e_mine > kExactWinnersEps) need = 1;
+                    else {
+#pragma unroll 4
+                        for (int q = part; q < n_work; q += PN)
+                            need |= (q != c && fabsf(w_val[q] - mine) <= w_eps[q] + e_mine) ? 1 : 0;
+                    }
+                }
+                need = lanes_sum(need, PN);
+                if (open && part == 0 && need) w_need[c] = 2;    // 2: decided in this pass (w_val still the computed value)
+            }
+            __syncthreads();
+            if (wide) {
+                // probability mass of the listed logits that get their exact value (fixed order: lanes, then the DPP tree)
+                if (wave == 0) {
+                    float pm = 0.f;
+                    for (int c = lane; c < n_work; c += 64)
+                        if (w_need[c] == 2) pm += __builtin_amdgcn_exp2f((w_val[c] - lse) * kLog2e);
+                    pm = wave_sum(pm);
+                    if (lane == 0) mass_eval_sh = pm;
+                }
+                __syncthreads();
+                if (leaves_too_much(1.f - fminf(mass_eval_sh, 1.f))) exhaustive = true;
+            }
         }
     }
     if (!exhaustive) {
-        // list the items to evaluate (any order: every result goes back to its own slot)
-        constexpr int PER = (kWorkCap + NT - 1) / NT;       // fixed trip count: the array stays in registers
-        int my_need[PER];
+        if (n_work > 64) {
+            // list the items to evaluate (any order: every result goes back to its own slot)
+            constexpr int PER = (kWorkCap + NT - 1) / NT;       // fixed trip count: the array stays in registers
+            int my_need[PER];
 #pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            const int c = tid + i * NT;
-            my_need[i] = (c < n_work && w_need[c]) ? (c | (w_need[c] == 2 ? kListedBit : 0)) : -1;
-        }
-        __syncthreads();
+            for (int i = 0; i < PER; ++i) {
+                const int c = tid + i * NT;
+                my_need[i] = (c < n_work && w_need[c]) ? (c | (w_need[c] == 2 ? kListedBit : 0)) : -1;
+            }
+            __syncthreads();
 #pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            int n_taken;
-            const uint32_t slot = wave_slots(&cnt_need, my_need[i] >= 0, n_taken);
-            if (my_need[i] >= 0) w_need[slot] = my_need[i];
-        }
-        __syncthreads();
-        // No item to evaluate: the k-th listed maximum is evaluated all the same, so that every row checks the bound
-        // it relied on against one exact value at least (take_exact).
-        if (cnt_need == 0u && tau_slot >= 0 && tau_slot < n_work && stat != nullptr) {
+            for (int i = 0; i < PER; ++i) {
+                int n_taken;
+                const uint32_t slot = wave_slots(&cnt_need, my_need[i] >= 0, n_taken);
+                if (my_need[i] >= 0) w_need[slot] = my_need[i];
+            }
             __syncthreads();
-            if (tid == 0) { w_need[0] = tau_slot | kListedBit; cnt_need = 1u; }
-            __syncthreads();
+            // No item to evaluate: the k-th listed maximum is evaluated all the same, so that every row checks the bound
+            // it relied on against one exact value at least (take_exact).
+            if (cnt_need == 0u && tau_slot >= 0 && tau_slot < n_work && stat != nullptr) {
+                __syncthreads();
+                if (tid == 0) { w_need[0] = tau_slot | kListedBit; cnt_need = 1u; }
+                __syncthreads();
+            }
         }
         if (so.on) {                                         // the sampling contenders join the list of columns to evaluate
             const uint32_t base_n = cnt_need;
@@ -1022,10 +1093,9 @@ __global__ __launch_bounds__(256) void exact_cols_kernel(
 
 size_t merge_defer_bytes(int rows) { return sizeof(int) * kDeferRowInts * (size_t)rows; }
 
-size_t merge_streams_lds_bytes(int nsr, int k, int n_vt) {
+size_t merge_streams_lds_bytes(int nsr, int n_vt) {
     const size_t n = (size_t)nsr * kStreamList;
-    const size_t ngroups = ((size_t)nsr + 63) / 64;
-    const size_t n_front = n + ngroups * 64 + (ngroups > 3 ? ngroups : 3) * k;
+    const size_t n_front = n + kTauCand;
     return sizeof(uint64_t) * (n_front > (size_t)kExhaustCap ? n_front : (size_t)kExhaustCap) + 20u * kWorkCap
            + sizeof(float) * (((size_t)(n_vt < kTsCap ? n_vt : kTsCap) + 3) & ~(size_t)3);
 }
@@ -1037,7 +1107,7 @@ hipError_t launch_merge_streams(const float *part, int rows, int nsr, int gw, in
                                 float unit, float tiny_w, int32_t *out_ids, float *out_logprobs, const int32_t *id_map,
                                 void *defer_buf, const SampleOut &so, int row_base, hipStream_t st)
 {
-    const size_t lds = merge_streams_lds_bytes(nsr, k, n_vt) + 2 * sizeof(float) * (size_t)K;   // + the row's contraction input, exact and as rounded
+    const size_t lds = merge_streams_lds_bytes(nsr, n_vt) + 2 * sizeof(float) * (size_t)K;   // + the row's contraction input, exact and as rounded
     static LdsLimit lds_limit;
     hipError_t e = lds_limit.raise(reinterpret_cast<const void *>(merge_streams_kernel), (int)lds);
     if (e != hipSuccess) return e;

@@ -268,7 +268,6 @@ inline MfmaPlan make_mfma_plan(HeadKind kind, int rows, int d, int r, int V) {
 // fewer stream records per row, and a row whose top-k crowd into one record pays an exact rescan of that record's
 // columns: at 512 rows a row still has 128 column blocks, with two or four records each.
 inline int mfma_max_rows_per_launch(int rows) { return rows > 512 ? 512 : rows; }
-size_t merge_streams_lds_bytes(int nsr, int k, int n_vt);
 
 // ---- few rows or long lists on the matrix cores, fp32-exact products (rows_head.hip) ----------------------------
 constexpr int kRowsMaxRows = 48;         // rows per launch: three 16-row MFMA tiles (their accumulators: 96 registers)
