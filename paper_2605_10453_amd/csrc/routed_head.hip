@@ -5,9 +5,9 @@
 //   routed_partial_kernel   block (slice of d, row): partial dot products h[row, slice] . W[slice, id] for the row's
 //                           k_route ids.  A column of W is one element per row of W, each in a cache line of its own,
 //                           so the gathers of one row are spread over many blocks and every thread keeps 16 in flight.
-//   routed_finish_kernel    one wavefront per row: fixed-order sum of the slices, log-sum-exp over the subset, rank by
+//   routed_finish_kernel    one block per row: fixed-order sum of the slices, log-sum-exp over the subset, rank by
 //                           (logit descending, id ascending), the k best.
-#include "device_utils.hpp"
+#include "gemv_parts.hpp"
 #include "launch.hpp"
 
 namespace slimspec {
@@ -15,6 +15,8 @@ namespace slimspec {
 namespace {
 constexpr int kRoutedThreads = 256;
 constexpr int kRoutedLoads = 16;      // gathers in flight per thread
+constexpr int kRoutedMaxSlices = 64;
+static_assert(kRoutedThreads == 256, "four wavefronts");
 }
 
 // route_ids [rows, k_route]; part [rows, slices, k_route]
@@ -63,6 +65,7 @@ __global__ __launch_bounds__(kRoutedThreads) void routed_rows_kernel(
     const int row = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const uint16_t *hr = h + (size_t)row * d;
     constexpr int IPW = 2;                        // ids per wavefront
+    constexpr int U = 4;                          // steps in flight (one after the other, d = 4096 was eight trips to memory: 7.0 us a launch)
     const WT *wrow[IPW];
     float acc[IPW];
 #pragma unroll
@@ -72,27 +75,29 @@ __global__ __launch_bounds__(kRoutedThreads) void routed_rows_kernel(
         wrow[q] = Wt + (size_t)((unsigned)id < (unsigned)V ? id : 0) * d;
         acc[q] = 0.f;
     }
-    for (int j = lane * 8; j < d; j += 512) {     // d is a multiple of 8
-        const uint4 hq = *reinterpret_cast<const uint4 *>(hr + j);
-        const float hv[8] = {bf16_lo(hq.x), bf16_hi(hq.x), bf16_lo(hq.y), bf16_hi(hq.y),
-                             bf16_lo(hq.z), bf16_hi(hq.z), bf16_lo(hq.w), bf16_hi(hq.w)};
-        float wv[IPW][8];
+    for (int j0 = 0; j0 < d; j0 += 512 * U) {     // d is a multiple of 8
+        uint4 hq[U];
+        decltype(load_raw8(wrow[0])) wq[U][IPW];
 #pragma unroll
-        for (int q = 0; q < IPW; ++q) {
-            if constexpr (sizeof(WT) == 2) {
-                const uint4 wq = *reinterpret_cast<const uint4 *>(wrow[q] + j);
-                wv[q][0] = bf16_lo(wq.x); wv[q][1] = bf16_hi(wq.x); wv[q][2] = bf16_lo(wq.y); wv[q][3] = bf16_hi(wq.y);
-                wv[q][4] = bf16_lo(wq.z); wv[q][5] = bf16_hi(wq.z); wv[q][6] = bf16_lo(wq.w); wv[q][7] = bf16_hi(wq.w);
-            } else {
-                const float4 a = *reinterpret_cast<const float4 *>(wrow[q] + j), b = *reinterpret_cast<const float4 *>(wrow[q] + j + 4);
-                wv[q][0] = a.x; wv[q][1] = a.y; wv[q][2] = a.z; wv[q][3] = a.w;
-                wv[q][4] = b.x; wv[q][5] = b.y; wv[q][6] = b.z; wv[q][7] = b.w;
-            }
+        for (int u = 0; u < U; ++u) {
+            if (j0 + 512 * u >= d) continue;      // (the same for the whole wavefront)
+            const int j = min(j0 + 512 * u + lane * 8, d - 8);
+            hq[u] = *reinterpret_cast<const uint4 *>(hr + j);
+#pragma unroll
+            for (int q = 0; q < IPW; ++q) wq[u][q] = load_raw8(wrow[q] + j);
         }
 #pragma unroll
-        for (int q = 0; q < IPW; ++q)
+        for (int u = 0; u < U; ++u) {
+            if (j0 + 512 * u + lane * 8 >= d) continue;
+            float hv[8], wv[8];
+            widen8(Raw8Bf16{hq[u]}, hv);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) acc[q] = fmaf(hv[e], wv[q][e], acc[q]);
+            for (int q = 0; q < IPW; ++q) {
+                widen8(wq[u][q], wv);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) acc[q] = fmaf(hv[e], wv[e], acc[q]);
+            }
+        }
     }
 #pragma unroll
     for (int q = 0; q < IPW; ++q) {
@@ -102,19 +107,31 @@ __global__ __launch_bounds__(kRoutedThreads) void routed_rows_kernel(
     }
 }
 
-__global__ __launch_bounds__(64) void routed_finish_kernel(
+// One block per row.  Wavefront w adds slices 16 w .. 16 w + 15, all of them requested together (one after the other, 48 slices were
+// 48 trips to memory: 12.8 us a launch); the first one does the rest.
+__global__ __launch_bounds__(kRoutedThreads) void routed_finish_kernel(
     const float *__restrict__ part, const int32_t *__restrict__ route_ids, int k_route, int slices, int k,
     int32_t *__restrict__ out_ids, float *__restrict__ out_logprobs)
 {
-    const int row = blockIdx.x, lane = threadIdx.x;
+    const int row = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    __shared__ float red[kRoutedThreads / 64][64];
     __shared__ uint64_t keys[64];
-    float y = kNegInf;
-    int id = kNoId;
-    if (lane < k_route) {
-        y = 0.f;
-        for (int s = 0; s < slices; ++s) y += part[((size_t)row * slices + s) * k_route + lane];      // fixed order
-        id = route_ids[(size_t)row * k_route + lane];
-    }
+    constexpr int PER = kRoutedMaxSlices / (kRoutedThreads / 64);
+    const int slot = min(lane, k_route - 1);
+    const int id_slot = route_ids[(size_t)row * k_route + slot];
+    if (wave * PER < slices) {
+        float v[PER], s = 0.f;
+#pragma unroll
+        for (int u = 0; u < PER; ++u) v[u] = part[((size_t)row * slices + min(wave * PER + u, slices - 1)) * k_route + slot];
+#pragma unroll
+        for (int u = 0; u < PER; ++u) s += wave * PER + u < slices ? v[u] : 0.f;      // fixed order
+        red[wave][lane] = s;
+    } else
+        red[wave][lane] = 0.f;
+    __syncthreads();
+    if (wave != 0) return;
+    const float y = lane < k_route ? ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane] : kNegInf;
+    const int id = lane < k_route ? id_slot : kNoId;
     const float m = wave_max(y);
     const float sum = wave_sum(lane < k_route ? fast_exp(y - m) : 0.f);
     const float lse = m + fast_log(sum);
@@ -123,7 +140,7 @@ __global__ __launch_bounds__(64) void routed_finish_kernel(
     lds_wave_sync();
     int rank = 0;
 #pragma unroll 8
-    for (int q = 0; q < 64; ++q) rank += (keys[q] > mine) ? 1 : 0;
+    for (int q = 0; q < k_route; ++q) rank += (keys[q] > mine) ? 1 : 0;
     if (lane < k_route && rank < k) {
         out_ids[(size_t)row * k + rank] = id;
         out_logprobs[(size_t)row * k + rank] = y - lse;
@@ -132,7 +149,7 @@ __global__ __launch_bounds__(64) void routed_finish_kernel(
 
 int routed_slices(int d) {
     int s = d / 64;                      // at least 64 rows of W per slice: 16 gathers per thread and phase
-    if (s > 64) s = 64;
+    if (s > kRoutedMaxSlices) s = kRoutedMaxSlices;
     if (s < 1) s = 1;
     return s;
 }
@@ -149,7 +166,7 @@ hipError_t launch_routed_exact(const uint16_t *h, const void *W, bool w_is_f32, 
         routed_partial_kernel<uint16_t><<<grid, kRoutedThreads, 0, st>>>(h, static_cast<const uint16_t *>(W), route_ids, part, d, V, k_route, slices, per_slice);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    routed_finish_kernel<<<rows, 64, 0, st>>>(part, route_ids, k_route, slices, k, out_ids, out_logprobs);
+    routed_finish_kernel<<<rows, kRoutedThreads, 0, st>>>(part, route_ids, k_route, slices, k, out_ids, out_logprobs);
     return hipGetLastError();
 }
 
@@ -163,7 +180,7 @@ hipError_t launch_routed_exact_token_major(const uint16_t *h, const void *Wt, bo
         routed_rows_kernel<uint16_t><<<grid, kRoutedThreads, 0, st>>>(h, static_cast<const uint16_t *>(Wt), route_ids, y, d, V, k_route);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    routed_finish_kernel<<<rows, 64, 0, st>>>(y, route_ids, k_route, 1, k, out_ids, out_logprobs);
+    routed_finish_kernel<<<rows, kRoutedThreads, 0, st>>>(y, route_ids, k_route, 1, k, out_ids, out_logprobs);
     return hipGetLastError();
 }
 
