@@ -338,17 +338,19 @@ inline RowsPlan make_rows_plan(HeadKind kind, int rows, int d, int r, int V, int
 
 // ---- which kernels a call runs ------------------------------------------------------------------------------------
 constexpr int kMfmaMaxK = 16;            // the lane streams keep 3 groups: enough for k <= 16 (larger k: rows_head.hip)
-constexpr int kMfmaMinRows = 5;          // below, rows whose calls rows_path_takes leaves are streamed in lock step
 constexpr int64_t kRowsMinWeights = 12 << 20;
+constexpr int kMfmaMinRows = 5;          // below, rows whose calls rows_path_takes leaves are streamed in lock step
 
 // Few rows, or lists longer than the lane streams keep (rows_head.hip); the rest is tile_path_takes's or streamed.
 // Where the lines lie (us per call at d = 4096, r = 512, V = 128256 unless said otherwise; the other path's time first,
 // this one's second):
 //   * k > kMfmaMaxK: always; the lane-owns-columns kernel reads the weights once per 8 rows (40 rows, k = 32: 420 / 61).
-//   * 3 and 4 rows, low-rank: the streaming kernel needs no kernel that finishes t.  It is ahead up to 256 chunks of 512
-//     columns (one round of its blocks) while r is small: r = 256 27.4 / 29.0, 384 34.6 / 35.2, 448 39.6 / 38.2, 512
-//     47.0 / 42.3; r = 256, V = 64000 24.9 / 25.6, r = 320 27.3 / 26.7; beyond 256 chunks (V = 151936) r = 128 29.7 / 24.8, r = 512 71 / 45.  Small
-//     weights: r = 200, V = 32000 20.6 / 22.6, r = 512, V = 32000 33.6 / 27.4.  Two rows: 39.3 / 41.9.
+//   * 3 and 4 rows, low-rank: the streaming kernel needs no kernel that finishes t.  It is level or a little behind up to 256 chunks of 512
+//     columns (one round of its blocks) while r is small: r = 256 28.6 / 28.6, 384 37.1 / 35.8, r = 256, V = 64000 25 / 25; behind where t takes one
+//     short launch (d = 512, r = 64, V = 16384 15.6 / 13.1, d = 1024, r = 128, V = 32768 16.7 / 14.6, V = 128256 21.5 / 20.2, r = 256, V = 65536 22.0 / 20.3)
+//     and beyond 256 chunks (V = 151936, r = 128 29.7 / 24.8, r = 512 71 / 45).
+//     Two rows: level or ahead up to 256 chunks (r = 512 39.1 / 41.8, r = 256 26.3 / 28.5, d = 2048, r = 256, V = 32768 17.4 / 20.3, d = 1024,
+//     r = 128 14.5 / 14.7), behind for the shortest contractions and beyond (d = 512, r = 64, V = 16384 14.0 / 13.0; r = 512, V = 151936 55.5 / 45.6).
 //   * full head, from 2 rows: 188.9 / 185.3; d = 1024, V = 8192 24.3 / 17.8.  Two rows with d = 256, V = 32000: 15.7 / 16.4.
 //   * up to 32 rows, k <= kMfmaMaxK: 23 rows 58.0 / 48.7; with prepared weights 24 rows 51.2 / 48.5, 32 rows 51.9 / 50.8.
 //   * 33 to 48 rows: a wavefront finishes up to six rows after the weights, which a short contraction does not pay for,
@@ -368,8 +370,9 @@ constexpr int64_t kRowsMinWeights = 12 << 20;
 inline bool rows_path_takes(HeadKind kind, int rows, int d, int r, int V, int k, bool prepared, bool sampling) {
     const bool low_rank = kind == HeadKind::LowRank;
     if (rows < 2 || !rows_path_fits(kind, d, r)) return false;
+    if (low_rank && rows == 2) return V > 256 * kChunkCols || d <= 512;
     if (low_rank && rows <= 4)
-        return rows > 2 && (int64_t)r * V >= kRowsMinWeights && (V > 256 * kChunkCols || r > (V > 65536 ? 384 : 256));
+        return (d < 2048 && r <= 256) || ((int64_t)r * V >= kRowsMinWeights && (V > 256 * kChunkCols || r > (V > 65536 ? 384 : 256)));
     if (k > kMfmaMaxK) return true;
     if (!low_rank && rows == 2) return d > 256;
     if (rows > kRowsMaxRows) return false;

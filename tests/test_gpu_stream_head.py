@@ -18,7 +18,7 @@ FP32_TOL = 6e-5      # fp32 sums of exact products: see test_gpu_rows_head.py
     (1, 64, 8, 8, 3), (1, 64, 8, 64, 64), (1, 72, 16, 72, 5), (1, 128, 40, 16384, 7), (1, 128, 72, 16392, 10), (1, 264, 136, 32776, 9),
     (1, 64, 264, 37208, 4), (1, 512, 320, 65544, 12), (1, 96, 104, 103472, 5), (1, 64, 24, 131072, 40), (1, 64, 48, 131080, 6),
     (1, 64, 16, 262152, 5), (1, 64, 8, 530000, 3), (1, 4096, 1032, 2056, 10), (1, 4096, 8, 4104, 33), (1, 64, 5000, 1000, 5),
-    (2, 96, 56, 20000, 11), (2, 64, 1000, 520, 6), (2, 64, 24, 131080, 9), (3, 64, 200, 9000, 17), (4, 520, 264, 40008, 64), (4, 64, 8, 8, 8),
+    (2, 520, 56, 20000, 11), (2, 1000, 1000, 520, 6), (2, 2048, 24, 131072, 9), (3, 64, 264, 9000, 17), (4, 2048, 264, 40008, 64), (4, 64, 264, 8, 8),
 ])
 def test_low_rank(gpu, oracle_mod, rows, d, r, V, k):
     torch, b = gpu
