@@ -125,6 +125,25 @@ __device__ __forceinline__ uint64_t wave_max_key(uint64_t k) {
     return u64_max(u64_from(ha, la), u64_from(hb, lb));
 }
 
+// Sum of v over every aligned group of P adjacent lanes (P a power of two, at most 64; the same in all lanes of the
+// group).  All lanes of the wavefront must be active at the call.
+__device__ __forceinline__ int lanes_sum(int v, int P) {
+    if (P > 1) v += (int)dpp_u32<0xB1>((uint32_t)v);
+    if (P > 2) v += (int)dpp_u32<0x4E>((uint32_t)v);
+    if (P > 4) v += (int)dpp_u32<0x141>((uint32_t)v);
+    if (P > 8) v += (int)dpp_u32<0x140>((uint32_t)v);
+    uint32_t a, b;
+    if (P > 16) { swap_pair<16>((uint32_t)v, a, b); v = (int)(a + b); }
+    if (P > 32) { swap_pair<32>((uint32_t)v, a, b); v = (int)(a + b); }
+    return v;
+}
+// Lanes that share the scan for one of n items when nthreads threads work on them: the largest power of two P with
+// n P <= nthreads (1 when there are more items than threads); returns log2 P.
+__device__ __forceinline__ int lanes_per_item_log2(int n, int nthreads) {
+    int p = 0;
+    while (p < 6 && (2 * n << p) <= nthreads) ++p;
+    return p;
+}
 // Bitonic sorts across lanes, descending.  An exchange pairs lane i with i ^ 1, 2, 8, 16 directly, with the mirror image in its
 // block of 4, 8, 16, 32 or 64, and with i ^ 4 as mirror in 8 after mirror in 4: two DPP min / max and a select each.
 __device__ __forceinline__ void sort_keep(uint32_t &v, uint32_t p, int lane, int upper_bit) {

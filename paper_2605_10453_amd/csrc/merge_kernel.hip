@@ -14,7 +14,7 @@
 //   (2) all threads: the lists' entries that reach T go to shared memory.  Where a row has few entries they were
 //       requested at the start, before T is known (one trip instead of two); otherwise the first eight of the lists whose
 //       heads reach T are read, and more of a list only where all eight are taken.
-//   (3) wavefront 0 selects and ranks the k first of them.
+//   (3) the k first of them are found by counting, or, where they are many, by wavefront 0.
 #include "gemv_parts.hpp"
 #include "launch.hpp"
 
@@ -36,6 +36,7 @@ struct MergeLds {
     uint64_t sel[kMergeSel];
     int list[kMergeLists];
     uint32_t n_list, n_cand, T, all_lists;
+    float lse;
     uint64_t draw;
     float draw_z;
 };
@@ -123,7 +124,8 @@ __global__ __launch_bounds__(kRowMergeThreads) void merge_kernel(
             for (int c0 = 0; c0 < chunks; c0 += 64 * H) {
                 load_heads(c0);
 #pragma unroll
-                for (int e = 0; e < H; ++e) n += __popcll(__ballot(bits_of(c0, e) >= bound));
+                for (int e = 0; e < H; ++e)
+                    if (c0 + 64 * e < chunks) n += __popcll(__ballot(bits_of(c0, e) >= bound));
             }
             return n;
         };
@@ -146,6 +148,7 @@ __global__ __launch_bounds__(kRowMergeThreads) void merge_kernel(
             load_heads(c0);
 #pragma unroll
             for (int e = 0; e < H; ++e) {
+                if (c0 + 64 * e >= chunks) break;
                 const uint32_t b = bits_of(c0, e);
                 bool take = b >= T;
                 if (ties) {
@@ -160,7 +163,7 @@ __global__ __launch_bounds__(kRowMergeThreads) void merge_kernel(
                 at += __popcll(mask);
             }
         }
-        if (lane == 0) { S.n_list = (uint32_t)min(at, kMergeLists); S.n_cand = 0u; S.T = T; S.all_lists = ties ? 0u : 1u; }
+        if (lane == 0) { S.n_list = (uint32_t)min(at, kMergeLists); S.n_cand = 0u; S.T = T; S.all_lists = ties ? 0u : 1u; S.lse = lse; }
     } else if (wave == 1 && part_smp) {
         // the Gumbel-max draw: the largest z + g over the chunks (unique keys)
         const float4 *smp = part_smp + (size_t)row * chunks;
@@ -227,17 +230,31 @@ __global__ __launch_bounds__(kRowMergeThreads) void merge_kernel(
         }
     }
     __syncthreads();
-    if (wave != 0) return;
 
     // ---- the k first of them
+    lse = S.lse;
     const auto emit = [&](uint64_t key, int rank) {
         const int id = (int)key_tiebreak(key);
         out_ids[(size_t)row * k + rank] = id_map ? id_map[id] : id;      // truncated vocabulary: column -> vocabulary id
         out_logprobs[(size_t)row * k + rank] = key_value(key) - lse;
     };
+    if (part_smp && tid == NT - 1) {
+        const int id = (int)key_tiebreak(S.draw);
+        so.lse[row] = lse;
+        so.sample_ids[row] = id_map ? id_map[id] : id;
+        so.sample_logprobs[row] = S.draw_z - lse;
+    }
     const int n = (int)S.n_cand;
-    if (n <= 2 * kCandSlack + k) wave_rank_keys(S.cand, n, k, lane, emit);
-    else {
+    if (n <= kMergeSel) {
+        // by counting, the scan for every entry shared by as many lanes as there are (k = 64: one wavefront alone took 3 us)
+        const int p = lanes_per_item_log2(n, NT), P = 1 << p, c = tid >> p, part = tid & (P - 1);
+        const uint64_t mine = c < n ? S.cand[c] : kNoKey;
+        int rank = 0;
+#pragma unroll 4
+        for (int q = part; q < n; q += P) rank += S.cand[q] > mine ? 1 : 0;
+        rank = lanes_sum(rank, P);
+        if (c < n && part == 0 && rank < k) emit(mine, rank);
+    } else if (wave == 0) {
         // as with the lists: the k-th largest lane maximum, raised where it admits many
         uint32_t lane_bits = 0u;
         for (int c = lane; c < n; c += 64) lane_bits = max(lane_bits, (uint32_t)(S.cand[c] >> 32));
@@ -275,12 +292,6 @@ __global__ __launch_bounds__(kRowMergeThreads) void merge_kernel(
                 if (lane == 0) emit(last, rank);
             }
         }
-    }
-    if (part_smp && lane == 0) {
-        const int id = (int)key_tiebreak(S.draw);
-        so.lse[row] = lse;
-        so.sample_ids[row] = id_map ? id_map[id] : id;
-        so.sample_logprobs[row] = S.draw_z - lse;
     }
 }
 

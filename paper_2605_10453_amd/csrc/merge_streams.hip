@@ -112,25 +112,6 @@ __device__ __forceinline__ void rank_all_pairs(const uint64_t *keys, int n, int 
     }
 }
 
-// Sum of v over every aligned group of P adjacent lanes (P a power of two, at most 64; the same in all lanes of the
-// group).  All lanes of the wavefront must be active at the call.
-__device__ __forceinline__ int lanes_sum(int v, int P) {
-    if (P > 1) v += (int)dpp_u32<0xB1>((uint32_t)v);
-    if (P > 2) v += (int)dpp_u32<0x4E>((uint32_t)v);
-    if (P > 4) v += (int)dpp_u32<0x141>((uint32_t)v);
-    if (P > 8) v += (int)dpp_u32<0x140>((uint32_t)v);
-    uint32_t a, b;
-    if (P > 16) { swap_pair<16>((uint32_t)v, a, b); v = (int)(a + b); }
-    if (P > 32) { swap_pair<32>((uint32_t)v, a, b); v = (int)(a + b); }
-    return v;
-}
-// Lanes that share the scan for one of n items when nthreads threads work on them: the largest power of two P with
-// n P <= nthreads (1 when there are more items than threads); returns log2 P.
-__device__ __forceinline__ int lanes_per_item_log2(int n, int nthreads) {
-    int p = 0;
-    while (p < 6 && (2 * n << p) <= nthreads) ++p;
-    return p;
-}
 // Slots of a shared list for the lanes of a wavefront that have `take` set: one atomic per wavefront instead of one per
 // lane (a thousand atomics on one shared-memory counter take tens of microseconds).  Every lane of the wavefront calls.
 __device__ __forceinline__ uint32_t wave_slots(uint32_t *counter, bool take, int &n_taken) {
