@@ -249,9 +249,15 @@ __global__ __launch_bounds__(NW * 64) void stream_topk_kernel(
         sums = red2;
         n_sums = kSumParts;
     }
-    for (int i = wave; i < rows_here; i += NW)
-        chunk_row_epilogue(sums + i * cw, n_sums, R * cw, cw, chunk_col, V, lane, k, sel + (wave % EW) * cw, (size_t)(row0 + i) * chunks + chunk,
-                           part_ms, part_val, part_id, part_smp, gumbel_key(seed_lo, seed_hi, (uint32_t)(row0 + i)));
+    for (int i = wave; i < rows_here; i += NW) {
+        const auto finish = [&](auto e_tag) {
+            chunk_row_epilogue<decltype(e_tag)::value>(sums + i * cw, n_sums, R * cw, cw, chunk_col, V, lane, k, sel + (wave % EW) * cw, (size_t)(row0 + i) * chunks + chunk,
+                                                       part_ms, part_val, part_id, part_smp, gumbel_key(seed_lo, seed_hi, (uint32_t)(row0 + i)));
+        };
+        if (cw <= 128) finish(std::integral_constant<int, 2>{});
+        else if (cw <= 256) finish(std::integral_constant<int, 4>{});
+        else finish(std::integral_constant<int, 8>{});
+    }
 }
 
 // ---------------------------------------------------------------------------

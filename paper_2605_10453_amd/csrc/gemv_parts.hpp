@@ -191,23 +191,24 @@ __device__ __forceinline__ void wave_topk(const uint32_t (&ob)[E], int n_e, Id i
 // column c), then (max, sum of exp, top-k) of the logits, written as the partial of (row, chunk).  One wavefront; all 64
 // lanes must call.  sel: cw keys of shared memory.
 //
-// Top-k: wave_topk.  Lane = columns 2 lane, 2 lane + 1 of every 128.
+// Top-k: wave_topk.  Lane = columns 2 lane, 2 lane + 1 of every 128; E: elements per lane, 2 for every 128 columns begun (known when
+// compiled, or every step branches).
 // part_smp (may be null): the chunk's best z_v + g_v with standard Gumbel noise g (Gumbel-max sampling), as
 // (z + g, id, z, -) of the winner; gk: the noise key of this row.
+template <int E>
 __device__ __forceinline__ void chunk_row_epilogue(const float *sums, int n, int stride, int cw, int chunk_col, int V, int lane, int k,
                                                    uint64_t *sel, size_t slot,
                                                    float2 *__restrict__ part_ms, float *__restrict__ part_val,
                                                    int *__restrict__ part_id,
                                                    float4 *__restrict__ part_smp, const GumbelKey &gk)
 {
-    constexpr int E = kChunkCols / 64;
     const auto act = [&](int e) { const int c = 128 * (e >> 1) + 2 * lane; return c < cw && chunk_col + c < V; };      // V and cw are even: both columns or none
     const auto id = [&](int e) { return (uint32_t)(chunk_col + 128 * (e >> 1) + 2 * lane + (e & 1)); };
     float z[E];
 #pragma unroll
     for (int e = 0; e < E; e += 2) {
         float2 s = make_float2(kNegInf, kNegInf);
-        if (64 * e < cw && act(e)) {
+        if (act(e)) {
             const float *src = sums + 64 * e + 2 * lane;
             s = make_float2(0.f, 0.f);
             int p = 0;                          // fixed order: the first rows of the contraction first
@@ -247,14 +248,14 @@ __device__ __forceinline__ void chunk_row_epilogue(const float *sums, int n, int
     float s = 0.f;
 #pragma unroll
     for (int e = 0; e < E; e += 2)
-        if (64 * e < cw) s += fast_exp(z[e] - m) + fast_exp(z[e + 1] - m);     // exp(-inf) = 0 for padding lanes
+        s += fast_exp(z[e] - m) + fast_exp(z[e + 1] - m);     // exp(-inf) = 0 for padding lanes
     s = wave_sum(s);
 
     if (lane == 0) part_ms[slot] = make_float2(m, s);
     uint32_t ob[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) ob[e] = act(e) ? float_order_bits(z[e]) : 0u;
-    wave_topk<E>(ob, 2 * ((cw + 127) / 128), id, lane, k, sel, cw, part_val + slot * k, part_id + slot * k);
+    wave_topk<E>(ob, E, id, lane, k, sel, cw, part_val + slot * k, part_id + slot * k);
 }
 
 }  // namespace slimspec
