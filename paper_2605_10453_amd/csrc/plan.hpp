@@ -38,7 +38,9 @@ inline DownPlan make_down_plan(bool low_rank, int d, int r) {
 // lanes cover k_parts rows of the weights at a time, and the block's wavefronts split the contraction (nw1 of them for a single
 // row; the launcher's choice otherwise).  The chunks are made so narrow that every CU gets one, and all of them are resident
 // together: up to 131072 columns as 256 blocks of 16 wavefronts, beyond (297 chunks of 512 at 151936 columns would be two
-// on 41 CUs) for a single row as 512 of 8 or 1024 of 4.  Multiples of 64 columns: whole cache lines wherever the rows are.
+// on 41 CUs) for a single row as 512 of 8 or 1024 of 4.  Multiples of 64 columns: whole cache lines wherever the rows are; where they are not
+// (V no multiple of 64) a single row's chunks come in units of 16, closer to one per CU (d = 2680, V = 19120, 152 / 239 chunks: 30.9 / 27.5 us a call, d = 7984,
+// V = 37208 110.9 / 106.0; several rows keep few lane groups: 8 fp32 rows, d = 440, V = 19192 18.3 / 20.2).
 // (With 512 columns whatever V, 66 to 90 CUs of 256 had a block at V = 33184 to 45856: 3.0-3.3 TB/s where 5.2-5.5 are reached now.)
 // Short contractions take smaller blocks: wavefronts without rows only lengthen the barriers.
 constexpr int kNarrowChunkRows = 64;     // more rows (fp32 weights) keep chunks of 512 columns: their lists would fill the workspace
@@ -53,8 +55,9 @@ inline ChunkGeom make_chunk_geom(int rows, int K, int V) {
         g.nw1 = full <= 512 ? 8 : 4;
     }
     if (rows <= kNarrowChunkRows) {
-        g.lanes = ((n16 + slots - 1) / slots + 7) / 8 * 8;
-        if (g.lanes > 64) g.lanes = 64;
+        const int unit = rows > 1 || V % 64 == 0 ? 8 : 2;
+        g.lanes = ((n16 + slots - 1) / slots + unit - 1) / unit * unit;
+        g.lanes = g.lanes < 8 ? 8 : g.lanes > 64 ? 64 : g.lanes;
     }
     g.k_parts = 64 / g.lanes;
     g.chunks = (n16 + g.lanes - 1) / g.lanes;
