@@ -49,6 +49,8 @@ __device__ __forceinline__ uint32_t float_order_bits(float v) {
     uint32_t u = __float_as_uint(v + 0.0f);
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
+// ... of a logit that may enter a list, where 0 means no entry: the not-a-number with all bits set, whose order bits that are, takes 1.
+__device__ __forceinline__ uint32_t list_bits(float v) { return max(1u, float_order_bits(v)); }
 __device__ __forceinline__ float float_from_order_bits(uint32_t o) {
     return __uint_as_float((o & 0x80000000u) ? (o & 0x7fffffffu) : ~o);
 }

@@ -254,7 +254,7 @@ __device__ __forceinline__ void chunk_row_epilogue(const float *sums, int n, int
     if (lane == 0) part_ms[slot] = make_float2(m, s);
     uint32_t ob[E];
 #pragma unroll
-    for (int e = 0; e < E; ++e) ob[e] = act(e) ? float_order_bits(z[e]) : 0u;
+    for (int e = 0; e < E; ++e) ob[e] = act(e) ? list_bits(z[e]) : 0u;
     wave_topk<E>(ob, E, id, lane, k, sel, cw, part_val + slot * k, part_id + slot * k);
 }
 

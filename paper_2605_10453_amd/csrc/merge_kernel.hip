@@ -91,12 +91,22 @@ __global__ __launch_bounds__(kRowMergeThreads) void merge_kernel(
     float lse = 0.f;
     if (wave == 0) {
         // this lane's chunks in increasing order, H at a time
+        // The maximum of nothing but not-a-numbers is -inf or has a sign and payload of its own, and may so exceed every entry: T
+        // would then admit none and the outputs stay unwritten.  Such a chunk's head is its list's first entry instead.
+        const auto heads_in_lists = [&](int c0) {
+#pragma unroll
+            for (int e = 0; e < H; ++e)
+                if (!(hm[e].x > kNegInf)) hm[e].x = pv[(size_t)min(c0 + 64 * e + lane, chunks - 1) * k];
+        };
         const auto load_heads = [&](int c0) {
             if (c0 == 0 && chunks <= 64 * H) return;             // still in registers
 #pragma unroll
             for (int e = 0; e < H; ++e) hm[e] = ms[min(c0 + 64 * e + lane, chunks - 1)];
+            heads_in_lists(c0);
         };
-        const auto bits_of = [&](int c0, int e) { return (c0 + 64 * e + lane < chunks) ? float_order_bits(hm[e].x) : 0u; };
+        heads_in_lists(0);
+        // (at least 1 for a list, as list_bits)
+        const auto bits_of = [&](int c0, int e) { return (c0 + 64 * e + lane < chunks) ? list_bits(hm[e].x) : 0u; };
         float m_t = kNegInf, s_t = 0.f;
         uint32_t lane_bits = 0u;
         for (int c0 = 0; c0 < chunks; c0 += 64 * H) {

@@ -326,7 +326,7 @@ __global__ __launch_bounds__(512) void rows_topk_kernel(
         if (lane == 0) part_ms[slot] = make_float2(m, s);
         uint32_t ob[E];
 #pragma unroll
-        for (int e = 0; e < E; ++e) ob[e] = act(e >> 1) ? float_order_bits(z[e]) : 0u;
+        for (int e = 0; e < E; ++e) ob[e] = act(e >> 1) ? list_bits(z[e]) : 0u;
         // the candidates' keys go where the row's logits were
         lds_wave_sync();
         wave_topk<E>(ob, 2 * G, id, lane, k, reinterpret_cast<uint64_t *>(zr), row_stride / 2, part_val + slot * k, part_id + slot * k);

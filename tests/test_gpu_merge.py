@@ -74,3 +74,40 @@ def test_draws(gpu, oracle_mod, rows, V):
     torch.cuda.synchronize()
     ora = oracle_mod.head_sample(x.h, x.A, x.B, k, 1234, return_logits=True)
     check_sample_outputs(torch, out, ora, 1234, V, ora.z, oracle_mod)
+
+
+@pytest.mark.parametrize("bits", [0x7fc00000, -0x400000, -1])
+@pytest.mark.parametrize("V,k", [(1032, 10), (8200, 10), (40008, 16), (200000, 5)])
+def test_rows_of_nothing_but_nan(gpu, V, k, bits):
+    """Weights that are no numbers, of either sign or with all bits set (fp32 memory that was never written). The logits cannot be
+    ordered, but every output is written, the ids are columns of the vocabulary, and other calls are not changed."""
+    torch, b = gpu
+    x = synth.make_inputs(synth.small_config(1, 64, 16, V, k), seed=V, with_full_head=True)
+    h, W = to_dev_bf16(x.h), to_dev_bf16(x.W).float()
+    id_map = torch.arange(V, dtype=torch.int32, device="cuda") * 3
+    bad = torch.full((64, V), bits, dtype=torch.int32, device="cuda").view(torch.float32)
+    before = b.truncated_head_topk(h, W, id_map, k)
+    out_ids = torch.full((1, k), -7, dtype=torch.int32, device="cuda")
+    out_lp = torch.zeros((1, k), device="cuda")
+    b.truncated_head_topk(h, bad, id_map, k, out_ids=out_ids, out_logprobs=out_lp)
+    after = b.truncated_head_topk(h, W, id_map, k)
+    torch.cuda.synchronize()
+    ids = out_ids.cpu().numpy()[0]
+    assert np.all((ids >= 0) & (ids < 3 * V) & (ids % 3 == 0)) and len(set(ids)) == k, ids
+    assert np.isnan(out_lp.cpu().numpy()).all()
+    assert torch.equal(before[0], after[0]) and torch.equal(before[1], after[1])
+
+
+@pytest.mark.parametrize("rows", [2, 5])
+@pytest.mark.parametrize("bits", [0x7fc0, -0x40, -1])
+def test_hidden_states_of_nothing_but_nan(gpu, rows, bits):
+    torch, b = gpu
+    V, k = 9000, 10
+    x = synth.make_inputs(synth.small_config(rows, 64, 16, V, k), seed=rows)
+    h = to_dev_bf16(x.h)
+    h[1] = torch.full((64,), bits, dtype=torch.int16, device="cuda").view(torch.bfloat16)
+    out_ids = torch.full((rows, k), -7, dtype=torch.int32, device="cuda")
+    b.slimspec_head_topk(h, to_dev_bf16(x.A), to_dev_bf16(x.B), k, out_ids=out_ids)
+    torch.cuda.synchronize()
+    ids = out_ids.cpu().numpy()[1]
+    assert np.all((ids >= 0) & (ids < V)) and len(set(ids)) == k, ids
