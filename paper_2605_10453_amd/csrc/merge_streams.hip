@@ -517,14 +517,20 @@ __global__ __launch_bounds__(kMergeThreads) void merge_streams_kernel(
         return;
     }
     // ---- tau: the k-th largest listed maximum, found by one wavefront (a chain: with all of them each link was a barrier).
-    // T = the k-th largest of its 64 lanes' largest listed maxima: k of them reach it, so tau does.  Those that reach T are few (k, and
+    // T = the k-th largest of its 64 lanes' largest listed maxima: k of them reach it, so tau does (each counts once: a lane beyond the
+    // last one holds none; with the last one in its place T could exceed tau).  Those that reach T are few (k, and
     // what else their lanes hold) but for equal ones, and are ranked among themselves.  (Ranking 256 to 512 heads all pairs, then the best k of every 64 of them, then their lists: 4.0 us of the kernel.)
     if (wave == 0) {
         constexpr int KPL = 24;                                  // keys per lane read together (512 records of 3)
         uint32_t lane_bits = 0u, hi[KPL];
         const auto load_bits = [&](int e0) {
 #pragma unroll
-            for (int i = 0; i < KPL; ++i) hi[i] = e0 + 64 * i < n ? (uint32_t)(keys[min(e0 + 64 * i + lane, n - 1)] >> 32) : 0u;
+            for (int i = 0; i < KPL; ++i) {
+                hi[i] = 0u;
+                if (e0 + 64 * i >= n) continue;                  // (the same for the whole wavefront)
+                const uint32_t bits = (uint32_t)(keys[min(e0 + 64 * i + lane, n - 1)] >> 32);
+                hi[i] = e0 + 64 * i + lane < n ? bits : 0u;
+            }
         };
         for (int e0 = 0; e0 < n; e0 += 64 * KPL) {
             load_bits(e0);
@@ -538,7 +544,7 @@ __global__ __launch_bounds__(kMergeThreads) void merge_streams_kernel(
 #pragma unroll
             for (int i = 0; i < KPL; ++i) {
                 if (e0 + 64 * i >= n) break;
-                const bool take = hi[i] >= T && e0 + 64 * i + lane < n;
+                const bool take = hi[i] >= T;                    // (T is at least 1)
                 const uint64_t mask = __ballot(take);
                 if (mask == 0ull) continue;
                 const int slot = n_cand + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));

@@ -21,8 +21,9 @@ int main()
         const bool rows_path = !fp32 && rows_path_takes(kind, rows, d, r, V, k, prepared != 0, sampling != 0);
         const char *kernel = rows_path ? "rows" : fp32 || !tile_path_takes(rows, k) ? "stream" : resident ? "resident" : "tile";
         const int gw = resident ? p.res.gw : p.gw, nsr = resident ? p.res.nsr : p.nsr;
-        std::printf("kernel=%s resident_fits=%d f16=%d rows_per_block=%d col_blocks=%d records=%d parks=%d\n", kernel, p.resident ? 1 : 0,
-                    f16 ? 1 : 0, p.rt, gw, nsr / gw, p.defer && merge_parks_rows(low_rank ? r : d, !low_rank || f16) && !prepared && !sampling ? 1 : 0);
+        std::printf("kernel=%s resident_fits=%d f16=%d rows_per_block=%d col_blocks=%d records=%d parks=%d parked_offset=%zu parked_row_bytes=%zu\n", kernel, p.resident ? 1 : 0,
+                    f16 ? 1 : 0, p.rt, gw, nsr / gw, p.defer && merge_parks_rows(low_rank ? r : d, !low_rank || f16) && !prepared && !sampling ? 1 : 0,
+                    p.off_defer, merge_defer_bytes(1));
     }
     return 0;
 }

@@ -511,6 +511,29 @@ def test_four_best_logits_in_one_lane_stream(gpu, oracle_mod, rows, r, V, record
         assert g_ids[i, :4].tolist() == cols, (i, g_ids[i], cols)
 
 
+@pytest.mark.parametrize("V", [2048, 10240])
+def test_best_logits_in_the_last_record(gpu, oracle_mod, V):
+    """The row's three largest logits, all equal, are the three groups that the last record lists, and the records' 3 * 32 or 3 * 160
+    maxima end inside a wavefront's 64 lanes.  The k-th largest of them must be found all the same: without it the row's
+    answer comes from the exact pass over the whole vocabulary, right but a hundred times slower.  Such a row is never parked,
+    and this one is: its three equal logits, at least, are evaluated exactly."""
+    torch, b = gpu
+    rows, d, k = 64, 2048, 10
+    assert_plan("full", rows, d, 8, V, k, kernel="tile", col_blocks=V // 256, records=4, parks=1)
+    x = synth.make_inputs(synth.small_config(rows, d, 8, V, k), seed=V, with_full_head=True)
+    cols = [V - 256 + 32 * j + 4 for j in (4, 5, 6)]
+    h0 = synth.bf16_bits_to_f64(x.h[0])
+    W = synth.plant_identical_columns(x.W.copy(), 12.0 * h0 / (h0 @ h0), cols)
+    workspace = torch.zeros(b.slimspec_workspace_bytes(rows, d, 8, V, k), dtype=torch.uint8, device="cuda")
+    ids, lp = b.full_head_topk(to_dev_bf16(x.h), to_dev_bf16(W), k, workspace=workspace)
+    torch.cuda.synchronize()
+    ora = oracle_mod.full_head_topk(x.h, W, k)
+    compare_with_oracle(ids.cpu().numpy(), lp.cpu().numpy(), ora.ids, ora.lse, lambda ri, ci: oracle_mod.full_logits_at(x.h, W, ri, ci), V)
+    assert ids.cpu().numpy()[0, :3].tolist() == cols
+    n_need = int(workspace[plan_of("full", rows, d, 8, V, k)["parked_offset"]:][:4].view(torch.int32)[0])      # row 0
+    assert n_need >= 3, n_need
+
+
 # ------------------------------------------------------------------ the five workloads at full size
 
 @pytest.mark.parametrize("seed", list(range(10)))
