@@ -294,11 +294,12 @@ size_t head_workspace_bytes(HeadKind kind, const slimspec_shape *shape, int32_t 
         const size_t m = mfma_workspace_bytes(kind, shape);
         if (m > need) need = m;
     }
-    // (whichever form of the call takes that path, and also where only a call of fewer rows does: a workspace serves fewer
-    // rows as well.  Of the forms the plain sampling call takes it wherever another one does.)
-    const int fewer = shape->rows < kRowsMaxRows ? shape->rows : kRowsMaxRows;
-    if (rows_path_takes(kind, fewer, shape->d, shape->r, shape->V, k, false, true)) {
-        const size_t w = rows_workspace_bytes(kind, shape, k);
+    // The most rows, of this many or fewer, with which a call takes that path: a workspace serves fewer rows as well, and the rules for two, for
+    // three and four, and for more rows do not nest.  (Of a call's forms the plain sampling call takes it wherever another one does.)
+    int fewer = shape->rows < kRowsMaxRows ? shape->rows : kRowsMaxRows;
+    while (fewer > 1 && !rows_path_takes(kind, fewer, shape->d, shape->r, shape->V, k, false, true)) --fewer;
+    if (fewer > 1) {
+        const size_t w = make_rows_plan(kind, fewer, shape->d, shape->r, shape->V, k).bytes;
         if (w > need) need = w;
     }
     return need;

@@ -1,5 +1,6 @@
 """The host-side plan of a call: pure arithmetic, checked without a GPU."""
 import ctypes
+import random
 
 import pytest
 
@@ -16,7 +17,7 @@ def test_resident_head_only_where_its_offsets_fit():
 
 
 @pytest.mark.parametrize("d,r,V,k", [(512, 64, 16384, 10), (4096, 512, 16384, 12), (4096, 512, 128256, 10), (6248, 392, 2789880, 1),
-                                     (3112, 40, 18352, 64), (1024, 520, 20000, 16), (64, 8, 8, 8)])
+                                     (3112, 40, 18352, 64), (1024, 520, 20000, 16), (64, 8, 8, 8), (512, 320, 16384, 10), (4096, 64, 151936, 10)])
 def test_a_workspace_serves_fewer_rows(d, r, V, k):
     """A caller sizes its workspace for the largest batch and runs smaller ones in it: the size never falls as rows are added."""
     lib = binding.load_library()
@@ -26,6 +27,24 @@ def test_a_workspace_serves_fewer_rows(d, r, V, k):
         sizes = [query(n) for n in range(1, 1100)]
         falls = [(n + 1, sizes[n - 1], sizes[n]) for n in range(1, len(sizes)) if sizes[n] < sizes[n - 1]]
         assert sizes[0] > 0 and not falls, (name, falls[:3])
+
+
+def test_a_workspace_serves_fewer_rows_at_random_shapes():
+    """... over shapes drawn near and across the lines of the dispatch: a few rows more or less, vocabularies about 131072 columns,
+    hidden sizes and ranks of both few-row rules, rows too long for shared memory."""
+    lib = binding.load_library()
+    rng = random.Random(5)
+    steps = [1, 2, 3, 4, 5, 6, 8, 9, 16, 31, 32, 33, 47, 48, 49, 63, 64, 65, 128, 129, 256, 257, 511, 512, 513, 700, 1024, 1025]
+    for _ in range(1500):
+        d = 8 * rng.choice([rng.randint(1, 64), rng.randint(64, 256), rng.randint(256, 1024), rng.randint(1024, 12000)])
+        r = 8 * rng.choice([rng.randint(1, 32), rng.randint(33, 64), rng.randint(65, 320)])
+        V = 8 * rng.choice([rng.randint(1, 1024), rng.randint(1024, 8192), rng.randint(8192, 16384), rng.randint(16385, 40000)])
+        k = min(V, rng.choice([1, 4, 10, 16, 17, 40, 64]))
+        for query in (lambda n: binding.slimspec_workspace_bytes(n, d, r, V, k),
+                      lambda n: int(lib.routed_workspace_bytes(ctypes.byref(binding.SlimspecShape(n, d, r, V)), k))):
+            sizes = [query(n) for n in steps]
+            falls = [(b, x, y) for b, x, y in zip(steps[1:], sizes, sizes[1:]) if y < x and y != 0]
+            assert not falls, (d, r, V, k, falls[:3])
 
 
 @pytest.mark.parametrize("r,V", [(256, 8192), (256, 32000), (512, 32000), (512, 128256), (1024, 128256)])
