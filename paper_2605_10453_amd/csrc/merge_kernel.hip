@@ -91,12 +91,13 @@ __global__ __launch_bounds__(kRowMergeThreads) void merge_kernel(
     float lse = 0.f;
     if (wave == 0) {
         // this lane's chunks in increasing order, H at a time
-        // The maximum of nothing but not-a-numbers is -inf or has a sign and payload of its own, and may so exceed every entry: T
-        // would then admit none and the outputs stay unwritten.  Such a chunk's head is its list's first entry instead.
+        // A chunk's maximum is its list's first entry, but not where the chunk holds a not-a-number: lists order those by their bits (a positive
+        // one comes before +inf), while the maximum ignores them and is -inf, or has a sign and payload of its own, where there is nothing else.  With
+        // such a head the list would not be taken, or T would admit no entry at all.  The chunk's sum is then no number either.
         const auto heads_in_lists = [&](int c0) {
 #pragma unroll
             for (int e = 0; e < H; ++e)
-                if (!(hm[e].x > kNegInf)) hm[e].x = pv[(size_t)min(c0 + 64 * e + lane, chunks - 1) * k];
+                if (!(hm[e].y < __builtin_huge_valf())) hm[e].x = pv[(size_t)min(c0 + 64 * e + lane, chunks - 1) * k];
         };
         const auto load_heads = [&](int c0) {
             if (c0 == 0 && chunks <= 64 * H) return;             // still in registers

@@ -111,3 +111,30 @@ def test_hidden_states_of_nothing_but_nan(gpu, rows, bits):
     torch.cuda.synchronize()
     ids = out_ids.cpu().numpy()[1]
     assert np.all((ids >= 0) & (ids < V)) and len(set(ids)) == k, ids
+
+
+@pytest.mark.parametrize("infinite", [False, True])
+@pytest.mark.parametrize("rows,V,k", [(1, 9000, 10), (1, 128256, 16), (1, 200000, 10), (2, 40008, 40), (7, 128256, 32)])
+def test_rows_that_mix_numbers_and_nan(gpu, rows, V, k, infinite):
+    """Logits that are no numbers come before every number, in the order of their ids, wherever the chunk boundaries lie and
+    however small the numbers beside them (with infinite: although every chunk also holds columns of +infinity)."""
+    torch, b = gpu
+    x = synth.make_inputs(synth.small_config(rows, 64, 16, V, k), seed=V + k)
+    x = replace(x, h=np.repeat(x.h[:1], rows, axis=0))
+    B = x.B.copy()
+    t0 = synth.bf16_bits_to_f64(x.h[0]) @ synth.bf16_bits_to_f64(x.A[:, 0])
+    if infinite:
+        B[1:, ::40] = 0
+        B[0, ::40] = 0x7f80 if t0 > 0 else 0xff80
+    nan_cols = sorted({V // 2 + 1, V - 3, 3 * V // 4, V - 300})[:k]
+    B[:, nan_cols] = 0x7fc0
+    ids, lp = b.slimspec_head_topk(to_dev_bf16(x.h), to_dev_bf16(x.A), to_dev_bf16(B), k)
+    torch.cuda.synchronize()
+    ids = ids.cpu().numpy()
+    assert np.isnan(lp.cpu().numpy()).all()
+    for row in ids:
+        assert row[:len(nan_cols)].tolist() == nan_cols, row
+        rest = row[len(nan_cols):]
+        assert len(set(row.tolist())) == k and np.all((rest >= 0) & (rest < V))
+        if infinite:
+            assert np.array_equal(rest, [c for c in range(0, V, 40) if c not in nan_cols][:len(rest)]), row
