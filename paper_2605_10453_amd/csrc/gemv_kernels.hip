@@ -42,9 +42,9 @@ __global__ __launch_bounds__(256) void widen_rows_kernel(
 // row i of the chunk to (max, sum of exp, top-k) and writes the partial.
 //
 // What bounds it: the weights' way from HBM, as long as every CU has a block and asks for enough of them (plan.hpp chooses
-// the chunks for that); with small weights the chain of trips before and after: the contraction input (one trip: all
-// of a thread's loads are requested together, and the first weights right behind them), the weights, the epilogue of one
-// wavefront.
+// the chunks for that); with small weights the chain of trips before and after: the contraction input (for one or two
+// rows as a rule one trip: all of a thread's loads are requested together, and the first weights right behind them), the weights, the
+// epilogue of one wavefront.
 //
 // Measured, one row (kernel; chunks of 512 columns and x as it comes, before, in brackets): full head, d = 7984, V = 37208 109 us
 // (180), d = 3208, V = 33184 41 (70); r = 1568, V = 40248 27.4 (44); r = 72, V = 103472 7.4 (10.5); d = 4096, V = 128256, where
@@ -124,7 +124,10 @@ __global__ __launch_bounds__(NW * 64) void stream_topk_kernel(
             const auto load_slices = [&](uint32_t e) {
                 if (e >= n4) return;                            // (a wavefront of none goes on to its weights)
 #pragma unroll
-                for (uint32_t u = 0; u < SL; ++u) v[u] = x[min(sg + 4u * u, last) * n4 + e];
+                for (uint32_t u = 0; u < SL; ++u) {
+                    if (4u * u > last) { v[u] = make_float4(0.f, 0.f, 0.f, 0.f); continue; }      // few slices: not the last one again and again
+                    v[u] = x[min(sg + 4u * u, last) * n4 + e];
+                }
             };
             const auto add_slices = [&](uint32_t e) {
                 float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -142,9 +145,12 @@ __global__ __launch_bounds__(NW * 64) void stream_topk_kernel(
             for (uint32_t e0 = 0; e0 + NT / 4 < n4; e0 += NT / 4, e += NT / 4) { load_slices(e); add_slices(e); }
             load_slices(e);
             __builtin_amdgcn_sched_barrier(0);
-            load_first();                                       // behind the last of them: vector memory returns in order
+            if constexpr (R <= 2) load_first();                 // behind the last of them: vector memory returns in order
             __builtin_amdgcn_sched_barrier(0);
             add_slices(e);
+            // More rows have several float4 per lane, and the weights in flight then delay the last of them more than they gain
+            // (before / behind the sum: 4 rows, d = 512, r = 264, V = 128256 26.4 / 25.4 us a call, d = 8192, r = 1024, V = 8192 30.9 / 28.8).
+            if constexpr (R > 2) load_first();
         } else {
             uint4 *xs = reinterpret_cast<uint4 *>(xs_raw);
             const int n8 = rows_here * K / 8;                   // rows beyond the last stay undefined: nobody reads their sums
