@@ -349,11 +349,14 @@ constexpr int kMfmaMinRows = 5;          // below, rows whose calls rows_path_ta
 // this one's second):
 //   * k > kMfmaMaxK: always; the lane-owns-columns kernel reads the weights once per 8 rows (40 rows, k = 32: 420 / 61).
 //   * 3 and 4 rows, low-rank: the streaming kernel needs no kernel that finishes t.  It is level or a little behind up to 256 chunks of 512
-//     columns (one round of its blocks) while r is small: r = 256 28.6 / 28.6, 384 37.1 / 35.8, r = 256, V = 64000 25 / 25; behind where t takes one
+//     columns (one round of its blocks) while r is small: r = 256 27.4 / 28.6, 384 33.8 / 35.8, r = 256, V = 64000 25 / 25; behind where t takes one
 //     short launch (d = 512, r = 64, V = 16384 15.6 / 13.1, d = 1024, r = 128, V = 32768 16.7 / 14.6, V = 128256 21.5 / 20.2, r = 256, V = 65536 22.0 / 20.3)
-//     and beyond 256 chunks (V = 151936, r = 128 29.7 / 24.8, r = 512 71 / 45).
-//     Two rows: level or ahead up to 256 chunks (r = 512 39.1 / 41.8, r = 256 26.3 / 28.5, d = 2048, r = 256, V = 32768 17.4 / 20.3, d = 1024,
-//     r = 128 14.5 / 14.7), behind for the shortest contractions and beyond (d = 512, r = 64, V = 16384 14.0 / 13.0; r = 512, V = 151936 55.5 / 45.6).
+//     and beyond 256 chunks (V = 151936: r = 256 39.4 / 29.1, r = 512 57.6 / 39.6; but of the smallest weights r = 16 18.0 / 19.3, r = 64 22.5 / 19.9).
+//   * 2 rows, low-rank: level up to 256 chunks (r = 512 39.1 / 41.8, r = 256 26.3 / 28.5, d = 2048, r = 256, V = 32768 17.4 / 20.3, d = 1024,
+//     r = 128 14.5 / 14.7).  This kernel from d = 512 down while t takes one launch (r = 16, V = 8192 13.3 / 12.5, r = 64 13.6 / 13.5, r = 256, V = 32768
+//     15.1 / 16.3, V = 128256 23.7 / 22.4), not where it takes two (r = 264, V = 32768 15.8 / 19.0, V = 128256 23.1 / 26.5, r = 512 17.3 / 20.5 and 31.4 / 34.2,
+//     r = 1024, V = 32768 25.1 / 27.4); and beyond 256 chunks (V = 151936: d = 4096, r = 16 17.7 / 19.1, r = 64 19.7 / 19.9, r = 256 34.5 / 28.9, r = 512 46.2 / 39.5;
+//     V = 200000: r = 64 19.9 / 24.4, r = 512 48.8 / 50.5).
 //   * full head, from 2 rows: 188.9 / 185.3; d = 1024, V = 8192 24.3 / 17.8.  Two rows with d = 256, V = 32000: 15.7 / 16.4.
 //   * up to 32 rows, k <= kMfmaMaxK: 23 rows 58.0 / 48.7; with prepared weights 24 rows 51.2 / 48.5, 32 rows 51.9 / 50.8.
 //   * 33 to 48 rows: a wavefront finishes up to six rows after the weights, which a short contraction does not pay for,
@@ -373,7 +376,7 @@ constexpr int kMfmaMinRows = 5;          // below, rows whose calls rows_path_ta
 inline bool rows_path_takes(HeadKind kind, int rows, int d, int r, int V, int k, bool prepared, bool sampling) {
     const bool low_rank = kind == HeadKind::LowRank;
     if (rows < 2 || !rows_path_fits(kind, d, r)) return false;
-    if (low_rank && rows == 2) return V > 256 * kChunkCols || d <= 512;
+    if (low_rank && rows == 2) return V > 256 * kChunkCols || (d <= 512 && r <= 256);
     if (low_rank && rows <= 4)
         return (d < 2048 && r <= 256) || ((int64_t)r * V >= kRowsMinWeights && (V > 256 * kChunkCols || r > (V > 65536 ? 384 : 256)));
     if (k > kMfmaMaxK) return true;
