@@ -314,8 +314,6 @@ struct StreamCall {
     float4 *smp; uint32_t seed_lo, seed_hi;
 };
 
-constexpr size_t kStreamLdsLimit = 150 * 1024;      // of the CU's 160 KB
-
 template <int R, int NW, typename WT, int SRC>
 static hipError_t launch_stream(const StreamCall<WT> &c, hipStream_t st)
 {
@@ -354,8 +352,7 @@ static hipError_t launch_stream_src(StreamCall<WT> c, float *wide, hipStream_t s
     if constexpr (sizeof(WT) == 2)                      // (the low-rank head's weights are bf16)
         if (c.nds > 0) return launch_stream_rows<WT, kSlices>(c, st);
     // the smallest block's need decides: rows too long for it are read from memory as fp32
-    const int R = c.rows_here <= 1 ? 1 : c.rows_here <= 2 ? 2 : c.rows_here <= 4 ? 4 : 8;
-    if (stream_lds_bytes(R, R == 8 ? 2 : 4, c.g, c.K, 2) <= kStreamLdsLimit) return launch_stream_rows<WT, kHalfRows>(c, st);
+    if (stream_rows_fit(c.rows_here, c.g, c.K)) return launch_stream_rows<WT, kHalfRows>(c, st);
     const hipError_t e = launch_widen_rows(static_cast<const uint16_t *>(c.x), wide, c.rows_here * c.K, st);
     if (e != hipSuccess) return e;
     c.x = wide;

@@ -78,6 +78,25 @@ inline size_t stream_lds_bytes(int R, int nw, const ChunkGeom &g, int K, int x_b
     const int n = stream_parts(nw, x_bytes ? g.k_parts : 1, K).n, cw = 8 * g.lanes;
     return 4 * (size_t)R * cw * (n + (n > kDirectParts ? kSumParts : 0)) + 8 * (size_t)(R < nw ? R : nw) * cw + (size_t)x_bytes * R * K;
 }
+constexpr size_t kStreamLdsLimit = 150 * 1024;      // of the CU's 160 KB
+// Do the bf16 rows of a launch (at most kGemvMaxRows) fit beside what its smallest block needs?
+inline bool stream_rows_fit(int rows, const ChunkGeom &g, int K) {
+    const int R = rows <= 1 ? 1 : rows <= 2 ? 2 : rows <= 4 ? 4 : 8;
+    return stream_lds_bytes(R, R == 8 ? 2 : 4, g, K, 2) <= kStreamLdsLimit;
+}
+// Full head: rows that do not fit are read from memory as fp32, and a wavefront's lanes then cover one row of the weights only.  Chunks of 64 columns
+// leave 56 lanes idle there: 256 columns instead (4 rows, d = 16384, V = 8192 524 / 344 us a call, V = 16384 470 / 358, 8 rows, fp32, d = 8192, V = 8192
+// 1380 / 1028; 128 columns from V = 16392 on are as good as these: V = 32000 364 / 361 and 1470 / 1504).
+constexpr int kWideChunkLanes = 32;
+inline ChunkGeom make_chunk_geom(HeadKind kind, int rows, int K, int V) {
+    ChunkGeom g = make_chunk_geom(rows, K, V);
+    if (kind == HeadKind::Full && rows > 1 && g.lanes < 16 && !stream_rows_fit(rows < kGemvMaxRows ? rows : kGemvMaxRows, g, K)) {
+        g.lanes = kWideChunkLanes;
+        g.k_parts = 64 / g.lanes;
+        g.chunks = ((V + 7) / 8 + g.lanes - 1) / g.lanes;
+    }
+    return g;
+}
 
 struct Plan {
     bool ok = false;
@@ -101,7 +120,7 @@ inline Plan make_plan(HeadKind kind, int rows, int d, int r, int V, int k) {
     Plan p;
     p.rows = rows; p.d = d; p.r = r; p.V = V; p.k = k;
     p.K = (kind == HeadKind::LowRank) ? r : d;
-    p.geom = make_chunk_geom(rows, p.K, V);
+    p.geom = make_chunk_geom(kind, rows, p.K, V);
     p.chunks = p.geom.chunks;
     size_t off = 0;
     p.off_x = off;          off = align_up(off + sizeof(float) * kGemvMaxRows * (size_t)p.K);

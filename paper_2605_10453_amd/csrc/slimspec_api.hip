@@ -286,8 +286,10 @@ size_t head_workspace_bytes(HeadKind kind, const slimspec_shape *shape, int32_t 
 {
     if (check_shape(kind, shape, k) != SLIMSPEC_OK) return 0;
     size_t need = make_plan(kind, shape->rows, shape->d, shape->r, shape->V, k).bytes;
-    if (shape->rows > kNarrowChunkRows) {      // (fewer rows have more chunks each: a workspace serves them as well)
-        const size_t w = make_plan(kind, kNarrowChunkRows, shape->d, shape->r, shape->V, k).bytes;
+    // (fewer rows may have more chunks each, and a workspace serves them as well: the most rows of each chunk geometry)
+    for (const int fewer : {1, 2, 4, kNarrowChunkRows}) {
+        if (fewer >= shape->rows) break;
+        const size_t w = make_plan(kind, fewer, shape->d, shape->r, shape->V, k).bytes;
         if (w > need) need = w;
     }
     if (shape->rows >= kMfmaMinRows) {

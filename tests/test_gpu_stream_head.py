@@ -34,14 +34,15 @@ def test_low_rank(gpu, oracle_mod, rows, d, r, V, k):
 
 @pytest.mark.parametrize("rows,d,V,k,fp32", [
     (1, 8, 8, 2, False), (1, 1000, 37208, 4, False), (1, 3208, 4104, 8, False), (1, 72, 131080, 64 - 4, False), (2, 104, 33000, 5, False),
-    (1, 40000, 520, 5, False),                                                 # h does not fit beside the partial sums
+    (1, 40000, 520, 5, False), (1, 80000, 72, 5, False), (1, 80000, 520, 5, False),      # h fits beside the partial sums, does not
+    (4, 16384, 200, 9, False), (3, 16384, 1032, 9, False), (6, 8192, 3080, 4, True), (9, 8192, 2056, 40, True),      # ... of several rows; the last group's fits
     (1, 104, 20000, 6, True), (2, 1000, 2056, 6, True), (5, 264, 9000, 10, True), (8, 2048, 1032, 20, True), (8, 6000, 520, 3, True),
     (19, 136, 8200, 5, True), (70, 72, 1544, 5, True),                         # groups of 8 rows; chunks of 512 columns from 65 rows on
 ])
 def test_full_head(gpu, oracle_mod, rows, d, V, k, fp32):
     torch, b = gpu
     print(f"stream kernel, full head: rows={rows} d={d} V={V} k={k} fp32={fp32}", flush=True)
-    assert_plan("full", rows, d, 8, V, k, fp32=fp32, kernel="stream")
+    assert_plan("full", rows, d, 8, V, k, fp32=fp32, kernel="stream", rows_in_lds=0 if d == 80000 or (rows > 1 and d >= 8192) else 1)
     x = synth.make_inputs(synth.small_config(rows, d, 8, V, k, peaked_every=4), seed=rows + d, with_full_head=True)
     W = synth.bf16_bits_to_f32(x.W) + np.float32(1e-4) if fp32 else x.W
     ids, lp = b.full_head_topk(to_dev_bf16(x.h), to_dev_f32(W) if fp32 else to_dev_bf16(W), k)

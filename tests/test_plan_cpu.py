@@ -75,6 +75,16 @@ def test_few_rows_take_the_kernel_that_measures_faster(kind, rows, d, r, V, k, k
     assert plan_of(kind, rows, d, r, V, k)["kernel"] == kernel
 
 
+@pytest.mark.parametrize("rows,d,V,in_lds,chunk_cols", [
+    (1, 80000, 8192, 0, 64), (2, 24000, 8192, 1, 64), (4, 12288, 8192, 1, 64), (4, 16384, 8192, 0, 256), (3, 16384, 16384, 0, 256), (4, 16384, 16392, 0, 128),
+    (8, 6144, 8192, 1, 64), (8, 8192, 8192, 0, 256), (64, 8192, 8192, 0, 256), (65, 8192, 8192, 0, 512), (8, 8192, 65536, 0, 256),
+])
+def test_rows_read_from_memory_have_no_narrow_chunks(rows, d, V, in_lds, chunk_cols):
+    """Rows of the full head that shared memory does not hold leave all lanes beyond a chunk's width idle."""
+    plan = plan_of("full", rows, d, 8, V, 10, fp32=True)
+    assert (plan["kernel"], plan["rows_in_lds"], plan["chunk_cols"]) == ("stream", in_lds, chunk_cols), plan
+
+
 def test_bench_names_the_kernel_the_library_runs():
     import os
     import sys
