@@ -326,3 +326,19 @@ def test_binding_rejects_mismatched_shapes_before_any_device_call(lib):
         b.slimspec_transpose_weights(torch.zeros(16, 800, dtype=torch.float32))
     with pytest.raises(ValueError):
         b.slimspec_transpose_weights(B, out=torch.zeros(16, 800, dtype=bf))
+
+
+def test_stream_handle_without_torchs_private_function(monkeypatch):
+    """The handle of the current stream comes from a function of torch that is not public; a build without it takes a Stream object."""
+    import importlib.util
+    import types
+    import torch
+    from paper_2605_10453_amd import binding
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    spec = importlib.util.spec_from_file_location("binding_without_private_function", binding.__file__)
+    module = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(module)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=0x1230))
+    assert module._stream_handle(None) == 0x1230
+    assert module._stream_handle(types.SimpleNamespace(cuda_stream=0x4560)) == 0x4560
