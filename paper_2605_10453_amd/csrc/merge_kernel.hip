@@ -10,6 +10,8 @@
 //   (1) wavefront 0 reads the chunk maxima (the lists' heads), up to 8 per lane in flight, and folds the log-sum-exp.
 //       T = the k-th largest of its 64 lanes' maxima: k heads reach it, so it bounds the answer from below.  (All-pairs
 //       counting of 251 heads by 1024 threads took longer than the loads: 6.6 us a launch, 13.5 with 500 chunks and a draw.)
+//       With fewer lists than k no head bounds anything: there T is the m-th largest of the lists' j-th entries, m j >= k.  (Every entry of 32 lists
+//       of 64, as T = 0 admits them, is 40 us of (3): one row, r = 16, V = 2048, k = 64 55 us a call, 14 with this T.)
 //       Wavefront 1 meanwhile finds the draw of a sampling call.
 //   (2) all threads: the lists' entries that reach T go to shared memory.  Where a row has few entries they were
 //       requested at the start, before T is known (one trip instead of two); otherwise the first eight of the lists whose
@@ -77,6 +79,11 @@ __global__ __launch_bounds__(kRowMergeThreads) void merge_kernel(
 #pragma unroll
         for (int e = 0; e < H; ++e) hm[e] = ms[min(64 * e + lane, chunks - 1)];
     }
+    // (j one more than it takes: m then leaves out the lists whose j-th entries are the smallest.  Not where (3) ranks all entries at once anyway.)
+    const bool few_lists = chunks < k && n_entries > kMergeSel;
+    const int j_th = few_lists ? min(k, (k + chunks - 1) / chunks + 1) : 1, m_th = (k + j_th - 1) / j_th;
+    float v_jth = 0.f;
+    if (wave == 0 && few_lists) v_jth = pv[(size_t)min(lane, chunks - 1) * k + j_th - 1];
     float v_ahead[kMergeAhead];
     int id_ahead[kMergeAhead];
     if (ahead) {
@@ -130,6 +137,11 @@ __global__ __launch_bounds__(kRowMergeThreads) void merge_kernel(
 
         const uint32_t sorted = wave_sort_desc(lane_bits, lane);
         uint32_t T = max(1u, (uint32_t)__builtin_amdgcn_readlane((int)sorted, k - 1));      // fewer than k lists: everything
+        if (few_lists) {                                         // (a last list without a j-th entry holds none; too few lists with one: everything)
+            const bool has = lane < chunks - 1 || (lane == chunks - 1 && j_th <= last_len);
+            const uint32_t sorted_j = wave_sort_desc(has ? list_bits(v_jth) : 0u, lane);
+            T = max(1u, (uint32_t)__builtin_amdgcn_readlane((int)sorted_j, m_th - 1));
+        }
         const auto count = [&](uint32_t bound) {
             int n = 0;
             for (int c0 = 0; c0 < chunks; c0 += 64 * H) {

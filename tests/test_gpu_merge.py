@@ -27,7 +27,7 @@ def check(gpu, oracle_mod, x, k):
 
 
 @pytest.mark.parametrize("rows", [1, 2, 7])
-@pytest.mark.parametrize("V,k", [(64, 64), (72, 33), (520, 64), (4096, 40), (12096, 39), (33000, 64), (70000, 10), (131080, 63), (300000, 5), (300000, 24)])
+@pytest.mark.parametrize("V,k", [(64, 64), (72, 33), (264, 64), (520, 64), (1000, 64), (2056, 64), (2056, 30), (4096, 40), (4096, 64), (12096, 39), (33000, 64), (70000, 10), (131080, 63), (300000, 5), (300000, 24)])
 def test_lists_of_every_number_and_length(gpu, oracle_mod, rows, V, k):
     print(f"merge: rows={rows} V={V} k={k}", flush=True)
     check(gpu, oracle_mod, synth.make_inputs(synth.small_config(rows, 64, 16, V, k, peaked_every=3), seed=V + k + rows), k)
@@ -35,7 +35,7 @@ def test_lists_of_every_number_and_length(gpu, oracle_mod, rows, V, k):
 
 @pytest.mark.parametrize("rows", [1, 6])
 @pytest.mark.parametrize("k", [1, 10, 50])
-@pytest.mark.parametrize("V", [9000, 131080])
+@pytest.mark.parametrize("V", [2056, 9000, 131080])
 def test_equal_heads_and_crowded_lists(gpu, oracle_mod, rows, k, V):
     """Periodic columns: every chunk's list is the same, the first chunks' ids win.  Then one chunk that holds all winners."""
     x = synth.make_inputs(synth.small_config(rows, 64, 16, V, k), seed=k)
