@@ -6,6 +6,7 @@ import pytest
 
 from paper_2605_10453_amd import synth
 from parity_util import compare_with_oracle, to_dev_bf16, to_dev_f32
+from plan_util import assert_plan
 
 pytestmark = pytest.mark.gpu
 
@@ -69,8 +70,8 @@ def test_truncated_head_tied_columns_break_by_column(gpu, oracle_mod):
 # ------------------------------------------------------------------ position-specific down-projections
 
 @pytest.mark.parametrize("sizes,d,r,V,k", [
-    ((1, 1, 1), 256, 32, 8200, 8),                  # streaming path, every row its own matrix
-    ((2, 0, 2), 128, 16, 5000, 5),                  # ... an empty position
+    ((1, 1, 1), 256, 32, 8200, 8),                  # every row its own matrix
+    ((2, 0, 2), 128, 16, 5000, 5),                  # an empty position
     ((4,), 128, 16, 5000, 5),                       # one position: the plain head
     ((3, 1, 0, 5), 96, 24, 2056, 7),                # matrix cores, groups smaller than a tile
     ((30, 1, 0, 25), 96, 24, 2056, 7),              # ... with stream records
@@ -103,6 +104,13 @@ def test_position_specific_down_projections(gpu, oracle_mod, sizes, d, r, V, k, 
     ora = oracle_mod.slimspec_head_topk_positions(x.h, stack, off, x.B, k, return_logits=True)
     z_at = lambda ri, ci: ora.z[ri, ci]
     compare_with_oracle(ids.cpu().numpy(), lp.cpu().numpy(), ora.ids, ora.lse, z_at, V)
+
+
+@pytest.mark.parametrize("sizes,d,r,V,k", [((1, 1), 1024, 32, 8200, 8), ((1, 1, 1), 2048, 32, 8200, 8), ((2, 0, 2), 2048, 32, 5000, 5), ((1, 3), 2056, 72, 9000, 20)])
+def test_positions_that_stream(gpu, oracle_mod, sizes, d, r, V, k):
+    """Two to four rows with different matrices on the streaming kernel: its down-projection loads every row's own weights."""
+    assert_plan("low", sum(sizes), d, r, V, k, kernel="stream")
+    test_position_specific_down_projections(gpu, oracle_mod, sizes, d, r, V, k, False)
 
 
 def test_positions_with_one_matrix_equal_the_plain_head(gpu):
@@ -162,6 +170,12 @@ def test_low_rank_head_sample(gpu, oracle_mod, rows, d, r, V, k, seed, prepared)
     ids, lp = b.slimspec_head_topk(to_dev_bf16(x.h), to_dev_bf16(x.A), to_dev_bf16(x.B), k)
     torch.cuda.synchronize()
     assert torch.equal(ids, out[0])
+
+
+@pytest.mark.parametrize("rows,d,r,V,k,seed", [(2, 1024, 32, 8200, 8, 21), (3, 2048, 32, 5000, 6, 22), (4, 2048, 64, 10248, 10, 23)])
+def test_low_rank_sample_of_several_rows_that_stream(gpu, oracle_mod, rows, d, r, V, k, seed):
+    assert_plan("low", rows, d, r, V, k, sampling=True, kernel="stream")
+    test_low_rank_head_sample(gpu, oracle_mod, rows, d, r, V, k, seed, False)
 
 
 @pytest.mark.parametrize("rows,w_f32", [(2, False), (3, True), (33, False), (65, False)])

@@ -116,7 +116,7 @@ SMALL = [
     (1, 64, 16, 140000, 10),        # one row, more than 256 chunks: narrower chunks, 8-wavefront blocks
     (1, 64, 16, 300000, 10),        # ... more than 512: 4-wavefront blocks
     (1, 64, 8, 600008, 5),          # ... more than 1024: full-width chunks in several rounds
-    (2, 64, 16, 140000, 10),        # two rows keep 512-column chunks
+    (2, 64, 16, 140000, 10),        # two rows: rows_topk_kernel
 ]
 
 

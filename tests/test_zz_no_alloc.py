@@ -11,8 +11,9 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("first,second", [((300, 256, 64, 20000, 10), (9, 128, 32, 4104, 10)),     # matrix cores, two row blocks -> one
-                                          ((3, 512, 64, 40000, 8), (1, 256, 32, 8192, 8)),          # streaming path
-                                          ((64, 256, 128, 9000, 16), (2, 64, 16, 1032, 5))])        # f16 operands -> streaming
+                                          ((3, 512, 64, 40000, 8), (1, 256, 32, 8192, 8)),          # few rows -> streaming
+                                          ((4, 2048, 64, 40000, 8), (2, 1024, 32, 8192, 8)),        # streaming, four rows -> two
+                                          ((64, 256, 128, 9000, 16), (2, 64, 16, 1032, 5))])        # f16 operands -> few rows
 def test_static_scratch_entry_matches_workspace_entry(oracle_mod, first, second):
     import torch
     from paper_2605_10453_amd import binding as b
