@@ -46,9 +46,9 @@ __global__ __launch_bounds__(256) void widen_rows_kernel(
 // rows as a rule one trip: all of a thread's loads are requested together, and the first weights right behind them), the weights, the
 // epilogue of one wavefront.
 //
-// Measured, one row (kernel; chunks of 512 columns and x as it comes, before, in brackets): full head, d = 7984, V = 37208 109 us
-// (180), d = 3208, V = 33184 41 (70); r = 1568, V = 40248 27.4 (44); r = 72, V = 103472 7.4 (10.5); d = 4096, V = 128256, where
-// the chunks are the same, 170.6 (171.3, and 4.7 in a launch that widened the row to fp32).  3 rows, r = 496, V = 19072 15.9 (22.3).
+// Measured, one row (kernel; chunks of 512 columns and x as it comes, before, in brackets): full head, d = 7984, V = 37208 96 us
+// (180), d = 3208, V = 33184 38 (70); r = 1568, V = 40248 25.2 (44); r = 72, V = 103472 7.2 (10.5); d = 4096, V = 128256, where
+// the chunks are the same, 169.9 (171.3, and 4.7 in a launch that widened the row to fp32).  3 rows, r = 496, V = 19072 15.2 (22.3).
 //
 // SRC: what x is.  kSlices: nds partial sums of the contraction input, [nds][R][K] fp32 (down_items_kernel's); four
 // adjacent lanes add a quarter of the slices each.  kHalfRows: the bf16 rows themselves, [rows_here][K] (full head).  Both

@@ -1,5 +1,5 @@
 // Device-side pieces shared by the streaming ("lane owns columns") kernels: raw weight loads and
-// the per-chunk epilogue (running max, sum of exp, top-k of one 512-column chunk).
+// the per-chunk epilogue (running max, sum of exp, top-k of one chunk of 64 to 512 columns).
 #pragma once
 #include "device_utils.hpp"
 #include "plan.hpp"

@@ -41,7 +41,7 @@ inline DownPlan make_down_plan(bool low_rank, int d, int r) {
 // on 41 CUs) for a single row as 512 of 8 or 1024 of 4.  Multiples of 64 columns: whole cache lines wherever the rows are; where they are not
 // (V no multiple of 64) a single row's chunks come in units of 16, closer to one per CU (d = 2680, V = 19120, 152 / 239 chunks: 30.9 / 27.5 us a call, d = 7984,
 // V = 37208 110.9 / 106.0; several rows keep few lane groups: 8 fp32 rows, d = 440, V = 19192 18.3 / 20.2).
-// (With 512 columns whatever V, 66 to 90 CUs of 256 had a block at V = 33184 to 45856: 3.0-3.3 TB/s where 5.2-5.5 are reached now.)
+// (With 512 columns whatever V, 66 to 90 CUs of 256 had a block at V = 33184 to 45856: 3.0-3.3 TB/s where 5.5-6.2 are reached now.)
 // Short contractions take smaller blocks: wavefronts without rows only lengthen the barriers.
 constexpr int kNarrowChunkRows = 64;     // more rows (fp32 weights) keep chunks of 512 columns: their lists would fill the workspace
 struct ChunkGeom { int lanes = 64, k_parts = 1, nw1 = 16, chunks = 0; };
@@ -366,7 +366,7 @@ constexpr int kMfmaMinRows = 5;          // below, rows whose calls rows_path_ta
 // Few rows, or lists longer than the lane streams keep (rows_head.hip); the rest is tile_path_takes's or streamed.
 // Where the lines lie (us per call at d = 4096, r = 512, V = 128256 unless said otherwise; the other path's time first,
 // this one's second):
-//   * k > kMfmaMaxK: always; the lane-owns-columns kernel reads the weights once per 8 rows (40 rows, k = 32: 420 / 61).
+//   * k > kMfmaMaxK: always; the lane-owns-columns kernel reads the weights once per 8 rows (40 rows, k = 32: 420 / 52).
 //   * 3 and 4 rows, low-rank: the streaming kernel needs no kernel that finishes t.  It is level or a little behind up to 256 chunks of 512
 //     columns (one round of its blocks) while r is small: r = 256 27.4 / 28.6, 384 33.8 / 35.8, r = 256, V = 64000 25 / 25; behind where t takes one
 //     short launch (d = 512, r = 64, V = 16384 15.6 / 13.1, d = 1024, r = 128, V = 32768 16.7 / 14.6, V = 128256 21.5 / 20.2, r = 256, V = 65536 22.0 / 20.3)
@@ -377,7 +377,8 @@ constexpr int kMfmaMinRows = 5;          // below, rows whose calls rows_path_ta
 //     r = 1024, V = 32768 25.1 / 27.4); and beyond 256 chunks (V = 151936: d = 4096, r = 16 17.7 / 19.1, r = 64 19.7 / 19.9, r = 256 34.5 / 28.9, r = 512 46.2 / 39.5;
 //     V = 200000: r = 64 19.9 / 24.4, r = 512 48.8 / 50.5).
 //   * full head, from 2 rows: 188.9 / 185.3; d = 1024, V = 8192 24.3 / 17.8.  Two rows with d = 256, V = 32000: 15.7 / 16.4.
-//   * up to 32 rows, k <= kMfmaMaxK: 23 rows 58.0 / 48.7; with prepared weights 24 rows 51.2 / 48.5, 32 rows 51.9 / 50.8.
+//   * up to 32 rows, k <= kMfmaMaxK: 23 rows 50.9 / 40.5, 32 rows 51.7 / 41.3 (the weights in the last-level cache; with prepared ones the other path takes
+//     51.2 and 51.9).
 //   * 33 to 48 rows: a wavefront finishes up to six rows after the weights, which a short contraction does not pay for,
 //     while head_tile_kernel's cost stays the same and its merge is cheap with prepared weights or few candidates.
 //       prepared: 33 rows 51.0 / 54.4, 48 rows 51.5 / 58.9 (r = 1024: 76.8 / 84.1); this kernel only where few tiles of the

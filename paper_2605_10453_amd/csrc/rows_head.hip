@@ -22,8 +22,8 @@
 // when compiled (GM): without it every step branched.
 //
 // Measured at d = 4096, r = 512, V = 128256 (kernel alone; 131 MB of weights are 22-26 us at a plain read's rate; one row per
-// wavefront and step, in brackets): 23 rows, k = 10 28.6 us (33.0), 40 rows, k = 32 37.7 (42.9), 4 rows, k = 64 30.1 (31.3); 27 rows with
-// draws, r = 456, V = 31664 17.5 (22.4).  Calls: 40 rows with k = 32 54.4 us, 23 rows 45.2.  Error of the
+// wavefront and step, in brackets): 23 rows, k = 10 27.8 us (33.0), 40 rows, k = 32 37.6 (42.9), 4 rows, k = 64 29.7 (31.3); 27 rows with
+// draws, r = 456, V = 31664 17.5 (22.4).  Calls: 40 rows with k = 32 52.4 us, 23 rows 42.6.  Error of the
 // log-probabilities against 64-bit arithmetic: 7.7e-8 relative, 1.0e-7 with one multiply-add per weight (40 rows, k = 32).
 #include "gemv_parts.hpp"
 #include "launch.hpp"
