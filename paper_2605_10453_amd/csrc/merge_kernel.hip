@@ -60,7 +60,7 @@ __device__ __forceinline__ void wave_rank_keys(const uint64_t *keys, int n, int 
 
 __global__ __launch_bounds__(kRowMergeThreads) void merge_kernel(
     const float2 *__restrict__ part_ms, const float *__restrict__ part_val, const int *__restrict__ part_id,
-    int chunks, int k, int last_len, int32_t *__restrict__ out_ids, float *__restrict__ out_logprobs,
+    int chunks, int k, int last_len, int j_th, int m_th, int32_t *__restrict__ out_ids, float *__restrict__ out_logprobs,
     const int32_t *__restrict__ id_map, SampleOut so, const float4 *__restrict__ part_smp)
 {
     __shared__ MergeLds S;
@@ -79,11 +79,8 @@ __global__ __launch_bounds__(kRowMergeThreads) void merge_kernel(
 #pragma unroll
         for (int e = 0; e < H; ++e) hm[e] = ms[min(64 * e + lane, chunks - 1)];
     }
-    // (j one more than it takes: m then leaves out the lists whose j-th entries are the smallest.  Not where (3) ranks all entries at once anyway.)
-    const bool few_lists = chunks < k && n_entries > kMergeSel;
-    const int j_th = few_lists ? min(k, (k + chunks - 1) / chunks + 1) : 1, m_th = (k + j_th - 1) / j_th;
     float v_jth = 0.f;
-    if (wave == 0 && few_lists) v_jth = pv[(size_t)min(lane, chunks - 1) * k + j_th - 1];
+    if (wave == 0 && j_th > 1) v_jth = pv[(size_t)min(lane, chunks - 1) * k + j_th - 1];
     float v_ahead[kMergeAhead];
     int id_ahead[kMergeAhead];
     if (ahead) {
@@ -102,6 +99,10 @@ __global__ __launch_bounds__(kRowMergeThreads) void merge_kernel(
         // one comes before +inf), while the maximum ignores them and is -inf, or has a sign and payload of its own, where there is nothing else.  With
         // such a head the list would not be taken, or T would admit no entry at all.  The chunk's sum is then no number either.
         const auto heads_in_lists = [&](int c0) {
+            bool any = false;
+#pragma unroll
+            for (int e = 0; e < H; ++e) any |= !(hm[e].y < __builtin_huge_valf());
+            if (__ballot(any) == 0ull) return;                   // as a rule (a branch per load: 300000 columns 0.9 us more)
 #pragma unroll
             for (int e = 0; e < H; ++e)
                 if (!(hm[e].y < __builtin_huge_valf())) hm[e].x = pv[(size_t)min(c0 + 64 * e + lane, chunks - 1) * k];
@@ -135,13 +136,10 @@ __global__ __launch_bounds__(kRowMergeThreads) void merge_kernel(
         const float s = wave_sum(m_t == kNegInf ? 0.f : s_t * fast_exp(m_t - M));
         lse = M + fast_log(s);
 
+        // (j-th entries: a lane has one list at most, the last one may not have as many; too few that have, or too few heads: everything)
+        if (j_th > 1) lane_bits = lane < chunks - 1 || (lane == chunks - 1 && j_th <= last_len) ? list_bits(v_jth) : 0u;
         const uint32_t sorted = wave_sort_desc(lane_bits, lane);
-        uint32_t T = max(1u, (uint32_t)__builtin_amdgcn_readlane((int)sorted, k - 1));      // fewer than k lists: everything
-        if (few_lists) {                                         // (a last list without a j-th entry holds none; too few lists with one: everything)
-            const bool has = lane < chunks - 1 || (lane == chunks - 1 && j_th <= last_len);
-            const uint32_t sorted_j = wave_sort_desc(has ? list_bits(v_jth) : 0u, lane);
-            T = max(1u, (uint32_t)__builtin_amdgcn_readlane((int)sorted_j, m_th - 1));
-        }
+        uint32_t T = max(1u, (uint32_t)__builtin_amdgcn_readlane((int)sorted, m_th - 1));
         const auto count = [&](uint32_t bound) {
             int n = 0;
             for (int c0 = 0; c0 < chunks; c0 += 64 * H) {
@@ -322,8 +320,12 @@ hipError_t launch_merge(const float2 *part_ms, const float *part_val, const int 
                         int rows, int chunks, int chunk_cols, int V, int k, int32_t *out_ids, float *out_logprobs, const int32_t *id_map,
                         const SampleOut &so, const float4 *part_smp, hipStream_t st)
 {
-    const int last_cols = V - (chunks - 1) * chunk_cols;
-    merge_kernel<<<rows, kRowMergeThreads, 0, st>>>(part_ms, part_val, part_id, chunks, k, last_cols < k ? last_cols : k, out_ids, out_logprobs,
+    const int last_cols = V - (chunks - 1) * chunk_cols, last_len = last_cols < k ? last_cols : k;
+    // (j one more than it takes: m then leaves out the lists whose j-th entries are the smallest.  Not where (3) ranks all entries anyway.  Worked
+    // out here: two divisions and a sort of its own in the kernel cost every call up to 0.5 us)
+    int j_th = 1;
+    if (chunks < k && (chunks - 1) * k + last_len > kMergeSel) j_th = (k + chunks - 1) / chunks + 1 < k ? (k + chunks - 1) / chunks + 1 : k;
+    merge_kernel<<<rows, kRowMergeThreads, 0, st>>>(part_ms, part_val, part_id, chunks, k, last_len, j_th, (k + j_th - 1) / j_th, out_ids, out_logprobs,
                                                     id_map, so, so.on ? part_smp : nullptr);
     return hipGetLastError();
 }
