@@ -294,6 +294,7 @@ inline int mfma_max_rows_per_launch(int rows) { return rows > 512 ? 512 : rows; 
 // ---- few rows or long lists on the matrix cores, fp32-exact products (rows_head.hip) ----------------------------
 constexpr int kRowsMaxRows = 48;         // rows per launch: three 16-row MFMA tiles (their accumulators: 96 registers)
 constexpr int kRowsMaxColGroups = 6;     // 128-column groups per block at most (their logits: 149 KB of LDS at 48 rows)
+constexpr int kRowsOneRoundCols = 256 * 128 * kRowsMaxColGroups;     // columns that 256 blocks cover, one per CU
 // Floats between two rows of logits in shared memory; a row's place is reused for its candidates' 64-bit keys.
 constexpr __host__ __device__ int rows_lds_stride(int G) { return (128 * G > 512 ? 128 * G : 512) + 8; }
 // A block covers G groups of 128 columns in KS slices of the contraction (at most 8 wavefronts).  G is the
@@ -374,8 +375,10 @@ constexpr int kMfmaMinRows = 5;          // below, rows whose calls rows_path_ta
 //   * 2 rows, low-rank: level up to 256 chunks (r = 512 39.1 / 41.8, r = 256 26.3 / 28.5, d = 2048, r = 256, V = 32768 17.4 / 20.3, d = 1024,
 //     r = 128 14.5 / 14.7).  This kernel from d = 512 down while t takes one launch (r = 16, V = 8192 13.3 / 12.5, r = 64 13.6 / 13.5, r = 256, V = 32768
 //     15.1 / 16.3, V = 128256 23.7 / 22.4), not where it takes two (r = 264, V = 32768 15.8 / 19.0, V = 128256 23.1 / 26.5, r = 512 17.3 / 20.5 and 31.4 / 34.2,
-//     r = 1024, V = 32768 25.1 / 27.4); and beyond 256 chunks (V = 151936: d = 4096, r = 16 17.7 / 19.1, r = 64 19.7 / 19.9, r = 256 34.5 / 28.9, r = 512 46.2 / 39.5;
-//     V = 200000: r = 64 19.9 / 24.4, r = 512 48.8 / 50.5).
+//     r = 1024, V = 32768 25.1 / 27.4).  Beyond 256 chunks this kernel (V = 151936: r = 512 53.1 / 42.5, r = 256 33.9 / 28.7, r = 128 25.4 / 23.8, d = 1024,
+//     r = 64 19.8 / 16.9), but not with small weights behind two launches (d = 4096, r = 16 17.1 / 18.6, r = 64 20.5 / 21.2), nor where its blocks are
+//     more than one round (V = 200000: r = 16 17.6 / 22.5, r = 64 21.3 / 26.1, r = 512 56.0 / 58.5, d = 1024, r = 64 20.8 / 21.8; V = 262144: r = 64
+//     22.4 / 28.8, r = 512 62.2 / 70.4).
 //   * full head, from 2 rows: 188.9 / 185.3; d = 1024, V = 8192 24.3 / 17.8.  Two rows with d = 256, V = 32000: 15.7 / 16.4.
 //   * up to 32 rows, k <= kMfmaMaxK: 23 rows 50.9 / 40.5, 32 rows 51.7 / 41.3 (the weights in the last-level cache; with prepared ones the other path takes
 //     51.2 and 51.9).
@@ -396,7 +399,10 @@ constexpr int kMfmaMinRows = 5;          // below, rows whose calls rows_path_ta
 inline bool rows_path_takes(HeadKind kind, int rows, int d, int r, int V, int k, bool prepared, bool sampling) {
     const bool low_rank = kind == HeadKind::LowRank;
     if (rows < 2 || !rows_path_fits(kind, d, r)) return false;
-    if (low_rank && rows == 2) return V > 256 * kChunkCols || (d <= 512 && r <= 256);
+    if (low_rank && rows == 2) {
+        if (V <= 256 * kChunkCols) return d <= 512 && r <= 256;
+        return V <= kRowsOneRoundCols && ((d < 2048 && r <= 256) || (int64_t)r * V >= kRowsMinWeights);
+    }
     if (low_rank && rows <= 4)
         return (d < 2048 && r <= 256) || ((int64_t)r * V >= kRowsMinWeights && (V > 256 * kChunkCols || r > (V > 65536 ? 384 : 256)));
     if (k > kMfmaMaxK) return true;

@@ -65,7 +65,8 @@ def test_prepared_weights_decide_between_33_and_48_rows(r, V):
     ("low", 3, 4096, 512, 128256, 10, "rows"), ("low", 4, 1024, 128, 151936, 32, "rows"),
     ("low", 4, 4096, 512, 16384, 10, "stream"), ("low", 2, 4096, 512, 128256, 40, "stream"), ("low", 48, 2048, 256, 32000, 3, "rows"),
     ("low", 2, 512, 256, 32768, 10, "rows"), ("low", 2, 512, 264, 32768, 10, "stream"), ("low", 2, 256, 512, 128256, 10, "stream"),
-    ("low", 2, 512, 1024, 8192, 64, "stream"), ("low", 2, 512, 512, 151936, 10, "rows"), ("low", 2, 4096, 64, 151936, 10, "rows"), ("low", 2, 520, 64, 16384, 10, "stream"),
+    ("low", 2, 512, 1024, 8192, 64, "stream"), ("low", 2, 512, 512, 151936, 10, "rows"), ("low", 2, 4096, 64, 151936, 10, "stream"), ("low", 2, 4096, 128, 151936, 10, "rows"), ("low", 2, 1024, 16, 151936, 10, "rows"),
+    ("low", 2, 4096, 512, 196608, 10, "rows"), ("low", 2, 4096, 512, 196616, 10, "stream"), ("low", 2, 512, 64, 200000, 10, "stream"), ("low", 2, 520, 64, 16384, 10, "stream"),
     ("full", 2, 256, 8, 32000, 10, "stream"), ("full", 2, 264, 8, 32000, 10, "rows"),
     ("full", 33, 512, 8, 64000, 1, "tile"), ("full", 48, 1024, 8, 64000, 1, "rows"), ("full", 48, 768, 8, 8192, 4, "rows"),
     ("full", 40, 512, 8, 128256, 10, "tile"), ("full", 40, 512, 8, 128256, 16, "rows"), ("full", 32, 256, 8, 8192, 1, "rows"),
