@@ -207,12 +207,11 @@ __device__ __forceinline__ uint32_t mix32(uint32_t x) {
     x ^= x >> 16; x *= 0x21F0AAADu; x ^= x >> 15; x *= 0x735A2D97u; x ^= x >> 15;
     return x;
 }
+constexpr uint32_t kGumbelIdStep = 0x9E3779B1u;
+__device__ __forceinline__ uint32_t gumbel_bits(uint32_t id_row_term, uint32_t hi_term) { return mix32(mix32(id_row_term) + hi_term); }
 // g / ln 2 (the noise in base-2 units: add it to a logit times log2 e)
 __device__ __forceinline__ float gumbel_base2(const GumbelKey &key, uint32_t id) {
-    uint32_t x = id * 0x9E3779B1u + key.row_term;
-    x = mix32(x);
-    x += key.hi_term;
-    x = mix32(x);
+    const uint32_t x = gumbel_bits(id * kGumbelIdStep + key.row_term, key.hi_term);
     const uint32_t m = 2u * (x >> 9) + 1u;                          // u = m / 2^24, m odd, < 2^24
     const float u = (float)m * 5.9604644775390625e-8f;              // exact
     const float series = u * (1.f + u * (0.5f + u * (0.33333334f + u * (0.25f + u * 0.2f))));
@@ -220,6 +219,12 @@ __device__ __forceinline__ float gumbel_base2(const GumbelKey &key, uint32_t id)
     const float E = (m < (1u << 18)) ? series : direct;
     return -__builtin_amdgcn_logf(E);
 }
+// An upper bound of it for four instructions behind the hash instead of twenty: kGumbelBoundBase - kGumbelBoundScale * gumbel_bound_bits().
+// With n' = x >> 9 << 9 as a float, n' / 2^32 < u < E, and a float's bits are its base-2 logarithm with the mantissa as a straight
+// line, which lies below it.  For a small u, i.e. noise that can decide a draw, the bound is at most 0.086 + 0.7 / (n + 1) too large.
+constexpr float kGumbelBoundBase = 159.f;               // 32 for the scale of x, 127 for the exponent's bias
+constexpr float kGumbelBoundScale = 1.1920928955078125e-7f;      // 2^-23
+__device__ __forceinline__ float gumbel_bound_bits(uint32_t x) { return (float)(int)__float_as_uint((float)(x & 0xfffffe00u)); }
 
 // Orders the shared-memory accesses of one wavefront: writes before it are visible to
 // the reads of the other lanes after it (the LDS serves a wavefront's requests in

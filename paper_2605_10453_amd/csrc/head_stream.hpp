@@ -103,48 +103,69 @@ __device__ __forceinline__ void stream_combine(Stream<L> &a, const Stream<L> &b)
 }
 
 // ---------------------------------------------------------------------------
-// Gumbel-max sampling next to a stream: the two largest z_v + g_v the lane has seen for the row (in the records'
-// units) with their vocabulary ids, and the third largest (a bound for everything else the lane saw).
-struct SampleTrack { float w1, w2, w3; int id1, id2; };
-__device__ __forceinline__ void sample_init(SampleTrack &s) { s.w1 = kNegBig; s.w2 = kNegBig; s.w3 = kNegBig; s.id1 = 0; s.id2 = 0; }
-
-// The 16 values of one group (relative to `ref`, as in stream_group_rel); id0: the vocabulary id of element 0, element
-// i sits at id0 + 8 (i / 4) + i % 4.  Ids rise with i and from group to group, so "strictly larger" keeps the smaller
-// id among equal sums.
-template <bool NAT>
-__device__ __forceinline__ void sample_group(SampleTrack &s, const float (&v)[16], float ref, const GumbelKey &gk, int id0)
-{
+// Gumbel-max sampling next to a stream.  The lane keeps upper bounds of z_v + g_v only (gumbel_bound_bits), in the shape of the top-k
+// lists: the two groups of 16 with the largest bounds (x: the bound, its low 4 bits = position in the group; y: the group's second
+// largest; tag: the group's name) and x of the best group that fell off.  The merge makes the draw of them: few elements of a row come
+// within 0.1 of the winner, and each of them is evaluated exactly there.  What bounds the kernel here is vector instructions: the
+// hash's 18 per element stay, but behind them there were 20 for the noise and 9 for the two best with their ids, and are 4 for the
+// bound and 3 for the group's best two.
+struct SampleTrack { float x[2], y[2], w3; int tag[2]; };
+__device__ __forceinline__ void sample_init(SampleTrack &s) {
+    s.w3 = kNegBig;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const int id = id0 + 8 * (i >> 2) + (i & 3);
-        const float g2 = gumbel_base2(gk, (uint32_t)id);
-        const float w = (v[i] + ref) + (NAT ? g2 * kLn2 : g2);
-        const bool first = w > s.w1, second = w > s.w2;
-        s.w3 = second ? s.w2 : vmax(s.w3, w);
-        s.w2 = first ? s.w1 : (second ? w : s.w2);
-        s.id2 = first ? s.id1 : (second ? id : s.id2);
-        s.id1 = first ? id : s.id1;
-        s.w1 = first ? w : s.w1;
+    for (int l = 0; l < 2; ++l) { s.x[l] = kNegBig; s.y[l] = kNegBig; s.tag[l] = 0; }
+}
+// a group's (x, y, tag) into the sorted pair
+__device__ __forceinline__ void sample_insert(SampleTrack &s, float x, float y, int tag) {
+#pragma unroll
+    for (int l = 0; l < 2; ++l) {
+        const bool c = x > s.x[l];
+        const float nx = c ? x : s.x[l], ny = c ? y : s.y[l];
+        const int nt = c ? tag : s.tag[l];
+        x = c ? s.x[l] : x; y = c ? s.y[l] : y; tag = c ? s.tag[l] : tag;
+        s.x[l] = nx; s.y[l] = ny; s.tag[l] = nt;
     }
+    s.w3 = vmax(s.w3, x);
+}
+
+// The 16 values of one group (relative to `ref`, as in stream_group_rel); id_row_term: the noise's counter (id times kGumbelIdStep +
+// the row's term) of element 0, element i's id is that of element 0 + 8 (i / 4) + i % 4.
+template <bool NAT>
+__device__ __forceinline__ void sample_group(SampleTrack &s, const float (&v)[16], float ref, uint32_t id_row_term, uint32_t hi_term, int tag)
+{
+    constexpr float scale = NAT ? -kGumbelBoundScale * kLn2 : -kGumbelBoundScale, base = NAT ? kGumbelBoundBase * kLn2 : kGumbelBoundBase;
+    const auto bound = [&](int i) {
+        const uint32_t x = gumbel_bits(id_row_term + (uint32_t)(8 * (i >> 2) + (i & 3)) * kGumbelIdStep, hi_term);
+        const float w = fmaf(gumbel_bound_bits(x), scale, v[i]);
+        return __uint_as_float((__float_as_uint(w) & 0xfffffff0u) | (uint32_t)i);
+    };
+    float p[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) p[i] = bound(i);
+    float gr, g2;
+    top2_of_16(p, gr, g2);
+    const float at = ref + base;
+    sample_insert(s, __uint_as_float((__float_as_uint(gr + at) & 0xfffffff0u) | (__float_as_uint(gr) & 15u)), g2 + at, tag);
 }
 
 // fold track b into a (both saw different logits of the same row)
 __device__ __forceinline__ void sample_combine(SampleTrack &a, const SampleTrack &b)
 {
-    // merge of two sorted pairs (ties: smaller id first); the third place takes what is left
-    const auto before = [](float wa, int ia, float wb, int ib) { return wa > wb || (wa == wb && ia < ib); };
-    SampleTrack r;
-    const bool a1 = before(a.w1, a.id1, b.w1, b.id1);
-    r.w1 = a1 ? a.w1 : b.w1; r.id1 = a1 ? a.id1 : b.id1;
-    // candidates for second: the loser of the heads, and the winner's own second
-    const float lw = a1 ? b.w1 : a.w1, ow = a1 ? a.w2 : b.w2;
-    const int li = a1 ? b.id1 : a.id1, oi = a1 ? a.id2 : b.id2;
-    const bool l2 = before(lw, li, ow, oi);
-    r.w2 = l2 ? lw : ow; r.id2 = l2 ? li : oi;
-    // third: the larger of what was not taken (values only)
-    const float rest = l2 ? fmaxf(ow, a1 ? b.w2 : a.w2) : fmaxf(lw, a1 ? a.w3 : b.w3);
-    r.w3 = fmaxf(rest, fmaxf(a.w3, b.w3));
-    a = r;
+    sample_insert(a, b.x[0], b.y[0], b.tag[0]);
+    sample_insert(a, b.x[1], b.y[1], b.tag[1]);
+    a.w3 = vmax(a.w3, b.w3);
+}
+
+// a record's part for the draw: 8 floats behind the stream's
+__device__ __forceinline__ void sample_store(float *w, const SampleTrack &s) {
+#pragma unroll
+    for (int l = 0; l < 2; ++l) { w[3 * l] = s.x[l]; w[3 * l + 1] = s.y[l]; w[3 * l + 2] = __int_as_float(s.tag[l]); }
+    w[6] = s.w3;
+}
+__device__ __forceinline__ void sample_load(SampleTrack &s, const float *w) {
+#pragma unroll
+    for (int l = 0; l < 2; ++l) { s.x[l] = w[3 * l]; s.y[l] = w[3 * l + 1]; s.tag[l] = __float_as_int(w[3 * l + 2]); }
+    s.w3 = w[6];
 }
 
 // Work of block g: row block rb and the vocabulary tiles col, col + gw, col + 2 gw, ...

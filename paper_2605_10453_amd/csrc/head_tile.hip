@@ -84,14 +84,13 @@ __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)
 // X: [8 ceil(K / 64)][rows_pad] 16-byte vectors: 8 consecutive contraction elements of one row, zero beyond K and
 //    beyond the last row; rows_pad a multiple of 64 WR.  NAT = false: the contraction input times log2(e), bf16
 //    (F16: f16): logits come out in base-2 units.  NAT = true: the bf16 input itself (full head): natural units.
-// M: [K][V] bf16 row-major, V and K multiples of 8
+// M: [K][V] bf16 row-major, V and K multiples of 8.
 // part: [rows][gw * hg.spb][3 + 3 L] stream records (values in base-2 units): hg.spb = 4, 2 or 1 per row and block
 // DBG != 0 (experiment builds only, -DSLIMSPEC_DIAG_DBG=n): timing experiments (1 no epilogue, 2 loads only, 3 no loads);
 // their results are meaningless
-// SAMPLE: every lane also keeps, per row, the largest logit + Gumbel noise it has seen (Gumbel-max sampling with the
-//         seed in `sd`; the noise's row index is sd.row_base + the row of this launch); records then have 20 floats:
-//         [12] the largest sum (in the record's units), [13] its id, [14] the second largest, [15] its id,
-//         [16] the third largest, [17..19] unused.
+// SAMPLE: every lane also keeps, per row, what the Gumbel-max draw needs (head_stream.hpp: SampleTrack; the seed is in `sd`, the
+//         noise's row index is sd.row_base + the row of this launch); records then have 20 floats: [12] [13] [14] bound, second
+//         largest bound and name of the best group, [15] [16] [17] of the second best, [18] the third best group's bound, [19] unused.
 struct SampleSeed { uint32_t seed_lo, seed_hi; int row_base; };
 
 template <int L, int WR, bool F16, bool NAT, int DBG, bool SAMPLE>
@@ -360,8 +359,9 @@ __global__ __launch_bounds__(128 * WR, 2) void head_tile_kernel(
                         if constexpr (SAMPLE) {
                             const uint32_t ln = lane_id_now();
                             const int srow = sd.row_base + row0 + (wr * 2 + rt) * 32 + (int)(ln & 31);
-                            sample_group<NAT>(smp[rt], v, ref, gumbel_key(sd.seed_lo, sd.seed_hi, (uint32_t)srow),
-                                              n0 + 32 * (4 * wv + jj) + 4 * (int)(ln >> 5));
+                            const GumbelKey gk = gumbel_key(sd.seed_lo, sd.seed_hi, (uint32_t)srow);
+                            const uint32_t id0 = (uint32_t)(n0 + 32 * (4 * wv + jj)) + 4u * (ln >> 5);
+                            sample_group<NAT>(smp[rt], v, ref, id0 * kGumbelIdStep + gk.row_term, gk.hi_term, c_vt * 8 + 4 * wv + jj);
                         }
                         __builtin_amdgcn_sched_barrier(0);
                     }
@@ -405,7 +405,7 @@ __global__ __launch_bounds__(128 * WR, 2) void head_tile_kernel(
     // streams' 32 or 64 per row, and a row whose best groups crowd into one record pays an exact rescan of all the
     // record's columns in the merge: the fewer records a row has in all (large row counts: few column blocks), the
     // less is folded.  From here on a tag also names the half: tag * 2 + half.
-    constexpr int REC = 3 + 3 * L + (SAMPLE ? 8 : 0);
+    constexpr int REC0 = 3 + 3 * L, REC = REC0 + (SAMPLE ? 8 : 0);
     if (hg.spb == kStreamsPerBlock) {
 #pragma unroll
         for (int rt = 0; rt < 2; ++rt) {
@@ -418,8 +418,8 @@ __global__ __launch_bounds__(128 * WR, 2) void head_tile_kernel(
 #pragma unroll
             for (int l = 0; l < L; ++l) { w[3 + 3 * l] = a.x[l]; w[4 + 3 * l] = a.y[l]; w[5 + 3 * l] = __int_as_float(a.tag[l] * 2 + half); }
             if constexpr (SAMPLE) {
-                w[3 + 3 * L] = smp[rt].w1; w[4 + 3 * L] = __int_as_float(smp[rt].id1); w[5 + 3 * L] = smp[rt].w2;
-                w[6 + 3 * L] = __int_as_float(smp[rt].id2); w[7 + 3 * L] = smp[rt].w3;
+                smp[rt].tag[0] = smp[rt].tag[0] * 2 + half; smp[rt].tag[1] = smp[rt].tag[1] * 2 + half;
+                sample_store(w + REC0, smp[rt]);
             }
         }
         return;
@@ -439,8 +439,12 @@ __global__ __launch_bounds__(128 * WR, 2) void head_tile_kernel(
         if (half == 0) stream_combine(a, o);                                // lanes 0..31 now hold both halves
         if constexpr (SAMPLE) {
             SampleTrack so;
-            so.w1 = __shfl_xor(smp[rt].w1, 32); so.w2 = __shfl_xor(smp[rt].w2, 32); so.w3 = __shfl_xor(smp[rt].w3, 32);
-            so.id1 = __shfl_xor(smp[rt].id1, 32); so.id2 = __shfl_xor(smp[rt].id2, 32);
+#pragma unroll
+            for (int l = 0; l < 2; ++l) {
+                smp[rt].tag[l] = smp[rt].tag[l] * 2 + half;
+                so.x[l] = __shfl_xor(smp[rt].x[l], 32); so.y[l] = __shfl_xor(smp[rt].y[l], 32); so.tag[l] = __shfl_xor(smp[rt].tag[l], 32);
+            }
+            so.w3 = __shfl_xor(smp[rt].w3, 32);
             if (half == 0) sample_combine(smp[rt], so);
         }
     }
@@ -455,8 +459,7 @@ __global__ __launch_bounds__(128 * WR, 2) void head_tile_kernel(
 #pragma unroll
                 for (int l = 0; l < L; ++l) { w[3 + 3 * l] = st[rt].x[l]; w[4 + 3 * l] = st[rt].y[l]; w[5 + 3 * l] = __int_as_float(st[rt].tag[l]); }
                 if constexpr (SAMPLE) {
-                    w[3 + 3 * L] = smp[rt].w1; w[4 + 3 * L] = __int_as_float(smp[rt].id1); w[5 + 3 * L] = smp[rt].w2;
-                    w[6 + 3 * L] = __int_as_float(smp[rt].id2); w[7 + 3 * L] = smp[rt].w3;
+                    sample_store(w + REC0, smp[rt]);
                 }
             }
         }
@@ -472,8 +475,7 @@ __global__ __launch_bounds__(128 * WR, 2) void head_tile_kernel(
 #pragma unroll
             for (int l = 0; l < L; ++l) { o[3 + 3 * l] = st[rt].x[l]; o[4 + 3 * l] = st[rt].y[l]; o[5 + 3 * l] = __int_as_float(st[rt].tag[l]); }
             if constexpr (SAMPLE) {
-                o[3 + 3 * L] = smp[rt].w1; o[4 + 3 * L] = __int_as_float(smp[rt].id1); o[5 + 3 * L] = smp[rt].w2;
-                o[6 + 3 * L] = __int_as_float(smp[rt].id2); o[7 + 3 * L] = smp[rt].w3;
+                sample_store(o + REC0, smp[rt]);
             }
         }
     }
@@ -490,8 +492,7 @@ __global__ __launch_bounds__(128 * WR, 2) void head_tile_kernel(
             stream_combine(st[rt], o);
             if constexpr (SAMPLE) {
                 SampleTrack so;
-                so.w1 = i[3 + 3 * L]; so.id1 = __float_as_int(i[4 + 3 * L]); so.w2 = i[5 + 3 * L];
-                so.id2 = __float_as_int(i[6 + 3 * L]); so.w3 = i[7 + 3 * L];
+                sample_load(so, i + REC0);
                 sample_combine(smp[rt], so);
             }
             if (row >= rows) continue;
@@ -500,8 +501,7 @@ __global__ __launch_bounds__(128 * WR, 2) void head_tile_kernel(
 #pragma unroll
             for (int l = 0; l < L; ++l) { w[3 + 3 * l] = st[rt].x[l]; w[4 + 3 * l] = st[rt].y[l]; w[5 + 3 * l] = __int_as_float(st[rt].tag[l]); }
             if constexpr (SAMPLE) {
-                w[3 + 3 * L] = smp[rt].w1; w[4 + 3 * L] = __int_as_float(smp[rt].id1); w[5 + 3 * L] = smp[rt].w2;
-                w[6 + 3 * L] = __int_as_float(smp[rt].id2); w[7 + 3 * L] = smp[rt].w3;
+                sample_store(w + REC0, smp[rt]);
             }
         }
     }

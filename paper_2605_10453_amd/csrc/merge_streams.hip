@@ -56,7 +56,10 @@ constexpr int kListedBit = 1 << 30;     // marks, in the list of items to evalua
 constexpr int kSampleBit = 1 << 29;     // ... an entry of the sampling contenders' list (smp_id / smp_z) instead
 constexpr float kEpsSigmas = 4.0f;      // eps_v = this many standard deviations of the rounding error of t in column v
                                         // (values are re-evaluated when within eps_a + eps_b = 5.6 sigma of their difference)
-constexpr int kSampleCap = 32;          // streams whose best z + g may be the row's Gumbel-max draw, at most
+constexpr int kSampleCap = 64;          // logits whose z + g may be the row's Gumbel-max draw, at most
+// What a recorded bound of z + g may be off by through its own arithmetic, in the record's units and relative to its size: 4 bits of a
+// sum of up to 160 + |z + g| for the position in the group, as many of the sum moved to its place, two roundings.
+constexpr float kSampleSlack = 5.0e-4f, kSampleSlackRel = 4.0e-6f;
 constexpr int kTsCap = 4096;            // vocabulary tiles whose column scale is kept in shared memory (1 M columns)
 constexpr float kEpsViolation = 1.5f;   // a re-evaluated value further than this many eps_v from its computed value
                                         // shows that the bound does not hold for this input: the row is done exhaustively
@@ -145,9 +148,10 @@ __device__ __forceinline__ void rank_all_pairs_wide(const uint64_t *keys, int n,
 
 }  // namespace
 
-// so.on (sampling calls): the records have rec_stride = kStreamRecSample floats and also carry every stream's best
-// and second best z + g (Gumbel noise); the row's draw is the largest over the streams, decided on exact logits
-// for every stream whose best is within the rounding bound of the largest.
+// so.on (sampling calls): the records have rec_stride = kStreamRecSample floats and also carry upper bounds of z + g (Gumbel noise) for
+// every stream: its two best groups (bound and member, second largest bound) and the best bound of all others.  The bound takes the
+// place of the noise itself in the head kernel, so here a recorded member's noise is put in its place; every member that could then
+// be the largest, and all members of a group whose second largest bound could, are evaluated exactly.
 __global__ __launch_bounds__(kMergeThreads) void merge_streams_kernel(
     const float *__restrict__ part, int rec_stride, int nsr, int gw, int n_vt,
     int resident,       // 0: records of head_tile_kernel, 1: of head_resident_kernel
@@ -184,7 +188,7 @@ __global__ __launch_bounds__(kMergeThreads) void merge_streams_kernel(
     __shared__ int crowd[kCrowdCap];
     __shared__ float mass_eval_sh;
     __shared__ uint64_t smp_wkey[NWAVES];                               // sampling: per-wavefront reductions
-    __shared__ float smp_wz[NWAVES], smp_w2[NWAVES], lse_out_sh;
+    __shared__ float smp_wz[NWAVES], smp_w3[NWAVES], lse_out_sh;
     __shared__ int smp_id[kSampleCap];
     __shared__ float smp_z[kSampleCap];
     __shared__ uint32_t smp_cnt;
@@ -599,40 +603,70 @@ __global__ __launch_bounds__(kMergeThreads) void merge_streams_kernel(
     // correction by the re-evaluated terms could itself overflow.
     bool exhaustive = !(eps < kExhaustiveEps) || !(lse == lse) || !(fabsf(lse) < 1e30f);
 
-    // ---- sampling: the streams whose best z + g could be the row's largest once the logits are exact
+    // column of member i of a group: MFMA tile (tag & 7) of vocabulary tile (tag >> 3) covers 32 adjacent columns
+    auto id_of = [&](int tag, int i, int half) {
+        const int pos = 8 * (i >> 2) + 4 * half + (i & 3);
+        return (tag >> 3) * 256 + 32 * (tag & 7) + pos;
+    };
+
+    // ---- sampling: the members whose z + g could be the row's largest once the logits are exact
     if (so.on) {
+        // z + g of entry q of a stream (computed logit, true noise); no entry, or not one of the head kernel's: -inf
+        const auto entry_value = [&](const float *sp, int q, int &id) {
+            const float x = sp[3 * q];
+            const int rawtag = __float_as_int(sp[3 * q + 2]);
+            id = id_of(rawtag >> 1, (int)(__float_as_uint(x) & 15u), rawtag & 1);
+            if (!(x > kNoValue) || (unsigned)id >= (unsigned)V) { id = -1; return kNegInf; }
+            const float bound = kGumbelBoundBase - kGumbelBoundScale * gumbel_bound_bits(gumbel_bits((uint32_t)id * kGumbelIdStep + gk.row_term, gk.hi_term));
+            return mask4(x) * unit - bound * kLn2 + gumbel_base2(gk, (uint32_t)id) * kLn2;
+        };
         uint64_t best = kNoKey;
-        float w2m = kNegInf;
+        float w3m = kNegInf;
         for (int sidx = tid; sidx < nsr; sidx += NT) {
             const float *sp = rec + (size_t)sidx * rec_stride + REC;
-            const float w1 = sp[0], w3 = sp[4];
-            if (w1 > kNoValue) best = u64_max(best, make_key(w1 * unit, (uint32_t)__float_as_int(sp[1])));
-            if (w3 > kNoValue) w2m = fmaxf(w2m, w3 * unit);        // bounds what the stream saw beyond its two recorded ids
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                int id;
+                const float w = entry_value(sp, q, id);
+                if (id >= 0) best = u64_max(best, make_key(w, (uint32_t)id));
+            }
+            if (sp[6] > kNoValue) w3m = fmaxf(w3m, sp[6] * unit);    // bounds what the stream saw beyond its two groups
         }
         float unused;
         const uint64_t top = block_best(best, 0.f, unused);
-        w2m = wave_max(w2m);
+        w3m = wave_max(w3m);
         if (tid == 0) smp_cnt = 0u;
-        if (lane == 0) smp_w2[wave] = w2m;
+        if (lane == 0) smp_w3[wave] = w3m;
         __syncthreads();
-        float W2 = smp_w2[0];
+        float W3 = smp_w3[0];
 #pragma unroll
-        for (int w = 1; w < NWAVES; ++w) W2 = fmaxf(W2, smp_w2[w]);
-        const float thr_s = key_value(top) - 2.f * eps;
+        for (int w = 1; w < NWAVES; ++w) W3 = fmaxf(W3, smp_w3[w]);
+        const float thr_s = key_value(top) - 2.f * (eps + kSampleSlack + kSampleSlackRel * fabsf(key_value(top)));
         for (int sidx = tid; sidx < nsr; sidx += NT) {
             const float *sp = rec + (size_t)sidx * rec_stride + REC;
 #pragma unroll
-            for (int q = 0; q < 2; ++q) {                    // the stream's best and second best
-                const int idq = __float_as_int(sp[2 * q + 1]);
-                if (sp[2 * q] > kNoValue && sp[2 * q] * unit >= thr_s && (unsigned)idq < (unsigned)V) {
+            for (int q = 0; q < 2; ++q) {
+                int id;
+                const float w = entry_value(sp, q, id);
+                if (id < 0) continue;
+                if (w >= thr_s) {
                     const uint32_t slot = atomicAdd(&smp_cnt, 1u);
-                    if (slot < (uint32_t)kSampleCap) smp_id[slot] = idq;
+                    if (slot < (uint32_t)kSampleCap) smp_id[slot] = id;
+                }
+                if (sp[3 * q + 1] * unit >= thr_s) {            // the group's other members too (rare)
+                    const int rawtag = __float_as_int(sp[3 * q + 2]);
+                    for (int i = 0; i < 16; ++i) {
+                        const int idi = id_of(rawtag >> 1, i, rawtag & 1);
+                        if (idi == id || (unsigned)idi >= (unsigned)V) continue;
+                        const uint32_t slot = atomicAdd(&smp_cnt, 1u);
+                        if (slot < (uint32_t)kSampleCap) smp_id[slot] = idi;
+                    }
                 }
             }
         }
         __syncthreads();
-        // a stream's third best within the bound (its id is not recorded), too many contenders, or none: whole row exact
-        if (top == kNoKey || smp_cnt == 0u || smp_cnt > (uint32_t)kSampleCap || W2 >= thr_s) exhaustive = true;
+        // a third group's bound within reach (its members are not recorded), too many contenders, or none: whole row exact
+        if (top == kNoKey || smp_cnt == 0u || smp_cnt > (uint32_t)kSampleCap || W3 >= thr_s) exhaustive = true;
     }
 
     // ---- collect
@@ -640,11 +674,6 @@ __global__ __launch_bounds__(kMergeThreads) void merge_streams_kernel(
         const uint32_t slot = atomicAdd(&cnt_work, 1u);
         if (slot < (uint32_t)kWorkCap) { w_id[slot] = id; w_val[slot] = val; w_need[slot] = 0; w_apx[slot] = 0.f; w_eps[slot] = e_item; }
         return slot;
-    };
-    // column of member i of a group: MFMA tile (tag & 7) of vocabulary tile (tag >> 3) covers 32 adjacent columns
-    auto id_of = [&](int tag, int i, int half) {
-        const int pos = 8 * (i >> 2) + 4 * half + (i & 3);
-        return (tag >> 3) * 256 + 32 * (tag & 7) + pos;
     };
     const bool wide = eps > kWideEps;
     // May the tokens that keep their computed logits, `rest` of the probability, still move the log-sum-exp?

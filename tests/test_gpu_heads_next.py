@@ -189,6 +189,36 @@ def test_full_head_sample(gpu, oracle_mod, rows, w_f32):
     check_sample_outputs(torch, out, ora, 77, 6152, ora.z, oracle_mod)
 
 
+@pytest.mark.parametrize("where", ["one group", "groups of one lane", "lanes"])
+@pytest.mark.parametrize("rows,head,k", [(60, "full", 5), (140, "full", 9), (60, "low", 5), (140, "low", 16)])
+def test_contenders_for_a_draw_that_share_a_record(gpu, oracle_mod, rows, head, k, where):
+    """Five columns whose z + g lie within 0.06 of each other and far above the rest: members of one group of 16 logits, of groups
+    that one lane holds (more than it lists: the row is done exhaustively), or apart.  What the matrix-core kernel records are bounds
+    that are up to 0.13 too large, so the draw rests on the exact values that the merge puts in their place."""
+    torch, b = gpu
+    V, d, seed = 8200, 64, 9
+    x = synth.make_inputs(synth.small_config(rows, d, 8, V, k), seed=31, with_full_head=True)
+    W = x.W.copy()
+    cols = {"one group": [2048 + 32 * 3 + c for c in (0, 1, 2, 3, 9)], "groups of one lane": [2048 + 32 * j for j in range(4)] + [2049],
+            "lanes": [7, 1500, 3001, 4444, 8199]}[where]
+    targets = [0, 3]                                           # rows the columns are made for: a mixture of two directions
+    h = synth.bf16_bits_to_f64(x.h)
+    g = {t: oracle_mod.gumbel_noise(seed, t, cols) for t in targets}
+    basis = np.stack([h[t] for t in targets])
+    for q, c in enumerate(cols):                               # least norm with h_t . W[:, c] = 24 - g_t(c) + offset
+        want = np.array([24.0 - g[t][q] + 0.015 * ((3 * q + i) % 5) for i, t in enumerate(targets)])
+        W[:, c] = synth.f32_to_bf16_bits((basis.T @ np.linalg.solve(basis @ basis.T, want)).astype(np.float32))
+    A = synth.f32_to_bf16_bits(np.eye(d, dtype=np.float32))    # low-rank head: t = h, so the same logits
+    hd, Wd = to_dev_bf16(x.h), to_dev_bf16(W)
+    out = b.full_head_sample(hd, Wd, k, seed) if head == "full" else b.slimspec_head_sample(hd, to_dev_bf16(A), Wd, k, seed)
+    torch.cuda.synchronize()
+    ora = oracle_mod.head_sample(x.h, None if head == "full" else A, W, k, seed, return_logits=True)
+    for t in targets:
+        w = np.sort(ora.z[t] + oracle_mod.gumbel_noise(seed, t, np.arange(V)))[::-1]
+        assert ora.sample_ids[t] in cols and w[0] - w[4] < 0.1 and w[4] - w[5] > 2, w[:6]
+    check_sample_outputs(torch, out, ora, seed, V, ora.z, oracle_mod)
+
+
 def test_sample_frequencies_on_the_gpu(gpu, oracle_mod):
     """Many seeds on one row: the drawn ids follow the checker's softmax (binomial bound on the most likely tokens)."""
     torch, b = gpu
