@@ -4,6 +4,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include "plan.hpp"
 
 namespace slimspec {
 
@@ -30,9 +31,16 @@ __device__ __forceinline__ uint32_t operand_bf16_bits(float t) {
     return (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
 }
 __device__ __forceinline__ _Float16 operand_f16(float t) { return (_Float16)(t * kLog2e); }
-// ... and the value of t it stands for
-__device__ __forceinline__ float operand_value(float t, bool as_f16) {
-    return (as_f16 ? (float)operand_f16(t) : __uint_as_float(operand_bf16_bits(t) << 16)) * kLn2;
+// ... as two bf16 pieces: the rounded value and what is left of it, rounded (the difference is exact)
+__device__ __forceinline__ uint32_t operand_rest_bf16_bits(float t) {
+    const uint32_t u = __float_as_uint(t * kLog2e - __uint_as_float(operand_bf16_bits(t) << 16));
+    return (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
+}
+// ... and the value of t it stands for (how: plan.hpp, kOperandBf16 ...)
+__device__ __forceinline__ float operand_value(float t, int how) {
+    if (how == kOperandF16) return (float)operand_f16(t) * kLn2;
+    const float hi = __uint_as_float(operand_bf16_bits(t) << 16);
+    return (how == kOperandTwoBf16 ? hi + __uint_as_float(operand_rest_bf16_bits(t) << 16) : hi) * kLn2;
 }
 
 // Order of the outputs: larger logit first, equal logits: smaller id first.

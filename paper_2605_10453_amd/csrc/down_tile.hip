@@ -264,7 +264,7 @@ __global__ __launch_bounds__(256) void down_tile_kernel(
 // t (a wavefront's share of a tile of down_tile_kernel); grid = 4 n_rt n_ct.
 //   t32   [rows_pad, r]            fp32 t (zero for padding rows)
 //   t16   [8 ceil(r / 64), rows_pad]   16-byte vectors of 8 values t log2(e) in bf16 or f16 (round to nearest even),
-//                                      zero for k >= r and for padding rows
+//                                      zero for k >= r and for padding rows; kOperandTwoBf16: the second pieces behind them
 //   stat  [2 ceil(r / 64), rows_pad]   per 32-column piece: (sum of (t - its 16-bit value)^2, sum of t^2) of its entries
 // PIECES: t leaves as three bf16 pieces instead, t16 [3][8 ceil(r / 64)][rows_pad] (no t32, stat or column scales).
 // The pieces are cut off the top of t's significand, 8 bits each: their sum is t exactly.
@@ -272,7 +272,7 @@ template <bool PIECES>
 __global__ __launch_bounds__(256) void down_finish_kernel(
     const float *__restrict__ part, int rows_pad, int r,
     float *__restrict__ t32, uint4 *__restrict__ t16, float2 *__restrict__ stat,
-    const uint16_t *__restrict__ B, int V, float2 *__restrict__ tilescale, int as_f16, DownGrid g)
+    const uint16_t *__restrict__ B, int V, float2 *__restrict__ tilescale, int operand, DownGrid g)
 {
     __shared__ float tile[32 * 33];
     __shared__ float red_a[4 * 32], red_b[4 * 32];
@@ -327,7 +327,7 @@ __global__ __launch_bounds__(256) void down_finish_kernel(
         const int row = tid & 31, cg = tid >> 5;
         const int kg = (n0 >> 3) + cg;
         const bool valid = row0 + row < rows && kg < (r >> 3);
-        const bool mine = row0 + row < row_end;                 // rows beyond belong to the next group's tiles
+        bool mine = row0 + row < row_end;                 // rows beyond belong to the next group's tiles
         float v[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) v[e] = valid ? tile[row * 33 + cg * 8 + e] : 0.f;
@@ -363,7 +363,22 @@ __global__ __launch_bounds__(256) void down_finish_kernel(
             o[1] = make_float4(v[4], v[5], v[6], v[7]);
         }
         uint4 packed;
-        if (!as_f16) {
+        if (operand == kOperandTwoBf16) {
+            uint32_t hb[8], lb[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                hb[e] = operand_bf16_bits(v[e]);
+                lb[e] = operand_rest_bf16_bits(v[e]);
+                const float dlt = v[e] - operand_value(v[e], kOperandTwoBf16);
+                a += dlt * dlt;
+                b += v[e] * dlt;
+            }
+            packed = make_uint4(hb[0] | (hb[1] << 16), hb[2] | (hb[3] << 16), hb[4] | (hb[5] << 16), hb[6] | (hb[7] << 16));
+            const int n_kg = two_pieces_stride(r) >> 3;            // groups of a piece
+            if (kg >= n_kg) mine = false;
+            if (mine) t16[(size_t)(n_kg + kg) * rows_pad + row0 + row] =
+                make_uint4(lb[0] | (lb[1] << 16), lb[2] | (lb[3] << 16), lb[4] | (lb[5] << 16), lb[6] | (lb[7] << 16));
+        } else if (operand != kOperandF16) {
             uint32_t hb[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
@@ -413,12 +428,12 @@ static hipError_t launch_down_tiles(const uint16_t *h, const uint16_t *A, float 
 hipError_t launch_down_projection_tiles(const uint16_t *h, const uint16_t *A, float *part, const DownGrid &g,
                                         int rows_pad, int d, int r,
                                         float *t32, void *t16, float2 *stat, const uint16_t *B, int V, float2 *tilescale,
-                                        bool as_f16, hipStream_t st)
+                                        Operand operand, hipStream_t st)
 {
     const hipError_t e = launch_down_tiles<false>(h, A, part, g, d, r, st);
     if (e != hipSuccess) return e;
     down_finish_kernel<false><<<4 * g.n_rt_all * g.n_ct + (V + 511) / 512, 256, 0, st>>>(
-        part, rows_pad, r, t32, static_cast<uint4 *>(t16), stat, B, V, tilescale, as_f16 ? 1 : 0, g);
+        part, rows_pad, r, t32, static_cast<uint4 *>(t16), stat, B, V, tilescale, operand, g);
     return hipGetLastError();
 }
 
@@ -428,7 +443,7 @@ hipError_t launch_down_projection_pieces(const uint16_t *h, const uint16_t *A, f
     const hipError_t e = launch_down_tiles<true>(h, A, part, g, d, r, st);
     if (e != hipSuccess) return e;
     down_finish_kernel<true><<<4 * g.n_rt_all * g.n_ct, 256, 0, st>>>(
-        part, rows_pad, r, nullptr, static_cast<uint4 *>(X), nullptr, nullptr, 0, nullptr, 0, g);
+        part, rows_pad, r, nullptr, static_cast<uint4 *>(X), nullptr, nullptr, 0, nullptr, kOperandExact, g);
     return hipGetLastError();
 }
 

@@ -70,11 +70,12 @@ constexpr float kNoMax = -1.0e30f;                        // a reference for a s
 // X: [8 ceil(K / 64)][rows_pad] 16-byte vectors: t log2(e) in bf16, 8 consecutive contraction elements of one row, zero
 //    beyond K and beyond the last row; rows_pad a multiple of 256.  M: [K][V] bf16 row-major, K and V multiples of 8.
 // part: [rows][gw * 2] records as head_tile_kernel writes them, one per half-wavefront.
-// KS: contraction steps of 16, ceil(K / 128) * 8.
+// KS: contraction steps of 16, ceil(K / 128) * 8.  split (16, 32 or 64, at least K; 0: one piece): X holds two pieces of
+// every element, [2][split / 8][rows_pad].
 template <int KS>
 __global__ __launch_bounds__(512, 2) void head_resident_kernel(
     const uint4 *__restrict__ X, const uint16_t *__restrict__ M, float *__restrict__ part,
-    int rows, int rows_pad, int K, int V, ResidentGrid hg)
+    int rows, int rows_pad, int K, int V, int split, ResidentGrid hg)
 {
     constexpr int L = kStreamList, REC = kStreamRec;
     constexpr int SPT = KS / 8;                           // stages per tile
@@ -101,13 +102,15 @@ __global__ __launch_bounds__(512, 2) void head_resident_kernel(
         const uint32_t rowb = (uint32_t)V * 2u;
         const uint32_t src_piece = (uint32_t)((lane & 7) ^ (((lane >> 3) & 3) << 1)) * 16u;
         uint32_t voff[kRLoads];
+        // two pieces of t (K <= 64, one stage) meet the same rows
+        const int row_mask = KS == 8 && split ? split - 1 : kRStageK - 1;
         const auto set_offsets = [&](int t, int st_k) {
             // columns beyond V re-read the last 16 bytes that exist, rows beyond K the last 8 (they meet zeros of X);
             // K is a multiple of 8: the 8 rows of a load all exist or none does
             const uint32_t c = min(src_piece, (uint32_t)(V - t * kRTile - 8) * 2u);
 #pragma unroll
             for (int u = 0; u < kRLoads; ++u)
-                voff[u] = (uint32_t)(min(16 * wave + 8 * u, K - 8 - st_k * kRStageK) + (lane >> 3)) * rowb + c;
+                voff[u] = (uint32_t)(min((16 * wave + 8 * u) & row_mask, K - 8 - st_k * kRStageK) + (lane >> 3)) * rowb + c;
         };
         const size_t stage_step = (size_t)kRStageK * rowb;
         const bool ragged_k = (K & (kRStageK - 1)) != 0;
@@ -143,7 +146,7 @@ __global__ __launch_bounds__(512, 2) void head_resident_kernel(
         // ---- the rows' operand: lane (row l32, contraction elements 16 s + 8 half ...)
         u32x4 xr[KS];
         {
-            const int n_groups = (K + 63) / 64 * 8;       // 8-element groups that X holds
+            const int n_groups = KS == 8 && split ? split / 4 : (K + 63) / 64 * 8;      // 8-element groups that X holds
             const uint4 *src = X + (size_t)half * rows_pad + row0 + l32;
 #pragma unroll
             for (int s = 0; s < KS; ++s) {
@@ -330,24 +333,25 @@ __global__ __launch_bounds__(512, 2) void head_resident_kernel(
 }
 
 template <int KS>
-static hipError_t launch_resident(const void *X, const uint16_t *M, float *part, int rows, int rows_pad, int K, int V,
+static hipError_t launch_resident(const void *X, int split, const uint16_t *M, float *part, int rows, int rows_pad, int K, int V,
                                   const ResidentGrid &g, hipStream_t st)
 {
     const int lds = kRNB * (int)kRStageBytes;
     static LdsLimit lds_limit;
     hipError_t e = lds_limit.raise(reinterpret_cast<const void *>(head_resident_kernel<KS>), lds);
     if (e != hipSuccess) return e;
-    head_resident_kernel<KS><<<g.n_rb * g.gw, 512, lds, st>>>(static_cast<const uint4 *>(X), M, part, rows, rows_pad, K, V, g);
+    head_resident_kernel<KS><<<g.n_rb * g.gw, 512, lds, st>>>(static_cast<const uint4 *>(X), M, part, rows, rows_pad, K, V, split, g);
     return hipGetLastError();
 }
 
-hipError_t launch_head_resident(const void *X, const uint16_t *M, float *part, int rows, int rows_pad, int K, int V,
+hipError_t launch_head_resident(const void *X, Operand operand, const uint16_t *M, float *part, int rows, int rows_pad, int K, int V,
                                 const ResidentGrid &g, hipStream_t st)
 {
-    if (K <= 128) return launch_resident<8>(X, M, part, rows, rows_pad, K, V, g, st);
-    if (K <= 256) return launch_resident<16>(X, M, part, rows, rows_pad, K, V, g, st);
-    if (K <= 384) return launch_resident<24>(X, M, part, rows, rows_pad, K, V, g, st);
-    return launch_resident<32>(X, M, part, rows, rows_pad, K, V, g, st);
+    const int split = operand == kOperandTwoBf16 ? two_pieces_stride(K) : 0;
+    if (K <= 128) return launch_resident<8>(X, split, M, part, rows, rows_pad, K, V, g, st);
+    if (K <= 256) return launch_resident<16>(X, 0, M, part, rows, rows_pad, K, V, g, st);
+    if (K <= 384) return launch_resident<24>(X, 0, M, part, rows, rows_pad, K, V, g, st);
+    return launch_resident<32>(X, 0, M, part, rows, rows_pad, K, V, g, st);
 }
 
 }  // namespace slimspec

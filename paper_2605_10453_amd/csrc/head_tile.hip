@@ -84,7 +84,8 @@ __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)
 // X: [8 ceil(K / 64)][rows_pad] 16-byte vectors: 8 consecutive contraction elements of one row, zero beyond K and
 //    beyond the last row; rows_pad a multiple of 64 WR.  NAT = false: the contraction input times log2(e), bf16
 //    (F16: f16): logits come out in base-2 units.  NAT = true: the bf16 input itself (full head): natural units.
-// M: [K][V] bf16 row-major, V and K multiples of 8.
+// M: [K][V] bf16 row-major, V and K multiples of 8.  split (16, 32 or 64, at least K; 0: one piece): X holds two pieces of
+//    every element, [2][split / 8][rows_pad].
 // part: [rows][gw * hg.spb][3 + 3 L] stream records (values in base-2 units): hg.spb = 4, 2 or 1 per row and block
 // DBG != 0 (experiment builds only, -DSLIMSPEC_DIAG_DBG=n): timing experiments (1 no epilogue, 2 loads only, 3 no loads);
 // their results are meaningless
@@ -96,7 +97,7 @@ struct SampleSeed { uint32_t seed_lo, seed_hi; int row_base; };
 template <int L, int WR, bool F16, bool NAT, int DBG, bool SAMPLE>
 __global__ __launch_bounds__(128 * WR, 2) void head_tile_kernel(
     const uint4 *__restrict__ X, const uint16_t *__restrict__ M, float *__restrict__ part,
-    int rows, int rows_pad, int K, int V, HeadGrid hg, SampleSeed sd)
+    int rows, int rows_pad, int K, int V, int split, HeadGrid hg, SampleSeed sd)
 {
     using S = TileShape<WR>;
     extern __shared__ __align__(1024) unsigned char lds_raw[];
@@ -108,10 +109,10 @@ __global__ __launch_bounds__(128 * WR, 2) void head_tile_kernel(
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
     const int rb = slot % hg.n_rb, col = (slot / hg.n_rb) * 8 + xcd;
     const int row0 = rb * S::RT;
-    const int nkb = (K + kTKB - 1) / kTKB;
+    const int nkb = split ? 2 * split / kTKB : (K + kTKB - 1) / kTKB;
     const int njobs = (col < hg.n_vt) ? (hg.n_vt - col + hg.gw - 1) / hg.gw : 0;
     const int total = njobs * nkb;
-    const bool ktail = (K & (kTKB - 1)) != 0;
+    const bool ktail = (K & (kTKB - 1)) != 0 || split;
 
     // ---- direct-to-LDS loads of one stage.
     // M load uu of this wavefront covers stage rows 2 MPW wave + 2 uu + (lane >> 5); lane -> stored piece
@@ -143,11 +144,11 @@ __global__ __launch_bounds__(128 * WR, 2) void head_tile_kernel(
     const unsigned char *mptr = m_wave + (size_t)col * kTNT * 2, *xptr = x_wave;
     const auto issue_stage = [&](uint32_t buf) {
         const uint32_t mb = buf + m_lds;
-        if (ktail && a_kb == nkb - 1) {
+        if (ktail && (a_kb == nkb - 1 || split)) {
             // last, partial k-block: rows beyond K are read from rows K - 2, K - 1 (they meet zeros of X)
             const uint32_t ce = mv[0], co = mv[1] - 2u * rowb;
             const unsigned char *tile0 = reinterpret_cast<const unsigned char *>(M) + (size_t)a_vt * kTNT * 2;
-            const int k0 = a_kb * kTKB + RPW * wave;
+            const int k0 = (a_kb * kTKB + RPW * wave) & (split - 1);      // (two pieces meet the same rows; split 0: all bits)
             dma16<0>(mb, ce, tile0 + (size_t)min(k0, K - 2) * rowb);
             dma16<1024>(mb, co, tile0 + (size_t)min(k0 + 2, K - 2) * rowb);
             if (S::MPW == 4) {
@@ -534,7 +535,7 @@ int head_tile_rows_per_block(int rows) {
 }
 
 template <int WR, bool F16, bool NAT, int DBG, bool SAMPLE>
-static hipError_t launch_tile_cfg(const void *X, const uint16_t *M, float *part, int rows, int rows_pad,
+static hipError_t launch_tile_cfg(const void *X, int split, const uint16_t *M, float *part, int rows, int rows_pad,
                                   int K, int V, int n_rb, int gw, const SampleSeed &sd, hipStream_t st)
 {
     using S = TileShape<WR>;
@@ -543,7 +544,7 @@ static hipError_t launch_tile_cfg(const void *X, const uint16_t *M, float *part,
     hipError_t e = lds_limit.raise(reinterpret_cast<const void *>(fn), S::LDS);
     if (e != hipSuccess) return e;
     HeadGrid hg{n_rb, gw, (V + kTNT - 1) / kTNT, streams_per_block(gw)};
-    fn<<<n_rb * gw, 64 * S::NW, S::LDS, st>>>(static_cast<const uint4 *>(X), M, part, rows, rows_pad, K, V, hg, sd);
+    fn<<<n_rb * gw, 64 * S::NW, S::LDS, st>>>(static_cast<const uint4 *>(X), M, part, rows, rows_pad, K, V, split, hg, sd);
     return hipGetLastError();
 }
 
@@ -554,16 +555,17 @@ static hipError_t launch_tile_cfg(const void *X, const uint16_t *M, float *part,
 #endif
 bool head_tile_timing_only() { return SLIMSPEC_DIAG_DBG != 0; }
 
-hipError_t launch_head_tile(const void *X, bool x_is_f16, bool natural_units, const uint16_t *M, float *part, int rows, int rows_pad,
+hipError_t launch_head_tile(const void *X, Operand operand, const uint16_t *M, float *part, int rows, int rows_pad,
                             int K, int V, int n_rb, int gw, const SampleOut &so, int row_base, hipStream_t st)
 {
     const bool big = head_tile_rows_per_block(rows) == 256;
     const SampleSeed sd{so.seed_lo, so.seed_hi, row_base};
-#define SLIMSPEC_TILE_S(F16, NAT, DBG, SMP) (big ? launch_tile_cfg<4, F16, NAT, DBG, SMP>(X, M, part, rows, rows_pad, K, V, n_rb, gw, sd, st) \
-                                                 : launch_tile_cfg<2, F16, NAT, DBG, SMP>(X, M, part, rows, rows_pad, K, V, n_rb, gw, sd, st))
+    const int split = operand == kOperandTwoBf16 ? two_pieces_stride(K) : 0;
+#define SLIMSPEC_TILE_S(F16, NAT, DBG, SMP) (big ? launch_tile_cfg<4, F16, NAT, DBG, SMP>(X, split, M, part, rows, rows_pad, K, V, n_rb, gw, sd, st) \
+                                                 : launch_tile_cfg<2, F16, NAT, DBG, SMP>(X, split, M, part, rows, rows_pad, K, V, n_rb, gw, sd, st))
 #define SLIMSPEC_TILE_F(F16, NAT, DBG) (so.on ? SLIMSPEC_TILE_S(F16, NAT, 0, true) : SLIMSPEC_TILE_S(F16, NAT, DBG, false))
-#define SLIMSPEC_TILE(DBG) (natural_units ? SLIMSPEC_TILE_F(false, true, DBG) \
-                                          : (x_is_f16 ? SLIMSPEC_TILE_F(true, false, DBG) : SLIMSPEC_TILE_F(false, false, DBG)))
+#define SLIMSPEC_TILE(DBG) (operand == kOperandExact ? SLIMSPEC_TILE_F(false, true, DBG) \
+                                          : (operand == kOperandF16 ? SLIMSPEC_TILE_F(true, false, DBG) : SLIMSPEC_TILE_F(false, false, DBG)))
     return SLIMSPEC_TILE(SLIMSPEC_DIAG_DBG);
 #undef SLIMSPEC_TILE
 #undef SLIMSPEC_TILE_F

@@ -69,7 +69,7 @@ constexpr int kStreamRecSample = kStreamRec + 8;  // ... of a sampling call
 static_assert(kStreamList == kStreamListPlan && kStreamRecSample == kStreamRecPlan, "the workspace plan is sized for these records");
 
 // t = h A for up to 512 rows: 64 x 64 tiles over slices of the contraction (partial tiles in `part`), then the
-// fixed-order sum of the slices: fp32 t, the 16-bit operand t log2(e) (bf16, or f16 when as_f16) in the k-grouped
+// fixed-order sum of the slices: fp32 t, the 16-bit operand t log2(e) (bf16, f16 or two bf16 pieces) in the k-grouped
 // layout of head_tile_kernel (zero beyond r and beyond the last row), per-row rounding statistics per 32 columns,
 // and per 256-column vocabulary tile (the largest column rms, the mean square) of B over a sample of its rows
 // (tilescale [ceil(V / 256)])
@@ -77,7 +77,7 @@ static_assert(kStreamList == kStreamListPlan && kStreamRecSample == kStreamRecPl
 hipError_t launch_down_projection_tiles(const uint16_t *h, const uint16_t *A, float *part, const DownGrid &g,
                                         int rows_pad, int d, int r,
                                         float *t32, void *t16, float2 *stat, const uint16_t *B, int V, float2 *tilescale,
-                                        bool as_f16, hipStream_t st);
+                                        Operand operand, hipStream_t st);
 
 // the same t as three bf16 pieces, t = hi + mid + lo exactly (rows_head.hip): X [3][8 ceil(r / 64)][rows_pad] 16-byte
 // vectors, zero beyond r and beyond the last row
@@ -95,15 +95,15 @@ hipError_t launch_rows_topk(const void *X, int pieces, const uint16_t *M, float2
 
 // vocabulary projection with the fused epilogue, stages loaded straight into LDS; X is 16-byte vectors of 8 contraction
 // elements, [ceil(K / 64) * 8][rows_pad], rows_pad a multiple of 128; columns of an MFMA tile are contiguous
-// x_is_f16: X holds f16 t log2(e) and the kernel turns the M tiles into f16 inside LDS (an 8 times
-// finer operand than bf16); otherwise X holds bf16 t log2(e)
-// natural_units: X holds the bf16 contraction input itself (full head) and the records carry natural-log values
+// operand: kOperandF16: X holds f16 t log2(e) and the kernel turns the M tiles into f16 inside LDS (an 8 times
+// finer operand than bf16); kOperandBf16: bf16 t log2(e); kOperandTwoBf16: its two pieces, the second one two_pieces_stride(K) elements
+// behind the first (K <= 64); kOperandExact: the bf16 contraction input itself (full head), and the records carry natural-log values
 // so.on: the records also carry every stream's Gumbel-max candidates (kStreamRecSample floats per record); row_base:
 // index of the launch's first row in the call (the noise is a function of the row's index in the call)
-hipError_t launch_head_tile(const void *X, bool x_is_f16, bool natural_units, const uint16_t *M, float *part, int rows, int rows_pad,
+hipError_t launch_head_tile(const void *X, Operand operand, const uint16_t *M, float *part, int rows, int rows_pad,
                             int K, int V, int n_rb, int gw, const SampleOut &so, int row_base, hipStream_t st);
-// the same with the row operand resident in registers: bf16 t log2(e), K <= kResidentMaxK, rows_pad a multiple of 256
-hipError_t launch_head_resident(const void *X, const uint16_t *M, float *part, int rows, int rows_pad, int K, int V,
+// the same with the row operand resident in registers: bf16 t log2(e) or two pieces, K <= kResidentMaxK, rows_pad a multiple of 256
+hipError_t launch_head_resident(const void *X, Operand operand, const uint16_t *M, float *part, int rows, int rows_pad, int K, int V,
                                 const ResidentGrid &g, hipStream_t st);
 // true only in an experiment build (-DSLIMSPEC_DIAG_DBG=n) where a timing-only variant replaces the kernel: its
 // output is not a result and the calls then return SLIMSPEC_UNSUPPORTED
@@ -115,13 +115,13 @@ hipError_t launch_regroup_rows(const uint16_t *h, void *X, int rows, int rows_pa
 // nsr records per row (4, 2 or 1 for each of the gw column blocks of the head kernel's grid; resident: they are
 // head_resident_kernel's); unit: factor from the
 // records' values to natural-log logits; tiny_w: magnitude below which the kernel flushed weights to zero;
-// operand16: 0 the head kernel's row operand was exact, 1 it was t log2(e) rounded to bf16, 2 to f16 (the merge then
-// recomputes, from the same rounding, the logit the head kernel saw for a column that has no recorded value);
+// operand: the head kernel's row operand (where it was rounded the merge recomputes, from the same rounding, the logit the head kernel
+// saw for a column that has no recorded value);
 // Mt: null, or the column-major copy of M, [V, K] (an exact logit then reads K adjacent elements; rows are not parked);
 // defer_buf: merge_defer_bytes(rows) of scratch, or null: with it, rows that need exact re-evaluations are finished by
 // two more launches that spread the column gathers over many CUs (worth it for long contractions only)
 hipError_t launch_merge_streams(const float *part, int rows, int nsr, int gw, int n_vt, bool resident,
-                                const void *xexact, bool x_is_bf16, int ldx, int operand16,
+                                const void *xexact, bool x_is_bf16, int ldx, Operand operand,
                                 const uint16_t *M, int K, int V, const uint16_t *Mt,
                                 const float2 *stat, int n_stat, int rows_pad, const float2 *tilescale, int k,
                                 float unit, float tiny_w, int32_t *out_ids, float *out_logprobs, const int32_t *id_map,

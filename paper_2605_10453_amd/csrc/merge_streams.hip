@@ -156,7 +156,7 @@ __global__ __launch_bounds__(kMergeThreads) void merge_streams_kernel(
     const float *__restrict__ part, int rec_stride, int nsr, int gw, int n_vt,
     int resident,       // 0: records of head_tile_kernel, 1: of head_resident_kernel
     const void *__restrict__ xexact, int x_is_bf16, int ldx,
-    int operand16,      // 0: the head kernel's row operand was exact; 1: it was t log2(e) rounded to bf16; 2: to f16
+    Operand operand,    // the head kernel's row operand
     const uint16_t *__restrict__ M, int K, int V,
     const uint16_t *__restrict__ Mt,      // null, or the caller's column-major copy of M, [V, K]: a column is K adjacent elements
     const float2 *__restrict__ stat, int n_stat, int rows_pad, const float2 *__restrict__ tilescale,
@@ -179,7 +179,7 @@ __global__ __launch_bounds__(kMergeThreads) void merge_streams_kernel(
     float *ts = w_eps + kWorkCap;                                       // [min(n_vt, kTsCap)]  column scale of B per vocabulary tile
     const bool ts_cached = n_vt <= kTsCap;                              // a larger vocabulary uses the largest scale for every tile
     float *xrow = ts + ((min(n_vt, kTsCap) + 3) & ~3);                  // [K]            the row's exact contraction input
-    float *xrow16 = xrow + K;                                           // [K]            ... as the head kernel had it (operand16 != 0)
+    float *xrow16 = xrow + K;                                           // [K]            ... as the head kernel had it (operand not exact)
     __shared__ float red_m[NWAVES], red_s[NWAVES];
     __shared__ uint64_t tau_key;
     __shared__ uint32_t cnt_work, cnt_hidden, cnt_need;
@@ -445,7 +445,7 @@ __global__ __launch_bounds__(kMergeThreads) void merge_streams_kernel(
     for (int j = tid; j < K; j += NT) {
         const float v = (j == tid) ? x_first : x_at(ctx, j);
         xrow[j] = v; x2 += v * v; x1 += fabsf(v);
-        if (operand16) xrow16[j] = operand_value(v, operand16 == 2);
+        if (operand != kOperandExact) xrow16[j] = operand_value(v, operand);
     }
     __shared__ float dt2_sh, tdt_sh;
     // Column scale of B per vocabulary tile (asked for early: by the time eps needs it, it has arrived): the largest
@@ -585,7 +585,9 @@ __global__ __launch_bounds__(kMergeThreads) void merge_streams_kernel(
     float dt_scale = 0.f, eps_abs;
     if (stat != nullptr) {
         dt_scale = kEpsSigmas * sqrtf(dt2_sh);
-        eps_abs = fabsf(tau) * 1.2e-5f + tiny_w * X1 + 1e-30f;
+        // (two pieces: nothing but eps_abs is left, and the k-th value may be far smaller than the first)
+        const float largest = operand == kOperandTwoBf16 ? fmaxf(fabsf(tau), fabsf(Mx * kLn2)) : fabsf(tau);
+        eps_abs = largest * 1.2e-5f + tiny_w * X1 + 1e-30f;
     }
     else eps_abs = fabsf(tau) * 1.6e-5f + 1e-6f;
     // Scale of a tile's columns: the rms of all of B (tens of thousands of sampled entries: no noise to speak of), or
@@ -889,7 +891,7 @@ __global__ __launch_bounds__(kMergeThreads) void merge_streams_kernel(
             __syncthreads();
         }
         // (a row with unlisted members on a bf16 operand stays here: their recomputed 16-bit logits come with the gathers)
-        const bool park_ok = !(operand16 == 1 && cnt_hidden != 0u);
+        const bool park_ok = !(operand == kOperandBf16 && cnt_hidden != 0u);
         if (park && park_ok && cnt_need != 0u && cnt_need <= (uint32_t)kDeferNeed && n_work <= kDeferWork) {
             // park the row: collected set, list of columns, the streams' log-sum-exp
             const int n_need = (int)cnt_need;
@@ -906,7 +908,7 @@ __global__ __launch_bounds__(kMergeThreads) void merge_streams_kernel(
         // whole block has 16 rows in flight per step; partial sums are combined in a fixed order
         const int n_need = (int)cnt_need;
         __shared__ float red_ex[NWAVES][16], red_ex16[NWAVES][16];
-        const bool with16 = operand16 != 0;
+        const bool with16 = operand != kOperandExact;
         // Column-major copy: a column is K adjacent elements.  kGatherRound columns per round; wavefront w takes columns w,
         // w + NWAVES, ... of the round, a lane 8 adjacent elements of the column per step (K = 512: one 16-byte load
         // per lane and column, all of a wavefront's columns in flight together); lanes in order inside the DPP tree.
@@ -1117,7 +1119,7 @@ size_t merge_streams_lds_bytes(int nsr, int n_vt) {
 }
 
 hipError_t launch_merge_streams(const float *part, int rows, int nsr, int gw, int n_vt, bool resident,
-                                const void *xexact, bool x_is_bf16, int ldx, int operand16,
+                                const void *xexact, bool x_is_bf16, int ldx, Operand operand,
                                 const uint16_t *M, int K, int V, const uint16_t *Mt,
                                 const float2 *stat, int n_stat, int rows_pad, const float2 *tilescale, int k,
                                 float unit, float tiny_w, int32_t *out_ids, float *out_logprobs, const int32_t *id_map,
@@ -1131,14 +1133,14 @@ hipError_t launch_merge_streams(const float *part, int rows, int nsr, int gw, in
     int *defer = (so.on || Mt != nullptr) ? nullptr : static_cast<int *>(defer_buf);
     const int rec_stride = so.on ? kStreamRecSample : kStreamRec;
     merge_streams_kernel<<<rows, kMergeThreads, lds, st>>>(part, rec_stride, nsr, gw, n_vt, resident ? 1 : 0, xexact, x_is_bf16 ? 1 : 0, ldx,
-                                                           operand16, M, K, V, Mt, stat, n_stat, rows_pad, tilescale, k, unit, tiny_w, out_ids, out_logprobs, id_map,
+                                                           operand, M, K, V, Mt, stat, n_stat, rows_pad, tilescale, k, unit, tiny_w, out_ids, out_logprobs, id_map,
                                                            defer, 0, so, row_base);
     if ((e = hipGetLastError()) != hipSuccess || !defer) return e;
     // parked rows: their exact columns on many CUs, then the rest of their merge
     exact_cols_kernel<<<dim3(kDeferSlices, rows), 256, 0, st>>>(defer, xexact, x_is_bf16 ? 1 : 0, ldx, M, K, V);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     merge_streams_kernel<<<rows, kMergeThreads, lds, st>>>(part, rec_stride, nsr, gw, n_vt, resident ? 1 : 0, xexact, x_is_bf16 ? 1 : 0, ldx,
-                                                           operand16, M, K, V, Mt, stat, n_stat, rows_pad, tilescale, k, unit, tiny_w, out_ids, out_logprobs, id_map,
+                                                           operand, M, K, V, Mt, stat, n_stat, rows_pad, tilescale, k, unit, tiny_w, out_ids, out_logprobs, id_map,
                                                            defer, 1, so, row_base);
     return hipGetLastError();
 }

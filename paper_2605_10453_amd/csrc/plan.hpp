@@ -235,6 +235,10 @@ inline ResidentGrid make_resident_grid(int n_rb, int V) {
     return g;
 }
 
+constexpr int kTwoPiecesMaxRank = 64;    // ranks whose t the many-row kernels take in two bf16 pieces (tile_operand below)
+// elements between the two pieces: the least that head_tile_kernel's stages of 32 allow
+constexpr __host__ __device__ int two_pieces_stride(int r) { return r <= 16 ? 16 : r <= 32 ? 32 : 64; }
+
 struct MfmaPlan {
     int rows = 0, rows_pad = 0, rt = 0, n_rb = 0, gw = 0, nsr = 0, n_vt = 0;
     bool resident = false;               // the row operand fits a wavefront's registers (bf16 operands)
@@ -242,7 +246,7 @@ struct MfmaPlan {
     DownGrid down;
     size_t off_down_part = 0;            // fp32 [slices][n_rt][n_ct][4][16][64]: partial tiles of t (sized for any grouping of the rows)
     size_t off_t32 = 0;                  // fp32 [rows_pad, r]
-    size_t off_t16 = 0;                  // 16-byte vectors [8 ceil(K / 64), rows_pad]: the head kernel's row operand
+    size_t off_t16 = 0;                  // 16-byte vectors [8 ceil(K / 64), rows_pad]: the head kernel's row operand (two of them for two pieces)
     size_t off_stat = 0;                 // float2 [2 ceil(r / 64), rows_pad]: per row and 32 columns of t, (sum of dt^2, sum of t dt), dt = t - rounded t
     size_t off_tilescale = 0;            // float2 [n_vt]: (column scale, mean square) of B per vocabulary tile
     size_t off_streams = 0;              // fp32 [rows, nsr, kStreamRec]
@@ -268,7 +272,7 @@ inline MfmaPlan make_mfma_plan(HeadKind kind, int rows, int d, int r, int V) {
     size_t off = 0;
     if (kind == HeadKind::LowRank) {
         p.off_t32 = off;       off = align_up(off + sizeof(float) * (size_t)p.rows_pad * r);
-        p.off_t16 = off;       off = align_up(off + 2 * (size_t)p.rows_pad * ((r + 63) / 64 * 64));
+        p.off_t16 = off;       off = align_up(off + 2 * (size_t)p.rows_pad * ((r + 63) / 64 * 64) * (r <= kTwoPiecesMaxRank ? 2 : 1));
         p.off_stat = off;      off = align_up(off + 2 * sizeof(float) * (size_t)p.rows_pad * 2 * ((r + 63) / 64));
         p.down = make_down_grid(rows, p.rows_pad, d, r);
         p.off_down_part = off; off = align_up(off + sizeof(float) * 4096 * down_part_tiles_bound(rows, r));
@@ -415,6 +419,10 @@ inline bool rows_path_takes(HeadKind kind, int rows, int d, int r, int V, int k,
 
 inline bool tile_path_takes(int rows, int k) { return rows >= kMfmaMinRows && k <= kMfmaMaxK; }
 
+// What the many-row kernels multiply the weights with: the bf16 rows of the full head, or t log2(e) rounded to bf16, to f16, or to
+// two bf16 pieces (its sixteen leading bits).
+enum Operand : int { kOperandExact, kOperandBf16, kOperandF16, kOperandTwoBf16 };
+
 // The direct-to-LDS kernel takes bf16 operands as they are, or turns the weight tiles into f16 inside LDS and takes an f16
 // t (8 times finer).  The conversion costs the projection kernel about 12 %; the finer operand saves most of the merge's
 // exact re-evaluations, which grow with k: measured break-even at k = 10, 5-9 % of the call in favour of f16 at k = 16.
@@ -424,6 +432,15 @@ inline bool tile_operand_f16(int k, bool prepared) {
     return SLIMSPEC_DIAG_OPERAND_F16 != 0 && !prepared;
 #endif
     return k > 12 && !prepared;
+}
+// Ranks up to 64 (kTwoPiecesMaxRank) take two bf16 pieces instead of one: with so few terms the columns' norms differ from each other by
+// a tenth and more, the bound on one piece's error does not hold for all of them, and a row that finds out is evaluated exhaustively.
+// The second piece costs head_resident_kernel, whose contraction is padded to 128, nothing, and head_tile_kernel a stage or two.  (One
+// piece / two, us a call: 375 rows, d = 584, r = 40, V = 64120, prepared 206-289 / 34.7; 129 rows, r = 56, V = 151936, prepared 237.6 / 42.3;
+// 512 rows, d = 1024, r = 64, V = 128256 234.3 / 56.1; 100 rows, r = 24, V = 128256, prepared 241.9 / 31.5; 64 rows, r = 16, V = 8192 66.4 / 28.9,
+// 27.5 where no row finds out; 100 rows, r = 64, V = 32000 33.0 / 32.5.  From r = 72 on none of some 20 calls found out.)
+inline Operand tile_operand(int r, int k, bool prepared) {
+    return tile_operand_f16(k, prepared) ? kOperandF16 : r <= kTwoPiecesMaxRank ? kOperandTwoBf16 : kOperandBf16;
 }
 
 // head_resident_kernel instead of head_tile_kernel: bf16 operands, no noise.

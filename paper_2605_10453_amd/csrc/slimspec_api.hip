@@ -132,32 +132,32 @@ int run_head_mfma(HeadKind kind, const void *h, const void *A, const void *M, co
             void *t16 = ws + p.off_t16;
             float2 *stat = reinterpret_cast<float2 *>(ws + p.off_stat);
             float2 *tilescale = reinterpret_cast<float2 *>(ws + p.off_tilescale);
-            const bool tile_f16 = tile_operand_f16(k, Mtb != nullptr);
+            const Operand operand = tile_operand(r, k, Mtb != nullptr);
             e = launch_down_projection_tiles(hrow, static_cast<const uint16_t *>(A), reinterpret_cast<float *>(ws + p.off_down_part), p.down,
-                                             p.rows_pad, d, r, t32, t16, stat, Mb, V, tilescale, tile_f16, s);
+                                             p.rows_pad, d, r, t32, t16, stat, Mb, V, tilescale, operand, s);
             if (e != hipSuccess) return fail_hip(e);
             if (timed && (e = hipEventRecord(g_ev_start, s)) != hipSuccess) return fail_hip(e);
-            const bool resident = resident_takes(p, tile_f16, so.on != 0);
-            e = resident ? launch_head_resident(t16, Mb, streams, rows, p.rows_pad, r, V, p.res, s)
-                         : launch_head_tile(t16, tile_f16, false, Mb, streams, rows, p.rows_pad, r, V, p.n_rb, p.gw, so, row0, s);
+            const bool resident = resident_takes(p, operand == kOperandF16, so.on != 0);
+            e = resident ? launch_head_resident(t16, operand, Mb, streams, rows, p.rows_pad, r, V, p.res, s)
+                         : launch_head_tile(t16, operand, Mb, streams, rows, p.rows_pad, r, V, p.n_rb, p.gw, so, row0, s);
             if (e != hipSuccess) return fail_hip(e);
             if (timed && (e = hipEventRecord(g_ev_stop, s)) != hipSuccess) return fail_hip(e);
             if (head_tile_timing_only()) return SLIMSPEC_UNSUPPORTED;      // diagnostic build, timing-only kernel: no result
             // the records are in base-2 units (t was scaled by log2 e); f16 mode flushes weights below 2^-25 to zero
-            e = launch_merge_streams(streams, rows, resident ? p.res.nsr : p.nsr, resident ? p.res.gw : p.gw, p.n_vt, resident, t32, false, r, tile_f16 ? 2 : 1, Mb, r, V, Mtb, stat, 2 * ((r + 63) / 64), p.rows_pad, tilescale, k,
-                                     0.6931471805599453f, tile_f16 ? 2.9802322e-8f : 0.f, out_ids + (size_t)row0 * k, out_logprobs + (size_t)row0 * k, id_map,
-                                     (p.defer && merge_parks_rows(r, tile_f16)) ? ws + p.off_defer : nullptr, so, row0, s);
+            e = launch_merge_streams(streams, rows, resident ? p.res.nsr : p.nsr, resident ? p.res.gw : p.gw, p.n_vt, resident, t32, false, r, operand, Mb, r, V, Mtb, stat, 2 * ((r + 63) / 64), p.rows_pad, tilescale, k,
+                                     0.6931471805599453f, operand == kOperandF16 ? 2.9802322e-8f : 0.f, out_ids + (size_t)row0 * k, out_logprobs + (size_t)row0 * k, id_map,
+                                     (p.defer && merge_parks_rows(r, operand == kOperandF16)) ? ws + p.off_defer : nullptr, so, row0, s);
             if (e != hipSuccess) return fail_hip(e);
         } else {
             // the full head runs the same kernel on h itself (bf16 exact, natural units): no rounding statistics
             void *hx = ws + p.off_t16;
             if ((e = launch_regroup_rows(hrow, hx, rows, p.rows_pad, d, s)) != hipSuccess) return fail_hip(e);
             if (timed && (e = hipEventRecord(g_ev_start, s)) != hipSuccess) return fail_hip(e);
-            e = launch_head_tile(hx, false, true, Mb, streams, rows, p.rows_pad, d, V, p.n_rb, p.gw, so, row0, s);
+            e = launch_head_tile(hx, kOperandExact, Mb, streams, rows, p.rows_pad, d, V, p.n_rb, p.gw, so, row0, s);
             if (e != hipSuccess) return fail_hip(e);
             if (timed && (e = hipEventRecord(g_ev_stop, s)) != hipSuccess) return fail_hip(e);
             if (head_tile_timing_only()) return SLIMSPEC_UNSUPPORTED;
-            e = launch_merge_streams(streams, rows, p.nsr, p.gw, p.n_vt, false, hrow, true, d, 0, Mb, d, V, Mtb, nullptr, 0, 0, nullptr, k,
+            e = launch_merge_streams(streams, rows, p.nsr, p.gw, p.n_vt, false, hrow, true, d, kOperandExact, Mb, d, V, Mtb, nullptr, 0, 0, nullptr, k,
                                      1.0f, 0.f, out_ids + (size_t)row0 * k, out_logprobs + (size_t)row0 * k, id_map,
                                      (p.defer && merge_parks_rows(d, true)) ? ws + p.off_defer : nullptr, so, row0, s);
             if (e != hipSuccess) return fail_hip(e);

@@ -43,3 +43,19 @@ def test_four_best_logits_in_one_stream(gpu, oracle_mod, rows, V):
     g_ids, _, _, _ = check_low_rank(gpu, oracle_mod, x, cfg.k, exact_rows=list(planted))
     for i, cols in planted.items():
         assert g_ids[i, :4].tolist() == cols, (i, g_ids[i], cols)
+
+
+# ranks around the two pieces' strides of 16, 32 and 64 elements and the first rank beyond them, for both kernels
+@pytest.mark.parametrize("rows,kernel", [(60, "tile"), (140, "resident")])
+@pytest.mark.parametrize("r,V", [(8, 520), (16, 2056), (24, 4104), (32, 9000), (40, 8200), (64, 70000), (72, 8200)])
+def test_ranks_in_two_pieces(gpu, oracle_mod, rows, kernel, r, V):
+    """Ranks up to 64 multiply the sixteen leading bits of t.  What is left of its rounding moves a logit by at most
+    2^-17 sum_j |t_j B[j, v]|, which is below 2^-17 sqrt(r) 18 < 1.1e-3 for logits of up to 18 whose terms do not cancel by more than
+    sqrt(r); the winners' own values are exact or within 1.2e-5 of the largest logit.  One piece (r = 72) keeps the bar of 2e-2."""
+    assert_plan("low", rows, 64, r, V, 7, kernel=kernel, f16=0)
+    x = synth.make_inputs(synth.small_config(rows, 64, r, V, 7, peaked_every=3), seed=5 * r + rows)
+    _, g_lp, ora, _ = check_low_rank(gpu, oracle_mod, x, 7)
+    if r <= 64:
+        err = np.abs(g_lp - ora.logprobs).max()
+        print(f"r={r} rows={rows} largest error {err:.2e}", flush=True)
+        assert err <= 1.1e-3, err
