@@ -53,11 +53,75 @@ __global__ __launch_bounds__(256) void widen_rows_kernel(
 // SRC: what x is.  kSlices: nds partial sums of the contraction input, [nds][R][K] fp32 (down_items_kernel's); four
 // adjacent lanes add a quarter of the slices each.  kHalfRows: the bf16 rows themselves, [rows_here][K] (full head).  Both
 // are put into shared memory.  kGlobal: fp32 [R][K], read from memory (rows too long for that; k_parts is 1).
-enum { kGlobal = 0, kSlices = 1, kHalfRows = 2 };
+// kOwn: one row, x_src is h [d], nds is d, and every block makes t = h A itself from A [d, K]: a launch less for what the block waits longer, at
+// most a few trips to the L2 (plan.hpp: own_input_takes).
+enum { kGlobal = 0, kSlices = 1, kHalfRows = 2, kOwn = 3 };
+
+// t = h A of one row into xs (shared memory), by the whole block: 64 columns at a time, a thread 8 of them in every
+// `slots`-th row, `then` (the weights' first loads) behind the last of A's.
+template <int NT, class Then>
+__device__ __forceinline__ void own_input(const uint16_t *__restrict__ h, const uint16_t *__restrict__ A, float (*redd)[kItemCols],
+                                          float *xs, int d, int r, int tid, Then then)
+{
+    constexpr int NW = NT / 64, U = 8;
+    const int lane = tid & 63, wave = tid >> 6;
+    const int pl = r > 32 ? 3 : r > 16 ? 2 : r > 8 ? 1 : 0;     // 2^pl adjacent threads cover a row's columns (64 of them at most)
+    const int piece = tid & ((1 << pl) - 1), slot = tid >> pl, slots = NT >> pl;
+    for (int c0 = 0; c0 < r; c0 += kItemCols) {
+        const int col = c0 + piece * 8;
+        float acc[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[e] = 0.f;
+        for (int j0 = 0; j0 < d; j0 += U * slots) {
+            const int j = j0 + slot;
+            uint4 w[U];
+            uint16_t hv[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (j0 + u * slots >= d) break;                // (the same for the whole block)
+                const int row = min(j + u * slots, d - 1);
+                w[u] = *reinterpret_cast<const uint4 *>(A + (size_t)row * r + min(col, r - 8));
+                hv[u] = h[row];
+            }
+            if (c0 + kItemCols >= r && j0 + U * slots >= d) then();
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (j + u * slots >= d) continue;
+                const float f[8] = {bf16_lo(w[u].x), bf16_hi(w[u].x), bf16_lo(w[u].y), bf16_hi(w[u].y),
+                                    bf16_lo(w[u].z), bf16_hi(w[u].z), bf16_lo(w[u].w), bf16_hi(w[u].w)};
+#pragma unroll
+                for (int e = 0; e < 8; ++e) acc[e] = fmaf(bf16_to_float(hv[u]), f[e], acc[e]);
+            }
+        }
+        // the lanes that hold the same columns
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            float v = acc[e];
+            if (pl < 1) v += dpp_f32<0xB1>(v);
+            if (pl < 2) v += dpp_f32<0x4E>(v);
+            if (pl < 3) v += dpp_f32<0x141>(dpp_f32<0x1B>(v));  // lane ^ 4
+            v += dpp_f32<0x128>(v);                             // lane ^ 8
+            uint32_t a, b;
+            swap_pair<16>(__float_as_uint(v), a, b);
+            v = __uint_as_float(a) + __uint_as_float(b);
+            swap_pair<32>(__float_as_uint(v), a, b);
+            v = __uint_as_float(a) + __uint_as_float(b);
+            if (lane < (1 << pl)) redd[wave][lane * 8 + e] = v;
+        }
+        __syncthreads();
+        if (tid < kItemCols && c0 + tid < r) {
+            float s = 0.f;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) s += redd[w][tid];     // fixed order
+            xs[c0 + tid] = s;
+        }
+        if (c0 + kItemCols < r) __syncthreads();
+    }
+}
 
 template <int R, int NW, typename WT, int SRC>
 __global__ __launch_bounds__(NW * 64) void stream_topk_kernel(
-    const void *__restrict__ x_src, int nds, const WT *__restrict__ M,
+    const void *__restrict__ x_src, int nds, const uint16_t *__restrict__ A, const WT *__restrict__ M,
     float2 *__restrict__ part_ms, float *__restrict__ part_val, int *__restrict__ part_id,
     int rows_here, int row0, int K, int V, int chunks, int lanes, int k_parts, StreamParts sp, int k,
     float4 *__restrict__ part_smp, uint32_t seed_lo, uint32_t seed_hi)
@@ -115,7 +179,10 @@ __global__ __launch_bounds__(NW * 64) void stream_topk_kernel(
                 for (int u = 0; u < 8; ++u) q[8 * g8 + u] = load_raw8(M + (size_t)(j0 + g8 * step + u) * V + o);
             }
         };
-        if constexpr (SRC == kSlices) {
+        if constexpr (SRC == kOwn) {
+            __shared__ float redd[NW][kItemCols];
+            own_input<NT>(static_cast<const uint16_t *>(x_src), A, redd, reinterpret_cast<float *>(xs_raw), nds, K, tid, load_first);
+        } else if constexpr (SRC == kSlices) {
             const float4 *x = static_cast<const float4 *>(x_src);
             float4 *xs = reinterpret_cast<float4 *>(xs_raw);
             const uint32_t n4 = (uint32_t)(R * K) / 4u, sg = tid & 3u, last = (uint32_t)nds - 1u;
@@ -166,7 +233,7 @@ __global__ __launch_bounds__(NW * 64) void stream_topk_kernel(
             float xv[R][8];
 #pragma unroll
             for (int i = 0; i < R; ++i) {
-                if constexpr (SRC == kSlices) {
+                if constexpr (SRC != kHalfRows) {
                     const float4 *p = reinterpret_cast<const float4 *>(xs_raw) + (i * K + j) / 4 + 2 * kp;
                     const float4 a = p[0], b = p[1];
                     xv[i][0] = a.x; xv[i][1] = a.y; xv[i][2] = a.z; xv[i][3] = a.w;
@@ -312,19 +379,22 @@ struct StreamCall {
     ChunkGeom g;
     int k;
     float4 *smp; uint32_t seed_lo, seed_hi;
+    const uint16_t *A = nullptr;
 };
+
+constexpr int stream_x_bytes(int src) { return src == kGlobal ? 0 : src == kHalfRows ? 2 : 4; }     // of an element of x in shared memory
 
 template <int R, int NW, typename WT, int SRC>
 static hipError_t launch_stream(const StreamCall<WT> &c, hipStream_t st)
 {
     const int per_xcd = (c.g.chunks + 7) / 8, k_parts = SRC == kGlobal ? 1 : c.g.k_parts;
-    const size_t dyn = stream_lds_bytes(R, NW, c.g, c.K, SRC == kGlobal ? 0 : SRC == kSlices ? 4 : 2);
+    const size_t dyn = stream_lds_bytes(R, NW, c.g, c.K, stream_x_bytes(SRC));
     if (dyn > 32 * 1024) {
         static LdsLimit lds_limit;
         const hipError_t e = lds_limit.raise(reinterpret_cast<const void *>(stream_topk_kernel<R, NW, WT, SRC>), (int)dyn);
         if (e != hipSuccess) return e;
     }
-    stream_topk_kernel<R, NW, WT, SRC><<<8 * per_xcd, NW * 64, dyn, st>>>(c.x, c.nds, c.M, c.ms, c.pv, c.pi, c.rows_here, c.row0, c.K, c.V, c.g.chunks,
+    stream_topk_kernel<R, NW, WT, SRC><<<8 * per_xcd, NW * 64, dyn, st>>>(c.x, c.nds, c.A, c.M, c.ms, c.pv, c.pi, c.rows_here, c.row0, c.K, c.V, c.g.chunks,
                                                                           c.g.lanes, k_parts, stream_parts(NW, k_parts, c.K), c.k, c.smp, c.seed_lo, c.seed_hi);
     return hipGetLastError();
 }
@@ -334,16 +404,20 @@ static hipError_t launch_stream_rows(const StreamCall<WT> &c, hipStream_t st)
 {
     // One row: the block size the chunk geometry asks for.  More rows: as many wavefronts as the shared memory of
     // the partial sums (NW * R * 2 KB) allows; they split the contraction, and every one of them keeps loads in flight.
-    const auto fits = [&](int R, int NW) { return stream_lds_bytes(R, NW, c.g, c.K, SRC == kGlobal ? 0 : SRC == kSlices ? 4 : 2) <= kStreamLdsLimit; };
+    const auto fits = [&](int R, int NW) { return stream_lds_bytes(R, NW, c.g, c.K, stream_x_bytes(SRC)) <= kStreamLdsLimit; };
     if (c.rows_here <= 1) {
-        if (c.g.nw1 == 16 && fits(1, 16)) return launch_stream<1, 16, WT, SRC>(c, st);
+        if constexpr (SRC != kOwn)                      // (its rule leaves blocks of 1024 threads out: they lack the registers)
+            if (c.g.nw1 == 16 && fits(1, 16)) return launch_stream<1, 16, WT, SRC>(c, st);
         if (c.g.nw1 >= 8 && fits(1, 8)) return launch_stream<1, 8, WT, SRC>(c, st);
         return launch_stream<1, 4, WT, SRC>(c, st);
     }
+    if constexpr (SRC == kOwn) return hipErrorInvalidValue;      // (a single row's)
+    else {
     if (c.rows_here <= 2)
         return fits(2, 16) ? launch_stream<2, 16, WT, SRC>(c, st) : fits(2, 8) ? launch_stream<2, 8, WT, SRC>(c, st) : launch_stream<2, 4, WT, SRC>(c, st);
     if (c.rows_here <= 4) return fits(4, 8) ? launch_stream<4, 8, WT, SRC>(c, st) : launch_stream<4, 4, WT, SRC>(c, st);
     return fits(8, 4) ? launch_stream<8, 4, WT, SRC>(c, st) : launch_stream<8, 2, WT, SRC>(c, st);
+    }
 }
 
 template <typename WT>
@@ -366,6 +440,12 @@ hipError_t launch_stream_topk(const void *x, int nds, float *wide, const void *M
     if (m_is_f32)
         return launch_stream_src<float>({x, nds, static_cast<const float *>(M), ms, pv, pi, rows_here, row0, K, V, g, k, smp, seed_lo, seed_hi}, wide, st);
     return launch_stream_src<uint16_t>({x, nds, static_cast<const uint16_t *>(M), ms, pv, pi, rows_here, row0, K, V, g, k, smp, seed_lo, seed_hi}, wide, st);
+}
+
+hipError_t launch_stream_topk_own_input(const uint16_t *h, const uint16_t *A, int d, const uint16_t *M, float2 *ms, float *pv, int *pi,
+                                        int K, int V, const ChunkGeom &g, int k, float4 *smp, uint32_t seed_lo, uint32_t seed_hi, hipStream_t st)
+{
+    return launch_stream_rows<uint16_t, kOwn>({h, d, M, ms, pv, pi, 1, 0, K, V, g, k, smp, seed_lo, seed_hi, A}, st);
 }
 
 }  // namespace slimspec

@@ -43,6 +43,9 @@ hipError_t launch_stream_topk(const void *x, int nds, float *wide, const void *M
                               float2 *part_ms, float *part_val, int *part_id,
                               int rows_here, int row0, int K, int V, const ChunkGeom &g, int k,
                               float4 *part_smp, uint32_t seed_lo, uint32_t seed_hi, hipStream_t st);
+// The same for a single row of the low-rank head, its down-projection included: x = h [d], A [d, K] (plan.hpp: own_input_takes).
+hipError_t launch_stream_topk_own_input(const uint16_t *h, const uint16_t *A, int d, const uint16_t *M, float2 *part_ms, float *part_val, int *part_id,
+                                        int K, int V, const ChunkGeom &g, int k, float4 *part_smp, uint32_t seed_lo, uint32_t seed_hi, hipStream_t st);
 
 // Combine the partials of every row into the final ids and log-probabilities.
 // Outputs of stochastic decoding (on: asked for): the noise seed, and per row the log-sum-exp over the vocabulary

@@ -98,6 +98,15 @@ inline ChunkGeom make_chunk_geom(HeadKind kind, int rows, int K, int V) {
     return g;
 }
 
+// A single row whose A is so small (64 KB) that every block of the streaming kernel makes all of t itself: one launch less.  Two launches
+// / one, us a call: d = 256, r = 32, V = 8192 13.1 / 9.5; d = 512, r = 64, V = 8192 14.1 / 13.1, V = 50000 13.7 / 11.9, V = 128256 13.8 / 12.9; d = 4096, r = 8,
+// V = 8192 13.4 / 10.6; d = 256, r = 128, V = 8192 13.7 / 11.5; d = 336, r = 96, V = 60000, sampling 20.5 / 16.5.  Not with twice as much (d = 1024, r = 64, V = 16384
+// 12.4 / 12.7, d = 512, r = 128, V = 50000 13.2 / 13.9), not where a CU has several blocks that read A (d = 512, r = 64, V = 151936 15.2 / 16.8), and not in
+// blocks of 16 wavefronts, whose registers the weights and A do not share (d = 256, r = 128, V = 128256 16.8 / 25.5).
+inline bool own_input_takes(const ChunkGeom &g, int rows, int d, int r, int V) {
+    return rows == 1 && r <= 128 && (int64_t)d * r <= 32768 && V <= 256 * kChunkCols && g.nw1 <= 8;
+}
+
 struct Plan {
     bool ok = false;
     int rows = 0, d = 0, r = 0, V = 0, k = 0;

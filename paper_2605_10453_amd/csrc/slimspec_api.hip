@@ -248,7 +248,18 @@ int run_head(HeadKind kind, const void *h, const void *A, const void *M, bool m_
     // scratch in stream order; one merge launch serves all rows.
     const DownPlan dp = make_down_plan(kind == HeadKind::LowRank, p.d, p.r);
     float *tpart = reinterpret_cast<float *>(ws + p.off_tpart);
-    for (int row0 = 0; row0 < p.rows; row0 += kGemvMaxRows) {
+    const bool own = kind == HeadKind::LowRank && own_input_takes(p.geom, p.rows, p.d, p.r, p.V);
+    if (own) {
+        const bool timed = g_ev_start != nullptr;
+        hipError_t e;
+        if (timed && (e = hipEventRecord(g_ev_start, s)) != hipSuccess) return fail_hip(e);
+        const uint16_t *A0 = static_cast<const uint16_t *>(A) + (size_t)(pos.n > 0 ? position_of_row(pos, 0) : 0) * p.d * p.r;
+        e = launch_stream_topk_own_input(hb, A0, p.d, static_cast<const uint16_t *>(M), part_ms, part_val, part_id, p.K, p.V, p.geom, k,
+                                         part_smp, so.seed_lo, so.seed_hi, s);
+        if (e != hipSuccess) return fail_hip(e);
+        if (timed && (e = hipEventRecord(g_ev_stop, s)) != hipSuccess) return fail_hip(e);
+    }
+    for (int row0 = 0; !own && row0 < p.rows; row0 += kGemvMaxRows) {
         const int rows_here = (p.rows - row0 < kGemvMaxRows) ? p.rows - row0 : kGemvMaxRows;
         hipError_t e;
         if (kind == HeadKind::LowRank) {

@@ -50,3 +50,27 @@ def test_full_head(gpu, oracle_mod, rows, d, V, k, fp32):
     ora = oracle_mod.full_head_topk(x.h, W, k)
     z_at = lambda ri, ci: oracle_mod.full_logits_at(x.h, W, ri, ci)
     compare_with_oracle(ids.cpu().numpy(), lp.cpu().numpy(), ora.ids, ora.lse, z_at, V, tie_tol=FP32_TOL, lp_tol=FP32_TOL)
+
+
+# one row whose A every block reads: ranks of 1, 2, 4 and 8 pieces per row of A and of two column blocks, hidden sizes below, at and off
+# the rows that a block takes per step, the rule's limits in d r, V and wavefronts, and the first shapes beyond them
+@pytest.mark.parametrize("d,r,V,k,own", [
+    (8, 8, 8, 2, 1), (4096, 8, 4104, 5, 1), (2048, 16, 8192, 64, 1), (1000, 24, 520, 7, 1), (1024, 32, 131072, 10, 1), (816, 40, 33000, 3, 1),
+    (512, 64, 8200, 12, 1), (256, 72, 16384, 33, 1), (272, 120, 9000, 4, 1), (256, 128, 40008, 9, 1), (520, 64, 2056, 5, 0), (16, 136, 1032, 5, 0),
+    (64, 16, 131080, 5, 0), (64, 128, 131072, 5, 0),
+])
+def test_input_made_by_every_block(gpu, oracle_mod, d, r, V, k, own):
+    torch, b = gpu
+    print(f"stream kernel, one row: d={d} r={r} V={V} k={k}", flush=True)
+    assert_plan("low", 1, d, r, V, k, kernel="stream", own_input=own)
+    x = synth.make_inputs(synth.small_config(1, d, r, V, k), seed=d + r)
+    z_at = lambda ri, ci: oracle_mod.slimspec_logits_at(x.h, x.A, x.B, ri, ci)
+    h, B = to_dev_bf16(x.h), to_dev_bf16(x.B)
+    stack = to_dev_bf16(np.concatenate([x.A[::-1], x.A, x.A[::-1]])).view(3, d, r)      # the second of three positions has the row
+    outs = [b.slimspec_head_topk(h, stack[1], B, k), b.slimspec_head_topk_positions(h, stack, [0, 0, 1, 1], B, k),
+            b.slimspec_head_sample(h, stack[1], B, k, 5)]
+    torch.cuda.synchronize()
+    ora = oracle_mod.head_sample(x.h, x.A, x.B, k, 5)
+    for out in outs:
+        compare_with_oracle(out[0].cpu().numpy(), out[1].cpu().numpy(), ora.ids, ora.lse, z_at, V, tie_tol=FP32_TOL, lp_tol=FP32_TOL)
+    assert int(outs[2][3][0]) == ora.sample_ids[0]
