@@ -179,7 +179,7 @@ __global__ __launch_bounds__(kMergeThreads) void merge_streams_kernel(
     float *ts = w_eps + kWorkCap;                                       // [min(n_vt, kTsCap)]  column scale of B per vocabulary tile
     const bool ts_cached = n_vt <= kTsCap;                              // a larger vocabulary uses the largest scale for every tile
     float *xrow = ts + ((min(n_vt, kTsCap) + 3) & ~3);                  // [K]            the row's exact contraction input
-    float *xrow16 = xrow + K;                                           // [K]            ... as the head kernel had it (operand not exact)
+    float *xrow16 = operand != kOperandExact ? xrow + K : xrow;         // [K]            ... as the head kernel had it
     __shared__ float red_m[NWAVES], red_s[NWAVES];
     __shared__ uint64_t tau_key;
     __shared__ uint32_t cnt_work, cnt_hidden, cnt_need;
@@ -1125,7 +1125,8 @@ hipError_t launch_merge_streams(const float *part, int rows, int nsr, int gw, in
                                 float unit, float tiny_w, int32_t *out_ids, float *out_logprobs, const int32_t *id_map,
                                 void *defer_buf, const SampleOut &so, int row_base, hipStream_t st)
 {
-    const size_t lds = merge_streams_lds_bytes(nsr, n_vt) + 2 * sizeof(float) * (size_t)K;   // + the row's contraction input, exact and as rounded
+    // + the row's contraction input, exact and, where it was rounded, as rounded
+    const size_t lds = merge_streams_lds_bytes(nsr, n_vt) + (operand != kOperandExact ? 2 : 1) * sizeof(float) * (size_t)K;
     static LdsLimit lds_limit;
     hipError_t e = lds_limit.raise(reinterpret_cast<const void *>(merge_streams_kernel), (int)lds);
     if (e != hipSuccess) return e;
