@@ -207,15 +207,15 @@ __device__ __forceinline__ uint32_t wave_sort_desc(uint32_t v, int lane) {
 //     n = x >> 9,  u = (2 n + 1) / 2^24,  E = -ln(1 - u) ~ Exp(1),  g = -ln E
 // The draws that decide a sample are the large ones, i.e. small E = small u: there E comes from the series of
 // -ln(1 - u) (the hardware logarithm of a number next to 1 would lose them); elsewhere 1 - u is exact in fp32.
+constexpr uint32_t kGumbelIdStep = 0x9E3779B1u, kGumbelRowStep = 0x85EBCA77u;
 struct GumbelKey { uint32_t row_term, hi_term; };      // row * 0x85EBCA77 + seed_lo,  seed_hi * 0xC2B2AE3D
 __device__ __forceinline__ GumbelKey gumbel_key(uint32_t seed_lo, uint32_t seed_hi, uint32_t row) {
-    return {row * 0x85EBCA77u + seed_lo, seed_hi * 0xC2B2AE3Du};
+    return {row * kGumbelRowStep + seed_lo, seed_hi * 0xC2B2AE3Du};
 }
 __device__ __forceinline__ uint32_t mix32(uint32_t x) {
     x ^= x >> 16; x *= 0x21F0AAADu; x ^= x >> 15; x *= 0x735A2D97u; x ^= x >> 15;
     return x;
 }
-constexpr uint32_t kGumbelIdStep = 0x9E3779B1u;
 __device__ __forceinline__ uint32_t gumbel_bits(uint32_t id_row_term, uint32_t hi_term) { return mix32(mix32(id_row_term) + hi_term); }
 // g / ln 2 (the noise in base-2 units: add it to a logit times log2 e)
 __device__ __forceinline__ float gumbel_base2(const GumbelKey &key, uint32_t id) {

@@ -19,6 +19,10 @@
 // slots (1200 cycles without loads and barriers), the loads into LDS (900) and the barriers (300).  12000 cycles pass
 // before the first MFMA: 256 KB of row operand per CU at the 30 bytes per cycle a CU takes in.
 //
+// Sampling: the draw's bounds are 22 vector instructions per logit, more than all the rest, and run between the MFMAs too: 512 rows, r = 512
+// 108 us by the profiler, 154 in head_tile_kernel with the noise itself; calls 222.2 (there; 182 with bounds) -> 159.1 us, 300 rows, r = 256,
+// prepared 152.2 -> 100.5.
+//
 // Weights: stages of 128 contraction elements x 64 columns (16 KB) travel global memory -> LDS without passing registers
 // (global_load_lds_dwordx4), eight stage buffers.  The 16-byte pieces of a 128-byte stage row are stored XOR-swizzled by
 // twice (row mod 4), so that the four rows of a transposing read (ds_read_b64_tr_b16) fall into different banks.
@@ -45,7 +49,8 @@ constexpr uint32_t kRStageBytes = kRStageK * kRTile * 2;  // 16 KB
 constexpr int kRNB = 8;                                   // stage buffers
 constexpr int kRLoads = 2;                                // loads per wavefront and stage, 8 stage rows each
 constexpr int kAhead = 1;                                 // contraction steps that weight fragments are read ahead
-constexpr int kSlots = 64;                                // slots of a tile's epilogue: 32 for each of 2 MFMA tiles
+constexpr int kSlots = 32;                                // slots of an MFMA tile's epilogue
+constexpr int kSampleSlots = 32;                          // ... and of its noise: two for each of its 16 elements
 
 template <int OFF>
 __device__ __forceinline__ void dma16(uint32_t buf, uint32_t voff, const void *base) {
@@ -72,12 +77,14 @@ constexpr float kNoMax = -1.0e30f;                        // a reference for a s
 // part: [rows][gw * 2] records as head_tile_kernel writes them, one per half-wavefront.
 // KS: contraction steps of 16, ceil(K / 128) * 8.  split (16, 32 or 64, at least K; 0: one piece): X holds two pieces of
 // every element, [2][split / 8][rows_pad].
-template <int KS>
+// SAMPLE: the records also carry what the Gumbel-max draw needs (head_stream.hpp; the second group's y is folded into the bound of
+// all others): 20 floats.
+template <int KS, bool SAMPLE>
 __global__ __launch_bounds__(512, 2) void head_resident_kernel(
     const uint4 *__restrict__ X, const uint16_t *__restrict__ M, float *__restrict__ part,
-    int rows, int rows_pad, int K, int V, int split, ResidentGrid hg)
+    int rows, int rows_pad, int K, int V, int split, ResidentGrid hg, uint32_t seed_lo, uint32_t seed_hi, int row_base)
 {
-    constexpr int L = kStreamList, REC = kStreamRec;
+    constexpr int L = kStreamList, REC = SAMPLE ? kStreamRecSample : kStreamRec;
     constexpr int SPT = KS / 8;                           // stages per tile
     constexpr int SYNC = SPT % 2 == 0 ? 2 : 1;            // stages per barrier (two: 70.5 -> 68.6 us at 512 rows)
     extern __shared__ __align__(1024) unsigned char lds_raw[];
@@ -93,6 +100,11 @@ __global__ __launch_bounds__(512, 2) void head_resident_kernel(
 
     Stream<L> st;
     stream_init(st);
+    // the draw's bounds: largest group (x, second largest y), second largest group (x), all others; the two groups' names, 2 (tile - col) / gw
+    // + MFMA tile, as 16 bits each (V <= kResidentMaxV)
+    static_assert(2 * ((kResidentMaxV / kResidentTileCols + 7) / 8) <= 1 << 16, "a group's name fits 16 bits");
+    float smp_x = kNegBig, smp_y = kNegBig, smp_x2 = kNegBig, smp_rest = kNegBig;
+    uint32_t smp_tags = 0u;
 
     if (n_tiles > 0) {
         // ---- direct-to-LDS loads.  Load u of this wavefront: stage rows 16 wave + 8 u + lane / 8; stored piece lane % 8
@@ -180,9 +192,11 @@ __global__ __launch_bounds__(512, 2) void head_resident_kernel(
         f32x16 acc[2][2];                                 // [tile parity][jj]
         float p[3], h5[5], l5[5], ha = 0.f, hb = 0.f, la = 0.f, gr = 0.f, g2 = 0.f, e0 = 0.f;
         int tg = 0;
-        const auto epilogue_slot = [&](auto u_tag, f32x16 (&a)[2], int tile) {
-            constexpr int U = decltype(u_tag)::value, jj = U >> 5, at = U & 31;
-            constexpr int w = at < 20 ? at : at < 24 ? -1 : at - 4;      // 20 .. 23: free
+        uint32_t hx = 0u, id_row = 0u;                    // (sampling)
+        constexpr int SLOTS = kSlots + (SAMPLE ? kSampleSlots : 0);
+        const auto epilogue_slot = [&](auto u_tag, f32x16 (&a)[2], int tile, int nth) {
+            constexpr int U = decltype(u_tag)::value, jj = U / SLOTS, at = U % SLOTS;
+            constexpr int w = at < 20 ? at : at < 24 ? -1 : at < kSlots ? at - 4 : -1;      // 20 .. 23: free
             Stream<L> &q = st;
             const f32x16 &v = a[jj];
 #define SLIMSPEC_PIN(x) asm volatile("" : "+v"(x))
@@ -227,6 +241,37 @@ __global__ __launch_bounds__(512, 2) void head_resident_kernel(
             } else if constexpr (w == 25) level(0);
             else if constexpr (w == 26) level(1);
             else if constexpr (w == 27) { level(2); q.U = vmax(q.U, gr); SLIMSPEC_PIN(q.U); }
+            if constexpr (at >= kSlots) {                 // the draw, behind the rest: element i in two slots; gr and g2 are the group's best two here
+                constexpr int i = (at - kSlots) >> 1;
+                const uint32_t hi_term = seed_hi * 0xC2B2AE3Du;
+                if constexpr (((at - kSlots) & 1) == 0) {
+                    if constexpr (i == 0) {
+                        const uint32_t ln = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));      // (recomputed: a register less)
+                        id_row = (uint32_t)(tile * kRTile + 32 * jj) * kGumbelIdStep + (ln >> 5) * (4u * kGumbelIdStep)
+                                 + gumbel_key(seed_lo, seed_hi, (uint32_t)(row_base + row0)).row_term + (ln & 31) * kGumbelRowStep;
+                        SLIMSPEC_PIN(id_row);
+                    }
+                    hx = mix32(id_row + (uint32_t)(8 * (i >> 2) + (i & 3)) * kGumbelIdStep) + hi_term;
+                    SLIMSPEC_PIN(hx);
+                } else {
+                    const float b = fmaf(gumbel_bound_bits(mix32(hx)), -kGumbelBoundScale, v[i]);
+                    const float p = __uint_as_float((__float_as_uint(b) & 0xfffffff0u) | (uint32_t)i);
+                    if constexpr (i == 0) { gr = p; g2 = kNegBig; }
+                    else { g2 = vmed3(gr, g2, p); gr = vmax(gr, p); }
+                    SLIMSPEC_PIN(gr); SLIMSPEC_PIN(g2);
+                }
+                if constexpr (at == SLOTS - 1) {
+                    float x = __uint_as_float((__float_as_uint(gr + kGumbelBoundBase) & 0xfffffff0u) | (__float_as_uint(gr) & 15u));
+                    float y = g2 + kGumbelBoundBase;
+                    const bool c1 = x > smp_x, c2 = x > smp_x2;
+                    smp_rest = vmax(smp_rest, c1 ? vmax(smp_x2, smp_y) : vmax(y, c2 ? smp_x2 : x));
+                    smp_tags = c1 ? smp_tags << 16 | (uint32_t)(2 * nth + jj) : c2 ? (smp_tags & 0xffffu) | (uint32_t)(2 * nth + jj) << 16 : smp_tags;
+                    smp_x2 = c1 ? smp_x : c2 ? x : smp_x2;
+                    smp_y = c1 ? y : smp_y;
+                    smp_x = c1 ? x : smp_x;
+                    SLIMSPEC_PIN(smp_rest); SLIMSPEC_PIN(smp_tags); SLIMSPEC_PIN(smp_x2); SLIMSPEC_PIN(smp_y); SLIMSPEC_PIN(smp_x);
+                }
+            }
 #undef SLIMSPEC_PIN
         };
         const auto mask_tail = [&](f32x16 (&a)[2], int tile) {
@@ -251,7 +296,8 @@ __global__ __launch_bounds__(512, 2) void head_resident_kernel(
         set_frag_addr();
         static_for<0, kAhead>([&](auto k_tag) { static_for<0, 4>([&](auto part_tag) { read_frag(frag_addr, k_tag, k_tag, part_tag); }); });
         // One tile: its MFMAs, and between them the epilogue of the tile before (EPI)
-        const auto do_tile = [&](auto par_tag, auto epi_tag, int tile) {
+        const auto do_tile = [&](auto par_tag, auto epi_tag, int nth) {
+            const int tile = col + nth * hg.gw;
             constexpr int P = decltype(par_tag)::value;
             constexpr bool EPI = decltype(epi_tag)::value != 0;
             const int prev = tile - hg.gw;
@@ -288,26 +334,26 @@ __global__ __launch_bounds__(512, 2) void head_resident_kernel(
                 // (after the last stage: a buffer loaded again, unused)
                 read_frag(frag_addr, Int<(ks + kAhead) & 7>{}, Int<(k + kAhead) % (kAhead + 1)>{}, Int<2 * jj>{});
                 read_frag(frag_addr, Int<(ks + kAhead) & 7>{}, Int<(k + kAhead) % (kAhead + 1)>{}, Int<2 * jj + 1>{});
-                if constexpr (EPI) static_for<n * kSlots / (2 * KS), (n + 1) * kSlots / (2 * KS)>([&](auto u_tag) { epilogue_slot(u_tag, acc[1 - P], prev); });
+                if constexpr (EPI) static_for<n * SLOTS / KS, (n + 1) * SLOTS / KS>([&](auto u_tag) { epilogue_slot(u_tag, acc[1 - P], prev, nth - 1); });
                 __builtin_amdgcn_sched_barrier(0);
             });
         };
-        const auto drain = [&](auto par_tag, int tile) {
+        const auto drain = [&](auto par_tag, int nth) {
             constexpr int P = decltype(par_tag)::value;
-            mask_tail(acc[P], tile);
-            static_for<0, kSlots>([&](auto u_tag) { epilogue_slot(u_tag, acc[P], tile); });
+            mask_tail(acc[P], col + nth * hg.gw);
+            static_for<0, 2 * SLOTS>([&](auto u_tag) { epilogue_slot(u_tag, acc[P], col + nth * hg.gw, nth); });
         };
-        do_tile(Int<0>{}, Int<0>{}, col);
+        do_tile(Int<0>{}, Int<0>{}, 0);
         int i = 1;
         for (; i + 1 < n_tiles; i += 2) {
-            do_tile(Int<1>{}, Int<1>{}, col + i * hg.gw);            // with it, the epilogue of tile i - 1 is done
-            do_tile(Int<0>{}, Int<1>{}, col + (i + 1) * hg.gw);
+            do_tile(Int<1>{}, Int<1>{}, i);                          // with it, the epilogue of tile i - 1 is done
+            do_tile(Int<0>{}, Int<1>{}, i + 1);
         }
         if (i < n_tiles) {
-            do_tile(Int<1>{}, Int<1>{}, col + i * hg.gw);
-            drain(Int<1>{}, col + i * hg.gw);
+            do_tile(Int<1>{}, Int<1>{}, i);
+            drain(Int<1>{}, i);
         } else
-            drain(Int<0>{}, col + (n_tiles - 1) * hg.gw);
+            drain(Int<0>{}, n_tiles - 1);
         wait_loads<0>();                                  // the surplus loads of the last stages
     }
 
@@ -321,6 +367,10 @@ __global__ __launch_bounds__(512, 2) void head_resident_kernel(
         o[0] = st.mc; o[1] = st.s; o[2] = st.U;
 #pragma unroll
         for (int l = 0; l < L; ++l) { o[3 + 3 * l] = st.x[l]; o[4 + 3 * l] = st.y[l]; o[5 + 3 * l] = __int_as_float(st.tag[l] * 2 + half); }
+        if constexpr (SAMPLE) {
+            const auto name = [&](uint32_t t) { return ((col + (int)(t >> 1) * hg.gw) * 2 + (int)(t & 1u)) * 2 + half; };
+            sample_store(o + kStreamRec, {{smp_x, smp_x2}, {smp_y, kNegBig}, smp_rest, {name(smp_tags & 0xffffu), name(smp_tags >> 16)}});
+        }
     }
     lds_wave_sync();
 #pragma unroll
@@ -332,26 +382,30 @@ __global__ __launch_bounds__(512, 2) void head_resident_kernel(
     }
 }
 
-template <int KS>
+template <int KS, bool SAMPLE>
 static hipError_t launch_resident(const void *X, int split, const uint16_t *M, float *part, int rows, int rows_pad, int K, int V,
-                                  const ResidentGrid &g, hipStream_t st)
+                                  const ResidentGrid &g, const SampleOut &so, int row_base, hipStream_t st)
 {
     const int lds = kRNB * (int)kRStageBytes;
     static LdsLimit lds_limit;
-    hipError_t e = lds_limit.raise(reinterpret_cast<const void *>(head_resident_kernel<KS>), lds);
+    hipError_t e = lds_limit.raise(reinterpret_cast<const void *>(head_resident_kernel<KS, SAMPLE>), lds);
     if (e != hipSuccess) return e;
-    head_resident_kernel<KS><<<g.n_rb * g.gw, 512, lds, st>>>(static_cast<const uint4 *>(X), M, part, rows, rows_pad, K, V, split, g);
+    head_resident_kernel<KS, SAMPLE><<<g.n_rb * g.gw, 512, lds, st>>>(static_cast<const uint4 *>(X), M, part, rows, rows_pad, K, V, split, g,
+                                                                      so.seed_lo, so.seed_hi, row_base);
     return hipGetLastError();
 }
 
 hipError_t launch_head_resident(const void *X, Operand operand, const uint16_t *M, float *part, int rows, int rows_pad, int K, int V,
-                                const ResidentGrid &g, hipStream_t st)
+                                const ResidentGrid &g, const SampleOut &so, int row_base, hipStream_t st)
 {
     const int split = operand == kOperandTwoBf16 ? two_pieces_stride(K) : 0;
-    if (K <= 128) return launch_resident<8>(X, split, M, part, rows, rows_pad, K, V, g, st);
-    if (K <= 256) return launch_resident<16>(X, 0, M, part, rows, rows_pad, K, V, g, st);
-    if (K <= 384) return launch_resident<24>(X, 0, M, part, rows, rows_pad, K, V, g, st);
-    return launch_resident<32>(X, 0, M, part, rows, rows_pad, K, V, g, st);
+#define SLIMSPEC_RESIDENT(KS) (so.on ? launch_resident<KS, true>(X, split, M, part, rows, rows_pad, K, V, g, so, row_base, st) \
+                                     : launch_resident<KS, false>(X, split, M, part, rows, rows_pad, K, V, g, so, row_base, st))
+    if (K <= 128) return SLIMSPEC_RESIDENT(8);
+    if (K <= 256) return SLIMSPEC_RESIDENT(16);
+    if (K <= 384) return SLIMSPEC_RESIDENT(24);
+    return SLIMSPEC_RESIDENT(32);
+#undef SLIMSPEC_RESIDENT
 }
 
 }  // namespace slimspec

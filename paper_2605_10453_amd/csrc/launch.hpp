@@ -107,7 +107,7 @@ hipError_t launch_head_tile(const void *X, Operand operand, const uint16_t *M, f
                             int K, int V, int n_rb, int gw, const SampleOut &so, int row_base, hipStream_t st);
 // the same with the row operand resident in registers: bf16 t log2(e) or two pieces, K <= kResidentMaxK, rows_pad a multiple of 256
 hipError_t launch_head_resident(const void *X, Operand operand, const uint16_t *M, float *part, int rows, int rows_pad, int K, int V,
-                                const ResidentGrid &g, hipStream_t st);
+                                const ResidentGrid &g, const SampleOut &so, int row_base, hipStream_t st);
 // true only in an experiment build (-DSLIMSPEC_DIAG_DBG=n) where a timing-only variant replaces the kernel: its
 // output is not a result and the calls then return SLIMSPEC_UNSUPPORTED
 bool head_tile_timing_only();

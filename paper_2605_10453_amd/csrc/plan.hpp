@@ -452,7 +452,7 @@ inline Operand tile_operand(int r, int k, bool prepared) {
     return tile_operand_f16(k, prepared) ? kOperandF16 : r <= kTwoPiecesMaxRank ? kOperandTwoBf16 : kOperandBf16;
 }
 
-// head_resident_kernel instead of head_tile_kernel: bf16 operands, no noise.
-inline bool resident_takes(const MfmaPlan &p, bool f16_operand, bool sampling) { return p.resident && !f16_operand && !sampling; }
+// head_resident_kernel instead of head_tile_kernel: bf16 operands.
+inline bool resident_takes(const MfmaPlan &p, bool f16_operand, bool /*sampling*/) { return p.resident && !f16_operand; }
 
 }  // namespace slimspec

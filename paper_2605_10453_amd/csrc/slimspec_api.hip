@@ -138,7 +138,7 @@ int run_head_mfma(HeadKind kind, const void *h, const void *A, const void *M, co
             if (e != hipSuccess) return fail_hip(e);
             if (timed && (e = hipEventRecord(g_ev_start, s)) != hipSuccess) return fail_hip(e);
             const bool resident = resident_takes(p, operand == kOperandF16, so.on != 0);
-            e = resident ? launch_head_resident(t16, operand, Mb, streams, rows, p.rows_pad, r, V, p.res, s)
+            e = resident ? launch_head_resident(t16, operand, Mb, streams, rows, p.rows_pad, r, V, p.res, so, row0, s)
                          : launch_head_tile(t16, operand, Mb, streams, rows, p.rows_pad, r, V, p.n_rb, p.gw, so, row0, s);
             if (e != hipSuccess) return fail_hip(e);
             if (timed && (e = hipEventRecord(g_ev_stop, s)) != hipSuccess) return fail_hip(e);

@@ -189,18 +189,20 @@ def test_full_head_sample(gpu, oracle_mod, rows, w_f32):
     check_sample_outputs(torch, out, ora, 77, 6152, ora.z, oracle_mod)
 
 
-@pytest.mark.parametrize("where", ["one group", "groups of one lane", "lanes"])
+@pytest.mark.parametrize("where", ["one group", "groups of one lane", "tiles of one block", "lanes"])
 @pytest.mark.parametrize("rows,head,k", [(60, "full", 5), (140, "full", 9), (60, "low", 5), (140, "low", 16)])
 def test_contenders_for_a_draw_that_share_a_record(gpu, oracle_mod, rows, head, k, where):
     """Five columns whose z + g lie within 0.06 of each other and far above the rest: members of one group of 16 logits, of groups
     that one lane holds (more than it lists: the row is done exhaustively), or apart.  What the matrix-core kernel records are bounds
     that are up to 0.13 too large, so the draw rests on the exact values that the merge puts in their place."""
     torch, b = gpu
-    V, d, seed = 8200, 64, 9
+    V, d, seed = 20000, 64, 9                                  # (head_resident_kernel: 256 column blocks, tiles of 64 columns)
+    if head == "low":
+        assert_plan("low", rows, d, d, V, k, sampling=True, kernel="resident" if rows == 140 and k <= 12 else "tile")
     x = synth.make_inputs(synth.small_config(rows, d, 8, V, k), seed=31, with_full_head=True)
     W = x.W.copy()
     cols = {"one group": [2048 + 32 * 3 + c for c in (0, 1, 2, 3, 9)], "groups of one lane": [2048 + 32 * j for j in range(4)] + [2049],
-            "lanes": [7, 1500, 3001, 4444, 8199]}[where]
+            "tiles of one block": [64 * (5 + 256 * t) + 32 * jj for t in (0, 1) for jj in (0, 1)] + [322], "lanes": [7, 1500, 3001, 14444, 19999]}[where]
     targets = [0, 3]                                           # rows the columns are made for: a mixture of two directions
     h = synth.bf16_bits_to_f64(x.h)
     g = {t: oracle_mod.gumbel_noise(seed, t, cols) for t in targets}
