@@ -43,6 +43,28 @@ __device__ __forceinline__ float operand_value(float t, int how) {
     return (how == kOperandTwoBf16 ? hi + __uint_as_float(operand_rest_bf16_bits(t) << 16) : hi) * kLn2;
 }
 
+// Eight floats as three bf16 pieces each, cut off the top of the significand, 8 bits each: their sum is the float exactly.
+// Infinity and not-a-number stay whole in the first piece (the low bits of a not-a-number may be all it has).
+__device__ __forceinline__ void cut_pieces(const float (&v)[8], uint4 (&piece)[3]) {
+    uint32_t b[3][8];
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+        const uint32_t u = __float_as_uint(v[c]);
+        const bool number = (u & 0x7f800000u) != 0x7f800000u;
+        const uint32_t top = u & 0xffff0000u;
+        const float rest = v[c] - __uint_as_float(top);
+        const uint32_t mid = __float_as_uint(rest) & 0xffff0000u;
+        const uint32_t low = __float_as_uint(rest - __uint_as_float(mid));
+        b[0][c] = number ? top : top | ((u & 0x007fffffu) ? 0x00400000u : 0u);
+        b[1][c] = number ? mid : 0u;
+        b[2][c] = number ? low : 0u;
+    }
+#pragma unroll
+    for (int p = 0; p < 3; ++p)
+        piece[p] = make_uint4((b[p][0] >> 16) | (b[p][1] & 0xffff0000u), (b[p][2] >> 16) | (b[p][3] & 0xffff0000u),
+                              (b[p][4] >> 16) | (b[p][5] & 0xffff0000u), (b[p][6] >> 16) | (b[p][7] & 0xffff0000u));
+}
+
 // Order of the outputs: larger logit first, equal logits: smaller id first.
 __device__ __forceinline__ bool ranks_before(float va, int ia, float vb, int ib) {
     return (va > vb) || (va == vb && ia < ib);

@@ -113,33 +113,21 @@ __global__ __launch_bounds__(64 * kDRWaves) void down_rows_kernel(
         t_tile[16 * nt + (ln & 15)][4 * (ln >> 4) + i] = s;
     }
     __syncthreads();
-    // thread (row, 8 columns): the pieces, cut off the top of the significand, 8 bits each: their sum is t exactly.  The last group's
+    // thread (row, 8 columns): the pieces.  The last group's
     // block also clears the rows of padding.
     const int row_end = grp + 1 == (int)gridDim.y ? rows_pad : hi;
     const size_t piece_stride = (size_t)((r + 63) / 64 * 8) * rows_pad;
     for (int e = tid; e < 2 * (row_end - lo); e += 64 * kDRWaves) {
         const int row = lo + (e >> 1), col = 8 * (e & 1);
         const bool valid = row < hi && n0 + col < r;
-        uint32_t b[3][8];
+        float v[8];
 #pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            const float v = valid ? t_tile[row - lo][col + c] : 0.f;
-            const uint32_t u = __float_as_uint(v);
-            const bool number = (u & 0x7f800000u) != 0x7f800000u;
-            const uint32_t top = u & 0xffff0000u;
-            const float rest = v - __uint_as_float(top);
-            const uint32_t mid = __float_as_uint(rest) & 0xffff0000u;
-            const uint32_t low = __float_as_uint(rest - __uint_as_float(mid));
-            // infinity and not-a-number stay whole in the first piece (the low bits of a not-a-number may be all it has)
-            b[0][c] = number ? top : top | ((u & 0x007fffffu) ? 0x00400000u : 0u);
-            b[1][c] = number ? mid : 0u;
-            b[2][c] = number ? low : 0u;
-        }
+        for (int c = 0; c < 8; ++c) v[c] = valid ? t_tile[row - lo][col + c] : 0.f;
+        uint4 piece[3];
+        cut_pieces(v, piece);
 #pragma unroll
         for (int p = 0; p < 3; ++p)
-            X[p * piece_stride + (size_t)((n0 + col) >> 3) * rows_pad + row] =
-                make_uint4((b[p][0] >> 16) | (b[p][1] & 0xffff0000u), (b[p][2] >> 16) | (b[p][3] & 0xffff0000u),
-                           (b[p][4] >> 16) | (b[p][5] & 0xffff0000u), (b[p][6] >> 16) | (b[p][7] & 0xffff0000u));
+            X[p * piece_stride + (size_t)((n0 + col) >> 3) * rows_pad + row] = piece[p];
     }
 }
 

@@ -138,7 +138,8 @@ __device__ __forceinline__ void column_scale_block(const uint16_t *__restrict__ 
 // only its slices' rows of A and columns of h.
 // STEPWISE: every 16-element step is summed on its own and then added (for the callers that report fp32-exact logits):
 // the matrix unit's internal roundings then happen at the size of one step's sum.
-template <bool STEPWISE>
+// ROWS: part is [slices][rows][r] instead, row by row and without the rows of padding.
+template <bool STEPWISE, bool ROWS>
 __global__ __launch_bounds__(256) void down_tile_kernel(
     const uint16_t *__restrict__ h, const uint16_t *__restrict__ A, float *__restrict__ part,
     int d, int r, DownGrid g)
@@ -258,6 +259,16 @@ __global__ __launch_bounds__(256) void down_tile_kernel(
         }
         wait_loads<0>();                                      // the surplus loads of the last stages
     }
+    if constexpr (ROWS) {
+        const int row = row0 + 32 * wr + l32, col = n0 + 32 * wc + 4 * half;
+        float *dst = part + ((size_t)slice * g.g_row0[g.n_groups] + row) * r + col;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (row < rows && col + 8 * q < r)
+                *reinterpret_cast<float4 *>(dst + 8 * q) = make_float4(acc0[4 * q] + acc1[4 * q], acc0[4 * q + 1] + acc1[4 * q + 1],
+                                                                       acc0[4 * q + 2] + acc1[4 * q + 2], acc0[4 * q + 3] + acc1[4 * q + 3]);
+        return;
+    }
     float *dst = part + ((((size_t)slice * g.n_rt + rt) * g.n_ct + ct) * 4 + wave) * (16 * 64) + lane;
 #pragma unroll
     for (int i = 0; i < 16; ++i) dst[i * 64] = acc0[i] + acc1[i];
@@ -336,27 +347,12 @@ __global__ __launch_bounds__(256) void down_finish_kernel(
         for (int e = 0; e < 8; ++e) v[e] = valid ? tile[row * 33 + cg * 8 + e] : 0.f;
         float a = 0.f, b = 0.f;
         if constexpr (PIECES) {
-            uint32_t b[3][8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const uint32_t u = __float_as_uint(v[e]);
-                const bool number = (u & 0x7f800000u) != 0x7f800000u;
-                const uint32_t hi = u & 0xffff0000u;
-                const float rest = v[e] - __uint_as_float(hi);
-                const uint32_t mid = __float_as_uint(rest) & 0xffff0000u;
-                const uint32_t lo = __float_as_uint(rest - __uint_as_float(mid));
-                // infinity and not-a-number stay whole in the first piece (the low bits of a not-a-number may be all it has)
-                b[0][e] = number ? hi : hi | ((u & 0x007fffffu) ? 0x00400000u : 0u);
-                b[1][e] = number ? mid : 0u;
-                b[2][e] = number ? lo : 0u;
-            }
+            uint4 piece[3];
+            cut_pieces(v, piece);
             if (mine) {
                 const size_t piece_stride = (size_t)((r + 63) / 64 * 8) * rows_pad;
 #pragma unroll
-                for (int p = 0; p < 3; ++p)
-                    t16[p * piece_stride + (size_t)kg * rows_pad + row0 + row] =
-                        make_uint4((b[p][0] >> 16) | (b[p][1] & 0xffff0000u), (b[p][2] >> 16) | (b[p][3] & 0xffff0000u),
-                                   (b[p][4] >> 16) | (b[p][5] & 0xffff0000u), (b[p][6] >> 16) | (b[p][7] & 0xffff0000u));
+                for (int p = 0; p < 3; ++p) t16[p * piece_stride + (size_t)kg * rows_pad + row0 + row] = piece[p];
             }
             return;
         }
@@ -415,16 +411,16 @@ __global__ __launch_bounds__(256) void down_finish_kernel(
                         ((red_b[tid] + red_b[32 + tid]) + red_b[64 + tid]) + red_b[96 + tid]);
 }
 
-template <bool STEPWISE>
+template <bool STEPWISE, bool ROWS = false>
 static hipError_t launch_down_tiles(const uint16_t *h, const uint16_t *A, float *part, const DownGrid &g, int d, int r, hipStream_t st)
 {
     static LdsLimit lds_limit;
-    hipError_t e = lds_limit.raise(reinterpret_cast<const void *>(down_tile_kernel<STEPWISE>), kDLds);
+    hipError_t e = lds_limit.raise(reinterpret_cast<const void *>(down_tile_kernel<STEPWISE, ROWS>), kDLds);
     if (e != hipSuccess) return e;
     const int tiles = g.n_rt * g.n_ct;
     // slices >= 8: every XCD has slices / 8 slices of every tile; fewer: 8 / slices XCDs share a slice and split the tiles
     const int blocks = g.slices >= 8 ? tiles * g.slices : 8 * ((tiles + 8 / g.slices - 1) / (8 / g.slices));
-    down_tile_kernel<STEPWISE><<<blocks, 256, kDLds, st>>>(h, A, part, d, r, g);
+    down_tile_kernel<STEPWISE, ROWS><<<blocks, 256, kDLds, st>>>(h, A, part, d, r, g);
     return hipGetLastError();
 }
 
@@ -438,6 +434,11 @@ hipError_t launch_down_projection_tiles(const uint16_t *h, const uint16_t *A, fl
     down_finish_kernel<false><<<4 * g.n_rt_all * g.n_ct + (V + 511) / 512, 256, 0, st>>>(
         part, rows_pad, r, t32, static_cast<uint4 *>(t16), stat, B, V, tilescale, operand, g);
     return hipGetLastError();
+}
+
+hipError_t launch_down_projection_slices(const uint16_t *h, const uint16_t *A, float *slices, const DownGrid &g, int d, int r, hipStream_t st)
+{
+    return launch_down_tiles<true, true>(h, A, slices, g, d, r, st);
 }
 
 hipError_t launch_down_projection_pieces(const uint16_t *h, const uint16_t *A, float *part, const DownGrid &g,

@@ -337,6 +337,19 @@ inline bool down_rows_takes(const DownGrid &g, int d, int r) {
     return r <= 256 && (d <= 1024 || (d <= 2048 && most <= 16));
 }
 
+// Up to 8 rows: down_tile_kernel leaves 8 slices of t row by row (or fewer, where the contraction has no more), which every block of
+// rows_topk_kernel adds itself, instead of a launch that does it once.  The number of slices, 0: not so.  (A launch / every block, us a call: 6 rows, d = 2056,
+// r = 136, V = 8192 18.0 / 15.6; 7 rows, d = 1464, r = 288, V = 22984 20.6 / 18.6; 6 rows in six positions, r = 216 22.8 / 20.5; 5 rows, d = 3576, r = 256, V = 74504
+// 26.7 / 25.6; 4 rows, d = 3600, r = 520 25.3 / 24.0; 4 rows of the router, d = 4096, r = 512, V = 128256 53.9 / 52.5; 8 rows 40.0 / 39.2.
+// Not with 4 slices where 16 blocks' worth of the contraction are cut (4 rows, r = 520 26.7, 8 rows, r = 512 42.0), nor with more rows: 12 rows, r = 256 23.6 / 24.3.)
+constexpr int kRowsSumRows = 8, kRowsMaxSlices = 8;
+constexpr int kRowsSumFloats = 32768;    // of the slices, which every block reads; half of it with long slices (8 rows, d = 8192, r = 504 25.1 / 26.7, r = 24 24.4 / 20.6)
+inline int rows_sum_slices(const DownGrid &g, int rows, int d, int r) {
+    if (rows > kRowsSumRows || r > 1024 || down_rows_takes(g, d, r)) return 0;
+    const int n = g.slices < kRowsMaxSlices ? g.slices : kRowsMaxSlices;
+    return rows * r * n <= (d <= 4096 ? kRowsSumFloats : kRowsSumFloats / 2) ? n : 0;
+}
+
 // Contractions this path takes: its row operand and partial tiles then fit beside the lists in a few tens of MB.
 inline bool rows_path_fits(HeadKind kind, int d, int r) { return kind == HeadKind::LowRank ? r <= 2048 : d <= 8192; }
 

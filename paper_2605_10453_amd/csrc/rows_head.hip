@@ -47,6 +47,10 @@ __device__ __forceinline__ uint32_t pair16(uint32_t a, uint32_t b) {
 constexpr int kPairCand = 64;
 constexpr int kPairMaxK = 32;            // longer lists take one row per wavefront
 constexpr int kPairKeys = kPairCand + 2; // (the two rows' candidates in different banks)
+// Bytes before the pieces of t that a block keeps: the rows' logits, the candidates.
+constexpr __host__ __device__ size_t rows_x_offset(int NT, int G, int waves, int k) {
+    return sizeof(float) * 16 * NT * (size_t)rows_lds_stride(G) + (k <= kPairMaxK ? sizeof(uint64_t) * 2 * kPairKeys * waves : 0);
+}
 
 // Sum over each half of 32 lanes, in every lane of it.
 __device__ __forceinline__ float half_sum(float v) {
@@ -91,9 +95,11 @@ __device__ __forceinline__ float max3_number(float a, float b, float c) { float 
 // Block b: columns [128 G b, 128 G (b + 1)); wavefront w: column group w % G, contraction slice w / G (none from KS on).
 // Partials of (row, chunk): see stream_topk_kernel.  row0: the index in the call of this launch's first row (noise).
 // GM: G at most (what a lane keeps of a row's logits is sized by it: known when compiled, or every step of the epilogue branches)
-template <int NT, int NP, int GM>
+// SUM (NT 1, NP 3): X is not given; the block adds the nds slices of t, fp32 [nds][rows][K], itself and keeps the pieces in shared memory,
+// where a small t takes less time than a launch that does it once (plan.hpp: rows_sum_slices).
+template <int NT, int NP, int GM, bool SUM>
 __global__ __launch_bounds__(512) void rows_topk_kernel(
-    const uint4 *__restrict__ X, const uint16_t *__restrict__ M,
+    const uint4 *__restrict__ X, const float *__restrict__ slices, int nds, const uint16_t *__restrict__ M,
     float2 *__restrict__ part_ms, float *__restrict__ part_val, int *__restrict__ part_id, float4 *__restrict__ part_smp,
     int rows, int row0, int K, int V, int chunks, int G, int KS, int k, uint32_t seed_lo, uint32_t seed_hi)
 {
@@ -107,7 +113,9 @@ __global__ __launch_bounds__(512) void rows_topk_kernel(
     const int n_steps = (K + 31) / 32, per = (n_steps + KS - 1) / KS;
     const int s_beg = min(n_steps, ks * per), s_end = min(n_steps, s_beg + per);
     const int chunk_col = blockIdx.x * (128 * G);
-    const size_t x_piece = (size_t)((K + 63) / 64 * 8) * RP;
+    const int x_groups = (K + 63) / 64 * 8;
+    const size_t x_piece = (size_t)x_groups * RP;
+    uint4 *const x_lds = reinterpret_cast<uint4 *>(reinterpret_cast<unsigned char *>(z_lds) + rows_x_offset(NT, G, (int)(blockDim.x >> 6), k));      // (SUM)
 
     f32x4 acc[8][NT];                                            // [column in the lane's 8][row tile]
 #pragma unroll
@@ -120,7 +128,7 @@ __global__ __launch_bounds__(512) void rows_topk_kernel(
     {
         // columns beyond V re-read the last group that exists (their logits are masked below)
         const uint16_t *const m_lane = M + min(chunk_col + cg * 128 + 8 * c16, V - 8);
-        const uint4 *const x_lane = X + (size_t)kg * RP + c16;
+        const uint4 *const x_lane = (SUM ? x_lds : X) + (size_t)kg * RP + c16;
         u32x4 q[2][8], xv[NP][NT];
         const auto load_m = [&](u32x4 (&dst)[8], int s) {
             // K is a multiple of 8: a lane's 8 rows exist or none do (then rows of the step that do are read, and dropped)
@@ -136,6 +144,50 @@ __global__ __launch_bounds__(512) void rows_topk_kernel(
                 for (int nt = 0; nt < NT; ++nt)
                     xv[p][nt] = *reinterpret_cast<const u32x4 *>(x_lane + p * x_piece + (size_t)(4 * s) * RP + 16 * nt);
         };
+        if constexpr (SUM) {
+            static_assert(NT == 1 && NP == 3, "a few rows of t");
+            constexpr int SB = kRowsMaxSlices;
+            const int n_items = rows * (K / 8), per_row = K / 8, nthreads = (int)blockDim.x;
+            float4 v[SB][2];
+            const auto load_slices = [&](int e) {                // item e: 8 adjacent columns of a row
+                const int row = e / per_row, g8 = e - row * per_row;
+                const float4 *src = reinterpret_cast<const float4 *>(slices + (size_t)row * K + 8 * g8);
+#pragma unroll
+                for (int u = 0; u < SB; ++u) {
+                    if (u >= nds) break;
+                    v[u][0] = src[(size_t)u * rows * (K / 4)];
+                    v[u][1] = src[(size_t)u * rows * (K / 4) + 1];
+                }
+            };
+            const auto store_pieces = [&](int e) {
+                const int row = e / per_row, g8 = e - row * per_row;
+                float t[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int u = 0; u < SB; ++u) {                   // fixed order
+                    if (u >= nds) break;
+                    t[0] += v[u][0].x; t[1] += v[u][0].y; t[2] += v[u][0].z; t[3] += v[u][0].w;
+                    t[4] += v[u][1].x; t[5] += v[u][1].y; t[6] += v[u][1].z; t[7] += v[u][1].w;
+                }
+                uint4 piece[3];
+                cut_pieces(t, piece);
+#pragma unroll
+                for (int p = 0; p < 3; ++p) x_lds[p * x_piece + (size_t)g8 * RP + row] = piece[p];
+            };
+            for (int e = tid; e < x_groups * RP; e += nthreads)  // rows beyond the last, elements beyond K
+                if ((e & (RP - 1)) >= rows || (e / RP) * 8 >= K) {
+#pragma unroll
+                    for (int p = 0; p < 3; ++p) x_lds[p * x_piece + e] = make_uint4(0u, 0u, 0u, 0u);
+                }
+            int e = tid;
+            for (; e + nthreads < n_items; e += nthreads) { load_slices(e); store_pieces(e); }
+            if (e < n_items) load_slices(e);
+            __builtin_amdgcn_sched_barrier(0);
+            if (s_beg < s_end) load_m(q[0], s_beg);              // the first weights right behind
+            if (s_beg + 1 < s_end) load_m(q[1], s_beg + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            if (e < n_items) store_pieces(e);
+            __syncthreads();
+        }
         const auto multiply = [&](u32x4 (&w)[8], int s) {
             if (32 * s + 32 > K) {                               // the last step of a K that is no multiple of 32
                 const uint32_t keep = (32 * s + 8 * kg < K) ? 0xffffffffu : 0u;
@@ -187,11 +239,14 @@ __global__ __launch_bounds__(512) void rows_topk_kernel(
                 }
             }
         } else if (s_beg + 1 == s_end) {
-            load_m(q[0], s_beg); load_x(s_beg); then();
+            if (!SUM) load_m(q[0], s_beg);
+            load_x(s_beg); then();
             multiply(q[0], s_beg);
         } else if (s_beg < s_end) {
-            load_m(q[0], s_beg); load_x(s_beg); then();
-            load_m(q[1], s_beg + 1); then();
+            if (!SUM) load_m(q[0], s_beg);
+            load_x(s_beg); then();
+            if (!SUM) load_m(q[1], s_beg + 1);
+            then();
             int s = s_beg;
             for (; s + 3 < s_end; s += 2) {
                 multiply(q[0], s); then();
@@ -277,6 +332,7 @@ __global__ __launch_bounds__(512) void rows_topk_kernel(
             const uint4 *Xq = X;
             int Vq = V, Kq = K, rowq = row;
             asm volatile("" : "+s"(Mq), "+s"(Xq), "+s"(Vq), "+s"(Kq), "+s"(rowq));
+            if constexpr (SUM) Xq = x_lds;
 #pragma unroll 1
             for (int g = 0; g < G; ++g) {
                 if (!act(g)) continue;
@@ -461,27 +517,29 @@ __global__ __launch_bounds__(512) void rows_topk_kernel(
     }
 }
 
-template <int NT, int NP, int GM>
-static hipError_t launch_rows(const void *X, const uint16_t *M, float2 *ms, float *pv, int *pi, float4 *smp, int rows, int row0,
+template <int NT, int NP, int GM, bool SUM>
+static hipError_t launch_rows(const RowsInput &x, const uint16_t *M, float2 *ms, float *pv, int *pi, float4 *smp, int rows, int row0,
                               int K, int V, const RowsGeom &g, int k, uint32_t seed_lo, uint32_t seed_hi, hipStream_t st)
 {
-    const size_t lds = sizeof(float) * 16 * NT * (size_t)rows_lds_stride(g.G) + (k <= kPairMaxK ? sizeof(uint64_t) * 2 * kPairKeys * g.waves : 0);
+    const size_t lds = rows_x_offset(NT, g.G, g.waves, k) + (SUM ? sizeof(uint4) * 3 * 16 * (size_t)((K + 63) / 64 * 8) : 0);
     static LdsLimit lds_limit;
-    hipError_t e = lds_limit.raise(reinterpret_cast<const void *>(rows_topk_kernel<NT, NP, GM>), (int)lds);
+    hipError_t e = lds_limit.raise(reinterpret_cast<const void *>(rows_topk_kernel<NT, NP, GM, SUM>), (int)lds);
     if (e != hipSuccess) return e;
-    rows_topk_kernel<NT, NP, GM><<<g.chunks, 64 * g.waves, lds, st>>>(static_cast<const uint4 *>(X), M, ms, pv, pi, smp, rows, row0,
-                                                                      K, V, g.chunks, g.G, g.KS, k, seed_lo, seed_hi);
+    rows_topk_kernel<NT, NP, GM, SUM><<<g.chunks, 64 * g.waves, lds, st>>>(static_cast<const uint4 *>(x.X), x.slices, x.nds, M, ms, pv, pi, smp,
+                                                                           rows, row0, K, V, g.chunks, g.G, g.KS, k, seed_lo, seed_hi);
     return hipGetLastError();
 }
 
-hipError_t launch_rows_topk(const void *X, int pieces, const uint16_t *M, float2 *ms, float *pv, int *pi, float4 *smp,
+hipError_t launch_rows_topk(const RowsInput &x, const uint16_t *M, float2 *ms, float *pv, int *pi, float4 *smp,
                             int rows, int row0, int K, int V, const RowsGeom &g, int k, uint32_t seed_lo, uint32_t seed_hi, hipStream_t st)
 {
     static_assert(kRowsMaxColGroups == 6, "the instances cover G = 1, 2, up to 4 and up to 6");
-#define SLIMSPEC_ROWS_G(NT, NP, GM) launch_rows<NT, NP, GM>(X, M, ms, pv, pi, smp, rows, row0, K, V, g, k, seed_lo, seed_hi, st)
-#define SLIMSPEC_ROWS(NT, NP) (g.G == 1 ? SLIMSPEC_ROWS_G(NT, NP, 1) : g.G == 2 ? SLIMSPEC_ROWS_G(NT, NP, 2) : g.G <= 4 ? SLIMSPEC_ROWS_G(NT, NP, 4) : SLIMSPEC_ROWS_G(NT, NP, 6))
-    if (pieces == 1) return rows <= 16 ? SLIMSPEC_ROWS(1, 1) : rows <= 32 ? SLIMSPEC_ROWS(2, 1) : SLIMSPEC_ROWS(3, 1);
-    return rows <= 16 ? SLIMSPEC_ROWS(1, 3) : rows <= 32 ? SLIMSPEC_ROWS(2, 3) : SLIMSPEC_ROWS(3, 3);
+#define SLIMSPEC_ROWS_G(NT, NP, GM, SUM) launch_rows<NT, NP, GM, SUM>(x, M, ms, pv, pi, smp, rows, row0, K, V, g, k, seed_lo, seed_hi, st)
+#define SLIMSPEC_ROWS(NT, NP, SUM) (g.G == 1 ? SLIMSPEC_ROWS_G(NT, NP, 1, SUM) : g.G == 2 ? SLIMSPEC_ROWS_G(NT, NP, 2, SUM) \
+                                             : g.G <= 4 ? SLIMSPEC_ROWS_G(NT, NP, 4, SUM) : SLIMSPEC_ROWS_G(NT, NP, 6, SUM))
+    if (x.slices) return SLIMSPEC_ROWS(1, 3, true);
+    if (x.pieces == 1) return rows <= 16 ? SLIMSPEC_ROWS(1, 1, false) : rows <= 32 ? SLIMSPEC_ROWS(2, 1, false) : SLIMSPEC_ROWS(3, 1, false);
+    return rows <= 16 ? SLIMSPEC_ROWS(1, 3, false) : rows <= 32 ? SLIMSPEC_ROWS(2, 3, false) : SLIMSPEC_ROWS(3, 3, false);
 #undef SLIMSPEC_ROWS
 #undef SLIMSPEC_ROWS_G
 }

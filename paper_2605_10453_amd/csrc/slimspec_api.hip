@@ -187,9 +187,16 @@ int run_head_rows(HeadKind kind, const void *h, const void *A, const void *M, co
         const uint16_t *hrow = static_cast<const uint16_t *>(h) + (size_t)row0 * d;
         void *X = ws + p.off_x;
         hipError_t e;
+        RowsInput in;
+        in.X = X; in.pieces = p.pieces;
         if (kind == HeadKind::LowRank) {
             if (pos.n > 0) p.down = down_grid_by_position(pos, row0, rows, p.rows_pad, d, r);
-            if (down_rows_takes(p.down, d, r))
+            if (const int n = rows_sum_slices(p.down, rows, d, r)) {
+                p.down.slices = n;
+                float *slices = reinterpret_cast<float *>(ws + p.off_down_part);
+                e = launch_down_projection_slices(hrow, static_cast<const uint16_t *>(A), slices, p.down, d, r, s);
+                in.slices = slices; in.nds = n;
+            } else if (down_rows_takes(p.down, d, r))
                 e = launch_down_rows(hrow, static_cast<const uint16_t *>(A), X, p.rows_pad, d, r, p.down, s);
             else
                 e = launch_down_projection_pieces(hrow, static_cast<const uint16_t *>(A), reinterpret_cast<float *>(ws + p.off_down_part),
@@ -203,7 +210,7 @@ int run_head_rows(HeadKind kind, const void *h, const void *A, const void *M, co
         float4 *smp = so.on ? reinterpret_cast<float4 *>(ws + p.off_part_smp) : nullptr;
         const bool timed = g_ev_start && row0 == 0;
         if (timed && (e = hipEventRecord(g_ev_start, s)) != hipSuccess) return fail_hip(e);
-        e = launch_rows_topk(X, p.pieces, Mb, ms, pv, pi, smp, rows, row0, K, V, p.geom, k, so.seed_lo, so.seed_hi, s);
+        e = launch_rows_topk(in, Mb, ms, pv, pi, smp, rows, row0, K, V, p.geom, k, so.seed_lo, so.seed_hi, s);
         if (e != hipSuccess) return fail_hip(e);
         if (timed && (e = hipEventRecord(g_ev_stop, s)) != hipSuccess) return fail_hip(e);
         SampleOut so_rows = so;

@@ -114,3 +114,36 @@ def test_rows_in_pairs(gpu, oracle_mod, rows, k, V):
     want, want_lp = b.slimspec_head_topk(h[:1].contiguous(), A, Bi, k)
     torch.cuda.synchronize()
     assert torch.equal(ids[0], want[0]) and torch.allclose(lp[0], want_lp[0], atol=FP32_TOL, rtol=0, equal_nan=True)
+
+
+# up to 8 rows whose slices of t every block adds: ranks that are no multiple of 64 or 32, the largest one, contractions that end in a partial
+# stage, all group sizes, chunks of 128 to 768 columns; and the first shapes on the other side of the rule
+@pytest.mark.parametrize("rows,d,r,V,k,slices", [
+    (3, 2048, 520, 30000, 10, 8), (4, 2056, 264, 50000, 17, 8), (5, 2056, 8, 136, 3, 8), (5, 1032, 264, 8200, 33, 8), (8, 2064, 72, 32776, 64, 8),
+    (7, 2600, 136, 65544, 10, 8), (6, 2056, 40, 98312, 16, 8), (8, 2056, 24, 131080, 20, 8), (5, 2056, 200, 165000, 5, 8), (8, 520, 512, 4104, 9, 8),
+    (4, 1024, 1024, 16392, 12, 8), (5, 1024, 1024, 1000, 12, 0), (8, 200, 264, 2056, 6, 2), (9, 2056, 72, 2056, 4, 0),
+])
+def test_input_summed_by_every_block(gpu, oracle_mod, rows, d, r, V, k, slices):
+    torch, b = gpu
+    print(f"rows kernel, slices: rows={rows} d={d} r={r} V={V} k={k}", flush=True)
+    assert_plan("low", rows, d, r, V, k, kernel="rows", sum_slices=slices)
+    x = synth.make_inputs(synth.small_config(rows, d, r, V, k, peaked_every=3), seed=rows + d + r)
+    h, A, B = to_dev_bf16(x.h), to_dev_bf16(x.A), to_dev_bf16(x.B)
+    ids, lp = b.slimspec_head_topk(h, A, B, k)
+    # the same rows as three positions, one of them empty, with the same matrix
+    p_ids, p_lp = b.slimspec_head_topk_positions(h, A.expand(3, d, r).contiguous(), [0, 1, 1, rows], B, k)
+    torch.cuda.synchronize()
+    ora = oracle_mod.slimspec_head_topk(x.h, x.A, x.B, k)
+    z_at = lambda ri, ci: oracle_mod.slimspec_logits_at(x.h, x.A, x.B, ri, ci)
+    for got in ((ids, lp), (p_ids, p_lp)):
+        compare_with_oracle(got[0].cpu().numpy(), got[1].cpu().numpy(), ora.ids, ora.lse, z_at, V, tie_tol=FP32_TOL, lp_tol=FP32_TOL)
+    if slices:                                           # not-a-number and infinite logits are summed again from the pieces in shared memory
+        Bi = B.clone()
+        Bi[r - 1, V // 2] = float("inf")
+        h2 = h.clone()
+        h2[rows - 1, d - 1] = float("nan")
+        got, got_lp = b.slimspec_head_topk(h2, A, Bi, k)
+        want, want_lp = b.slimspec_head_topk(h[:1].contiguous(), A, Bi, k)
+        torch.cuda.synchronize()
+        assert torch.equal(got[0], want[0]) and torch.allclose(got_lp[0], want_lp[0], atol=FP32_TOL, rtol=0, equal_nan=True)
+        assert torch.isnan(got_lp[rows - 1]).all()
