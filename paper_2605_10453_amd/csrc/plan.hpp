@@ -4,6 +4,7 @@
 #pragma once
 #include <stddef.h>
 #include <stdint.h>
+#include <initializer_list>
 
 namespace slimspec {
 
@@ -258,13 +259,16 @@ struct MfmaPlan {
     size_t off_t16 = 0;                  // 16-byte vectors [8 ceil(K / 64), rows_pad]: the head kernel's row operand (two of them for two pieces)
     size_t off_stat = 0;                 // float2 [2 ceil(r / 64), rows_pad]: per row and 32 columns of t, (sum of dt^2, sum of t dt), dt = t - rounded t
     size_t off_tilescale = 0;            // float2 [n_vt]: (column scale, mean square) of B per vocabulary tile
-    size_t off_streams = 0;              // fp32 [rows, nsr, kStreamRec]
+    size_t off_streams = 0;              // fp32 [rows, nsr, kStreamRec] of one launch
+    size_t records = 0;                  // ... records there is room for
     size_t off_defer = 0;                // parked rows of the merge (long contractions only; bytes 0 otherwise)
     bool defer = false;
     size_t bytes = 0;
 };
 
-// rows here is the number of rows of ONE launch (at most kPlanSlotsPerXcd row blocks)
+// rows here is the number of rows of ONE launch (at most kPlanSlotsPerXcd row blocks), or of two that share a down-projection: the grids
+// are then of no use, but the scratch serves both.
+constexpr int kMaxLaunchRows = 512;
 inline MfmaPlan make_mfma_plan(HeadKind kind, int rows, int d, int r, int V) {
     MfmaPlan p;
     p.rows = rows;
@@ -293,16 +297,26 @@ inline MfmaPlan make_mfma_plan(HeadKind kind, int rows, int d, int r, int V) {
     if (p.resident) p.res = make_resident_grid(p.n_rb, V);
     // (room for the records of one row block, the most a row has: a workspace then serves fewer rows as well)
     const int nsr_res = p.resident ? make_resident_grid(1, V).nsr : 0;
-    p.off_streams = off;       off = align_up(off + sizeof(float) * (size_t)rows * (p.nsr > nsr_res ? p.nsr : nsr_res) * kStreamRecPlan);
+    p.records = (size_t)rows * (p.nsr > nsr_res ? p.nsr : nsr_res);
+    if (rows > kMaxLaunchRows)           // (of one launch at a time, and fewer rows have more records each)
+        for (const int of_launch : {kMaxLaunchRows, rows - kMaxLaunchRows}) {
+            const size_t n = make_mfma_plan(kind, of_launch, d, r, V).records;
+            if (n > p.records) p.records = n;
+        }
+    p.off_streams = off;       off = align_up(off + sizeof(float) * p.records * kStreamRecPlan);
     p.defer = (kind == HeadKind::Full ? d : r) >= kDeferMinKFine;      // room for it; the call decides (merge_parks_rows)
-    if (p.defer) { p.off_defer = off; off = align_up(off + merge_defer_bytes(rows)); }
+    if (p.defer) { p.off_defer = off; off = align_up(off + merge_defer_bytes(rows < kMaxLaunchRows ? rows : kMaxLaunchRows)); }
     p.bytes = off;
     return p;
 }
 // Rows of one launch of the matrix-core kernels.  More rows per launch would leave fewer column blocks (gw), hence
 // fewer stream records per row, and a row whose top-k crowd into one record pays an exact rescan of that record's
 // columns: at 512 rows a row still has 128 column blocks, with two or four records each.
-inline int mfma_max_rows_per_launch(int rows) { return rows > 512 ? 512 : rows; }
+inline int mfma_max_rows_per_launch(int rows) { return rows > kMaxLaunchRows ? kMaxLaunchRows : rows; }
+// Rows that share a down-projection: those of two launches.
+inline int mfma_joint_rows(HeadKind kind, int rows) {
+    return kind == HeadKind::LowRank && rows > kMaxLaunchRows ? (rows < 2 * kMaxLaunchRows ? rows : 2 * kMaxLaunchRows) : mfma_max_rows_per_launch(rows);
+}
 
 // ---- few rows or long lists on the matrix cores, fp32-exact products (rows_head.hip) ----------------------------
 constexpr int kRowsMaxRows = 48;         // rows per launch: three 16-row MFMA tiles (their accumulators: 96 registers)

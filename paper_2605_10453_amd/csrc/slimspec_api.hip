@@ -66,6 +66,24 @@ size_t mfma_workspace_bytes(HeadKind kind, const slimspec_shape *s)
     return need;
 }
 
+// Low-rank calls of more than one launch: the down-projection serves two launches at once where the workspace has room for their rows (one
+// read of A and of the column samples instead of two, and no half-empty round of blocks; two / one, us a call: 700 rows in six positions 177.4 / 161.4,
+// 600 rows, d = 1024, r = 128, V = 32000 74.6 / 67.9, 537 rows, d = 4816, r = 664, prepared 204.0 / 191.0).
+// The query asks for the room; a workspace that only fits launch by launch, the static scratch of the largest shapes too, still serves.
+size_t mfma_joint_workspace_bytes(HeadKind kind, const slimspec_shape *s)
+{
+    const int joint = mfma_joint_rows(kind, s->rows);
+    size_t need = mfma_workspace_bytes(kind, s);
+    if (joint > mfma_max_rows_per_launch(s->rows)) {
+        for (const int rows : {joint, s->rows % joint}) {
+            if (rows == 0) continue;
+            const size_t w = make_mfma_plan(kind, rows, s->d, s->r, s->V).bytes;
+            if (w > need) need = w;
+        }
+    }
+    return need;
+}
+
 // Device address of this device's copy of `scratch` (looked up at the first call on the device).
 int static_scratch_address(void **out)
 {
@@ -115,52 +133,62 @@ int run_head_mfma(HeadKind kind, const void *h, const void *A, const void *M, co
     char *ws = static_cast<char *>(workspace);
     const int d = shape->d, r = shape->r, V = shape->V;
     const int per = mfma_max_rows_per_launch(shape->rows);
+    const int joint = workspace_bytes >= mfma_joint_workspace_bytes(kind, shape) ? mfma_joint_rows(kind, shape->rows) : per;
     const uint16_t *hb = static_cast<const uint16_t *>(h);
     const uint16_t *Mb = static_cast<const uint16_t *>(M);
     const uint16_t *Mtb = static_cast<const uint16_t *>(Mt);      // column-major copy of M, or null
-    for (int row0 = 0; row0 < shape->rows; row0 += per) {
-        const int rows = (shape->rows - row0 < per) ? shape->rows - row0 : per;
-        // a last, smaller batch may fall below the matrix-core threshold; it still runs here
-        MfmaPlan p = make_mfma_plan(kind, rows, d, r, V);
-        if (kind == HeadKind::LowRank && pos.n > 0) p.down = down_grid_by_position(pos, row0, rows, p.rows_pad, d, r);
-        float *streams = reinterpret_cast<float *>(ws + p.off_streams);
-        const uint16_t *hrow = hb + (size_t)row0 * d;
+    for (int first = 0; first < shape->rows; first += joint) {
+        const int rows_joint = (shape->rows - first < joint) ? shape->rows - first : joint;
+        // the scratch arrays of all these rows; a last, smaller batch may fall below the matrix-core threshold, and still runs here
+        MfmaPlan all = make_mfma_plan(kind, rows_joint, d, r, V);
+        if (kind == HeadKind::LowRank && pos.n > 0) all.down = down_grid_by_position(pos, first, rows_joint, all.rows_pad, d, r);
+        float *streams = reinterpret_cast<float *>(ws + all.off_streams);
+        void *defer = all.defer ? ws + all.off_defer : nullptr;
         hipError_t e;
-        const bool timed = g_ev_start && row0 == 0;
+        const Operand operand = kind == HeadKind::LowRank ? tile_operand(r, k, Mtb != nullptr) : kOperandExact;
+        float *t32 = reinterpret_cast<float *>(ws + all.off_t32);
+        float2 *stat = reinterpret_cast<float2 *>(ws + all.off_stat);
+        float2 *tilescale = reinterpret_cast<float2 *>(ws + all.off_tilescale);
         if (kind == HeadKind::LowRank) {
-            float *t32 = reinterpret_cast<float *>(ws + p.off_t32);
-            void *t16 = ws + p.off_t16;
-            float2 *stat = reinterpret_cast<float2 *>(ws + p.off_stat);
-            float2 *tilescale = reinterpret_cast<float2 *>(ws + p.off_tilescale);
-            const Operand operand = tile_operand(r, k, Mtb != nullptr);
-            e = launch_down_projection_tiles(hrow, static_cast<const uint16_t *>(A), reinterpret_cast<float *>(ws + p.off_down_part), p.down,
-                                             p.rows_pad, d, r, t32, t16, stat, Mb, V, tilescale, operand, s);
+            e = launch_down_projection_tiles(hb + (size_t)first * d, static_cast<const uint16_t *>(A), reinterpret_cast<float *>(ws + all.off_down_part),
+                                             all.down, all.rows_pad, d, r, t32, ws + all.off_t16, stat, Mb, V, tilescale, operand, s);
             if (e != hipSuccess) return fail_hip(e);
-            if (timed && (e = hipEventRecord(g_ev_start, s)) != hipSuccess) return fail_hip(e);
-            const bool resident = resident_takes(p, operand == kOperandF16, so.on != 0);
-            e = resident ? launch_head_resident(t16, operand, Mb, streams, rows, p.rows_pad, r, V, p.res, so, row0, s)
-                         : launch_head_tile(t16, operand, Mb, streams, rows, p.rows_pad, r, V, p.n_rb, p.gw, so, row0, s);
-            if (e != hipSuccess) return fail_hip(e);
-            if (timed && (e = hipEventRecord(g_ev_stop, s)) != hipSuccess) return fail_hip(e);
-            if (head_tile_timing_only()) return SLIMSPEC_UNSUPPORTED;      // diagnostic build, timing-only kernel: no result
-            // the records are in base-2 units (t was scaled by log2 e); f16 mode flushes weights below 2^-25 to zero
-            e = launch_merge_streams(streams, rows, resident ? p.res.nsr : p.nsr, resident ? p.res.gw : p.gw, p.n_vt, resident, t32, false, r, operand, Mb, r, V, Mtb, stat, 2 * ((r + 63) / 64), p.rows_pad, tilescale, k,
-                                     0.6931471805599453f, operand == kOperandF16 ? 2.9802322e-8f : 0.f, out_ids + (size_t)row0 * k, out_logprobs + (size_t)row0 * k, id_map,
-                                     (p.defer && merge_parks_rows(r, operand == kOperandF16)) ? ws + p.off_defer : nullptr, so, row0, s);
-            if (e != hipSuccess) return fail_hip(e);
-        } else {
-            // the full head runs the same kernel on h itself (bf16 exact, natural units): no rounding statistics
-            void *hx = ws + p.off_t16;
-            if ((e = launch_regroup_rows(hrow, hx, rows, p.rows_pad, d, s)) != hipSuccess) return fail_hip(e);
-            if (timed && (e = hipEventRecord(g_ev_start, s)) != hipSuccess) return fail_hip(e);
-            e = launch_head_tile(hx, kOperandExact, Mb, streams, rows, p.rows_pad, d, V, p.n_rb, p.gw, so, row0, s);
-            if (e != hipSuccess) return fail_hip(e);
-            if (timed && (e = hipEventRecord(g_ev_stop, s)) != hipSuccess) return fail_hip(e);
-            if (head_tile_timing_only()) return SLIMSPEC_UNSUPPORTED;
-            e = launch_merge_streams(streams, rows, p.nsr, p.gw, p.n_vt, false, hrow, true, d, kOperandExact, Mb, d, V, Mtb, nullptr, 0, 0, nullptr, k,
-                                     1.0f, 0.f, out_ids + (size_t)row0 * k, out_logprobs + (size_t)row0 * k, id_map,
-                                     (p.defer && merge_parks_rows(d, true)) ? ws + p.off_defer : nullptr, so, row0, s);
-            if (e != hipSuccess) return fail_hip(e);
+        }
+        for (int row0 = first; row0 < first + rows_joint; row0 += per) {
+            const int rows = (first + rows_joint - row0 < per) ? first + rows_joint - row0 : per, at = row0 - first;
+            const MfmaPlan p = make_mfma_plan(kind, rows, d, r, V);
+            const bool timed = g_ev_start && row0 == 0;
+            int32_t *ids = out_ids + (size_t)row0 * k;
+            float *lps = out_logprobs + (size_t)row0 * k;
+            if (kind == HeadKind::LowRank) {
+                if (timed && (e = hipEventRecord(g_ev_start, s)) != hipSuccess) return fail_hip(e);
+                const bool resident = resident_takes(p, operand == kOperandF16, so.on != 0);
+                const void *x = ws + all.off_t16 + 16 * (size_t)at;
+                e = resident ? launch_head_resident(x, operand, Mb, streams, rows, all.rows_pad, r, V, p.res, so, row0, s)
+                             : launch_head_tile(x, operand, Mb, streams, rows, all.rows_pad, r, V, p.n_rb, p.gw, so, row0, s);
+                if (e != hipSuccess) return fail_hip(e);
+                if (timed && (e = hipEventRecord(g_ev_stop, s)) != hipSuccess) return fail_hip(e);
+                if (head_tile_timing_only()) return SLIMSPEC_UNSUPPORTED;      // diagnostic build, timing-only kernel: no result
+                // the records are in base-2 units (t was scaled by log2 e); f16 mode flushes weights below 2^-25 to zero
+                e = launch_merge_streams(streams, rows, resident ? p.res.nsr : p.nsr, resident ? p.res.gw : p.gw, p.n_vt, resident, t32 + (size_t)at * r, false, r, operand,
+                                         Mb, r, V, Mtb, stat + at, 2 * ((r + 63) / 64), all.rows_pad, tilescale, k,
+                                         0.6931471805599453f, operand == kOperandF16 ? 2.9802322e-8f : 0.f, ids, lps, id_map,
+                                         merge_parks_rows(r, operand == kOperandF16) ? defer : nullptr, so, row0, s);
+                if (e != hipSuccess) return fail_hip(e);
+            } else {
+                // the full head runs the same kernel on h itself (bf16 exact, natural units): no rounding statistics
+                const uint16_t *hrow = hb + (size_t)row0 * d;
+                void *hx = ws + all.off_t16;
+                if ((e = launch_regroup_rows(hrow, hx, rows, p.rows_pad, d, s)) != hipSuccess) return fail_hip(e);
+                if (timed && (e = hipEventRecord(g_ev_start, s)) != hipSuccess) return fail_hip(e);
+                e = launch_head_tile(hx, kOperandExact, Mb, streams, rows, p.rows_pad, d, V, p.n_rb, p.gw, so, row0, s);
+                if (e != hipSuccess) return fail_hip(e);
+                if (timed && (e = hipEventRecord(g_ev_stop, s)) != hipSuccess) return fail_hip(e);
+                if (head_tile_timing_only()) return SLIMSPEC_UNSUPPORTED;
+                e = launch_merge_streams(streams, rows, p.nsr, p.gw, p.n_vt, false, hrow, true, d, kOperandExact, Mb, d, V, Mtb, nullptr, 0, 0, nullptr, k,
+                                         1.0f, 0.f, ids, lps, id_map, merge_parks_rows(d, true) ? defer : nullptr, so, row0, s);
+                if (e != hipSuccess) return fail_hip(e);
+            }
         }
     }
     return SLIMSPEC_OK;
@@ -300,7 +328,8 @@ SampleOut sample_out(uint64_t seed, float *out_lse, int32_t *out_sample_ids, flo
 }
 
 // Scratch one call of `kind` needs (the query slimspec_workspace_bytes reports the larger of the two heads).
-size_t head_workspace_bytes(HeadKind kind, const slimspec_shape *shape, int32_t k)
+// joint: with room for two launches' down-projection at once; without it the call runs all the same
+size_t head_workspace_bytes(HeadKind kind, const slimspec_shape *shape, int32_t k, bool joint)
 {
     if (check_shape(kind, shape, k) != SLIMSPEC_OK) return 0;
     size_t need = make_plan(kind, shape->rows, shape->d, shape->r, shape->V, k).bytes;
@@ -311,7 +340,7 @@ size_t head_workspace_bytes(HeadKind kind, const slimspec_shape *shape, int32_t 
         if (w > need) need = w;
     }
     if (shape->rows >= kMfmaMinRows) {
-        const size_t m = mfma_workspace_bytes(kind, shape);
+        const size_t m = joint ? mfma_joint_workspace_bytes(kind, shape) : mfma_workspace_bytes(kind, shape);
         if (m > need) need = m;
     }
     // The most rows, of this many or fewer, with which a call takes that path: a workspace serves fewer rows as well, and the rules for two, for
@@ -335,8 +364,8 @@ size_t slimspec_workspace_bytes(const slimspec_shape *shape, int32_t k)
 {
     if (!shape) return 0;
     // the larger of: streaming path (also serves fp32 W and large k), matrix-core path, for both heads
-    const size_t full = head_workspace_bytes(HeadKind::Full, shape, k);
-    const size_t low = head_workspace_bytes(HeadKind::LowRank, shape, k);
+    const size_t full = head_workspace_bytes(HeadKind::Full, shape, k, true);
+    const size_t low = head_workspace_bytes(HeadKind::LowRank, shape, k, true);
     return full > low ? full : low;
 }
 
@@ -375,7 +404,7 @@ int slimspec_head_topk_static(const void *h, const void *A, const void *B,
 {
     const int st = check_shape(HeadKind::LowRank, shape, k);
     if (st != SLIMSPEC_OK) return st;
-    if (head_workspace_bytes(HeadKind::LowRank, shape, k) > (size_t)SLIMSPEC_STATIC_SCRATCH_BYTES)
+    if (head_workspace_bytes(HeadKind::LowRank, shape, k, false) > (size_t)SLIMSPEC_STATIC_SCRATCH_BYTES)
         return SLIMSPEC_SCRATCH_LIMIT;
     if (!h || !A || !B || !out_ids || !out_logprobs) return SLIMSPEC_INVALID_ARGUMENT;      // before any HIP call
     void *ptr = nullptr;
@@ -431,7 +460,7 @@ int full_head_sample(const void *h, const void *W, slimspec_dtype w_dtype,
 size_t routed_workspace_bytes(const slimspec_shape *shape, int32_t k_route)
 {
     if (!shape) return 0;
-    const size_t router = head_workspace_bytes(HeadKind::LowRank, shape, k_route);
+    const size_t router = head_workspace_bytes(HeadKind::LowRank, shape, k_route, false);
     if (router == 0) return 0;
     const size_t n = (size_t)shape->rows * k_route;
     return align_up(router) + align_up(4 * n) + align_up(4 * n) + align_up(4 * n * routed_slices(shape->d));
@@ -452,7 +481,7 @@ int run_routed(const void *h, const void *A, const void *B, const void *Bt, cons
     if (!aligned16(W)) return SLIMSPEC_UNSUPPORTED;
     if (workspace_bytes < routed_workspace_bytes(shape, k_route)) return SLIMSPEC_WORKSPACE_TOO_SMALL;
     char *ws = static_cast<char *>(workspace);
-    const size_t router = align_up(head_workspace_bytes(HeadKind::LowRank, shape, k_route));
+    const size_t router = align_up(head_workspace_bytes(HeadKind::LowRank, shape, k_route, false));
     const size_t n = (size_t)shape->rows * k_route;
     int32_t *route_ids = reinterpret_cast<int32_t *>(ws + router);
     float *route_lp = reinterpret_cast<float *>(ws + router + align_up(4 * n));

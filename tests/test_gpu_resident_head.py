@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 
 from paper_2605_10453_amd import synth
+from parity_util import compare_with_oracle, to_dev_bf16
 from plan_util import assert_plan
 from test_gpu_parity import check_low_rank, gpu  # noqa: F401  (the module's fixture)
 
@@ -59,3 +60,21 @@ def test_ranks_in_two_pieces(gpu, oracle_mod, rows, kernel, r, V):
         err = np.abs(g_lp - ora.logprobs).max()
         print(f"r={r} rows={rows} largest error {err:.2e}", flush=True)
         assert err <= 1.1e-3, err
+
+
+@pytest.mark.parametrize("rows,d,r,V,k", [(513, 64, 264, 2056, 6), (700, 64, 520, 4104, 10), (1100, 64, 264, 2056, 6), (1540, 64, 40, 1032, 12), (600, 64, 1024, 2056, 16)])
+def test_two_launches_share_a_down_projection(gpu, oracle_mod, rows, d, r, V, k):
+    """More rows than one launch takes: with the workspace that the query names the down-projection serves two launches at once, with what
+    512 rows need one; the last launch of a call, and of a pair, has 1 to 512 rows."""
+    torch, b = gpu
+    x = synth.make_inputs(synth.small_config(rows, d, r, V, k, peaked_every=6), seed=rows + r)
+    ora = oracle_mod.slimspec_head_topk(x.h, x.A, x.B, k)
+    z_at = lambda ri, ci: oracle_mod.slimspec_logits_at(x.h, x.A, x.B, ri, ci)
+    for n in (rows, 512):
+        size = b.slimspec_workspace_bytes(n, d, r, V, k)
+        ws = torch.full((size + 256,), 0x5a, dtype=torch.uint8, device="cuda")
+        print(f"rows={rows} workspace of {n} rows: {size} bytes", flush=True)
+        ids, lp = b.slimspec_head_topk(to_dev_bf16(x.h), to_dev_bf16(x.A), to_dev_bf16(x.B), k, workspace=ws[:size])
+        torch.cuda.synchronize()
+        compare_with_oracle(ids.cpu().numpy(), lp.cpu().numpy(), ora.ids, ora.lse, z_at, V)
+        assert (ws[size:] == 0x5a).all()
