@@ -193,9 +193,10 @@ __device__ __forceinline__ void wave_topk(const uint32_t (&ob)[E], int n_e, Id i
 //
 // Top-k: wave_topk.  Lane = columns 2 lane, 2 lane + 1 of every 128; E: elements per lane, 2 for every 128 columns begun (known when
 // compiled, or every step branches).
+// TOPK, DRAW: which of the two parts this call makes (a sampling call gives them to two wavefronts where the block has one to spare).
 // part_smp (may be null): the chunk's best z_v + g_v with standard Gumbel noise g (Gumbel-max sampling), as
 // (z + g, id, z, -) of the winner; gk: the noise key of this row.
-template <int E>
+template <int E, bool TOPK, bool DRAW>
 __device__ __forceinline__ void chunk_row_epilogue(const float *sums, int n, int stride, int cw, int chunk_col, int V, int lane, int k,
                                                    uint64_t *sel, size_t slot,
                                                    float2 *__restrict__ part_ms, float *__restrict__ part_val,
@@ -227,7 +228,7 @@ __device__ __forceinline__ void chunk_row_epilogue(const float *sums, int n, int
         z[e] = s.x; z[e + 1] = s.y;
     }
 
-    if (part_smp) {
+    if (DRAW && part_smp) {
         // keys are unique (one per id), so exactly one lane holds the wavefront's largest
         uint64_t best = kNoKey;
         float zb = 0.f;
@@ -241,6 +242,7 @@ __device__ __forceinline__ void chunk_row_epilogue(const float *sums, int n, int
         if (best != kNoKey && best == top)
             part_smp[slot] = make_float4(key_value(top), __int_as_float((int)key_tiebreak(top)), zb, 0.f);
     }
+    if constexpr (!TOPK) return;
     float lm = z[0];
 #pragma unroll
     for (int e = 1; e < E; ++e) lm = fmaxf(lm, z[e]);
