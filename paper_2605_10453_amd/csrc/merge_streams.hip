@@ -148,10 +148,14 @@ __device__ __forceinline__ void rank_all_pairs_wide(const uint64_t *keys, int n,
 
 }  // namespace
 
-// so.on (sampling calls): the records have rec_stride = kStreamRecSample floats and also carry upper bounds of z + g (Gumbel noise) for
+// DRAW (sampling calls): the records have rec_stride = kStreamRecSample floats and also carry upper bounds of z + g (Gumbel noise) for
 // every stream: its two best groups (bound and member, second largest bound) and the best bound of all others.  The bound takes the
 // place of the noise itself in the head kernel, so here a recorded member's noise is put in its place; every member that could then
-// be the largest, and all members of a group whose second largest bound could, are evaluated exactly.
+// be the largest, and all members of a group whose second largest bound could, are evaluated exactly.  An instance of its own: this kernel's
+// time is the length of its instruction chain, and the draw's scalar registers and arrays in one instance for all calls cost those without
+// draws 0.5 to 1 us (us a call, one instance / two: 311 rows, d = 3952, r = 488, V = 26000 61.9 / 59.4; 161 rows, d = 2016, r = 128, V = 102000 42.6 / 41.5;
+// 476 rows, d = 1120, r = 128, V = 46000 39.4 / 38.4).
+template <bool DRAW>
 __global__ __launch_bounds__(kMergeThreads) void merge_streams_kernel(
     const float *__restrict__ part, int rec_stride, int nsr, int gw, int n_vt,
     int resident,       // 0: records of head_tile_kernel, 1: of head_resident_kernel
@@ -328,7 +332,7 @@ __global__ __launch_bounds__(kMergeThreads) void merge_streams_kernel(
                 }
                 const uint64_t key = make_key(z[e], (uint32_t)(col + e));
                 if (key > thr) work[atomicAdd(&cnt_buf, 1u)] = key;     // at most k + 4 NT = kExhaustCap entries: fits
-                if (so.on) {
+                if constexpr (DRAW) {
                     const uint64_t skey = make_key(z[e] + gumbel_base2(gk, (uint32_t)(col + e)) * kLn2, (uint32_t)(col + e));
                     if (skey > sbest) { sbest = skey; sbest_z = z[e]; }
                 }
@@ -366,7 +370,7 @@ __global__ __launch_bounds__(kMergeThreads) void merge_streams_kernel(
         out_ids[(size_t)row * k + tid] = id_map ? id_map[id] : id;
         out_logprobs[(size_t)row * k + tid] = key_value(work[tid]) - lse_exact;
     }
-    if (so.on) {
+    if constexpr (DRAW) {
         float zs;
         const uint64_t top = block_best(sbest, sbest_z, zs);
         write_sample(top, zs, lse_exact);
@@ -508,7 +512,7 @@ __global__ __launch_bounds__(kMergeThreads) void merge_streams_kernel(
             out_ids[(size_t)row * k + tid] = id_map ? id_map[tid] : tid;
             out_logprobs[(size_t)row * k + tid] = -__builtin_amdgcn_logf((float)V) * kLn2;
         }
-        if (so.on) {                                        // the draw: the largest noise alone
+        if constexpr (DRAW) {                                        // the draw: the largest noise alone
             uint64_t best = kNoKey;
             for (int v = tid; v < V; v += NT) {
                 const uint64_t key = make_key(gumbel_base2(gk, (uint32_t)v) * kLn2, (uint32_t)v);
@@ -612,7 +616,7 @@ __global__ __launch_bounds__(kMergeThreads) void merge_streams_kernel(
     };
 
     // ---- sampling: the members whose z + g could be the row's largest once the logits are exact
-    if (so.on) {
+    if constexpr (DRAW) {
         // z + g of entry q of a stream (computed logit, true noise); no entry, or not one of the head kernel's: -inf
         const auto entry_value = [&](const float *sp, int q, int &id) {
             const float x = sp[3 * q];
@@ -881,7 +885,7 @@ __global__ __launch_bounds__(kMergeThreads) void merge_streams_kernel(
                 __syncthreads();
             }
         }
-        if (so.on) {                                         // the sampling contenders join the list of columns to evaluate
+        if constexpr (DRAW) {                                         // the sampling contenders join the list of columns to evaluate
             const uint32_t base_n = cnt_need;
             __syncthreads();
             if (base_n + smp_cnt <= (uint32_t)kWorkCap) {
@@ -942,7 +946,7 @@ __global__ __launch_bounds__(kMergeThreads) void merge_streams_kernel(
                 zc[q] = 0.f; zc16[q] = 0.f;
                 const int ent = w_need[g0 + min(wave + q * NWAVES, n_here - 1)];
                 const int it = ent & (kSampleBit - 1);
-                col[q] = Mt + (size_t)((ent & kSampleBit) ? smp_id[it] : w_id[it]) * K;
+                col[q] = Mt + (size_t)(DRAW && (ent & kSampleBit) ? smp_id[it] : w_id[it]) * K;
             }
             for (int j = lane * 8; j < K; j += 512) {        // K is a multiple of 8
                 uint4 wq[CPW];
@@ -979,7 +983,7 @@ __global__ __launch_bounds__(kMergeThreads) void merge_streams_kernel(
             __syncthreads();
             if (tid < n_here) {                                 // tid < 64: `entry` is this column's
                 const float z = z_col[tid];
-                if (entry & kSampleBit) smp_z[entry & (kSampleBit - 1)] = z;
+                if (DRAW && (entry & kSampleBit)) smp_z[entry & (kSampleBit - 1)] = z;
                 else take_exact(entry, z, round16 ? z16_col[tid] : z, Mx);
             }
             __syncthreads();
@@ -988,7 +992,7 @@ __global__ __launch_bounds__(kMergeThreads) void merge_streams_kernel(
             const int u = lane & 15, jsub = lane >> 4;
             const int entry = w_need[min(g0 + u, n_need - 1)];
             const int item = entry & (kSampleBit - 1);
-            const int id = (entry & kSampleBit) ? smp_id[item] : w_id[item];
+            const int id = DRAW && (entry & kSampleBit) ? smp_id[item] : w_id[item];
             // (the second sum only in a batch that holds a column without a recorded value: every wavefront sees the same
             // 16 entries, so all of them decide alike)
             const bool batch16 = with16 && __ballot((entry & (kListedBit | kSampleBit)) == 0) != 0ull;
@@ -1030,7 +1034,7 @@ __global__ __launch_bounds__(kMergeThreads) void merge_streams_kernel(
                 float z = red_ex[0][tid], z16 = red_ex16[0][tid];
 #pragma unroll
                 for (int w = 1; w < NWAVES; ++w) { z += red_ex[w][tid]; z16 += red_ex16[w][tid]; }
-                if (entry & kSampleBit) smp_z[item] = z;
+                if (DRAW && (entry & kSampleBit)) smp_z[item] = z;
                 else take_exact(entry, z, batch16 ? z16 : z, Mx);     // tid < 16: u == tid, so `entry` is this column's
             }
             __syncthreads();
@@ -1039,7 +1043,7 @@ __global__ __launch_bounds__(kMergeThreads) void merge_streams_kernel(
         if (!eps_violated) {
             uint64_t skey = kNoKey;
             float sz = 0.f;
-            if (so.on) {                                     // the draw: the contenders' exact logits plus their noise
+            if constexpr (DRAW) {                                     // the draw: the contenders' exact logits plus their noise
                 uint64_t mine = kNoKey;
                 float zm = 0.f;
                 if (tid < (int)smp_cnt) {
@@ -1049,7 +1053,7 @@ __global__ __launch_bounds__(kMergeThreads) void merge_streams_kernel(
                 skey = block_best(mine, zm, sz);
             }
             finish(n_work, S, Mx, lse);
-            if (so.on) {
+            if constexpr (DRAW) {
                 __syncthreads();
                 write_sample(skey, sz, lse_out_sh);
             }
@@ -1127,23 +1131,26 @@ hipError_t launch_merge_streams(const float *part, int rows, int nsr, int gw, in
 {
     // + the row's contraction input, exact and, where it was rounded, as rounded
     const size_t lds = merge_streams_lds_bytes(nsr, n_vt) + (operand != kOperandExact ? 2 : 1) * sizeof(float) * (size_t)K;
-    static LdsLimit lds_limit;
-    hipError_t e = lds_limit.raise(reinterpret_cast<const void *>(merge_streams_kernel), (int)lds);
-    if (e != hipSuccess) return e;
-    // sampling calls evaluate in place; with a column-major copy an exact logit is one short read: nothing to park
-    int *defer = (so.on || Mt != nullptr) ? nullptr : static_cast<int *>(defer_buf);
-    const int rec_stride = so.on ? kStreamRecSample : kStreamRec;
-    merge_streams_kernel<<<rows, kMergeThreads, lds, st>>>(part, rec_stride, nsr, gw, n_vt, resident ? 1 : 0, xexact, x_is_bf16 ? 1 : 0, ldx,
-                                                           operand, M, K, V, Mt, stat, n_stat, rows_pad, tilescale, k, unit, tiny_w, out_ids, out_logprobs, id_map,
-                                                           defer, 0, so, row_base);
-    if ((e = hipGetLastError()) != hipSuccess || !defer) return e;
-    // parked rows: their exact columns on many CUs, then the rest of their merge
-    exact_cols_kernel<<<dim3(kDeferSlices, rows), 256, 0, st>>>(defer, xexact, x_is_bf16 ? 1 : 0, ldx, M, K, V);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    merge_streams_kernel<<<rows, kMergeThreads, lds, st>>>(part, rec_stride, nsr, gw, n_vt, resident ? 1 : 0, xexact, x_is_bf16 ? 1 : 0, ldx,
-                                                           operand, M, K, V, Mt, stat, n_stat, rows_pad, tilescale, k, unit, tiny_w, out_ids, out_logprobs, id_map,
-                                                           defer, 1, so, row_base);
-    return hipGetLastError();
+    const auto launch = [&](auto kernel, LdsLimit &lds_limit) -> hipError_t {
+        hipError_t e = lds_limit.raise(reinterpret_cast<const void *>(kernel), (int)lds);
+        if (e != hipSuccess) return e;
+        // sampling calls evaluate in place; with a column-major copy an exact logit is one short read: nothing to park
+        int *defer = (so.on || Mt != nullptr) ? nullptr : static_cast<int *>(defer_buf);
+        const int rec_stride = so.on ? kStreamRecSample : kStreamRec;
+        const auto merge = [&](int resume) {
+            kernel<<<rows, kMergeThreads, lds, st>>>(part, rec_stride, nsr, gw, n_vt, resident ? 1 : 0, xexact, x_is_bf16 ? 1 : 0, ldx,
+                                                     operand, M, K, V, Mt, stat, n_stat, rows_pad, tilescale, k, unit, tiny_w, out_ids, out_logprobs, id_map,
+                                                     defer, resume, so, row_base);
+            return hipGetLastError();
+        };
+        if ((e = merge(0)) != hipSuccess || !defer) return e;
+        // parked rows: their exact columns on many CUs, then the rest of their merge
+        exact_cols_kernel<<<dim3(kDeferSlices, rows), 256, 0, st>>>(defer, xexact, x_is_bf16 ? 1 : 0, ldx, M, K, V);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        return merge(1);
+    };
+    static LdsLimit lds_limit, lds_limit_draw;
+    return so.on ? launch(merge_streams_kernel<true>, lds_limit_draw) : launch(merge_streams_kernel<false>, lds_limit);
 }
 
 }  // namespace slimspec

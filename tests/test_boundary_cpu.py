@@ -130,6 +130,11 @@ def test_kernels_use_no_scratch_memory(source, kernel):
     found = [(n, int(sz)) for n, sz in zip(names, scratch) if kernel in n]
     assert len(found) >= 1, text[-2000:]
     assert all(sz == 0 for _, sz in found), found
+    if kernel == "merge_streams_kernel":
+        # calls without draws run an instance of their own that keeps nothing of the draw (its contenders alone are 512 bytes)
+        shared = re.findall(r"LDS Size \[bytes/block\]: (\d+)", text)
+        with_draw, without = ([int(sz) for n, sz in zip(names, shared) if kernel + "ILb%dE" % draw in n] for draw in (1, 0))
+        assert len(with_draw) == len(without) == 1 and without[0] + 512 <= with_draw[0], list(zip(names, shared))
 
 
 @pytest.mark.parametrize("source,kernel", [("head_resident.hip", "head_resident_kernel"), ("head_tile.hip", "head_tile_kernel")])
