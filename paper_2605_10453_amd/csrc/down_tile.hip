@@ -131,7 +131,7 @@ __device__ __forceinline__ void column_scale_block(const uint16_t *__restrict__ 
     }
 }
 
-// part [slices][n_rt][n_ct][4 wavefronts][16][64] fp32: the accumulators as the wavefronts hold them; wavefront
+// part [slices][n_rt][n_ct][4 wavefronts][16][64] fp32, a second launch's behind the first's: the accumulators as the wavefronts hold them; wavefront
 // (wr, wc) of tile (rt, ct) owns rows 64 rt + 32 wr + lane % 32 and, for element i, column
 // 64 ct + 32 wc + 8 (i / 4) + 4 (lane / 32) + i % 4.
 // Block g works on XCD g % 8 (each XCD has its own L2): slices are dealt to the XCDs first, so that an XCD reads
@@ -142,7 +142,7 @@ __device__ __forceinline__ void column_scale_block(const uint16_t *__restrict__ 
 template <bool STEPWISE, bool ROWS>
 __global__ __launch_bounds__(256) void down_tile_kernel(
     const uint16_t *__restrict__ h, const uint16_t *__restrict__ A, float *__restrict__ part,
-    int d, int r, DownGrid g)
+    int d, int r, int blocks_first, DownGrid g)
 {
     extern __shared__ __align__(1024) unsigned char lds_raw[];
     const uint32_t lds0 = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) unsigned char *)lds_raw);
@@ -151,14 +151,19 @@ __global__ __launch_bounds__(256) void down_tile_kernel(
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wr = wave >> 1, wc = wave & 1;
 
+    // this block's launch of the two that share the grid: its slices, its row tiles [rt_beg, rt_beg + n_rt), its partial tiles
+    const bool second = (int)blockIdx.x >= blocks_first;
+    const int slices = second ? g.slices_second : g.slices;
+    const int rt_beg = second ? g.rt_second : 0, n_rt = second ? g.n_rt - g.rt_second : g.rt_second;
     int slice, tile;
     {
-        const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-        if (g.slices >= 8) { slice = xcd + 8 * (slot % (g.slices >> 3)); tile = slot / (g.slices >> 3); }
-        else { slice = xcd % g.slices; tile = xcd / g.slices + (8 / g.slices) * slot; }
+        const int b = (int)blockIdx.x - (second ? blocks_first : 0);      // (blocks_first is a multiple of 8)
+        const int xcd = b & 7, slot = b >> 3;
+        if (slices >= 8) { slice = xcd + 8 * (slot % (slices >> 3)); tile = slot / (slices >> 3); }
+        else { slice = xcd % slices; tile = xcd / slices + (8 / slices) * slot; }
     }
-    if (tile >= g.n_rt * g.n_ct) return;
-    const int rt = tile % g.n_rt, ct = tile / g.n_rt;
+    if (tile >= n_rt * g.n_ct) return;
+    const int rt = rt_beg + tile % n_rt, ct = tile / n_rt;
     int grp = 0;                                               // the group of rows (one down-projection matrix) this row tile belongs to
     while (grp + 1 < g.n_groups && rt >= g.g_tile0[grp + 1]) ++grp;
     const int row0 = g.g_row0[grp] + (rt - g.g_tile0[grp]) * kDT, n0 = ct * kDT;
@@ -172,7 +177,7 @@ __global__ __launch_bounds__(256) void down_tile_kernel(
 
     // stages [s_beg, s_end); the last stage of all may hold 8, 16 or 24 elements only (see `ragged`)
     const int n_stages = (d + kDKB - 1) / kDKB;
-    const int per = (n_stages + g.slices - 1) / g.slices;
+    const int per = (n_stages + slices - 1) / slices;
     const int s_beg = min(n_stages, slice * per), s_end = min(n_stages, s_beg + per);
     const int nst = (n0 < r) ? s_end - s_beg : 0;                         // columns of padding load nothing
     if (nst > 0) {
@@ -269,7 +274,8 @@ __global__ __launch_bounds__(256) void down_tile_kernel(
                                                                        acc0[4 * q + 2] + acc1[4 * q + 2], acc0[4 * q + 3] + acc1[4 * q + 3]);
         return;
     }
-    float *dst = part + ((((size_t)slice * g.n_rt + rt) * g.n_ct + ct) * 4 + wave) * (16 * 64) + lane;
+    if (second) part += (size_t)g.slices * g.rt_second * g.n_ct * (4 * 16 * 64);
+    float *dst = part + ((((size_t)slice * n_rt + (rt - rt_beg)) * g.n_ct + ct) * 4 + wave) * (16 * 64) + lane;
 #pragma unroll
     for (int i = 0; i < 16; ++i) dst[i * 64] = acc0[i] + acc1[i];
 }
@@ -306,12 +312,14 @@ __global__ __launch_bounds__(256) void down_finish_kernel(
     const int rows = (grp < g.n_groups) ? row_end : 0;         // rows that carry values
 
     // the slices, in order: several loads of a thread are in flight together (they come from other CUs' writes)
-    const size_t slice_stride = (size_t)g.n_rt * g.n_ct * 4 * (16 * 64);
-    const float *src = part + (((size_t)rt * g.n_ct + ct) * 4 + w) * (16 * 64);
+    const bool second = rt >= g.rt_second;
+    const size_t slice_stride = (size_t)(second ? g.n_rt - g.rt_second : g.rt_second) * g.n_ct * 4 * (16 * 64);
+    const float *src = part + (((size_t)(rt - (second ? g.rt_second : 0)) * g.n_ct + ct) * 4 + w) * (16 * 64);
+    if (second) src += (size_t)g.slices * g.rt_second * g.n_ct * (4 * 16 * 64);
     // a thread owns four (i, lane) pairs of the accumulator layout; the loads of SB slices of all four are in flight together
     constexpr int SB = 8;
     float v4[4] = {0.f, 0.f, 0.f, 0.f};
-    const int n_slices = grp < g.n_groups ? g.slices : 0;
+    const int n_slices = grp < g.n_groups ? (second ? g.slices_second : g.slices) : 0;
     for (int s0 = 0; s0 < n_slices; s0 += SB) {
         float x[SB][4];
 #pragma unroll
@@ -417,10 +425,10 @@ static hipError_t launch_down_tiles(const uint16_t *h, const uint16_t *A, float 
     static LdsLimit lds_limit;
     hipError_t e = lds_limit.raise(reinterpret_cast<const void *>(down_tile_kernel<STEPWISE, ROWS>), kDLds);
     if (e != hipSuccess) return e;
-    const int tiles = g.n_rt * g.n_ct;
     // slices >= 8: every XCD has slices / 8 slices of every tile; fewer: 8 / slices XCDs share a slice and split the tiles
-    const int blocks = g.slices >= 8 ? tiles * g.slices : 8 * ((tiles + 8 / g.slices - 1) / (8 / g.slices));
-    down_tile_kernel<STEPWISE, ROWS><<<blocks, 256, kDLds, st>>>(h, A, part, d, r, g);
+    const auto blocks = [](int tiles, int slices) { return slices >= 8 ? tiles * slices : 8 * ((tiles + 8 / slices - 1) / (8 / slices)); };
+    const int first = blocks(g.rt_second * g.n_ct, g.slices), second = blocks((g.n_rt - g.rt_second) * g.n_ct, g.slices_second);
+    down_tile_kernel<STEPWISE, ROWS><<<first + second, 256, kDLds, st>>>(h, A, part, d, r, first, g);
     return hipGetLastError();
 }
 

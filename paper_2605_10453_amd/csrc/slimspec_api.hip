@@ -67,9 +67,10 @@ size_t mfma_workspace_bytes(HeadKind kind, const slimspec_shape *s)
 }
 
 // Low-rank calls of more than one launch: the down-projection serves two launches at once where the workspace has room for their rows (one
-// read of A and of the column samples instead of two, and no half-empty round of blocks; two / one, us a call: 700 rows in six positions 177.4 / 161.4,
+// read of A and of the column samples instead of two, and no half-empty round of blocks; two / one, us a call: 700 rows in six positions 177.3 / 160.2,
 // 600 rows, d = 1024, r = 128, V = 32000 74.6 / 67.9, 537 rows, d = 4816, r = 664, prepared 204.0 / 191.0).
-// The query asks for the room; a workspace that only fits launch by launch, the static scratch of the largest shapes too, still serves.
+// The query asks for the room; a workspace that only fits launch by launch, the static scratch of the largest shapes too, still serves, with
+// the same results: a launch's rows keep its slices (plan.hpp: join_down_grids).
 size_t mfma_joint_workspace_bytes(HeadKind kind, const slimspec_shape *s)
 {
     const int joint = mfma_joint_rows(kind, s->rows);
@@ -141,7 +142,11 @@ int run_head_mfma(HeadKind kind, const void *h, const void *A, const void *M, co
         const int rows_joint = (shape->rows - first < joint) ? shape->rows - first : joint;
         // the scratch arrays of all these rows; a last, smaller batch may fall below the matrix-core threshold, and still runs here
         MfmaPlan all = make_mfma_plan(kind, rows_joint, d, r, V);
-        if (kind == HeadKind::LowRank && pos.n > 0) all.down = down_grid_by_position(pos, first, rows_joint, all.rows_pad, d, r);
+        if (kind == HeadKind::LowRank && pos.n > 0) {
+            const int n = rows_joint < per ? rows_joint : per;
+            all.down = down_grid_by_position(pos, first, n, rows_joint > n ? n : all.rows_pad, d, r);
+            if (rows_joint > n) all.down = join_down_grids(all.down, down_grid_by_position(pos, first + n, rows_joint - n, all.rows_pad - n, d, r));
+        }
         float *streams = reinterpret_cast<float *>(ws + all.off_streams);
         void *defer = all.defer ? ws + all.off_defer : nullptr;
         hipError_t e;

@@ -78,3 +78,30 @@ def test_two_launches_share_a_down_projection(gpu, oracle_mod, rows, d, r, V, k)
         torch.cuda.synchronize()
         compare_with_oracle(ids.cpu().numpy(), lp.cpu().numpy(), ora.ids, ora.lse, z_at, V)
         assert (ws[size:] == 0x5a).all()
+
+
+@pytest.mark.parametrize("sizes,d,r,V,k", [((700,), 1024, 512, 2056, 10), ((600,), 2056, 136, 4104, 7), ((1024,), 1024, 512, 2056, 16), ((1100,), 520, 264, 1032, 12),
+                                           ((300, 250, 50), 1024, 264, 2056, 5), ((512, 1, 0, 187), 1024, 512, 2056, 10)])
+def test_results_do_not_depend_on_the_workspace(gpu, oracle_mod, sizes, d, r, V, k):
+    """A row's down-projection is cut into the same slices, added in the same order, whether two launches share it or not: a workspace
+    that fits one launch at a time, the library's own scratch and the query's workspace give the same bits."""
+    torch, b = gpu
+    rows = sum(sizes)
+    x = synth.make_inputs(synth.small_config(rows, d, r, V, k, peaked_every=6), seed=rows + d)
+    h, A, B = to_dev_bf16(x.h), to_dev_bf16(x.A), to_dev_bf16(x.B)
+    off = [sum(sizes[:p]) for p in range(len(sizes) + 1)]
+    stack = torch.stack([A.roll(p, 0) for p in range(len(sizes))])
+
+    def run(n):
+        ws = torch.full((b.slimspec_workspace_bytes(n, d, r, V, k),), 0x5a, dtype=torch.uint8, device="cuda")
+        if len(sizes) == 1:
+            return b.slimspec_head_topk(h, A, B, k, workspace=ws)
+        return b.slimspec_head_topk_positions(h, stack, off, B, k, workspace=ws)
+
+    print(f"workspaces of 512 and {rows} rows, d={d} r={r}", flush=True)
+    outs = [run(rows), run(512)]
+    if len(sizes) == 1:
+        outs.append(b.slimspec_head_topk_static(h, A, B, k))
+    torch.cuda.synchronize()
+    for ids, lp in outs[1:]:
+        assert torch.equal(ids, outs[0][0]) and torch.equal(lp.view(torch.int32), outs[0][1].view(torch.int32))
