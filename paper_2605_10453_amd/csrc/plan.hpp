@@ -288,6 +288,11 @@ struct MfmaPlan {
 // rows here is the number of rows of ONE launch (at most kPlanSlotsPerXcd row blocks), or of two that share a down-projection: the grids
 // are then of no use, but the scratch serves both.
 constexpr int kMaxLaunchRows = 512;
+// The largest hidden size and rank of the low-rank head: down_tile_kernel's 32-bit byte offsets reach over the rows of h of two launches
+// and over the 32 rows of a stage of A.
+constexpr int kMaxHidden = 1 << 21, kMaxRank = 1 << 24;
+static_assert(2ll * kMaxLaunchRows * 2 * kMaxHidden <= 1ll << 32, "offsets into the rows of h");
+static_assert(32ll * 2 * kMaxRank <= 1ll << 32, "offsets into a stage of A");
 inline MfmaPlan make_mfma_plan(HeadKind kind, int rows, int d, int r, int V) {
     MfmaPlan p;
     p.rows = rows;

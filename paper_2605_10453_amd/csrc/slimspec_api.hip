@@ -45,8 +45,8 @@ int check_shape(HeadKind kind, const slimspec_shape *s, int32_t k)
     // kResidentMaxV) and of an element of A (d * r).
     if ((int64_t)s->V > (int64_t)1 << 28) return SLIMSPEC_UNSUPPORTED;
     if (kind == HeadKind::LowRank && (int64_t)s->d * s->r >= (int64_t)1 << 31) return SLIMSPEC_UNSUPPORTED;
-    // ... and of a row of h inside one launch's 512 rows, and of 32 rows of A (the many-row down-projection)
-    if (kind == HeadKind::LowRank && (s->d > (1 << 21) || s->r > (1 << 24))) return SLIMSPEC_UNSUPPORTED;
+    // ... and those of the many-row down-projection
+    if (kind == HeadKind::LowRank && (s->d > kMaxHidden || s->r > kMaxRank)) return SLIMSPEC_UNSUPPORTED;
     if (!lists_supported(s->rows, s->V, k)) return SLIMSPEC_UNSUPPORTED;
     return SLIMSPEC_OK;
 }
