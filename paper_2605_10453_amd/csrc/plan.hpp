@@ -508,6 +508,6 @@ inline Operand tile_operand(int r, int k, bool prepared) {
 }
 
 // head_resident_kernel instead of head_tile_kernel: bf16 operands.
-inline bool resident_takes(const MfmaPlan &p, bool f16_operand, bool /*sampling*/) { return p.resident && !f16_operand; }
+inline bool resident_takes(const MfmaPlan &p, bool f16_operand) { return p.resident && !f16_operand; }
 
 }  // namespace slimspec

@@ -167,7 +167,7 @@ int run_head_mfma(HeadKind kind, const void *h, const void *A, const void *M, co
             float *lps = out_logprobs + (size_t)row0 * k;
             if (kind == HeadKind::LowRank) {
                 if (timed && (e = hipEventRecord(g_ev_start, s)) != hipSuccess) return fail_hip(e);
-                const bool resident = resident_takes(p, operand == kOperandF16, so.on != 0);
+                const bool resident = resident_takes(p, operand == kOperandF16);
                 const void *x = ws + all.off_t16 + 16 * (size_t)at;
                 e = resident ? launch_head_resident(x, operand, Mb, streams, rows, all.rows_pad, r, V, p.res, so, row0, s)
                              : launch_head_tile(x, operand, Mb, streams, rows, all.rows_pad, r, V, p.n_rb, p.gw, so, row0, s);

@@ -17,7 +17,7 @@ int main()
         const HeadKind kind = std::strcmp(kind_name, "full") == 0 ? HeadKind::Full : HeadKind::LowRank;
         const bool low_rank = kind == HeadKind::LowRank;
         const MfmaPlan p = make_mfma_plan(kind, mfma_max_rows_per_launch(rows), d, r, V);
-        const bool f16 = low_rank && tile_operand_f16(k, prepared != 0), resident = resident_takes(p, f16, sampling != 0);
+        const bool f16 = low_rank && tile_operand_f16(k, prepared != 0), resident = resident_takes(p, f16);
         const bool rows_path = !fp32 && rows_path_takes(kind, rows, d, r, V, k, prepared != 0, sampling != 0);
         const char *kernel = rows_path ? "rows" : fp32 || !tile_path_takes(rows, k) ? "stream" : resident ? "resident" : "tile";
         const ChunkGeom g = make_chunk_geom(kind, rows, low_rank ? r : d, V);
