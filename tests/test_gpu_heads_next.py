@@ -190,15 +190,18 @@ def test_full_head_sample(gpu, oracle_mod, rows, w_f32):
 
 
 @pytest.mark.parametrize("where", ["one group", "groups of one lane", "tiles of one block", "lanes"])
-@pytest.mark.parametrize("rows,head,k", [(60, "full", 5), (140, "full", 9), (60, "low", 5), (140, "low", 16)])
-def test_contenders_for_a_draw_that_share_a_record(gpu, oracle_mod, rows, head, k, where):
+@pytest.mark.parametrize("rows,head,k,d,kernel,f16", [
+    (60, "full", 5, 64, "tile", 0), (140, "full", 9, 64, "tile", 0), (60, "low", 5, 64, "tile", 0), (140, "low", 16, 64, "tile", 1),
+    (140, "low", 9, 64, "resident", 0), (140, "low", 9, 128, "resident", 0)])       # ... on two bf16 pieces, on one
+def test_contenders_for_a_draw_that_share_a_record(gpu, oracle_mod, rows, head, k, d, kernel, f16, where):
     """Five columns whose z + g lie within 0.06 of each other and far above the rest: members of one group of 16 logits, of groups
     that one lane holds (more than it lists: the row is done exhaustively), or apart.  What the matrix-core kernel records are bounds
     that are up to 0.13 too large, so the draw rests on the exact values that the merge puts in their place."""
     torch, b = gpu
-    V, d, seed = 20000, 64, 9                                  # (head_resident_kernel: 256 column blocks, tiles of 64 columns)
-    if head == "low":
-        assert_plan("low", rows, d, d, V, k, sampling=True, kernel="resident" if rows == 140 and k <= 12 else "tile")
+    V, seed = 20000, 9
+    assert_plan(head, rows, d, d, V, k, sampling=True, kernel=kernel, f16=f16)
+    if kernel == "resident":                                   # ("tiles of one block": its block 5 works on tiles 5 and 261 of 64 columns)
+        assert_plan(head, rows, d, d, V, k, sampling=True, col_blocks=256, records=2)
     x = synth.make_inputs(synth.small_config(rows, d, 8, V, k), seed=31, with_full_head=True)
     W = x.W.copy()
     cols = {"one group": [2048 + 32 * 3 + c for c in (0, 1, 2, 3, 9)], "groups of one lane": [2048 + 32 * j for j in range(4)] + [2049],

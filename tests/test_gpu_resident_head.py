@@ -7,6 +7,7 @@ import pytest
 from paper_2605_10453_amd import synth
 from parity_util import compare_with_oracle, to_dev_bf16
 from plan_util import assert_plan
+from test_gpu_heads_next import check_sample_outputs
 from test_gpu_parity import check_low_rank, gpu  # noqa: F401  (the module's fixture)
 
 pytestmark = pytest.mark.gpu
@@ -105,3 +106,20 @@ def test_results_do_not_depend_on_the_workspace(gpu, oracle_mod, sizes, d, r, V,
     torch.cuda.synchronize()
     for ids, lp in outs[1:]:
         assert torch.equal(ids, outs[0][0]) and torch.equal(lp.view(torch.int32), outs[0][1].view(torch.int32))
+
+
+@pytest.mark.parametrize("rows,d,r,V,k,kernel", [(513, 64, 40, 2056, 5, "resident"), (700, 520, 264, 4104, 10, "resident"), (700, 64, 520, 2056, 7, "tile"), (1100, 64, 72, 1032, 12, "resident")])
+def test_draws_of_more_rows_than_one_launch(gpu, oracle_mod, rows, d, r, V, k, kernel):
+    """The noise is a function of the row's index in the call, in every launch, with and without a shared down-projection."""
+    torch, b = gpu
+    assert_plan("low", rows, d, r, V, k, sampling=True, kernel=kernel)
+    x = synth.make_inputs(synth.small_config(rows, d, r, V, k, peaked_every=6), seed=rows + r)
+    ora = oracle_mod.head_sample(x.h, x.A, x.B, k, 2 ** 35 + 11, return_logits=True)
+    outs = []
+    for n in (rows, 512):
+        ws = torch.full((b.slimspec_workspace_bytes(n, d, r, V, k),), 0x5a, dtype=torch.uint8, device="cuda")
+        print(f"draws of {rows} rows, workspace of {n}", flush=True)
+        outs.append(b.slimspec_head_sample(to_dev_bf16(x.h), to_dev_bf16(x.A), to_dev_bf16(x.B), k, 2 ** 35 + 11, workspace=ws))
+        torch.cuda.synchronize()
+        check_sample_outputs(torch, outs[-1], ora, 2 ** 35 + 11, V, ora.z, oracle_mod)
+    assert all(torch.equal(p.view(torch.int32), q.view(torch.int32)) for p, q in zip(*outs))
