@@ -28,8 +28,8 @@
  * absolute accuracy is that of fp32 at the magnitude of the logits (about 1e-3 at logits
  * of a few thousand, 1e-1 at 1e5), whatever the path.  With up to 48 rows (32 where the
  * caller passes prepared weights and does not sample and r > 64), and for k > 16, t = h A stays in fp32
- * throughout (r <= 2048; beyond, up to four rows).  With more rows the matrix cores take a 16-bit t (bf16, or f16 for k > 12) for the sum of
- * exponentials and for finding the candidates; every candidate whose rank or reported
+ * throughout (r <= 2048; beyond, up to four rows).  With more rows the matrix cores take a 16-bit t (bf16, or f16 for k > 12; for
+ * r <= 64 and bf16, t's sixteen leading bits) for the sum of exponentials and for finding the candidates; every candidate whose rank or reported
  * value could depend on that rounding is then evaluated again from the fp32 t.
  *
  * Ownership / asynchrony: every pointer is caller-owned; the library allocates and

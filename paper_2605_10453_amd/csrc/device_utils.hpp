@@ -251,7 +251,9 @@ __device__ __forceinline__ float gumbel_base2(const GumbelKey &key, uint32_t id)
 }
 // An upper bound of it for four instructions behind the hash instead of twenty: kGumbelBoundBase - kGumbelBoundScale * gumbel_bound_bits().
 // With n' = x >> 9 << 9 as a float, n' / 2^32 < u < E, and a float's bits are its base-2 logarithm with the mantissa as a straight
-// line, which lies below it.  For a small u, i.e. noise that can decide a draw, the bound is at most 0.086 + 0.7 / (n + 1) too large.
+// line, which lies below it.  For u < 1/32, i.e. noise that can decide a draw, the bound is at most 0.103 + log2(1 + 1 / (2 n)) too large:
+// 0.69 for n = 1, 0.2 for n = 6.  n = 0 (one id in 2^23) has no such logarithm: its bound is 159, 135 too large, and the id's group
+// takes the first place of its list whatever its logit is (the merge has the noise itself; the list is a place shorter).
 constexpr float kGumbelBoundBase = 159.f;               // 32 for the scale of x, 127 for the exponent's bias
 constexpr float kGumbelBoundScale = 1.1920928955078125e-7f;      // 2^-23
 __device__ __forceinline__ float gumbel_bound_bits(uint32_t x) { return (float)(int)__float_as_uint((float)(x & 0xfffffe00u)); }

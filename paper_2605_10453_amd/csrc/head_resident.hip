@@ -20,8 +20,8 @@
 // before the first MFMA: 256 KB of row operand per CU at the 30 bytes per cycle a CU takes in.
 //
 // Sampling: the draw's bounds are 22 vector instructions per logit, more than all the rest, and run between the MFMAs too: 512 rows, r = 512
-// 108 us by the profiler, 154 in head_tile_kernel with the noise itself; calls 222.2 (there; 182 with bounds) -> 159.1 us, 300 rows, r = 256,
-// prepared 152.2 -> 100.5.
+// 97 to 112 us by the profiler, 154 in head_tile_kernel with the noise itself; calls 223.3 (there; 182 with bounds) -> 159.6 us, with a row
+// whose best groups crowd into one record 223.4 -> 222.3 (prepared 197.3 -> 136.2 and 197.8 -> 188.5); 300 rows, r = 256, prepared 152.2 -> 100.5.
 //
 // Weights: stages of 128 contraction elements x 64 columns (16 KB) travel global memory -> LDS without passing registers
 // (global_load_lds_dwordx4), eight stage buffers.  The 16-byte pieces of a 128-byte stage row are stored XOR-swizzled by

@@ -92,6 +92,7 @@ __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)
 // SAMPLE: every lane also keeps, per row, what the Gumbel-max draw needs (head_stream.hpp: SampleTrack; the seed is in `sd`, the
 //         noise's row index is sd.row_base + the row of this launch); records then have 20 floats: [12] [13] [14] bound, second
 //         largest bound and name of the best group, [15] [16] [17] of the second best, [18] the third best group's bound, [19] unused.
+//         (These instances keep 52 to 56 scalar registers in vector lanes, 23 to 30 with the noise itself; none goes to memory.)
 struct SampleSeed { uint32_t seed_lo, seed_hi; int row_base; };
 
 template <int L, int WR, bool F16, bool NAT, int DBG, bool SAMPLE>

@@ -249,7 +249,8 @@ constexpr int kResidentMaxV = 1 << 24;   // the kernel's 32-bit offsets reach ov
 // block and row, of up to 32 groups at 128 column blocks.  (Four records of 16 groups each make a crowded record, i.e. an
 // exact rescan of its columns, eight times rarer than the one 512-row call in a hundred it is at k = 10, and half as long,
 // but cost every call 4 us.  A call with one such row: 179 us plain, 128 with prepared weights, against 115 and 96 without;
-// head_tile_kernel with four records 148 and 117 against 126 and 105.)
+// head_tile_kernel with four records 148 and 117 against 126 and 105.  With four planted columns 182 and 151 against 119 and 97, and with
+// draws, for which such a row is as likely, 222 and 189 against 160 and 136.)
 struct ResidentGrid { int n_rb = 1, gw = 8, n_t = 0, nsr = 0; };
 inline ResidentGrid make_resident_grid(int n_rb, int V) {
     ResidentGrid g;
@@ -454,15 +455,17 @@ constexpr int kMfmaMinRows = 5;          // below, rows whose calls rows_path_ta
 //     while head_tile_kernel's cost stays the same and its merge is cheap with prepared weights or few candidates.
 //       prepared: 33 rows 51.0 / 54.4, 48 rows 51.5 / 58.9 (r = 1024: 76.8 / 84.1); this kernel only where few tiles of the
 //         vocabulary leave head_tile_kernel long contractions on few CUs (48 rows, r = 2048: V = 32000 74 / 68, V = 8192 68 / 53)
-//         and for the smallest ranks, whose wide rounding bounds send peaked rows to head_tile_kernel's exact passes now and then
-//         (48 rows, r = 64: V = 32000 28.0 / 29.7, V = 128256 211 / 36);
+//         and for the smallest ranks, where the head kernel is short beside its merge of 9 us (60 rows, r = 64, V = 14000: 4 + 4 for t, 9, 9) and
+//         this kernel's merge takes 4 (33 and 48 rows, d = 512: r = 16, V = 8192 26.3 / 15.9 and 26.5 / 17.1, r = 64, V = 32000 28.0 / 18.1 and
+//         29.3 / 19.5, V = 128256 32.5 / 22.2 and 32.7 / 24.1; d = 4096, r = 64, V = 128256 32.6 / 26.6 and 32.7 / 28.0);
 //       plain low-rank calls stay, and with them their fp32 t: 48 rows, k = 10 0.99 to 1.4 times as fast; with k = 3 and r = 256
 //         they give up a little (40 rows, V = 8192 30.9 / 33.1, 48 rows, V = 32000 34.1 / 36.9);
 //       full head, k = 4, 48 rows: d = 256 22.7 / 28.8 at V = 32000, 30.0 / 34.4 at V = 128256; d = 1024 41.8 / 36.0 and 67.3 / 66.3.
 //         The other path's re-evaluated columns cost in proportion to k d, this one's epilogue to V: it is behind up to d = 768 while
 //         k d stays below about 17 sqrt(V) and k below 16 (V = 8192: k = 4, d = 256 22.8 / 26.9, 36 rows, k = 6, d = 512 31.6 / 26.6; V =
 //         128256: k = 10, d = 512 46.1 / 47.0, k = 16 51.8 / 47.4), not with so small a V that head_tile_kernel's blocks are few (d = 768, V = 8192, k = 1 28.3 / 25.3).
-//     Sampling calls stay: the noise is dearer in head_tile_kernel (r = 64, V = 8192, 48 rows 47.2 / 33.4).
+//     Sampling calls stay, prepared ones too: the draw is dearer in head_tile_kernel and its merge (48 rows: r = 64, V = 8192 41.0 / 20.9, r = 256, V = 32000
+//     47.5 / 32.3, r = 512, V = 128256 73.3 / 58.4, prepared 67.8 / 58.5).
 //   * more rows would need a second launch, and lose.
 inline bool rows_path_takes(HeadKind kind, int rows, int d, int r, int V, int k, bool prepared, bool sampling) {
     const bool low_rank = kind == HeadKind::LowRank;
@@ -502,7 +505,8 @@ inline bool tile_operand_f16(int k, bool prepared) {
 // The second piece costs head_resident_kernel, whose contraction is padded to 128, nothing, and head_tile_kernel a stage or two.  (One
 // piece / two, us a call: 375 rows, d = 584, r = 40, V = 64120, prepared 206-289 / 34.7; 129 rows, r = 56, V = 151936, prepared 237.6 / 42.3;
 // 512 rows, d = 1024, r = 64, V = 128256 234.3 / 56.1; 100 rows, r = 24, V = 128256, prepared 241.9 / 31.5; 64 rows, r = 16, V = 8192 66.4 / 28.9,
-// 27.5 where no row finds out; 100 rows, r = 64, V = 32000 33.0 / 32.5.  From r = 72 on none of some 20 calls found out.)
+// 27.5 where no row finds out; 60 rows, r = 64, V = 14000, prepared, none finds out, 27.4 / 28.2; 100 rows, r = 64, V = 32000 33.0 / 32.5.  From r = 72
+// on none of some 20 calls found out.  Relative error of the log-probabilities against 64 bits, a dozen calls: 1.2e-4 to 2.5e-4 / 4e-7 to 9e-7.)
 inline Operand tile_operand(int r, int k, bool prepared) {
     return tile_operand_f16(k, prepared) ? kOperandF16 : r <= kTwoPiecesMaxRank ? kOperandTwoBf16 : kOperandBf16;
 }

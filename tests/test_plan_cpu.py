@@ -57,7 +57,7 @@ def test_prepared_weights_decide_between_33_and_48_rows(r, V):
         assert plan_of("low", rows, 8 * r, r, V, 10, prepared=True)["kernel"] == "tile"
         assert plan_of("low", rows, 8 * r, r, V, 10, prepared=True, sampling=True)["kernel"] == ("rows" if rows <= 48 else "tile")
     assert plan_of("low", 40, 8 * r, r, V, 40, prepared=True)["kernel"] == "rows"          # a list the records cannot hold
-    assert plan_of("low", 48, 512, 64, V, 10, prepared=True)["kernel"] == "rows"           # wide rounding bounds
+    assert plan_of("low", 48, 512, 64, V, 10, prepared=True)["kernel"] == "rows"           # the records' merge takes longer than the head kernel
 
 
 @pytest.mark.parametrize("kind,rows,d,r,V,k,kernel", [
