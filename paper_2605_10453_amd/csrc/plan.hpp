@@ -384,11 +384,15 @@ inline bool down_rows_takes(const DownGrid &g, int d, int r) {
 // rows_topk_kernel adds itself, instead of a launch that does it once.  The number of slices, 0: not so.  (A launch / every block, us a call: 6 rows, d = 2056,
 // r = 136, V = 8192 18.0 / 15.6; 7 rows, d = 1464, r = 288, V = 22984 20.6 / 18.6; 6 rows in six positions, r = 216 22.8 / 20.5; 5 rows, d = 3576, r = 256, V = 74504
 // 26.7 / 25.6; 4 rows, d = 3600, r = 520 25.3 / 24.0; 4 rows of the router, d = 4096, r = 512, V = 128256 53.9 / 52.5; 8 rows 40.0 / 39.2.
-// Not with 4 slices where 16 blocks' worth of the contraction are cut (4 rows, r = 520 26.7, 8 rows, r = 512 42.0), nor with more rows: 12 rows, r = 256 23.6 / 24.3.)
+// Not with 4 slices where 16 blocks' worth of the contraction are cut (4 rows, r = 520 26.7, 8 rows, r = 512 42.0), nor with more rows: 12 rows, r = 256 23.6 / 24.3.
+// Not where blocks are more than one round, of which each adds the slices again: 8 rows, r = 256, V = 196608 33.8 / 32.5, V = 262144 48.7 / 51.3, r = 128,
+// V = 1048576 101.9 / 110.6, 5 rows, r = 64, V = 524288 41.3 / 42.7; nor with long slices, of which 16 would be summed otherwise: 8 rows, d = 5120, r = 24 to
+// 240 1 to 5 % faster, d = 6144 up to 2.5 % faster, r = 128, V = 128256 23.7 / 24.0, d = 8192, r = 24 18.9 / 19.2, r = 128, V = 128256 24.6 / 25.6.)
 constexpr int kRowsSumRows = 8, kRowsMaxSlices = 8;
-constexpr int kRowsSumFloats = 32768;    // of the slices, which every block reads; half of it with long slices (8 rows, d = 8192, r = 504 25.1 / 26.7, r = 24 24.4 / 20.6)
-inline int rows_sum_slices(const DownGrid &g, int rows, int d, int r) {
-    if (rows > kRowsSumRows || r > 1024 || down_rows_takes(g, d, r)) return 0;
+constexpr int kRowsSumFloats = 32768;    // of the slices, which every block reads; half of it from d = 4096 on
+constexpr int kRowsSumHidden = 5120;
+inline int rows_sum_slices(const DownGrid &g, int rows, int d, int r, int V) {
+    if (rows > kRowsSumRows || r > 1024 || d > kRowsSumHidden || V > kRowsOneRoundCols || down_rows_takes(g, d, r)) return 0;
     const int n = g.slices < kRowsMaxSlices ? g.slices : kRowsMaxSlices;
     return rows * r * n <= (d <= 4096 ? kRowsSumFloats : kRowsSumFloats / 2) ? n : 0;
 }

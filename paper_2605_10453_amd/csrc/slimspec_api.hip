@@ -224,7 +224,7 @@ int run_head_rows(HeadKind kind, const void *h, const void *A, const void *M, co
         in.X = X; in.pieces = p.pieces;
         if (kind == HeadKind::LowRank) {
             if (pos.n > 0) p.down = down_grid_by_position(pos, row0, rows, p.rows_pad, d, r);
-            if (const int n = rows_sum_slices(p.down, rows, d, r)) {
+            if (const int n = rows_sum_slices(p.down, rows, d, r, V)) {
                 p.down.slices = n;
                 float *slices = reinterpret_cast<float *>(ws + p.off_down_part);
                 e = launch_down_projection_slices(hrow, static_cast<const uint16_t *>(A), slices, p.down, d, r, s);

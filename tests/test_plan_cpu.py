@@ -76,6 +76,17 @@ def test_few_rows_take_the_kernel_that_measures_faster(kind, rows, d, r, V, k, k
     assert plan_of(kind, rows, d, r, V, k)["kernel"] == kernel
 
 
+@pytest.mark.parametrize("rows,d,r,V,slices", [
+    (8, 4096, 256, 128256, 8), (8, 4096, 256, 196608, 8), (8, 4096, 256, 196616, 0), (8, 4096, 128, 1048576, 0), (5, 4096, 64, 524288, 0),
+    (8, 5120, 128, 128256, 8), (8, 5128, 128, 128256, 0), (8, 8192, 24, 8192, 0), (4, 4096, 1024, 128256, 8), (9, 4096, 128, 128256, 0),
+])
+def test_blocks_add_the_slices_only_where_that_is_less_work(rows, d, r, V, slices):
+    """Every block adds them: not with more than one round of blocks, nor with slices so long that halving their number costs more than
+    the launch that adds them."""
+    plan = plan_of("low", rows, d, r, V, 10)
+    assert (plan["kernel"], plan["sum_slices"]) == ("rows", slices), plan
+
+
 @pytest.mark.parametrize("rows,d,V,in_lds,chunk_cols", [
     (1, 80000, 8192, 0, 64), (2, 24000, 8192, 1, 64), (4, 12288, 8192, 1, 64), (4, 16384, 8192, 0, 256), (3, 16384, 16384, 0, 256), (4, 16384, 16392, 0, 128),
     (8, 6144, 8192, 1, 64), (8, 8192, 8192, 0, 256), (64, 8192, 8192, 0, 256), (65, 8192, 8192, 0, 512), (8, 8192, 65536, 0, 256),
