@@ -103,9 +103,13 @@ inline ChunkGeom make_chunk_geom(HeadKind kind, int rows, int K, int V) {
 // / one, us a call: d = 256, r = 32, V = 8192 13.1 / 9.5; d = 512, r = 64, V = 8192 14.1 / 13.1, V = 50000 13.7 / 11.9, V = 128256 13.8 / 12.9; d = 4096, r = 8,
 // V = 8192 13.4 / 10.6; d = 256, r = 128, V = 8192 13.7 / 11.5; d = 336, r = 96, V = 60000, sampling 20.5 / 16.5.  Not with twice as much (d = 1024, r = 64, V = 16384
 // 12.4 / 12.7, d = 512, r = 128, V = 50000 13.2 / 13.9), not where a CU has several blocks that read A (d = 512, r = 64, V = 151936 15.2 / 16.8), and not in
-// blocks of 16 wavefronts, whose registers the weights and A do not share (d = 256, r = 128, V = 128256 16.8 / 25.5).
-inline bool own_input_takes(const ChunkGeom &g, int rows, int d, int r, int V) {
-    return rows == 1 && r <= 128 && (int64_t)d * r <= 32768 && V <= 256 * kChunkCols && g.nw1 <= 8;
+// blocks of 16 wavefronts, whose registers the weights and A do not share (d = 256, r = 128, V = 128256 16.8 / 25.5).  Ranks beyond 64, whose columns of A
+// come in two trips, only while the weights are short (r = 120, d = 264: V = 8192 13.5 / 12.6, V = 20000 13.5 / 13.0, V = 40000 12.9 to 13.1 / 13.5, V = 60000
+// 13.4 / 14.3; r = 128, d = 256: V = 40000 13.4 / 13.4, V = 60000 13.6 / 14.6; r = 72 level from V = 24000 to 131072) or with draws, whose calls wait for the
+// host, for every launch (r = 72 to 128, V = 24000 to 60000 20.2 to 20.6 / 16.5 to 16.9).
+constexpr int kOwnShortV = 40960;
+inline bool own_input_takes(const ChunkGeom &g, int rows, int d, int r, int V, bool sampling) {
+    return rows == 1 && r <= 128 && (int64_t)d * r <= 32768 && V <= 256 * kChunkCols && g.nw1 <= 8 && (r <= 64 || V <= kOwnShortV || sampling);
 }
 
 struct Plan {

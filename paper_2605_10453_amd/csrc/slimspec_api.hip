@@ -288,7 +288,7 @@ int run_head(HeadKind kind, const void *h, const void *A, const void *M, bool m_
     // scratch in stream order; one merge launch serves all rows.
     const DownPlan dp = make_down_plan(kind == HeadKind::LowRank, p.d, p.r);
     float *tpart = reinterpret_cast<float *>(ws + p.off_tpart);
-    const bool own = kind == HeadKind::LowRank && own_input_takes(p.geom, p.rows, p.d, p.r, p.V);
+    const bool own = kind == HeadKind::LowRank && own_input_takes(p.geom, p.rows, p.d, p.r, p.V, so.on != 0);
     if (own) {
         const bool timed = g_ev_start != nullptr;
         hipError_t e;

@@ -87,6 +87,16 @@ def test_blocks_add_the_slices_only_where_that_is_less_work(rows, d, r, V, slice
     assert (plan["kernel"], plan["sum_slices"]) == ("rows", slices), plan
 
 
+@pytest.mark.parametrize("d,r,V,plain,sampling", [
+    (256, 32, 8192, 1, 1), (512, 64, 131072, 1, 1), (256, 128, 40960, 1, 1), (264, 120, 60000, 0, 1), (256, 128, 40968, 0, 1), (336, 96, 60000, 0, 1),
+    (256, 128, 128256, 0, 0), (512, 64, 131080, 0, 0), (264, 128, 8192, 0, 0),
+])
+def test_blocks_make_the_input_only_where_that_is_less_work(d, r, V, plain, sampling):
+    """Two trips for A against a launch: beyond r = 64 only with few columns, or where the call waits for the host anyway."""
+    assert plan_of("low", 1, d, r, V, 10)["own_input"] == plain
+    assert plan_of("low", 1, d, r, V, 10, sampling=True)["own_input"] == sampling
+
+
 @pytest.mark.parametrize("rows,d,V,in_lds,chunk_cols", [
     (1, 80000, 8192, 0, 64), (2, 24000, 8192, 1, 64), (4, 12288, 8192, 1, 64), (4, 16384, 8192, 0, 256), (3, 16384, 16384, 0, 256), (4, 16384, 16392, 0, 128),
     (8, 6144, 8192, 1, 64), (8, 8192, 8192, 0, 256), (64, 8192, 8192, 0, 256), (65, 8192, 8192, 0, 512), (8, 8192, 65536, 0, 256),
