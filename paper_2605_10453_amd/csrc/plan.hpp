@@ -393,7 +393,7 @@ inline bool down_rows_takes(const DownGrid &g, int d, int r) {
 // V = 1048576 101.9 / 110.6, 5 rows, r = 64, V = 524288 41.3 / 42.7; nor with long slices, of which 16 would be summed otherwise: 8 rows, d = 5120, r = 24 to
 // 240 1 to 5 % faster, d = 6144 up to 2.5 % faster, r = 128, V = 128256 23.7 / 24.0, d = 8192, r = 24 18.9 / 19.2, r = 128, V = 128256 24.6 / 25.6.)
 constexpr int kRowsSumRows = 8, kRowsMaxSlices = 8;
-constexpr int kRowsSumFloats = 32768;    // of the slices, which every block reads; half of it from d = 4096 on
+constexpr int kRowsSumFloats = 32768;    // of the slices, which every block reads; half of it beyond d = 4096
 constexpr int kRowsSumHidden = 5120;
 inline int rows_sum_slices(const DownGrid &g, int rows, int d, int r, int V) {
     if (rows > kRowsSumRows || r > 1024 || d > kRowsSumHidden || V > kRowsOneRoundCols || down_rows_takes(g, d, r)) return 0;
