@@ -17,6 +17,7 @@
 // "my part of the stage needed next has landed", and the barrier that follows publishes the stage.
 #include "device_utils.hpp"
 #include "launch.hpp"
+#include <type_traits>
 
 namespace slimspec {
 
@@ -139,10 +140,11 @@ __device__ __forceinline__ void column_scale_block(const uint16_t *__restrict__ 
 // STEPWISE: every 16-element step is summed on its own and then added (for the callers that report fp32-exact logits):
 // the matrix unit's internal roundings then happen at the size of one step's sum.
 // ROWS: part is [slices][rows][r] instead, row by row and without the rows of padding.
-template <bool STEPWISE, bool ROWS>
+// GRID: DownGrid, or JointDownGrid for two launches' rows.
+template <bool STEPWISE, bool ROWS, class GRID>
 __global__ __launch_bounds__(256) void down_tile_kernel(
     const uint16_t *__restrict__ h, const uint16_t *__restrict__ A, float *__restrict__ part,
-    int d, int r, int blocks_first, DownGrid g)
+    int d, int r, GRID g)
 {
     extern __shared__ __align__(1024) unsigned char lds_raw[];
     const uint32_t lds0 = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) unsigned char *)lds_raw);
@@ -152,12 +154,16 @@ __global__ __launch_bounds__(256) void down_tile_kernel(
     const int wr = wave >> 1, wc = wave & 1;
 
     // this block's launch of the two that share the grid: its slices, its row tiles [rt_beg, rt_beg + n_rt), its partial tiles
-    const bool second = (int)blockIdx.x >= blocks_first;
-    const int slices = second ? g.slices_second : g.slices;
-    const int rt_beg = second ? g.rt_second : 0, n_rt = second ? g.n_rt - g.rt_second : g.rt_second;
+    uint32_t b = blockIdx.x;
+    int slices = g.slices, rt_beg = 0, n_rt = g.n_rt;
+    bool second = false;
+    if constexpr (std::is_same_v<GRID, JointDownGrid>) {
+        second = b >= (uint32_t)g.blocks_first;
+        n_rt = second ? g.n_rt - g.rt_second : g.rt_second;
+        if (second) { b -= g.blocks_first; slices = g.slices_second; rt_beg = g.rt_second; }
+    }
     int slice, tile;
     {
-        const int b = (int)blockIdx.x - (second ? blocks_first : 0);      // (blocks_first is a multiple of 8)
         const int xcd = b & 7, slot = b >> 3;
         if (slices >= 8) { slice = xcd + 8 * (slot % (slices >> 3)); tile = slot / (slices >> 3); }
         else { slice = xcd % slices; tile = xcd / slices + (8 / slices) * slot; }
@@ -274,7 +280,8 @@ __global__ __launch_bounds__(256) void down_tile_kernel(
                                                                        acc0[4 * q + 2] + acc1[4 * q + 2], acc0[4 * q + 3] + acc1[4 * q + 3]);
         return;
     }
-    if (second) part += (size_t)g.slices * g.rt_second * g.n_ct * (4 * 16 * 64);
+    if constexpr (std::is_same_v<GRID, JointDownGrid>)
+        if (second) part += (size_t)g.slices * g.rt_second * g.n_ct * (4 * 16 * 64);
     float *dst = part + ((((size_t)slice * n_rt + (rt - rt_beg)) * g.n_ct + ct) * 4 + wave) * (16 * 64) + lane;
 #pragma unroll
     for (int i = 0; i < 16; ++i) dst[i * 64] = acc0[i] + acc1[i];
@@ -288,11 +295,11 @@ __global__ __launch_bounds__(256) void down_tile_kernel(
 //   stat  [2 ceil(r / 64), rows_pad]   per 32-column piece: (sum of (t - its 16-bit value)^2, sum of t^2) of its entries
 // PIECES: t leaves as three bf16 pieces instead, t16 [3][8 ceil(r / 64)][rows_pad] (no t32, stat or column scales).
 // The pieces are cut off the top of t's significand, 8 bits each: their sum is t exactly.
-template <bool PIECES>
+template <bool PIECES, class GRID>
 __global__ __launch_bounds__(256) void down_finish_kernel(
     const float *__restrict__ part, int rows_pad, int r,
     float *__restrict__ t32, uint4 *__restrict__ t16, float2 *__restrict__ stat,
-    const uint16_t *__restrict__ B, int V, float2 *__restrict__ tilescale, int operand, DownGrid g)
+    const uint16_t *__restrict__ B, int V, float2 *__restrict__ tilescale, int operand, GRID g)
 {
     __shared__ float tile[32 * 33];
     __shared__ float red_a[4 * 32], red_b[4 * 32];
@@ -312,14 +319,18 @@ __global__ __launch_bounds__(256) void down_finish_kernel(
     const int rows = (grp < g.n_groups) ? row_end : 0;         // rows that carry values
 
     // the slices, in order: several loads of a thread are in flight together (they come from other CUs' writes)
-    const bool second = rt >= g.rt_second;
-    const size_t slice_stride = (size_t)(second ? g.n_rt - g.rt_second : g.rt_second) * g.n_ct * 4 * (16 * 64);
-    const float *src = part + (((size_t)(rt - (second ? g.rt_second : 0)) * g.n_ct + ct) * 4 + w) * (16 * 64);
-    if (second) src += (size_t)g.slices * g.rt_second * g.n_ct * (4 * 16 * 64);
+    int slices = g.slices, rt_beg = 0, n_rt = g.n_rt;
+    if constexpr (std::is_same_v<GRID, JointDownGrid>) {
+        const bool second = rt >= g.rt_second;
+        n_rt = second ? g.n_rt - g.rt_second : g.rt_second;
+        if (second) { part += (size_t)g.slices * g.rt_second * g.n_ct * (4 * 16 * 64); slices = g.slices_second; rt_beg = g.rt_second; }
+    }
+    const size_t slice_stride = (size_t)n_rt * g.n_ct * 4 * (16 * 64);
+    const float *src = part + (((size_t)(rt - rt_beg) * g.n_ct + ct) * 4 + w) * (16 * 64);
     // a thread owns four (i, lane) pairs of the accumulator layout; the loads of SB slices of all four are in flight together
     constexpr int SB = 8;
     float v4[4] = {0.f, 0.f, 0.f, 0.f};
-    const int n_slices = grp < g.n_groups ? (second ? g.slices_second : g.slices) : 0;
+    const int n_slices = grp < g.n_groups ? slices : 0;
     for (int s0 = 0; s0 < n_slices; s0 += SB) {
         float x[SB][4];
 #pragma unroll
@@ -419,40 +430,40 @@ __global__ __launch_bounds__(256) void down_finish_kernel(
                         ((red_b[tid] + red_b[32 + tid]) + red_b[64 + tid]) + red_b[96 + tid]);
 }
 
-template <bool STEPWISE, bool ROWS = false>
-static hipError_t launch_down_tiles(const uint16_t *h, const uint16_t *A, float *part, const DownGrid &g, int d, int r, hipStream_t st)
+template <bool STEPWISE, bool ROWS, class GRID>
+static hipError_t launch_down_tiles(const uint16_t *h, const uint16_t *A, float *part, const GRID &g, int blocks, int d, int r, hipStream_t st)
 {
     static LdsLimit lds_limit;
-    hipError_t e = lds_limit.raise(reinterpret_cast<const void *>(down_tile_kernel<STEPWISE, ROWS>), kDLds);
+    hipError_t e = lds_limit.raise(reinterpret_cast<const void *>(down_tile_kernel<STEPWISE, ROWS, GRID>), kDLds);
     if (e != hipSuccess) return e;
-    // slices >= 8: every XCD has slices / 8 slices of every tile; fewer: 8 / slices XCDs share a slice and split the tiles
-    const auto blocks = [](int tiles, int slices) { return slices >= 8 ? tiles * slices : 8 * ((tiles + 8 / slices - 1) / (8 / slices)); };
-    const int first = blocks(g.rt_second * g.n_ct, g.slices), second = blocks((g.n_rt - g.rt_second) * g.n_ct, g.slices_second);
-    down_tile_kernel<STEPWISE, ROWS><<<first + second, 256, kDLds, st>>>(h, A, part, d, r, first, g);
+    down_tile_kernel<STEPWISE, ROWS, GRID><<<blocks, 256, kDLds, st>>>(h, A, part, d, r, g);
     return hipGetLastError();
 }
 
-hipError_t launch_down_projection_tiles(const uint16_t *h, const uint16_t *A, float *part, const DownGrid &g,
+hipError_t launch_down_projection_tiles(const uint16_t *h, const uint16_t *A, float *part, const DownGrid &first, const DownGrid *second,
                                         int rows_pad, int d, int r,
                                         float *t32, void *t16, float2 *stat, const uint16_t *B, int V, float2 *tilescale,
                                         Operand operand, hipStream_t st)
 {
-    const hipError_t e = launch_down_tiles<false>(h, A, part, g, d, r, st);
-    if (e != hipSuccess) return e;
-    down_finish_kernel<false><<<4 * g.n_rt_all * g.n_ct + (V + 511) / 512, 256, 0, st>>>(
-        part, rows_pad, r, t32, static_cast<uint4 *>(t16), stat, B, V, tilescale, operand, g);
-    return hipGetLastError();
+    const auto launch = [&](const auto &g, int blocks) {
+        const hipError_t e = launch_down_tiles<false, false>(h, A, part, g, blocks, d, r, st);
+        if (e != hipSuccess) return e;
+        down_finish_kernel<false><<<4 * g.n_rt_all * g.n_ct + (V + 511) / 512, 256, 0, st>>>(
+            part, rows_pad, r, t32, static_cast<uint4 *>(t16), stat, B, V, tilescale, operand, g);
+        return hipGetLastError();
+    };
+    return second ? launch(join_down_grids(first, *second), down_tile_blocks(first) + down_tile_blocks(*second)) : launch(first, down_tile_blocks(first));
 }
 
 hipError_t launch_down_projection_slices(const uint16_t *h, const uint16_t *A, float *slices, const DownGrid &g, int d, int r, hipStream_t st)
 {
-    return launch_down_tiles<true, true>(h, A, slices, g, d, r, st);
+    return launch_down_tiles<true, true>(h, A, slices, g, down_tile_blocks(g), d, r, st);
 }
 
 hipError_t launch_down_projection_pieces(const uint16_t *h, const uint16_t *A, float *part, const DownGrid &g,
                                          int rows_pad, int d, int r, void *X, hipStream_t st)
 {
-    const hipError_t e = launch_down_tiles<true>(h, A, part, g, d, r, st);
+    const hipError_t e = launch_down_tiles<true, false>(h, A, part, g, down_tile_blocks(g), d, r, st);
     if (e != hipSuccess) return e;
     down_finish_kernel<true><<<4 * g.n_rt_all * g.n_ct, 256, 0, st>>>(
         part, rows_pad, r, nullptr, static_cast<uint4 *>(X), nullptr, nullptr, 0, nullptr, kOperandExact, g);

@@ -77,7 +77,8 @@ static_assert(kStreamList == kStreamListPlan && kStreamRecSample == kStreamRecPl
 // and per 256-column vocabulary tile (the largest column rms, the mean square) of B over a sample of its rows
 // (tilescale [ceil(V / 256)])
 // (A: the stack of down-projection matrices, [d, r] each; the grid names the rows and the matrix of every group)
-hipError_t launch_down_projection_tiles(const uint16_t *h, const uint16_t *A, float *part, const DownGrid &g,
+// second: the rows of a second launch of the head kernel, or null
+hipError_t launch_down_projection_tiles(const uint16_t *h, const uint16_t *A, float *part, const DownGrid &first, const DownGrid *second,
                                         int rows_pad, int d, int r,
                                         float *t32, void *t16, float2 *stat, const uint16_t *B, int V, float2 *tilescale,
                                         Operand operand, hipStream_t st);

@@ -186,19 +186,26 @@ inline bool merge_parks_rows(int K, bool fine_operand) { return K >= kDeferMinK 
 // blocks for every CU, at least two stages of 32 contraction elements per block.  The rows come in groups that share
 // a down-projection matrix (one group unless the call names one matrix per drafted position); a row tile never
 // crosses a group, and the rows of padding [rows, rows_pad) form one more group that is only zero-filled.
-// Two launches' rows at once (join_down_grids): the second launch's row tiles stand behind the first's, and either keeps its number of
-// slices, so that a row's sums are the same, in the same order, as when every launch has its own down-projection.
 constexpr int kMaxPositions = 16;
-struct DownGrid {
+template <int G>                         // groups at most, without the padding
+struct DownGridOf {
     int n_rt = 0;                        // row tiles that hold rows, over all groups
     int n_rt_all = 0;                    // ... with the tiles of the padding group
     int n_ct = 0, slices = 1;
-    int rt_second = 0, slices_second = 1;     // row tiles from rt_second on (n_rt: none) are a second launch's, with its slices
-    int n_groups = 0;                    // groups with rows (a position that both launches hold rows of counts twice); group n_groups is the padding
-    int g_row0[kMaxPositions + 3] = {};  // first row of group g; g_row0[n_groups] = rows, g_row0[n_groups + 1] = rows_pad
-    int g_tile0[kMaxPositions + 3] = {}; // first row tile of group g; g_tile0[n_groups + 1] = n_rt_all
-    int g_mat[kMaxPositions + 2] = {};   // which matrix of the stack the group uses
+    int n_groups = 0;                    // groups with rows; group n_groups is the padding
+    int g_row0[G + 2] = {};              // first row of group g; g_row0[n_groups] = rows, g_row0[n_groups + 1] = rows_pad
+    int g_tile0[G + 2] = {};             // first row tile of group g; g_tile0[n_groups + 1] = n_rt_all
+    int g_mat[G + 1] = {};               // which matrix of the stack the group uses
 };
+using DownGrid = DownGridOf<kMaxPositions>;
+// Two launches' rows at once: the second launch's row tiles stand behind the first's, and either keeps its number of slices, so that a
+// row's sums are the same, in the same order, as when every launch has its own down-projection.  A type of its own, with kernels of its own: five
+// more words of arguments and the choice between the two cost the calls of one launch 0.4 us (23 rows 42.4 / 42.8 us).
+struct JointDownGrid : DownGridOf<kMaxPositions + 1> {      // (a position that both launches hold rows of counts twice)
+    int rt_second = 0, slices_second = 1;     // row tiles from rt_second on are the second launch's, with its slices
+    int blocks_first = 0;                     // blocks of down_tile_kernel that work for the first
+};
+static_assert(sizeof(DownGrid) == sizeof(int) * (5 + 2 * (kMaxPositions + 2) + kMaxPositions + 1), "nothing of it is an argument of one launch's kernels");
 // group g covers rows [g_first[g], g_first[g + 1]) of the launch (g_first[n_groups] = rows), all groups non-empty
 inline DownGrid make_down_grid(int rows, int rows_pad, int d, int r, int n_groups = 1, const int *g_first = nullptr,
                                const int *g_mat = nullptr) {
@@ -220,14 +227,24 @@ inline DownGrid make_down_grid(int rows, int rows_pad, int d, int r, int n_group
     // (two blocks per CU, i.e. twice the slices, measured slower: 10.7 + 4.6 against 8.9 + 4.5 us at 512 rows)
     // (at most 16 slices: with 32, at 16 and 64 rows, the tile kernel measures the same and the sum of the slices 1.1 us more)
     while (g.slices < 16 && tiles * g.slices < 256 && n_stages / (2 * g.slices) >= 2) g.slices *= 2;
-    g.rt_second = g.n_rt;
     return g;
 }
+// Blocks of down_tile_kernel.  slices >= 8: every XCD has slices / 8 slices of every tile; fewer: 8 / slices XCDs share a slice and split the
+// tiles.  A multiple of 8.
+inline int down_tile_blocks(const DownGrid &g) {
+    const int tiles = g.n_rt * g.n_ct;
+    return g.slices >= 8 ? tiles * g.slices : 8 * ((tiles + 8 / g.slices - 1) / (8 / g.slices));
+}
 // a: the first launch's rows, no padding; b: the second's
-inline DownGrid join_down_grids(const DownGrid &a, const DownGrid &b) {
-    DownGrid g = a;
+inline JointDownGrid join_down_grids(const DownGrid &a, const DownGrid &b) {
+    JointDownGrid g;
     const int rows = a.g_row0[a.n_groups];
+    for (int q = 0; q < a.n_groups; ++q) { g.g_row0[q] = a.g_row0[q]; g.g_tile0[q] = a.g_tile0[q]; g.g_mat[q] = a.g_mat[q]; }
+    g.n_ct = a.n_ct;
+    g.slices = a.slices;
     g.slices_second = b.slices;
+    g.rt_second = a.n_rt;
+    g.blocks_first = down_tile_blocks(a);
     g.n_rt = a.n_rt + b.n_rt;
     g.n_rt_all = a.n_rt + b.n_rt_all;
     g.n_groups = a.n_groups + b.n_groups;
@@ -277,7 +294,7 @@ struct MfmaPlan {
     int rows = 0, rows_pad = 0, rt = 0, n_rb = 0, gw = 0, nsr = 0, n_vt = 0;
     bool resident = false;               // the row operand fits a wavefront's registers (bf16 operands)
     ResidentGrid res;
-    DownGrid down;
+    DownGrid down, down_second;          // (the second of two launches)
     size_t off_down_part = 0;            // fp32 [slices][n_rt][n_ct][4][16][64] of each launch: partial tiles of t (sized for any grouping of the rows)
     size_t off_t32 = 0;                  // fp32 [rows_pad, r]
     size_t off_t16 = 0;                  // 16-byte vectors [8 ceil(K / 64), rows_pad]: the head kernel's row operand (two of them for two pieces)
@@ -317,8 +334,8 @@ inline MfmaPlan make_mfma_plan(HeadKind kind, int rows, int d, int r, int V) {
         p.off_t16 = off;       off = align_up(off + 2 * (size_t)p.rows_pad * ((r + 63) / 64 * 64) * (r <= kTwoPiecesMaxRank ? 2 : 1));
         p.off_stat = off;      off = align_up(off + 2 * sizeof(float) * (size_t)p.rows_pad * 2 * ((r + 63) / 64));
         const int first = rows < kMaxLaunchRows ? rows : kMaxLaunchRows;
-        p.down = rows == first ? make_down_grid(rows, p.rows_pad, d, r)
-                               : join_down_grids(make_down_grid(first, first, d, r), make_down_grid(rows - first, p.rows_pad - first, d, r));
+        p.down = make_down_grid(first, rows == first ? p.rows_pad : first, d, r);
+        if (rows > first) p.down_second = make_down_grid(rows - first, p.rows_pad - first, d, r);
         size_t tiles = down_part_tiles_bound(first, r);
         if (rows > first) tiles += down_part_tiles_bound(rows - first, r);
         p.off_down_part = off; off = align_up(off + sizeof(float) * 4096 * tiles);

@@ -145,7 +145,7 @@ int run_head_mfma(HeadKind kind, const void *h, const void *A, const void *M, co
         if (kind == HeadKind::LowRank && pos.n > 0) {
             const int n = rows_joint < per ? rows_joint : per;
             all.down = down_grid_by_position(pos, first, n, rows_joint > n ? n : all.rows_pad, d, r);
-            if (rows_joint > n) all.down = join_down_grids(all.down, down_grid_by_position(pos, first + n, rows_joint - n, all.rows_pad - n, d, r));
+            if (rows_joint > n) all.down_second = down_grid_by_position(pos, first + n, rows_joint - n, all.rows_pad - n, d, r);
         }
         float *streams = reinterpret_cast<float *>(ws + all.off_streams);
         void *defer = all.defer ? ws + all.off_defer : nullptr;
@@ -156,7 +156,7 @@ int run_head_mfma(HeadKind kind, const void *h, const void *A, const void *M, co
         float2 *tilescale = reinterpret_cast<float2 *>(ws + all.off_tilescale);
         if (kind == HeadKind::LowRank) {
             e = launch_down_projection_tiles(hb + (size_t)first * d, static_cast<const uint16_t *>(A), reinterpret_cast<float *>(ws + all.off_down_part),
-                                             all.down, all.rows_pad, d, r, t32, ws + all.off_t16, stat, Mb, V, tilescale, operand, s);
+                                             all.down, rows_joint > per ? &all.down_second : nullptr, all.rows_pad, d, r, t32, ws + all.off_t16, stat, Mb, V, tilescale, operand, s);
             if (e != hipSuccess) return fail_hip(e);
         }
         for (int row0 = first; row0 < first + rows_joint; row0 += per) {
