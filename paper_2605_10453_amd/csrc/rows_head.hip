@@ -537,9 +537,12 @@ hipError_t launch_rows_topk(const RowsInput &x, const uint16_t *M, float2 *ms, f
 #define SLIMSPEC_ROWS_G(NT, NP, GM, SUM) launch_rows<NT, NP, GM, SUM>(x, M, ms, pv, pi, smp, rows, row0, K, V, g, k, seed_lo, seed_hi, st)
 #define SLIMSPEC_ROWS(NT, NP, SUM) (g.G == 1 ? SLIMSPEC_ROWS_G(NT, NP, 1, SUM) : g.G == 2 ? SLIMSPEC_ROWS_G(NT, NP, 2, SUM) \
                                              : g.G <= 4 ? SLIMSPEC_ROWS_G(NT, NP, 4, SUM) : SLIMSPEC_ROWS_G(NT, NP, 6, SUM))
+    // The kernels lie in memory in this order of first use.  With those that add slices first, the ones for three pieces took longer with the same
+    // instructions (7 rows, d = 6392, r = 1040, V = 11896 27.9 / 27.5 us a call, 16 rows, d = 4096, r = 1024, V = 32000 30.0 / 29.4, 4 rows of the router
+    // 52.4 / 52.1), and what this order costs is less (5 rows, r = 256, V = 74504 22.6 / 22.7, 23 rows 42.3 / 42.6); with them last 22.6 / 23.1 there.
+    if (x.pieces == 3 && !x.slices) return rows <= 16 ? SLIMSPEC_ROWS(1, 3, false) : rows <= 32 ? SLIMSPEC_ROWS(2, 3, false) : SLIMSPEC_ROWS(3, 3, false);
     if (x.slices) return SLIMSPEC_ROWS(1, 3, true);
-    if (x.pieces == 1) return rows <= 16 ? SLIMSPEC_ROWS(1, 1, false) : rows <= 32 ? SLIMSPEC_ROWS(2, 1, false) : SLIMSPEC_ROWS(3, 1, false);
-    return rows <= 16 ? SLIMSPEC_ROWS(1, 3, false) : rows <= 32 ? SLIMSPEC_ROWS(2, 3, false) : SLIMSPEC_ROWS(3, 3, false);
+    return rows <= 16 ? SLIMSPEC_ROWS(1, 1, false) : rows <= 32 ? SLIMSPEC_ROWS(2, 1, false) : SLIMSPEC_ROWS(3, 1, false);
 #undef SLIMSPEC_ROWS
 #undef SLIMSPEC_ROWS_G
 }

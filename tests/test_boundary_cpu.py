@@ -110,7 +110,7 @@ def test_product_path_does_not_touch_the_checker():
 
 
 @pytest.mark.parametrize("source,kernel", [("head_tile.hip", "head_tile_kernel"), ("merge_streams.hip", "merge_streams_kernel"),
-                                           ("head_resident.hip", "head_resident_kernel")])
+                                           ("head_resident.hip", "head_resident_kernel"), ("rows_head.hip", "rows_topk_kernel")])
 def test_kernels_use_no_scratch_memory(source, kernel):
     """head_tile_kernel and head_resident_kernel count their own vector-memory loads (s_waitcnt vmcnt(N)); a register spill would add
     loads the count does not know about.  merge_streams_kernel once kept a small array in scratch memory, which
@@ -137,6 +137,10 @@ def test_kernels_use_no_scratch_memory(source, kernel):
         shared = re.findall(r"LDS Size \[bytes/block\]: (\d+)", text)
         with_draw, without = ([int(sz) for n, sz in zip(names, shared) if kernel + "ILb%dE" % draw in n] for draw in (1, 0))
         assert len(with_draw) == len(without) == 1 and without[0] + 512 <= with_draw[0], list(zip(names, shared))
+    if kernel == "rows_topk_kernel":
+        # three pieces of t before the instances that add slices: laid out behind them they take up to 2 % longer
+        kind = [(3 if "ELi3ELi" in n else 1, "ELb1E" in n) for n in names if kernel in n]
+        assert len(kind) == 28 and max(i for i, q in enumerate(kind) if q == (3, False)) < kind.index((3, True)), kind
 
 
 @pytest.mark.parametrize("source,kernel", [("head_resident.hip", "head_resident_kernel"), ("head_tile.hip", "head_tile_kernel")])
