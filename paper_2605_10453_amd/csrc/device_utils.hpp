@@ -137,6 +137,18 @@ SLIMSPEC_WAVE_REDUCE_F32(wave_max, op_max)
 SLIMSPEC_WAVE_REDUCE_F32(wave_sum, op_add)
 #undef SLIMSPEC_WAVE_REDUCE_F32
 
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+    v = max(v, dpp_u32<0xB1>(v));
+    v = max(v, dpp_u32<0x4E>(v));
+    v = max(v, dpp_u32<0x141>(v));
+    v = max(v, dpp_u32<0x140>(v));
+    uint32_t a, b;
+    swap_pair<16>(v, a, b);
+    v = max(a, b);
+    swap_pair<32>(v, a, b);
+    return max(a, b);
+}
+
 __device__ __forceinline__ uint64_t u64_from(uint32_t hi, uint32_t lo) { return ((uint64_t)hi << 32) | lo; }
 __device__ __forceinline__ uint64_t u64_max(uint64_t a, uint64_t b) { return a > b ? a : b; }
 
@@ -257,6 +269,74 @@ __device__ __forceinline__ float gumbel_base2(const GumbelKey &key, uint32_t id)
 constexpr float kGumbelBoundBase = 159.f;               // 32 for the scale of x, 127 for the exponent's bias
 constexpr float kGumbelBoundScale = 1.1920928955078125e-7f;      // 2^-23
 __device__ __forceinline__ float gumbel_bound_bits(uint32_t x) { return (float)(int)__float_as_uint((float)(x & 0xfffffe00u)); }
+
+// What follows serves tails that are chains of instructions.  On this chip a dependent vector instruction takes 5.5 cycles, a DPP step 14, a permlane swap
+// 32, a branch on what vector instructions found 70, an LDS round trip 75 and with two barriers 120 to 200, an LDS addition by one lane 250.
+//
+// A bound that at least k elements reach: `lanes` adjacent lanes hold elements, and the largest order bits of each group of 2^gl of them (at most 2^most)
+// are known.  Class i of k is made of the groups i, i + k, ... (`deep` of them, at most 8); the smallest maximum of the classes is the bound.
+// (d = 4096, V = 128256, k = 10: 28 entries of the lists reach it; a sort would leave 12.)
+struct BoundPlan { int gl, n_groups, deep; bool all; };
+constexpr int kBoundGroups = 32;                                 // for k <= 16
+__device__ __forceinline__ BoundPlan make_bound_plan(int lanes, int k, int most) {
+    BoundPlan p;
+    // the largest gl that leaves 2 k groups: ceil(lanes / 2^gl) >= 2 k
+    p.gl = __clz(2 * k - 1) - __clz(max(1, lanes - 1));
+    if (p.gl > 0 && ((2 * k - 1) << p.gl) > lanes - 1) --p.gl;
+    p.gl = min(max(p.gl, 0), most);
+    if (k <= 16) p.gl = max(p.gl, lanes <= kBoundGroups ? 0 : 27 - __clz(lanes - 1));      // no more than 32 groups, and 17 at least
+    p.n_groups = (lanes + (1 << p.gl) - 1) >> p.gl;
+    p.deep = 1;
+    while (p.deep < 8 && (p.deep + 1) * k <= p.n_groups) ++p.deep;
+    p.all = p.n_groups < k;                                      // too few for a bound: every element reaches 1
+    asm volatile("" : "+s"(p.gl), "+s"(p.n_groups), "+s"(p.deep));      // (worked out here, ahead of the elements, which wait for memory)
+    return p;
+}
+// ... lane's class (beyond the last: all bits)
+__device__ __forceinline__ uint32_t class_max(const uint32_t *groups, const BoundPlan &p, int k, int i) {
+    uint32_t t = i < k ? groups[i] : ~0u;
+#pragma unroll
+    for (int j = 1; j < 8; ++j) {
+        if (j >= p.deep) break;                                  // (the same for all, and known before)
+        t = max(t, groups[i + j * k]);                           // (lanes without a class: nothing beyond all bits)
+    }
+    return t;
+}
+// The bound for k <= 16; groups[kBoundGroups] with zeros beyond the last, and room for 128; top: the largest order bits of all.  The same in all lanes.
+__device__ __forceinline__ uint32_t bound_of_groups(const uint32_t *groups, const BoundPlan &p, int k, int lane, uint32_t &top) {
+    const int i = lane & 15;
+    top = max(groups[i], groups[16 + i]);
+    uint32_t t = class_max(groups, p, k, i);
+    const auto both = [&](uint32_t a, uint32_t b) { t = min(t, a); top = max(top, b); };
+    both(dpp_u32<0xB1>(t), dpp_u32<0xB1>(top));
+    both(dpp_u32<0x4E>(t), dpp_u32<0x4E>(top));
+    both(dpp_u32<0x141>(t), dpp_u32<0x141>(top));
+    both(dpp_u32<0x140>(t), dpp_u32<0x140>(top));
+    return p.all ? 1u : max(1u, t);
+}
+// Sum of v over the lanes up to and including this one.
+__device__ __forceinline__ uint32_t wave_prefix_sum(uint32_t v) {
+    v += dpp_u32<0x111>(v);                                      // row_shr:1, 2, 4, 8 (zero from outside the row of 16)
+    v += dpp_u32<0x112>(v);
+    v += dpp_u32<0x114>(v);
+    v += dpp_u32<0x118>(v);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);      // row_bcast:15 into the odd rows
+    return v + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);      // row_bcast:31 into the upper half
+}
+// How many of the W lists' keys are larger than `key`; longest: the longest list's length, the same in all lanes.  Eight adjacent lanes share the scan
+// and all get the sum.  Eight slots behind every list's last key are zeros.
+template <int W, int CAP>
+__device__ __forceinline__ int rank_in_lists(const uint64_t (*lists)[CAP], const int (&n)[W], int longest, uint64_t key, int lane) {
+    int rank = 0;
+    for (int q0 = 0; q0 < longest; q0 += 8) {
+        uint64_t other[W];
+#pragma unroll
+        for (int w = 0; w < W; ++w) other[w] = lists[w][min(q0, n[w]) + (lane & 7)];
+#pragma unroll
+        for (int w = 0; w < W; ++w) rank += other[w] > key ? 1 : 0;
+    }
+    return lanes_sum(rank, 8);
+}
 
 // Orders the shared-memory accesses of one wavefront: writes before it are visible to
 // the reads of the other lanes after it (the LDS serves a wavefront's requests in

@@ -4,15 +4,25 @@
 // and the k first (logit desc, id asc) of all lists' entries.  The order of every reduction is fixed and the selection
 // works on unique keys (order bits of the logit, then the inverted id), so the output does not depend on scheduling.
 //
-// What bounds it: latency.  The partials were written by other CUs, so every load is a trip to the memory side (about
-// 1 us), and a block-wide step costs a barrier; there is hardly any work.  So one wavefront does everything that is a
-// chain, without barriers, and the others only fetch lists:
-//   (1) wavefront 0 reads the chunk maxima (the lists' heads), up to 8 per lane in flight, and folds the log-sum-exp.
+// What bounds it: the length of its chain of instructions.  There is hardly any work and one trip to memory (0.4 us; a second pass over the same lists
+// took 3.6 us of the first one's 3.9), but a lone wavefront takes 5 to 14 cycles per dependent instruction (device_utils.hpp).
+//
+// Lists of up to 16 ids whose entries a block's threads can hold (`few`, the usual call): every thread keeps up to eight entries and one chunk's (m, s).
+//   (1) T: the smallest of the maxima of k groups of entries (device_utils.hpp), so k entries reach it; two or three times as many do, where a sort
+//       would leave hardly more than k, but they are ranked by all threads and the sort is a chain of 21 exchanges.  M = max m_c in the same steps.
+//   (2) every wavefront puts its entries that reach T into a list of its own in shared memory (additions to a common counter take 250 cycles), and
+//       the terms of the log-sum-exp are added, one per thread.
+//   (3) the k first are found by counting.
+// Two barriers.  Measured with one wavefront for all of this / now: one row, d = 4096, r = 512, V = 128256 33.9 / 32.7 us a call, with draws at V = 151936
+// 45.7 / 45.4, 23 rows 42.4 / 41.2, the full head at d = 624, V = 23344, k = 1 12.7 / 11.3, 3 rows, r = 496, V = 19072, k = 29 (general code) 24.9 / 24.8.
+//
+// Other calls: one wavefront does everything that is a chain, without barriers, and the others only fetch lists:
+//   (1) wavefront 0 reads the chunk maxima (the lists' heads), up to 8 per lane in flight.
 //       T = the k-th largest of its 64 lanes' maxima: k heads reach it, so it bounds the answer from below.  (All-pairs
 //       counting of 251 heads by 1024 threads took longer than the loads: 6.6 us a launch, 13.5 with 500 chunks and a draw.)
 //       With fewer lists than k no head bounds anything: there T is the m-th largest of the lists' j-th entries, m j >= k.  (Every entry of 32 lists
 //       of 64, as T = 0 admits them, is 40 us of (3): one row, r = 16, V = 2048, k = 64 55 us a call, 14 with this T.)
-//       Wavefront 1 meanwhile finds the draw of a sampling call.
+//       Wavefront 1 meanwhile finds the draw of a sampling call, wavefront 2 folds the log-sum-exp.
 //   (2) all threads: the lists' entries that reach T go to shared memory.  Where a row has few entries they were
 //       requested at the start, before T is known (one trip instead of two); otherwise the first eight of the lists whose
 //       heads reach T are read, and more of a list only where all eight are taken.
@@ -26,7 +36,10 @@ namespace {
 
 constexpr int kRowMergeThreads = 512;
 constexpr int kMergeHeads = 8;                                   // heads per lane in flight
-constexpr int kMergeAhead = 5;                                   // entries per thread that are requested before T is known
+constexpr int kMergeAhead = 8;                                   // entries per thread that are requested before T is known
+constexpr int kMergeShort = 16;                                  // ids of a short list at most
+constexpr int kMergeWaves = kRowMergeThreads / 64;
+constexpr int kMergeMine = 64;                                   // entries of a wavefront's list at most
 constexpr int kMergeLists = SLIMSPEC_KMAX_INTERNAL + kCandSlack; // lists that may hold winners, at most
 constexpr int kMergeCand = kMergeLists * SLIMSPEC_KMAX_INTERNAL; // their entries, at most
 constexpr int kMergeSel = 256;                                   // entries that are ranked all pairs, at most
@@ -41,6 +54,11 @@ struct MergeLds {
     float lse;
     uint64_t draw;
     float draw_z;
+    // short lists
+    uint64_t mine[kMergeWaves][kMergeMine + 8], wave_draw[kMergeWaves];
+    uint32_t groups[128];
+    int n_mine[kMergeWaves];
+    float wave_s[kMergeWaves], wave_draw_z[kMergeWaves];
 };
 
 // The k largest of n keys in shared memory, by one wavefront: f(key, rank).
@@ -74,8 +92,10 @@ __global__ __launch_bounds__(kRowMergeThreads) void merge_kernel(
     // Entries of the last chunk's list from last_len on are filler (it may have fewer than k columns; the others have k).
     const int n_entries = (chunks - 1) * k + last_len;
     const bool ahead = n_entries <= kMergeAhead * NT;
+    const bool few = ahead && k <= kMergeShort && chunks <= NT;
     float2 hm[H];
-    if (wave == 0) {
+    if (few) hm[0] = ms[min(tid, chunks - 1)];
+    else if (wave == 0 || wave == 2) {
 #pragma unroll
         for (int e = 0; e < H; ++e) hm[e] = ms[min(64 * e + lane, chunks - 1)];
     }
@@ -86,6 +106,7 @@ __global__ __launch_bounds__(kRowMergeThreads) void merge_kernel(
     if (ahead) {
 #pragma unroll
         for (int u = 0; u < kMergeAhead; ++u) {
+            if (u * NT >= n_entries) break;                      // (the same for all)
             const int e = min(tid + u * NT, n_entries - 1);
             v_ahead[u] = pv[e];
             id_ahead[u] = pi[e];
@@ -93,7 +114,103 @@ __global__ __launch_bounds__(kRowMergeThreads) void merge_kernel(
     }
 
     float lse = 0.f;
-    if (wave == 0) {
+    const auto emit = [&](uint64_t key, int rank) {
+        const int id = (int)key_tiebreak(key);
+        out_ids[(size_t)row * k + rank] = id_map ? id_map[id] : id;      // truncated vocabulary: column -> vocabulary id
+        out_logprobs[(size_t)row * k + rank] = key_value(key) - lse;
+    };
+    const auto emit_draw = [&](uint64_t key, float z) {
+        const int id = (int)key_tiebreak(key);
+        so.lse[row] = lse;
+        so.sample_ids[row] = id_map ? id_map[id] : id;
+        so.sample_logprobs[row] = z - lse;
+    };
+    const auto rank_by_counting = [&](int n) {                   // the scan for every entry shared by as many lanes as there are
+        const int p = lanes_per_item_log2(n, NT), P = 1 << p, c = tid >> p, part = tid & (P - 1);
+        const uint64_t mine = c < n ? S.cand[c] : kNoKey;
+        int rank = 0;
+#pragma unroll 4
+        for (int q = part; q < n; q += P) rank += S.cand[q] > mine ? 1 : 0;
+        rank = lanes_sum(rank, P);
+        if (c < n && part == 0 && rank < k) emit(mine, rank);
+    };
+    if (few) {
+        const bool have = tid < chunks;
+        float4 draw = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (part_smp) draw = part_smp[(size_t)row * chunks + min(tid, chunks - 1)];
+        const BoundPlan bound = make_bound_plan(min(n_entries, NT), k, 5);
+        if (tid < kBoundGroups && tid >= bound.n_groups) S.groups[tid] = 0u;
+        uint32_t bits[kMergeAhead], most = 0u;
+#pragma unroll
+        for (int u = 0; u < kMergeAhead; ++u) {
+            bits[u] = 0u;
+            if (u * NT >= n_entries) break;                      // (the same for all)
+            if (tid + u * NT < n_entries) bits[u] = float_order_bits(v_ahead[u]);
+            most = max(most, bits[u]);
+        }
+        if (bound.gl > 0) most = max(most, dpp_u32<0xB1>(most));
+        if (bound.gl > 1) most = max(most, dpp_u32<0x4E>(most));
+        if (bound.gl > 2) most = max(most, dpp_u32<0x141>(most));
+        if (bound.gl > 3) most = max(most, dpp_u32<0x140>(most));
+        if (bound.gl > 4) most = max(most, lane_xor16(most, lane));
+        if ((tid & ((1 << bound.gl) - 1)) == 0 && (tid >> bound.gl) < bound.n_groups) S.groups[tid >> bound.gl] = most;
+        __syncthreads();
+        uint32_t top;
+        const uint32_t T = bound_of_groups(S.groups, bound, k, lane, top);
+        const float M = float_from_order_bits(top);              // the largest list's head; a row with a not-a-number ends up below
+        uint32_t n_lane = 0u;
+#pragma unroll
+        for (int u = 0; u < kMergeAhead; ++u) {
+            if (u * NT >= n_entries) break;
+            n_lane += bits[u] >= T ? 1u : 0u;
+        }
+        const uint32_t upto = wave_prefix_sum(n_lane);
+        const int n_mine = __builtin_amdgcn_readlane((int)upto, 63);      // entries of this wavefront
+        int at = (int)(upto - n_lane);
+#pragma unroll
+        for (int u = 0; u < kMergeAhead; ++u) {
+            if (u * NT >= n_entries) break;
+            if (bits[u] >= T) S.mine[wave][min(at++, kMergeMine)] = u64_from(bits[u], ~(uint32_t)id_ahead[u]);      // (beyond: the list is not used)
+        }
+        if (lane < 8) S.mine[wave][min(n_mine, kMergeMine) + lane] = kNoKey;
+        S.n_mine[wave] = n_mine;
+        const float s = wave_sum(have ? hm[0].y * fast_exp(hm[0].x - M) : 0.f);
+        S.wave_s[wave] = s;
+        if (part_smp) {                                          // the largest z + g over the chunks (unique keys)
+            const uint64_t key = have ? make_key(draw.x, (uint32_t)__float_as_int(draw.y)) : kNoKey, largest = wave_max_key(key);
+            if (key == largest) { S.wave_draw[wave] = largest; S.wave_draw_z[wave] = draw.z; }
+        }
+        __syncthreads();
+        // A wavefront ranks its own entries, eight at a time, the scan shared by eight lanes.
+        int n_w[kMergeWaves], longest = 0;
+        float sum = 0.f;
+#pragma unroll
+        for (int w = 0; w < kMergeWaves; ++w) {
+            n_w[w] = __builtin_amdgcn_readfirstlane(S.n_mine[w]);
+            longest = max(longest, n_w[w]);
+            sum += S.wave_s[w];                                  // fixed order
+        }
+        lse = M + fast_log(sum);
+        // (too many entries at the bound, or a logit that is no finite number, in whose chunk the sum is none either: the general code)
+        if (__builtin_amdgcn_readfirstlane(sum < __builtin_huge_valf() ? 1 : 0) != 0 && longest <= kMergeMine) {
+            for (int c0 = 0; c0 < n_mine; c0 += 8) {
+                const uint64_t key = S.mine[wave][c0 + (lane >> 3)];       // (zeros behind the last)
+                const int rank = rank_in_lists(S.mine, n_w, longest, key, lane);
+                if (key != kNoKey && (lane & 7) == 0 && rank < k) emit(key, rank);
+            }
+            if (part_smp && tid == NT - 1) {
+                int w = 0;
+                for (int i = 1; i < kMergeWaves; ++i)
+                    if (S.wave_draw[i] > S.wave_draw[w]) w = i;
+                emit_draw(S.wave_draw[w], S.wave_draw_z[w]);
+            }
+            return;
+        }
+#pragma unroll
+        for (int e = 0; e < H; ++e) hm[e] = ms[min(64 * e + lane, chunks - 1)];
+    }
+
+    if (wave == 0 || wave == 2) {
         // this lane's chunks in increasing order, H at a time
         // A chunk's maximum is its list's first entry, but not where the chunk holds a not-a-number: lists order those by their bits (a positive
         // one comes before +inf), while the maximum ignores them and is -inf, or has a sign and payload of its own, where there is nothing else.  With
@@ -116,75 +233,80 @@ __global__ __launch_bounds__(kRowMergeThreads) void merge_kernel(
         heads_in_lists(0);
         // (at least 1 for a list, as list_bits)
         const auto bits_of = [&](int c0, int e) { return (c0 + 64 * e + lane < chunks) ? list_bits(hm[e].x) : 0u; };
-        float m_t = kNegInf, s_t = 0.f;
-        uint32_t lane_bits = 0u;
-        for (int c0 = 0; c0 < chunks; c0 += 64 * H) {
-            load_heads(c0);
-            float m_new = m_t;
+        if (wave == 2) {
+            float m_t = kNegInf, s_t = 0.f;
+            for (int c0 = 0; c0 < chunks; c0 += 64 * H) {
+                load_heads(c0);
+                float m_new = m_t;
 #pragma unroll
-            for (int e = 0; e < H; ++e) {
-                if (c0 + 64 * e + lane < chunks) m_new = fmaxf(m_new, hm[e].x);
-                lane_bits = max(lane_bits, bits_of(c0, e));
+                for (int e = 0; e < H; ++e)
+                    if (c0 + 64 * e + lane < chunks) m_new = fmaxf(m_new, hm[e].x);
+                s_t = (m_t == kNegInf) ? 0.f : s_t * fast_exp(m_t - m_new);
+#pragma unroll
+                for (int e = 0; e < H; ++e)                      // a chunk with no logit above -inf adds nothing (its sum is not a number)
+                    if (c0 + 64 * e + lane < chunks && hm[e].x != kNegInf) s_t += hm[e].y * fast_exp(hm[e].x - m_new);
+                m_t = m_new;
             }
-            s_t = (m_t == kNegInf) ? 0.f : s_t * fast_exp(m_t - m_new);
-#pragma unroll
-            for (int e = 0; e < H; ++e)                          // a chunk with no logit above -inf adds nothing (its sum is not a number)
-                if (c0 + 64 * e + lane < chunks && hm[e].x != kNegInf) s_t += hm[e].y * fast_exp(hm[e].x - m_new);
-            m_t = m_new;
-        }
-        const float M = wave_max(m_t);
-        const float s = wave_sum(m_t == kNegInf ? 0.f : s_t * fast_exp(m_t - M));
-        lse = M + fast_log(s);
-
-        // (j-th entries: a lane has one list at most, the last one may not have as many; too few that have, or too few heads: everything)
-        if (j_th > 1) lane_bits = lane < chunks - 1 || (lane == chunks - 1 && j_th <= last_len) ? list_bits(v_jth) : 0u;
-        const uint32_t sorted = wave_sort_desc(lane_bits, lane);
-        uint32_t T = max(1u, (uint32_t)__builtin_amdgcn_readlane((int)sorted, m_th - 1));
-        const auto count = [&](uint32_t bound) {
-            int n = 0;
+            const float M = wave_max(m_t);
+            const float s = wave_sum(m_t == kNegInf ? 0.f : s_t * fast_exp(m_t - M));
+            if (lane == 0) S.lse = M + fast_log(s);
+        } else {
+            uint32_t lane_bits = 0u;
             for (int c0 = 0; c0 < chunks; c0 += 64 * H) {
                 load_heads(c0);
 #pragma unroll
-                for (int e = 0; e < H; ++e)
-                    if (c0 + 64 * e < chunks) n += __popcll(__ballot(bits_of(c0, e) >= bound));
+                for (int e = 0; e < H; ++e) lane_bits = max(lane_bits, bits_of(c0, e));
             }
-            return n;
-        };
-        // many lists at the bound (k close to 64): raise it while k of them reach it
-        int n = count(T), above = 0;
-        if (n > k + kCandSlack) {
-            uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)sorted) + 1u;        // no head reaches it
-            while (n > k + kCandSlack && hi - T > 1u) {
-                const uint32_t mid = T + (hi - T) / 2;
-                const int c = count(mid);
-                if (c >= k) { T = mid; n = c; } else { hi = mid; above = c; }
-            }
-        }
-        // Still more: lists with equal heads.  Of those, the first ones of the row suffice: their heads precede
-        // every entry of the later ones.
-        const bool ties = n > k + kCandSlack;
-        int quota = ties ? k - above : n;                        // lists with a head equal to T that are taken (above: the heads beyond it)
-        int at = 0;
-        for (int c0 = 0; c0 < chunks; c0 += 64 * H) {
-            load_heads(c0);
+            // (j-th entries: a lane has one list at most, the last one may not have as many; too few that have, or too few heads: everything)
+            if (j_th > 1) lane_bits = lane < chunks - 1 || (lane == chunks - 1 && j_th <= last_len) ? list_bits(v_jth) : 0u;
+            const uint32_t sorted = wave_sort_desc(lane_bits, lane);
+            uint32_t T = max(1u, (uint32_t)__builtin_amdgcn_readlane((int)sorted, m_th - 1));
+            const auto count = [&](uint32_t bound) {
+                int n = 0;
+                for (int c0 = 0; c0 < chunks; c0 += 64 * H) {
+                    load_heads(c0);
 #pragma unroll
-            for (int e = 0; e < H; ++e) {
-                if (c0 + 64 * e >= chunks) break;
-                const uint32_t b = bits_of(c0, e);
-                bool take = b >= T;
-                if (ties) {
-                    const uint64_t equal = __ballot(b == T);
-                    const int before = __builtin_amdgcn_mbcnt_hi((uint32_t)(equal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)equal, 0u));
-                    take = b > T || (b == T && before < quota);
-                    quota = max(0, quota - (int)__popcll(equal));
+                    for (int e = 0; e < H; ++e)
+                        if (c0 + 64 * e < chunks) n += __popcll(__ballot(bits_of(c0, e) >= bound));
                 }
-                const uint64_t mask = __ballot(take);
-                const int slot = at + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-                if (take && slot < kMergeLists) S.list[slot] = c0 + 64 * e + lane;
-                at += __popcll(mask);
+                return n;
+            };
+            // many lists at the bound (k close to 64): raise it while k of them reach it
+            int n = count(T), above = 0;
+            if (n > k + kCandSlack) {
+                uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)sorted) + 1u;        // no head reaches it
+                while (n > k + kCandSlack && hi - T > 1u) {
+                    const uint32_t mid = T + (hi - T) / 2;
+                    const int c = count(mid);
+                    if (c >= k) { T = mid; n = c; } else { hi = mid; above = c; }
+                }
             }
+            // Still more: lists with equal heads.  Of those, the first ones of the row suffice: their heads precede
+            // every entry of the later ones.
+            const bool ties = n > k + kCandSlack;
+            int quota = ties ? k - above : n;                        // lists with a head equal to T that are taken (above: the heads beyond it)
+            int at = 0;
+            for (int c0 = 0; c0 < chunks; c0 += 64 * H) {
+                load_heads(c0);
+#pragma unroll
+                for (int e = 0; e < H; ++e) {
+                    if (c0 + 64 * e >= chunks) break;
+                    const uint32_t b = bits_of(c0, e);
+                    bool take = b >= T;
+                    if (ties) {
+                        const uint64_t equal = __ballot(b == T);
+                        const int before = __builtin_amdgcn_mbcnt_hi((uint32_t)(equal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)equal, 0u));
+                        take = b > T || (b == T && before < quota);
+                        quota = max(0, quota - (int)__popcll(equal));
+                    }
+                    const uint64_t mask = __ballot(take);
+                    const int slot = at + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+                    if (take && slot < kMergeLists) S.list[slot] = c0 + 64 * e + lane;
+                    at += __popcll(mask);
+                }
+            }
+            if (lane == 0) { S.n_list = (uint32_t)min(at, kMergeLists); S.n_cand = 0u; S.T = T; S.all_lists = ties ? 0u : 1u; }
         }
-        if (lane == 0) { S.n_list = (uint32_t)min(at, kMergeLists); S.n_cand = 0u; S.T = T; S.all_lists = ties ? 0u : 1u; S.lse = lse; }
     } else if (wave == 1 && part_smp) {
         // the Gumbel-max draw: the largest z + g over the chunks (unique keys)
         const float4 *smp = part_smp + (size_t)row * chunks;
@@ -254,27 +376,10 @@ __global__ __launch_bounds__(kRowMergeThreads) void merge_kernel(
 
     // ---- the k first of them
     lse = S.lse;
-    const auto emit = [&](uint64_t key, int rank) {
-        const int id = (int)key_tiebreak(key);
-        out_ids[(size_t)row * k + rank] = id_map ? id_map[id] : id;      // truncated vocabulary: column -> vocabulary id
-        out_logprobs[(size_t)row * k + rank] = key_value(key) - lse;
-    };
-    if (part_smp && tid == NT - 1) {
-        const int id = (int)key_tiebreak(S.draw);
-        so.lse[row] = lse;
-        so.sample_ids[row] = id_map ? id_map[id] : id;
-        so.sample_logprobs[row] = S.draw_z - lse;
-    }
+    if (part_smp && tid == NT - 1) emit_draw(S.draw, S.draw_z);
     const int n = (int)S.n_cand;
     if (n <= kMergeSel) {
-        // by counting, the scan for every entry shared by as many lanes as there are (k = 64: one wavefront alone took 3 us)
-        const int p = lanes_per_item_log2(n, NT), P = 1 << p, c = tid >> p, part = tid & (P - 1);
-        const uint64_t mine = c < n ? S.cand[c] : kNoKey;
-        int rank = 0;
-#pragma unroll 4
-        for (int q = part; q < n; q += P) rank += S.cand[q] > mine ? 1 : 0;
-        rank = lanes_sum(rank, P);
-        if (c < n && part == 0 && rank < k) emit(mine, rank);
+        rank_by_counting(n);                                     // (k = 64: one wavefront alone took 3 us)
     } else if (wave == 0) {
         // as with the lists: the k-th largest lane maximum, raised where it admits many
         uint32_t lane_bits = 0u;
