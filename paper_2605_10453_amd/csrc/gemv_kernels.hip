@@ -38,8 +38,8 @@ __global__ __launch_bounds__(256) void widen_rows_kernel(
 // One block per chunk of 8 * lanes adjacent columns of the vocabulary.  M is the [K, V] weight matrix (bf16 or fp32).
 // A lane owns 8 adjacent columns; a wavefront's 64 lanes are 64 / lanes (`k_parts`) rows of M at a time, so a narrow
 // chunk fills the wavefront as well, and the NW k_parts lane groups of a block split the contraction into ranges of
-// `per` rows (a multiple of 8).  Their partial sums meet in shared memory in a fixed order, and wavefront i % NW reduces
-// row i of the chunk to (max, sum of exp, top-k) and writes the partial.
+// `per` rows (a multiple of 8).  Their partial sums meet in shared memory in a fixed order, and wavefront i % NW (a single row: the block,
+// block_row_epilogue) reduces row i of the chunk to (max, sum of exp, top-k) and writes the partial.
 //
 // What bounds it: the weights' way from HBM, as long as every CU has a block and asks for enough of them (plan.hpp chooses
 // the chunks for that); with small weights the chain of trips before and after: the contraction input (for one or two
@@ -141,6 +141,15 @@ __global__ __launch_bounds__(NW * 64) void stream_topk_kernel(
     const int cw = 8 * lanes, chunk_col = chunk * cw, col = chunk_col + 8 * g;
     const bool active = kp < k_parts && col < V;          // V is a multiple of 8: all 8 columns valid or none
 
+    __shared__ std::conditional_t<R == 1, BlockRowLds, char> one_row;
+    BlockRowPlan row_plan;
+    const auto plan_row = [&]() {                               // (behind the first loads)
+        if constexpr (R == 1) {
+            row_plan = make_block_row_plan(cw, chunk_col, V, k);
+            if (tid < kBoundGroups && tid >= row_plan.bound.n_groups) one_row.groups[tid] = 0u;
+        }
+    };
+
     float acc[R][8];
 #pragma unroll
     for (int i = 0; i < R; ++i)
@@ -228,6 +237,7 @@ __global__ __launch_bounds__(NW * 64) void stream_topk_kernel(
                 if (e0 + tid < n8) xs[e0 + tid] = v;
             }
         }
+        plan_row();
         __syncthreads();
         const auto fma_group = [&](const RawT *w, int j) __attribute__((always_inline)) {      // rows j + 8 kp ... of the lane group
             float xv[R][8];
@@ -270,7 +280,9 @@ __global__ __launch_bounds__(NW * 64) void stream_topk_kernel(
                     fma_group(w, j);
                 }
         }
-    } else if (active) {
+    } else {
+      plan_row();
+      if (active) {
         const float *x = static_cast<const float *>(x_src);
         const auto rows_from = [&](int j, auto n_tag) {         // (k_parts is 1)
             constexpr int N = decltype(n_tag)::value;
@@ -293,6 +305,7 @@ __global__ __launch_bounds__(NW * 64) void stream_topk_kernel(
         for (; j + U <= j1; j += U) rows_from(j, std::integral_constant<int, U>{});
         if constexpr (U > 8)
             for (; j < j1; j += 8) rows_from(j, std::integral_constant<int, 8>{});
+      }
     }
     const int part = wave * k_parts + kp;
     if (kp < k_parts && part < n_parts) {
@@ -304,6 +317,11 @@ __global__ __launch_bounds__(NW * 64) void stream_topk_kernel(
         }
     }
     __syncthreads();
+    if constexpr (R == 1) {
+        block_row_epilogue<NW>(one_row, row_plan, red, red2, n_parts, cw, chunk_col, tid, k, (size_t)row0 * chunks + chunk, part_ms, part_val, part_id, part_smp,
+                               gumbel_key(seed_lo, seed_hi, (uint32_t)row0));
+        return;
+    }
     // many lane groups (narrow chunks): every thread adds some of their sums first
     const float *sums = red;
     int n_sums = n_parts;
@@ -332,8 +350,7 @@ __global__ __launch_bounds__(NW * 64) void stream_topk_kernel(
         else if (cw <= 256) finish(std::integral_constant<int, 4>{}, topk_tag, draw_tag, i);
         else finish(std::integral_constant<int, 8>{}, topk_tag, draw_tag, i);
     };
-    // The block's tail, which nothing overlaps: a row's top-k by one wavefront, its draw by another where there are twice as many (one row, d = 5120, r = 640,
-    // V = 151936 47.4 -> 46.6 us a call, d = 4096, r = 512, V = 128256 35.7 -> 34.6, r = 256, V = 100000, k = 64 26.9 -> 25.9).
+    // The block's tail, which nothing overlaps: a row's top-k by one wavefront, its draw by another where there are twice as many.
     if constexpr (2 * R <= NW) {
         if (wave < rows_here) finish_row(std::true_type{}, std::false_type{}, wave);
         else if (part_smp && wave >= R && wave < R + rows_here) finish_row(std::false_type{}, std::true_type{}, wave - R);

@@ -3,6 +3,7 @@
 #pragma once
 #include "device_utils.hpp"
 #include "plan.hpp"
+#include <type_traits>
 
 namespace slimspec {
 
@@ -258,6 +259,166 @@ __device__ __forceinline__ void chunk_row_epilogue(const float *sums, int n, int
 #pragma unroll
     for (int e = 0; e < E; ++e) ob[e] = act(e) ? list_bits(z[e]) : 0u;
     wave_topk<E>(ob, E, id, lane, k, sel, cw, part_val + slot * k, part_id + slot * k);
+}
+
+// The same for the only row of a block, by all its wavefronts: what one wavefront does as a chain of dependent instructions, which nothing overlaps, takes
+// two barriers here.  A lane of the first four wavefronts, one per SIMD, has two adjacent columns: with more wavefronts they would wait for each
+// other's instructions.  sums [n][cw], sums2: room for kSumParts more.  All threads call, behind a barrier; S.groups are zeros beyond the plan's.
+//   (1) the partial sums of the columns, in two steps where they are many (narrow chunks: cw <= 256);
+//   (2) T: the smallest of the maxima of k groups of columns (device_utils.hpp), hence k elements reach it;
+//   (3) the elements that reach T are ranked by counting, eight by a wavefront at a time.
+// By time stamps the tail of d = 4096, r = 512, V = 128256 takes 1.5 us (one wavefront: 2.5), the call 32.0 (32.7).  With every wavefront of the block in
+// it the tail took 1.9, and 2 us more where the last chunk has few columns and all of them reached the bound.
+constexpr int kBlockRowWaves = 4, kBlockRowMine = 128;      // wavefronts with columns; keys of one's list at most
+struct BlockRowLds {
+    uint64_t mine[kBlockRowWaves][kBlockRowMine + 8], wave_draw[kBlockRowWaves];
+    uint32_t groups[512];                                        // (lanes without a class read beyond the 256)
+    int n_mine[kBlockRowWaves];
+    float wave_s[kBlockRowWaves], wave_draw_z[kBlockRowWaves], m;
+};
+struct BlockRowPlan { int lanes; BoundPlan bound; };
+__device__ __forceinline__ BlockRowPlan make_block_row_plan(int cw, int chunk_col, int V, int k) {
+    BlockRowPlan p;
+    p.lanes = min(cw, V - chunk_col) / 2;                        // cw and V are even
+    p.bound = make_bound_plan(p.lanes, k, 4);
+    return p;
+}
+template <int NW>
+__device__ __forceinline__ void block_row_epilogue(BlockRowLds &S, const BlockRowPlan &plan, const float *sums, float *sums2, int n, int cw, int chunk_col, int tid, int k,
+                                                   size_t slot, float2 *__restrict__ part_ms, float *__restrict__ part_val,
+                                                   int *__restrict__ part_id, float4 *__restrict__ part_smp, const GumbelKey &gk)
+{
+    static_assert(NW >= kBlockRowWaves, "the wavefronts with columns");
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const auto add = [&](const float2 *src, int n_src, int stride) {      // fixed order, the first rows of the contraction first
+        float2 s = make_float2(0.f, 0.f);
+        const auto batch = [&](auto n_tag) {
+            constexpr int N = decltype(n_tag)::value;
+            float2 v[N];
+#pragma unroll
+            for (int u = 0; u < N; ++u) v[u] = src[u * stride];
+#pragma unroll
+            for (int u = 0; u < N; ++u) { s.x += v[u].x; s.y += v[u].y; }
+            src += N * stride;
+        };
+        int p = n_src;
+        for (; p >= 16; p -= 16) batch(std::integral_constant<int, 16>{});
+        if (p & 8) batch(std::integral_constant<int, 8>{});
+        if (p & 4) batch(std::integral_constant<int, 4>{});
+        if (p & 2) batch(std::integral_constant<int, 2>{});
+        if (p & 1) batch(std::integral_constant<int, 1>{});
+        return s;
+    };
+    const int n2 = cw / 2;
+    if (n > kDirectParts) {
+        const int wide = n2 > 64 ? 1 : 0, cb = wave & wide, gi = wave >> wide, G = (NW >> wide) < kSumParts ? NW >> wide : kSumParts;
+        if (gi < G && 64 * cb + lane < n2)
+            reinterpret_cast<float2 *>(sums2)[gi * n2 + 64 * cb + lane] = add(reinterpret_cast<const float2 *>(sums) + gi * n2 + 64 * cb + lane, (n - gi + G - 1) / G, G * n2);
+        __syncthreads();
+        sums = sums2;
+        n = G;
+    }
+    const bool with_columns = wave * 64 < plan.lanes;            // (at most 256 lanes: the first four wavefronts)
+    const bool act = tid < plan.lanes;
+    const uint32_t id0 = (uint32_t)(chunk_col + 2 * tid);
+    float2 z = make_float2(kNegInf, kNegInf);
+    uint32_t b0 = 0u, b1 = 0u;
+    const int gl = plan.bound.gl, n_groups = plan.bound.n_groups;
+    if (with_columns) {
+        if (act) {
+            z = add(reinterpret_cast<const float2 *>(sums) + tid, n, n2);
+            b0 = list_bits(z.x); b1 = list_bits(z.y);
+        }
+        uint32_t most = max(b0, b1);
+        if (gl > 0) most = max(most, dpp_u32<0xB1>(most));
+        if (gl > 1) most = max(most, dpp_u32<0x4E>(most));
+        if (gl > 2) most = max(most, dpp_u32<0x141>(most));
+        if (gl > 3) most = max(most, dpp_u32<0x140>(most));
+        if (act && (tid & ((1 << gl) - 1)) == 0) S.groups[tid >> gl] = most;
+    }
+    __syncthreads();
+    int n_mine = 0;
+    if (with_columns) {
+        uint32_t T, top;
+        if (k <= 16) T = bound_of_groups(S.groups, plan.bound, k, lane, top);
+        else {
+            top = 0u;
+            for (int i = lane; i < n_groups; i += 64) top = max(top, S.groups[i]);
+            top = wave_max_u32(top);
+            T = ~wave_max_u32(~class_max(S.groups, plan.bound, k, lane));
+            T = plan.bound.all ? 1u : max(1u, T);
+        }
+        const float M = float_from_order_bits(top);              // (where it is no number, the sum of exponentials is none either)
+        // (two ballots are fewer instructions here than a prefix sum over the lanes)
+        const auto push = [&](bool take, uint32_t bits, uint32_t id) {
+            const uint64_t mask = __ballot(take);
+            const int at = n_mine + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+            if (take) S.mine[wave][at] = u64_from(bits, ~id);
+            n_mine += __popcll(mask);
+        };
+        push(b0 >= T, b0, id0);
+        push(b1 >= T, b1, id0 + 1u);
+        const float s = wave_sum(act ? fast_exp(z.x - M) + fast_exp(z.y - M) : 0.f);
+        S.wave_s[wave] = s;
+        S.m = M;                                                 // (the same in every wavefront)
+        if (part_smp) {                                          // the largest z + g
+            uint64_t best = kNoKey;
+            float zb = z.x;
+            if (act) {
+                best = make_key(z.x + gumbel_base2(gk, id0) * kLn2, id0);
+                const uint64_t k1 = make_key(z.y + gumbel_base2(gk, id0 + 1u) * kLn2, id0 + 1u);
+                if (k1 > best) { best = k1; zb = z.y; }
+            }
+            const uint64_t largest = wave_max_key(best);         // unique keys: one lane holds it
+            if (best == largest) { S.wave_draw[wave] = largest; S.wave_draw_z[wave] = zb; }
+        }
+    }
+    if (wave < kBlockRowWaves) {
+        if (lane < 8) S.mine[wave][n_mine + lane] = kNoKey;
+        S.n_mine[wave] = n_mine;
+    }
+    __syncthreads();
+    constexpr int RW = NW < 8 ? NW : 8;                          // wavefronts that go on: more would only wait for each other's instructions
+    if (wave >= RW) return;
+    const int n_waves = (plan.lanes + 63) >> 6;
+    if (tid == RW * 64 - 1) {
+        float s = S.wave_s[0];
+        for (int w = 1; w < n_waves; ++w) s += S.wave_s[w];      // fixed order
+        part_ms[slot] = make_float2(S.m, s);
+        if (part_smp) {
+            int best = 0;
+            for (int w = 1; w < n_waves; ++w)
+                if (S.wave_draw[w] > S.wave_draw[best]) best = w;
+            part_smp[slot] = make_float4(key_value(S.wave_draw[best]), __int_as_float((int)key_tiebreak(S.wave_draw[best])), S.wave_draw_z[best], 0.f);
+        }
+    }
+    // A wavefront ranks eight of all the lists' elements at a time.
+    int n_w[kBlockRowWaves], n_all = 0, longest = 0;
+#pragma unroll
+    for (int w = 0; w < kBlockRowWaves; ++w) {
+        n_w[w] = __builtin_amdgcn_readfirstlane(S.n_mine[w]);
+        n_all += n_w[w];
+        longest = max(longest, n_w[w]);
+    }
+    for (int c0 = 8 * wave; c0 < n_all; c0 += 8 * RW) {
+        const int c = c0 + (lane >> 3);
+        int at = c, before = 0;                                  // its place in the lists
+#pragma unroll
+        for (int w = 0; w + 1 < kBlockRowWaves; ++w) {
+            before += n_w[w];
+            at = c >= before ? c - before + (w + 1) * (kBlockRowMine + 8) : at;
+        }
+        const uint64_t key = c < n_all ? S.mine[0][at] : kNoKey;
+        const int rank = rank_in_lists(S.mine, n_w, longest, key, lane);
+        if (c < n_all && (lane & 7) == 0 && rank < k) {
+            part_val[slot * k + rank] = key_value(key);
+            part_id[slot * k + rank] = (int)key_tiebreak(key);
+        }
+    }
+    if (tid >= n_all && tid < k) {                               // fewer than k columns in this chunk
+        part_val[slot * k + tid] = kNegInf;
+        part_id[slot * k + tid] = kNoId;
+    }
 }
 
 }  // namespace slimspec
