@@ -390,6 +390,12 @@ inline RowsGeom make_rows_geom(int K, int V) {
     g.chunks = (groups + g.G - 1) / g.G;
     return g;
 }
+// The slices of the contraction are added at once, from a place of their own each, by all threads: the more slices and the fewer rows (only rows
+// that exist are written), the more that saves.  (One after the other / at once, us a call: 8 slices, d = 4096, r = 512, V = 20000 8 rows 22.4 / 21.6,
+// 16 rows 22.9 / 22.1, 32 rows 29.2 / 29.4, V = 32768 28.9 / 29.5; 4 slices, d = 1024, r = 128, V = 65536 3 rows 15.6 / 15.3, 8 rows 16.0 / 15.9, 16 rows 17.1 / 17.3.)
+constexpr int kRowsMaxKS = 8;
+constexpr size_t kRowsLdsLimit = 156 * 1024;
+inline bool rows_meet_at_once(int KS, int rows) { return KS > 2 && KS <= kRowsMaxKS && rows <= (KS > 4 ? 16 : 8); }
 // Its down-projection in one launch (down_rows.hip) or in two (down_tile.hip).  One block per 16 columns of t reads all of h and
 // of its columns of A, 32 bytes of every row: that takes longer than the second launch once there are many rows of either, and
 // from 1 KB per row of A on they come from few of the L2's channels.  Calls at V = 32768 (one / two launches, us; rows of the largest

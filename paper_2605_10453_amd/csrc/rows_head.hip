@@ -27,6 +27,7 @@
 // log-probabilities against 64-bit arithmetic: 7.7e-8 relative, 1.0e-7 with one multiply-add per weight (40 rows, k = 32).
 #include "gemv_parts.hpp"
 #include "launch.hpp"
+#include <type_traits>
 
 namespace slimspec {
 
@@ -51,6 +52,9 @@ constexpr int kPairKeys = kPairCand + 2; // (the two rows' candidates in differe
 constexpr __host__ __device__ size_t rows_x_offset(int NT, int G, int waves, int k) {
     return sizeof(float) * 16 * NT * (size_t)rows_lds_stride(G) + (k <= kPairMaxK ? sizeof(uint64_t) * 2 * kPairKeys * waves : 0);
 }
+
+// Floats between two rows of a slice's sums.
+constexpr __host__ __device__ int rows_meet_stride(int G) { return 128 * G + 4; }
 
 // Sum over each half of 32 lanes, in every lane of it.
 __device__ __forceinline__ float half_sum(float v) {
@@ -97,11 +101,12 @@ __device__ __forceinline__ float max3_number(float a, float b, float c) { float 
 // GM: G at most (what a lane keeps of a row's logits is sized by it: known when compiled, or every step of the epilogue branches)
 // SUM (NT 1, NP 3): X is not given; the block adds the nds slices of t, fp32 [nds][rows][K], itself and keeps the pieces in shared memory,
 // where a small t takes less time than a launch that does it once (plan.hpp: rows_sum_slices).
+// meet_at: where in shared memory, in floats, the slices of the contraction leave their sums; 0: no place for them.
 template <int NT, int NP, int GM, bool SUM>
 __global__ __launch_bounds__(512) void rows_topk_kernel(
     const uint4 *__restrict__ X, const float *__restrict__ slices, int nds, const uint16_t *__restrict__ M,
     float2 *__restrict__ part_ms, float *__restrict__ part_val, int *__restrict__ part_id, float4 *__restrict__ part_smp,
-    int rows, int row0, int K, int V, int chunks, int G, int KS, int k, uint32_t seed_lo, uint32_t seed_hi)
+    int rows, int row0, int K, int V, int chunks, int G, int KS, int k, uint32_t seed_lo, uint32_t seed_hi, int meet_at)
 {
     extern __shared__ __align__(16) float z_lds[];               // [16 NT][row_stride]
     constexpr int RP = 16 * NT;
@@ -268,26 +273,98 @@ __global__ __launch_bounds__(512) void rows_topk_kernel(
         }
     }
 
-    // the slices of the contraction meet in shared memory, the last slice first (a fixed order)
-    for (int kk = KS - 1; kk >= 0; --kk) {
-        if (ks == kk) {
+    // The slices of the contraction meet in shared memory, the last slice first (a fixed order).  Element (m = 4 kg + i, n = c16) of tile j
+    // is column 8 m + j of row 16 nt + n.  One slice after the other, each reading what the one before it left, is a chain of KS trips
+    // and barriers behind the last weights, most wavefronts idle.  So few rows are added at once, by all threads, where a slice has a place
+    // of its own (plan.hpp: rows_meet_at_once), and two slices finish half of the elements each.  One after the other / now, us a call: full
+    // head, 4 rows, d = 1024, V = 32000 21.3 / 19.7, 7 rows, d = 4096, V = 20000 43.0 / 42.1; d = 4096, r = 512: 8 rows, V = 32768 23.3 / 22.4,
+    // 16 rows 23.4 / 22.6; two slices: 40 rows, k = 32, V = 128256 53.0 / 52.7, 32 rows, V = 90000 39.7 / 39.3.
+    const auto place = [&](int nt, int i) { return z_lds + (16 * nt + c16) * row_stride + cg * 128 + 8 * (4 * kg + i); };
+    const auto put_sums = [&](float *at, int stride) {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+            if (16 * nt + c16 < rows) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    float4 *dst = reinterpret_cast<float4 *>(at + (16 * nt + c16) * stride + cg * 128 + 8 * (4 * kg + i));
+                    dst[0] = make_float4(acc[0][nt][i], acc[1][nt][i], acc[2][nt][i], acc[3][nt][i]);
+                    dst[1] = make_float4(acc[4][nt][i], acc[5][nt][i], acc[6][nt][i], acc[7][nt][i]);
+                }
+            }
+    };
+    if (meet_at > 0) {
+        const int stride = rows_meet_stride(G), region = rows * stride;
+        float *const others = z_lds + meet_at;                   // [KS - 1][rows][stride]; slice 0's are where the logits go
+        if (ks < KS) put_sums(ks == 0 ? z_lds : others + (ks - 1) * region, ks == 0 ? row_stride : stride);
+        __syncthreads();
+        const int items = rows * G, per_row = (65536 + G - 1) / G;       // a half-wavefront takes 128 columns of a row
+        for (int e = tid >> 5; e < items; e += (int)(blockDim.x >> 5)) {
+            const int row = e * per_row >> 16, col = 128 * (e - row * G) + 4 * (lane & 31);
+            const float *src = others + row * stride + col;
+            float4 *dst = reinterpret_cast<float4 *>(z_lds + row * row_stride + col);
+            float4 p[kRowsMaxKS];
+#pragma unroll
+            for (int u = 0; u < kRowsMaxKS; ++u) {
+                if (u >= KS) break;
+                p[u] = u == 0 ? dst[0] : *reinterpret_cast<const float4 *>(src + (u - 1) * region);
+            }
+            float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+            for (int u = kRowsMaxKS - 1; u >= 0; --u) {
+                if (u >= KS) continue;
+                if (u == KS - 1) a = p[u];
+                else { a.x += p[u].x; a.y += p[u].y; a.z += p[u].z; a.w += p[u].w; }
+            }
+            dst[0] = a;
+        }
+        __syncthreads();
+    } else if (KS == 2) {
+        // either slice finishes half of the elements: the other's half of its own waits where the logits go
+        const auto half_of = [&](auto first) {
+            constexpr int F = decltype(first)::value;
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    // element (m = 4 kg + i, n = c16) of tile j is column 8 m + j of row 16 nt + n
-                    float4 *dst = reinterpret_cast<float4 *>(z_lds + (16 * nt + c16) * row_stride + cg * 128 + 8 * (4 * kg + i));
-                    float4 a = make_float4(acc[0][nt][i], acc[1][nt][i], acc[2][nt][i], acc[3][nt][i]);
-                    float4 b = make_float4(acc[4][nt][i], acc[5][nt][i], acc[6][nt][i], acc[7][nt][i]);
-                    if (kk != KS - 1) {
-                        const float4 c = dst[0], d = dst[1];
-                        a.x += c.x; a.y += c.y; a.z += c.z; a.w += c.w;
-                        b.x += d.x; b.y += d.y; b.z += d.z; b.w += d.w;
-                    }
-                    dst[0] = a; dst[1] = b;
+                for (int i = 2 - F; i < 4 - F; ++i) {
+                    float4 *dst = reinterpret_cast<float4 *>(place(nt, i));
+                    dst[0] = make_float4(acc[0][nt][i], acc[1][nt][i], acc[2][nt][i], acc[3][nt][i]);
+                    dst[1] = make_float4(acc[4][nt][i], acc[5][nt][i], acc[6][nt][i], acc[7][nt][i]);
                 }
-        }
+            __syncthreads();
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int i = F; i < F + 2; ++i) {
+                    float4 *dst = reinterpret_cast<float4 *>(place(nt, i));
+                    const float4 c = dst[0], d = dst[1];
+                    dst[0] = make_float4(acc[0][nt][i] + c.x, acc[1][nt][i] + c.y, acc[2][nt][i] + c.z, acc[3][nt][i] + c.w);
+                    dst[1] = make_float4(acc[4][nt][i] + d.x, acc[5][nt][i] + d.y, acc[6][nt][i] + d.z, acc[7][nt][i] + d.w);
+                }
+        };
+        if (ks == 0) half_of(std::integral_constant<int, 0>{});
+        else if (ks == 1) half_of(std::integral_constant<int, 2>{});
+        else __syncthreads();
         __syncthreads();
+    } else {
+        for (int kk = KS - 1; kk >= 0; --kk) {
+            if (ks == kk) {
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        float4 *dst = reinterpret_cast<float4 *>(place(nt, i));
+                        float4 a = make_float4(acc[0][nt][i], acc[1][nt][i], acc[2][nt][i], acc[3][nt][i]);
+                        float4 b = make_float4(acc[4][nt][i], acc[5][nt][i], acc[6][nt][i], acc[7][nt][i]);
+                        if (kk != KS - 1) {
+                            const float4 c = dst[0], d = dst[1];
+                            a.x += c.x; a.y += c.y; a.z += c.z; a.w += c.w;
+                            b.x += d.x; b.y += d.y; b.z += d.z; b.w += d.w;
+                        }
+                        dst[0] = a; dst[1] = b;
+                    }
+            }
+            __syncthreads();
+        }
     }
 
     // One row by a whole wavefront: running max, sum of exp and top-k of the chunk.  Lane = columns 2 lane, 2 lane + 1 of every
@@ -521,12 +598,15 @@ template <int NT, int NP, int GM, bool SUM>
 static hipError_t launch_rows(const RowsInput &x, const uint16_t *M, float2 *ms, float *pv, int *pi, float4 *smp, int rows, int row0,
                               int K, int V, const RowsGeom &g, int k, uint32_t seed_lo, uint32_t seed_hi, hipStream_t st)
 {
-    const size_t lds = rows_x_offset(NT, g.G, g.waves, k) + (SUM ? sizeof(uint4) * 3 * 16 * (size_t)((K + 63) / 64 * 8) : 0);
+    size_t lds = rows_x_offset(NT, g.G, g.waves, k) + (SUM ? sizeof(uint4) * 3 * 16 * (size_t)((K + 63) / 64 * 8) : 0);
+    int meet_at = 0;                     // floats before the slices' sums, 0: not so
+    const size_t meet = sizeof(float) * (size_t)(g.KS - 1) * rows * rows_meet_stride(g.G);
+    if (rows_meet_at_once(g.KS, rows) && lds + meet <= kRowsLdsLimit) { meet_at = (int)(lds / sizeof(float)); lds += meet; }
     static LdsLimit lds_limit;
     hipError_t e = lds_limit.raise(reinterpret_cast<const void *>(rows_topk_kernel<NT, NP, GM, SUM>), (int)lds);
     if (e != hipSuccess) return e;
     rows_topk_kernel<NT, NP, GM, SUM><<<g.chunks, 64 * g.waves, lds, st>>>(static_cast<const uint4 *>(x.X), x.slices, x.nds, M, ms, pv, pi, smp,
-                                                                           rows, row0, K, V, g.chunks, g.G, g.KS, k, seed_lo, seed_hi);
+                                                                           rows, row0, K, V, g.chunks, g.G, g.KS, k, seed_lo, seed_hi, meet_at);
     return hipGetLastError();
 }
 
