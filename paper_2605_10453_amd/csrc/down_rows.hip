@@ -11,6 +11,7 @@
 //     happen at the size of one step's sum.
 #include "device_utils.hpp"
 #include "launch.hpp"
+#include "read_ahead.hpp"
 
 namespace slimspec {
 
@@ -29,10 +30,10 @@ constexpr int kDRCols = 16;
 
 // X: [3][8 ceil(r / 64)][rows_pad] 16-byte vectors of 8 consecutive columns of t; zero beyond r and beyond the last row.
 // Block (XCD-aware number b of a 16-column tile, group y): the rows of group y with the group's matrix; NT: 16-row tiles of the
-// largest group.
+// largest group.  Blocks beyond the tiles read weights ahead.
 template <int NT>
 __global__ __launch_bounds__(64 * kDRWaves) void down_rows_kernel(
-    const uint16_t *__restrict__ h, const uint16_t *__restrict__ A, uint4 *__restrict__ X, int rows_pad, int d, int r, DownGrid g)
+    const uint16_t *__restrict__ h, const uint16_t *__restrict__ A, uint4 *__restrict__ X, int rows_pad, int d, int r, DownGrid g, ReadAhead ahead)
 {
     constexpr int kDRBatch = NT == 1 ? 8 : 4;                          // steps in flight per wavefront
     __shared__ __align__(16) float part[kDRWaves][NT][4][64];          // [wavefront][row tile][element][lane]; before that the wavefronts' tiles of A
@@ -40,7 +41,13 @@ __global__ __launch_bounds__(64 * kDRWaves) void down_rows_kernel(
     static_assert(sizeof(part[0]) >= 1024, "a wavefront's 32 x 16 tile of A fits where its sums go later");
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int n_tiles = gridDim.x, tile = (n_tiles & 7) == 0 ? (int)(blockIdx.x & 7) * (n_tiles >> 3) + (int)(blockIdx.x >> 3) : (int)blockIdx.x;
+    const int n_tiles = (r + 63) / 64 * 4;
+    if ((int)blockIdx.x >= n_tiles) {
+        const int first = (n_tiles + 7) & ~7;
+        if ((int)blockIdx.x >= first && blockIdx.y == 0) read_ahead_block<kDRWaves>(ahead, (int)blockIdx.x - first);
+        return;
+    }
+    const int tile = (n_tiles & 7) == 0 ? (int)(blockIdx.x & 7) * (n_tiles >> 3) + (int)(blockIdx.x >> 3) : (int)blockIdx.x;
     const int grp = blockIdx.y, n0 = tile * kDRCols;
     const int lo = g.g_row0[grp], hi = g.g_row0[grp + 1];
     const int kg = lane >> 4, l16 = lane & 15;
@@ -132,20 +139,21 @@ __global__ __launch_bounds__(64 * kDRWaves) void down_rows_kernel(
 }
 
 template <int NT>
-static hipError_t launch_down_rows_nt(const uint16_t *h, const uint16_t *A, void *X, int rows_pad, int d, int r, const DownGrid &g, hipStream_t st)
+static hipError_t launch_down_rows_nt(const uint16_t *h, const uint16_t *A, void *X, int rows_pad, int d, int r, const DownGrid &g, const ReadAhead &ahead, hipStream_t st)
 {
-    const dim3 grid((r + 63) / 64 * 4, g.n_groups);
-    down_rows_kernel<NT><<<grid, 64 * kDRWaves, 0, st>>>(h, A, static_cast<uint4 *>(X), rows_pad, d, r, g);
+    const int n_tiles = (r + 63) / 64 * 4;
+    const dim3 grid(ahead.blocks ? (n_tiles + 7) / 8 * 8 + ahead.blocks : n_tiles, g.n_groups);
+    down_rows_kernel<NT><<<grid, 64 * kDRWaves, 0, st>>>(h, A, static_cast<uint4 *>(X), rows_pad, d, r, g, ahead);
     return hipGetLastError();
 }
 
-hipError_t launch_down_rows(const uint16_t *h, const uint16_t *A, void *X, int rows_pad, int d, int r, const DownGrid &g, hipStream_t st)
+hipError_t launch_down_rows(const uint16_t *h, const uint16_t *A, void *X, int rows_pad, int d, int r, const DownGrid &g, const ReadAhead &ahead, hipStream_t st)
 {
     int most = 0;
     for (int q = 0; q < g.n_groups; ++q) most = g.g_row0[q + 1] - g.g_row0[q] > most ? g.g_row0[q + 1] - g.g_row0[q] : most;
-    if (most <= 16) return launch_down_rows_nt<1>(h, A, X, rows_pad, d, r, g, st);
-    if (most <= 32) return launch_down_rows_nt<2>(h, A, X, rows_pad, d, r, g, st);
-    return launch_down_rows_nt<3>(h, A, X, rows_pad, d, r, g, st);
+    if (most <= 16) return launch_down_rows_nt<1>(h, A, X, rows_pad, d, r, g, ahead, st);
+    if (most <= 32) return launch_down_rows_nt<2>(h, A, X, rows_pad, d, r, g, ahead, st);
+    return launch_down_rows_nt<3>(h, A, X, rows_pad, d, r, g, ahead, st);
 }
 
 }  // namespace slimspec

@@ -17,6 +17,7 @@
 // "my part of the stage needed next has landed", and the barrier that follows publishes the stage.
 #include "device_utils.hpp"
 #include "launch.hpp"
+#include "read_ahead.hpp"
 #include <type_traits>
 
 namespace slimspec {
@@ -141,11 +142,14 @@ __device__ __forceinline__ void column_scale_block(const uint16_t *__restrict__ 
 // the matrix unit's internal roundings then happen at the size of one step's sum.
 // ROWS: part is [slices][rows][r] instead, row by row and without the rows of padding.
 // GRID: DownGrid, or JointDownGrid for two launches' rows.
+// Blocks from n_blocks on (ROWS) read weights ahead.
 template <bool STEPWISE, bool ROWS, class GRID>
 __global__ __launch_bounds__(256) void down_tile_kernel(
     const uint16_t *__restrict__ h, const uint16_t *__restrict__ A, float *__restrict__ part,
-    int d, int r, GRID g)
+    int d, int r, int n_blocks, GRID g, ReadAhead ahead)
 {
+    if constexpr (ROWS)
+        if ((int)blockIdx.x >= n_blocks) { read_ahead_block<4>(ahead, (int)blockIdx.x - n_blocks); return; }
     extern __shared__ __align__(1024) unsigned char lds_raw[];
     const uint32_t lds0 = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) unsigned char *)lds_raw);
     const int tid = threadIdx.x, lane = tid & 63;
@@ -294,17 +298,22 @@ __global__ __launch_bounds__(256) void down_tile_kernel(
 //                                      zero for k >= r and for padding rows; kOperandTwoBf16: the second pieces behind them
 //   stat  [2 ceil(r / 64), rows_pad]   per 32-column piece: (sum of (t - its 16-bit value)^2, sum of t^2) of its entries
 // PIECES: t leaves as three bf16 pieces instead, t16 [3][8 ceil(r / 64)][rows_pad] (no t32, stat or column scales).
-// The pieces are cut off the top of t's significand, 8 bits each: their sum is t exactly.
+// The pieces are cut off the top of t's significand, 8 bits each: their sum is t exactly.  Further blocks of the launch read weights ahead.
 template <bool PIECES, class GRID>
 __global__ __launch_bounds__(256) void down_finish_kernel(
     const float *__restrict__ part, int rows_pad, int r,
     float *__restrict__ t32, uint4 *__restrict__ t16, float2 *__restrict__ stat,
-    const uint16_t *__restrict__ B, int V, float2 *__restrict__ tilescale, int operand, GRID g)
+    const uint16_t *__restrict__ B, int V, float2 *__restrict__ tilescale, int operand, GRID g, ReadAhead ahead)
 {
     __shared__ float tile[32 * 33];
     __shared__ float red_a[4 * 32], red_b[4 * 32];
     __shared__ float colsh[3 * 64 * 8];
     const int tid = threadIdx.x;
+    if (PIECES && (int)blockIdx.x >= 4 * g.n_rt_all * g.n_ct) {
+        const int first = (4 * g.n_rt_all * g.n_ct + 7) & ~7;
+        if ((int)blockIdx.x >= first) read_ahead_block<4>(ahead, (int)blockIdx.x - first);
+        return;
+    }
     if (!PIECES && (int)blockIdx.x >= 4 * g.n_rt_all * g.n_ct) {
         // (next to the tile kernel's blocks instead, these blocks cost 6.7 us at 512 rows; here 2-3)
         column_scale_block(B, r, V, tilescale, (int)blockIdx.x - 4 * g.n_rt_all * g.n_ct, colsh, tid);
@@ -431,12 +440,12 @@ __global__ __launch_bounds__(256) void down_finish_kernel(
 }
 
 template <bool STEPWISE, bool ROWS, class GRID>
-static hipError_t launch_down_tiles(const uint16_t *h, const uint16_t *A, float *part, const GRID &g, int blocks, int d, int r, hipStream_t st)
+static hipError_t launch_down_tiles(const uint16_t *h, const uint16_t *A, float *part, const GRID &g, int blocks, int d, int r, const ReadAhead &ahead, hipStream_t st)
 {
     static LdsLimit lds_limit;
     hipError_t e = lds_limit.raise(reinterpret_cast<const void *>(down_tile_kernel<STEPWISE, ROWS, GRID>), kDLds);
     if (e != hipSuccess) return e;
-    down_tile_kernel<STEPWISE, ROWS, GRID><<<blocks, 256, kDLds, st>>>(h, A, part, d, r, g);
+    down_tile_kernel<STEPWISE, ROWS, GRID><<<blocks + ahead.blocks, 256, kDLds, st>>>(h, A, part, d, r, blocks, g, ahead);
     return hipGetLastError();
 }
 
@@ -446,27 +455,27 @@ hipError_t launch_down_projection_tiles(const uint16_t *h, const uint16_t *A, fl
                                         Operand operand, hipStream_t st)
 {
     const auto launch = [&](const auto &g, int blocks) {
-        const hipError_t e = launch_down_tiles<false, false>(h, A, part, g, blocks, d, r, st);
+        const hipError_t e = launch_down_tiles<false, false>(h, A, part, g, blocks, d, r, ReadAhead(), st);
         if (e != hipSuccess) return e;
         down_finish_kernel<false><<<4 * g.n_rt_all * g.n_ct + (V + 511) / 512, 256, 0, st>>>(
-            part, rows_pad, r, t32, static_cast<uint4 *>(t16), stat, B, V, tilescale, operand, g);
+            part, rows_pad, r, t32, static_cast<uint4 *>(t16), stat, B, V, tilescale, operand, g, ReadAhead());
         return hipGetLastError();
     };
     return second ? launch(join_down_grids(first, *second), down_tile_blocks(first) + down_tile_blocks(*second)) : launch(first, down_tile_blocks(first));
 }
 
-hipError_t launch_down_projection_slices(const uint16_t *h, const uint16_t *A, float *slices, const DownGrid &g, int d, int r, hipStream_t st)
+hipError_t launch_down_projection_slices(const uint16_t *h, const uint16_t *A, float *slices, const DownGrid &g, int d, int r, const ReadAhead &ahead, hipStream_t st)
 {
-    return launch_down_tiles<true, true>(h, A, slices, g, down_tile_blocks(g), d, r, st);
+    return launch_down_tiles<true, true>(h, A, slices, g, down_tile_blocks(g), d, r, ahead, st);
 }
 
 hipError_t launch_down_projection_pieces(const uint16_t *h, const uint16_t *A, float *part, const DownGrid &g,
-                                         int rows_pad, int d, int r, void *X, hipStream_t st)
+                                         int rows_pad, int d, int r, void *X, const ReadAhead &ahead, hipStream_t st)
 {
-    const hipError_t e = launch_down_tiles<true, false>(h, A, part, g, down_tile_blocks(g), d, r, st);
+    const hipError_t e = launch_down_tiles<true, false>(h, A, part, g, down_tile_blocks(g), d, r, ReadAhead(), st);
     if (e != hipSuccess) return e;
-    down_finish_kernel<true><<<4 * g.n_rt_all * g.n_ct, 256, 0, st>>>(
-        part, rows_pad, r, nullptr, static_cast<uint4 *>(X), nullptr, nullptr, 0, nullptr, kOperandExact, g);
+    down_finish_kernel<true><<<(4 * g.n_rt_all * g.n_ct + 7) / 8 * 8 + ahead.blocks, 256, 0, st>>>(
+        part, rows_pad, r, nullptr, static_cast<uint4 *>(X), nullptr, nullptr, 0, nullptr, kOperandExact, g, ahead);
     return hipGetLastError();
 }
 

@@ -83,16 +83,17 @@ hipError_t launch_down_projection_tiles(const uint16_t *h, const uint16_t *A, fl
                                         float *t32, void *t16, float2 *stat, const uint16_t *B, int V, float2 *tilescale,
                                         Operand operand, hipStream_t st);
 
+// ahead: the weights that further blocks of the launch read (plan.hpp: rows_read_ahead)
 // the same t as three bf16 pieces, t = hi + mid + lo exactly (rows_head.hip): X [3][8 ceil(r / 64)][rows_pad] 16-byte
 // vectors, zero beyond r and beyond the last row
 hipError_t launch_down_projection_pieces(const uint16_t *h, const uint16_t *A, float *part, const DownGrid &g,
-                                         int rows_pad, int d, int r, void *X, hipStream_t st);
+                                         int rows_pad, int d, int r, void *X, const ReadAhead &ahead, hipStream_t st);
 
 // ... its slices alone, [g.slices][rows][r] fp32 (plan.hpp: rows_sum_slices)
-hipError_t launch_down_projection_slices(const uint16_t *h, const uint16_t *A, float *slices, const DownGrid &g, int d, int r, hipStream_t st);
+hipError_t launch_down_projection_slices(const uint16_t *h, const uint16_t *A, float *slices, const DownGrid &g, int d, int r, const ReadAhead &ahead, hipStream_t st);
 
 // ... in one launch, for up to kRowsMaxRows rows (down_rows.hip; plan.hpp: down_rows_takes)
-hipError_t launch_down_rows(const uint16_t *h, const uint16_t *A, void *X, int rows_pad, int d, int r, const DownGrid &g, hipStream_t st);
+hipError_t launch_down_rows(const uint16_t *h, const uint16_t *A, void *X, int rows_pad, int d, int r, const DownGrid &g, const ReadAhead &ahead, hipStream_t st);
 
 // Partials per (row, chunk of 128 G columns) for up to kRowsMaxRows rows, the weights read once (rows_head.hip).
 // X: [pieces][8 ceil(K / 64)][16 ceil(rows / 16)] 16-byte vectors; pieces 1: the bf16 input itself, 3: the pieces of t

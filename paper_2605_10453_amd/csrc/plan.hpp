@@ -112,6 +112,42 @@ inline bool own_input_takes(const ChunkGeom &g, int rows, int d, int r, int V, b
     return rows == 1 && r <= 128 && (int64_t)d * r <= 32768 && V <= 256 * kChunkCols && g.nw1 <= 8 && (r <= 64 || V <= kOwnShortV || sampling);
 }
 
+// ---- reading weights ahead (read_ahead.hpp) ------------------------------------------------------------------------
+// The launches that make t for rows_topk_kernel leave the memory idle.  Further blocks of them read the weights that its blocks ask for
+// first into the L2 (4 MB) of the XCD that will ask: a launch's blocks are dealt to the XCDs in turn, always from the first one on, and
+// a line stays there from one launch to the next.
+constexpr int kAheadLoads = 12;          // of a wavefront, a kilobyte each (16: a CU with such a block takes longer than the others; 8: more blocks)
+struct ReadAhead {
+    const uint16_t *M = nullptr;         // [K, V]
+    int K = 0, V = 0;
+    int lanes = 64, halves = 0;          // a unit is 8 lanes adjacent columns, a chunk of rows_topk_kernel 1 << halves units
+    int n_units = 0, chunks = 0;         // units per XCD, chunks in all
+    int n_ranges = 1, per = 0;           // its slices of the contraction, `per` rows each
+    int rows_step = 1, n_t = 0;          // the first n_t steps of 64 / lanes rows of each
+    int q_n = 0, q_div = 0, q_mod = 0;   // wavefronts per unit, and that number by n_ranges
+    uint32_t units_inverse = 0, ranges_inverse = 0;      // 2^32 / n, rounded up
+    int blocks = 0;                      // of the launch, a multiple of 8; 0: nothing to read
+};
+// A wavefront's place: unit and first (range, step); slot: its number among those of its XCD.
+struct AheadSlot { bool on; int col0, t, range; };
+constexpr __host__ __device__ int ahead_quotient(int n, int by, uint32_t inverse) { return by == 1 ? n : (int)(((uint64_t)(uint32_t)n * inverse) >> 32); }
+constexpr __host__ __device__ AheadSlot ahead_slot(const ReadAhead &a, int xcd, int slot) {
+    const int q = ahead_quotient(slot, a.n_units, a.units_inverse), unit = slot - q * a.n_units;
+    const int chunk = xcd + 8 * (unit >> a.halves);
+    const int t = ahead_quotient(q, a.n_ranges, a.ranges_inverse);
+    return {q < a.q_n && chunk < a.chunks, 8 * a.lanes * ((chunk << a.halves) + (unit & ((1 << a.halves) - 1))), t, q - t * a.n_ranges};
+}
+// The first of the rows_step rows of a load; a wavefront's loads beyond the last step repeat it.
+constexpr __host__ __device__ int ahead_row(const ReadAhead &a, const AheadSlot &s) {
+    const int row = s.range * a.per + (s.t < a.n_t ? s.t : a.n_t - 1) * a.rows_step;
+    return row < a.K - a.rows_step ? row : a.K - a.rows_step;
+}
+constexpr __host__ __device__ void ahead_next(const ReadAhead &a, AheadSlot &s) {
+    s.t += a.q_div;
+    s.range += a.q_mod;
+    if (s.range >= a.n_ranges) { s.range -= a.n_ranges; ++s.t; }
+}
+
 struct Plan {
     bool ok = false;
     int rows = 0, d = 0, r = 0, V = 0, k = 0;
@@ -396,6 +432,36 @@ inline RowsGeom make_rows_geom(int K, int V) {
 constexpr int kRowsMaxKS = 8;
 constexpr size_t kRowsLdsLimit = 156 * 1024;
 inline bool rows_meet_at_once(int KS, int rows) { return KS > 2 && KS <= kRowsMaxKS && rows <= (KS > 4 ? 16 : 8); }
+// What a launch before rows_topk_kernel reads ahead: the beginning of every slice of the contraction, in blocks of nw wavefronts.  How much: what
+// comes while the launch's own blocks work; more makes it longer.  (Nothing / this, us a call: down_rows_kernel, 9 MB: 7 rows, d = 1024, r = 256, V = 30000
+// 16.7 / 15.2; 5 rows, r = 128, V = 128256 18.0 / 17.0 (6 MB 17.2, 16 MB 17.0); 16 rows, d = 2048, r = 256, V = 65536 21.5 / 20.3 (6 MB 20.7, 16 MB 20.5); 12 rows in four
+// positions, r = 200, V = 60000 18.7 / 17.9 (16 MB 18.4).  The slices of up to 8 rows, 8 MB: d = 4096, r = 256, V = 128256 25.0 / 24.4 (4 MB 25.1); 4 rows
+// of the router 51.5 / 50.3.  The kernel that adds the slices, 4 MB: 12 rows, d = 4096, r = 512, V = 60000 28.4 / 27.2, 30 rows, d = 3000, r = 400, V = 20000 28.1 / 27.6, 23 rows
+// 41.1 / 40.8, 40 rows, k = 32 52.1 / 51.7; not the tile kernel before it, which its loads delay: 40 rows, d = 6000, r = 1000, V = 100000 69.7 / 70.2, and 69.4
+// with the former alone.  Nor the down-projection of one row, whose blocks fill the CUs: 32.2 / 32.1, 45.7 / 45.6.)
+constexpr int kAheadDownRows = 9 << 20, kAheadSlices = 8 << 20, kAheadFinish = 4 << 20;
+inline ReadAhead rows_read_ahead(const uint16_t *M, int K, int V, const RowsGeom &g, int bytes, int nw) {
+    ReadAhead a;
+    const int steps = (K + 31) / 32, per = (steps + g.KS - 1) / g.KS;
+    a.n_ranges = (steps + per - 1) / per;
+    a.per = 32 * per;
+    const int64_t fits = bytes / (2 * (int64_t)V * a.n_ranges);
+    const int rows = fits < a.per ? (int)fits : a.per;       // of every slice
+    if (rows < 1) return a;
+    a.M = M; a.K = K; a.V = V;
+    a.lanes = 16 * g.G;
+    while (a.lanes > 64) { a.lanes /= 2; ++a.halves; }
+    a.rows_step = 64 / a.lanes;
+    a.n_t = (rows + a.rows_step - 1) / a.rows_step;
+    a.chunks = g.chunks;
+    a.n_units = (a.chunks + 7) / 8 << a.halves;
+    a.q_n = (a.n_ranges * a.n_t + kAheadLoads - 1) / kAheadLoads;
+    a.q_div = a.q_n / a.n_ranges; a.q_mod = a.q_n % a.n_ranges;
+    const auto inverse = [](int n) { return (uint32_t)(((uint64_t(1) << 32) + n - 1) / n); };
+    a.units_inverse = inverse(a.n_units); a.ranges_inverse = inverse(a.n_ranges);
+    a.blocks = 8 * ((a.n_units * a.q_n + nw - 1) / nw);
+    return a;
+}
 // Its down-projection in one launch (down_rows.hip) or in two (down_tile.hip).  One block per 16 columns of t reads all of h and
 // of its columns of A, 32 bytes of every row: that takes longer than the second launch once there are many rows of either, and
 // from 1 KB per row of A on they come from few of the L2's channels.  Calls at V = 32768 (one / two launches, us; rows of the largest

@@ -222,18 +222,19 @@ int run_head_rows(HeadKind kind, const void *h, const void *A, const void *M, co
         hipError_t e;
         RowsInput in;
         in.X = X; in.pieces = p.pieces;
+        const auto ahead = [&](int bytes, int nw) { return rows_read_ahead(Mb, K, V, p.geom, bytes, nw); };
         if (kind == HeadKind::LowRank) {
             if (pos.n > 0) p.down = down_grid_by_position(pos, row0, rows, p.rows_pad, d, r);
             if (const int n = rows_sum_slices(p.down, rows, d, r, V)) {
                 p.down.slices = n;
                 float *slices = reinterpret_cast<float *>(ws + p.off_down_part);
-                e = launch_down_projection_slices(hrow, static_cast<const uint16_t *>(A), slices, p.down, d, r, s);
+                e = launch_down_projection_slices(hrow, static_cast<const uint16_t *>(A), slices, p.down, d, r, ahead(kAheadSlices, 4), s);
                 in.slices = slices; in.nds = n;
             } else if (down_rows_takes(p.down, d, r))
-                e = launch_down_rows(hrow, static_cast<const uint16_t *>(A), X, p.rows_pad, d, r, p.down, s);
+                e = launch_down_rows(hrow, static_cast<const uint16_t *>(A), X, p.rows_pad, d, r, p.down, ahead(kAheadDownRows, 16), s);
             else
                 e = launch_down_projection_pieces(hrow, static_cast<const uint16_t *>(A), reinterpret_cast<float *>(ws + p.off_down_part),
-                                                  p.down, p.rows_pad, d, r, X, s);
+                                                  p.down, p.rows_pad, d, r, X, ahead(kAheadFinish, 4), s);
         } else
             e = launch_regroup_rows(hrow, X, rows, p.rows_pad, d, s);
         if (e != hipSuccess) return fail_hip(e);
