@@ -96,10 +96,11 @@ hipError_t launch_down_projection_slices(const uint16_t *h, const uint16_t *A, f
 hipError_t launch_down_rows(const uint16_t *h, const uint16_t *A, void *X, int rows_pad, int d, int r, const DownGrid &g, const ReadAhead &ahead, hipStream_t st);
 
 // Partials per (row, chunk of 128 G columns) for up to kRowsMaxRows rows, the weights read once (rows_head.hip).
-// X: [pieces][8 ceil(K / 64)][16 ceil(rows / 16)] 16-byte vectors; pieces 1: the bf16 input itself, 3: the pieces of t
+// X: [pieces][8 ceil(K / 64)][16 ceil(rows / 16)] 16-byte vectors; pieces 1: the bf16 input itself, 3: the pieces of t; by_rows (pieces 1): the
+// input as it lies in memory, [rows, K]
 // ... or, for up to kRowsSumRows rows, slices (not null): nds of them, fp32 [nds][rows][K], that every block adds itself
 // smp (null: off), seed: see launch_stream_topk; row0: index in the call of the first row
-struct RowsInput { const void *X = nullptr; int pieces = 1; const float *slices = nullptr; int nds = 0; };
+struct RowsInput { const void *X = nullptr; int pieces = 1; bool by_rows = false; const float *slices = nullptr; int nds = 0; };
 hipError_t launch_rows_topk(const RowsInput &x, const uint16_t *M, float2 *ms, float *pv, int *pi, float4 *smp,
                             int rows, int row0, int K, int V, const RowsGeom &g, int k, uint32_t seed_lo, uint32_t seed_hi, hipStream_t st);
 

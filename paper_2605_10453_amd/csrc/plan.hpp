@@ -490,6 +490,11 @@ inline int rows_sum_slices(const DownGrid &g, int rows, int d, int r, int V) {
     return rows * r * n <= (d <= 4096 ? kRowsSumFloats : kRowsSumFloats / 2) ? n : 0;
 }
 
+// The full head's rows as they lie in memory, or regrouped by a launch of their own.  A load of 16 rows touches 16 lines instead of 8 and every slice of
+// the contraction loads all rows, so what a block reads of them decides.  (Regrouped / as they lie, us a call: 8 rows, d = 512, V = 8192 12.1 / 10.0, 3 rows,
+// d = 1024, V = 60000 30.6 / 28.3, 8 rows, d = 8000, V = 20000 78.1 / 76.0, 20 rows, d = 2048, V = 60000 54.4 / 52.2, 48 rows, d = 1024, V = 20000 29.5 / 28.4;
+// 16 rows, d = 4096, V = 20000 46.3 / 46.7, 48 rows, d = 2048, V = 60000 59.4 / 61.3, 32 rows, d = 8000 87.5 / 92.6, 48 rows, d = 8000, V = 8192 78.8 / 86.9.)
+inline bool rows_read_by_rows(int rows, int d) { return (int64_t)rows * d < 65536; }
 // Contractions this path takes: its row operand and partial tiles then fit beside the lists in a few tens of MB.
 inline bool rows_path_fits(HeadKind kind, int d, int r) { return kind == HeadKind::LowRank ? r <= 2048 : d <= 8192; }
 

@@ -94,7 +94,8 @@ __device__ __forceinline__ float max3_number(float a, float b, float c) { float 
 }  // namespace
 
 // X: [NP][8 ceil(K / 64)][16 NT] 16-byte vectors of 8 consecutive contraction elements of one row: the bf16 input
-//    itself (NP = 1: full head) or the pieces of t (NP = 3); zero beyond K and beyond the last row.
+//    itself (NP = 1: full head) or the pieces of t (NP = 3); zero beyond K and beyond the last row.  by_rows (NP = 1): the bf16 input as it
+//    lies in memory, [rows, K], whose loads touch twice as many lines, against a launch that regroups it (plan.hpp: rows_read_by_rows).
 // M: [K, V] bf16 row-major, V and K multiples of 8
 // Block b: columns [128 G b, 128 G (b + 1)); wavefront w: column group w % G, contraction slice w / G (none from KS on).
 // Partials of (row, chunk): see stream_topk_kernel.  row0: the index in the call of this launch's first row (noise).
@@ -106,7 +107,7 @@ template <int NT, int NP, int GM, bool SUM>
 __global__ __launch_bounds__(512) void rows_topk_kernel(
     const uint4 *__restrict__ X, const float *__restrict__ slices, int nds, const uint16_t *__restrict__ M,
     float2 *__restrict__ part_ms, float *__restrict__ part_val, int *__restrict__ part_id, float4 *__restrict__ part_smp,
-    int rows, int row0, int K, int V, int chunks, int G, int KS, int k, uint32_t seed_lo, uint32_t seed_hi, int meet_at)
+    int rows, int row0, int K, int V, int chunks, int G, int KS, int k, uint32_t seed_lo, uint32_t seed_hi, int meet_at, int by_rows)
 {
     extern __shared__ __align__(16) float z_lds[];               // [16 NT][row_stride]
     constexpr int RP = 16 * NT;
@@ -135,6 +136,13 @@ __global__ __launch_bounds__(512) void rows_topk_kernel(
         const uint16_t *const m_lane = M + min(chunk_col + cg * 128 + 8 * c16, V - 8);
         const uint4 *const x_lane = (SUM ? x_lds : X) + (size_t)kg * RP + c16;
         u32x4 q[2][8], xv[NP][NT];
+        // (NP 1) where the lane's row of each tile begins, in elements, and what lies between 8 elements of a row and the next, and between steps
+        uint32_t x_row[NT];
+        const uint32_t x_kg = by_rows ? 8u : 8u * RP, x_step = 4u * x_kg;
+        if constexpr (NP == 1) {
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) x_row[nt] = by_rows ? (uint32_t)min(16 * nt + c16, rows - 1) * (uint32_t)K : 8u * (uint32_t)(16 * nt + c16);
+        }
         const auto load_m = [&](u32x4 (&dst)[8], int s) {
             // K is a multiple of 8: a lane's 8 rows exist or none do (then rows of the step that do are read, and dropped)
             const int k0 = 32 * s + ((32 * s + 8 * kg < K) ? 8 * kg : 0);
@@ -143,11 +151,18 @@ __global__ __launch_bounds__(512) void rows_topk_kernel(
             for (int u = 0; u < 8; ++u) dst[u] = *reinterpret_cast<const u32x4 *>(p + (size_t)u * V);
         };
         const auto load_x = [&](int s) {
+            if constexpr (NP == 1) {
+                const uint32_t at = (uint32_t)s * x_step + ((32 * s + 8 * kg < K) ? (uint32_t)kg * x_kg : 0u);
+                const uint16_t *h = reinterpret_cast<const uint16_t *>(X) + at;
 #pragma unroll
-            for (int p = 0; p < NP; ++p)
+                for (int nt = 0; nt < NT; ++nt) xv[0][nt] = *reinterpret_cast<const u32x4 *>(h + x_row[nt]);
+            } else {
 #pragma unroll
-                for (int nt = 0; nt < NT; ++nt)
-                    xv[p][nt] = *reinterpret_cast<const u32x4 *>(x_lane + p * x_piece + (size_t)(4 * s) * RP + 16 * nt);
+                for (int p = 0; p < NP; ++p)
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt)
+                        xv[p][nt] = *reinterpret_cast<const u32x4 *>(x_lane + p * x_piece + (size_t)(4 * s) * RP + 16 * nt);
+            }
         };
         if constexpr (SUM) {
             static_assert(NT == 1 && NP == 3, "a few rows of t");
@@ -200,6 +215,12 @@ __global__ __launch_bounds__(512) void rows_topk_kernel(
                 for (int u = 0; u < 8; ++u)
 #pragma unroll
                     for (int e = 0; e < 4; ++e) w[u][e] &= keep;
+                if constexpr (NP == 1) {                         // (an infinity there must not meet the cleared weights)
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) xv[0][nt][e] &= keep;
+                }
             }
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
@@ -606,7 +627,7 @@ static hipError_t launch_rows(const RowsInput &x, const uint16_t *M, float2 *ms,
     hipError_t e = lds_limit.raise(reinterpret_cast<const void *>(rows_topk_kernel<NT, NP, GM, SUM>), (int)lds);
     if (e != hipSuccess) return e;
     rows_topk_kernel<NT, NP, GM, SUM><<<g.chunks, 64 * g.waves, lds, st>>>(static_cast<const uint4 *>(x.X), x.slices, x.nds, M, ms, pv, pi, smp,
-                                                                           rows, row0, K, V, g.chunks, g.G, g.KS, k, seed_lo, seed_hi, meet_at);
+                                                                           rows, row0, K, V, g.chunks, g.G, g.KS, k, seed_lo, seed_hi, meet_at, x.by_rows ? 1 : 0);
     return hipGetLastError();
 }
 

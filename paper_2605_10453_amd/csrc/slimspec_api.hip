@@ -235,9 +235,11 @@ int run_head_rows(HeadKind kind, const void *h, const void *A, const void *M, co
             else
                 e = launch_down_projection_pieces(hrow, static_cast<const uint16_t *>(A), reinterpret_cast<float *>(ws + p.off_down_part),
                                                   p.down, p.rows_pad, d, r, X, ahead(kAheadFinish, 4), s);
-        } else
-            e = launch_regroup_rows(hrow, X, rows, p.rows_pad, d, s);
-        if (e != hipSuccess) return fail_hip(e);
+            if (e != hipSuccess) return fail_hip(e);
+        } else if (rows_read_by_rows(rows, d)) {
+            in.X = hrow; in.by_rows = true;
+        } else if ((e = launch_regroup_rows(hrow, X, rows, p.rows_pad, d, s)) != hipSuccess)
+            return fail_hip(e);
         float2 *ms = reinterpret_cast<float2 *>(ws + p.off_part_ms);
         float *pv = reinterpret_cast<float *>(ws + p.off_part_val);
         int *pi = reinterpret_cast<int *>(ws + p.off_part_id);

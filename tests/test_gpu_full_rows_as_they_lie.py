@@ -1,0 +1,44 @@
+"""The full head's rows as rows_topk_kernel reads them (csrc/plan.hpp: rows_read_by_rows) against the CPU fp64 checker: on both sides of the line, row counts
+around the 16-row tiles, hidden sizes that end inside a step of 32, and an infinite element in the last eight."""
+import numpy as np
+import pytest
+
+from paper_2605_10453_amd import synth
+from parity_util import compare_with_oracle, to_dev_bf16
+from plan_util import assert_plan
+from test_gpu_parity import gpu  # noqa: F401  (the module's fixture)
+from test_gpu_rows_head import FP32_TOL
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("rows,d,V", [(2, 264, 136), (3, 72, 8200), (8, 8184, 1000), (9, 8184, 1000), (15, 4368, 2056), (16, 4088, 2056), (16, 4096, 2056),
+                                      (17, 1032, 33000), (32, 2040, 1000), (33, 2040, 1000), (48, 1360, 2056), (48, 1368, 2056)])
+def test_both_sides_of_the_line(gpu, oracle_mod, rows, d, V):
+    torch, b = gpu
+    k = 17                                                       # (a list that every row count sends to this kernel)
+    assert_plan("full", rows, d, 8, V, k, kernel="rows")
+    print(f"full head, rows as they lie: rows={rows} d={d} V={V}", flush=True)
+    x = synth.make_inputs(synth.small_config(rows, d, 8, V, k, peaked_every=4), seed=rows + d, with_full_head=True)
+    ids, lp = b.full_head_topk(to_dev_bf16(x.h), to_dev_bf16(x.W), k)
+    torch.cuda.synchronize()
+    ora = oracle_mod.full_head_topk(x.h, x.W, k)
+    z_at = lambda ri, ci: oracle_mod.full_logits_at(x.h, x.W, ri, ci)
+    compare_with_oracle(ids.cpu().numpy(), lp.cpu().numpy(), ora.ids, ora.lse, z_at, V, tie_tol=FP32_TOL, lp_tol=FP32_TOL)
+
+
+@pytest.mark.parametrize("rows,d", [(3, 40), (18, 72)])
+def test_an_infinite_element_stays_in_its_row(gpu, oracle_mod, rows, d):
+    """h[1] = +inf in its last element: every other row is as before."""
+    torch, b = gpu
+    V, k = 1000, 5
+    x = synth.make_inputs(synth.small_config(rows, d, 8, V, k), seed=d, with_full_head=True)
+    h = x.h.copy()
+    h[1, d - 1] = 0x7f80
+    W = to_dev_bf16(x.W)
+    ids0, lp0 = b.full_head_topk(to_dev_bf16(x.h), W, k)
+    ids1, lp1 = b.full_head_topk(to_dev_bf16(h), W, k)
+    torch.cuda.synchronize()
+    others = np.arange(rows) != 1
+    assert np.array_equal(ids0.cpu().numpy()[others], ids1.cpu().numpy()[others])
+    assert np.array_equal(lp0.cpu().numpy()[others], lp1.cpu().numpy()[others])
