@@ -313,7 +313,7 @@ __global__ __launch_bounds__(512) void rows_topk_kernel(
                 }
             }
     };
-    if (meet_at > 0) {
+    if (NT == 1 && meet_at > 0) {                                // (no more than 16 rows)
         const int stride = rows_meet_stride(G), region = rows * stride;
         float *const others = z_lds + meet_at;                   // [KS - 1][rows][stride]; slice 0's are where the logits go
         if (ks < KS) put_sums(ks == 0 ? z_lds : others + (ks - 1) * region, ks == 0 ? row_stride : stride);
@@ -622,7 +622,7 @@ static hipError_t launch_rows(const RowsInput &x, const uint16_t *M, float2 *ms,
     size_t lds = rows_x_offset(NT, g.G, g.waves, k) + (SUM ? sizeof(uint4) * 3 * 16 * (size_t)((K + 63) / 64 * 8) : 0);
     int meet_at = 0;                     // floats before the slices' sums, 0: not so
     const size_t meet = sizeof(float) * (size_t)(g.KS - 1) * rows * rows_meet_stride(g.G);
-    if (rows_meet_at_once(g.KS, rows) && lds + meet <= kRowsLdsLimit) { meet_at = (int)(lds / sizeof(float)); lds += meet; }
+    if (NT == 1 && rows_meet_at_once(g.KS, rows) && lds + meet <= kRowsLdsLimit) { meet_at = (int)(lds / sizeof(float)); lds += meet; }
     static LdsLimit lds_limit;
     hipError_t e = lds_limit.raise(reinterpret_cast<const void *>(rows_topk_kernel<NT, NP, GM, SUM>), (int)lds);
     if (e != hipSuccess) return e;
