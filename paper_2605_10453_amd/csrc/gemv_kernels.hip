@@ -38,8 +38,8 @@ __global__ __launch_bounds__(256) void widen_rows_kernel(
 // One block per chunk of 8 * lanes adjacent columns of the vocabulary.  M is the [K, V] weight matrix (bf16 or fp32).
 // A lane owns 8 adjacent columns; a wavefront's 64 lanes are 64 / lanes (`k_parts`) rows of M at a time, so a narrow
 // chunk fills the wavefront as well, and the NW k_parts lane groups of a block split the contraction into ranges of
-// `per` rows (a multiple of 8).  Their partial sums meet in shared memory in a fixed order, and wavefront i % NW (a single row: the block,
-// block_row_epilogue) reduces row i of the chunk to (max, sum of exp, top-k) and writes the partial.
+// `per` rows (a multiple of 8).  Their partial sums meet in shared memory in a fixed order, and wavefront i % NW (a single row in a wide chunk: the
+// block, block_row_epilogue) reduces row i of the chunk to (max, sum of exp, top-k) and writes the partial.
 //
 // What bounds it: the weights' way from HBM, as long as every CU has a block and asks for enough of them (plan.hpp chooses
 // the chunks for that); with small weights the chain of trips before and after: the contraction input (for one or two
@@ -145,6 +145,7 @@ __global__ __launch_bounds__(NW * 64) void stream_topk_kernel(
     BlockRowPlan row_plan;
     const auto plan_row = [&]() {                               // (behind the first loads)
         if constexpr (R == 1) {
+            if (!block_row_takes(cw, k)) return;
             row_plan = make_block_row_plan(cw, chunk_col, V, k);
             if (tid < kBoundGroups && tid >= row_plan.bound.n_groups) one_row.groups[tid] = 0u;
         }
@@ -317,8 +318,8 @@ __global__ __launch_bounds__(NW * 64) void stream_topk_kernel(
         }
     }
     __syncthreads();
-    if constexpr (R == 1) {
-        block_row_epilogue<NW>(one_row, row_plan, red, red2, n_parts, cw, chunk_col, tid, k, (size_t)row0 * chunks + chunk, part_ms, part_val, part_id, part_smp,
+    if (R == 1 && block_row_takes(cw, k)) {
+        if constexpr (R == 1) block_row_epilogue<NW>(one_row, row_plan, red, red2, n_parts, cw, chunk_col, tid, k, (size_t)row0 * chunks + chunk, part_ms, part_val, part_id, part_smp,
                                gumbel_key(seed_lo, seed_hi, (uint32_t)row0));
         return;
     }
