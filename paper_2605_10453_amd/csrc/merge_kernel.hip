@@ -25,7 +25,7 @@
 //       Wavefront 1 meanwhile finds the draw of a sampling call, wavefront 2 folds the log-sum-exp.
 //   (2) all threads: the lists' entries that reach T go to shared memory.  Where a row has few entries they were
 //       requested at the start, before T is known (one trip instead of two); otherwise the first eight of the lists whose
-//       heads reach T are read, and more of a list only where all eight are taken.
+//       heads reach T are read, and more of a list only where all eight are taken.  (plan.hpp: merge_kind, which code a call takes)
 //   (3) the k first of them are found by counting, or, where they are many, by wavefront 0.
 #include "gemv_parts.hpp"
 #include "launch.hpp"
@@ -34,10 +34,7 @@ namespace slimspec {
 
 namespace {
 
-constexpr int kRowMergeThreads = 512;
 constexpr int kMergeHeads = 8;                                   // heads per lane in flight
-constexpr int kMergeAhead = 8;                                   // entries per thread that are requested before T is known
-constexpr int kMergeShort = 16;                                  // ids of a short list at most
 constexpr int kMergeWaves = kRowMergeThreads / 64;
 constexpr int kMergeMine = 64;                                   // entries of a wavefront's list at most
 constexpr int kMergeLists = SLIMSPEC_KMAX_INTERNAL + kCandSlack; // lists that may hold winners, at most
@@ -78,7 +75,7 @@ __device__ __forceinline__ void wave_rank_keys(const uint64_t *keys, int n, int 
 
 __global__ __launch_bounds__(kRowMergeThreads) void merge_kernel(
     const float2 *__restrict__ part_ms, const float *__restrict__ part_val, const int *__restrict__ part_id,
-    int chunks, int k, int last_len, int j_th, int m_th, int32_t *__restrict__ out_ids, float *__restrict__ out_logprobs,
+    int chunks, int k, int last_len, int j_th, int m_th, MergeKind kind, int32_t *__restrict__ out_ids, float *__restrict__ out_logprobs,
     const int32_t *__restrict__ id_map, SampleOut so, const float4 *__restrict__ part_smp)
 {
     __shared__ MergeLds S;
@@ -91,8 +88,7 @@ __global__ __launch_bounds__(kRowMergeThreads) void merge_kernel(
 
     // Entries of the last chunk's list from last_len on are filler (it may have fewer than k columns; the others have k).
     const int n_entries = (chunks - 1) * k + last_len;
-    const bool ahead = n_entries <= kMergeAhead * NT;
-    const bool few = ahead && k <= kMergeShort && chunks <= NT;
+    const bool few = kind == kMergeShortLists, ahead = kind != kMergeLongLists;
     float2 hm[H];
     if (few) hm[0] = ms[min(tid, chunks - 1)];
     else if (wave == 0 || wave == 2) {
@@ -425,13 +421,13 @@ hipError_t launch_merge(const float2 *part_ms, const float *part_val, const int 
                         int rows, int chunks, int chunk_cols, int V, int k, int32_t *out_ids, float *out_logprobs, const int32_t *id_map,
                         const SampleOut &so, const float4 *part_smp, hipStream_t st)
 {
-    const int last_cols = V - (chunks - 1) * chunk_cols, last_len = last_cols < k ? last_cols : k;
+    const int last_len = merge_last_len(chunks, chunk_cols, V, k);
     // (j one more than it takes: m then leaves out the lists whose j-th entries are the smallest.  Not where (3) ranks all entries anyway.  Worked
     // out here: two divisions and a sort of its own in the kernel cost every call up to 0.5 us)
     int j_th = 1;
     if (chunks < k && (chunks - 1) * k + last_len > kMergeSel) j_th = (k + chunks - 1) / chunks + 1 < k ? (k + chunks - 1) / chunks + 1 : k;
-    merge_kernel<<<rows, kRowMergeThreads, 0, st>>>(part_ms, part_val, part_id, chunks, k, last_len, j_th, (k + j_th - 1) / j_th, out_ids, out_logprobs,
-                                                    id_map, so, so.on ? part_smp : nullptr);
+    merge_kernel<<<rows, kRowMergeThreads, 0, st>>>(part_ms, part_val, part_id, chunks, k, last_len, j_th, (k + j_th - 1) / j_th, merge_kind(chunks, last_len, k),
+                                                    out_ids, out_logprobs, id_map, so, so.on ? part_smp : nullptr);
     return hipGetLastError();
 }
 

@@ -535,6 +535,27 @@ inline RowsPlan make_rows_plan(HeadKind kind, int rows, int d, int r, int V, int
     return p;
 }
 
+// ---- merge of the chunk lists (merge_kernel.hip) -------------------------------------------------------------------
+// Short lists (up to 16 ids) take code of their own as long as the block's threads hold all entries, eight each, and a chunk each.  Long ones
+// are requested before the bound is known up to five entries per thread: with more, fetching what the bound leaves out takes longer than the second
+// trip to memory (d = 1024, r = 128, us a call, requested / not: 4 rows, V = 20480, k = 24 13.9 / 13.5, V = 8192, k = 48 15.9 / 15.3, 40 rows, V = 16384,
+// k = 30 24.4 / 23.6, one row, V = 20480, k = 24 12.0 / 11.5).
+constexpr int kRowMergeThreads = 512;
+constexpr int kMergeShort = 16;          // ids of a short list at most
+constexpr int kMergeAhead = 8;           // entries per thread of short lists
+constexpr int kMergeAheadLong = 5;       // ... of long ones
+enum MergeKind : int { kMergeLongLists, kMergeLongListsAhead, kMergeShortLists };
+// ids in the last chunk's list (the others have k)
+inline int merge_last_len(int chunks, int chunk_cols, int V, int k) {
+    const int last_cols = V - (chunks - 1) * chunk_cols;
+    return last_cols < k ? last_cols : k;
+}
+inline MergeKind merge_kind(int chunks, int last_len, int k) {
+    const int n_entries = (chunks - 1) * k + last_len;
+    if (k <= kMergeShort && chunks <= kRowMergeThreads && n_entries <= kMergeAhead * kRowMergeThreads) return kMergeShortLists;
+    return n_entries <= kMergeAheadLong * kRowMergeThreads ? kMergeLongListsAhead : kMergeLongLists;
+}
+
 // ---- which kernels a call runs ------------------------------------------------------------------------------------
 constexpr int kMfmaMaxK = 16;            // the lane streams keep 3 groups: enough for k <= 16 (larger k: rows_head.hip)
 constexpr int64_t kRowsMinWeights = 12 << 20;
