@@ -7,7 +7,7 @@
 // What bounds it: the length of its chain of instructions.  There is hardly any work and one trip to memory (0.4 us; a second pass over the same lists
 // took 3.6 us of the first one's 3.9), but a lone wavefront takes 5 to 14 cycles per dependent instruction (device_utils.hpp).
 //
-// Lists of up to 16 ids whose entries a block's threads can hold (`few`, the usual call): every thread keeps up to eight entries and one chunk's (m, s).
+// Lists of up to 16 ids (10 in a launch of more than 24 rows) whose entries a block's threads can hold (`few`, the usual call; plan.hpp: merge_kind): every thread keeps up to eight entries and one chunk's (m, s).
 //   (1) T: the smallest of the maxima of k groups of entries (device_utils.hpp), so k entries reach it; two or three times as many do, where a sort
 //       would leave hardly more than k, but they are ranked by all threads and the sort is a chain of 21 exchanges.  M = max m_c in the same steps.
 //   (2) every wavefront puts its entries that reach T into a list of its own in shared memory (additions to a common counter take 250 cycles), and
@@ -25,7 +25,7 @@
 //       Wavefront 1 meanwhile finds the draw of a sampling call, wavefront 2 folds the log-sum-exp.
 //   (2) all threads: the lists' entries that reach T go to shared memory.  Where a row has few entries they were
 //       requested at the start, before T is known (one trip instead of two); otherwise the first eight of the lists whose
-//       heads reach T are read, and more of a list only where all eight are taken.  (plan.hpp: merge_kind, which code a call takes)
+//       heads reach T are read, and more of a list only where all eight are taken.
 //   (3) the k first of them are found by counting, or, where they are many, by wavefront 0.
 #include "gemv_parts.hpp"
 #include "launch.hpp"
@@ -426,7 +426,7 @@ hipError_t launch_merge(const float2 *part_ms, const float *part_val, const int 
     // out here: two divisions and a sort of its own in the kernel cost every call up to 0.5 us)
     int j_th = 1;
     if (chunks < k && (chunks - 1) * k + last_len > kMergeSel) j_th = (k + chunks - 1) / chunks + 1 < k ? (k + chunks - 1) / chunks + 1 : k;
-    merge_kernel<<<rows, kRowMergeThreads, 0, st>>>(part_ms, part_val, part_id, chunks, k, last_len, j_th, (k + j_th - 1) / j_th, merge_kind(chunks, last_len, k),
+    merge_kernel<<<rows, kRowMergeThreads, 0, st>>>(part_ms, part_val, part_id, chunks, k, last_len, j_th, (k + j_th - 1) / j_th, merge_kind(rows, chunks, last_len, k),
                                                     out_ids, out_logprobs, id_map, so, so.on ? part_smp : nullptr);
     return hipGetLastError();
 }

@@ -23,7 +23,7 @@ int main()
         const ChunkGeom g = make_chunk_geom(kind, rows, low_rank ? r : d, V);
         const RowsGeom rg = make_rows_geom(low_rank ? r : d, V);
         const int chunks = rows_path ? rg.chunks : g.chunks, chunk_cols = rows_path ? 128 * rg.G : 8 * g.lanes;
-        const MergeKind merge = merge_kind(chunks, merge_last_len(chunks, chunk_cols, V, k), k);
+        const MergeKind merge = merge_kind(rows_path && rows > kRowsMaxRows ? kRowsMaxRows : rows, chunks, merge_last_len(chunks, chunk_cols, V, k), k);
         const int gw = resident ? p.res.gw : p.gw, nsr = resident ? p.res.nsr : p.nsr;
         std::printf("kernel=%s resident_fits=%d f16=%d rows_per_block=%d col_blocks=%d records=%d parks=%d parked_offset=%zu parked_row_bytes=%zu chunk_cols=%d rows_in_lds=%d own_input=%d sum_slices=%d merge=%s\n", kernel, p.resident ? 1 : 0,
                     f16 ? 1 : 0, p.rt, gw, nsr / gw, p.defer && merge_parks_rows(low_rank ? r : d, !low_rank || f16) && !prepared && !sampling ? 1 : 0,

@@ -2,7 +2,9 @@
 import pytest
 
 from paper_2605_10453_amd import synth
+from parity_util import to_dev_bf16
 from plan_util import assert_plan
+from test_gpu_heads_next import check_sample_outputs
 from test_gpu_merge import check
 from test_gpu_parity import gpu  # noqa: F401  (the module's fixture)
 
@@ -16,3 +18,22 @@ def test_entries_requested_ahead(gpu, oracle_mod, rows, V, k, merge):
     assert_plan("low", rows, 64, 16, V, k, merge=merge)
     print(f"merge lists: rows={rows} V={V} k={k} {merge}", flush=True)
     check(gpu, oracle_mod, synth.make_inputs(synth.small_config(rows, 64, 16, V, k, peaked_every=3), seed=V + k), k)
+
+
+# short lists: up to 16 ids of up to 24 rows, up to 10 of more
+@pytest.mark.parametrize("rows,V,k,merge", [(24, 8632, 16, "short"), (25, 8632, 10, "short"), (25, 8632, 11, "long_ahead"), (25, 41000, 16, "long"), (48, 8632, 10, "short"),
+                                            (48, 8632, 11, "long_ahead"), (33, 128256, 13, "long"), (24, 66000, 14, "short")])
+def test_short_lists_by_rows(gpu, oracle_mod, rows, V, k, merge):
+    assert_plan("low", rows, 64, 16, V, k, merge=merge)
+    print(f"merge lists: rows={rows} V={V} k={k} {merge}", flush=True)
+    check(gpu, oracle_mod, synth.make_inputs(synth.small_config(rows, 64, 16, V, k, peaked_every=3), seed=V + k), k)
+
+
+def test_draws_of_many_rows_with_more_than_ten_ids(gpu, oracle_mod):
+    torch, b = gpu
+    rows, V, k = 25, 8632, 12
+    x = synth.make_inputs(synth.small_config(rows, 64, 16, V, k), seed=V)
+    out = b.slimspec_head_sample(to_dev_bf16(x.h), to_dev_bf16(x.A), to_dev_bf16(x.B), k, 1234)
+    torch.cuda.synchronize()
+    ora = oracle_mod.head_sample(x.h, x.A, x.B, k, 1234, return_logits=True)
+    check_sample_outputs(torch, out, ora, 1234, V, ora.z, oracle_mod)
