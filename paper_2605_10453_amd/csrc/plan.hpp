@@ -537,16 +537,17 @@ inline RowsPlan make_rows_plan(HeadKind kind, int rows, int d, int r, int V, int
 
 // ---- merge of the chunk lists (merge_kernel.hip) -------------------------------------------------------------------
 // Short lists take code of their own as long as the block's threads hold all entries, eight each, and a chunk each: up to 16 ids, and up to 10 in a launch
-// of more than 24 rows.  The bound it works with is the smallest maximum of k classes, which now and then admits many more than k entries, the more the
-// larger k; the slowest row decides how long the launch takes, and of many rows one is such a row.  (The other code / this one, us a call, mean over five
-// inputs, d = 512, r = 64: V = 8632 42 rows k = 10 17.2 / 17.3, k = 11 17.6 / 19.1, k = 13 18.2 / 18.4, 32 rows k = 11 15.0 / 15.4, k = 13 15.5 / 15.9, 24 rows k = 11 14.3 / 14.0,
-// 12 rows 12.6 / 12.3; V = 16384, k = 13 42 rows 18.1 / 18.9, 24 rows 14.6 / 15.2; V = 33000 24 rows k = 11 16.0 / 15.7, k = 16 16.5 / 16.3, 12 rows 14.2 / 13.6 and 14.8 / 14.3;
-// V = 128256, k = 11 42 rows 22.9 / 22.2, 24 rows 18.9 / 18.6.)  Long ones
+// of more than 24 rows with up to 128 lists each.  The bound it works with is the smallest maximum of k classes.  A class of few lists has few heads, and
+// now and then the bound admits many more than k entries, the more the larger k; the slowest row decides how long the launch takes, and of many rows
+// one is such a row.  (The other code / this one, mean over five to eight inputs: d = 512, r = 64, V = 8632, us a call 42 rows k = 10 17.2 / 17.3, k = 11 17.6 / 19.1,
+// k = 13 18.2 / 18.4, 32 rows k = 11 15.0 / 15.4, k = 13 15.5 / 15.9, 24 rows k = 11 14.3 / 14.0, 12 rows 12.6 / 12.3; V = 16384, 42 rows, k = 13 18.1 / 18.9.  k = 11 to 16 of 28 to
+// 48 rows: 64 lists 0.92 to 0.99 of its time, 100 lists 0.97 to 1.00, 130 to 250 lists 0.97 to 1.03, among them the full head, 32 rows, d = 992, V = 52064, k = 12 32.0 / 31.7.)  Long ones
 // are requested before the bound is known up to five entries per thread: with more, fetching what the bound leaves out takes longer than the second
 // trip to memory (d = 1024, r = 128, us a call, requested / not: 4 rows, V = 20480, k = 24 13.9 / 13.5, V = 8192, k = 48 15.9 / 15.3, 40 rows, V = 16384,
 // k = 30 24.4 / 23.6, one row, V = 20480, k = 24 12.0 / 11.5).
 constexpr int kRowMergeThreads = 512;
-constexpr int kMergeShort = 16, kMergeShortManyRows = 10, kMergeFewRows = 24;     // ids of a short list at most, and in a launch of more rows than a few
+constexpr int kMergeShort = 16, kMergeShortFewLists = 10;      // ids of a short list at most, and of ...
+constexpr int kMergeFewRows = 24, kMergeFewLists = 128;  // ... a launch of more rows than these with up to these lists each
 constexpr int kMergeAhead = 8;           // entries per thread of short lists
 constexpr int kMergeAheadLong = 5;       // ... of long ones
 enum MergeKind : int { kMergeLongLists, kMergeLongListsAhead, kMergeShortLists };
@@ -557,7 +558,7 @@ inline int merge_last_len(int chunks, int chunk_cols, int V, int k) {
 }
 inline MergeKind merge_kind(int rows, int chunks, int last_len, int k) {
     const int n_entries = (chunks - 1) * k + last_len;
-    if (k <= (rows <= kMergeFewRows ? kMergeShort : kMergeShortManyRows) && chunks <= kRowMergeThreads && n_entries <= kMergeAhead * kRowMergeThreads) return kMergeShortLists;
+    if (k <= (rows > kMergeFewRows && chunks <= kMergeFewLists ? kMergeShortFewLists : kMergeShort) && chunks <= kRowMergeThreads && n_entries <= kMergeAhead * kRowMergeThreads) return kMergeShortLists;
     return n_entries <= kMergeAheadLong * kRowMergeThreads ? kMergeLongListsAhead : kMergeLongLists;
 }
 

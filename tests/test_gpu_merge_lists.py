@@ -20,9 +20,9 @@ def test_entries_requested_ahead(gpu, oracle_mod, rows, V, k, merge):
     check(gpu, oracle_mod, synth.make_inputs(synth.small_config(rows, 64, 16, V, k, peaked_every=3), seed=V + k), k)
 
 
-# short lists: up to 16 ids of up to 24 rows, up to 10 of more
-@pytest.mark.parametrize("rows,V,k,merge", [(24, 8632, 16, "short"), (25, 8632, 10, "short"), (25, 8632, 11, "long_ahead"), (25, 41000, 16, "long"), (48, 8632, 10, "short"),
-                                            (48, 8632, 11, "long_ahead"), (33, 128256, 13, "long"), (24, 66000, 14, "short")])
+# short lists: up to 16 ids, up to 10 of more than 24 rows with up to 128 lists each
+@pytest.mark.parametrize("rows,V,k,merge", [(24, 8632, 16, "short"), (25, 8632, 10, "short"), (25, 8632, 11, "long_ahead"), (25, 16384, 16, "long_ahead"), (25, 16392, 16, "short"), (48, 8632, 10, "short"),
+                                            (48, 8632, 11, "long_ahead"), (33, 128256, 13, "short"), (48, 12000, 14, "long_ahead")])
 def test_short_lists_by_rows(gpu, oracle_mod, rows, V, k, merge):
     assert_plan("low", rows, 64, 16, V, k, merge=merge)
     print(f"merge lists: rows={rows} V={V} k={k} {merge}", flush=True)

@@ -116,10 +116,12 @@ def test_entries_are_requested_ahead_only_where_that_is_faster(rows, V, k, merge
     assert plan_of("low", rows, 1024, 128, V, k)["merge"] == merge
 
 
-@pytest.mark.parametrize("rows,k,merge", [(1, 16, "short"), (24, 16, "short"), (25, 10, "short"), (25, 11, "long_ahead"), (48, 10, "short"), (48, 11, "long_ahead"), (32, 16, "long_ahead")])
-def test_short_lists_of_many_rows_have_at_most_ten_ids(rows, k, merge):
-    """The slowest of a launch's rows decides, and with many ids the short lists' bound now and then admits far too many entries: 42 rows, k = 11 8 % slower."""
-    assert plan_of("low", rows, 1024, 128, 8632, k)["merge"] == merge
+@pytest.mark.parametrize("rows,V,k,merge", [(1, 8632, 16, "short"), (24, 8632, 16, "short"), (25, 8632, 10, "short"), (25, 8632, 11, "long_ahead"), (48, 8632, 10, "short"),
+                                            (48, 8632, 11, "long_ahead"), (32, 16384, 16, "long_ahead"), (32, 16392, 16, "short"), (48, 128256, 16, "short")])
+def test_many_rows_of_few_short_lists_have_at_most_ten_ids(rows, V, k, merge):
+    """The slowest of a launch's rows decides, and with many ids in few lists the short lists' bound now and then admits far too many entries: 42 rows, k = 11,
+    V = 8632 8 % slower."""
+    assert plan_of("low", rows, 1024, 128, V, k)["merge"] == merge
 
 
 def test_bench_names_the_kernel_the_library_runs():
