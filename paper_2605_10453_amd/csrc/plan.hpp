@@ -495,11 +495,25 @@ inline int rows_sum_slices(const DownGrid &g, int rows, int d, int r, int V) {
     return rows * r * n <= (d <= 4096 ? kRowsSumFloats : kRowsSumFloats / 2) ? n : 0;
 }
 
-// The full head's rows as they lie in memory, or regrouped by a launch of their own.  A load of 16 rows touches 16 lines instead of 8 and every slice of
-// the contraction loads all rows, so what a block reads of them decides.  (Regrouped / as they lie, us a call: 8 rows, d = 512, V = 8192 12.1 / 10.0, 3 rows,
-// d = 1024, V = 60000 30.6 / 28.3, 8 rows, d = 8000, V = 20000 78.1 / 76.0, 20 rows, d = 2048, V = 60000 54.4 / 52.2, 48 rows, d = 1024, V = 20000 29.5 / 28.4;
-// 16 rows, d = 4096, V = 20000 46.3 / 46.7, 48 rows, d = 2048, V = 60000 59.4 / 61.3, 32 rows, d = 8000 87.5 / 92.6, 48 rows, d = 8000, V = 8192 78.8 / 86.9.)
-inline bool rows_read_by_rows(int rows, int d) { return (int64_t)rows * d < 65536; }
+// The full head's rows as they lie in memory, or regrouped by a launch of their own (2 to 4 us).  A load of 16 rows touches 16 lines instead of 8, which are
+// half used: a block waits longer for its rows, the more the more elements they have.  Nobody sees that where a block has one group of columns, or where
+// the weights' way from HBM is the bound (four groups in a round that fills the chip).  It costs most where one wavefront takes a whole contraction
+// (five and six groups) and V is no multiple of 64, so that the weights' loads touch more lines as well.  (Regrouped / as they lie, us a call, k = 10: 8 rows,
+// d = 512, V = 8192 14.7 / 12.0, d = 8184, V = 50000 158.0 / 156.2; one group: 48 rows, d = 1360, V = 32000 32.5 / 31.5; four that fill: 48 rows, d = 1360, V = 120000
+// 71.6 / 71.1; five, V = 151752: 32 rows, d = 1080 74.3 / 78.9, 24 rows, d = 2216, V = 131704 119.7 / 126.1; 16 rows, d = 4088, V = 50000 84.5 / 87.8; two: 32 rows, d = 1800, V = 50000
+// 48.1 / 50.7, 40 rows, d = 1024, V = 41000 31.5 / 30.1; 40 rows, d = 1024, V = 151936 68.8 / 67.1, 48 rows, d = 1360 87.0 / 90.0; others: 33 rows, d = 1024, V = 80000 45.2 / 44.0,
+// 48 rows, d = 1024, V = 100000 54.5 / 56.7, d = 1360, V = 140000 85.0 / 94.3.  Of 3467 calls of 2 to 48 rows, d = 272 to 8176, V = 8192 to 190016, these lines leave 13 more than
+// 0.5 % slower than regrouped, one more than 1 % (1.8 %), the mean 5.4 % faster; rows * d < 65536 alone left 202, up to 10 %.)
+constexpr int kFillingChunks = 232;      // blocks from which on the chip counts as full
+inline bool rows_read_by_rows(int rows, int d, int V, const RowsGeom &g) {
+    const bool fills = g.chunks >= kFillingChunks;
+    const int most = rows <= 8 || g.G == 1 || (g.G == 4 && fills) ? 65536
+                   : g.G > 4 && V % 64 != 0 ? 20000
+                   : rows <= 24 ? 60000
+                   : g.G == 2 ? (fills ? 58000 : 50000)
+                   : fills ? 50000 : 36000;
+    return (int64_t)rows * d < most;
+}
 // Contractions this path takes: its row operand and partial tiles then fit beside the lists in a few tens of MB.
 inline bool rows_path_fits(HeadKind kind, int d, int r) { return kind == HeadKind::LowRank ? r <= 2048 : d <= 8192; }
 

@@ -236,7 +236,7 @@ int run_head_rows(HeadKind kind, const void *h, const void *A, const void *M, co
                 e = launch_down_projection_pieces(hrow, static_cast<const uint16_t *>(A), reinterpret_cast<float *>(ws + p.off_down_part),
                                                   p.down, p.rows_pad, d, r, X, ahead(kAheadFinish, 4), s);
             if (e != hipSuccess) return fail_hip(e);
-        } else if (rows_read_by_rows(rows, d)) {
+        } else if (rows_read_by_rows(rows, d, V, p.geom)) {
             in.X = hrow; in.by_rows = true;
         } else if ((e = launch_regroup_rows(hrow, X, rows, p.rows_pad, d, s)) != hipSuccess)
             return fail_hip(e);

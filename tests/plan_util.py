@@ -24,7 +24,7 @@ def plan_of(kind: str, rows: int, d: int, r: int, V: int, k: int, fp32=False, pr
     col_blocks, records (per row and column block), parks (rows that wait for their exact columns), parked_offset and
     parked_row_bytes (where in the workspace a row does, its number of columns first); resident_fits; for stream, chunk_cols,
     rows_in_lds (whether a launch's row input fits shared memory) and own_input (the kernel makes t itself);
-    for rows, sum_slices (slices of t that its blocks add, 0: none); for stream and rows, merge (how merge_kernel takes the chunks' lists: short,
+    for rows, sum_slices (slices of t that its blocks add, 0: none) and rows_as_they_lie (the full head's rows are read without a launch that regroups them); for stream and rows, merge (how merge_kernel takes the chunks' lists: short,
     long_ahead or long)."""
     line = f"{kind} {rows} {d} {r} {V} {k} {int(fp32)} {int(prepared)} {int(sampling)}\n"
     out = subprocess.run([_probe()], input=line, capture_output=True, text=True, check=True).stdout

@@ -27,6 +27,22 @@ def test_both_sides_of_the_line(gpu, oracle_mod, rows, d, V):
     compare_with_oracle(ids.cpu().numpy(), lp.cpu().numpy(), ora.ids, ora.lse, z_at, V, tie_tol=FP32_TOL, lp_tol=FP32_TOL)
 
 
+# blocks of two, three, four and six groups of columns, on either side of what they take
+@pytest.mark.parametrize("rows,d,V,by_rows", [(48, 1040, 33000, 1), (48, 1048, 33000, 0), (48, 744, 66000, 1), (48, 752, 66000, 0), (25, 2400, 100000, 0), (48, 1360, 120000, 1),
+                                              (33, 1512, 190016, 1), (20, 3000, 33000, 0), (17, 1168, 132008, 1), (17, 1184, 132008, 0)])
+def test_blocks_of_several_groups(gpu, oracle_mod, rows, d, V, by_rows):
+    torch, b = gpu
+    k = 17
+    assert_plan("full", rows, d, 8, V, k, kernel="rows", rows_as_they_lie=by_rows)
+    print(f"full head, rows as they lie {by_rows}: rows={rows} d={d} V={V}", flush=True)
+    x = synth.make_inputs(synth.small_config(rows, d, 8, V, k, peaked_every=4), seed=rows + d, with_full_head=True)
+    ids, lp = b.full_head_topk(to_dev_bf16(x.h), to_dev_bf16(x.W), k)
+    torch.cuda.synchronize()
+    ora = oracle_mod.full_head_topk(x.h, x.W, k)
+    z_at = lambda ri, ci: oracle_mod.full_logits_at(x.h, x.W, ri, ci)
+    compare_with_oracle(ids.cpu().numpy(), lp.cpu().numpy(), ora.ids, ora.lse, z_at, V, tie_tol=FP32_TOL, lp_tol=FP32_TOL)
+
+
 @pytest.mark.parametrize("rows,d", [(3, 40), (18, 72)])
 def test_an_infinite_element_stays_in_its_row(gpu, oracle_mod, rows, d):
     """h[1] = +inf in its last element: every other row is as before."""

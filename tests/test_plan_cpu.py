@@ -124,6 +124,18 @@ def test_many_rows_of_few_short_lists_have_at_most_ten_ids(rows, V, k, merge):
     assert plan_of("low", rows, 1024, 128, V, k)["merge"] == merge
 
 
+@pytest.mark.parametrize("rows,d,V,by_rows", [
+    (8, 8184, 50000, 1), (8, 8192, 50000, 0), (48, 1360, 32768, 1), (16, 4088, 20000, 1), (16, 4096, 20000, 0), (48, 1360, 120000, 1), (48, 1368, 120000, 0), (24, 2496, 50000, 1),
+    (24, 2504, 50000, 0), (16, 4088, 50000, 0), (48, 1200, 60000, 1), (48, 1216, 60000, 0), (48, 1040, 50000, 1), (48, 1048, 50000, 0), (32, 1800, 50000, 0), (40, 1024, 151936, 1),
+    (48, 1360, 151936, 0), (33, 1024, 80000, 1), (33, 1096, 80000, 0), (48, 800, 140000, 0), (48, 1024, 100000, 0), (48, 1360, 140000, 0), (32, 1800, 140000, 0), (48, 744, 100000, 1),
+    (32, 1120, 110000, 1), (32, 1080, 151936, 1), (32, 1080, 151752, 0), (24, 2216, 131704, 0), (8, 2216, 131704, 1), (16, 1248, 190008, 1), (16, 1256, 190008, 0),
+])
+def test_full_rows_are_regrouped_where_reading_them_as_they_lie_is_slower(rows, d, V, by_rows):
+    """48 rows, d = 1360, V = 140000 took 10 % longer when only rows * d decided."""
+    plan = plan_of("full", rows, d, 8, V, 10)
+    assert (plan["kernel"], plan["rows_as_they_lie"]) == ("rows", by_rows), plan
+
+
 def test_bench_names_the_kernel_the_library_runs():
     import os
     import sys
