@@ -7,7 +7,7 @@
 // What bounds it: the length of its chain of instructions.  There is hardly any work and one trip to memory (0.4 us; a second pass over the same lists
 // took 3.6 us of the first one's 3.9), but a lone wavefront takes 5 to 14 cycles per dependent instruction (device_utils.hpp).
 //
-// Lists of up to 16 ids (10 in a launch of more than 24 rows of few lists) whose entries a block's threads can hold (`few`, the usual call; plan.hpp: merge_kind): every thread keeps up to eight entries and one chunk's (m, s).
+// Lists of up to 16 ids (10 in a launch of more than 24 rows of few lists) whose entries a block's threads can hold (`few`, the usual call; plan.hpp: merge_ahead_most): every thread keeps up to eight entries and one chunk's (m, s).
 //   (1) T: the smallest of the maxima of k groups of entries (device_utils.hpp), so k entries reach it; two or three times as many do, where a sort
 //       would leave hardly more than k, but they are ranked by all threads and the sort is a chain of 21 exchanges.  M = max m_c in the same steps.
 //   (2) every wavefront puts its entries that reach T into a list of its own in shared memory (additions to a common counter take 250 cycles), and
@@ -75,7 +75,7 @@ __device__ __forceinline__ void wave_rank_keys(const uint64_t *keys, int n, int 
 
 __global__ __launch_bounds__(kRowMergeThreads) void merge_kernel(
     const float2 *__restrict__ part_ms, const float *__restrict__ part_val, const int *__restrict__ part_id,
-    int chunks, int k, int last_len, int j_th, int m_th, MergeKind kind, int32_t *__restrict__ out_ids, float *__restrict__ out_logprobs,
+    int chunks, int k, int last_len, int j_th, int m_th, int ahead_most, int32_t *__restrict__ out_ids, float *__restrict__ out_logprobs,
     const int32_t *__restrict__ id_map, SampleOut so, const float4 *__restrict__ part_smp)
 {
     __shared__ MergeLds S;
@@ -88,7 +88,8 @@ __global__ __launch_bounds__(kRowMergeThreads) void merge_kernel(
 
     // Entries of the last chunk's list from last_len on are filler (it may have fewer than k columns; the others have k).
     const int n_entries = (chunks - 1) * k + last_len;
-    const bool few = kind == kMergeShortLists, ahead = kind != kMergeLongLists;
+    // (Told by the host which code to take, the compiler lays the block out along the two ways, and long lists took 0.5 us longer: the router of four rows 51.1 / 51.8 us.)
+    const bool ahead = n_entries <= ahead_most, few = ahead && ahead_most == kMergeAhead * NT;
     float2 hm[H];
     if (few) hm[0] = ms[min(tid, chunks - 1)];
     else if (wave == 0 || wave == 2) {
@@ -426,7 +427,7 @@ hipError_t launch_merge(const float2 *part_ms, const float *part_val, const int 
     // out here: two divisions and a sort of its own in the kernel cost every call up to 0.5 us)
     int j_th = 1;
     if (chunks < k && (chunks - 1) * k + last_len > kMergeSel) j_th = (k + chunks - 1) / chunks + 1 < k ? (k + chunks - 1) / chunks + 1 : k;
-    merge_kernel<<<rows, kRowMergeThreads, 0, st>>>(part_ms, part_val, part_id, chunks, k, last_len, j_th, (k + j_th - 1) / j_th, merge_kind(rows, chunks, last_len, k),
+    merge_kernel<<<rows, kRowMergeThreads, 0, st>>>(part_ms, part_val, part_id, chunks, k, last_len, j_th, (k + j_th - 1) / j_th, merge_ahead_most(rows, chunks, k),
                                                     out_ids, out_logprobs, id_map, so, so.on ? part_smp : nullptr);
     return hipGetLastError();
 }

@@ -564,16 +564,15 @@ constexpr int kMergeShort = 16, kMergeShortFewLists = 10;      // ids of a short
 constexpr int kMergeFewRows = 24, kMergeFewLists = 128;  // ... a launch of more rows than these with up to these lists each
 constexpr int kMergeAhead = 8;           // entries per thread of short lists
 constexpr int kMergeAheadLong = 5;       // ... of long ones
-enum MergeKind : int { kMergeLongLists, kMergeLongListsAhead, kMergeShortLists };
 // ids in the last chunk's list (the others have k)
 inline int merge_last_len(int chunks, int chunk_cols, int V, int k) {
     const int last_cols = V - (chunks - 1) * chunk_cols;
     return last_cols < k ? last_cols : k;
 }
-inline MergeKind merge_kind(int rows, int chunks, int last_len, int k) {
-    const int n_entries = (chunks - 1) * k + last_len;
-    if (k <= (rows > kMergeFewRows && chunks <= kMergeFewLists ? kMergeShortFewLists : kMergeShort) && chunks <= kRowMergeThreads && n_entries <= kMergeAhead * kRowMergeThreads) return kMergeShortLists;
-    return n_entries <= kMergeAheadLong * kRowMergeThreads ? kMergeLongListsAhead : kMergeLongLists;
+// The most entries that are requested ahead: kMergeAhead per thread, or kMergeAheadLong where the lists count as long.
+inline int merge_ahead_most(int rows, int chunks, int k) {
+    const bool short_lists = chunks <= kRowMergeThreads && k <= (rows > kMergeFewRows && chunks <= kMergeFewLists ? kMergeShortFewLists : kMergeShort);
+    return (short_lists ? kMergeAhead : kMergeAheadLong) * kRowMergeThreads;
 }
 
 // ---- which kernels a call runs ------------------------------------------------------------------------------------
