@@ -7,7 +7,7 @@
 // What bounds it: the length of its chain of instructions.  There is hardly any work and one trip to memory (0.4 us; a second pass over the same lists
 // took 3.6 us of the first one's 3.9), but a lone wavefront takes 5 to 14 cycles per dependent instruction (device_utils.hpp).
 //
-// Lists of up to 16 ids (10 in a launch of more than 24 rows of few lists) whose entries a block's threads can hold (`few`, the usual call; plan.hpp: merge_ahead_most): every thread keeps up to eight entries and one chunk's (m, s).
+// Lists of up to 16 ids (10 in a launch of more than 24 rows of few lists) whose entries a block's threads can hold (SHORT, the usual call; plan.hpp: merge_short_lists): every thread keeps up to eight entries and one chunk's (m, s).
 //   (1) T: the smallest of the maxima of k groups of entries (device_utils.hpp), so k entries reach it; two or three times as many do, where a sort
 //       would leave hardly more than k, but they are ranked by all threads and the sort is a chain of 21 exchanges.  M = max m_c in the same steps.
 //   (2) every wavefront puts its entries that reach T into a list of its own in shared memory (additions to a common counter take 250 cycles), and
@@ -73,9 +73,12 @@ __device__ __forceinline__ void wave_rank_keys(const uint64_t *keys, int n, int 
 
 }  // namespace
 
+// SHORT: lists that the code for short ones takes (the other code as well, for rows that it leaves); long lists have an instance without it, whose blocks
+// would otherwise jump over it: the compiler's layout of one then moved calls of the other by up to 1.1 us (the router of four rows 50.8 / 51.9).
+template <bool SHORT>
 __global__ __launch_bounds__(kRowMergeThreads) void merge_kernel(
     const float2 *__restrict__ part_ms, const float *__restrict__ part_val, const int *__restrict__ part_id,
-    int chunks, int k, int last_len, int j_th, int m_th, int ahead_most, int32_t *__restrict__ out_ids, float *__restrict__ out_logprobs,
+    int chunks, int k, int last_len, int j_th, int m_th, int32_t *__restrict__ out_ids, float *__restrict__ out_logprobs,
     const int32_t *__restrict__ id_map, SampleOut so, const float4 *__restrict__ part_smp)
 {
     __shared__ MergeLds S;
@@ -88,21 +91,21 @@ __global__ __launch_bounds__(kRowMergeThreads) void merge_kernel(
 
     // Entries of the last chunk's list from last_len on are filler (it may have fewer than k columns; the others have k).
     const int n_entries = (chunks - 1) * k + last_len;
-    // (Told by the host which code to take, the compiler lays the block out along the two ways, and long lists took 0.5 us longer: the router of four rows 51.1 / 51.8 us.)
-    const bool ahead = n_entries <= ahead_most, few = ahead && ahead_most == kMergeAhead * NT;
+    constexpr int A = SHORT ? kMergeAhead : kMergeAheadLong;
+    const bool ahead = SHORT || n_entries <= A * NT;
     float2 hm[H];
-    if (few) hm[0] = ms[min(tid, chunks - 1)];
+    if (SHORT) hm[0] = ms[min(tid, chunks - 1)];
     else if (wave == 0 || wave == 2) {
 #pragma unroll
         for (int e = 0; e < H; ++e) hm[e] = ms[min(64 * e + lane, chunks - 1)];
     }
     float v_jth = 0.f;
     if (wave == 0 && j_th > 1) v_jth = pv[(size_t)min(lane, chunks - 1) * k + j_th - 1];
-    float v_ahead[kMergeAhead];
-    int id_ahead[kMergeAhead];
+    float v_ahead[A];
+    int id_ahead[A];
     if (ahead) {
 #pragma unroll
-        for (int u = 0; u < kMergeAhead; ++u) {
+        for (int u = 0; u < A; ++u) {
             if (u * NT >= n_entries) break;                      // (the same for all)
             const int e = min(tid + u * NT, n_entries - 1);
             v_ahead[u] = pv[e];
@@ -131,15 +134,15 @@ __global__ __launch_bounds__(kRowMergeThreads) void merge_kernel(
         rank = lanes_sum(rank, P);
         if (c < n && part == 0 && rank < k) emit(mine, rank);
     };
-    if (few) {
+    if constexpr (SHORT) {
         const bool have = tid < chunks;
         float4 draw = make_float4(0.f, 0.f, 0.f, 0.f);
         if (part_smp) draw = part_smp[(size_t)row * chunks + min(tid, chunks - 1)];
         const BoundPlan bound = make_bound_plan(min(n_entries, NT), k, 5);
         if (tid < kBoundGroups && tid >= bound.n_groups) S.groups[tid] = 0u;
-        uint32_t bits[kMergeAhead], most = 0u;
+        uint32_t bits[A], most = 0u;
 #pragma unroll
-        for (int u = 0; u < kMergeAhead; ++u) {
+        for (int u = 0; u < A; ++u) {
             bits[u] = 0u;
             if (u * NT >= n_entries) break;                      // (the same for all)
             if (tid + u * NT < n_entries) bits[u] = float_order_bits(v_ahead[u]);
@@ -157,7 +160,7 @@ __global__ __launch_bounds__(kRowMergeThreads) void merge_kernel(
         const float M = float_from_order_bits(top);              // the largest list's head; a row with a not-a-number ends up below
         uint32_t n_lane = 0u;
 #pragma unroll
-        for (int u = 0; u < kMergeAhead; ++u) {
+        for (int u = 0; u < A; ++u) {
             if (u * NT >= n_entries) break;
             n_lane += bits[u] >= T ? 1u : 0u;
         }
@@ -165,7 +168,7 @@ __global__ __launch_bounds__(kRowMergeThreads) void merge_kernel(
         const int n_mine = __builtin_amdgcn_readlane((int)upto, 63);      // entries of this wavefront
         int at = (int)(upto - n_lane);
 #pragma unroll
-        for (int u = 0; u < kMergeAhead; ++u) {
+        for (int u = 0; u < A; ++u) {
             if (u * NT >= n_entries) break;
             if (bits[u] >= T) S.mine[wave][min(at++, kMergeMine)] = u64_from(bits[u], ~(uint32_t)id_ahead[u]);      // (beyond: the list is not used)
         }
@@ -340,7 +343,7 @@ __global__ __launch_bounds__(kRowMergeThreads) void merge_kernel(
     };
     if (ahead && S.all_lists) {
 #pragma unroll
-        for (int u = 0; u < kMergeAhead; ++u) push(tid + u * NT < n_entries, v_ahead[u], id_ahead[u]);
+        for (int u = 0; u < A; ++u) push(tid + u * NT < n_entries, v_ahead[u], id_ahead[u]);
     } else {
         // eight lanes per list, which is sorted: its next eight entries only where all of these were taken
         const int sub = lane & 7, n_list = (int)S.n_list;
@@ -427,8 +430,12 @@ hipError_t launch_merge(const float2 *part_ms, const float *part_val, const int 
     // out here: two divisions and a sort of its own in the kernel cost every call up to 0.5 us)
     int j_th = 1;
     if (chunks < k && (chunks - 1) * k + last_len > kMergeSel) j_th = (k + chunks - 1) / chunks + 1 < k ? (k + chunks - 1) / chunks + 1 : k;
-    merge_kernel<<<rows, kRowMergeThreads, 0, st>>>(part_ms, part_val, part_id, chunks, k, last_len, j_th, (k + j_th - 1) / j_th, merge_ahead_most(rows, chunks, k),
-                                                    out_ids, out_logprobs, id_map, so, so.on ? part_smp : nullptr);
+    const auto launch = [&](auto kernel) {
+        kernel<<<rows, kRowMergeThreads, 0, st>>>(part_ms, part_val, part_id, chunks, k, last_len, j_th, (k + j_th - 1) / j_th, out_ids, out_logprobs,
+                                                  id_map, so, so.on ? part_smp : nullptr);
+    };
+    if (merge_short_lists(rows, chunks, last_len, k)) launch(merge_kernel<true>);
+    else launch(merge_kernel<false>);
     return hipGetLastError();
 }
 

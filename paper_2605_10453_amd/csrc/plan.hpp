@@ -569,10 +569,9 @@ inline int merge_last_len(int chunks, int chunk_cols, int V, int k) {
     const int last_cols = V - (chunks - 1) * chunk_cols;
     return last_cols < k ? last_cols : k;
 }
-// The most entries that are requested ahead: kMergeAhead per thread, or kMergeAheadLong where the lists count as long.
-inline int merge_ahead_most(int rows, int chunks, int k) {
-    const bool short_lists = chunks <= kRowMergeThreads && k <= (rows > kMergeFewRows && chunks <= kMergeFewLists ? kMergeShortFewLists : kMergeShort);
-    return (short_lists ? kMergeAhead : kMergeAheadLong) * kRowMergeThreads;
+inline bool merge_short_lists(int rows, int chunks, int last_len, int k) {
+    return k <= (rows > kMergeFewRows && chunks <= kMergeFewLists ? kMergeShortFewLists : kMergeShort)
+        && chunks <= kRowMergeThreads && (chunks - 1) * k + last_len <= kMergeAhead * kRowMergeThreads;
 }
 
 // ---- which kernels a call runs ------------------------------------------------------------------------------------

@@ -1,4 +1,4 @@
-"""Which code of csrc/merge_kernel.hip takes a call's lists (csrc/plan.hpp: merge_ahead_most), against the CPU fp64 checker: both sides of every line."""
+"""Which code of csrc/merge_kernel.hip takes a call's lists (csrc/plan.hpp: merge_short_lists), against the CPU fp64 checker: both sides of every line."""
 import pytest
 
 from paper_2605_10453_amd import synth
