@@ -137,18 +137,6 @@ SLIMSPEC_WAVE_REDUCE_F32(wave_max, op_max)
 SLIMSPEC_WAVE_REDUCE_F32(wave_sum, op_add)
 #undef SLIMSPEC_WAVE_REDUCE_F32
 
-__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
-    v = max(v, dpp_u32<0xB1>(v));
-    v = max(v, dpp_u32<0x4E>(v));
-    v = max(v, dpp_u32<0x141>(v));
-    v = max(v, dpp_u32<0x140>(v));
-    uint32_t a, b;
-    swap_pair<16>(v, a, b);
-    v = max(a, b);
-    swap_pair<32>(v, a, b);
-    return max(a, b);
-}
-
 __device__ __forceinline__ uint64_t u64_from(uint32_t hi, uint32_t lo) { return ((uint64_t)hi << 32) | lo; }
 __device__ __forceinline__ uint64_t u64_max(uint64_t a, uint64_t b) { return a > b ? a : b; }
 
@@ -273,18 +261,18 @@ __device__ __forceinline__ float gumbel_bound_bits(uint32_t x) { return (float)(
 // What follows serves tails that are chains of instructions.  On this chip a dependent vector instruction takes 5.5 cycles, a DPP step 14, a permlane swap
 // 32, a branch on what vector instructions found 70, an LDS round trip 75 and with two barriers 120 to 200, an LDS addition by one lane 250.
 //
-// A bound that at least k elements reach: `lanes` adjacent lanes hold elements, and the largest order bits of each group of 2^gl of them (at most 2^most)
-// are known.  Class i of k is made of the groups i, i + k, ... (`deep` of them, at most 8); the smallest maximum of the classes is the bound.
-// (d = 4096, V = 128256, k = 10: 28 entries of the lists reach it; a sort would leave 12.)
+// A bound that at least k elements reach, k <= 16: `lanes` adjacent lanes hold elements, and the largest order bits of each group of 2^gl of them (at most
+// 2^most, no more than 32 groups) are known.  Class i of k is made of the groups i, i + k, ... (`deep` of them, at most 8); the smallest maximum of the classes
+// is the bound.  (d = 4096, V = 128256, k = 10: 28 entries of the lists reach it; a sort would leave 12.)
+constexpr int kBoundMaxK = 16, kBoundGroups = 32;
 struct BoundPlan { int gl, n_groups, deep; bool all; };
-constexpr int kBoundGroups = 32;                                 // for k <= 16
 __device__ __forceinline__ BoundPlan make_bound_plan(int lanes, int k, int most) {
     BoundPlan p;
     // the largest gl that leaves 2 k groups: ceil(lanes / 2^gl) >= 2 k
     p.gl = __clz(2 * k - 1) - __clz(max(1, lanes - 1));
     if (p.gl > 0 && ((2 * k - 1) << p.gl) > lanes - 1) --p.gl;
     p.gl = min(max(p.gl, 0), most);
-    if (k <= 16) p.gl = max(p.gl, lanes <= kBoundGroups ? 0 : 27 - __clz(lanes - 1));      // no more than 32 groups, and 17 at least
+    p.gl = max(p.gl, lanes <= kBoundGroups ? 0 : 27 - __clz(lanes - 1));      // no more than 32 groups, and 17 at least
     p.n_groups = (lanes + (1 << p.gl) - 1) >> p.gl;
     p.deep = 1;
     while (p.deep < 8 && (p.deep + 1) * k <= p.n_groups) ++p.deep;
@@ -302,7 +290,7 @@ __device__ __forceinline__ uint32_t class_max(const uint32_t *groups, const Boun
     }
     return t;
 }
-// The bound for k <= 16; groups[kBoundGroups] with zeros beyond the last, and room for 128; top: the largest order bits of all.  The same in all lanes.
+// The bound; groups[kBoundGroups] with zeros beyond the last, and room for 128; top: the largest order bits of all.  The same in all lanes.
 __device__ __forceinline__ uint32_t bound_of_groups(const uint32_t *groups, const BoundPlan &p, int k, int lane, uint32_t &top) {
     const int i = lane & 15;
     top = max(groups[i], groups[16 + i]);

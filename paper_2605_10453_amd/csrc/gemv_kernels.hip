@@ -319,7 +319,7 @@ __global__ __launch_bounds__(NW * 64) void stream_topk_kernel(
     }
     __syncthreads();
     if (R == 1 && block_row_takes(cw, k)) {
-        if constexpr (R == 1) block_row_epilogue<NW>(one_row, row_plan, red, red2, n_parts, cw, chunk_col, tid, k, (size_t)row0 * chunks + chunk, part_ms, part_val, part_id, part_smp,
+        if constexpr (R == 1) block_row_epilogue<NW>(one_row, row_plan, red, n_parts, cw, chunk_col, tid, k, (size_t)row0 * chunks + chunk, part_ms, part_val, part_id, part_smp,
                                gumbel_key(seed_lo, seed_hi, (uint32_t)row0));
         return;
     }

@@ -261,18 +261,20 @@ __device__ __forceinline__ void chunk_row_epilogue(const float *sums, int n, int
     wave_topk<E>(ob, E, id, lane, k, sel, cw, part_val + slot * k, part_id + slot * k);
 }
 
-// The same for the only row of a block, by all its wavefronts: what one wavefront does as a chain of dependent instructions, which nothing overlaps, takes
-// two barriers here.  A lane of the first four wavefronts, one per SIMD, has two adjacent columns: with more wavefronts they would wait for each
-// other's instructions.  sums [n][cw], sums2: room for kSumParts more.  All threads call, behind a barrier; S.groups are zeros beyond the plan's.
-//   (1) the partial sums of the columns, in two steps where they are many (narrow chunks: cw <= 256);
+// The same for the only row of a block in a wide chunk, by all its wavefronts, for lists of up to 16 ids (plan.hpp: block_row_takes): what one wavefront does
+// as a chain of dependent instructions, which nothing overlaps, takes two barriers here.  A lane of the first four wavefronts, one per SIMD, has two adjacent
+// columns: with more wavefronts they would wait for each other's instructions.  sums [n][cw], n at most kDirectParts: a wavefront is one lane group there.
+// All threads call, behind a barrier; S.groups are zeros beyond the plan's.
+//   (1) the partial sums of the columns;
 //   (2) T: the smallest of the maxima of k groups of columns (device_utils.hpp), hence k elements reach it;
 //   (3) the elements that reach T are ranked by counting, eight by a wavefront at a time.
 // By time stamps the tail of d = 4096, r = 512, V = 128256 takes 1.5 us (one wavefront: 2.5), the call 32.0 (32.7).  With every wavefront of the block in
-// it the tail took 1.9, and 2 us more where the last chunk has few columns and all of them reached the bound.
+// it the tail took 1.9, and 2 us more where the last chunk has few columns and all of them reached the bound.  (Every instance for a single row has room for S
+// in shared memory, 5 KB, also where its chunks are narrow: a CU then has one block.)
 constexpr int kBlockRowWaves = 4, kBlockRowMine = 128;      // wavefronts with columns; keys of one's list at most
 struct BlockRowLds {
     uint64_t mine[kBlockRowWaves][kBlockRowMine + 8], wave_draw[kBlockRowWaves];
-    uint32_t groups[512];                                        // (lanes without a class read beyond the 256)
+    uint32_t groups[128];                                        // (lanes without a class read beyond the 32)
     int n_mine[kBlockRowWaves];
     float wave_s[kBlockRowWaves], wave_draw_z[kBlockRowWaves], m;
 };
@@ -283,8 +285,10 @@ __device__ __forceinline__ BlockRowPlan make_block_row_plan(int cw, int chunk_co
     p.bound = make_bound_plan(p.lanes, k, 4);
     return p;
 }
+static_assert(!block_row_takes(kChunkCols, kBoundMaxK + 1), "lists that bound_of_groups serves");
+static_assert(!block_row_takes(8 * 32, 1) && kDirectParts >= 16, "more than half of a wavefront's lanes per chunk, hence one partial sum per wavefront");
 template <int NW>
-__device__ __forceinline__ void block_row_epilogue(BlockRowLds &S, const BlockRowPlan &plan, const float *sums, float *sums2, int n, int cw, int chunk_col, int tid, int k,
+__device__ __forceinline__ void block_row_epilogue(BlockRowLds &S, const BlockRowPlan &plan, const float *sums, int n, int cw, int chunk_col, int tid, int k,
                                                    size_t slot, float2 *__restrict__ part_ms, float *__restrict__ part_val,
                                                    int *__restrict__ part_id, float4 *__restrict__ part_smp, const GumbelKey &gk)
 {
@@ -310,20 +314,12 @@ __device__ __forceinline__ void block_row_epilogue(BlockRowLds &S, const BlockRo
         return s;
     };
     const int n2 = cw / 2;
-    if (n > kDirectParts) {
-        const int wide = n2 > 64 ? 1 : 0, cb = wave & wide, gi = wave >> wide, G = (NW >> wide) < kSumParts ? NW >> wide : kSumParts;
-        if (gi < G && 64 * cb + lane < n2)
-            reinterpret_cast<float2 *>(sums2)[gi * n2 + 64 * cb + lane] = add(reinterpret_cast<const float2 *>(sums) + gi * n2 + 64 * cb + lane, (n - gi + G - 1) / G, G * n2);
-        __syncthreads();
-        sums = sums2;
-        n = G;
-    }
     const bool with_columns = wave * 64 < plan.lanes;            // (at most 256 lanes: the first four wavefronts)
     const bool act = tid < plan.lanes;
     const uint32_t id0 = (uint32_t)(chunk_col + 2 * tid);
     float2 z = make_float2(kNegInf, kNegInf);
     uint32_t b0 = 0u, b1 = 0u;
-    const int gl = plan.bound.gl, n_groups = plan.bound.n_groups;
+    const int gl = plan.bound.gl;
     if (with_columns) {
         if (act) {
             z = add(reinterpret_cast<const float2 *>(sums) + tid, n, n2);
@@ -339,15 +335,8 @@ __device__ __forceinline__ void block_row_epilogue(BlockRowLds &S, const BlockRo
     __syncthreads();
     int n_mine = 0;
     if (with_columns) {
-        uint32_t T, top;
-        if (k <= 16) T = bound_of_groups(S.groups, plan.bound, k, lane, top);
-        else {
-            top = 0u;
-            for (int i = lane; i < n_groups; i += 64) top = max(top, S.groups[i]);
-            top = wave_max_u32(top);
-            T = ~wave_max_u32(~class_max(S.groups, plan.bound, k, lane));
-            T = plan.bound.all ? 1u : max(1u, T);
-        }
+        uint32_t top;
+        const uint32_t T = bound_of_groups(S.groups, plan.bound, k, lane, top);
         const float M = float_from_order_bits(top);              // (where it is no number, the sum of exponentials is none either)
         // (two ballots are fewer instructions here than a prefix sum over the lanes)
         const auto push = [&](bool take, uint32_t bits, uint32_t id) {

@@ -41,6 +41,7 @@ constexpr int kMergeLists = SLIMSPEC_KMAX_INTERNAL + kCandSlack; // lists that m
 constexpr int kMergeCand = kMergeLists * SLIMSPEC_KMAX_INTERNAL; // their entries, at most
 constexpr int kMergeSel = 256;                                   // entries that are ranked all pairs, at most
 static_assert(kMergeAhead * kRowMergeThreads <= kMergeCand, "entries taken ahead fit as well");
+static_assert(kMergeShort <= kBoundMaxK, "lists that bound_of_groups serves");
 static_assert(kMergeSel >= 2 * kMergeLists, "what a bound admits beyond this many are equal logits");
 
 struct MergeLds {
