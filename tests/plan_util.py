@@ -23,7 +23,8 @@ def plan_of(kind: str, rows: int, d: int, r: int, V: int, k: int, fp32=False, pr
     """What a call runs.  kernel: stream, rows, tile or resident; and, for the last two, f16 (operands), rows_per_block,
     col_blocks, records (per row and column block), parks (rows that wait for their exact columns), parked_offset and
     parked_row_bytes (where in the workspace a row does, its number of columns first); resident_fits; for stream, chunk_cols,
-    rows_in_lds (whether a launch's row input fits shared memory) and own_input (the kernel makes t itself);
+    rows_in_lds (whether a launch's row input fits shared memory), own_input (the kernel makes t itself) and block_tail (all
+    wavefronts of a block finish its only row);
     for rows, sum_slices (slices of t that its blocks add, 0: none) and rows_as_they_lie (the full head's rows are read without a launch that regroups them); for stream and rows, merge (how merge_kernel takes the chunks' lists: short,
     long_ahead or long)."""
     line = f"{kind} {rows} {d} {r} {V} {k} {int(fp32)} {int(prepared)} {int(sampling)}\n"
