@@ -80,10 +80,13 @@ inline size_t stream_lds_bytes(int R, int nw, const ChunkGeom &g, int K, int x_b
     return 4 * (size_t)R * cw * (n + (n > kDirectParts ? kSumParts : 0)) + 8 * (size_t)(R < nw ? R : nw) * cw + (size_t)x_bytes * R * K;
 }
 // A single row's tail by the whole block (gemv_parts.hpp: block_row_epilogue) instead of by one wavefront: wide chunks and short lists, whose elements are
-// many and whose candidates few.  (One wavefront / the block, us a call, d = 2048, r = 256: V = 128256, chunks of 512, k = 10 22.3 / 20.8, k = 16 22.5 / 22.1, k = 24
-// 22.8 / 23.9; V = 110000, of 432, k = 10 20.2 / 19.8, k = 16 20.6 / 21.5; V = 90000, of 352, k = 10 18.1 / 18.4; V = 32768, of 128, k = 10 14.3 / 14.8, k = 24 15.0 / 17.1;
-// d = 512, r = 40, V = 20000 11.3 / 12.2; full head, d = 1688, V = 87960, k = 38 57.7 / 60.0.)
-constexpr __host__ __device__ bool block_row_takes(int cw, int k) { return cw >= 400 && k <= (cw == kChunkCols ? 16 : 10); }
+// many and whose candidates few.  Chunks of 512 columns have 32 groups for the bound, two for each of 16 ids; narrower ones have fewer, the bound admits more, and
+// more than 64 candidates take the wavefronts a second round.  (One wavefront / the block, us a call, d = 2048, r = 256: chunks of 512, V = 128256 k = 4 21.2 / 19.7,
+// k = 10 21.3 / 20.4, k = 16 22.1 / 21.6, k = 24 22.8 / 23.9; of 496, V = 125000 k = 10 20.5 / 19.7, k = 13 21.7 / 21.0, k = 15 21.4 / 21.5; of 464 k = 13 20.5 / 19.8, k = 14
+// 20.4 / 19.7, k = 15 20.6 / 21.4; of 448 k = 13 19.7 / 19.3, k = 15 19.6 / 20.7; of 432, V = 110000 k = 10 19.4 / 18.8, k = 13 19.9 / 19.3, k = 14 20.0 / 20.5, k = 16 20.2 / 20.9; of 400,
+// V = 102400 k = 10 19.0 / 18.5, k = 13 19.7 / 19.0, k = 15 19.7 / 20.5; of 352, V = 90000, k = 10 18.1 / 18.4; of 128, V = 32768, k = 10 14.3 / 14.8, k = 24 15.0 / 17.1; d = 512, r = 40,
+// V = 20000 11.3 / 12.2; full head, d = 1688, V = 87960, k = 38 57.7 / 60.0.)
+constexpr __host__ __device__ bool block_row_takes(int cw, int k) { return cw >= 400 && k <= (cw == kChunkCols ? 16 : 13); }
 constexpr size_t kStreamLdsLimit = 150 * 1024;      // of the CU's 160 KB
 // Do the bf16 rows of a launch (at most kGemvMaxRows) fit beside what its smallest block needs?
 inline bool stream_rows_fit(int rows, const ChunkGeom &g, int K) {

@@ -30,8 +30,16 @@ def test_one_row(gpu, oracle_mod, d, r, V, cols, ks):
         check_sample_outputs(torch, out, ora, 99, V, ora.z, oracle_mod)
 
 
+@pytest.mark.parametrize("V,k,tail", [(104000, 13, 1), (104000, 14, 0), (102008, 13, 1), (125000, 13, 1), (125000, 16, 0), (131072, 16, 1)])
+def test_lists_on_either_side_of_the_line(gpu, oracle_mod, V, k, tail):
+    for d, r in ((64, 16), (520, 264)):
+        assert_plan("low", 1, d, r, V, k, block_tail=tail)
+        print(f"wide chunks, the line: d={d} r={r} V={V} k={k}", flush=True)
+        check(gpu, oracle_mod, synth.make_inputs(synth.small_config(1, d, r, V, k), seed=V + k + r), k)
+
+
 @pytest.mark.parametrize("V,last,k", [(V, last, k) for V, last in ((128520, 8), (128528, 16), (128576, 64), (128896, 384), (131072, 512)) for k in (1, 8, 9, 16)]
-                         + [(104008, 8, k) for k in (1, 8, 9, 10)])
+                         + [(104008, 8, k) for k in (1, 8, 9, 13)])
 def test_last_chunks_of_few_columns(gpu, oracle_mod, V, last, k):
     """Fewer columns than ids or than groups for a bound, wavefronts without columns; then the winners among them."""
     torch, b = gpu

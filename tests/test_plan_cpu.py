@@ -136,6 +136,15 @@ def test_full_rows_are_regrouped_where_reading_them_as_they_lie_is_slower(rows, 
     assert (plan["kernel"], plan["rows_as_they_lie"]) == ("rows", by_rows), plan
 
 
+@pytest.mark.parametrize("V,cols,most", [(131072, 512, 16), (128256, 512, 16), (125000, 496, 13), (110000, 432, 13), (102400, 448, 13), (102000, 400, 13), (97920, 384, 0), (32768, 128, 0),
+                                         (151936, 320, 0), (262144, 512, 16)])
+def test_a_single_rows_tail_by_the_block(V, cols, most):
+    """Wide chunks and lists of up to 16 ids, 13 in chunks of 400 to 504 columns; k = 11 to 13 took 3 % longer there by one wavefront."""
+    for k in range(1, 20):
+        plan = plan_of("low", 1, 2048, 256, V, k)
+        assert (plan["chunk_cols"], plan["block_tail"]) == (cols, int(k <= most)), plan
+
+
 def test_bench_names_the_kernel_the_library_runs():
     import os
     import sys
