@@ -43,8 +43,8 @@ __global__ __launch_bounds__(64 * kDRWaves) void down_rows_kernel(
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n_tiles = (r + 63) / 64 * 4;
     if ((int)blockIdx.x >= n_tiles) {
-        const int first = (n_tiles + 7) & ~7;
-        if ((int)blockIdx.x >= first && blockIdx.y == 0) read_ahead_block<kDRWaves>(ahead, (int)blockIdx.x - first);
+        const int first = (n_tiles + 7) & ~7, n_each = (int)gridDim.x - first;         // (of every group, a multiple of 8)
+        if ((int)blockIdx.x >= first) read_ahead_block<kDRWaves>(ahead, (int)blockIdx.y * n_each + (int)blockIdx.x - first);
         return;
     }
     const int tile = (n_tiles & 7) == 0 ? (int)(blockIdx.x & 7) * (n_tiles >> 3) + (int)(blockIdx.x >> 3) : (int)blockIdx.x;
@@ -141,8 +141,8 @@ __global__ __launch_bounds__(64 * kDRWaves) void down_rows_kernel(
 template <int NT>
 static hipError_t launch_down_rows_nt(const uint16_t *h, const uint16_t *A, void *X, int rows_pad, int d, int r, const DownGrid &g, const ReadAhead &ahead, hipStream_t st)
 {
-    const int n_tiles = (r + 63) / 64 * 4;
-    const dim3 grid(ahead.blocks ? (n_tiles + 7) / 8 * 8 + ahead.blocks : n_tiles, g.n_groups);
+    const int n_tiles = (r + 63) / 64 * 4, n_each = ahead_blocks_each(ahead, g.n_groups);
+    const dim3 grid(n_each ? (n_tiles + 7) / 8 * 8 + n_each : n_tiles, g.n_groups);
     down_rows_kernel<NT><<<grid, 64 * kDRWaves, 0, st>>>(h, A, static_cast<uint4 *>(X), rows_pad, d, r, g, ahead);
     return hipGetLastError();
 }

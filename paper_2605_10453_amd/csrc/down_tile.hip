@@ -474,7 +474,8 @@ hipError_t launch_down_projection_pieces(const uint16_t *h, const uint16_t *A, f
 {
     const hipError_t e = launch_down_tiles<true, false>(h, A, part, g, down_tile_blocks(g), d, r, ReadAhead(), st);
     if (e != hipSuccess) return e;
-    down_finish_kernel<true><<<(4 * g.n_rt_all * g.n_ct + 7) / 8 * 8 + ahead.blocks, 256, 0, st>>>(
+    const int blocks = 4 * g.n_rt_all * g.n_ct;
+    down_finish_kernel<true><<<ahead.blocks ? (blocks + 7) / 8 * 8 + ahead.blocks : blocks, 256, 0, st>>>(
         part, rows_pad, r, nullptr, static_cast<uint4 *>(X), nullptr, nullptr, 0, nullptr, kOperandExact, g, ahead);
     return hipGetLastError();
 }

@@ -15,13 +15,14 @@ PROGRAM = r"""
 #include <vector>
 using namespace slimspec;
 int main() {
-    int K, V, bytes, nw;
-    while (std::scanf("%%d %%d %%d %%d", &K, &V, &bytes, &nw) == 4) {
+    int K, V, bytes, nw, groups;
+    while (std::scanf("%%d %%d %%d %%d %%d", &K, &V, &bytes, &nw, &groups) == 5) {
         const RowsGeom g = make_rows_geom(K, V);
         const ReadAhead a = rows_read_ahead(reinterpret_cast<const uint16_t *>(16), K, V, g, bytes, nw);
         std::vector<char> seen((size_t)K * (V / 8));
         long bad = 0, loads = 0;
-        for (int b = 0; b < a.blocks; ++b)
+        const int each = ahead_blocks_each(a, groups);
+        for (int b = 0; b < groups * each; ++b)             // row b / each of the grid; a block's XCD is its place in its row by 8
             for (int w = 0; w < nw; ++w) {
                 AheadSlot s = ahead_slot(a, b & 7, (b >> 3) * nw + w);
                 for (int n = 0; s.on && n < kAheadLoads; ++n, ahead_next(a, s))
@@ -40,7 +41,9 @@ int main() {
                 const int row = range * a.per + t;
                 for (int c = 0; row < K && c < V / 8; ++c) missed += !seen[(size_t)row * (V / 8) + c];
             }
-        std::printf("%%ld %%ld %%ld %%d\n", bad, missed, loads, a.blocks);
+        long distinct = 0;
+        for (char c : seen) distinct += c;
+        std::printf("%%ld %%ld %%ld %%ld %%d %%d\n", bad, missed, loads, distinct, a.blocks, each);
     }
 }
 """
@@ -57,12 +60,36 @@ def walk(tmp_path_factory):
 @pytest.mark.parametrize("K", [8, 40, 136, 264, 520, 2048])
 @pytest.mark.parametrize("V", [8, 136, 8200, 20000, 33000, 66008, 98312, 131080, 165000, 196616])
 def test_loads_lie_inside_and_cover(walk, K, V):
+    # the geometry of rows_topk_kernel: G groups of 128 columns per block, slices of the contraction
+    cols = -(-V // 128)
+    G = -(-cols // 256)
+    G = 4 if G > 6 else G
+    steps = -(-K // 32)
+    per = -(-steps // min(8 // G, steps))
+    ranges = -(-steps // per)
+    lanes = 16 * G if G <= 4 else 8 * G                          # of a unit; a wavefront's load covers 64 / lanes rows of it
+    rows_at_once, units = 64 // lanes, -(-(V // 8) // lanes)
     for nbytes in (1 << 20, 4 << 20, 9 << 20):
         for nw in (4, 16):
-            bad, missed, loads, blocks = walk(f"{K} {V} {nbytes} {nw}\n")
+            bad, missed, loads, distinct, blocks, each = walk(f"{K} {V} {nbytes} {nw} 1\n")
             assert bad == 0 and missed == 0, (nbytes, nw, bad, missed)
-            assert blocks % 8 == 0 and 16 * loads <= 4 * nbytes + 64 * 1024 * blocks, (nbytes, nw, loads, blocks)
+            assert blocks % 8 == 0 and each == blocks
+            # no more than asked for, but for the rows that a load at the end of a range covers besides
+            assert 16 * distinct <= nbytes + ranges * (rows_at_once - 1) * 2 * V, (nbytes, nw, distinct)
+            # loads that repeat another: of a unit's last wavefront at most all but one, and what of the last range lies beyond K
+            rows = min(nbytes // (2 * V * ranges), 32 * per)
+            beyond = sum(1 for t in range(0, rows, rows_at_once) if (ranges - 1) * 32 * per + t > K - rows_at_once) + 1 if rows else 0
+            assert loads - distinct <= 64 * units * (11 + beyond), (nbytes, nw, loads, distinct)
+
+
+@pytest.mark.parametrize("groups", [2, 3, 5, 16])
+@pytest.mark.parametrize("K,V", [(64, 128256), (128, 32768), (256, 60000), (40, 136)])
+def test_several_groups_share_the_blocks(walk, groups, K, V):
+    """down_rows_kernel has a row of blocks per group: they read the same as one row does, and no more blocks than that takes."""
+    one, shared = walk(f"{K} {V} {9 << 20} 16 1\n"), walk(f"{K} {V} {9 << 20} 16 {groups}\n")
+    assert shared[:4] == one[:4] and shared[5] % 8 == 0
+    assert one[4] <= groups * shared[5] < one[4] + 8 * groups
 
 
 def test_nothing_where_a_row_of_each_slice_is_more(walk):
-    assert walk(f"512 {1 << 23} {4 << 20} 4\n")[2:] == [0, 0]
+    assert walk(f"512 {1 << 23} {4 << 20} 4 3\n")[2:] == [0, 0, 0, 0]
