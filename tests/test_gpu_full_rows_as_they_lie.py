@@ -43,18 +43,25 @@ def test_blocks_of_several_groups(gpu, oracle_mod, rows, d, V, by_rows):
     compare_with_oracle(ids.cpu().numpy(), lp.cpu().numpy(), ora.ids, ora.lse, z_at, V, tie_tol=FP32_TOL, lp_tol=FP32_TOL)
 
 
-@pytest.mark.parametrize("rows,d", [(3, 40), (18, 72)])
-def test_an_infinite_element_stays_in_its_row(gpu, oracle_mod, rows, d):
-    """h[1] = +inf in its last element: every other row is as before."""
+@pytest.mark.parametrize("rows,d,by_rows", [(3, 40, 1), (18, 72, 1), (16, 4072, 1), (16, 4104, 0), (40, 1608, 1), (40, 1640, 0)])
+def test_an_infinite_element(gpu, oracle_mod, rows, d, by_rows):
+    """h[1] = +inf in its last element.  Lanes beyond the last element read the row's last eight once more, against weights that were cleared: that must not
+    make row 1's logits not-a-numbers.  They are +inf or -inf by the sign of the last weight, so the first k columns with a positive one win; and every
+    other row is as before.  On both sides of the line: the row as it lies and regrouped."""
     torch, b = gpu
     V, k = 1000, 5
+    assert_plan("full", rows, d, 8, V, k, kernel="rows", rows_as_they_lie=by_rows)
+    assert d % 32 == 8                                           # the last step of 32 holds the last eight elements alone
     x = synth.make_inputs(synth.small_config(rows, d, 8, V, k), seed=d, with_full_head=True)
-    h = x.h.copy()
+    h, W_bits = x.h.copy(), x.W.copy()
     h[1, d - 1] = 0x7f80
-    W = to_dev_bf16(x.W)
+    W_bits[d - 1][(W_bits[d - 1] & 0x7fff) == 0] = 0x3c00        # no zeros: their product with the infinity would be no number
+    W = to_dev_bf16(W_bits)
+    print(f"an infinite element: rows={rows} d={d}", flush=True)
     ids0, lp0 = b.full_head_topk(to_dev_bf16(x.h), W, k)
     ids1, lp1 = b.full_head_topk(to_dev_bf16(h), W, k)
     torch.cuda.synchronize()
+    assert ids1[1].cpu().numpy().tolist() == np.flatnonzero(W_bits[d - 1] < 0x8000)[:k].tolist()
     others = np.arange(rows) != 1
     assert np.array_equal(ids0.cpu().numpy()[others], ids1.cpu().numpy()[others])
     assert np.array_equal(lp0.cpu().numpy()[others], lp1.cpu().numpy()[others])

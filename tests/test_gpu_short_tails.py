@@ -1,6 +1,7 @@
-"""The tails of few-row calls (csrc/gemv_parts.hpp: block_row_epilogue, csrc/merge_kernel.hip: short lists) against the CPU fp64 checker, at
-the sizes where their bounds can go wrong: fewer groups of columns or of entries than ids, one group more or less, chunks of every width, last chunks of
-few columns, wavefronts whose own lists are longer than a scan or overflow."""
+"""The tails of few-row calls against the CPU fp64 checker: the merge of short lists (csrc/merge_kernel.hip) at the sizes where its bound can go wrong, fewer
+groups of entries than ids, one group more or less, wavefronts whose own lists are longer than a scan or overflow; and a row's tail by one wavefront
+(csrc/gemv_parts.hpp: chunk_row_epilogue), chunks of 64 to 320 columns, last chunks of few columns.  Wide chunks, whose tail is the whole block's:
+test_gpu_wide_chunk_tails.py."""
 from dataclasses import replace
 
 import numpy as np
