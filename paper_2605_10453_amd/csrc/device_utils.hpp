@@ -258,8 +258,9 @@ constexpr float kGumbelBoundBase = 159.f;               // 32 for the scale of x
 constexpr float kGumbelBoundScale = 1.1920928955078125e-7f;      // 2^-23
 __device__ __forceinline__ float gumbel_bound_bits(uint32_t x) { return (float)(int)__float_as_uint((float)(x & 0xfffffe00u)); }
 
-// What follows serves tails that are chains of instructions.  On this chip a dependent vector instruction takes 5.5 cycles, a DPP step 14, a permlane swap
-// 32, a branch on what vector instructions found 70, an LDS round trip 75 and with two barriers 120 to 200, an LDS addition by one lane 250.
+// What follows serves tails that are chains of instructions.  Cycles per step of such a chain, one wavefront on a CU: a vector instruction 8, one with a DPP operand
+// 12, a permlane swap with its move and maximum 28, a comparison and a branch on its ballot 64, an LDS read 69, an LDS write and a read behind barriers 133
+// (four wavefronts) to 158 (eight), an LDS addition by one lane whose result all wait for 174.
 //
 // A bound that at least k elements reach, k <= 16: `lanes` adjacent lanes hold elements, and the largest order bits of each group of 2^gl of them (at most
 // 2^most, no more than 32 groups) are known.  Class i of k is made of the groups i, i + k, ... (`deep` of them, at most 8); the smallest maximum of the classes

@@ -5,12 +5,12 @@
 // works on unique keys (order bits of the logit, then the inverted id), so the output does not depend on scheduling.
 //
 // What bounds it: the length of its chain of instructions.  There is hardly any work and one trip to memory (0.4 us; a second pass over the same lists
-// took 3.6 us of the first one's 3.9), but a lone wavefront takes 5 to 14 cycles per dependent instruction (device_utils.hpp).
+// took 3.6 us of the first one's 3.9), but a lone wavefront takes 8 to 28 cycles per dependent instruction (device_utils.hpp).
 //
 // Lists of up to 16 ids (10 in a launch of more than 24 rows of few lists) whose entries a block's threads can hold (SHORT, the usual call; plan.hpp: merge_short_lists): every thread keeps up to eight entries and one chunk's (m, s).
 //   (1) T: the smallest of the maxima of k groups of entries (device_utils.hpp), so k entries reach it; two or three times as many do, where a sort
 //       would leave hardly more than k, but they are ranked by all threads and the sort is a chain of 21 exchanges.  M = max m_c in the same steps.
-//   (2) every wavefront puts its entries that reach T into a list of its own in shared memory (additions to a common counter take 250 cycles), and
+//   (2) every wavefront puts its entries that reach T into a list of its own in shared memory (an addition to a common counter takes 174 cycles), and
 //       the terms of the log-sum-exp are added, one per thread.
 //   (3) the k first are found by counting.
 // Two barriers.  Measured with one wavefront for all of this / now: one row, d = 4096, r = 512, V = 128256 33.9 / 32.7 us a call, with draws at V = 151936
