@@ -303,13 +303,17 @@ __device__ __forceinline__ uint32_t bound_of_groups(const uint32_t *groups, cons
     both(dpp_u32<0x140>(t), dpp_u32<0x140>(top));
     return p.all ? 1u : max(1u, t);
 }
-// Sum of v over the lanes up to and including this one.
-__device__ __forceinline__ uint32_t wave_prefix_sum(uint32_t v) {
+// Sum of v over the lanes of this half up to and including this one.
+__device__ __forceinline__ uint32_t half_prefix_sum(uint32_t v) {
     v += dpp_u32<0x111>(v);                                      // row_shr:1, 2, 4, 8 (zero from outside the row of 16)
     v += dpp_u32<0x112>(v);
     v += dpp_u32<0x114>(v);
     v += dpp_u32<0x118>(v);
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);      // row_bcast:15 into the odd rows
+    return v + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);      // row_bcast:15 into the upper row of a half
+}
+// ... over all lanes
+__device__ __forceinline__ uint32_t wave_prefix_sum(uint32_t v) {
+    v = half_prefix_sum(v);
     return v + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);      // row_bcast:31 into the upper half
 }
 // How many of the W lists' keys are larger than `key`; longest: the longest list's length, the same in all lanes.  Eight adjacent lanes share the scan

@@ -444,6 +444,26 @@ inline RowsGeom make_rows_geom(int K, int V) {
 constexpr int kRowsMaxKS = 8;
 constexpr size_t kRowsLdsLimit = 156 * 1024;
 inline bool rows_meet_at_once(int KS, int rows) { return KS > 2 && KS <= kRowsMaxKS && rows <= (KS > 4 ? 16 : 8); }
+constexpr __host__ __device__ int rows_meet_stride(int G) { return 128 * G + 4; }      // floats between two rows of a slice's sums
+// What the epilogue of two rows needs in shared memory beside their logits, per wavefront: each row's candidates.
+constexpr int kPairCand = 64;
+constexpr int kPairMaxK = 32;            // longer lists take one row per wavefront
+constexpr int kPairKeys = kPairCand + 2; // (the two rows' candidates in different banks)
+// Bytes before the pieces of t that a block keeps: the rows' logits, the candidates.
+constexpr __host__ __device__ size_t rows_x_offset(int NT, int G, int waves, int k) {
+    return sizeof(float) * 16 * NT * (size_t)rows_lds_stride(G) + (k <= kPairMaxK ? sizeof(uint64_t) * 2 * kPairKeys * waves : 0);
+}
+// Shared memory of a block of rows_topk_kernel; meet_at: floats before the place where the slices' sums meet at once, 0: they meet otherwise
+// (sum: the block keeps t's pieces, see rows_sum_slices).
+struct RowsLds { size_t bytes = 0; int meet_at = 0; };
+inline RowsLds rows_lds(int rows, int K, const RowsGeom &g, int k, bool sum) {
+    const int NT = (rows + 15) / 16;
+    RowsLds l;
+    l.bytes = rows_x_offset(NT, g.G, g.waves, k) + (sum ? 3 * 16 * 16 * (size_t)((K + 63) / 64 * 8) : 0);
+    const size_t meet = sizeof(float) * (size_t)(g.KS - 1) * rows * rows_meet_stride(g.G);
+    if (NT == 1 && rows_meet_at_once(g.KS, rows) && l.bytes + meet <= kRowsLdsLimit) { l.meet_at = (int)(l.bytes / sizeof(float)); l.bytes += meet; }
+    return l;
+}
 // What a launch before rows_topk_kernel reads ahead: the beginning of every slice of the contraction, in blocks of nw wavefronts.  How much: what
 // comes while the launch's own blocks work; more makes it longer.  (Nothing / this, us a call: down_rows_kernel, 9 MB: 7 rows, d = 1024, r = 256, V = 30000
 // 16.7 / 15.2; 5 rows, r = 128, V = 128256 18.0 / 17.0 (6 MB 17.2, 16 MB 17.0); 16 rows, d = 2048, r = 256, V = 65536 21.5 / 20.3 (6 MB 20.7, 16 MB 20.5); 12 rows in four

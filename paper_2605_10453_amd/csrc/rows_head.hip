@@ -44,18 +44,6 @@ __device__ __forceinline__ uint32_t pair16(uint32_t a, uint32_t b) {
     return __builtin_amdgcn_perm(b, a, HIGH ? 0x07060302u : 0x05040100u);
 }
 
-// What the epilogue of two rows needs in shared memory beside their logits, per wavefront: each row's candidates.
-constexpr int kPairCand = 64;
-constexpr int kPairMaxK = 32;            // longer lists take one row per wavefront
-constexpr int kPairKeys = kPairCand + 2; // (the two rows' candidates in different banks)
-// Bytes before the pieces of t that a block keeps: the rows' logits, the candidates.
-constexpr __host__ __device__ size_t rows_x_offset(int NT, int G, int waves, int k) {
-    return sizeof(float) * 16 * NT * (size_t)rows_lds_stride(G) + (k <= kPairMaxK ? sizeof(uint64_t) * 2 * kPairKeys * waves : 0);
-}
-
-// Floats between two rows of a slice's sums.
-constexpr __host__ __device__ int rows_meet_stride(int G) { return 128 * G + 4; }
-
 // Sum over each half of 32 lanes, in every lane of it.
 __device__ __forceinline__ float half_sum(float v) {
     v += dpp_f32<0xB1>(v);
@@ -76,14 +64,6 @@ __device__ __forceinline__ uint64_t half_max_key(uint64_t k) {
     swap_pair<16>((uint32_t)(k >> 32), ha, hb);
     swap_pair<16>((uint32_t)k, la, lb);
     return u64_max(u64_from(ha, la), u64_from(hb, lb));
-}
-// Sum of v over the lanes of this half up to and including this one.
-__device__ __forceinline__ uint32_t half_prefix_sum(uint32_t v) {
-    v += dpp_u32<0x111>(v);                                      // row_shr:1, 2, 4, 8 (zero from outside the row of 16)
-    v += dpp_u32<0x112>(v);
-    v += dpp_u32<0x114>(v);
-    v += dpp_u32<0x118>(v);
-    return v + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);      // row_bcast:15 into the upper row of a half
 }
 // bits = 2 bits + (z >= t)
 __device__ __forceinline__ void shift_in_ge(uint32_t &bits, float z, float t) {
@@ -619,15 +599,12 @@ template <int NT, int NP, int GM, bool SUM>
 static hipError_t launch_rows(const RowsInput &x, const uint16_t *M, float2 *ms, float *pv, int *pi, float4 *smp, int rows, int row0,
                               int K, int V, const RowsGeom &g, int k, uint32_t seed_lo, uint32_t seed_hi, hipStream_t st)
 {
-    size_t lds = rows_x_offset(NT, g.G, g.waves, k) + (SUM ? sizeof(uint4) * 3 * 16 * (size_t)((K + 63) / 64 * 8) : 0);
-    int meet_at = 0;                     // floats before the slices' sums, 0: not so
-    const size_t meet = sizeof(float) * (size_t)(g.KS - 1) * rows * rows_meet_stride(g.G);
-    if (NT == 1 && rows_meet_at_once(g.KS, rows) && lds + meet <= kRowsLdsLimit) { meet_at = (int)(lds / sizeof(float)); lds += meet; }
+    const RowsLds lds = rows_lds(rows, K, g, k, SUM);
     static LdsLimit lds_limit;
-    hipError_t e = lds_limit.raise(reinterpret_cast<const void *>(rows_topk_kernel<NT, NP, GM, SUM>), (int)lds);
+    hipError_t e = lds_limit.raise(reinterpret_cast<const void *>(rows_topk_kernel<NT, NP, GM, SUM>), (int)lds.bytes);
     if (e != hipSuccess) return e;
-    rows_topk_kernel<NT, NP, GM, SUM><<<g.chunks, 64 * g.waves, lds, st>>>(static_cast<const uint4 *>(x.X), x.slices, x.nds, M, ms, pv, pi, smp,
-                                                                           rows, row0, K, V, g.chunks, g.G, g.KS, k, seed_lo, seed_hi, meet_at, x.by_rows ? 1 : 0);
+    rows_topk_kernel<NT, NP, GM, SUM><<<g.chunks, 64 * g.waves, lds.bytes, st>>>(static_cast<const uint4 *>(x.X), x.slices, x.nds, M, ms, pv, pi, smp,
+                                                                           rows, row0, K, V, g.chunks, g.G, g.KS, k, seed_lo, seed_hi, lds.meet_at, x.by_rows ? 1 : 0);
     return hipGetLastError();
 }
 

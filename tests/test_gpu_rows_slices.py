@@ -11,6 +11,12 @@ from test_gpu_rows_head import FP32_TOL
 pytestmark = pytest.mark.gpu
 
 
+def how(K, V, rows):
+    """Groups of 128 columns per block (one round of 256 blocks), what is left of eight wavefronts splits the contraction's steps of 32."""
+    n = min(8 // -(-(-(-V // 128)) // 256), -(-K // 32))
+    return {1: "one", 2: "halves"}.get(n, "at_once" if rows <= (16 if n > 4 else 8) else "in_turn")
+
+
 # contraction steps of 32: 2, 3, 5, 9 (a slice of eight stays empty), 16; V: blocks of 1, 2, 3 and 6 groups of 128 columns (8, 4, 2 and 1 slices)
 @pytest.mark.parametrize("r", [40, 72, 136, 264, 512])
 @pytest.mark.parametrize("V,rows", [(1000, (5, 8, 9, 16, 17, 33)), (8200, (7,)), (33000, (5, 8, 9, 40)), (66000, (5, 18, 48)), (165000, (6,))])
@@ -18,7 +24,7 @@ def test_low_rank(gpu, oracle_mod, r, V, rows):
     torch, b = gpu
     d, k = 96, 7
     for n in rows:
-        assert_plan("low", n, d, r, V, k, kernel="rows")
+        assert_plan("low", n, d, r, V, k, kernel="rows", slices_meet=how(r, V, n))
         print(f"slices meet: rows={n} r={r} V={V}", flush=True)
         x = synth.make_inputs(synth.small_config(n, d, r, V, k, peaked_every=4), seed=n + r)
         ids, lp = b.slimspec_head_topk(to_dev_bf16(x.h), to_dev_bf16(x.A), to_dev_bf16(x.B), k)
@@ -32,6 +38,7 @@ def test_low_rank(gpu, oracle_mod, r, V, rows):
 def test_full_head(gpu, oracle_mod, rows, d, V):
     torch, b = gpu
     k = 11
+    assert_plan("full", rows, d, 8, V, k, kernel="rows", slices_meet=how(d, V, rows))
     print(f"slices meet, full head: rows={rows} d={d} V={V}", flush=True)
     x = synth.make_inputs(synth.small_config(rows, d, 8, V, k, peaked_every=4), seed=rows + d, with_full_head=True)
     ids, lp = b.full_head_topk(to_dev_bf16(x.h), to_dev_bf16(x.W), k)
