@@ -44,7 +44,7 @@ __global__ __launch_bounds__(256) void widen_rows_kernel(
 // What bounds it: the weights' way from HBM, as long as every CU has a block and asks for enough of them (plan.hpp chooses
 // the chunks for that); with small weights the chain of trips before and after: the contraction input (for one or two
 // rows as a rule one trip: all of a thread's loads are requested together, and the first weights right behind them), the weights, the
-// epilogue of one wavefront.
+// epilogue of one wavefront (a single row in a wide chunk: of the block).
 //
 // Measured, one row (kernel; chunks of 512 columns and x as it comes, before, in brackets): full head, d = 7984, V = 37208 96 us
 // (180), d = 3208, V = 33184 38 (70); r = 1568, V = 40248 25.2 (44); r = 72, V = 103472 7.2 (10.5); d = 4096, V = 128256, where

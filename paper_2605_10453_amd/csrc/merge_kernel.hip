@@ -7,22 +7,25 @@
 // What bounds it: the length of its chain of instructions.  There is hardly any work and one trip to memory (0.4 us; a second pass over the same lists
 // took 3.6 us of the first one's 3.9), but a lone wavefront takes 8 to 28 cycles per dependent instruction (device_utils.hpp).
 //
-// Lists of up to 16 ids (10 in a launch of more than 24 rows of few lists) whose entries a block's threads can hold (SHORT, the usual call; plan.hpp: merge_short_lists): every thread keeps up to eight entries and one chunk's (m, s).
+// Lists of up to 16 ids (10 in a launch of more than 24 rows of few lists) whose entries a block's threads can hold (SHORT, the usual call; plan.hpp:
+// merge_short_lists): every thread keeps up to eight entries and one chunk's (m, s).
 //   (1) T: the smallest of the maxima of k groups of entries (device_utils.hpp), so k entries reach it; two or three times as many do, where a sort
 //       would leave hardly more than k, but they are ranked by all threads and the sort is a chain of 21 exchanges.  M = max m_c in the same steps.
 //   (2) every wavefront puts its entries that reach T into a list of its own in shared memory (an addition to a common counter takes 174 cycles), and
 //       the terms of the log-sum-exp are added, one per thread.
 //   (3) the k first are found by counting.
 // Two barriers.  Measured with one wavefront for all of this / now: one row, d = 4096, r = 512, V = 128256 33.9 / 32.7 us a call, with draws at V = 151936
-// 45.7 / 45.4, 23 rows 42.4 / 41.2, the full head at d = 624, V = 23344, k = 1 12.7 / 11.3, 3 rows, r = 496, V = 19072, k = 29 (general code) 24.9 / 24.8.
+// 45.7 / 45.4, 23 rows 42.4 / 41.2, the full head at d = 624, V = 23344, k = 1 12.7 / 11.3.  Rows with more entries at the bound than the lists hold, or with
+// a logit that is no finite number, go on with what follows.
 //
-// Other calls: one wavefront does everything that is a chain, without barriers, and the others only fetch lists:
+// Other calls (an instance of their own): one wavefront does everything that is a chain, without barriers, and the others only fetch lists:
 //   (1) wavefront 0 reads the chunk maxima (the lists' heads), up to 8 per lane in flight.
 //       T = the k-th largest of its 64 lanes' maxima: k heads reach it, so it bounds the answer from below.  (All-pairs
 //       counting of 251 heads by 1024 threads took longer than the loads: 6.6 us a launch, 13.5 with 500 chunks and a draw.)
 //       With fewer lists than k no head bounds anything: there T is the m-th largest of the lists' j-th entries, m j >= k.  (Every entry of 32 lists
 //       of 64, as T = 0 admits them, is 40 us of (3): one row, r = 16, V = 2048, k = 64 55 us a call, 14 with this T.)
-//       Wavefront 1 meanwhile finds the draw of a sampling call, wavefront 2 folds the log-sum-exp.
+//       Wavefront 1 meanwhile finds the draw of a sampling call, wavefront 2 folds the log-sum-exp (by wavefront 0, before the bound / by wavefront 2:
+//       4 rows, d = 1024, r = 128, V = 8192, k = 40 14.6 / 14.3 us a call, 16 rows, V = 128256, k = 32 22.5 / 22.1, one row, d = 2048, r = 256, k = 40 24.0 / 23.7).
 //   (2) all threads: the lists' entries that reach T go to shared memory.  Where a row has few entries they were
 //       requested at the start, before T is known (one trip instead of two); otherwise the first eight of the lists whose
 //       heads reach T are read, and more of a list only where all eight are taken.

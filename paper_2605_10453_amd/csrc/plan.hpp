@@ -470,7 +470,9 @@ inline RowsLds rows_lds(int rows, int K, const RowsGeom &g, int k, bool sum) {
 // positions, r = 200, V = 60000 18.7 / 17.9 (16 MB 18.4).  The slices of up to 8 rows, 8 MB: d = 4096, r = 256, V = 128256 25.0 / 24.4 (4 MB 25.1); 4 rows
 // of the router 51.5 / 50.3.  The kernel that adds the slices, 4 MB: 12 rows, d = 4096, r = 512, V = 60000 28.4 / 27.2, 30 rows, d = 3000, r = 400, V = 20000 28.1 / 27.6, 23 rows
 // 41.1 / 40.8, 40 rows, k = 32 52.1 / 51.7; not the tile kernel before it, which its loads delay: 40 rows, d = 6000, r = 1000, V = 100000 69.7 / 70.2, and 69.4
-// with the former alone.  Nor the down-projection of one row, whose blocks fill the CUs: 32.2 / 32.1, 45.7 / 45.6.)
+// with the former alone.  Nor the down-projection of one row, whose blocks fill the CUs: 32.2 / 32.1, 45.7 / 45.6.  Over 84 calls of 9 to 48 rows with the kernel that
+// adds the slices 0.996 of the time.  With more than one round of blocks, V = 200000 to 1000000, what the later rounds' blocks find is less, and nothing is lost:
+// 5 rows, d = 512, r = 64 0.93 (V = 262144) to 0.99, 7 rows, d = 1024, r = 256 0.98 to 1.00, 12 and 40 rows, d = 4096, r = 512 0.996 to 1.007, noise.)
 constexpr int kAheadDownRows = 9 << 20, kAheadSlices = 8 << 20, kAheadFinish = 4 << 20;
 inline ReadAhead rows_read_ahead(const uint16_t *M, int K, int V, const RowsGeom &g, int bytes, int nw) {
     ReadAhead a;

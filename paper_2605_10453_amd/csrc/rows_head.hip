@@ -23,7 +23,7 @@
 //
 // Measured at d = 4096, r = 512, V = 128256 (kernel alone; 131 MB of weights are 22-26 us at a plain read's rate; one row per
 // wavefront and step, in brackets): 23 rows, k = 10 27.8 us (33.0), 40 rows, k = 32 37.6 (42.9), 4 rows, k = 64 29.7 (31.3); 27 rows with
-// draws, r = 456, V = 31664 17.5 (22.4).  Calls: 40 rows with k = 32 52.4 us, 23 rows 42.6.  Error of the
+// draws, r = 456, V = 31664 17.5 (22.4).  Calls: 40 rows with k = 32 51.2 to 52.6 us by the machine, 23 rows 41.0 to 41.4.  Error of the
 // log-probabilities against 64-bit arithmetic: 7.7e-8 relative, 1.0e-7 with one multiply-add per weight (40 rows, k = 32).
 #include "gemv_parts.hpp"
 #include "launch.hpp"
@@ -279,7 +279,7 @@ __global__ __launch_bounds__(512) void rows_topk_kernel(
     // and barriers behind the last weights, most wavefronts idle.  So few rows are added at once, by all threads, where a slice has a place
     // of its own (plan.hpp: rows_meet_at_once), and two slices finish half of the elements each.  One after the other / now, us a call: full
     // head, 4 rows, d = 1024, V = 32000 21.3 / 19.7, 7 rows, d = 4096, V = 20000 43.0 / 42.1; d = 4096, r = 512: 8 rows, V = 32768 23.3 / 22.4,
-    // 16 rows 23.4 / 22.6; two slices: 40 rows, k = 32, V = 128256 53.0 / 52.7, 32 rows, V = 90000 39.7 / 39.3.
+    // 16 rows 23.4 / 22.6; two slices, V = 66000 to 128256, 120 calls: 33 rows 0.993 of the time, 48 rows 0.991, up to 32 rows level (0.97 to 1.02), with draws the same.
     const auto place = [&](int nt, int i) { return z_lds + (16 * nt + c16) * row_stride + cg * 128 + 8 * (4 * kg + i); };
     const auto put_sums = [&](float *at, int stride) {
 #pragma unroll
