@@ -149,8 +149,7 @@ static hipError_t launch_down_rows_nt(const uint16_t *h, const uint16_t *A, void
 
 hipError_t launch_down_rows(const uint16_t *h, const uint16_t *A, void *X, int rows_pad, int d, int r, const DownGrid &g, const ReadAhead &ahead, hipStream_t st)
 {
-    int most = 0;
-    for (int q = 0; q < g.n_groups; ++q) most = g.g_row0[q + 1] - g.g_row0[q] > most ? g.g_row0[q + 1] - g.g_row0[q] : most;
+    const int most = largest_group(g);
     if (most <= 16) return launch_down_rows_nt<1>(h, A, X, rows_pad, d, r, g, ahead, st);
     if (most <= 32) return launch_down_rows_nt<2>(h, A, X, rows_pad, d, r, g, ahead, st);
     return launch_down_rows_nt<3>(h, A, X, rows_pad, d, r, g, ahead, st);

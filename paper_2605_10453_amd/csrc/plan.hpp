@@ -123,7 +123,9 @@ inline bool own_input_takes(const ChunkGeom &g, int rows, int d, int r, int V, b
 // ---- reading weights ahead (read_ahead.hpp) ------------------------------------------------------------------------
 // The launches that make t for rows_topk_kernel leave the memory idle.  Further blocks of them read the weights that its blocks ask for
 // first into the L2 (4 MB) of the XCD that will ask: a launch's blocks are dealt to the XCDs in turn, always from the first one on, and
-// a line stays there from one launch to the next.
+// a line stays there from one launch to the next.  (Nothing / read into the next XCD's L2 / into the right one, us a call: 5 rows, d = 1024, r = 128, V = 128256
+// 17.6 / 17.5 / 16.5, 7 rows, r = 256, V = 30000 15.9 / 15.5 / 14.3, 12 rows, d = 4096, r = 512, V = 60000 27.7 / 28.7 / 27.3.  Counters do not show it: a run that
+// collects them empties the caches between launches.)
 constexpr int kAheadLoads = 12;          // of a wavefront, a kilobyte each (16: a CU with such a block takes longer than the others; 8: more blocks)
 struct ReadAhead {
     const uint16_t *M = nullptr;         // [K, V]
@@ -501,10 +503,21 @@ inline ReadAhead rows_read_ahead(const uint16_t *M, int K, int V, const RowsGeom
 // from 1 KB per row of A on they come from few of the L2's channels.  Calls at V = 32768 (one / two launches, us; rows of the largest
 // group with one matrix): d = 1024, r = 128 5 rows 14.8 / 18.2, 23 rows 19.7 / 21.2, 40 rows 24.0 / 25.0; d = 2048, r = 256 5 rows 20.8 / 21.9, 16 rows
 // 22.3 / 22.5, 23 rows 26.1 / 25.6, 12 rows in four groups 21.1 / 23.5; d = 4096, r = 512, V = 128256 5 rows 50.6 / 42.0.
-inline bool down_rows_takes(const DownGrid &g, int d, int r) {
+inline int largest_group(const DownGrid &g) {
     int most = 0;
     for (int q = 0; q < g.n_groups; ++q) most = g.g_row0[q + 1] - g.g_row0[q] > most ? g.g_row0[q + 1] - g.g_row0[q] : most;
-    return r <= 256 && (d <= 1024 || (d <= 2048 && most <= 16));
+    return most;
+}
+inline bool down_rows_takes(const DownGrid &g, int d, int r) { return r <= 256 && (d <= 1024 || (d <= 2048 && largest_group(g) <= 16)); }
+// Does that one launch read weights ahead?  It takes longer for it, the less it has to do itself (512 elements of d are one step of its wavefronts) and the
+// longer the weights' way is: what is gained must be more.  (Nothing / 9 MB, us a call, the weights in the last-level cache and, in brackets, 600 MB of copies in
+// turn: 8 rows, d = 256, r = 128, V = 30000 5 % (8) slower, d = 512 5 % (5), d = 768 2 % (3), d = 1024 1 % (0) faster; d = 512, r = 64, V = 65536 1 % (3)
+// slower, r = 128, V = 60000 4 % faster (4 slower), d = 1024 7 % (2) faster; d = 384, r = 128, V = 128256 2 % faster (5 slower), d = 256 1 % faster (6 slower); 40 rows, d = 512,
+// r = 64, V = 65536 1 % (1) faster, d = 384, r = 128, V = 60000 6 % faster (level).  Over 312 such calls 1.5 % (0.2) faster with these lines; without them 1.3 % faster
+// (1.4 slower), 44 (141) of them by more than 1.5 % slower, up to 5 % (10), now none (30, up to 5 %).)
+inline bool down_rows_reads_ahead(const DownGrid &g, int d, int r, int V) {
+    const int64_t weights = (int64_t)r * V;
+    return largest_group(g) > 16 ? d >= 512 || (d > 256 && weights >= 7000000) : d > 384 && d * weights >= 3500000000;
 }
 
 // Up to 8 rows: down_tile_kernel leaves 8 slices of t row by row (or fewer, where the contraction has no more), which every block of

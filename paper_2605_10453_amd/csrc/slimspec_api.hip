@@ -231,7 +231,8 @@ int run_head_rows(HeadKind kind, const void *h, const void *A, const void *M, co
                 e = launch_down_projection_slices(hrow, static_cast<const uint16_t *>(A), slices, p.down, d, r, ahead(kAheadSlices, 4), s);
                 in.slices = slices; in.nds = n;
             } else if (down_rows_takes(p.down, d, r))
-                e = launch_down_rows(hrow, static_cast<const uint16_t *>(A), X, p.rows_pad, d, r, p.down, ahead(kAheadDownRows, 16), s);
+                e = launch_down_rows(hrow, static_cast<const uint16_t *>(A), X, p.rows_pad, d, r, p.down,
+                                     down_rows_reads_ahead(p.down, d, r, V) ? ahead(kAheadDownRows, 16) : ReadAhead(), s);
             else
                 e = launch_down_projection_pieces(hrow, static_cast<const uint16_t *>(A), reinterpret_cast<float *>(ws + p.off_down_part),
                                                   p.down, p.rows_pad, d, r, X, ahead(kAheadFinish, 4), s);

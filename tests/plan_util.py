@@ -25,7 +25,7 @@ def plan_of(kind: str, rows: int, d: int, r: int, V: int, k: int, fp32=False, pr
     parked_row_bytes (where in the workspace a row does, its number of columns first); resident_fits; for stream, chunk_cols,
     rows_in_lds (whether a launch's row input fits shared memory), own_input (the kernel makes t itself) and block_tail (all
     wavefronts of a block finish its only row);
-    for rows, slices_meet (how the sums of the slices of the contraction meet: one, at_once, halves or in_turn), sum_slices (slices of t that its blocks add, 0: none) and rows_as_they_lie (the full head's rows are read without a launch that regroups them); for stream and rows, merge (how merge_kernel takes the chunks' lists: short,
+    for rows, reads_ahead (MB of the weights that the launches which make t read ahead, at most), slices_meet (how the sums of the slices of the contraction meet: one, at_once, halves or in_turn), sum_slices (slices of t that its blocks add, 0: none) and rows_as_they_lie (the full head's rows are read without a launch that regroups them); for stream and rows, merge (how merge_kernel takes the chunks' lists: short,
     long_ahead or long)."""
     line = f"{kind} {rows} {d} {r} {V} {k} {int(fp32)} {int(prepared)} {int(sampling)}\n"
     out = subprocess.run([_probe()], input=line, capture_output=True, text=True, check=True).stdout
